@@ -291,6 +291,7 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     ctx->horizon_bytes = 0;
     ctx->hz_n = ctx->hz_len = ctx->hz_o_bound = 0;
     ctx->hz_M = 0;
+    ctx->pad_outputs = 0;
     ctx->timing = 0;
     ctx->timed = 0;
     ctx->resume_rows = 0;
@@ -382,6 +383,13 @@ int kvsched_set_o_max(kvsched_ctx *ctx, int32_t o_max_bound)
     if (!ctx || o_max_bound < 0) return KVSCHED_EINVAL;
     if (o_max_bound > KVSCHED_MAX_O) return KVSCHED_ERANGE;
     ctx->o_max_bound = o_max_bound;
+    return KVSCHED_OK;
+}
+
+int kvsched_set_pad_outputs(kvsched_ctx *ctx, int on)
+{
+    if (!ctx) return KVSCHED_EINVAL;
+    ctx->pad_outputs = on ? 1 : 0;
     return KVSCHED_OK;
 }
 
@@ -608,9 +616,11 @@ static int run_sortedF(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int3
     hipStream_t st = (hipStream_t)stream;
     rc = ensure_scratch(ctx, kvs_sortedF_scratch_bytes(n));
     if (rc != KVSCHED_OK) return rc;
-    rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
-    if (rc != KVSCHED_OK) return rc;
-    return kvs_launch_sortedF(n, s, o, (int32_t)M, ga, gb, tie_rule, feas_mode, order_out, batch_end_out, F_out,
+    if (n > kvs_sortedF_small_max(feas_mode)) {
+        rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
+        if (rc != KVSCHED_OK) return rc;
+    }
+    return kvs_launch_sortedF(n, s, o, (int32_t)M, ga, gb, tie_rule, feas_mode, ctx->pad_outputs, order_out, batch_end_out, F_out,
                               num_batches_out, ctx->d_scratch, ctx->d_words, st);
 }
 

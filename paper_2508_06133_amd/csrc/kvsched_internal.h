@@ -30,6 +30,7 @@ struct kvsched_ctx {
     void *static_scratch;  // this device's address of the library's fixed working array (never freed)
     void *d_tables;        // exact DP: tables and records, grows on demand
     size_t tables_bytes;
+    int pad_outputs;       // Phase-1 calls write zeros behind the last batch
     int timing;            // record events around the timeline kernel
     int timed;             // a pair of events has been recorded
     int32_t resume_rows;   // rows of the last kvsched_simulate call if it resumed rows from snapshots, else 0
@@ -169,10 +170,11 @@ int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t
                           int32_t *batch_end_out, double *F_out, int32_t *swaps_out, int32_t *num_batches_out,
                           void *scratch, int32_t *d_words, hipStream_t st);
 
-// sortedf.hip
+// sortedf.hip (up to kvs_sortedF_small_max requests the launch replaces the length scan; pad: zeros behind the last batch)
+int32_t kvs_sortedF_small_max(int32_t feas_mode);
 size_t kvs_sortedF_scratch_bytes(int32_t n);
 int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                       int32_t tie_rule, int32_t feas_mode,
+                       int32_t tie_rule, int32_t feas_mode, int32_t pad,
                        int32_t *order_out, int32_t *batch_end_out, double *F_out, int32_t *num_batches_out,
                        void *scratch, int32_t *d_words, hipStream_t st);
 

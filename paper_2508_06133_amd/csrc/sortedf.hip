@@ -5,577 +5,1025 @@
 // effective length ga s_i + gb o_i replaces o_i in the metric's numerator, nowhere else.
 //
 // Since every batch is a prefix of what remains, the remaining requests stay sorted: one key
-// sort serves all batches, and batch b is the segment [a_b, a_b + k*) of the sorted array.
-// One workgroup does the whole construction:
-//   1. stable LSD radix sort of the ids by o            -> requests in (o, id) order
-//   2. continue the same sort on s+o                    -> requests in (s+o, o, id) order
-//   3. prefix sums W (of s+o) and S (of o) over that order
-//   4. per batch: feasible extent K by a two-level search on W (sum of peaks <= M), extended by a
-//      bisection on the simultaneous-start memory profile when that is the feasibility asked for;
-//      argmin over k <= K of S_k / k^2 compared in exact 128-bit integers, tie rule applied;
-//      F reported as one fp64 division
-//   5. stable sort of the (o, id)-ordered ids by batch number -> each batch in nondecreasing o
-// The working arrays and a copy of the lengths (56 bytes per request) live in LDS when they fit
-// beside the sort's tables (n up to about 2200), else in the caller's scratch buffer in HBM: the construction is a chain of short
-// dependent steps by one workgroup, so its time is the latency of those arrays; in particular a
-// barrier waits until every store before it has been acknowledged, which for HBM takes microseconds.
+// sort serves all batches, and batch b is the segment [a_b, a_b + k*) of the sorted array:
+//   1. sort 64-bit keys (s+o, o, id); keys that do not fit in 64 bits (budgets beyond some 2^22 with
+//      many requests: the host decides from M and n) are replaced by (s+o, rank in the (o, id) order)
+//   2. prefix sums W (of s+o), S (of o) and G (of the effective lengths) over that order
+//   3. per batch: the feasible extent K (sum of peaks <= M; or the simultaneous-start memory profile),
+//      then the argmin over k <= K of G_k / k^2 compared in exact integers, tie rule applied
+//   4. sort (batch, o, id): each batch in nondecreasing o; the metric as one fp64 division
+// Up to 4096 requests (2048 under the profile constraint) one workgroup does everything in LDS and
+// registers; beyond that the sorts and scans are launches over the whole chip and only step 3, a chain
+// by nature, is one workgroup's.
 #include "phase1_util.h"
+#include "sort_util.h"
 
 namespace {
 
-constexpr int TPB = 1024;
-constexpr int NWAVES = TPB / 64;
+constexpr int kRun = 2048;          // keys one workgroup sorts (1024 threads, two each)
+constexpr int kFan = 8;             // runs merged by one pass
+constexpr int kNextMax = 256;       // batches among the first so many requests are found by one wavefront
+constexpr int kSmallBuckets = 2048; // completion-time buckets of the profile test in LDS
+constexpr int kLargeBuckets = 4096;
 
-struct Lds {
-    RadixLds<TPB> radix;
-    int hist[2];
-    long long scan_a[NWAVES];
-    long long scan_b[NWAVES];
-    long long carry_a, carry_b;
-    long long red_S[NWAVES];
-    int red_k[NWAVES];
-    long long best_S;
-    int best_k;
-    int flag;
-    int fit[2];
+struct SortedArgs {
+    int32_t n;
+    const int32_t *s, *o;
+    int32_t M, ga, gb, tie_rule;
+    int32_t *order_out, *batch_end_out;
+    double *F_out;
+    int32_t *num_batches_out;
+    int32_t *words;
+    int32_t id_bits, o_bits;  // key fields: (s+o) above o_bits bits of o above id_bits bits of the id
+    int32_t packed;           // 0: the keys would not fit, (s+o, rank by (o, id)) instead
+    int32_t pad;              // zeros behind the last batch in batch_end_out / F_out
+};
+
+// Arrays by sorted position (LDS or scratch), shared by both variants.
+struct Sums {
+    const u64 *W, *S, *G;  // [n + 1]
+    const int *s, *o;      // [n] (profile constraint only)
 };
 
 // sign of Sa/ka^2 - Sb/kb^2 in exact integers (Sa, Sb < 2^63; ka, kb < 2^31)
-__device__ __forceinline__ int cmp_F(long long Sa, int ka, long long Sb, int kb)
+__device__ __forceinline__ int cmp_F(u64 Sa, int ka, u64 Sb, int kb)
 {
-    const unsigned long long qa = (unsigned long long)ka * (unsigned long long)ka;
-    const unsigned long long qb = (unsigned long long)kb * (unsigned long long)kb;
-    const unsigned long long l_hi = __umul64hi((unsigned long long)Sa, qb), l_lo = (unsigned long long)Sa * qb;
-    const unsigned long long r_hi = __umul64hi((unsigned long long)Sb, qa), r_lo = (unsigned long long)Sb * qa;
+    const u64 qa = (u64)ka * (u64)ka;
+    const u64 qb = (u64)kb * (u64)kb;
+    const u64 l_hi = __umul64hi(Sa, qb), l_lo = Sa * qb;
+    const u64 r_hi = __umul64hi(Sb, qa), r_lo = Sb * qa;
     if (l_hi != r_hi) return l_hi < r_hi ? -1 : 1;
     if (l_lo != r_lo) return l_lo < r_lo ? -1 : 1;
     return 0;
 }
 
-// is prefix (Sa, ka) a better batch than (Sb, kb)?  kb == 0 means "none yet".
-__device__ __forceinline__ bool better(long long Sa, int ka, long long Sb, int kb, int tie_rule)
+// is prefix (Sa, ka) a better batch than (Sb, kb)?  k == 0 means "none".  SMALL: every S < 2^32 and
+// every k < 2^16, so both cross products fit in 64 bits.
+template <bool SMALL>
+__device__ __forceinline__ bool better(u64 Sa, int ka, u64 Sb, int kb, int tie_rule)
 {
-    if (ka == 0) return false;
-    if (kb == 0) return true;
-    const int c = cmp_F(Sa, ka, Sb, kb);
-    if (c != 0) return c < 0;
-    return tie_rule == KVSCHED_TIE_LARGER ? ka > kb : ka < kb;
-}
-
-// The same question when every S < 2^32 and every k < 2^16: both cross products fit in 64 bits.
-__device__ __forceinline__ bool better_small(unsigned Sa, int ka, unsigned Sb, int kb, int tie_rule)
-{
-    const unsigned long long l = (unsigned long long)Sa * (unsigned)(kb * kb);
-    const unsigned long long r = (unsigned long long)Sb * (unsigned)(ka * ka);
-    const bool wins = l != r ? l < r : (tie_rule == KVSCHED_TIE_LARGER ? ka > kb : ka < kb);
-    return ka != 0 && (kb == 0 || wins);
-}
-
-template <int CTRL>
-__device__ __forceinline__ void take_better_small(unsigned &bS, int &bk, int tie_rule)
-{
-    const unsigned oS = (unsigned)__builtin_amdgcn_update_dpp((int)bS, (int)bS, CTRL, 0xf, 0xf, false);
-    const int ok = __builtin_amdgcn_update_dpp(bk, bk, CTRL, 0xf, 0xf, false);
-    if (better_small(oS, ok, bS, bk, tie_rule)) { bS = oS; bk = ok; }
-}
-
-// Best (S, k) of a 16-lane row into all its lanes: lane exchanges 1, 2 apart, then the two
-// mirrorings (quads, halves).  "Better" is a strict total order on distinct k, so any tree works.
-__device__ __forceinline__ void row_best_small(unsigned &bS, int &bk, int tie_rule)
-{
-    take_better_small<0xB1>(bS, bk, tie_rule);   // quad_perm [1,0,3,2]
-    take_better_small<0x4E>(bS, bk, tie_rule);   // quad_perm [2,3,0,1]
-    take_better_small<0x141>(bS, bk, tie_rule);  // row_half_mirror
-    take_better_small<0x140>(bS, bk, tie_rule);  // row_mirror
-}
-
-// Largest k in [0, rem] with g(k) <= M, for g increasing in k (k = 1..rem).  Every thread
-// receives it.  While a thread's share of the probes is short (rem <= 4 TPB) each thread counts
-// the fitting probes of its own run of consecutive k and the one thread whose run holds the
-// boundary publishes the answer: one barrier.  `slot` alternates between back-to-back calls.
-template <class G>
-__device__ int count_fitting(int rem, G g, int32_t M, Lds &L, int slot)
-{
-    const int tid = threadIdx.x;
-    const int stride = (rem + TPB - 1) / TPB;
-    if (stride <= 4) {
-        const int k0 = tid * stride;  // this thread probes k0+1 .. k0+stride, and k0+stride+1 to see the boundary
-        bool fit[5];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int k = k0 + 1 + j;
-            fit[j] = j <= stride && k <= rem && g((long long)k) <= (long long)M;
-        }
-        int c = 0;
-        bool beyond = false;  // does the first probe after this thread's run fit?
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            if (j < stride) c += fit[j] ? 1 : 0;
-            if (j == stride) beyond = fit[j];
-        }
-        // a prefix of all probes fits: the boundary lies in the run that fits at least partly and
-        // is not followed by a fitting probe; if nothing fits at all, thread 0 reports 0
-        if ((c > 0 && !beyond) || (tid == 0 && c == 0)) L.fit[slot] = k0 + c;
-        __syncthreads();
-        return L.fit[slot];
+    if constexpr (SMALL) {
+        const u64 l = (u64)(unsigned)Sa * ((unsigned)kb * (unsigned)kb);
+        const u64 r = (u64)(unsigned)Sb * ((unsigned)ka * (unsigned)ka);
+        const bool wins = l != r ? l < r : (tie_rule == KVSCHED_TIE_LARGER ? ka > kb : ka < kb);
+        return ka != 0 && (kb == 0 || wins);
+    } else {
+        if (ka == 0) return false;
+        if (kb == 0) return true;
+        const int c = cmp_F(Sa, ka, Sb, kb);
+        if (c != 0) return c < 0;
+        return tie_rule == KVSCHED_TIE_LARGER ? ka > kb : ka < kb;
     }
-    const long long k1 = (long long)(tid + 1) * stride;  // coarse probes, a prefix of them fits
-    const bool ok1 = k1 <= rem && g(k1) <= (long long)M;
-    int K = __syncthreads_count(ok1) * stride;
-    const long long k2 = (long long)K + tid + 1;  // fine probes inside the next stride
-    const bool ok2 = tid < stride && k2 <= rem && g(k2) <= (long long)M;
-    K += __syncthreads_count(ok2);
+}
+
+// The best (S, k) of the 64 lanes' own, k in every lane (0: no lane has one); S of it in bS.  A float quotient
+// (good to a few 1e-7) leaves nearly always one lane; only lanes within 4e-6 of the least are compared exactly.
+template <bool SMALL>
+__device__ __forceinline__ int wave_best(u64 &bS, int bk, int tie_rule)
+{
+    const float kf = (float)bk;
+    const float f = bk > 0 ? (SMALL ? (float)(unsigned)bS : (float)bS) * __builtin_amdgcn_rcpf(kf * kf) : 3.0e38f;
+    const float least = __uint_as_float(wave_min_u32(__float_as_uint(f)));
+    u64 near = __builtin_amdgcn_ballot_w64(bk > 0 && f <= least * 1.000004f);
+    if (near == 0) return 0;
+    int at = __ffsll((long long)near) - 1;
+    u64 S = lane_value_u64(bS, at);
+    int k = __builtin_amdgcn_readlane(bk, at);
+    near &= near - 1;
+    while (near != 0) {
+        at = __ffsll((long long)near) - 1;
+        near &= near - 1;
+        const u64 So = lane_value_u64(bS, at);
+        const int ko = __builtin_amdgcn_readlane(bk, at);
+        if (better<SMALL>(So, ko, S, k, tie_rule)) S = So, k = ko;
+    }
+    bS = S;
+    return k;
+}
+
+// One wavefront: size of the batch that starts at place a (0: none; -1: undecided, only with `limited`, when
+// its extent passes kNextMax).  Feasible are the k <= rem with W_k - W_0 <= M.  256 sizes a turn, their sums read together.
+template <bool SMALL>
+__device__ __forceinline__ int wave_batch(const Sums &c, int a, int rem, u64 M, int tie_rule, bool limited)
+{
+    const int lane = threadIdx.x & 63;
+    const u64 W0 = c.W[a], G0 = c.G[a];
+    u64 bS = 0;
+    int bk = 0;
+    for (int base = 0; base < rem; base += 256) {
+        u64 w[4], g[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = min(base + 64 * q + lane + 1, rem);
+            w[q] = c.W[a + k];
+            g[q] = c.G[a + k];
+        }
+        bool ok = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = base + 64 * q + lane + 1;
+            ok = k <= rem && w[q] - W0 <= M;
+            if (ok && better<SMALL>(g[q] - G0, k, bS, bk, tie_rule)) bS = g[q] - G0, bk = k;
+        }
+        if (__builtin_amdgcn_ballot_w64(ok) != ~0ull) break;  // (feasibility is monotone: the end lies in these 256)
+        if (limited && base + 256 < rem) return -1;
+    }
+    return wave_best<SMALL>(bS, bk, tie_rule);
+}
+
+// One wavefront: the longest feasible prefix at place a under the simultaneous-start profile, if it is shorter than
+// kNextMax (or rem is); else -1.  Lane l of row q stands for the completion time o of place a + 64 q + l and sums the
+// memory held then, sum over {i: o_i >= o} of (s_i + o) (Section 4), as the requests join one by one; the first that
+// takes a sum above M ends the prefix.  (Times of requests that have not joined impose nothing the joined ones do
+// not: the memory rises from there to the next completion.)
+__device__ __forceinline__ int wave_profile_extent(const Sums &c, int a, int rem, unsigned M)
+{
+    const int lane = threadIdx.x & 63;
+    const u64 P0 = c.W[a] - c.S[a];
+    unsigned acc[4];
+    int sv[4], ov[4];
+    int hi = 0;  // beyond: even the memory at the earliest completion, at least sum (s_i + 1), is too much
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int k = 64 * q + lane + 1;
+        const int kk = min(k, rem);
+        const bool ok = k <= rem && c.W[a + kk] - c.S[a + kk] - P0 + (u64)k <= (u64)M;
+        sv[q] = c.s[a + kk - 1];
+        ov[q] = k <= rem ? c.o[a + kk - 1] : 0x7fffffff;
+        acc[q] = 0;
+        hi += __popcll(__builtin_amdgcn_ballot_w64(ok));
+    }
+    int K = -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = min(64, hi - 64 * q);
+        for (int l = 0; l < m; ++l) {
+            const int si = __builtin_amdgcn_readlane(sv[q], l);
+            const int oi = __builtin_amdgcn_readlane(ov[q], l);
+            unsigned most = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[r] += oi >= ov[r] ? (unsigned)si + (unsigned)ov[r] : 0u;
+                most = max(most, acc[r]);
+            }
+            if (__builtin_amdgcn_ballot_w64(most > M) != 0) {
+                K = 64 * q + l;
+                break;
+            }
+        }
+        if (K >= 0) break;
+    }
+    if (K >= 0) return K;
+    return hi < kNextMax || rem <= kNextMax ? hi : -1;
+}
+
+// Largest k in [0, rem] with g(k) <= M, for g increasing in k: coarse probes, then fine ones.  Every thread
+// of a workgroup of 1024 receives it.
+template <class G>
+__device__ __forceinline__ int count_fitting(int rem, G g, u64 M)
+{
+    int K = 0, span = rem;  // g(K) fits; the answer lies in [K, K + span]
+    while (span > 0) {
+        const int step = (span + 1023) / 1024;
+        const int k = (int)(threadIdx.x + 1) * step;
+        const bool ok = k <= span && g(K + k) <= M;
+        const int cnt = __syncthreads_count(ok);
+        const int top = K + span;
+        K += cnt * step;
+        span = min(top, K + step - 1) - K;
+        __syncthreads();
+    }
     return K;
 }
 
-// Do the k requests at places [a, a + k) of the (s+o, o, id) order, started together, stay within
-// M at every completion time?  Memory at time o_j = sum over {i: o_i >= o_j} of (s_i + o_j)
-// (Section 4).  The ids are visited in decreasing o through a list in ascending o that holds every
-// member (all requests in (o, id) order, or the candidates of the batch sorted by o); running sums
-// of s and of the count over the members seen so far give the memory at each member's completion
-// (among equal o the last one visited sees the whole group, the earlier ones a part of it, which
-// cannot exceed it).  Every thread receives the answer.
-__device__ bool profile_fits(int n, int a, int k, const int32_t *s, const int32_t *o, const int *by_o,
-                             const int *pos_w, int32_t M, Lds &L)
+// The profile test for a growing prefix by a whole workgroup of 1024: buckets by completion time (o - 1, or the
+// rank in the (o, id) order when times are too long for that), base = suffix sums (requests that complete at or after
+// the bucket's time, and their prompts) of the prefix accepted so far, delta = those about to join.
+template <bool IN_LDS>  // (one instantiation per address space)
+struct Profile {
+    unsigned *base_c, *base_s, *delta_c, *delta_s;
+    int buckets;
+    const int *rank_of;   // by position; null: buckets are completion times
+    const int *o_of_rank;
+
+    __device__ __forceinline__ unsigned time_of(int b) const { return rank_of ? (unsigned)o_of_rank[b] : (unsigned)b + 1u; }
+
+    __device__ __forceinline__ void clear()
+    {
+        for (int b = threadIdx.x; b < buckets; b += 1024) base_c[b] = base_s[b] = delta_c[b] = delta_s[b] = 0;
+        __syncthreads();
+    }
+
+    // Do the places [from, to) fit beside the accepted ones?  If so they are accepted.
+    __device__ __forceinline__ bool join(const Sums &c, int from, int to, unsigned M, unsigned *wave_c, unsigned *wave_s)
+    {
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+        for (int p = from + tid; p < to; p += 1024) {
+            const int b = rank_of ? rank_of[p] : c.o[p] - 1;
+            atomicAdd(&delta_c[b], 1u);
+            atomicAdd(&delta_s[b], (unsigned)c.s[p]);
+        }
+        __syncthreads();
+        // suffix sums: wavefront 0 takes the latest times, the first lane the latest of all
+        const int rows = (buckets + 1023) >> 10;
+        const int top = buckets - 1 - 64 * rows * wave - lane;
+        unsigned cc = 0, cs = 0;
+        for (int j = 0; j < rows; ++j) {
+            const int b = top - 64 * j;
+            const unsigned vc = wave_scan_u32(b >= 0 ? delta_c[b] : 0u) + cc;
+            const unsigned vs = wave_scan_u32(b >= 0 ? delta_s[b] : 0u) + cs;
+            if (b >= 0) delta_c[b] = vc, delta_s[b] = vs;
+            cc = (unsigned)__builtin_amdgcn_readlane((int)vc, 63);
+            cs = (unsigned)__builtin_amdgcn_readlane((int)vs, 63);
+        }
+        if (lane == 0) wave_c[wave] = cc, wave_s[wave] = cs;
+        __syncthreads();
+        unsigned off_c = 0, off_s = 0;
+        for (int v = 0; v < wave; ++v) off_c += wave_c[v], off_s += wave_s[v];
+        int viol = 0;
+        for (int j = 0; j < rows; ++j) {
+            const int b = top - 64 * j;
+            if (b >= 0) {
+                const unsigned nc = base_c[b] + delta_c[b] + off_c, ns = base_s[b] + delta_s[b] + off_s;
+                viol |= (u64)ns + (u64)nc * time_of(b) > (u64)M;
+            }
+        }
+        const bool fits = __syncthreads_or(viol) == 0;
+        for (int j = 0; j < rows; ++j) {
+            const int b = top - 64 * j;
+            if (b >= 0) {
+                if (fits) base_c[b] += delta_c[b] + off_c, base_s[b] += delta_s[b] + off_s;
+                delta_c[b] = delta_s[b] = 0;
+            }
+        }
+        __syncthreads();
+        return fits;
+    }
+
+    // Longest feasible prefix at place a (clear() before; everything is zero again behind it).
+    __device__ __forceinline__ int extent(const Sums &c, int a, int rem, unsigned M, unsigned *wave_c, unsigned *wave_s)
+    {
+        // the sum of peaks bounds the memory from above, sum (s_i + 1) from below
+        const u64 W0 = c.W[a], P0 = c.W[a] - c.S[a];
+        int lo = count_fitting(rem, [&](int k) { return c.W[a + k] - W0; }, (u64)M);
+        int hi = count_fitting(rem, [&](int k) { return c.W[a + k] - c.S[a + k] - P0 + (u64)k; }, (u64)M);
+        if (lo < hi) {
+            join(c, a, a + lo, M, wave_c, wave_s);
+            int step = max(64, lo >> 2);
+            bool failed = false;
+            while (lo < hi) {
+                const int st = failed ? (hi - lo + 1) >> 1 : min(step, hi - lo);
+                if (join(c, a + lo, a + lo + st, M, wave_c, wave_s)) {
+                    lo += st;
+                    step <<= 1;
+                } else {
+                    hi = lo + st - 1;
+                    failed = true;
+                }
+            }
+            clear();
+        }
+        return lo;
+    }
+};
+
+// argmin over k = 1..K at place a by a workgroup of 1024; every thread receives k*.
+template <bool SMALL>
+__device__ int group_argmin(const Sums &c, int a, int K, int tie_rule, u64 *red_S, int *red_k)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    long long carry_s = 0;
-    int carry_c = 0, viol = 0;
-    for (int tile = 0; tile < n; tile += TPB) {
-        const int idx = n - 1 - (tile + tid);
-        int id = 0, c = 0;
-        long long sv = 0;
-        if (idx >= 0) {
-            id = by_o[idx];
-            const int p = pos_w[id];
-            if (p >= a && p < a + k) { c = 1; sv = s[id]; }
-        }
-        const int member = c;
-        for (int d = 1; d < 64; d <<= 1) {
-            const long long us = __shfl_up(sv, d);
-            const int uc = __shfl_up(c, d);
-            if (lane >= d) { sv += us; c += uc; }
-        }
-        if (lane == 63) { L.scan_a[wave] = sv; L.scan_b[wave] = c; }
-        __syncthreads();
-        long long off_s = carry_s, tot_s = carry_s;
-        long long off_c = carry_c, tot_c = carry_c;
-        for (int v = 0; v < NWAVES; ++v) {
-            const long long xs = L.scan_a[v], xc = L.scan_b[v];
-            if (v < wave) { off_s += xs; off_c += xc; }
-            tot_s += xs;
-            tot_c += xc;
-        }
-        if (member && (sv + off_s) + (c + off_c) * (long long)o[id] > (long long)M) viol = 1;
-        carry_s = tot_s;
-        carry_c = (int)tot_c;
-        __syncthreads();
-        if (carry_c >= k) break;  // uniform: every member has been seen
+    const u64 G0 = c.G[a];
+    u64 bS = 0;
+    int bk = 0;
+    for (int k = tid + 1; k <= K; k += 1024) {
+        const u64 Sk = c.G[a + k] - G0;
+        if (better<SMALL>(Sk, k, bS, bk, tie_rule)) bS = Sk, bk = k;
     }
-    return __syncthreads_or(viol) == 0;
+    bk = wave_best<SMALL>(bS, bk, tie_rule);
+    if (lane == 0) red_S[wave] = bS, red_k[wave] = bk;
+    __syncthreads();
+    bS = red_S[lane & 15];
+    bk = lane < 16 ? red_k[lane & 15] : 0;
+    bk = wave_best<SMALL>(bS, bk, tie_rule);
+    __syncthreads();
+    return bk;
 }
 
-// PROFILE: feas_mode is KVSCHED_FEAS_PROFILE (its code stays out of the other instantiation)
-template <bool IN_LDS, bool PROFILE>
-__global__ __launch_bounds__(TPB) void sortedF_kernel(int32_t n, const int32_t *s_in, const int32_t *o_in, int32_t M,
-                                                      int32_t ga, int32_t gb, int32_t tie_rule, int32_t feas_mode,
-                                                      int32_t *order_out, int32_t *batch_end_out, double *F_out,
-                                                      int32_t *num_batches_out, int *buf0, int *buf1, int *by_o,
-                                                      long long *cumW, long long *cumS, long long *cumG,
-                                                      int *batch_of, int *pos_w, int32_t *words)
+__device__ __forceinline__ u64 field_mask(int bits) { return (1ull << bits) - 1ull; }
+
+// The batch a place belongs to: the first with ends[b] > place.
+__device__ __forceinline__ int batch_of_place(const int *ends, int nb, int place)
 {
-    __shared__ Lds L;
-    extern __shared__ long long lds_arrays[];
-    // In this instantiation every working array below is carved from LDS and nothing else, so that
-    // the accesses compile to LDS instructions (a pointer that may be either costs HBM-like latency).
-    const int32_t *s = s_in, *o = o_in;
-    int *ends = batch_end_out;  // batch ends: collected in LDS and copied out at the end, or written in place
-    int *s_lds = nullptr, *o_lds = nullptr;  // the lengths too: every later read of them is a gather by request id
-    if constexpr (IN_LDS) {
-        const size_t np = ((size_t)n + 64) & ~(size_t)63;
-        const bool alias = cumG == cumS;
-        cumW = lds_arrays;
-        cumS = cumW + np;
-        cumG = alias ? cumS : cumS + np;
-        buf0 = (int *)(lds_arrays + 3 * np);
-        buf1 = buf0 + np;
-        by_o = buf1 + np;
-        batch_of = by_o + np;
-        pos_w = batch_of + np;
-        ends = pos_w + np;
-        s_lds = ends + np;
-        o_lds = s_lds + np;
+    int lo = 0, hi = nb - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ends[mid] > place) hi = mid;
+        else lo = mid + 1;
     }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    return lo;
+}
 
-    // ---- well-formedness and key widths
-    int omax = 0, wmax = 0, bad = 0;
-    for (int i = tid; i < n; i += TPB) {
-        const int sv = s_in[i], ov = o_in[i];
-        if constexpr (IN_LDS) {
-            s_lds[i] = sv;
-            o_lds[i] = ov;
-        }
-        if (sv < 1 || ov < 1 || (long long)sv + ov > (long long)M) bad = 1;
-        omax = max(omax, ov);
-        wmax = max(wmax, (sv < 1 || ov < 1) ? 0 : (int)min((long long)sv + ov, (long long)M));
-    }
-    if (tid == 0) L.flag = 0;
-    __syncthreads();
-    if (bad) atomicOr(&L.flag, 1);
-    if (tid < 2) L.hist[tid] = 0;
-    __syncthreads();
-    atomicMax(&L.hist[0], omax);
-    atomicMax(&L.hist[1], wmax);
-    __syncthreads();
-    omax = L.hist[0];
-    wmax = L.hist[1];
-    const bool any_bad = L.flag != 0;
-    __syncthreads();
-    if (any_bad) {  // a request that can never run: report, emit no batches
-        if (tid == 0) {
-            atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
-            *num_batches_out = 0;
-        }
-        return;
-    }
+// ------------------------------------------------------------------------------ one workgroup
 
-    if constexpr (IN_LDS) {
-        s = s_lds;
-        o = o_lds;
-    }
+// Everything in one workgroup: n <= TPB * E requests, element 64 E wave + 64 e + lane of an order in k[e].
+// Also the length scan of the call (status word, longest decode).  What bounds it is latency, a chain of short
+// steps: 64 requests run without a barrier that waits for anyone (one wavefront), 2000 in @NS@.
+template <int TPB, int E, bool PROFILE>
+__global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
+{
+    constexpr int N = TPB * E, NW = TPB / 64;
+    extern __shared__ u64 lds64[];
+    // the sort's two buffers and the prefix sums are never alive together
+    u64 *W = lds64, *G = W + N + 2, *S = PROFILE ? G + N + 2 : G;
+    int *ends = (int *)(lds64 + (PROFILE ? 3 : 2) * (N + 2));
+    int *by_o = ends + N;  // id at a rank of the (o, id) order, and the inverse (only when ranks are needed)
+    int *rank_of = by_o + N;
+    int *next = rank_of + N;  // size of the batch a place would start (when found for all places)
+    int *s_pos = next;        // PROFILE: lengths by sorted position, rank by sorted position
+    int *o_pos = s_pos + N, *rank_pos = o_pos + N, *o_of_rank = rank_pos + N;
+    unsigned *hist = (unsigned *)(o_of_rank + N);
+    __shared__ u64 tot_w[NW], tot_q[NW], red_S[16];
+    __shared__ int red_k[16], sh[4];
+    __shared__ unsigned wave_c[16], wave_s[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n;
+    const int i0 = 64 * E * wave + lane;
+    const u64 M = (u64)p.M;
 
-    // ---- 1/2: key sorts (ids start in id order, every pass is stable)
-    for (int i = tid; i < n; i += TPB) buf0[i] = i;
+    // ---- lengths, well-formedness, keys
+    if (tid == 0) sh[0] = 0, sh[1] = 0, sh[2] = 0;
     __syncthreads();
-    int *cur = buf0, *alt = buf1;
-    auto key_o = [o](int id) { return o[id]; };
-    auto key_w = [s, o](int id) { return s[id] + o[id]; };
-    for (int shift = 0; shift < bits_of(omax); shift += 8) {
-        radix_pass(cur, alt, n, shift, key_o, L.radix);
-        int *t = cur; cur = alt; alt = t;
+    int sv[E], ov[E], bad = 0, omax = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        sv[e] = ov[e] = 1;
+        if (i < n) sv[e] = p.s[i], ov[e] = p.o[i];
+        if (sv[e] < 1 || ov[e] < 1 || (long long)sv[e] + ov[e] > (long long)p.M) bad = 1;
+        if (i < n) omax = max(omax, ov[e]);
     }
-    for (int i = tid; i < n; i += TPB) by_o[i] = cur[i];
+    for (int d = 32; d > 0; d >>= 1) omax = max(omax, __shfl_xor(omax, d));
+    if (lane == 0) atomicMax(&sh[1], omax);
+    if (bad) atomicOr(&sh[0], 1);
     __syncthreads();
-    for (int shift = 0; shift < bits_of(wmax); shift += 8) {
-        radix_pass(cur, alt, n, shift, key_w, L.radix);
-        int *t = cur; cur = alt; alt = t;
-    }
-    const int *sorted = cur;  // (s+o, o, id) ascending
-    if (PROFILE) {
-        for (int i = tid; i < n; i += TPB) pos_w[sorted[i]] = i;
-    }
-
-    // ---- 3: inclusive prefix sums over the sorted order; cumW[0] = cumS[0] = 0
+    bad = sh[0];
+    omax = sh[1];
     if (tid == 0) {
-        L.carry_a = 0;
-        L.carry_b = 0;
-        cumW[0] = 0;
-        cumS[0] = 0;
-        cumG[0] = 0;  // (cumG is cumS itself under the F-metric)
+        p.words[KVS_W_STATUS] = bad ? KVSCHED_DEV_BAD_LENGTH : 0;
+        p.words[KVS_W_OMAX] = omax;
+        p.words[KVS_W_MINPOS] = 0x7fffffff;
+        p.words[KVS_W_MAXPOS] = -1;
+        if (bad) *p.num_batches_out = 0;
     }
-    __syncthreads();
-    for (int tile = 0; tile < n; tile += TPB) {
-        const int i = tile + tid;
-        long long w = 0, q = 0;
-        if (i < n) {
-            const int id = sorted[i];
-            q = o[id];
-            w = (long long)s[id] + q;
-        }
-        for (int d = 1; d < 64; d <<= 1) {
-            const long long uw = __shfl_up(w, d), uq = __shfl_up(q, d);
-            if (lane >= d) { w += uw; q += uq; }
-        }
-        if (lane == 63) { L.scan_a[wave] = w; L.scan_b[wave] = q; }
-        __syncthreads();
-        long long offw = L.carry_a, offq = L.carry_b;
-        for (int v = 0; v < wave; ++v) { offw += L.scan_a[v]; offq += L.scan_b[v]; }
-        if (i < n) { cumW[i + 1] = w + offw; cumS[i + 1] = q + offq; }
-        __syncthreads();
-        if (tid == TPB - 1) { L.carry_a = w + offw; L.carry_b = q + offq; }
-        __syncthreads();
-    }
-    if (cumG != cumS) {  // sum of the effective lengths = ga (W - S) + gb S
-        __threadfence_block();
-        __syncthreads();
-        for (int i = tid; i <= n; i += TPB) cumG[i] = (long long)ga * (cumW[i] - cumS[i]) + (long long)gb * cumS[i];
-    }
-    __threadfence_block();
-    __syncthreads();
-
-    // ---- 4 and 5 by one wavefront when everything sits in LDS and feasibility is the sum of peaks:
-    // the steps that follow are short and dependent; sixteen wavefronts meeting at barriers after
-    // each of them take 2.5 us a batch, one wavefront on its own 2 us (and the final sort 8 us instead of 4).
-    if constexpr (IN_LDS && !PROFILE) {
-        if (wave != 0) return;
-        const bool small1 = n < 65536 && cumG[n] < (1ll << 32);
-        int a1 = 0, nb1 = 0;
-        while (a1 < n) {
-            const long long W0 = cumW[a1], G0 = cumG[a1];
-            // feasible extent K: 64 probes a turn narrow [lo, lo + span] (fit(lo) holds; fit is monotone)
-            int lo = 0, span = n - a1;
-            while (span > 0) {
-                const int step = (span + 63) >> 6;
-                const int k = lo + (lane + 1) * step;
-                const bool ok = k <= lo + span && cumW[a1 + k] - W0 <= (long long)M;
-                const int c = __popcll(__builtin_amdgcn_ballot_w64(ok));  // a prefix of the probes fits
-                const int hi = lo + span;
-                lo += c * step;
-                span = min(hi, lo + step - 1) - lo;
-            }
-            const int K = lo;
-            if (K < 1) {  // cannot happen for well-formed input; never spin
-                if (lane == 0) atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
-                break;
-            }
-            int bk = 0;
-            if (small1) {
-                unsigned bs = 0;
-                for (int k = lane + 1; k <= K; k += 64) {
-                    const unsigned Sk = (unsigned)(cumG[a1 + k] - G0);
-                    if (better_small(Sk, k, bs, bk, tie_rule)) { bs = Sk; bk = k; }
-                }
-                row_best_small(bs, bk, tie_rule);
-                for (int d = 16; d <= 32; d <<= 1) {
-                    const unsigned oS = (unsigned)__shfl_xor((int)bs, d);
-                    const int ok = __shfl_xor(bk, d);
-                    if (better_small(oS, ok, bs, bk, tie_rule)) { bs = oS; bk = ok; }
-                }
-            } else {
-                long long bS = 0;
-                for (int k = lane + 1; k <= K; k += 64) {
-                    const long long Sk = cumG[a1 + k] - G0;
-                    if (better(Sk, k, bS, bk, tie_rule)) { bS = Sk; bk = k; }
-                }
-                for (int d = 1; d < 64; d <<= 1) {  // (exchanges both ways: every lane ends with the winner)
-                    const long long oS = __shfl_xor(bS, d);
-                    const int ok = __shfl_xor(bk, d);
-                    if (better(oS, ok, bS, bk, tie_rule)) { bS = oS; bk = ok; }
-                }
-            }
-            const int kstar = __builtin_amdgcn_readfirstlane(bk);
-            if (lane == 0) ends[nb1] = a1 + kstar;
-            for (int i = lane; i < kstar; i += 64) batch_of[sorted[a1 + i]] = nb1;
-            a1 += kstar;
-            ++nb1;
-        }
-        if (lane == 0) *num_batches_out = nb1;
-        for (int b = lane; b < nb1; b += 64) {
-            const int lo = b == 0 ? 0 : ends[b - 1], hi = ends[b];
-            batch_end_out[b] = hi;
-            const double k = (double)(hi - lo);
-            F_out[b] = (double)(cumG[hi] - cumG[lo]) / ((double)gb * k * k);
-        }
-        // the (o, id)-sorted ids by batch number (stable): `sorted` and the other sort buffer are free now
-        const int *src1 = by_o;
-        int *dst1 = alt, *oth1 = cur;
-        auto key_b1 = [batch_of](int id) { return batch_of[id]; };
-        for (int shift = 0; shift < bits_of(nb1 - 1); shift += 8) {
-            radix_pass_wave(src1, dst1, n, shift, key_b1, L.radix.hist);
-            src1 = dst1;
-            dst1 = oth1;
-            oth1 = (int *)src1;
-        }
-        for (int i = lane; i < n; i += 64) order_out[i] = src1[i];
+    if (bad) {  // a request that can never run: no batches
+        if (p.pad)
+            for (int i = tid; i < n; i += TPB) p.batch_end_out[i] = 0, p.F_out[i] = 0.0;
         return;
     }
+    u64 key[E];
+    const u64 id_mask = field_mask(p.id_bits);
+    const bool ranks = !p.packed || (PROFILE && omax > kSmallBuckets);
+    if (ranks) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = i0 + 64 * e;
+            key[e] = i < n ? ((u64)ov[e] << p.id_bits) | (u64)i : ~0ull;
+        }
+        block_sort<TPB, E>(key, lds64);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int r = i0 + 64 * e;
+            if (r < n) {
+                const int id = (int)(key[e] & id_mask);
+                by_o[r] = id;
+                rank_of[id] = r;
+                if (PROFILE) o_of_rank[r] = (int)(key[e] >> p.id_bits);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        const u64 w = (u64)sv[e] + (u64)ov[e];
+        if (i >= n) key[e] = ~0ull;
+        else if (p.packed) key[e] = (((w << p.o_bits) | (u64)ov[e]) << p.id_bits) | (u64)i;
+        else key[e] = (w << p.id_bits) | (u64)rank_of[i];
+    }
+    block_sort<TPB, E>(key, lds64);
+    __syncthreads();
 
-    // ---- 4: batches
-    const bool small = n < 65536 && cumG[n] < (1ll << 32);
+    // ---- prefix sums over the sorted order
+    u64 w[E], q[E], cw = 0, cq = 0;
+    int id[E], oid[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        id[e] = oid[e] = 0;
+        u64 wv = 0, qv = 0;
+        if (i < n) {
+            if (p.packed) {
+                id[e] = (int)(key[e] & id_mask);
+                qv = (key[e] >> p.id_bits) & field_mask(p.o_bits);
+                wv = key[e] >> (p.id_bits + p.o_bits);
+            } else {
+                id[e] = by_o[(int)(key[e] & id_mask)];
+                qv = (u64)p.o[id[e]];
+                wv = key[e] >> p.id_bits;
+            }
+            oid[e] = (int)qv;
+            if (PROFILE) {
+                o_pos[i] = (int)qv;
+                s_pos[i] = (int)(wv - qv);
+                if (ranks) rank_pos[i] = rank_of[id[e]];
+            }
+        }
+        w[e] = wave_scan_u64(wv) + cw;
+        q[e] = wave_scan_u64(qv) + cq;
+        cw = lane_value_u64(w[e], 63);
+        cq = lane_value_u64(q[e], 63);
+    }
+    if (lane == 0) tot_w[wave] = cw, tot_q[wave] = cq;
+    __syncthreads();
+    u64 off_w = 0, off_q = 0, all_w = 0, all_q = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+        const u64 xw = tot_w[v], xq = tot_q[v];
+        if (v < wave) off_w += xw, off_q += xq;
+        all_w += xw;
+        all_q += xq;
+    }
+    const u64 ga = (u64)p.ga, gb = (u64)p.gb;
+    const u64 all_g = ga * (all_w - all_q) + gb * all_q;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        if (i < n) {
+            const u64 wi = w[e] + off_w, qi = q[e] + off_q;
+            W[i + 1] = wi;
+            if (PROFILE) S[i + 1] = qi;
+            G[i + 1] = ga * (wi - qi) + gb * qi;
+        }
+    }
+    if (tid == 0) W[0] = G[0] = S[0] = 0;
+    __syncthreads();
+
+    // ---- batches
+    const Sums c{W, S, G, s_pos, o_pos};
+    const bool small = all_g < (1ull << 32);
+    int nb = 0;
+    if constexpr (!PROFILE) {
+        if (NW > 1 && all_w > M * (u64)(n / 32 + 1)) {
+            // many small batches: all wavefronts find the batch that each place would start, then the chain is followed
+            for (int a = wave; a < n; a += NW) {
+                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule, false)
+                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule, false);
+                if (lane == 0) next[a] = k;
+            }
+            __syncthreads();
+            if (wave == 0) {
+                for (int a = 0; a < n;) {
+                    const int k = __builtin_amdgcn_readfirstlane(next[a]);
+                    if (k < 1) break;  // cannot happen for well-formed input; never spin
+                    a += k;
+                    if (lane == 0) ends[nb] = a;
+                    ++nb;
+                }
+                if (lane == 0) sh[2] = nb;
+            }
+        } else if (wave == 0) {  // one wavefront, no barriers
+            for (int a = 0; a < n;) {
+                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule, false)
+                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule, false);
+                if (k < 1) break;
+                a += k;
+                if (lane == 0) ends[nb] = a;
+                ++nb;
+            }
+            if (lane == 0) sh[2] = nb;
+        }
+        __syncthreads();
+        nb = sh[2];
+    } else if constexpr (NW == 1) {
+        for (int a = 0; a < n;) {  // (n <= 64 < kNextMax: always decided)
+            const int K = wave_profile_extent(c, a, n - a, (unsigned)M);
+            const int k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule, false)
+                                : wave_batch<false>(c, a, K, ~0ull, p.tie_rule, false);
+            if (k < 1) break;
+            a += k;
+            if (lane == 0) ends[nb] = a;
+            ++nb;
+        }
+        __syncthreads();
+    } else {
+        static_assert(TPB == 1024 || !PROFILE || TPB == 64, "the workgroup-wide profile test takes 1024 threads");
+        Profile<true> prof{hist, hist + kSmallBuckets, hist + 2 * kSmallBuckets, hist + 3 * kSmallBuckets,
+                                 ranks ? n : omax, ranks ? rank_pos : nullptr, o_of_rank};
+        prof.clear();
+        for (int a = 0; a < n;) {
+            if (wave == 0) {
+                const int K = wave_profile_extent(c, a, n - a, (unsigned)M);
+                int k = -1;
+                if (K >= 0)
+                    k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule, false)
+                              : wave_batch<false>(c, a, K, ~0ull, p.tie_rule, false);
+                if (lane == 0) sh[3] = k;
+            }
+            __syncthreads();
+            int k = sh[3];
+            __syncthreads();
+            if (k < 0) {
+                const int K = prof.extent(c, a, n - a, (unsigned)M, wave_c, wave_s);
+                k = small ? group_argmin<true>(c, a, K, p.tie_rule, red_S, red_k)
+                          : group_argmin<false>(c, a, K, p.tie_rule, red_S, red_k);
+            }
+            if (k < 1) break;
+            a += k;
+            if (tid == 0) ends[nb] = a;
+            ++nb;
+        }
+        __syncthreads();
+    }
+
+    // ---- metric values, and the batches in nondecreasing o
+    for (int b = tid; b < (p.pad ? n : nb); b += TPB) {
+        if (b < nb) {
+            const int lo = b == 0 ? 0 : ends[b - 1], hi = ends[b];
+            p.batch_end_out[b] = hi;
+            const double k = (double)(hi - lo);
+            p.F_out[b] = (double)(G[hi] - G[lo]) / ((double)p.gb * k * k);
+        } else {
+            p.batch_end_out[b] = 0;
+            p.F_out[b] = 0.0;
+        }
+    }
+    if (tid == 0) {
+        *p.num_batches_out = nb;
+        if (nb == 0 || ends[nb - 1] != n) atomicOr(&p.words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        key[e] = ~0ull;
+        if (i < n) {
+            const u64 b = (u64)batch_of_place(ends, nb, i);
+            key[e] = p.packed ? (((b << p.o_bits) | (u64)oid[e]) << p.id_bits) | (u64)id[e]
+                              : (b << p.id_bits) | (u64)rank_of[id[e]];
+        }
+    }
+    __syncthreads();
+    block_sort<TPB, E>(key, lds64);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = i0 + 64 * e;
+        if (i < n) {
+            const int v = (int)(key[e] & id_mask);
+            p.order_out[i] = p.packed ? v : by_o[v];
+        }
+    }
+}
+
+// Words of dynamic LDS of the kernel above.
+constexpr size_t small_lds_bytes(int N, bool profile)
+{
+    return (size_t)(profile ? 3 : 2) * 8 * (N + 2) + (size_t)(profile ? 7 : 4) * 4 * N + (profile ? 16 * kSmallBuckets : 0);
+}
+static_assert(small_lds_bytes(4096, false) >= 16 * 4096 && small_lds_bytes(2048, true) + 2048 <= 160 * 1024, "fits the LDS");
+
+// ------------------------------------------------------------------------- many workgroups
+
+// What the launches of a large construction share (arrays in the context's scratch).
+struct LargeArrays {
+    u64 *key[2];
+    u64 *W, *S, *G, *tot;  // tot: two sums per 4096 places
+    int *s_pos, *o_pos;
+    int *by_o, *rank_of, *rank_pos, *o_of_rank;  // (only when the (o, id) order is sorted too)
+    unsigned char *next;
+    unsigned *hist;
+};
+
+__device__ __forceinline__ bool faulty(const SortedArgs &p) { return (p.words[KVS_W_STATUS] & KVSCHED_DEV_BAD_LENGTH) != 0; }
+
+enum { KEYS_BY_O, KEYS_BY_SIZE, KEYS_BY_BATCH };
+
+// Keys of kRun consecutive requests (places, for KEYS_BY_BATCH), sorted.
+template <int WHAT>
+__global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArrays m, const u64 *by_place, u64 *out)
+{
+    __shared__ u64 buf[2 * kRun];
+    if (faulty(p)) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const u64 id_mask = field_mask(p.id_bits);
+    const int nb = WHAT == KEYS_BY_BATCH ? *p.num_batches_out : 0;
+    u64 key[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int i = kRun * blockIdx.x + 128 * wave + 64 * e + lane;
+        key[e] = ~0ull;
+        if (i < p.n) {
+            if constexpr (WHAT == KEYS_BY_O) {
+                key[e] = ((u64)p.o[i] << p.id_bits) | (u64)i;
+            } else if constexpr (WHAT == KEYS_BY_SIZE) {
+                const u64 o = (u64)p.o[i], w = (u64)p.s[i] + o;
+                key[e] = p.packed ? (((w << p.o_bits) | o) << p.id_bits) | (u64)i : (w << p.id_bits) | (u64)m.rank_of[i];
+            } else {
+                const u64 old = by_place[i];
+                const u64 b = (u64)batch_of_place(p.batch_end_out, nb, i);
+                const u64 low = p.packed ? old & field_mask(p.o_bits + p.id_bits) : old & id_mask;
+                key[e] = (b << (p.packed ? p.o_bits + p.id_bits : p.id_bits)) | low;
+            }
+        }
+    }
+    block_sort<1024, 2>(key, buf);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int i = kRun * blockIdx.x + 128 * wave + 64 * e + lane;
+        if (i < p.n) out[i] = key[e];
+    }
+}
+
+// One pass of merging sorted runs of `run` keys, kFan at a time: the keys are distinct, so a key's place is its place
+// in its own run plus the number of smaller keys in the others, found by binary searches that advance together.
+// The last pass may emit what the key stands for: MERGE_IDS the request ids (the order), MERGE_RANKS the (o, id)
+// order and its inverse.
+enum { MERGE_KEYS, MERGE_IDS, MERGE_RANKS };
+template <int EMIT>
+__global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArrays m, const u64 *in, u64 *out, int run)
+{
+    if (faulty(p)) return;
+    const int g = blockIdx.x * 256 + threadIdx.x, n = p.n;
+    if (g >= n) return;
+    const u64 key = in[g];
+    const int r = g / run, first = r / kFan * kFan;
+    int below[kFan - 1], start[kFan - 1], len[kFan - 1];
+#pragma unroll
+    for (int q = 0; q < kFan - 1; ++q) {
+        const int rr = first + q + (first + q >= r ? 1 : 0);
+        const long long st = (long long)rr * run;
+        start[q] = (int)min(st, (long long)n);
+        len[q] = (int)min((long long)run, (long long)n - start[q]);
+        below[q] = 0;
+    }
+    for (int step = run; step > 0; step >>= 1) {
+#pragma unroll
+        for (int q = 0; q < kFan - 1; ++q) {
+            const int at = below[q] + step - 1;
+            if (at < len[q] && in[start[q] + at] < key) below[q] += step;
+        }
+    }
+    int place = first * run + (g - r * run);
+#pragma unroll
+    for (int q = 0; q < kFan - 1; ++q) place += below[q];
+    const int v = (int)(key & field_mask(p.id_bits));
+    if constexpr (EMIT == MERGE_KEYS) {
+        out[place] = key;
+    } else if constexpr (EMIT == MERGE_IDS) {
+        p.order_out[place] = p.packed ? v : m.by_o[v];
+    } else {
+        m.by_o[place] = v;
+        m.rank_of[v] = place;
+        m.o_of_rank[place] = (int)(key >> p.id_bits);
+    }
+}
+
+// Lengths by sorted place, and the sums of s+o and o over each 4096 places.
+__global__ __launch_bounds__(1024) void place_lengths_kernel(SortedArgs p, LargeArrays m, const u64 *sorted, int ranks)
+{
+    if (faulty(p)) return;
+    __shared__ u64 tw[16], tq[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const u64 id_mask = field_mask(p.id_bits);
+    u64 aw = 0, aq = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
+        if (i < p.n) {
+            const u64 key = sorted[i];
+            u64 w, o;
+            int rank = 0;
+            if (p.packed) {
+                o = (key >> p.id_bits) & field_mask(p.o_bits);
+                w = key >> (p.id_bits + p.o_bits);
+                if (ranks) rank = m.rank_of[(int)(key & id_mask)];
+            } else {
+                rank = (int)(key & id_mask);
+                o = (u64)m.o_of_rank[rank];
+                w = key >> p.id_bits;
+            }
+            m.s_pos[i] = (int)(w - o);
+            m.o_pos[i] = (int)o;
+            if (ranks) m.rank_pos[i] = rank;
+            aw += w;
+            aq += o;
+        }
+    }
+    aw = lane_value_u64(wave_scan_u64(aw), 63);
+    aq = lane_value_u64(wave_scan_u64(aq), 63);
+    if (lane == 0) tw[wave] = aw, tq[wave] = aq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 1; v < 16; ++v) aw += tw[v], aq += tq[v];
+        m.tot[2 * blockIdx.x] = aw;
+        m.tot[2 * blockIdx.x + 1] = aq;
+    }
+}
+
+__global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeArrays m)
+{
+    if (faulty(p)) return;
+    __shared__ u64 tw[16], tq[16], bw[16], bq[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    u64 fw = 0, fq = 0;  // everything before this block
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += 1024) fw += m.tot[2 * b], fq += m.tot[2 * b + 1];
+    fw = lane_value_u64(wave_scan_u64(fw), 63);
+    fq = lane_value_u64(wave_scan_u64(fq), 63);
+    if (lane == 0) bw[wave] = fw, bq[wave] = fq;
+    u64 w[4], q[4], cw = 0, cq = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
+        const u64 o = i < p.n ? (u64)m.o_pos[i] : 0, s = i < p.n ? (u64)m.s_pos[i] : 0;
+        w[e] = wave_scan_u64(s + o) + cw;
+        q[e] = wave_scan_u64(o) + cq;
+        cw = lane_value_u64(w[e], 63);
+        cq = lane_value_u64(q[e], 63);
+    }
+    if (lane == 0) tw[wave] = cw, tq[wave] = cq;
+    __syncthreads();
+    u64 ow = 0, oq = 0;
+    for (int v = 0; v < 16; ++v) {
+        ow += bw[v] + (v < wave ? tw[v] : 0);
+        oq += bq[v] + (v < wave ? tq[v] : 0);
+    }
+    const u64 ga = (u64)p.ga, gb = (u64)p.gb;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
+        if (i < p.n) {
+            const u64 wi = w[e] + ow, qi = q[e] + oq;
+            m.W[i + 1] = wi;
+            m.S[i + 1] = qi;
+            m.G[i + 1] = ga * (wi - qi) + gb * qi;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) m.W[0] = m.S[0] = m.G[0] = 0;
+}
+
+__device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c) { return p.n < 65536 && c.G[p.n] < (1ull << 32); }
+
+// The batch every place would start, one wavefront each; 0 where it is not decided by kNextMax - 1 requests.
+template <bool PROFILE>
+__global__ __launch_bounds__(256) void next_batch_kernel(SortedArgs p, LargeArrays m)
+{
+    if (faulty(p)) return;
+    const int a = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (a >= p.n) return;
+    const Sums c{m.W, m.S, m.G, m.s_pos, m.o_pos};
+    const bool small = small_numbers(p, c);
+    int rem = p.n - a;
+    u64 M = (u64)p.M;
+    int k = 0;
+    if constexpr (PROFILE) {
+        rem = wave_profile_extent(c, a, rem, (unsigned)M);
+        M = ~0ull;
+    }
+    if (rem > 0) k = small ? wave_batch<true>(c, a, rem, M, p.tie_rule, true) : wave_batch<false>(c, a, rem, M, p.tie_rule, true);
+    if ((threadIdx.x & 63) == 0) m.next[a] = (unsigned char)(k > 0 && k < kNextMax ? k : 0);
+}
+
+// The chain of batches by one workgroup: the small ones are read off next[] (in LDS when there is room), the others
+// found by all threads.
+template <bool PROFILE>
+__global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeArrays m, int next_lds)
+{
+    extern __shared__ u64 lds64[];
+    __shared__ u64 red_S[16];
+    __shared__ int red_k[16], sh[2];
+    __shared__ unsigned wave_c[16], wave_s[16];
+    const int tid = threadIdx.x, n = p.n;
+    if (faulty(p)) {
+        if (tid == 0) *p.num_batches_out = 0;
+        if (p.pad)
+            for (int i = tid; i < n; i += 1024) p.batch_end_out[i] = 0, p.F_out[i] = 0.0;
+        return;
+    }
+    const Sums c{m.W, m.S, m.G, m.s_pos, m.o_pos};
+    const bool small = small_numbers(p, c);
+    const u64 M = (u64)p.M;
+    unsigned *hist_lds = (unsigned *)lds64;
+    unsigned char *next_in = (unsigned char *)lds64 + (PROFILE ? 16 * kLargeBuckets : 0);
+    if (next_lds)
+        for (int i = tid; i < n; i += 1024) next_in[i] = m.next[i];
+    const bool by_rank = p.words[KVS_W_OMAX] > kLargeBuckets;  // (then the ranks are there)
+    const int *rank_pos = by_rank ? m.rank_pos : nullptr;
+    const int buckets = by_rank ? n : p.words[KVS_W_OMAX];
+    if constexpr (PROFILE) {
+        for (int i = tid; i < 4 * kLargeBuckets; i += 1024) hist_lds[i] = 0;
+        if (buckets > kLargeBuckets) {
+            for (int i = tid; i < 4 * n; i += 1024) m.hist[i] = 0;
+        }
+    }
+    __syncthreads();
     int a = 0, nb = 0;
     while (a < n) {
-        const int rem = n - a;
-        const long long W0 = cumW[a], S0 = cumS[a], G0 = cumG[a];
-        // feasible extent K: the longest prefix within the budget (feasibility is monotone in k)
-        int K = count_fitting(rem, [&](long long k) { return cumW[a + k] - W0; }, M, L, 0);  // sum of peaks <= M
-        if (PROFILE && K >= 1 && K < rem) {
-            // Started together, the prefix must stay within M at every completion time.  The sum of
-            // peaks bounds that memory from above (so K is feasible), and the memory at the earliest
-            // completion is at least sum (s_i + 1) (so nothing beyond hi is); bisect in between.
-            int lo = K;
-            int hi = count_fitting(rem, [&](long long k) { return (cumW[a + k] - W0) - (cumS[a + k] - S0) + k; }, M, L, 1);
-            const int *list = by_o;  // ascending o, holds every member of any prefix probed
-            int len = n;
-            if (!IN_LDS && lo < hi) {
-                // Many requests: a probe through all of them costs more than the batch is worth, and hi
-                // (nothing beyond it fits even at the earliest completion) can lie far above the answer
-                // when decode lengths are long.  So the candidates of this batch are sorted by o once
-                // (stable passes, two spare arrays) and serve every probe; and only the first `cap` of
-                // them, doubled while all of them fit.
-                int cap = min(hi, lo + max(lo, TPB));
-                for (;;) {
-                    const int *src = sorted + a;
-                    int *dst = alt, *oth = pos_w + (((size_t)n + 64) & ~(size_t)63);
-                    for (int shift = 0; shift < bits_of(omax); shift += 8) {
-                        radix_pass(src, dst, cap, shift, key_o, L.radix);
-                        src = dst;
-                        dst = oth;
-                        oth = (int *)src;
-                    }
-                    list = src;
-                    len = cap;
-                    if (cap < hi) {
-                        if (profile_fits(len, a, cap, s, o, list, pos_w, M, L)) {
-                            lo = cap;
-                            cap = min(hi, 2 * cap);
-                            continue;
-                        }
-                        hi = cap - 1;
-                    }
-                    break;
-                }
+        if (tid < 64) {  // follow the chain as far as it is known
+            while (a < n) {
+                const int k = __builtin_amdgcn_readfirstlane(next_lds ? (int)next_in[a] : (int)m.next[a]);
+                if (k < 1) break;
+                a += k;
+                if (tid == 0) p.batch_end_out[nb] = a;
+                ++nb;
             }
-            while (lo < hi) {
-                const int mid = lo + (hi - lo + 1) / 2;
-                if (profile_fits(len, a, mid, s, o, list, pos_w, M, L)) lo = mid;
-                else hi = mid - 1;
-            }
-            K = lo;
-        }
-        if (K < 1) {  // cannot happen for well-formed input; never spin
-            if (tid == 0) atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
-            break;
-        }
-        long long bS = 0;
-        int bk = 0;
-        if (small) {  // every numerator below 2^32, every size below 2^16: 64-bit cross products, lane exchanges
-            unsigned bs = 0;
-            for (int k = tid + 1; k <= K; k += TPB) {
-                const unsigned Sk = (unsigned)(cumG[a + k] - G0);
-                if (better_small(Sk, k, bs, bk, tie_rule)) { bs = Sk; bk = k; }
-            }
-            if (wave * 64 < K) {  // (a wave without candidates leaves the arithmetic units to the others)
-                row_best_small(bs, bk, tie_rule);
-                for (int d = 16; d <= 32; d <<= 1) {
-                    const unsigned oS = (unsigned)__shfl_xor((int)bs, d);
-                    const int ok = __shfl_xor(bk, d);
-                    if (better_small(oS, ok, bs, bk, tie_rule)) { bs = oS; bk = ok; }
-                }
-            }
-            if (lane == 0) { L.red_S[wave] = bs; L.red_k[wave] = bk; }
-            __syncthreads();
-            if (wave == 0) {  // the waves' winners in the first row of lanes
-                static_assert(NWAVES == 16, "one 16-lane row holds the waves' winners");
-                bs = (unsigned)L.red_S[lane & 15];
-                bk = L.red_k[lane & 15];
-                row_best_small(bs, bk, tie_rule);
-                if (lane == 0) {
-                    L.best_k = bk;
-                    ends[nb] = a + bk;
-                }
-            }
-        } else {
-            for (int k = tid + 1; k <= K; k += TPB) {
-                const long long Sk = cumG[a + k] - G0;
-                if (better(Sk, k, bS, bk, tie_rule)) { bS = Sk; bk = k; }
-            }
-            if (wave * 64 < K) {
-                for (int d = 32; d > 0; d >>= 1) {
-                    const long long oS = __shfl_down(bS, d);
-                    const int ok = __shfl_down(bk, d);
-                    if (better(oS, ok, bS, bk, tie_rule)) { bS = oS; bk = ok; }
-                }
-            }
-            if (lane == 0) { L.red_S[wave] = bS; L.red_k[wave] = bk; }
-            __syncthreads();
-            if (wave == 0) {  // the waves' winners, one per lane
-                bS = lane < NWAVES ? L.red_S[lane] : 0;
-                bk = lane < NWAVES ? L.red_k[lane] : 0;
-                for (int d = NWAVES / 2; d > 0; d >>= 1) {
-                    const long long oS = __shfl_down(bS, d);
-                    const int ok = __shfl_down(bk, d);
-                    if (better(oS, ok, bS, bk, tie_rule)) { bS = oS; bk = ok; }
-                }
-                if (lane == 0) {
-                    L.best_k = bk;
-                    ends[nb] = a + bk;
-                }
-            }
+            if (tid == 0) sh[0] = a, sh[1] = nb;
         }
         __syncthreads();
-        // (no barrier closes the iteration: the next one passes a barrier before it writes what is read here)
-        const int kstar = L.best_k;
-        for (int i = tid; i < kstar; i += TPB) batch_of[sorted[a + i]] = nb;
-        a += kstar;
+        a = sh[0];
+        nb = sh[1];
+        if (a >= n) break;
+        int K;
+        if constexpr (!PROFILE) {
+            const u64 W0 = c.W[a];
+            K = count_fitting(n - a, [&](int k) { return c.W[a + k] - W0; }, M);
+        } else if (buckets <= kLargeBuckets) {
+            Profile<true> prof{hist_lds, hist_lds + kLargeBuckets, hist_lds + 2 * kLargeBuckets, hist_lds + 3 * kLargeBuckets,
+                               buckets, rank_pos, m.o_of_rank};
+            K = prof.extent(c, a, n - a, (unsigned)M, wave_c, wave_s);
+        } else {
+            Profile<false> prof{m.hist, m.hist + n, m.hist + 2 * (size_t)n, m.hist + 3 * (size_t)n, buckets, rank_pos, m.o_of_rank};
+            K = prof.extent(c, a, n - a, (unsigned)M, wave_c, wave_s);
+        }
+        const int k = small ? group_argmin<true>(c, a, K, p.tie_rule, red_S, red_k)
+                            : group_argmin<false>(c, a, K, p.tie_rule, red_S, red_k);
+        if (k < 1) {  // cannot happen for well-formed input; never spin
+            if (tid == 0) atomicOr(&p.words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
+            break;
+        }
+        a += k;
+        if (tid == 0) p.batch_end_out[nb] = a;
         ++nb;
     }
     __threadfence_block();
     __syncthreads();
-    // metric values of the batches: one fp64 division each
-    for (int b = tid; b < nb; b += TPB) {
-        const int lo = b == 0 ? 0 : ends[b - 1], hi = ends[b];
-        if constexpr (IN_LDS) batch_end_out[b] = hi;
-        const double k = (double)(hi - lo);
-        F_out[b] = (double)(cumG[hi] - cumG[lo]) / ((double)gb * k * k);
+    if (tid == 0) *p.num_batches_out = nb;
+    for (int b = tid; b < (p.pad ? n : nb); b += 1024) {
+        if (b < nb) {
+            const int lo = b == 0 ? 0 : p.batch_end_out[b - 1], hi = p.batch_end_out[b];
+            const double k = (double)(hi - lo);
+            p.F_out[b] = (double)(m.G[hi] - m.G[lo]) / ((double)p.gb * k * k);
+        } else {
+            p.F_out[b] = 0.0;
+        }
     }
-    if (tid == 0) *num_batches_out = nb;
-    __threadfence_block();
-    __syncthreads();
-
-    // ---- 5: order the (o, id)-sorted ids by batch number (stable)
-    int *src = by_o;
-    int *dst = (cur == buf0) ? buf1 : buf0;  // `sorted` is no longer needed after step 4, but keep it intact
-    int *other = (int *)cur;
-    auto key_b = [batch_of](int id) { return batch_of[id]; };
-    bool first = true;
-    for (int shift = 0; shift < bits_of(nb - 1); shift += 8) {
-        radix_pass(src, dst, n, shift, key_b, L.radix);
-        if (first) { src = dst; dst = other; first = false; }
-        else { int *t = src; src = dst; dst = t; }
-    }
-    for (int i = tid; i < n; i += TPB) order_out[i] = src[i];
+    if (p.pad)
+        for (int b = nb + tid; b < n; b += 1024) p.batch_end_out[b] = 0;
 }
+
+int ok() { return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP; }
+
+template <int TPB, int E, bool PROFILE>
+int launch_small(const SortedArgs &p, hipStream_t st)
+{
+    constexpr size_t bytes = small_lds_bytes(TPB * E, PROFILE);
+    if constexpr (bytes > 64 * 1024) {
+        static const hipError_t granted = hipFuncSetAttribute((const void *)sortedF_small_kernel<TPB, E, PROFILE>,
+                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (granted != hipSuccess) return KVSCHED_EHIP;
+    }
+    hipLaunchKernelGGL((sortedF_small_kernel<TPB, E, PROFILE>), dim3(1), dim3(TPB), bytes, st, p);
+    return ok();
+}
+
+// Merge sorted runs of kRun keys of m.key[0] (through m.key[1] and back) to the end; returns where the keys are
+// (EMIT other than MERGE_KEYS: the last pass emits instead and the result is void).
+template <int EMIT>
+const u64 *launch_merges(const SortedArgs &p, const LargeArrays &m, hipStream_t st)
+{
+    const dim3 grid((unsigned)((p.n + 255) / 256)), block(256);
+    int at = 0;
+    for (long long run = kRun; run < p.n; run *= kFan) {
+        const bool last = run * kFan >= p.n;
+        if (last) hipLaunchKernelGGL((merge_runs_kernel<EMIT>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run);
+        else hipLaunchKernelGGL((merge_runs_kernel<MERGE_KEYS>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run);
+        at ^= 1;
+    }
+    return m.key[at];
+}
+
+template <bool PROFILE>
+int launch_chain(const SortedArgs &p, const LargeArrays &m, hipStream_t st)
+{
+    constexpr int most = 150 * 1024;
+    static const hipError_t granted = hipFuncSetAttribute((const void *)batch_chain_kernel<PROFILE>,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (granted != hipSuccess) return KVSCHED_EHIP;
+    int bytes = PROFILE ? 16 * kLargeBuckets : 0;
+    const int next_lds = bytes + p.n <= most;
+    if (next_lds) bytes += p.n;
+    hipLaunchKernelGGL((batch_chain_kernel<PROFILE>), dim3(1), dim3(1024), bytes, st, p, m, next_lds);
+    return ok();
+}
+
+int bits_for(long long v)  // bits that hold 0..v
+{
+    int b = 1;
+    while (b < 62 && (v >> b) != 0) ++b;
+    return b;
+}
+
+size_t padded(int32_t n) { return ((size_t)n + 64) & ~(size_t)63; }
 
 }  // namespace
 
+// Largest construction done by one workgroup: n = 4096 takes 4 keys a thread; the profile test's arrays leave room
+// for 2048.
+int32_t kvs_sortedF_small_max(int32_t feas_mode) { return feas_mode == KVSCHED_FEAS_PROFILE ? 2048 : 4096; }
+
 size_t kvs_sortedF_scratch_bytes(int32_t n)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    return np * (8 * sizeof(int) + 3 * sizeof(long long)) + 256;
+    if (n <= kvs_sortedF_small_max(KVSCHED_FEAS_PROFILE)) return 256;
+    const size_t np = padded(n);
+    // two key arrays and three sums; block sums; six arrays of ints, four of profile buckets; a byte each
+    return np * 5 * sizeof(u64) + (2 * sizeof(u64)) * (np / 4096 + 1) + np * 10 * sizeof(int) + np + 1024;
 }
 
+// Up to kvs_sortedF_small_max requests the kernel scans the lengths itself (status word and longest decode);
+// beyond, the caller has launched the length scan before.
 int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                       int32_t tie_rule, int32_t feas_mode, int32_t *order_out, int32_t *batch_end_out, double *F_out, int32_t *num_batches_out,
-                       void *scratch, int32_t *d_words, hipStream_t st)
+                       int32_t tie_rule, int32_t feas_mode, int32_t pad, int32_t *order_out, int32_t *batch_end_out,
+                       double *F_out, int32_t *num_batches_out, void *scratch, int32_t *d_words, hipStream_t st)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    long long *cumW = (long long *)scratch;
-    long long *cumS = cumW + np;
-    long long *cumG = (ga == 0 && gb == 1) ? cumS : cumS + np;
-    int *buf0 = (int *)(cumS + 2 * np);
-    int *buf1 = buf0 + np;
-    int *by_o = buf1 + np;
-    int *batch_of = by_o + np;
-    int *pos_w = batch_of + np;
-    const size_t arrays = kvs_sortedF_scratch_bytes(n);
-    const int profile = feas_mode == KVSCHED_FEAS_PROFILE ? 1 : 0;
-    constexpr size_t kLdsPerWorkgroup = 160 * 1024;
-    if (arrays + sizeof(Lds) <= kLdsPerWorkgroup) {
-        // more than 64 KB of LDS in all: the kernel's limit on the dynamic part is raised first, as far as needed
-        static size_t granted[2] = {64 * 1024 - sizeof(Lds), 64 * 1024 - sizeof(Lds)};
-        if (arrays > granted[profile]) {
-            const void *fn = profile ? (const void *)sortedF_kernel<true, true> : (const void *)sortedF_kernel<true, false>;
-            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)arrays) != hipSuccess)
-                return KVSCHED_EHIP;
-            granted[profile] = arrays;
+    SortedArgs p;
+    p.n = n;
+    p.s = s;
+    p.o = o;
+    p.M = M;
+    p.ga = ga;
+    p.gb = gb;
+    p.tie_rule = tie_rule;
+    p.order_out = order_out;
+    p.batch_end_out = batch_end_out;
+    p.F_out = F_out;
+    p.num_batches_out = num_batches_out;
+    p.words = d_words;
+    p.id_bits = bits_for(n - 1);
+    p.o_bits = bits_for(M);
+    // the keys (s+o, o, id) and (batch, o, id) in 64 bits, and not all ones (that stands for "no key")
+    p.packed = 2 * p.o_bits + p.id_bits <= 63 && p.o_bits + 2 * p.id_bits <= 63;
+    p.pad = pad;
+    const bool profile = feas_mode == KVSCHED_FEAS_PROFILE;
+    // One workgroup: as few wavefronts as hold the keys one each (a barrier costs by the wavefront), two or four each
+    // beyond 1024.
+    if (n <= kvs_sortedF_small_max(feas_mode)) {
+        if (profile) {
+            if (n <= 64) return launch_small<64, 1, true>(p, st);
+            if (n <= 1024) return launch_small<1024, 1, true>(p, st);
+            return launch_small<1024, 2, true>(p, st);
         }
-        if (profile)
-            hipLaunchKernelGGL((sortedF_kernel<true, true>), dim3(1), dim3(TPB), arrays, st, n, s, o, M, ga, gb, tie_rule,
-                               feas_mode, order_out, batch_end_out, F_out, num_batches_out, buf0, buf1, by_o, cumW,
-                               cumS, cumG, batch_of, pos_w, d_words);
-        else
-            hipLaunchKernelGGL((sortedF_kernel<true, false>), dim3(1), dim3(TPB), arrays, st, n, s, o, M, ga, gb, tie_rule,
-                               feas_mode, order_out, batch_end_out, F_out, num_batches_out, buf0, buf1, by_o, cumW,
-                               cumS, cumG, batch_of, pos_w, d_words);
-    } else if (profile) {
-        hipLaunchKernelGGL((sortedF_kernel<false, true>), dim3(1), dim3(TPB), 0, st, n, s, o, M, ga, gb, tie_rule,
-                           feas_mode, order_out, batch_end_out, F_out, num_batches_out, buf0, buf1, by_o, cumW, cumS,
-                           cumG, batch_of, pos_w, d_words);
-    } else {
-        hipLaunchKernelGGL((sortedF_kernel<false, false>), dim3(1), dim3(TPB), 0, st, n, s, o, M, ga, gb, tie_rule,
-                           feas_mode, order_out, batch_end_out, F_out, num_batches_out, buf0, buf1, by_o, cumW, cumS,
-                           cumG, batch_of, pos_w, d_words);
+        if (n <= 64) return launch_small<64, 1, false>(p, st);
+        if (n <= 256) return launch_small<256, 1, false>(p, st);
+        if (n <= 1024) return launch_small<1024, 1, false>(p, st);
+        if (n <= 2048) return launch_small<1024, 2, false>(p, st);
+        return launch_small<1024, 4, false>(p, st);
     }
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+    const size_t np = padded(n);
+    LargeArrays m;
+    u64 *q = (u64 *)scratch;
+    m.key[0] = q;
+    m.key[1] = q + np;
+    m.W = q + 2 * np;
+    m.S = q + 3 * np;
+    m.G = q + 4 * np;
+    m.tot = q + 5 * np;
+    int *i = (int *)(m.tot + 2 * (np / 4096 + 1));
+    m.s_pos = i;
+    m.o_pos = i + np;
+    m.by_o = i + 2 * np;
+    m.rank_of = i + 3 * np;
+    m.rank_pos = i + 4 * np;
+    m.o_of_rank = i + 5 * np;
+    m.hist = (unsigned *)(i + 6 * np);
+    m.next = (unsigned char *)(i + 10 * np);
+    const dim3 runs((unsigned)((n + kRun - 1) / kRun)), sums((unsigned)((n + 4095) / 4096));
+    // Ranks in the (o, id) order are needed by keys that do not fit and, under the profile constraint, when completion
+    // times may be too many for buckets in LDS.
+    const int ranks = !p.packed || (profile && M > kLargeBuckets);
+    if (ranks) {
+        hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_O>), runs, dim3(1024), 0, st, p, m, (const u64 *)nullptr, m.key[0]);
+        (void)launch_merges<MERGE_RANKS>(p, m, st);
+    }
+    hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_SIZE>), runs, dim3(1024), 0, st, p, m, (const u64 *)nullptr, m.key[0]);
+    const u64 *sorted = launch_merges<MERGE_KEYS>(p, m, st);
+    if (sorted != m.key[1]) {  // (the batches' keys are written beside them)
+        m.key[0] = m.key[1];
+        m.key[1] = (u64 *)sorted;
+    }
+    hipLaunchKernelGGL(place_lengths_kernel, sums, dim3(1024), 0, st, p, m, sorted, ranks);
+    hipLaunchKernelGGL(prefix_sums_kernel, sums, dim3(1024), 0, st, p, m);
+    const dim3 waves((unsigned)((n + 3) / 4));
+    if (profile) hipLaunchKernelGGL((next_batch_kernel<true>), waves, dim3(256), 0, st, p, m);
+    else hipLaunchKernelGGL((next_batch_kernel<false>), waves, dim3(256), 0, st, p, m);
+    const int rc = profile ? launch_chain<true>(p, m, st) : launch_chain<false>(p, m, st);
+    if (rc != KVSCHED_OK) return rc;
+    hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_BATCH>), runs, dim3(1024), 0, st, p, m, sorted, m.key[0]);
+    (void)launch_merges<MERGE_IDS>(p, m, st);
+    return ok();
 }

@@ -48,6 +48,7 @@ def _load() -> ctypes.CDLL:
     lib.kvsched_strerror.argtypes = [ctypes.c_int]
     lib.kvsched_strerror.restype = ctypes.c_char_p
     lib.kvsched_set_o_max.argtypes = [vp, i32]
+    lib.kvsched_set_pad_outputs.argtypes = [vp, ctypes.c_int]
     lib.kvsched_reserve.argtypes = [vp, i32, i32, i32]
     lib.kvsched_device_status.argtypes = [vp, vp, ctypes.POINTER(i32)]
     lib.kvsched_enable_timing.argtypes = [vp, ctypes.c_int]
@@ -94,6 +95,7 @@ class Context:
     def __init__(self, device: int = 0):
         self._h = ctypes.c_void_p()
         self.device = int(device)
+        self._pads = False  # are the Phase-1 calls set to write zeros behind the last batch?
         rc = _lib.kvsched_create(ctypes.byref(self._h), self.device)
         if rc != OK:
             raise KvschedError(rc, "kvsched_create")
@@ -201,17 +203,25 @@ class Context:
             raise KvschedError(rc, "kvsched_neighbor_stop_positions")
         return out
 
+    def _pad_outputs(self, on: bool):
+        if on != self._pads:
+            rc = _lib.kvsched_set_pad_outputs(self._h, 1 if on else 0)
+            if rc != OK:
+                raise KvschedError(rc, "kvsched_set_pad_outputs")
+            self._pads = on
+
     def sortedF(self, s, o, M, tie_rule: int = TIE_LARGER, feas_mode: int = FEAS_SUM_OF_PEAKS, out=None):
         """-> (order [n] int32, batch_end [n] int32, F [n] float64, num_batches [1] int32); the first
         num_batches entries of batch_end / F are meaningful.  out: the four tensors to write into
-        (a caller in a loop keeps them; otherwise they are allocated, batch_end and F zero-filled)."""
+        (a caller in a loop keeps them; otherwise they are allocated, batch_end and F zero behind the last batch)."""
         n = s.shape[0]
         dev = s.device
+        self._pad_outputs(out is None)
         if out is None:
             order = torch.empty(n, dtype=torch.int32, device=dev)
-            ends = torch.zeros(n, dtype=torch.int32, device=dev)
-            F = torch.zeros(n, dtype=torch.float64, device=dev)
-            nb = torch.zeros(1, dtype=torch.int32, device=dev)
+            ends = torch.empty(n, dtype=torch.int32, device=dev)
+            F = torch.empty(n, dtype=torch.float64, device=dev)
+            nb = torch.empty(1, dtype=torch.int32, device=dev)
         else:
             order, ends, F, nb = out
             _dev(order, torch.int32, "order"), _dev(ends, torch.int32, "batch_end")
