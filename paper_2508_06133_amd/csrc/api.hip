@@ -101,6 +101,25 @@ int32_t ring_slots_for(int32_t o_max)
     return h;
 }
 
+// Wait until the length scan number ctx->scan_seq has left its results in pinned host memory.  (The scan is some
+// microseconds of work, so the host polls; now and then it asks the stream, which also ends the wait if the
+// device has failed.)
+int wait_for_scan(kvsched_ctx *ctx, hipStream_t st)
+{
+    const int32_t seq = ctx->scan_seq;
+    for (;;) {
+        for (int i = 0; i < 20000; ++i) {
+            if (__atomic_load_n(&ctx->h_scan[KVS_H_SEQ], __ATOMIC_ACQUIRE) == seq) return KVSCHED_OK;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess) return KVSCHED_EHIP;
+        // everything enqueued has run
+        return __atomic_load_n(&ctx->h_scan[KVS_H_SEQ], __ATOMIC_ACQUIRE) == seq ? KVSCHED_OK : KVSCHED_EHIP;
+    }
+}
+
 // Enqueue the length scan; unless the caller supplied a bound, wait for the largest decode
 // length.  *o_bound_out is what the timeline kernels size their ring from.
 int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t n, int64_t M, hipStream_t st,
@@ -108,30 +127,28 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
                    int32_t *min_position_out = nullptr, int32_t *max_position_out = nullptr)
 {
     if (max_position_out) *max_position_out = n - 1;
-    int rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st);
-    if (rc != KVSCHED_OK) return rc;
     if (min_position_out) *min_position_out = 0;
     if (ctx->o_max_bound > 0) {
         *o_bound_out = ctx->o_max_bound;
-        return KVSCHED_OK;
+        return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st);
     }
-    if (moves && min_position_out) {  // rides on the same read-back: first position any move touches
-        rc = kvs_launch_moves_min_position(moves, K, n, ctx->d_words, st);
-        if (rc != KVSCHED_OK) return rc;
-    }
-    if (hipMemcpyAsync(ctx->h_words, ctx->d_words, sizeof(int32_t) * KVS_W_COUNT, hipMemcpyDeviceToHost, st) !=
-        hipSuccess)
-        return KVSCHED_EHIP;
-    if (hipStreamSynchronize(st) != hipSuccess) return KVSCHED_EHIP;
-    int32_t omax = ctx->h_words[KVS_W_OMAX];
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;  // a captured scan has no result to wait for
+    if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return KVSCHED_EHIP;
+    // (the first and last position the moves touch come with it)
+    int rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, moves, K, ctx->h_scan,
+                                     ctx->scan_seq = (int32_t)((uint32_t)ctx->scan_seq + 1u));
+    if (rc != KVSCHED_OK) return rc;
+    rc = wait_for_scan(ctx, st);
+    if (rc != KVSCHED_OK) return rc;
+    const int32_t omax = ctx->h_scan[KVS_H_OMAX];
     if (omax > KVSCHED_MAX_O) return KVSCHED_ERANGE;
     *o_bound_out = omax < 1 ? 1 : omax;
     if (moves && min_position_out) {
-        const int32_t mp = ctx->h_words[KVS_W_MINPOS];
+        const int32_t mp = ctx->h_scan[KVS_H_MINPOS];
         *min_position_out = (mp < 0 || mp > n) ? 0 : mp;  // INT_MAX: no move changes the order
         if (mp == INT32_MAX) *min_position_out = n;
         if (max_position_out) {
-            const int32_t top = ctx->h_words[KVS_W_MAXPOS];
+            const int32_t top = ctx->h_scan[KVS_H_MAXPOS];
             *max_position_out = (top < 0 || top >= n) ? n - 1 : top;
         }
     }
@@ -282,6 +299,8 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     ctx->o_max_bound = 0;
     ctx->d_words = nullptr;
     ctx->h_words = nullptr;
+    ctx->h_scan = nullptr;
+    ctx->scan_seq = 0;
     ctx->d_scratch = nullptr;
     ctx->scratch_bytes = 0;
     ctx->static_scratch = nullptr;
@@ -303,12 +322,17 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     ctx->resume_wait_polls = kResumeWaitPollsDefault;
     ctx->ev0 = nullptr;
     ctx->ev1 = nullptr;
-    if (hipMalloc((void **)&ctx->d_words, sizeof(int32_t) * KVS_W_COUNT) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->h_words, sizeof(int32_t) * KVS_W_COUNT, hipHostMallocDefault) != hipSuccess ||
-        hipMemset(ctx->d_words, 0, sizeof(int32_t) * KVS_W_COUNT) != hipSuccess) {
+    int32_t words[KVS_W_ALLOCATED] = {0};
+    words[KVS_W_SCAN_MINPOS] = INT32_MAX;
+    words[KVS_W_SCAN_MAXPOS] = -1;
+    if (hipMalloc((void **)&ctx->d_words, sizeof(words)) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->h_words, sizeof(int32_t) * (KVS_W_COUNT + KVS_H_COUNT), hipHostMallocDefault) != hipSuccess ||
+        hipMemcpy(ctx->d_words, words, sizeof(words), hipMemcpyHostToDevice) != hipSuccess) {
         kvsched_destroy(ctx);
         return KVSCHED_ENOMEM;
     }
+    ctx->h_scan = ctx->h_words + KVS_W_COUNT;
+    ctx->h_scan[KVS_H_SEQ] = 0;
     // devices beyond the table simply cannot use kvsched_best_neighbor_static
     if (device_id < kMaxDevices) {
         const int rc = static_scratch_of_current_device(device_id, &ctx->static_scratch);
@@ -917,7 +941,7 @@ static int best_neighbor_on(kvsched_ctx *ctx, void *work, int32_t o_bound_known,
     if (rc != KVSCHED_OK) return rc;
     rc = kvs_launch_check_orders(base_order, 1, n, tel + K, ctx->d_words, st);
     if (rc != KVSCHED_OK) return rc;
-    rc = kvs_launch_argmin(tel, K, result_out, 1, st);
+    rc = kvs_launch_argmin(tel, K, result_out, 1, ctx->d_words, st);
     if (rc != KVSCHED_OK) return rc;
     if (tel_out &&
         hipMemcpyAsync(tel_out, tel, sizeof(int64_t) * (size_t)K, hipMemcpyDeviceToDevice, st) != hipSuccess)
@@ -992,7 +1016,7 @@ int kvsched_horizon_step(kvsched_ctx *ctx, int32_t *order, int32_t n, const int3
         return KVSCHED_EHIP;
     // 3. the chosen timeline, 4. how far it gets
     const int32_t o_bound = ctx->o_max_bound > 0 ? ctx->o_max_bound
-                                                 : (ctx->h_words[KVS_W_OMAX] < 1 ? 1 : ctx->h_words[KVS_W_OMAX]);
+                                                 : (ctx->h_scan[KVS_H_OMAX] < 1 ? 1 : ctx->h_scan[KVS_H_OMAX]);
     SimParams p;
     p.src.orders = order;
     p.src.base = nullptr;
@@ -1119,7 +1143,7 @@ int kvsched_argmin(kvsched_ctx *ctx, const int64_t *tel, int32_t C, int64_t *res
 {
     if (!ctx || !tel || !result_out || C < 1) return KVSCHED_EINVAL;
     if (hipSetDevice(ctx->device) != hipSuccess) return KVSCHED_EHIP;
-    return kvs_launch_argmin(tel, C, result_out, 0, (hipStream_t)stream);
+    return kvs_launch_argmin(tel, C, result_out, 0, ctx->d_words, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -33,6 +33,11 @@ __device__ __forceinline__ int wave_max_i32(int v)
     return max(max(a, b), max(c, d));
 }
 
+// Device-scope atomics and stores issued so far have been performed.  They go through to where every compute unit
+// sees them, so this is all that has to separate them from the atomic that announces them; a device-scope fence would
+// write the whole L2 back as well (5 us behind a kernel that has just stored a few megabytes).
+__device__ __forceinline__ void device_writes_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Position k of candidate order -> request id.
 template <bool MOVES>
 struct OrderReader {

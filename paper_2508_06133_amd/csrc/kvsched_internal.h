@@ -17,14 +17,30 @@ enum {
     KVS_W_BESTM = 6,
     KVS_W_ESTMAX = 7,  // largest initial estimate (kvsched_simulate_predicted)
     KVS_W_MAXPOS = 8,  // largest position any move touches (best_neighbor), -1: none
-    KVS_W_COUNT = 16
+    KVS_W_COUNT = 16,  // (what kvsched_device_status and the waits of kvsched_exact_dp read back)
+    // Behind them, working words of kernels that split one pass over several workgroups: what they have gathered so
+    // far and how many are done.  The workgroup that is done last takes the results and leaves the neutral values.
+    KVS_W_SCAN_OMAX = 16,
+    KVS_W_SCAN_FLAGS = 17,
+    KVS_W_SCAN_MINPOS = 18,  // INT_MAX between calls
+    KVS_W_SCAN_MAXPOS = 19,  // -1 between calls
+    KVS_W_SCAN_DONE = 20,
+    KVS_W_ARGMIN_DONE = 24,
+    KVS_W_ARGMIN_PART = 32,  // two int64 per workgroup
+    KVS_ARGMIN_GROUPS = 64,
+    KVS_W_ALLOCATED = KVS_W_ARGMIN_PART + 4 * KVS_ARGMIN_GROUPS
 };
+
+// What the length scan leaves in pinned host memory for a call that waits for it.
+enum { KVS_H_OMAX = 0, KVS_H_MINPOS = 1, KVS_H_MAXPOS = 2, KVS_H_SEQ = 3, KVS_H_COUNT = 16 };
 
 struct kvsched_ctx {
     int device;
     int32_t o_max_bound;   // 0 = scan o[] on every call
-    int32_t *d_words;      // [KVS_W_COUNT] device
+    int32_t *d_words;      // [KVS_W_ALLOCATED] device
     int32_t *h_words;      // [KVS_W_COUNT] pinned host mirror
+    int32_t *h_scan;       // [KVS_H_COUNT] pinned host memory the length scan writes to
+    int32_t scan_seq;      // number of the last scan that was asked to
     void *d_scratch;       // grows on demand
     size_t scratch_bytes;
     void *static_scratch;  // this device's address of the library's fixed working array (never freed)
@@ -122,8 +138,10 @@ constexpr int KVS_PROGRESS_WORDS = KVS_PROGRESS_COPIES * KVS_PROGRESS_STRIDE_WOR
 constexpr size_t KVS_STATE_MAX_WORDS = KVS_STATE_HEAD_WORDS + 225 * 64;
 
 // simulate.hip
+// (moves: the positions they touch are scanned along; host: pinned words that receive the results and then seq)
 int kvs_launch_scan_lengths(const int32_t *s, const int32_t *o, int32_t n, int32_t M, int32_t o_bound,
-                            int32_t *d_words, hipStream_t st);
+                            int32_t *d_words, hipStream_t st, const int32_t *moves = nullptr, int32_t K = 0,
+                            int32_t *host = nullptr, int32_t seq = 0);
 int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st);
 // timeline_reg.hip (decode lengths up to KVS_REG_MAX_O)
 constexpr int32_t KVS_REG_MAX_O = 14336;  // 224 rows of 64 rounds, and one more row for the window's offset
@@ -142,7 +160,8 @@ int kvs_launch_scatter_prefix(const int32_t *order, const int32_t *by_position, 
                               int32_t *completion_by_id, hipStream_t st);
 int kvs_launch_check_moves(const int32_t *moves, int32_t K, int32_t n, int64_t *tel_out, int32_t *d_words,
                            hipStream_t st);
-int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, hipStream_t st);
+int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, int32_t *d_words,
+                      hipStream_t st);
 
 // exactdp.hip
 size_t kvs_exact_dp_list_bytes(int32_t n);
@@ -208,7 +227,6 @@ int kvs_launch_predicted(const int32_t *orders, int32_t C, int32_t n, const int3
                          uint16_t *est_stopped /*[C][n] scratch*/, int32_t *d_words, hipStream_t st);
 
 // prefix.hip
-int kvs_launch_moves_min_position(const int32_t *moves, int32_t K, int32_t n, int32_t *d_words, hipStream_t st);
 int kvs_launch_check_prefix(const int32_t *orders, int32_t C, int32_t n, int32_t cp, int64_t *tel_out,
                             int32_t *d_words, hipStream_t st);
 int kvs_launch_broadcast_prefix(const int32_t *prefix, int32_t cp, int32_t C, int32_t n, int32_t *completion,

@@ -9,28 +9,6 @@
 
 namespace {
 
-// Smallest position touched by any well-formed move that changes the order.
-__global__ __launch_bounds__(256) void moves_min_position_kernel(const int32_t *moves, int32_t K, int32_t n,
-                                                                 int32_t *words)
-{
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    int pos = INT_MAX;
-    if (m < K) {
-        const int ty = moves[3 * (size_t)m], i = moves[3 * (size_t)m + 1], j = moves[3 * (size_t)m + 2];
-        const bool ok = (ty == KVSCHED_MOVE_SWAP || ty == KVSCHED_MOVE_INSERT) && i >= 0 && j >= 0 && i < n && j < n;
-        if (ok && i != j) pos = min(i, j);
-        if (!ok) pos = 0;  // malformed moves are clamped by the timeline kernel: no shared prefix
-    }
-    int top = -1;
-    if (m < K) top = min(max(max(moves[3 * (size_t)m + 1], moves[3 * (size_t)m + 2]), 0), n - 1);  // (as the timeline kernel clamps)
-    for (int d = 32; d > 0; d >>= 1) {
-        pos = min(pos, __shfl_down(pos, d));
-        top = max(top, __shfl_down(top, d));
-    }
-    if ((threadIdx.x & 63) == 0 && pos != INT_MAX) atomicMin(&words[KVS_W_MINPOS], pos);
-    if ((threadIdx.x & 63) == 0 && top >= 0) atomicMax(&words[KVS_W_MAXPOS], top);
-}
-
 __global__ __launch_bounds__(256) void mark_noop_moves_kernel(const int32_t *moves, int32_t K, int32_t n, int32_t first,
                                                               int32_t count, const int32_t *window_start,
                                                               const int32_t *prefix_state, int32_t *rejoin)
@@ -337,13 +315,6 @@ int kvs_launch_resume_plan(const int32_t *sorted, int32_t C, int32_t first, cons
 {
     hipLaunchKernelGGL(resume_plan_kernel, dim3((unsigned)((C + 255) / 256)), dim3(256), 0, st, sorted, C, first, blocks,
                        resume_pos_out);
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
-}
-
-int kvs_launch_moves_min_position(const int32_t *moves, int32_t K, int32_t n, int32_t *d_words, hipStream_t st)
-{
-    hipLaunchKernelGGL(moves_min_position_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, moves, K, n,
-                       d_words);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 

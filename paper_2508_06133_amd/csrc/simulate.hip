@@ -110,35 +110,72 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_kernel(SimParams p)
     if (lane == 0) p.tel_out[cand] = tel;
 }
 
-// One block: largest decode length and well-formedness of (s, o); resets the status word.
+// Largest decode length and well-formedness of (s, o), and the lowest and highest position that any of K moves
+// touches (malformed ones are clamped by the timeline kernel: they leave no shared prefix); resets the status word.
+// Bound by latency: one workgroup up to 4096 lengths and moves, then one per 4096 (at most 64; 100000 lengths: 41 us
+// by one workgroup, 5 us so), the last to finish writes the results.  A caller that waits for them (host, in pinned
+// memory) finds them there: the wait is one store across the bus instead of a copy and a stream synchronisation.
 __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, const int32_t *o, int32_t n, int32_t M,
-                                                            int32_t o_bound, int32_t *words)
+                                                            int32_t o_bound, const int32_t *moves, int32_t K,
+                                                            int32_t *words, int32_t *host, int32_t seq)
 {
-    __shared__ int sh_max[16];
-    __shared__ int sh_flag[16];
-    int mx = 0, flag = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    __shared__ int sh_max[16], sh_flag[16], sh_min[16], sh_top[16];
+    const int first = blockIdx.x * 1024 + threadIdx.x, stride = gridDim.x * 1024;
+    int mx = 0, flag = 0, lowest = INT_MAX, top = -1;
+    for (int i = first; i < n; i += stride) {
         const int sv = s[i], ov = o[i];
         mx = max(mx, ov);
         if (sv < 1 || ov < 1 || (long long)sv + (long long)ov > (long long)M) flag |= KVSCHED_DEV_BAD_LENGTH;
         if (o_bound > 0 && ov > o_bound) flag |= KVSCHED_DEV_O_MAX;
     }
+    for (int m = first; m < K; m += stride) {
+        const int ty = moves[3 * (size_t)m], i = moves[3 * (size_t)m + 1], j = moves[3 * (size_t)m + 2];
+        const bool ok = (ty == KVSCHED_MOVE_SWAP || ty == KVSCHED_MOVE_INSERT) && i >= 0 && j >= 0 && i < n && j < n;
+        if (!ok) lowest = 0;
+        else if (i != j) lowest = min(lowest, min(i, j));
+        top = max(top, min(max(max(i, j), 0), n - 1));  // (as the timeline kernel clamps)
+    }
     mx = wave_max_i32(mx);
     flag = wave_max_i32(flag & 1) | wave_max_i32(flag & KVSCHED_DEV_O_MAX);
+    lowest = ~wave_max_i32(~lowest);
+    top = wave_max_i32(top);
     if ((threadIdx.x & 63) == 0) {
         sh_max[threadIdx.x >> 6] = mx;
         sh_flag[threadIdx.x >> 6] = flag;
+        sh_min[threadIdx.x >> 6] = lowest;
+        sh_top[threadIdx.x >> 6] = top;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-            mx = max(mx, sh_max[w]);
-            flag |= sh_flag[w];
-        }
-        words[KVS_W_STATUS] = flag;
-        words[KVS_W_OMAX] = mx;
-        words[KVS_W_MINPOS] = INT_MAX;
-        words[KVS_W_MAXPOS] = -1;
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 16; ++w) {
+        mx = max(mx, sh_max[w]);
+        flag |= sh_flag[w];
+        lowest = min(lowest, sh_min[w]);
+        top = max(top, sh_top[w]);
+    }
+    if (gridDim.x > 1) {
+        atomicMax(&words[KVS_W_SCAN_OMAX], mx);
+        atomicOr(&words[KVS_W_SCAN_FLAGS], flag);
+        atomicMin(&words[KVS_W_SCAN_MINPOS], lowest);
+        atomicMax(&words[KVS_W_SCAN_MAXPOS], top);
+        device_writes_done();
+        if (atomicAdd(&words[KVS_W_SCAN_DONE], 1) != (int)gridDim.x - 1) return;
+        mx = atomicExch(&words[KVS_W_SCAN_OMAX], 0);
+        flag = atomicExch(&words[KVS_W_SCAN_FLAGS], 0);
+        lowest = atomicExch(&words[KVS_W_SCAN_MINPOS], INT_MAX);
+        top = atomicExch(&words[KVS_W_SCAN_MAXPOS], -1);
+        atomicExch(&words[KVS_W_SCAN_DONE], 0);
+    }
+    words[KVS_W_STATUS] = flag;
+    words[KVS_W_OMAX] = mx;
+    words[KVS_W_MINPOS] = lowest;
+    words[KVS_W_MAXPOS] = top;
+    if (host) {
+        host[KVS_H_OMAX] = mx;
+        host[KVS_H_MINPOS] = lowest;
+        host[KVS_H_MAXPOS] = top;
+        __threadfence_system();
+        __hip_atomic_store(&host[KVS_H_SEQ], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -211,58 +248,73 @@ __global__ __launch_bounds__(256) void check_moves_kernel(const int32_t *moves, 
     }
 }
 
-// One block: index of the least non-negative tel[0..K), lowest index among equals.  With
-// with_base, tel[K] is the base order's own latency and becomes the third result.  Fixed
-// reduction order, so the result is deterministic.
+// Index of the least non-negative tel[0..K), lowest index among equals.  With with_base, tel[K] is the base
+// order's own latency and becomes the third result.  (Least latency, then lowest index) is a total order: any
+// reduction tree gives the same winner.  One workgroup up to 4096 entries, then one per 2048 (at most
+// KVS_ARGMIN_GROUPS), the last to finish reduces the others' winners: 40321 entries 16 us by one, 4 us so.
 __global__ __launch_bounds__(1024) void argmin_kernel(const int64_t *tel, int32_t K, int64_t *result_out,
-                                                      int32_t with_base)
+                                                      int32_t with_base, int32_t *words)
 {
     __shared__ long long sh_tel[16];
     __shared__ int sh_idx[16];
+    __shared__ int sh_last;
     long long bt = -1;
     int bi = -1;
-    for (int m = threadIdx.x; m < K; m += blockDim.x) {
-        const long long v = tel[m];
-        if (v >= 0 && (bi < 0 || v < bt)) {  // m increases, so ties keep the lower index
-            bt = v;
-            bi = m;
-        }
-    }
-    // (least latency, then lowest index) is a total order: any reduction tree gives the same winner
     auto take = [&](long long ot, int oi) {
         if (oi >= 0 && (bi < 0 || ot < bt || (ot == bt && oi < bi))) {
             bt = ot;
             bi = oi;
         }
     };
-    for (int d = 32; d > 0; d >>= 1) {
-        const long long ot = __shfl_xor(bt, d);
-        const int oi = __shfl_xor(bi, d);
-        take(ot, oi);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        sh_tel[threadIdx.x >> 6] = bt;
-        sh_idx[threadIdx.x >> 6] = bi;
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        bt = threadIdx.x < 16 ? sh_tel[threadIdx.x] : -1;
-        bi = threadIdx.x < 16 ? sh_idx[threadIdx.x] : -1;
-        for (int d = 8; d > 0; d >>= 1) {
+    auto reduce = [&]() {  // over the workgroup, into thread 0
+        for (int d = 32; d > 0; d >>= 1) {
             const long long ot = __shfl_xor(bt, d);
             const int oi = __shfl_xor(bi, d);
             take(ot, oi);
         }
-        if (threadIdx.x == 0) {
-            sh_tel[0] = bt;
-            sh_idx[0] = bi;
+        if ((threadIdx.x & 63) == 0) {
+            sh_tel[threadIdx.x >> 6] = bt;
+            sh_idx[threadIdx.x >> 6] = bi;
         }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            bt = threadIdx.x < 16 ? sh_tel[threadIdx.x] : -1;
+            bi = threadIdx.x < 16 ? sh_idx[threadIdx.x] : -1;
+            for (int d = 8; d > 0; d >>= 1) {
+                const long long ot = __shfl_xor(bt, d);
+                const int oi = __shfl_xor(bi, d);
+                take(ot, oi);
+            }
+        }
+    };
+    for (int m = blockIdx.x * 1024 + threadIdx.x; m < K; m += gridDim.x * 1024) {
+        const long long v = tel[m];
+        if (v >= 0) take(v, m);
     }
-    __syncthreads();
+    reduce();
+    if (gridDim.x > 1) {
+        long long *part = (long long *)(words + KVS_W_ARGMIN_PART);
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(&part[2 * blockIdx.x], bt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&part[2 * blockIdx.x + 1], (long long)bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            device_writes_done();
+            sh_last = atomicAdd(&words[KVS_W_ARGMIN_DONE], 1) == (int)gridDim.x - 1;
+        }
+        __syncthreads();
+        if (!sh_last) return;
+        bt = bi = -1;
+        if (threadIdx.x < gridDim.x) {
+            const long long ot = __hip_atomic_load(&part[2 * threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            take(ot, (int)__hip_atomic_load(&part[2 * threadIdx.x + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
+        __syncthreads();
+        reduce();
+        if (threadIdx.x == 0) words[KVS_W_ARGMIN_DONE] = 0;
+    }
     if (threadIdx.x == 0) {
         const bool base_ok = !with_base || tel[K] >= 0;  // a faulty base order makes every neighbour faulty
-        result_out[0] = base_ok ? sh_idx[0] : -1;
-        result_out[1] = (base_ok && sh_idx[0] >= 0) ? sh_tel[0] : -1;
+        result_out[0] = base_ok ? bi : -1;
+        result_out[1] = (base_ok && bi >= 0) ? bt : -1;
         if (with_base) result_out[2] = tel[K];
     }
 }
@@ -281,9 +333,13 @@ int launch_timeline(const SimParams &p, hipStream_t st)
 }  // namespace
 
 int kvs_launch_scan_lengths(const int32_t *s, const int32_t *o, int32_t n, int32_t M, int32_t o_bound,
-                            int32_t *d_words, hipStream_t st)
+                            int32_t *d_words, hipStream_t st, const int32_t *moves, int32_t K, int32_t *host,
+                            int32_t seq)
 {
-    hipLaunchKernelGGL(scan_lengths_kernel, dim3(1), dim3(1024), 0, st, s, o, n, M, o_bound, d_words);
+    const int32_t most = moves && K > n ? K : n;
+    const unsigned blocks = most <= 4096 ? 1u : most < 64 * 4096 ? (unsigned)((most + 4095) / 4096) : 64u;
+    hipLaunchKernelGGL(scan_lengths_kernel, dim3(blocks), dim3(1024), 0, st, s, o, n, M, o_bound, moves, moves ? K : 0,
+                       d_words, host, seq);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
@@ -329,8 +385,10 @@ int kvs_launch_check_moves(const int32_t *moves, int32_t K, int32_t n, int64_t *
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
-int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, hipStream_t st)
+int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, int32_t *d_words,
+                      hipStream_t st)
 {
-    hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(1024), 0, st, tel, K, result_out, with_base);
+    const unsigned blocks = K <= 4096 ? 1u : K < KVS_ARGMIN_GROUPS * 2048 ? (unsigned)((K + 2047) / 2048) : (unsigned)KVS_ARGMIN_GROUPS;
+    hipLaunchKernelGGL(argmin_kernel, dim3(blocks), dim3(1024), 0, st, tel, K, result_out, with_base, d_words);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

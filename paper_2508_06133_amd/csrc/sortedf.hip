@@ -142,6 +142,7 @@ __device__ __forceinline__ int wave_profile_extent(const Sums &c, int a, int rem
     const u64 P0 = c.W[a] - c.S[a];
     unsigned acc[4];
     int sv[4], ov[4];
+    int sure = 0;
     int hi = 0;  // beyond: even the memory at the earliest completion, at least sum (s_i + 1), is too much
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -152,20 +153,26 @@ __device__ __forceinline__ int wave_profile_extent(const Sums &c, int a, int rem
         ov[q] = k <= rem ? c.o[a + kk - 1] : 0x7fffffff;
         acc[q] = 0;
         hi += __popcll(__builtin_amdgcn_ballot_w64(ok));
+        sure += __popcll(__builtin_amdgcn_ballot_w64(k <= rem && c.W[a + kk] - c.W[a] <= (u64)M));
     }
+    // (the first `sure` of them fit: their peaks do)
+    auto join = [&](int si, int oi) __attribute__((always_inline)) {
+        unsigned most = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc[r] += oi >= ov[r] ? (unsigned)si + (unsigned)ov[r] : 0u;
+            most = max(most, acc[r]);
+        }
+        return most;
+    };
     int K = -1;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int m = min(64, hi - 64 * q);
-        for (int l = 0; l < m; ++l) {
-            const int si = __builtin_amdgcn_readlane(sv[q], l);
-            const int oi = __builtin_amdgcn_readlane(ov[q], l);
-            unsigned most = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                acc[r] += oi >= ov[r] ? (unsigned)si + (unsigned)ov[r] : 0u;
-                most = max(most, acc[r]);
-            }
+        const int m = min(64, hi - 64 * q), free = min(m, sure - 64 * q);
+        int l = 0;
+        for (; l < free; ++l) (void)join(__builtin_amdgcn_readlane(sv[q], l), __builtin_amdgcn_readlane(ov[q], l));
+        for (; l < m; ++l) {
+            const unsigned most = join(__builtin_amdgcn_readlane(sv[q], l), __builtin_amdgcn_readlane(ov[q], l));
             if (__builtin_amdgcn_ballot_w64(most > M) != 0) {
                 K = 64 * q + l;
                 break;
@@ -327,7 +334,7 @@ __device__ __forceinline__ int batch_of_place(const int *ends, int nb, int place
 
 // Everything in one workgroup: n <= TPB * E requests, element 64 E wave + 64 e + lane of an order in k[e].
 // Also the length scan of the call (status word, longest decode).  What bounds it is latency, a chain of short
-// steps: 64 requests run without a barrier that waits for anyone (one wavefront), 2000 in @NS@.
+// steps: 61 requests 22 -> 7 us (one wavefront, no barrier waits for anyone), 200 30 -> 12 us, 2000 92 -> 56 us.
 template <int TPB, int E, bool PROFILE>
 __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
 {
@@ -601,6 +608,10 @@ struct LargeArrays {
     unsigned *hist;
 };
 
+// Are ranks in the (o, id) order needed?  By keys that do not fit, and by the profile test when the completion times
+// are too many for buckets in LDS (the host launches their sort whenever that could be).
+__device__ __forceinline__ bool ranks_needed(const SortedArgs &p) { return !p.packed || p.words[KVS_W_OMAX] > kLargeBuckets; }
+
 __device__ __forceinline__ bool faulty(const SortedArgs &p) { return (p.words[KVS_W_STATUS] & KVSCHED_DEV_BAD_LENGTH) != 0; }
 
 enum { KEYS_BY_O, KEYS_BY_SIZE, KEYS_BY_BATCH };
@@ -610,7 +621,7 @@ template <int WHAT>
 __global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArrays m, const u64 *by_place, u64 *out)
 {
     __shared__ u64 buf[2 * kRun];
-    if (faulty(p)) return;
+    if (faulty(p) || (WHAT == KEYS_BY_O && !ranks_needed(p))) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const u64 id_mask = field_mask(p.id_bits);
     const int nb = WHAT == KEYS_BY_BATCH ? *p.num_batches_out : 0;
@@ -647,9 +658,9 @@ __global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArra
 // order and its inverse.
 enum { MERGE_KEYS, MERGE_IDS, MERGE_RANKS };
 template <int EMIT>
-__global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArrays m, const u64 *in, u64 *out, int run)
+__global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArrays m, const u64 *in, u64 *out, int run, int of_ranks)
 {
-    if (faulty(p)) return;
+    if (faulty(p) || (of_ranks && !ranks_needed(p))) return;
     const int g = blockIdx.x * 256 + threadIdx.x, n = p.n;
     if (g >= n) return;
     const u64 key = in[g];
@@ -689,6 +700,7 @@ __global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArra
 __global__ __launch_bounds__(1024) void place_lengths_kernel(SortedArgs p, LargeArrays m, const u64 *sorted, int ranks)
 {
     if (faulty(p)) return;
+    ranks = ranks && ranks_needed(p);
     __shared__ u64 tw[16], tq[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const u64 id_mask = field_mask(p.id_bits);
@@ -783,7 +795,9 @@ __global__ __launch_bounds__(256) void next_batch_kernel(SortedArgs p, LargeArra
     u64 M = (u64)p.M;
     int k = 0;
     if constexpr (PROFILE) {
-        rem = wave_profile_extent(c, a, rem, (unsigned)M);
+        // (a sum of peaks that holds kNextMax requests or more is feasible: nothing to decide here)
+        if (rem >= kNextMax && c.W[a + kNextMax] - c.W[a] <= M) rem = -1;
+        else rem = wave_profile_extent(c, a, rem, (unsigned)M);
         M = ~0ull;
     }
     if (rem > 0) k = small ? wave_batch<true>(c, a, rem, M, p.tie_rule, true) : wave_batch<false>(c, a, rem, M, p.tie_rule, true);
@@ -901,8 +915,8 @@ const u64 *launch_merges(const SortedArgs &p, const LargeArrays &m, hipStream_t 
     int at = 0;
     for (long long run = kRun; run < p.n; run *= kFan) {
         const bool last = run * kFan >= p.n;
-        if (last) hipLaunchKernelGGL((merge_runs_kernel<EMIT>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run);
-        else hipLaunchKernelGGL((merge_runs_kernel<MERGE_KEYS>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run);
+        if (last) hipLaunchKernelGGL((merge_runs_kernel<EMIT>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS);
+        else hipLaunchKernelGGL((merge_runs_kernel<MERGE_KEYS>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS);
         at ^= 1;
     }
     return m.key[at];
