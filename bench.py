@@ -605,6 +605,9 @@ def bench_horizon(args, ctx, dev) -> int:
             self.ms.append(ctx.last_timeline_ms())
             return out
 
+        def horizon_completion(self, *a):
+            return ctx.horizon_completion(*a)
+
     p1_out = ctx.sortedF(s, o, M)
 
     def run(keep_tel=False, max_steps=None, timed=None, keep_completion=False):
@@ -641,8 +644,7 @@ def bench_horizon(args, ctx, dev) -> int:
     timelines = replans * (K + 2)  # the moves, the order as it stands, the chosen order again for its completion rounds
 
     # ---- accounting (outside the timed region).  Every candidate of a window repeats the order up to
-    # the first position a move touches: the library places that prefix once (windows behind position 64)
-    # or starts each move from the state saved at its 64-position block (first window).  Credited per
+    # the first position its move touches and starts from the state saved at its 64-position block.  Credited per
     # candidate: rounds waited through from its start point on + windows checked and updated for the
     # positions from there on, with the start rounds of the chosen timeline of that re-plan standing in
     # for the candidates' own (they differ inside the window only; 2 sum(o) dominates).
@@ -652,8 +654,8 @@ def bench_horizon(args, ctx, dev) -> int:
     waited = 0   # rounds that entered a window while its request waited
     window = 0   # rounds of the windows themselves: each inspected once and updated once
     hbm_bytes = 0
-    kept_prefix = 0
     stops_seen = []  # per re-plan: moves not placed to their end
+    placed_before = 0  # blocks the re-plan before left: the order as it stands goes on from there
     for rec in log:
         moves = workloads.window_moves(rng, K, rec["lo"], rec["hi"])
         touched = np.minimum(moves[:, 1], moves[:, 2])
@@ -662,17 +664,10 @@ def bench_horizon(args, ctx, dev) -> int:
         start = (rec["completion"].astype(np.int64) - o_h)[order]  # start rounds of the chosen order, by position
         cum = np.concatenate([[0], np.cumsum(o_h[order])])
         lowest = int(touched[~ident].min()) if (~ident).any() else n
-        if lowest >= 64:  # common prefix placed once, every candidate starts behind it
-            first = np.full(K + 1, lowest, dtype=np.int64)
-            # the prefix itself: continued from the state the step before left behind its own prefix
-            kept = kept_prefix if 64 <= kept_prefix <= lowest else 0
-            waited += int(start[lowest - 1] - (start[kept - 1] if kept > 0 else 0))
-            window += int(cum[lowest] - cum[kept])
-            kept_prefix = lowest
-        else:  # from the saved state of the move's block (identity moves: of the last block)
-            kept_prefix = 0
-            first = np.where(ident, (n - 1) // 64 * 64, touched // 64 * 64).astype(np.int64)
-            first = np.concatenate([first, [0]])  # the order as it stands runs from the start and saves the states
+        # from the saved state of the move's block (identity moves: of the last block)
+        first = np.where(ident, (n - 1) // 64 * 64, touched // 64 * 64).astype(np.int64)
+        first = np.concatenate([first, [placed_before]])
+        placed_before = min(rec["committed"], (n - 1) // 64 * 64) // 64 * 64
         t_first = np.where(first > 0, start[np.maximum(first - 1, 0)], 0)
         # a move whose timeline became the order's own again was placed up to there only, or not at all
         stop = np.maximum(np.concatenate([accounted.stops[len(stops_seen)], [n]]), first)
@@ -680,10 +675,11 @@ def bench_horizon(args, ctx, dev) -> int:
         t_end = np.where(stop < n, np.where(stop > first, start[np.maximum(stop - 1, 0)], t_first), start[-1])
         waited += int((t_end - t_first).sum())
         window += int((cum[stop] - cum[first]).sum())
-        # ... and the chosen order once more, from the common prefix's state on where there is one
-        chosen_first = lowest if lowest >= 64 else 0
-        waited += int(start[-1] - (start[chosen_first - 1] if chosen_first > 0 else 0))
-        window += int(cum[n] - cum[chosen_first])
+        # ... and the chosen order once more, from the block of the first position touched to the commit point
+        chosen_first, chosen_end = lowest // 64 * 64, max(rec["committed"], lowest // 64 * 64)
+        if chosen_end > chosen_first:
+            waited += int(start[chosen_end - 1] - (start[chosen_first - 1] if chosen_first > 0 else 0))
+            window += int(cum[chosen_end] - cum[chosen_first])
         hbm_bytes += 12 * K + 8 * (K + 1) + 12 * n
     kernel_ms_total = float(np.sum(timed.ms))
     launches = len(timed.ms)

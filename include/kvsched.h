@@ -379,17 +379,25 @@ int kvsched_best_neighbor_static(kvsched_ctx *ctx, const int32_t *base_order, in
  *   result_out      [6]    int64: {best move, its total latency, latency of the order before
  *                   the move, committed positions, requests completed by T, T}
  *
- * Between steps the context keeps the timeline state behind the positions that no move of the last
- * step touched (with copies of that part of the order and of s and o, in a buffer of its own of
- * about 16 n bytes + 60 KB): the next step places only what lies between there and its own moves.
+ * Without completion_out the new order's timeline is placed only as far as the commit point needs it
+ * (kvsched_horizon_completion() gives what it has).  Between steps the context keeps that timeline's states at every
+ * 64th position and its start rounds (with copies of the order and of s and o, in a buffer of its own of about 20 n bytes
+ * + a saved state of up to 58 KB per 64 positions): the next step's timelines start from them.
  * The copies are compared with `order`, s and o on the device at every step; when the caller has
- * changed any of them (or n, M, or moved the window back) the step starts from position 0 as if
+ * changed any of them (or n, M) the step starts from position 0 as if
  * nothing had been kept.  Results never depend on it.
  */
 int kvsched_horizon_step(kvsched_ctx *ctx, int32_t *order, int32_t n, const int32_t *moves, int32_t K,
                          const int32_t *s, const int32_t *o, int64_t M, int64_t completed_in,
                          int32_t complete_every, int64_t *tel_out, int32_t *completion_out,
                          int64_t *result_out, void *stream);
+
+/* Completion rounds, by request id, of the order the LAST kvsched_horizon_step call on this context chose, as far as it
+ * placed it: of every request when completion_out was given to it or when it committed all positions (result_out[3] == n),
+ * else of those started by its round T at least (entries of the others are left as they are).  order (as that call left
+ * it), n and o must be that call's.  EINVAL if no such call was made. */
+int kvsched_horizon_completion(kvsched_ctx *ctx, const int32_t *order, int32_t n, const int32_t *o, int32_t *completion_out,
+                               void *stream);
 
 /*
  * Scheduling under online arrivals (Section 6, "Heuristics under Online Arrival"; the policies of

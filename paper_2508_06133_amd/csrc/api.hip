@@ -130,7 +130,7 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
     if (min_position_out) *min_position_out = 0;
     if (ctx->o_max_bound > 0) {
         *o_bound_out = ctx->o_max_bound;
-        return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st);
+        return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st, moves, K);
     }
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;  // a captured scan has no result to wait for
     if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return KVSCHED_EHIP;
@@ -200,33 +200,32 @@ __global__ void kvs_fill_zero_i32(int32_t *dst, int32_t n)
 }
 size_t state_bytes() { return align256(sizeof(int32_t) * KVS_STATE_MAX_WORDS); }
 
-// The horizon step's own buffer (kept between steps): state | order copy | s copy | o copy | completion by position | flag.
-struct HorizonBuffers {
-    int32_t *state, *order, *s, *o, *comp_pos, *ok;
-};
-
-size_t horizon_row_bytes(int32_t n) { return align256(sizeof(int32_t) * (size_t)n); }
-
-HorizonBuffers horizon_buffers(kvsched_ctx *ctx, int32_t n)
+// The horizon step's own buffer (kept between steps).
+HorizonKept horizon_kept(kvsched_ctx *ctx, int32_t n)
 {
+    const size_t row = align256(sizeof(int32_t) * (size_t)n);
     char *b = (char *)ctx->d_horizon;
-    const size_t row = horizon_row_bytes(n);
-    HorizonBuffers h;
-    h.state = (int32_t *)b;
-    h.order = (int32_t *)(b + state_bytes());
-    h.s = (int32_t *)(b + state_bytes() + row);
-    h.o = (int32_t *)(b + state_bytes() + 2 * row);
-    h.comp_pos = (int32_t *)(b + state_bytes() + 3 * row);
-    h.ok = (int32_t *)(b + state_bytes() + 4 * row);
+    HorizonKept h;
+    h.ctrl = (int32_t *)b;
+    h.progress = h.ctrl + KVS_HZ_WORDS;
+    b += align256(sizeof(int32_t) * (KVS_HZ_WORDS + KVS_PROGRESS_WORDS));
+    h.order = (int32_t *)b;
+    h.s = (int32_t *)(b + row);
+    h.o = (int32_t *)(b + 2 * row);
+    h.start = (int32_t *)(b + 3 * row);
+    h.completion = (int32_t *)(b + 4 * row);
+    h.snapshots = (int32_t *)(b + 5 * row);
     return h;
 }
 
-// (growing it forgets what was kept)
-int ensure_horizon(kvsched_ctx *ctx, int32_t n)
+// Room for n positions with saved states of `stride` words; growing it forgets what was kept.
+int ensure_horizon(kvsched_ctx *ctx, int32_t n, int32_t stride)
 {
-    const size_t bytes = state_bytes() + 4 * horizon_row_bytes(n) + 256;
+    const size_t bytes = align256(sizeof(int32_t) * (KVS_HZ_WORDS + KVS_PROGRESS_WORDS)) +
+                         5 * align256(sizeof(int32_t) * (size_t)n) +
+                         sizeof(int32_t) * (size_t)((n - 1) / WAVE_POSITIONS) * (size_t)stride + 256;
     if (bytes <= ctx->horizon_bytes) return KVSCHED_OK;
-    ctx->hz_len = 0;
+    ctx->hz_kept = ctx->hz_completion = 0;
     if (ctx->d_horizon) {
         if (hipDeviceSynchronize() != hipSuccess) return KVSCHED_EHIP;
         (void)hipFree(ctx->d_horizon);
@@ -234,19 +233,15 @@ int ensure_horizon(kvsched_ctx *ctx, int32_t n)
         ctx->horizon_bytes = 0;
     }
     if (hipMalloc(&ctx->d_horizon, bytes) != hipSuccess) return KVSCHED_ENOMEM;
+    if (hipMemset(ctx->d_horizon, 0, sizeof(int32_t) * KVS_HZ_WORDS) != hipSuccess) return KVSCHED_EHIP;
     ctx->horizon_bytes = bytes;
     return KVSCHED_OK;
 }
 
-
 // Run positions [0, cp) of `row0` once and leave the timeline state in `state`;
 // completion rounds of those positions (position order) go to prefix_completion if not NULL.
-// prefix_completion: completion rounds of the prefix, by position (by_id = 0: an array of cp entries) or by
-// request id (by_id = 1: a row of n entries of which the prefix's requests are written), or null.
-// from_len > 0: state holds the timeline after the first from_len positions; they are skipped if *resume_ok != 0.
 int run_shared_prefix(const int32_t *row0, int32_t cp, int32_t n, const int32_t *s, const int32_t *o, int64_t M,
-                      int32_t o_bound, int32_t *d_words, int32_t *state, int32_t *prefix_completion, hipStream_t st,
-                      int by_id = 0, int32_t from_len = 0, const int32_t *resume_ok = nullptr)
+                      int32_t o_bound, int32_t *d_words, int32_t *state, int32_t *prefix_completion, hipStream_t st)
 {
     SimParams q;
     q.src.orders = row0;
@@ -259,17 +254,12 @@ int run_shared_prefix(const int32_t *row0, int32_t cp, int32_t n, const int32_t 
     q.M = (int32_t)M;
     q.tel_out = nullptr;
     q.completion_out = prefix_completion;
-    q.completion_by_position = by_id ? 0 : 1;
+    q.completion_by_position = 1;
     q.d_words = d_words;
     q.o_bound = o_bound;
     q.k_begin = 0;
     q.k_end = cp;
     q.state_out = state;
-    if (from_len > 0 && resume_ok) {
-        q.k_begin = from_len;
-        q.state_in = state;
-        q.resume_ok = resume_ok;
-    }
     return kvs_launch_simulate_reg(q, st);
 }
 
@@ -308,7 +298,7 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     ctx->tables_bytes = 0;
     ctx->d_horizon = nullptr;
     ctx->horizon_bytes = 0;
-    ctx->hz_n = ctx->hz_len = ctx->hz_o_bound = 0;
+    ctx->hz_kept = ctx->hz_n = ctx->hz_o_bound = ctx->hz_completion = 0;
     ctx->hz_M = 0;
     ctx->pad_outputs = 0;
     ctx->timing = 0;
@@ -391,7 +381,7 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
         if (pre > need) need = pre;
     }
     if (moves > 0) {
-        const size_t hor = neighbor_scratch_bytes(moves, n, ctx->o_max_bound) + 2 * row_bytes + 256;
+        const size_t hor = neighbor_scratch_bytes(moves, n, ctx->o_max_bound) + row_bytes + 256;
         if (hor > need) need = hor;
     }
     const int32_t keep = ctx->resume_rows;  // reserving is no call: the last resume plan stays readable unless the buffer moves
@@ -795,16 +785,9 @@ size_t neighbor_scratch_bytes(int32_t K, int32_t n, int32_t o_bound)
 // o_bound_known > 0: the caller's bound on the decode lengths; nothing is read back from the device
 // (so the lowest position the moves touch is not known either and no common prefix is placed ahead:
 // moves far into the order start from the base order's saved states instead).
-// For kvsched_horizon_step (keep != nullptr, with prefix_completion_by_id and prefix_len_out): when a common
-// prefix is placed ahead, its state is left in the horizon buffers, its requests' completion rounds go to
-// prefix_completion_by_id and its length is returned.  If the buffers hold the state of a shorter prefix from
-// the step before (ctx->hz_len positions, same n, M and decode bound), the prefix run starts there, provided the
-// order up to there and the lengths still equal the copies kept with it (compared on the device).
 static int best_neighbor_on(kvsched_ctx *ctx, void *work, int32_t o_bound_known, const int32_t *base_order, int32_t n,
                             const int32_t *moves, int32_t K, const int32_t *s, const int32_t *o, int64_t M,
-                            int64_t *tel_out, int64_t *result_out, hipStream_t st,
-                            const HorizonBuffers *keep = nullptr, int32_t *prefix_completion_by_id = nullptr,
-                            int32_t *prefix_len_out = nullptr)
+                            int64_t *tel_out, int64_t *result_out, hipStream_t st)
 {
     // work: [K+1] latencies (neighbours, then the base order) | state of the shared prefix | resume plan
     const size_t tel_bytes = align256(sizeof(int64_t) * ((size_t)K + 1));
@@ -844,28 +827,10 @@ static int best_neighbor_on(kvsched_ctx *ctx, void *work, int32_t o_bound_known,
     // No move touches a position before min_pos: that prefix of the base order is common to
     // every neighbour, so it is placed once and all timelines resume from its state.
     if (min_pos >= kMinSharedPrefix && o_bound <= KVS_REG_MAX_O) {
-        if (keep) {
-            int32_t from = 0;
-            if (ctx->hz_len >= kMinSharedPrefix && ctx->hz_len <= min_pos && ctx->hz_n == n && ctx->hz_M == M &&
-                ctx->hz_o_bound == o_bound)
-                from = ctx->hz_len;
-            ctx->hz_len = 0;  // (until this step has left its own)
-            rc = kvs_launch_horizon_verify(base_order, s, o, n, from, min_pos, keep->order, keep->s, keep->o, keep->ok, st);
-            if (rc != KVSCHED_OK) return rc;
-            state = keep->state;
-            rc = run_shared_prefix(base_order, min_pos, n, s, o, M, o_bound, ctx->d_words, state, keep->comp_pos, st, 0,
-                                   from, keep->ok);
-            if (rc != KVSCHED_OK) return rc;
-            rc = kvs_launch_scatter_prefix(base_order, keep->comp_pos, min_pos, n, prefix_completion_by_id, st);
-            if (rc != KVSCHED_OK) return rc;
-            ctx->hz_len = min_pos, ctx->hz_n = n, ctx->hz_M = M, ctx->hz_o_bound = o_bound;
-        } else {
-            rc = run_shared_prefix(base_order, min_pos, n, s, o, M, o_bound, ctx->d_words, state, nullptr, st);
-            if (rc != KVSCHED_OK) return rc;
-        }
+        rc = run_shared_prefix(base_order, min_pos, n, s, o, M, o_bound, ctx->d_words, state, nullptr, st);
+        if (rc != KVSCHED_OK) return rc;
         p.k_begin = min_pos;
         p.state_in = state;
-        if (prefix_len_out) *prefix_len_out = min_pos;
         // A move that only reorders requests the base order starts in one and the same round changes no
         // completion round (see the timeline kernel): the base order is placed once more, alone, through the last
         // position any move touches, and the moves found to be of that kind are not run at all.
@@ -886,8 +851,6 @@ static int best_neighbor_on(kvsched_ctx *ctx, void *work, int32_t o_bound_known,
             p.skip = rejoin_block;
             stops_early = true;
         }
-    } else if (keep) {
-        ctx->hz_len = 0;
     }
     if (!p.state_in && ctx->resume_wait_polls > 0 && resume_pays(ctx, K + 1, n, o_bound)) {
         // Moves anywhere in the order (no prefix common to all): a move at positions i, j leaves the
@@ -929,24 +892,56 @@ static int best_neighbor_on(kvsched_ctx *ctx, void *work, int32_t o_bound_known,
         rc = run_timelines(ctx, p, H, st);
     }
     if (rc != KVSCHED_OK) return rc;
-    if (stops_early) {
-        rc = kvs_launch_rejoin_finish(rejoin_block, K + 1, K, tel, st);
-        if (rc != KVSCHED_OK) return rc;
-        if (work == ctx->d_scratch) {
-            ctx->neighbor_stop_offset = (size_t)((char *)rejoin_block - (char *)work);
-            ctx->neighbor_moves = K;
-        }
+    if (stops_early && work == ctx->d_scratch) {
+        ctx->neighbor_stop_offset = (size_t)((char *)rejoin_block - (char *)work);
+        ctx->neighbor_moves = K;
     }
-    rc = kvs_launch_check_moves(moves, K, n, tel, ctx->d_words, st);
-    if (rc != KVSCHED_OK) return rc;
     rc = kvs_launch_check_orders(base_order, 1, n, tel + K, ctx->d_words, st);
     if (rc != KVSCHED_OK) return rc;
-    rc = kvs_launch_argmin(tel, K, result_out, 1, ctx->d_words, st);
+    return kvs_launch_neighbor_finish(tel, stops_early ? rejoin_block : nullptr, moves, K, n, tel_out, result_out,
+                                      ctx->d_words, st);
+}
+
+// A horizon step without saved states: best neighbour, the move, the chosen timeline from its first position, commit point.
+static int horizon_step_plain(kvsched_ctx *ctx, int32_t *order, int32_t n, const int32_t *moves, int32_t K, const int32_t *s,
+                              const int32_t *o, int64_t M, int64_t completed_in, int32_t complete_every, int64_t *tel_out,
+                              int32_t *completion_out, int64_t *result_out, hipStream_t st)
+{
+    char *base = (char *)ctx->d_scratch;
+    const size_t tel_bytes = neighbor_scratch_bytes(K, n, ctx->o_max_bound);
+    int32_t *new_order = (int32_t *)(base + tel_bytes);
+    int64_t *tel1 = (int64_t *)(base + tel_bytes + align256(sizeof(int32_t) * (size_t)n));
+    int32_t *comp = completion_out ? completion_out : horizon_kept(ctx, n).completion;
+    int rc = best_neighbor_on(ctx, ctx->d_scratch, ctx->o_max_bound, order, n, moves, K, s, o, M, tel_out, result_out, st);
     if (rc != KVSCHED_OK) return rc;
-    if (tel_out &&
-        hipMemcpyAsync(tel_out, tel, sizeof(int64_t) * (size_t)K, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return KVSCHED_EHIP;
-    return KVSCHED_OK;
+    rc = kvs_launch_apply_best_move(order, n, moves, result_out, new_order, st);
+    if (rc != KVSCHED_OK) return rc;
+    hipLaunchKernelGGL(kvs_copy_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, order, new_order, n);
+    if (hipGetLastError() != hipSuccess) return KVSCHED_EHIP;
+    const int32_t o_bound = ctx->o_max_bound > 0 ? ctx->o_max_bound
+                                                 : (ctx->h_scan[KVS_H_OMAX] < 1 ? 1 : ctx->h_scan[KVS_H_OMAX]);
+    SimParams p;
+    p.src.orders = order;
+    p.src.base = nullptr;
+    p.src.moves = nullptr;
+    p.C = 1;
+    p.n = n;
+    p.s = s;
+    p.o = o;
+    p.M = (int32_t)M;
+    p.tel_out = tel1;
+    p.completion_out = comp;
+    p.completion_by_position = 0;
+    p.d_words = ctx->d_words;
+    p.o_bound = o_bound;
+    rc = p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st)
+                                    : kvs_launch_simulate(p, ring_slots_for(o_bound), st);
+    if (rc != KVSCHED_OK) return rc;
+    if (!completion_out) {
+        ctx->hz_completion = 2;
+        ctx->hz_n = n;
+    }
+    return kvs_launch_horizon_advance_by_id(order, comp, o, n, completed_in, complete_every, result_out + 3, st);
 }
 
 int kvsched_best_neighbor(kvsched_ctx *ctx, const int32_t *base_order, int32_t n, const int32_t *moves, int32_t K,
@@ -988,57 +983,140 @@ int kvsched_horizon_step(kvsched_ctx *ctx, int32_t *order, int32_t n, const int3
     if (!order || !moves || !result_out || completed_in < 0 || complete_every < 1) return KVSCHED_EINVAL;
     if (K < 1 || K == INT32_MAX) return KVSCHED_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    // scratch: [K+1] latencies of best_neighbor | new order [n] | completion rounds [n] | one latency
-    const size_t tel_bytes = neighbor_scratch_bytes(K, n, ctx->o_max_bound);  // best_neighbor's part
+    ctx->hz_completion = 0;
+    // scratch: [K+1] latencies of best_neighbor and its plan | new order [n] | one latency
+    const size_t tel_bytes = neighbor_scratch_bytes(K, n, ctx->o_max_bound);
     const size_t row_bytes = align256(sizeof(int32_t) * (size_t)n);
-    rc = ensure_scratch(ctx, tel_bytes + 2 * row_bytes + 256);
+    rc = ensure_scratch(ctx, tel_bytes + row_bytes + 256);
     if (rc != KVSCHED_OK) return rc;
     char *base = (char *)ctx->d_scratch;
-    int32_t *new_order = (int32_t *)(base + tel_bytes);
-    int32_t *comp = completion_out ? completion_out : (int32_t *)(base + tel_bytes + row_bytes);
-    int64_t *tel1 = (int64_t *)(base + tel_bytes + 2 * row_bytes);
-    // 1. best move of the window (result_out[0..2]).  When the positions before the window are placed once for
-    //    all moves, their completion rounds are kept and the state behind them serves the chosen order too.
-    rc = ensure_horizon(ctx, n);
-    if (rc != KVSCHED_OK) return rc;
-    const HorizonBuffers keep = horizon_buffers(ctx, n);
-    int32_t prefix_len = 0;
-    rc = best_neighbor_on(ctx, ctx->d_scratch, ctx->o_max_bound, order, n, moves, K, s, o, M, tel_out, result_out, st,
-                          &keep, comp, &prefix_len);
-    if (rc != KVSCHED_OK) {
-        ctx->hz_len = 0;
-        return rc;
+    int32_t o_bound = ctx->o_max_bound;
+    const bool states_wanted = n > 2 * WAVE_POSITIONS && ctx->resume_wait_polls > 0 && ctx->resume_min_rows != 0;
+    if (!(states_wanted && o_bound <= KVS_REG_MAX_O)) {  // short orders, and where saved states are ruled out: step by step
+        ctx->hz_kept = 0;
+        rc = ensure_horizon(ctx, n, 0);
+        if (rc != KVSCHED_OK) return rc;
+        return horizon_step_plain(ctx, order, n, moves, K, s, o, M, completed_in, complete_every, tel_out, completion_out,
+                                  result_out, st);
     }
-    // 2. take it
-    rc = kvs_launch_apply_best_move(order, n, moves, result_out, new_order, st);
+    rc = scan_and_bound(ctx, s, o, n, M, st, &o_bound, moves, K);
     if (rc != KVSCHED_OK) return rc;
-    if (hipMemcpyAsync(order, new_order, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return KVSCHED_EHIP;
-    // 3. the chosen timeline, 4. how far it gets
-    const int32_t o_bound = ctx->o_max_bound > 0 ? ctx->o_max_bound
-                                                 : (ctx->h_scan[KVS_H_OMAX] < 1 ? 1 : ctx->h_scan[KVS_H_OMAX]);
+    if ((int64_t)n * (int64_t)ring_slots_for(o_bound) >= kMaxM) return KVSCHED_ERANGE;
+    if (o_bound > KVS_REG_MAX_O) {
+        ctx->hz_kept = 0;
+        rc = ensure_horizon(ctx, n, 0);
+        if (rc != KVSCHED_OK) return rc;
+        return horizon_step_plain(ctx, order, n, moves, K, s, o, M, completed_in, complete_every, tel_out, completion_out,
+                                  result_out, st);
+    }
+    const int32_t stride = kvs_reg_state_words(o_bound), nblk = (n - 1) / WAVE_POSITIONS, C = K + 1;
+    rc = ensure_horizon(ctx, n, stride);
+    if (rc != KVSCHED_OK) return rc;
+    const HorizonKept h = horizon_kept(ctx, n);
+    // (a state holds the largest file's words or fewer: kept ones are of use only to the same file)
+    const int32_t kept = ctx->hz_kept && ctx->hz_n == n && ctx->hz_M == M && kvs_reg_state_words(ctx->hz_o_bound) == stride;
+    ctx->hz_kept = 0;  // (until this step has left its own)
+    // 1. the candidates.  Each starts from the state saved at the last 64-position boundary before what its move
+    //    touches: left there by the step before as far as that placed its order, and beyond by the wave that runs the
+    //    order as it stands, in the same launch.
+    const size_t list_bytes = align256(sizeof(int32_t) * (size_t)C);
+    int64_t *tel = (int64_t *)base;
+    char *lists = base + align256(sizeof(int64_t) * (size_t)C) + state_bytes();
+    int32_t *rejoin_block = (int32_t *)lists;
+    int32_t *blocks = (int32_t *)(lists + list_bytes + row_bytes);
+    int32_t *sorted = (int32_t *)(lists + 2 * list_bytes + row_bytes);
+    int32_t *tmp = (int32_t *)(lists + 3 * list_bytes + row_bytes);
+    rc = kvs_launch_horizon_begin(h, kept, order, s, o, n, moves, K, blocks, st);
+    if (rc != KVSCHED_OK) return rc;
+    rc = kvs_launch_sort_by_blocks(blocks, C, K, tmp, sorted, nullptr, 0, st);
+    if (rc != KVSCHED_OK) return rc;
     SimParams p;
-    p.src.orders = order;
-    p.src.base = nullptr;
-    p.src.moves = nullptr;
-    p.C = 1;
+    p.src.orders = nullptr;
+    p.src.base = order;
+    p.src.moves = moves;
+    p.C = C;
     p.n = n;
     p.s = s;
     p.o = o;
     p.M = (int32_t)M;
-    p.tel_out = tel1;
-    p.completion_out = comp;
+    p.tel_out = tel;
+    p.completion_out = nullptr;
     p.completion_by_position = 0;
     p.d_words = ctx->d_words;
     p.o_bound = o_bound;
-    if (prefix_len > 0) {  // (only with the register kernel) no move touches these positions: the new order shares them
-        p.k_begin = prefix_len;
-        p.state_in = keep.state;
-    }
-    rc = p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st)
-                                    : kvs_launch_simulate(p, ring_slots_for(o_bound), st);
+    p.cand_list = sorted;
+    p.resume_block = blocks;
+    p.snapshots = h.snapshots;
+    p.snap_stride = stride;
+    p.snap_blocks = nblk;
+    p.snap_flags = h.progress;
+    p.snap_wait_polls = ctx->resume_wait_polls;
+    p.snap_cand = K;
+    p.snap_start = h.ctrl + KVS_HZ_AVAIL;
+    p.rejoin_block = rejoin_block;
+    p.start0 = h.start;
+    p.rejoin_blocks = nblk;
+    if (ctx->timing && hipEventRecord(ctx->ev0, st) != hipSuccess) return KVSCHED_EHIP;
+    rc = kvs_launch_simulate_reg(p, st);
     if (rc != KVSCHED_OK) return rc;
-    return kvs_launch_horizon_advance(order, comp, o, n, completed_in, complete_every, result_out + 3, st);
+    if (ctx->timing) {
+        if (hipEventRecord(ctx->ev1, st) != hipSuccess) return KVSCHED_EHIP;
+        ctx->timed = 1;
+    }
+    ctx->neighbor_stop_offset = (size_t)((char *)rejoin_block - base);
+    ctx->neighbor_moves = K;
+    rc = kvs_launch_check_orders(order, 1, n, tel + K, ctx->d_words, st);
+    if (rc != KVSCHED_OK) return rc;
+    rc = kvs_launch_neighbor_finish(tel, rejoin_block, moves, K, n, tel_out, result_out, ctx->d_words, st);
+    if (rc != KVSCHED_OK) return rc;
+    // 2. the best move is taken; 3. the new order's timeline, from the first block that changed, to its end if its
+    //    completion rounds are asked for, else until the commit point is behind it; 4. the commit point
+    rc = kvs_launch_horizon_choose(h, order, n, moves, result_out, ctx->d_words, stride, completed_in, complete_every,
+                                   completion_out ? 1 : 0, st);
+    if (rc != KVSCHED_OK) return rc;
+    SimParams q;
+    q.src.orders = order;
+    q.src.base = nullptr;
+    q.src.moves = nullptr;
+    q.C = 1;
+    q.n = n;
+    q.s = s;
+    q.o = o;
+    q.M = (int32_t)M;
+    q.tel_out = nullptr;
+    q.completion_out = nullptr;
+    q.completion_by_position = 0;
+    q.d_words = ctx->d_words;
+    q.o_bound = o_bound;
+    q.cand_list = h.ctrl + KVS_HZ_ZERO;
+    q.snapshots = h.snapshots;
+    q.snap_stride = stride;
+    q.snap_blocks = nblk;
+    q.snap_start = h.ctrl + KVS_HZ_FIRST;
+    q.t_limit = h.ctrl + KVS_HZ_LIMIT;
+    q.placed_out = h.ctrl + KVS_HZ_PLACED;
+    q.start0 = h.start;
+    rc = kvs_launch_simulate_reg(q, st);
+    if (rc != KVSCHED_OK) return rc;
+    rc = kvs_launch_horizon_advance(h, order, n, nblk, completed_in, complete_every, completion_out, result_out + 3, st);
+    if (rc != KVSCHED_OK) return rc;
+    ctx->hz_kept = ctx->hz_completion = 1;
+    ctx->hz_n = n;
+    ctx->hz_M = M;
+    ctx->hz_o_bound = o_bound;
+    return KVSCHED_OK;
+}
+
+int kvsched_horizon_completion(kvsched_ctx *ctx, const int32_t *order, int32_t n, const int32_t *o, int32_t *completion_out,
+                               void *stream)
+{
+    if (!ctx || !order || !o || !completion_out || n < 1 || !ctx->hz_completion || ctx->hz_n != n) return KVSCHED_EINVAL;
+    if (hipSetDevice(ctx->device) != hipSuccess) return KVSCHED_EHIP;
+    const HorizonKept h = horizon_kept(ctx, n);
+    if (ctx->hz_completion == 1) return kvs_launch_horizon_completion(h, order, o, n, completion_out, (hipStream_t)stream);
+    hipLaunchKernelGGL(kvs_copy_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, completion_out,
+                       h.completion, n);
+    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
 int kvsched_online(kvsched_ctx *ctx, int32_t B, const int32_t *streams, int32_t N, const int32_t *a,
@@ -1143,7 +1221,7 @@ int kvsched_argmin(kvsched_ctx *ctx, const int64_t *tel, int32_t C, int64_t *res
 {
     if (!ctx || !tel || !result_out || C < 1) return KVSCHED_EINVAL;
     if (hipSetDevice(ctx->device) != hipSuccess) return KVSCHED_EHIP;
-    return kvs_launch_argmin(tel, C, result_out, 0, ctx->d_words, (hipStream_t)stream);
+    return kvs_launch_argmin(tel, C, result_out, ctx->d_words, (hipStream_t)stream);
 }
 
 }  // extern "C"

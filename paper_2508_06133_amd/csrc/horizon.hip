@@ -3,8 +3,23 @@
 // order, commit what the timeline admits, plan again).  All requests are present at round 0;
 // the committed part of the order is the prefix of positions already admitted.
 #include "kvsched_internal.h"
+#include "device_util.h"
+
+#include <limits.h>
 
 namespace {
+
+// position k of the order with move (ty, i, j) applied = position moved_from(...) of the order before
+__device__ __forceinline__ int moved_from(int k, int ty, int i, int j)
+{
+    if (ty == KVSCHED_MOVE_SWAP) return k == i ? j : (k == j ? i : k);
+    if (i < j) {
+        if (k >= i && k <= j) return k == j ? i : k + 1;
+    } else {
+        if (k >= j && k <= i) return k == j ? i : k - 1;
+    }
+    return k;
+}
 
 // order_out = order with move moves[result[0]] applied (result[0] < 0: unchanged).
 __global__ __launch_bounds__(256) void apply_best_move_kernel(const int32_t *order, int32_t n, const int32_t *moves,
@@ -14,112 +29,215 @@ __global__ __launch_bounds__(256) void apply_best_move_kernel(const int32_t *ord
     if (k >= n) return;
     const long long best = result[0];
     int pos = k;
-    if (best >= 0) {
-        const int ty = moves[3 * best];
-        const int i = min(max(moves[3 * best + 1], 0), n - 1);
-        const int j = min(max(moves[3 * best + 2], 0), n - 1);
-        if (ty == KVSCHED_MOVE_SWAP) {
-            pos = (k == i) ? j : ((k == j) ? i : k);
-        } else if (i < j) {
-            if (k >= i && k <= j) pos = (k == j) ? i : k + 1;
-        } else {
-            if (k >= j && k <= i) pos = (k == j) ? i : k - 1;
-        }
-    }
+    if (best >= 0)
+        pos = moved_from(k, moves[3 * best], min(max(moves[3 * best + 1], 0), n - 1), min(max(moves[3 * best + 2], 0), n - 1));
     order_out[k] = order[pos];
 }
 
-// One block.  T = round by which min(n, completed_in + complete_every) requests have
-// completed (the k-th smallest completion round); result = {positions admitted by T (they form
-// a prefix of the order, start rounds being nondecreasing along it), requests completed by
-// T, T}.
-__global__ __launch_bounds__(1024) void horizon_advance_kernel(const int32_t *order, const int32_t *completion,
-                                                              const int32_t *o, int32_t n, long long completed_in,
-                                                              int32_t complete_every, int64_t *result_out)
-{
-    __shared__ int sh_cnt;
-    __shared__ int sh_max;
-    const int tid = threadIdx.x;
-    if (tid == 0) sh_max = 0;
-    __syncthreads();
-    int mx = 0;
-    for (int i = tid; i < n; i += blockDim.x) mx = max(mx, completion[i]);
-    atomicMax(&sh_max, mx);
-    __syncthreads();
-    long long kk = completed_in + complete_every;
-    if (kk > n) kk = n;
-    if (kk < 1) kk = 1;
-    const int k = (int)kk;
-    int lo = 0, hi = sh_max;  // smallest T in [lo, hi] with #{c <= T} >= k
-    while (lo < hi) {
-        const int mid = lo + ((hi - lo) >> 1);
-        if (tid == 0) sh_cnt = 0;
-        __syncthreads();
+// The values of a workgroup of 1024 that order statistics are taken of: HELD of them per thread stay in registers
+// (16384 in all), any beyond are fetched again at every turn.
+constexpr int HELD = 16;
+template <class F>
+struct Values {
+    F at;
+    int count;
+    int held[HELD];
+    int *sum;  // one word of LDS, and the turn's parity
+    int turn;
+
+    __device__ __forceinline__ Values(F f, int n, int *lds) : at(f), count(n), sum(lds), turn(0)
+    {
+#pragma unroll
+        for (int e = 0; e < HELD; ++e) {
+            const int k = threadIdx.x + 1024 * e;
+            held[e] = k < count ? at(k) : INT_MAX;
+        }
+    }
+
+    // how many values are <= v (every thread receives it; v < INT_MAX)
+    __device__ __forceinline__ int up_to(int v)
+    {
         int c = 0;
-        for (int i = tid; i < n; i += blockDim.x) c += completion[i] <= mid;
-        atomicAdd(&sh_cnt, c);
+#pragma unroll
+        for (int e = 0; e < HELD; ++e) c += held[e] <= v;
+        for (int k = threadIdx.x + 1024 * HELD; k < count; k += 1024) c += at(k) <= v;
+        for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+        turn = (turn + 1) % 3;  // (the word of the turn after next is cleared behind this turn's barrier)
+        if ((threadIdx.x & 63) == 0) atomicAdd(&sum[turn], c);
         __syncthreads();
-        const int total = sh_cnt;
+        if (threadIdx.x == 0) sum[(turn + 2) % 3] = 0;
+        return sum[turn];
+    }
+
+    // the k-th smallest, 1 <= k <= count; values lie in [0, 2^30)
+    __device__ __forceinline__ int kth(int k)
+    {
+        int mx = 0;
+#pragma unroll
+        for (int e = 0; e < HELD; ++e)
+            if (held[e] != INT_MAX) mx = max(mx, held[e]);
+        for (int q = threadIdx.x + 1024 * HELD; q < count; q += 1024) mx = max(mx, at(q));
+        mx = wave_max_i32(mx);
         __syncthreads();
-        if (total >= k) hi = mid; else lo = mid + 1;
+        if ((threadIdx.x & 63) == 0) atomicMax(&sum[3], mx);
+        __syncthreads();
+        int lo = 0, hi = sum[3];
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (up_to(mid) >= k) hi = mid;
+            else lo = mid + 1;
+        }
+        return lo;
     }
-    const int T = lo;
-    if (tid == 0) sh_cnt = 0;
-    __syncthreads();
-    int done = 0, admitted = 0;
-    for (int i = tid; i < n; i += blockDim.x) {
-        done += completion[i] <= T;
-        const int r = order[i];
-        admitted += (completion[r] - o[r]) <= T;
+};
+
+// Is what the context keeps still true?  Several workgroups, the last to finish draws the conclusion.
+__global__ __launch_bounds__(256) void horizon_begin_kernel(HorizonKept h, int32_t kept, const int32_t *order,
+                                                            const int32_t *s, const int32_t *o, int32_t n,
+                                                            const int32_t *moves, int32_t K, int32_t *blocks)
+{
+    const int first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+    const int avail = kept ? h.ctrl[KVS_HZ_AVAIL] : 0;
+    int bad = !kept;
+    for (int i = first; i < n; i += stride) {
+        const int sv = s[i], ov = o[i], id = order[i];
+        if (kept) bad |= (sv != h.s[i]) | (ov != h.o[i]) | (i < 64 * avail && id != h.order[i]);
+        h.s[i] = sv;
+        h.o[i] = ov;
+        h.order[i] = id;
     }
-    atomicAdd(&sh_cnt, done);
+    const int cap = (n - 1) >> 6;
+    for (int m = first; m <= K; m += stride) {  // (as move_blocks_kernel)
+        int nb = 0;
+        if (m < K) {
+            const int ty = moves[3 * (size_t)m], i = moves[3 * (size_t)m + 1], j = moves[3 * (size_t)m + 2];
+            const bool ok = (ty == KVSCHED_MOVE_SWAP || ty == KVSCHED_MOVE_INSERT) && i >= 0 && j >= 0 && i < n && j < n;
+            if (ok) nb = i == j ? cap : min(min(i, j) >> 6, cap);
+        }
+        blocks[m] = nb;
+    }
+    const bool any = __syncthreads_or(bad) != 0;
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        if (any) atomicOr(&h.ctrl[KVS_HZ_BAD], 1);
+        device_writes_done();
+        last = atomicAdd(&h.ctrl[KVS_HZ_DONE], 1) == (int)gridDim.x - 1;
+    }
     __syncthreads();
-    const int done_all = sh_cnt;
+    if (!last) return;
+    __shared__ int valid;
+    if (threadIdx.x == 0) {
+        valid = atomicExch(&h.ctrl[KVS_HZ_BAD], 0) ? 0 : avail;
+        atomicExch(&h.ctrl[KVS_HZ_DONE], 0);
+        h.ctrl[KVS_HZ_AVAIL] = valid;
+        h.ctrl[KVS_HZ_ZERO] = 0;
+    }
     __syncthreads();
-    if (tid == 0) sh_cnt = 0;
+    for (int i = threadIdx.x; i < KVS_PROGRESS_COPIES; i += 256) h.progress[KVS_PROGRESS_STRIDE_WORDS * i] = valid;
+}
+
+// One workgroup.  The move is applied to the order (and its copy).  The new order's timeline is wanted up to the round
+// by which k = completed_in + complete_every requests have completed.  The positions before the block of the first
+// one any move touches are placed already: the k-th smallest completion among them bounds that round from above, and every position behind starts no
+// earlier than the ones before it; so the timeline may stop once its round has passed that bound.
+__global__ __launch_bounds__(1024) void horizon_choose_kernel(HorizonKept h, int32_t *order, int32_t n, const int32_t *moves,
+                                                              const int64_t *result, const int32_t *words, int32_t stride,
+                                                              long long completed_in, int32_t complete_every, int32_t full)
+{
+    __shared__ int lds[4];
+    if (threadIdx.x < 4) lds[threadIdx.x] = 0;
+    const int first_block = min(max(words[KVS_W_MINPOS], 0) >> 6, (n - 1) >> 6);  // no move touches what lies before
+    const long long best = result[0];
+    if (best >= 0) {
+        const int ty = moves[3 * best];
+        const int i = min(max(moves[3 * best + 1], 0), n - 1), j = min(max(moves[3 * best + 2], 0), n - 1);
+        const int lo = min(i, j), hi = max(i, j);
+        for (int k = lo + threadIdx.x; k <= hi; k += 1024) order[k] = h.order[moved_from(k, ty, i, j)];
+        __syncthreads();
+        for (int k = lo + threadIdx.x; k <= hi; k += 1024) h.order[k] = order[k];
+    }
     __syncthreads();
-    atomicAdd(&sh_cnt, admitted);
+    const int placed = 64 * first_block;
+    const long long k = min(completed_in + complete_every, (long long)n);
+    int limit = INT_MAX;
+    if (!full && k <= placed && best >= 0) {  // (uniform)
+        auto completion = [&](int p) { return h.start[p] + h.o[min(max(h.order[p], 0), n - 1)]; };
+        Values<decltype(completion)> c(completion, placed, lds);
+        limit = c.kth((int)max(k, 1ll));
+    }
+    if (threadIdx.x == 0) {
+        h.ctrl[KVS_HZ_FIRST] = first_block;
+        h.ctrl[KVS_HZ_LIMIT] = limit;
+        h.ctrl[KVS_HZ_PLACED] = 0;
+        // no valid candidate: the states may be missing; the timeline then ends where it would start
+        if (best < 0 && first_block > 0) h.snapshots[(size_t)(first_block - 1) * (size_t)stride + 1] = -1;
+    }
+}
+
+// One workgroup.  T = round by which min(n, completed_in + complete_every) requests have completed (the k-th smallest
+// completion round); result = {positions admitted by T (they form a prefix of the order, start rounds being
+// nondecreasing along it), requests completed by T, T}.
+template <class START, class COMPLETION>
+__device__ __forceinline__ void commit_point(int n, int placed, START start, COMPLETION completion, long long completed_in,
+                                             int complete_every, int64_t *result_out, int *lds)
+{
+    const int k = (int)max(min(min(completed_in + complete_every, (long long)n), (long long)placed), 1ll);
+    int T = 0, done = 0;
+    if (placed > 0) {
+        Values<COMPLETION> c(completion, placed, lds);
+        T = c.kth(k);
+        done = c.up_to(T);
+    }
+    int admitted = 0;
+    for (int q = threadIdx.x; q < placed; q += 1024) admitted += start(q) <= T;
+    for (int d = 32; d > 0; d >>= 1) admitted += __shfl_xor(admitted, d);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&lds[4], admitted);
     __syncthreads();
-    if (tid == 0) {
-        result_out[0] = sh_cnt;
-        result_out[1] = done_all;
+    if (threadIdx.x == 0) {
+        result_out[0] = lds[4];
+        result_out[1] = done;
         result_out[2] = T;
     }
 }
 
-
-// One workgroup.  ok[0] = 1 iff the first old_len entries of the order and all lengths equal their copies;
-// afterwards the copies hold order[0 .. new_len), s and o.
-__global__ __launch_bounds__(1024) void horizon_verify_kernel(const int32_t *order, const int32_t *s, const int32_t *o,
-                                                              int32_t n, int32_t old_len, int32_t new_len,
-                                                              int32_t *order_copy, int32_t *s_copy, int32_t *o_copy,
-                                                              int32_t *ok)
+__global__ __launch_bounds__(1024) void horizon_advance_kernel(HorizonKept h, const int32_t *order, int32_t n, int32_t blocks,
+                                                              long long completed_in, int32_t complete_every,
+                                                              int32_t *completion_out, int64_t *result_out)
 {
-    int same = 1;
-    for (int i = threadIdx.x; i < n; i += 1024) {
-        const int sv = s[i], ov = o[i];
-        same &= (sv == s_copy[i]) & (ov == o_copy[i]);
-        s_copy[i] = sv;
-        o_copy[i] = ov;
-    }
-    for (int k = threadIdx.x; k < new_len; k += 1024) {
-        const int id = order[k];
-        if (k < old_len) same &= id == order_copy[k];
-        order_copy[k] = id;
-    }
-    const int all = __syncthreads_and(same);
-    if (threadIdx.x == 0) ok[0] = all ? 1 : 0;
+    __shared__ int lds[5];
+    if (threadIdx.x < 5) lds[threadIdx.x] = 0;
+    __syncthreads();
+    const int placed = min(h.ctrl[KVS_HZ_PLACED], n);
+    auto start = [&](int p) { return h.start[p]; };
+    auto completion = [&](int p) { return h.start[p] + h.o[min(max(order[p], 0), n - 1)]; };
+    if (completion_out)
+        for (int p = threadIdx.x; p < placed; p += 1024) completion_out[min(max(order[p], 0), n - 1)] = completion(p);
+    commit_point(n, placed, start, completion, completed_in, complete_every, result_out, lds);
+    if (threadIdx.x == 0) h.ctrl[KVS_HZ_AVAIL] = min(placed >> 6, blocks);
 }
 
-__global__ void scatter_prefix_kernel(const int32_t *order, const int32_t *by_position, int32_t len, int32_t n,
-                                      int32_t *completion_by_id)
+__global__ __launch_bounds__(1024) void horizon_advance_by_id_kernel(const int32_t *order, const int32_t *by_id,
+                                                                    const int32_t *o, int32_t n, long long completed_in,
+                                                                    int32_t complete_every, int64_t *result_out)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < len) {
-        const int id = order[k];
-        if (id >= 0 && id < n) completion_by_id[id] = by_position[k];
-    }
+    __shared__ int lds[5];
+    if (threadIdx.x < 5) lds[threadIdx.x] = 0;
+    __syncthreads();
+    auto start = [&](int p) { return by_id[order[p]] - o[order[p]]; };
+    auto completion = [&](int i) { return by_id[i]; };
+    commit_point(n, n, start, completion, completed_in, complete_every, result_out, lds);
 }
+
+__global__ __launch_bounds__(256) void horizon_completion_kernel(HorizonKept h, const int32_t *order, const int32_t *o,
+                                                                 int32_t n, int32_t *completion_out)
+{
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= n || p >= h.ctrl[KVS_HZ_PLACED]) return;
+    const int id = min(max(order[p], 0), n - 1);
+    completion_out[id] = h.start[p] + o[id];
+}
+
+int ok() { return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP; }
 
 }  // namespace
 
@@ -128,31 +246,47 @@ int kvs_launch_apply_best_move(const int32_t *order, int32_t n, const int32_t *m
 {
     hipLaunchKernelGGL(apply_best_move_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, order, n, moves,
                        result, order_out);
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+    return ok();
 }
 
-int kvs_launch_horizon_advance(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
-                               int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st)
+int kvs_launch_horizon_begin(const HorizonKept &h, int32_t kept, const int32_t *order, const int32_t *s, const int32_t *o,
+                             int32_t n, const int32_t *moves, int32_t K, int32_t *blocks, hipStream_t st)
 {
-    hipLaunchKernelGGL(horizon_advance_kernel, dim3(1), dim3(1024), 0, st, order, completion, o, n,
+    const int most = n > K + 1 ? n : K + 1;
+    const unsigned groups = most >= 64 * 1024 ? 64u : (unsigned)((most + 1023) / 1024);
+    hipLaunchKernelGGL(horizon_begin_kernel, dim3(groups), dim3(256), 0, st, h, kept, order, s, o, n, moves, K, blocks);
+    return ok();
+}
+
+int kvs_launch_horizon_choose(const HorizonKept &h, int32_t *order, int32_t n, const int32_t *moves, const int64_t *result,
+                              const int32_t *d_words, int32_t stride, int64_t completed_in, int32_t complete_every,
+                              int32_t full, hipStream_t st)
+{
+    hipLaunchKernelGGL(horizon_choose_kernel, dim3(1), dim3(1024), 0, st, h, order, n, moves, result, d_words, stride,
+                       (long long)completed_in, complete_every, full);
+    return ok();
+}
+
+int kvs_launch_horizon_advance(const HorizonKept &h, const int32_t *order, int32_t n, int32_t blocks, int64_t completed_in,
+                               int32_t complete_every, int32_t *completion_out, int64_t *result_out, hipStream_t st)
+{
+    hipLaunchKernelGGL(horizon_advance_kernel, dim3(1), dim3(1024), 0, st, h, order, n, blocks, (long long)completed_in,
+                       complete_every, completion_out, result_out);
+    return ok();
+}
+
+int kvs_launch_horizon_advance_by_id(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
+                                     int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st)
+{
+    hipLaunchKernelGGL(horizon_advance_by_id_kernel, dim3(1), dim3(1024), 0, st, order, completion, o, n,
                        (long long)completed_in, complete_every, result_out);
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+    return ok();
 }
 
-int kvs_launch_horizon_verify(const int32_t *order, const int32_t *s, const int32_t *o, int32_t n, int32_t old_len,
-                              int32_t new_len, int32_t *order_copy, int32_t *s_copy, int32_t *o_copy, int32_t *ok,
-                              hipStream_t st)
+int kvs_launch_horizon_completion(const HorizonKept &h, const int32_t *order, const int32_t *o, int32_t n,
+                                  int32_t *completion_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(horizon_verify_kernel, dim3(1), dim3(1024), 0, st, order, s, o, n, old_len, new_len, order_copy,
-                       s_copy, o_copy, ok);
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
-}
-
-int kvs_launch_scatter_prefix(const int32_t *order, const int32_t *by_position, int32_t len, int32_t n,
-                              int32_t *completion_by_id, hipStream_t st)
-{
-    if (len < 1) return KVSCHED_OK;
-    hipLaunchKernelGGL(scatter_prefix_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, order, by_position,
-                       len, n, completion_by_id);
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+    hipLaunchKernelGGL(horizon_completion_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, h, order, o, n,
+                       completion_out);
+    return ok();
 }

@@ -57,12 +57,14 @@ struct kvsched_ctx {
     int32_t resume_min_rows;  // kvsched_simulate resumes rows from row 0's snapshots from this many rows on
     int32_t resume_wait_polls;  // ... in one launch, a row waiting at most so many polls for its snapshot; 0: in two launches
     hipEvent_t ev0, ev1;
-    // kvsched_horizon_step: the state behind the positions no move touched at the last step, with what it was
-    // computed from (copies of the order's prefix and of the lengths, compared on the device before use)
-    void *d_horizon;          // state | order copy [n] | s copy [n] | o copy [n] | completion rounds by position [n] | flag
+    // kvsched_horizon_step: the chosen order's saved states and start rounds as far as the last step placed it, with
+    // what they were computed from (copies of the order and of the lengths, compared on the device before use)
+    void *d_horizon;
     size_t horizon_bytes;
-    int32_t hz_n, hz_len, hz_o_bound;  // hz_len = 0: nothing kept
+    int32_t hz_kept;             // 0: nothing kept
+    int32_t hz_n, hz_o_bound;    // ... for these
     int64_t hz_M;
+    int32_t hz_completion;       // what kvsched_horizon_completion has: 0 nothing, 1 start rounds, 2 completion rounds by id
 };
 
 // How a candidate's order is presented to the timeline kernel.
@@ -92,8 +94,6 @@ struct SimParams {
     int32_t k_end = 0;
     const int32_t *state_in = nullptr;
     int32_t *state_out = nullptr;
-    // ... unless *resume_ok == 0 (when set): then from position 0 and an empty timeline after all
-    const int32_t *resume_ok = nullptr;
     // Register kernel, explicit rows only: resuming rows from snapshots of row 0.  When cand_list is
     // set, wave w of the launch runs candidate cand_list[w].  Snapshot j (j >= 1) is the timeline
     // state of row 0 after 64 j positions, at snapshots + (j - 1) * snap_stride.  The wave that runs
@@ -129,6 +129,12 @@ struct SimParams {
     // Candidates with skip[c] != INT_MAX are not run at all: they are known to stop at block skip[c] (the
     // encoding of rejoin_block; in practice 0, nothing to place); their tel_out is set to 0.
     const int32_t *skip = nullptr;
+    // The wave that writes the snapshots may itself start from one left by an earlier launch, number *snap_start (the
+    // progress word then starts there too), and stop at the first 64-position boundary at which the round has passed
+    // *t_limit; *placed_out = positions placed.
+    const int32_t *snap_start = nullptr;
+    const int32_t *t_limit = nullptr;
+    int32_t *placed_out = nullptr;
 };
 constexpr int KVS_STATE_HEAD_WORDS = 192;
 // the progress word of the snapshot hand-over: this many copies, this far apart (SimParams::snap_flags)
@@ -150,18 +156,11 @@ int32_t kvs_reg_state_words(int32_t o_bound);  // words of one snapshot for this
 
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
                             hipStream_t st);
-// horizon.hip: ok = (order[0 .. old_len) and the lengths equal their copies); the copies are then brought up to
-// date (order[0 .. new_len), s, o)
-int kvs_launch_horizon_verify(const int32_t *order, const int32_t *s, const int32_t *o, int32_t n, int32_t old_len,
-                              int32_t new_len, int32_t *order_copy, int32_t *s_copy, int32_t *o_copy, int32_t *ok,
-                              hipStream_t st);
-// completion_by_id[order[k]] = by_position[k], k < len
-int kvs_launch_scatter_prefix(const int32_t *order, const int32_t *by_position, int32_t len, int32_t n,
-                              int32_t *completion_by_id, hipStream_t st);
-int kvs_launch_check_moves(const int32_t *moves, int32_t K, int32_t n, int64_t *tel_out, int32_t *d_words,
-                           hipStream_t st);
-int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, int32_t *d_words,
-                      hipStream_t st);
+int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t *d_words, hipStream_t st);
+// The end of a local-search step: latencies of timelines that stopped early completed from the base order's (rejoin or
+// NULL), malformed moves marked, latencies copied to tel_out (or NULL), best move, its latency and the base order's.
+int kvs_launch_neighbor_finish(const int64_t *tel, const int32_t *rejoin, const int32_t *moves, int32_t K, int32_t n,
+                               int64_t *tel_out, int64_t *result_out, int32_t *d_words, hipStream_t st);
 
 // exactdp.hip
 size_t kvs_exact_dp_list_bytes(int32_t n);
@@ -206,11 +205,44 @@ int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t
                             int32_t *d_words, const int32_t *resume_block, const int32_t *row0,
                             const int32_t *rejoin_block, hipStream_t st);
 
-// horizon.hip
+// horizon.hip.  What the context keeps between horizon steps (one device buffer).
+enum {
+    KVS_HZ_AVAIL = 0,   // blocks of 64 positions of the order whose saved states are valid
+    KVS_HZ_BAD = 1,     // working words of the comparison with the copies
+    KVS_HZ_DONE = 2,
+    KVS_HZ_FIRST = 3,   // block the chosen order's timeline starts from
+    KVS_HZ_LIMIT = 4,   // round behind which it need not go on
+    KVS_HZ_PLACED = 5,  // positions it has placed
+    KVS_HZ_ZERO = 6,
+    KVS_HZ_WORDS = 64
+};
+struct HorizonKept {
+    int32_t *ctrl;      // [KVS_HZ_WORDS]
+    int32_t *progress;  // [KVS_PROGRESS_WORDS]
+    int32_t *order, *s, *o;   // copies
+    int32_t *start;           // start rounds of the order by position (ctrl[KVS_HZ_PLACED] of them)
+    int32_t *completion;      // by request id, where the saved states are not used
+    int32_t *snapshots;
+};
+// Before the candidates: is what the context keeps (kept != 0: something) still true of the caller's arrays?  Copies
+// brought up to date, KVS_HZ_AVAIL and the progress words set; blocks[m] = what move m shares with the order (entry K: 0).
+int kvs_launch_horizon_begin(const HorizonKept &h, int32_t kept, const int32_t *order, const int32_t *s, const int32_t *o,
+                             int32_t n, const int32_t *moves, int32_t K, int32_t *blocks, hipStream_t st);
+// After them: the best move applied to the order in place, and how far the new order's timeline has to go (everything
+// if `full`): it starts from block first_block.
+int kvs_launch_horizon_choose(const HorizonKept &h, int32_t *order, int32_t n, const int32_t *moves, const int64_t *result,
+                              const int32_t *d_words, int32_t stride, int64_t completed_in, int32_t complete_every,
+                              int32_t full, hipStream_t st);
+// After the new order's timeline: commit point; completion rounds by request id if wanted.
+int kvs_launch_horizon_advance(const HorizonKept &h, const int32_t *order, int32_t n, int32_t blocks, int64_t completed_in,
+                               int32_t complete_every, int32_t *completion_out, int64_t *result_out, hipStream_t st);
+// The same from completion rounds by request id.
+int kvs_launch_horizon_advance_by_id(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
+                                     int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st);
 int kvs_launch_apply_best_move(const int32_t *order, int32_t n, const int32_t *moves, const int64_t *result,
                                int32_t *order_out, hipStream_t st);
-int kvs_launch_horizon_advance(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
-                               int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st);
+int kvs_launch_horizon_completion(const HorizonKept &h, const int32_t *order, const int32_t *o, int32_t n,
+                                  int32_t *completion_out, hipStream_t st);
 
 // online.hip
 int kvs_launch_online(int32_t B, const int32_t *streams, int32_t N, const int32_t *a, const int32_t *s,

@@ -236,24 +236,14 @@ __global__ __launch_bounds__(1024) void check_orders_wide_kernel(const int32_t *
     }
 }
 
-__global__ __launch_bounds__(256) void check_moves_kernel(const int32_t *moves, int32_t K, int32_t n,
-                                                          int64_t *tel_out, int32_t *words)
-{
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= K) return;
-    const int ty = moves[3 * (size_t)m], i = moves[3 * (size_t)m + 1], j = moves[3 * (size_t)m + 2];
-    if ((ty != KVSCHED_MOVE_SWAP && ty != KVSCHED_MOVE_INSERT) || i < 0 || j < 0 || i >= n || j >= n) {
-        tel_out[m] = -1;
-        atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_MOVE);
-    }
-}
-
-// Index of the least non-negative tel[0..K), lowest index among equals.  With with_base, tel[K] is the base
-// order's own latency and becomes the third result.  (Least latency, then lowest index) is a total order: any
+// Index of the least non-negative tel[0..K), lowest index among equals.  (Least latency, then lowest index) is a total order: any
 // reduction tree gives the same winner.  One workgroup up to 4096 entries, then one per 2048 (at most
 // KVS_ARGMIN_GROUPS), the last to finish reduces the others' winners: 40321 entries 16 us by one, 4 us so.
+// MOVES: the end of a local-search step in the same pass (see kvs_launch_neighbor_finish).
+template <bool MOVES>
 __global__ __launch_bounds__(1024) void argmin_kernel(const int64_t *tel, int32_t K, int64_t *result_out,
-                                                      int32_t with_base, int32_t *words)
+                                                      const int32_t *rejoin, const int32_t *moves, int32_t n,
+                                                      int64_t *tel_out, int32_t *words)
 {
     __shared__ long long sh_tel[16];
     __shared__ int sh_idx[16];
@@ -288,7 +278,19 @@ __global__ __launch_bounds__(1024) void argmin_kernel(const int64_t *tel, int32_
         }
     };
     for (int m = blockIdx.x * 1024 + threadIdx.x; m < K; m += gridDim.x * 1024) {
-        const long long v = tel[m];
+        long long v = tel[m];
+        if constexpr (MOVES) {
+            if (rejoin && rejoin[m] != INT_MAX) {  // its sum of completion rounds is relative to the base order's
+                const long long t0 = tel[K];
+                v = t0 < 0 ? -1 : v + t0;
+            }
+            const int ty = moves[3 * (size_t)m], i = moves[3 * (size_t)m + 1], j = moves[3 * (size_t)m + 2];
+            if ((ty != KVSCHED_MOVE_SWAP && ty != KVSCHED_MOVE_INSERT) || i < 0 || j < 0 || i >= n || j >= n) {
+                v = -1;
+                atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_MOVE);
+            }
+            if (tel_out) tel_out[m] = v;
+        }
         if (v >= 0) take(v, m);
     }
     reduce();
@@ -312,10 +314,10 @@ __global__ __launch_bounds__(1024) void argmin_kernel(const int64_t *tel, int32_
         if (threadIdx.x == 0) words[KVS_W_ARGMIN_DONE] = 0;
     }
     if (threadIdx.x == 0) {
-        const bool base_ok = !with_base || tel[K] >= 0;  // a faulty base order makes every neighbour faulty
+        const bool base_ok = !MOVES || tel[K] >= 0;  // a faulty base order makes every neighbour faulty
         result_out[0] = base_ok ? bi : -1;
         result_out[1] = (base_ok && bi >= 0) ? bt : -1;
-        if (with_base) result_out[2] = tel[K];
+        if (MOVES) result_out[2] = tel[K];
     }
 }
 
@@ -364,7 +366,8 @@ int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t
 {
     const size_t per_wave = (size_t)((n + 31) >> 5) * sizeof(unsigned int);
     if (per_wave > 65536) return KVSCHED_ERANGE;
-    if (n >= 16384 && C <= 8192) {  // long rows, not enough of them to fill the chip with a wavefront each
+    // long rows, not enough of them to fill the chip with a wavefront each (one row of 10000: 31 us by a wavefront)
+    if ((n >= 16384 && C <= 8192) || (n >= 1024 && C <= 512)) {
         hipLaunchKernelGGL(check_orders_wide_kernel, dim3((unsigned)C), dim3(1024), per_wave, st, orders, C, n, tel_out,
                            d_words);
     } else if (per_wave * 4 <= 65536) {
@@ -377,18 +380,22 @@ int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
-int kvs_launch_check_moves(const int32_t *moves, int32_t K, int32_t n, int64_t *tel_out, int32_t *d_words,
-                           hipStream_t st)
+static unsigned argmin_groups(int32_t K)
 {
-    hipLaunchKernelGGL(check_moves_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, moves, K, n,
-                       tel_out, d_words);
+    return K <= 4096 ? 1u : K < KVS_ARGMIN_GROUPS * 2048 ? (unsigned)((K + 2047) / 2048) : (unsigned)KVS_ARGMIN_GROUPS;
+}
+
+int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t *d_words, hipStream_t st)
+{
+    hipLaunchKernelGGL((argmin_kernel<false>), dim3(argmin_groups(K)), dim3(1024), 0, st, tel, K, result_out,
+                       (const int32_t *)nullptr, (const int32_t *)nullptr, 0, (int64_t *)nullptr, d_words);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
-int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t with_base, int32_t *d_words,
-                      hipStream_t st)
+int kvs_launch_neighbor_finish(const int64_t *tel, const int32_t *rejoin, const int32_t *moves, int32_t K, int32_t n,
+                               int64_t *tel_out, int64_t *result_out, int32_t *d_words, hipStream_t st)
 {
-    const unsigned blocks = K <= 4096 ? 1u : K < KVS_ARGMIN_GROUPS * 2048 ? (unsigned)((K + 2047) / 2048) : (unsigned)KVS_ARGMIN_GROUPS;
-    hipLaunchKernelGGL(argmin_kernel, dim3(blocks), dim3(1024), 0, st, tel, K, result_out, with_base, d_words);
+    hipLaunchKernelGGL((argmin_kernel<true>), dim3(argmin_groups(K)), dim3(1024), 0, st, tel, K, result_out, rejoin, moves,
+                       n, tel_out, d_words);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

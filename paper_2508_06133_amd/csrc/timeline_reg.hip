@@ -741,10 +741,6 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
     // (a prefix shared by all candidates) comes from memory when there is one
     int k_first = p.k_begin;
     const int32_t *state_in = p.state_in;
-    if (p.resume_ok && scalar_read(p.resume_ok, 0) == 0) {  // what the state was computed from has changed since
-        k_first = 0;
-        state_in = nullptr;
-    }
     const int n = p.k_end > 0 ? p.k_end : n_all;  // one past the last position placed here
     // Rejoining row 0.  A row that differs from row 0 only at positions i..j holds the same requests
     // there in another order.  If row 0 starts the requests of positions i - 1 .. j in one and the same
@@ -793,6 +789,15 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
     }
     const bool takes_snapshots = RES && p.snap_blocks > 0 && cand == p.snap_cand;
+    // (CONT, LIMIT: which launches use this; the scalar registers it takes would cost the others a wavefront per SIMD)
+    constexpr bool CONT = RES && (MOVES || !ONE), LIMIT = RES && !ONE;
+    if (CONT && takes_snapshots && p.snap_start) {
+        const int rb = scalar_read(p.snap_start, 0);
+        if (rb > 0) {
+            k_first = 64 * rb;
+            state_in = p.snapshots + (size_t)(rb - 1) * (size_t)p.snap_stride;
+        }
+    }
     int b64 = 0;             // round of lane 0 of register 0: 64 * floor((t + 1) / 64)
     int t = 0;               // start round of the previous request in the order
     long long tel_lane = 0;  // completion rounds summed per lane; added up over the lanes at the end
@@ -822,6 +827,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
             ov_n = p.o[rq_n];
         }
     }
+    if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = n;  // (unless it stops before)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
     for (int k0 = k_first; k0 < n_stop; k0 += WAVE) {
         if (RES && k0 == rejoin_k && rest_is_row0(k0 >> 6)) {  // the state is row 0's after k0 positions
@@ -831,11 +837,16 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
             n_stop = 0;
             continue;
         }
-        if (takes_snapshots && k0 > 0 && (k0 >> 6) <= p.snap_blocks) {  // the state after k0 positions
+        if (takes_snapshots && k0 > (CONT ? k_first : 0) && (k0 >> 6) <= p.snap_blocks) {  // the state after k0 positions
             int32_t *snap = p.snapshots + (size_t)((k0 >> 6) - 1) * (size_t)p.snap_stride;
             state_head_store<NR>(snap, b64, t, tel_lane, lane);
             prof_store<NR>(snap + KVS_STATE_HEAD_WORDS, lane);
             if (ONE) snapshot_publish<NR>(p.snap_flags, k0 >> 6, lane);
+            if (LIMIT && p.t_limit && t > snapshot_word<NR>(p.t_limit, 0)) {  // nobody asked for what comes later
+                *p.placed_out = k0;  // (every lane, same value)
+                n_stop = 0;
+                continue;
+            }
         }
         const int cnt = __builtin_amdgcn_readfirstlane(min(WAVE, n - k0));
         const int k = k0 + cnt - 1 - lane;  // this lane's position (none if k < k0)
@@ -854,6 +865,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // cannot be scheduled: report, do not loop forever
             if (lane == 0) {
                 if (p.tel_out) p.tel_out[cand] = -1;
+                if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = 0;
                 if (p.state_out) p.state_out[1] = -1;  // poisons every timeline that resumes from it
             }
             if (ONE && takes_snapshots)  // nobody shall wait for the snapshots that will not come

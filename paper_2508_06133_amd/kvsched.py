@@ -68,6 +68,7 @@ def _load() -> ctypes.CDLL:
     lib.kvsched_best_neighbor.argtypes = [vp, vp, i32, vp, i32, vp, vp, i64, vp, vp, vp]
     lib.kvsched_best_neighbor_static.argtypes = [vp, vp, i32, vp, i32, vp, vp, i64, i32, vp, vp, vp]
     lib.kvsched_horizon_step.argtypes = [vp, vp, i32, vp, i32, vp, vp, i64, i64, i32, vp, vp, vp, vp]
+    lib.kvsched_horizon_completion.argtypes = [vp, vp, i32, vp, vp, vp]
     lib.kvsched_online.argtypes = [vp, i32, vp, i32, vp, vp, vp, i64, i32, vp, i32, vp, vp]
     return lib
 
@@ -348,6 +349,16 @@ class Context:
         if rc != OK:
             raise KvschedError(rc, "kvsched_horizon_step")
         return tel, res
+
+    def horizon_completion(self, order, o, completion_out):
+        """Completion rounds (by request id) of the order the last horizon_step() chose, as far as it placed it: all of
+        them when that step committed every position."""
+        rc = _lib.kvsched_horizon_completion(self._h, _dev(order, torch.int32, "order"), order.shape[0],
+                                             _dev(o, torch.int32, "o"),
+                                             _dev(completion_out, torch.int32, "completion_out"), _stream())
+        if rc != OK:
+            raise KvschedError(rc, "kvsched_horizon_completion")
+        return completion_out
 
     def online(self, streams, a, s, o, M, completion_out, stats_out=None, backlog_cap: int = ONLINE_MAX_BACKLOG):
         """streams [B, 8] int32 descriptors {first request, count, planner, period, window,
