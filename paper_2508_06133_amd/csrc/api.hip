@@ -101,7 +101,17 @@ int32_t ring_slots_for(int32_t o_max)
     return h;
 }
 
-// Wait until the length scan number ctx->scan_seq has left its results in pinned host memory.  (The scan is some
+int32_t next_seq(kvsched_ctx *ctx) { return ctx->scan_seq = (int32_t)((uint32_t)ctx->scan_seq + 1u); }
+
+// A wait inside a captured stream would have nothing to wait for.
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
+// Wait until the launch number ctx->scan_seq (length scan, or a batch of the exact DP) has left its results in pinned
+// host memory.  (The scan is some
 // microseconds of work, so the host polls; now and then it asks the stream, which also ends the wait if the
 // device has failed.)
 int wait_for_scan(kvsched_ctx *ctx, hipStream_t st)
@@ -132,11 +142,10 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
         *o_bound_out = ctx->o_max_bound;
         return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st, moves, K);
     }
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;  // a captured scan has no result to wait for
-    if (hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return KVSCHED_EHIP;
+    if (capturing(st)) return KVSCHED_EHIP;
     // (the first and last position the moves touch come with it)
     int rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, moves, K, ctx->h_scan,
-                                     ctx->scan_seq = (int32_t)((uint32_t)ctx->scan_seq + 1u));
+                                     next_seq(ctx));
     if (rc != KVSCHED_OK) return rc;
     rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;
@@ -693,13 +702,15 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
         return kvs_launch_exact_dp_small(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, lg, ctx->d_scratch, ctx->d_tables,
                                          order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
     }
-    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, feas_mode, ctx->d_scratch, ctx->d_words, num_batches_out, st);
+    if (capturing(st)) return KVSCHED_EHIP;
+    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, ga, gb, feas_mode, ctx->d_scratch, ctx->d_words, num_batches_out,
+                                     ctx->h_scan, next_seq(ctx), st);
     if (rc != KVSCHED_OK) return rc;
-    rc = read_words(ctx, st);
+    rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;
-    int32_t r = ctx->h_words[KVS_W_REMAIN], kmax = ctx->h_words[KVS_W_KMAX];
+    int32_t r = ctx->h_scan[KVS_H_REMAIN], kmax = ctx->h_scan[KVS_H_KMAX], kmin = ctx->h_scan[KVS_H_KMIN];
     if (r == 0) return KVSCHED_OK;  // malformed lengths: reported in the device status, no batches
-    if (r != n || kmax < 1 || kmax > n) return KVSCHED_EHIP;
+    if (r != n || kmax < 1 || kmax > n || kmin < 1 || kmin > kmax) return KVSCHED_EHIP;
     if (const int lg = kvs_exact_dp_small_lg(n, kmax, (int32_t)M)) {  // fits after all, with the true bound
         rc = ensure_tables(ctx, kvs_exact_dp_small_record_bytes(n, kmax, lg));
         if (rc != KVSCHED_OK) return rc;
@@ -712,16 +723,18 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
     if (rc != KVSCHED_OK) return rc;
     int32_t nb = 0;
     while (r > 0) {  // r falls by at least one per batch
-        rc = kvs_launch_exact_dp_batch(n, r, kmax, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, nb, ctx->d_scratch,
-                                       ctx->d_tables, batch_end_out, F_out, ctx->d_words, st);
+        rc = kvs_launch_exact_dp_batch(n, r, kmin, kmax, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, nb, ctx->d_scratch,
+                                       ctx->d_tables, batch_end_out, F_out, ctx->d_words, ctx->h_scan, next_seq(ctx), st);
         if (rc != KVSCHED_OK) return rc;
-        rc = read_words(ctx, st);
+        rc = wait_for_scan(ctx, st);
         if (rc != KVSCHED_OK) return rc;
-        const int32_t r_next = ctx->h_words[KVS_W_REMAIN], k_next = ctx->h_words[KVS_W_KMAX];
+        const int32_t r_next = ctx->h_scan[KVS_H_REMAIN], k_next = ctx->h_scan[KVS_H_KMAX], min_next = ctx->h_scan[KVS_H_KMIN];
         ++nb;
-        if (r_next < 0 || r_next >= r || k_next > kmax || (r_next > 0 && k_next < 1)) return KVSCHED_EHIP;
+        if (r_next < 0 || r_next >= r || k_next > kmax || (r_next > 0 && (k_next < 1 || min_next < 1 || min_next > k_next)))
+            return KVSCHED_EHIP;
         r = r_next;
         kmax = k_next;
+        kmin = min_next;
     }
     return kvs_launch_exact_dp_emit(n, nb, ctx->d_scratch, order_out, num_batches_out, st);
 }

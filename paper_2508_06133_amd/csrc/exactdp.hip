@@ -4,13 +4,20 @@
 // requests taken one by one, k running downward, a state replaced only by a strictly smaller
 // value; at the end every state is scored F = dp[k][m] / k^2.
 //
-// On the GPU one request is one launch over all (k, m) states at once, reading the table of the
-// previous request and writing a second one (which is what "k downward" achieves in place): one
-// wavefront covers 64 consecutive loads m of one cardinality k, and its ballot of "this state was
-// improved by request t" is the only record kept of the chosen sets (bits[t][k][m / 64]).  The set
+// On the GPU a launch offers four requests to the states at once, reading the table before them and writing a second
+// one: the value of (k, m) behind four requests depends on the sixteen states before them that lack a part of the four
+// (row k - |part|, load m - its load), combined one request after the other, which is what "k downward" achieves in
+// place.  One wavefront covers 64 consecutive loads m of one cardinality k, and its ballots of "this state was
+// improved by request t" are the only record kept of the chosen sets (bits[t][k][m / 64]).  The set
 // of the best state is recovered by walking those records backwards: at state (k, m) the last
 // request that improved it is a member, and the walk continues at (k - 1, m - load) among the
 // earlier requests.  That is the set Algorithm 2 carries in path[k][m].
+//
+// Only states that can be part of the answer are kept up to date.  Let kmin be the least k at which the k smallest
+// values could sum to as good a metric as a batch known to be feasible (the best prefix in ascending cost).  A chosen set
+// has at least kmin members, so after t of r requests a state needs k >= kmin - (r - t), and its load lies between the sum
+// of the k smallest loads and M minus that of the kmin - k smallest.  Every state on the way to the answer satisfies
+// this, and so does every state its value or its record depends on; the others hold values that are too large at worst.
 //
 // feas_mode 0: load = sum (s+o) <= M, requests in input order (Algorithm 2 as printed).
 // feas_mode 1: the constraint of Algorithm 1's Phase 1 (all of X started together stays within M
@@ -23,9 +30,11 @@ namespace {
 
 constexpr int DP_T = 1024;  // threads of the single-workgroup helper kernels
 constexpr int DP_NW = DP_T / 64;
-constexpr int DP_INF = 0x7fffffff;
+constexpr int DP_INF = 0x7fffffff;        // (one-workgroup kernel)
+constexpr unsigned DP_NONE = 0x80000000u; // no set: above every value (< 2^31), and still below 2^32 with one more added
 constexpr int DP_STEP_T = 256;
-constexpr int DP_ARGMIN_BLOCKS = 256;
+constexpr int DP_STEP_M = 512;            // loads per workgroup of a step launch, two per thread
+constexpr int DP_G = 4;                   // requests per step launch
 
 struct HelperLds {
     RadixLds<DP_T> radix;
@@ -135,53 +144,80 @@ __device__ int prepare_body(int32_t n, const int32_t *s, const int32_t *o, int32
     return prefix_fit(by_cost, n, s, o, feas_mode, M, L);
 }
 
-__global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
-                                                          int32_t feas_mode, int *proc, int *by_o, int *by_cost,
-                                                          int *buf0, int *buf1, int *batch_of, int32_t *words,
-                                                          int32_t *num_batches_out)
-{
-    __shared__ HelperLds L;
-    const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
-                                  num_batches_out, L);
-    if (kmax >= 0 && threadIdx.x == 0) {
-        words[KVS_W_REMAIN] = n;
-        words[KVS_W_KMAX] = kmax;
-    }
-}
-
-__global__ __launch_bounds__(DP_STEP_T) void dp_init_kernel(int *a, int *b, size_t count)
+// Both tables, each with DP_G rows of "no set" in front of row 0.
+__global__ __launch_bounds__(DP_STEP_T) void dp_init_kernel(unsigned *a, size_t count, size_t table, int Mp)
 {
     const size_t i = (size_t)blockIdx.x * DP_STEP_T + threadIdx.x;
-    if (i < count) {
-        const int v = i == 0 ? 0 : DP_INF;  // dp[0][0] = 0
-        a[i] = v;
-        b[i] = v;
-    }
+    if (i < count) a[i] = i % table == (size_t)DP_G * Mp ? 0u : DP_NONE;  // dp[0][0] = 0
 }
 
-// Request proc[t] offered to every state: row k = blockIdx.y + 1, loads blockIdx.x * 256 ...
-__global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(const int *proc, int t, const int32_t *s, const int32_t *o,
-                                                            int32_t M, int32_t ga, int32_t gb, int32_t feas_mode,
-                                                            const int *src, int *dst, unsigned long long *bits_t, int Mp)
+// What the step launches read, laid out so that one round trip brings it: per request in processing order its load,
+// decode length and value; per row k the loads a chosen set can pass through (see the top of the file).
+struct DpPlan {
+    const int4 *req;
+    const int2 *range;
+};
+
+// Requests proc[t0 .. t0 + DP_G) offered to row k = k_first + blockIdx.y, loads blockIdx.x * DP_STEP_M ...
+// Bound by the launch and by L2 reads (16 per state and four requests, where one request a launch took 2 reads and a
+// write each): 200 requests, M = 16384: 497 launches of 4.5 us become 126 of 5.6 us (two dependent reads and a write take 4 of them).
+template <int MODE>
+__global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0, int r, int32_t M, const unsigned *src,
+                                                            unsigned *dst, unsigned long long *bits, size_t per_t, int Mp,
+                                                            int k_first)
 {
-    const int k = blockIdx.y + 1;
-    const int m = blockIdx.x * DP_STEP_T + threadIdx.x;  // < Mp by the launch shape
-    const int id = proc[t];
-    const int oi = o[id];
-    const int load = feas_mode ? s[id] : s[id] + oi;
-    const int gi = ga * s[id] + gb * oi;  // what dp sums: o, or the effective length of the G metric
-    const size_t at = (size_t)k * Mp + m;
-    const int old = src[at];
-    int cand = DP_INF;
-    if (m <= M && m >= load) {
-        const int prev = src[at - Mp - load];
-        const bool fits = feas_mode == 0 || (long long)m + (long long)oi * k <= (long long)M;
-        if (prev != DP_INF && fits) cand = prev + gi;
+    const int k = k_first + (int)blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int m0 = (int)blockIdx.x * DP_STEP_M + 128 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int2 range = plan.range[k];
+    const int lo = range.x, hi = range.y;
+    unsigned load[DP_G], gain[DP_G];
+    int len[DP_G];
+#pragma unroll
+    for (int g = 0; g < DP_G; ++g) {  // (behind the last request: entries that join nothing)
+        const int4 q = plan.req[t0 + g];
+        load[g] = (unsigned)q.x;
+        len[g] = q.y;
+        gain[g] = (unsigned)q.z;
     }
-    const bool take = cand < old;
-    dst[at] = take ? cand : old;
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(take);
-    if ((threadIdx.x & 63) == 0) bits_t[(size_t)k * (Mp >> 6) + (m >> 6)] = bal;
+    if (m0 > hi || m0 + 127 < lo) return;
+    unsigned off[1 << DP_G];
+    off[0] = 0;
+#pragma unroll
+    for (int h = 1; h < (1 << DP_G); ++h) off[h] = off[h & (h - 1)] + load[__builtin_ctz(h)];
+    const unsigned *row = src + (size_t)(k + DP_G) * Mp;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int mc = m0 + 64 * c;
+        if (mc > hi || mc + 63 < lo) continue;
+        const unsigned m = (unsigned)(mc + lane);
+        unsigned f[1 << DP_G];  // f[h]: the state that lacks the requests of h, behind those below h's lowest
+#pragma unroll
+        for (int h = 0; h < (1 << DP_G); ++h)
+            f[h] = *(off[h] <= m ? row + ((long long)m - off[h] - (long long)__builtin_popcount(h) * Mp) : src);  // (src[0]: no set)
+        static_assert(DP_G == 4, "sixteen states");
+        // all sixteen reads are in flight before the first is waited for
+        asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),
+                     "+v"(f[8]), "+v"(f[9]), "+v"(f[10]), "+v"(f[11]), "+v"(f[12]), "+v"(f[13]), "+v"(f[14]), "+v"(f[15]));
+        unsigned long long took[DP_G];
+#pragma unroll
+        for (int g = 0; g < DP_G; ++g) {
+#pragma unroll
+            for (int h = 0; h < (1 << DP_G); h += 2 << g) {
+                unsigned with = f[h | (1 << g)] + gain[g];
+                if (MODE && (long long)m - (long long)off[h] + (long long)len[g] * (k - __builtin_popcount(h)) > (long long)M) with = DP_NONE;
+                if (h == 0) took[g] = __builtin_amdgcn_ballot_w64(with < f[0]);
+                f[h] = min(f[h], with);
+            }
+        }
+        dst[(size_t)(k + DP_G) * Mp + m] = f[0];
+        if (lane == 0) {
+            unsigned long long *b = bits + (size_t)t0 * per_t + (size_t)k * (Mp >> 6) + (mc >> 6);
+#pragma unroll
+            for (int g = 0; g < DP_G; ++g)
+                if (t0 + g < r) b[(size_t)g * per_t] = took[g];
+        }
+    }
 }
 
 // sign of Sa/ka^2 - Sb/kb^2 (S < 2^31, k <= 4096: the products stay below 2^55)
@@ -262,85 +298,83 @@ __device__ void publish_batch(long long bS, int bk, int32_t gb, int32_t done, in
     }
 }
 
-// Stage 1: workgroup b reduces rows 1 + b, 1 + b + G, ...; stage 2: one workgroup reduces the G partials.
-__global__ __launch_bounds__(DP_T) void dp_argmin_rows_kernel(const int *dp, int kmax, int32_t M, int Mp,
-                                                              int32_t tie_rule, long long *partial)
+// Row k = kmin + blockIdx.x of the last table: its least value and the least load that has it, as value << 32 | load.
+__global__ __launch_bounds__(DP_T) void dp_argmin_rows_kernel(const unsigned *dp, int kmin, int Mp, DpPlan plan,
+                                                              unsigned long long *partial)
 {
-    __shared__ HelperLds L;
-    long long bS;
-    int bk, bm;
-    argmin_body(dp, 1 + (int)blockIdx.x, (int)gridDim.x, kmax, M, Mp, tie_rule, L, bS, bk, bm);
+    __shared__ unsigned long long red[DP_NW];
+    const int k = kmin + (int)blockIdx.x;
+    const int lo = plan.range[k].x, hi = plan.range[k].y;
+    unsigned long long best = ~0ull;
+    for (int m = max(lo, 0) + threadIdx.x; m <= hi; m += DP_T) {
+        const unsigned v = dp[(size_t)(k + DP_G) * Mp + m];
+        best = min(best, ((unsigned long long)v << 32) | (unsigned)m);
+    }
+    for (int d = 32; d > 0; d >>= 1) best = min(best, (unsigned long long)__shfl_xor((long long)best, d));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        partial[3 * blockIdx.x + 0] = bS;
-        partial[3 * blockIdx.x + 1] = bk;
-        partial[3 * blockIdx.x + 2] = bm;
+        for (int v = 1; v < DP_NW; ++v) best = min(best, red[v]);
+        partial[blockIdx.x] = best;
     }
 }
 
-__global__ __launch_bounds__(DP_T) void dp_argmin_kernel(const long long *partial, int G, int32_t tie_rule, int32_t gb,
-                                                         int32_t done, int32_t nb, int32_t *batch_end_out,
-                                                         double *F_out, int32_t *words)
-{
-    __shared__ HelperLds L;
-    long long bS = 0;
-    int bk = 0, bm = 0;
-    for (int g = threadIdx.x; g < G; g += DP_T) {
-        const long long S = partial[3 * g];
-        const int k = (int)partial[3 * g + 1], m = (int)partial[3 * g + 2];
-        if (dp_better(S, k, m, bS, bk, bm, tie_rule)) { bS = S; bk = k; bm = m; }
-    }
-    reduce_best(tie_rule, L, bS, bk, bm);
-    if (threadIdx.x == 0) {
-        words[KVS_W_BESTK] = bk;
-        words[KVS_W_BESTM] = bm;
-        publish_batch(bS, bk, gb, done, nb, batch_end_out, F_out, words);
-    }
-}
-
-// One wavefront follows the records back from the best state and stamps the members with the
-// batch number.  A set of k needs k requests, so only records of requests t >= k - 1 exist (rows
-// above t + 1 are not launched and hold nothing of this batch).  Every pass lowers `bound`, so the
-// loop ends.
-__device__ void walk_body(const unsigned long long *bits, const int *proc, int r, int kmax, int Mp, const int32_t *s,
-                          const int32_t *o, int32_t feas_mode, int32_t nb, int *batch_of, int k, int m)
+// One wavefront follows the records back from the best state (k, m) and stamps the members with the batch number.  The
+// records of six consecutive requests are read together, one lane for each way the later of them may have been members
+// (63 states): a round trip to memory serves six requests instead of the one to two that tests of (k, m) against a run of
+// requests do.  (Ten at a time by sixteen wavefronts is slower: a thousand reads all over the records.)
+// load[t]: loads in processing order (LDS).
+__device__ void walk_body(const unsigned long long *bits, const int *proc, int r, int kmax, int Mp, const int *load,
+                          int32_t nb, int *batch_of, int k, int m)
 {
     const int lane = threadIdx.x & 63;
     const size_t per_t = (size_t)(kmax + 1) * (Mp >> 6);
+    // lane v >= 1 is a node of a binary tree: depth floor(log2 v), its low bits the choices above (latest first)
+    const int depth = 31 - __builtin_clz(lane | 1);
     int bound = r - 1;
-    while (k > 0 && bound >= 0 && m >= 0) {
-        const int t = bound - lane;
-        bool hit = false;
-        if (t >= k - 1) hit = (bits[(size_t)t * per_t + (size_t)k * (Mp >> 6) + (m >> 6)] >> (m & 63)) & 1ull;
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(hit);
-        if (bal == 0) {
-            bound -= 64;
-            continue;
+    while (k > 0 && bound >= 0) {
+        const int ahead = lane < 6 && lane <= bound ? load[bound - lane] : 0;
+        const int ids = lane < 6 && lane <= bound ? proc[bound - lane] : 0;
+        int kk = k, mm = m;
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            const int l = __builtin_amdgcn_readlane(ahead, d);
+            if (d < depth && ((lane >> (depth - 1 - d)) & 1)) {
+                kk -= 1;
+                mm -= l;
+            }
         }
-        const int tstar = bound - (int)__builtin_ctzll(bal);  // the latest such request
-        const int id = proc[tstar];
-        if (lane == 0) batch_of[id] = nb;
-        m -= feas_mode ? s[id] : s[id] + o[id];
-        k -= 1;
-        bound = tstar - 1;
+        const int t = bound - depth;
+        bool hit = false;
+        if (lane > 0 && t >= 0 && kk > 0 && mm >= 0)
+            hit = (bits[(size_t)t * per_t + (size_t)kk * (Mp >> 6) + (mm >> 6)] >> (mm & 63)) & 1ull;
+        const unsigned long long tree = __builtin_amdgcn_ballot_w64(hit);
+        int v = 1;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            if (k > 0 && bound >= 0) {
+                const int in = (int)((tree >> v) & 1ull);
+                if (in) {
+                    if (lane == d) batch_of[ids] = nb;
+                    m -= __builtin_amdgcn_readlane(ahead, d);
+                    k -= 1;
+                }
+                v = 2 * v + in;
+                bound -= 1;
+            }
+        }
     }
 }
 
-__global__ __launch_bounds__(64) void dp_walk_kernel(const unsigned long long *bits, const int *proc, int r, int kmax,
-                                                     int Mp, const int32_t *s, const int32_t *o, int32_t feas_mode,
-                                                     int32_t nb, int *batch_of, const int32_t *words)
-{
-    walk_body(bits, proc, r, kmax, Mp, s, o, feas_mode, nb, batch_of, words[KVS_W_BESTK], words[KVS_W_BESTM]);
-}
-
-// Members leave proc[] and by_cost[] (both keep their order); kept = the new count, kmax = the new
+// Members leave proc[], by_cost[] and left_by_o[] (or NULL; all keep their order); kept = the new count, kmax = the new
 // bound on the batch size.
-__device__ void compact_body(int *proc, int *by_cost, int *tmp, int r, int32_t nb, const int *batch_of, const int32_t *s,
+__device__ void compact_body(int *proc, int *by_cost, int *left_by_o, int *tmp, int r, int32_t nb, const int *batch_of, const int32_t *s,
                              const int32_t *o, int32_t feas_mode, int32_t M, HelperLds &L, int &kept, int &kmax)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     kept = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        int *list = pass == 0 ? proc : by_cost;
+    for (int pass = 0; pass < (left_by_o ? 3 : 2); ++pass) {
+        int *list = pass == 0 ? proc : pass == 1 ? by_cost : left_by_o;
         int carry = 0;
         for (int tile = 0; tile < r; tile += DP_T) {
             const int i = tile + tid;
@@ -376,17 +410,156 @@ __device__ void compact_body(int *proc, int *by_cost, int *tmp, int r, int32_t n
     kmax = kept > 0 ? prefix_fit(by_cost, kept, s, o, feas_mode, M, L) : 0;
 }
 
-__global__ __launch_bounds__(DP_T) void dp_compact_kernel(int *proc, int *by_cost, int *tmp, int r, int32_t nb,
-                                                          const int *batch_of, const int32_t *s, const int32_t *o,
-                                                          int32_t feas_mode, int32_t M, int32_t *words)
+// For the kmax cheapest of the r requests: cost[k] = sum of the k least costs (cost[0] = 0), and kmin (see the top).
+// Every thread receives kmin.
+__device__ int bounds_body(const int *by_cost, const int *left_by_o, int kmax, const int32_t *s, const int32_t *o, int32_t M,
+                           int32_t ga, int32_t gb, int32_t feas_mode, int *cost, HelperLds &L)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ long long sc[3][DP_NW];
+    auto scan3 = [&](long long (&v)[3], long long (&carry)[3]) {  // inclusive sums over the workgroup, behind carry
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            for (int d = 1; d < 64; d <<= 1) {
+                const long long u = __shfl_up(v[q], d);
+                if (lane >= d) v[q] += u;
+            }
+            if (lane == 63) sc[q][wave] = v[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            long long off = carry[q];
+            for (int u = 0; u < DP_NW; ++u) {
+                if (u == wave) v[q] += off;
+                off += sc[q][u];
+            }
+            carry[q] = off;
+        }
+        __syncthreads();
+    };
+    // the best prefix in ascending cost that fits by its peaks (it then fits under either constraint)
+    long long bS = 0;
+    int bk = 0, bm = 0;
+    long long carry[3] = {0, 0, 0};
+    for (int tile = 0; tile < kmax; tile += DP_T) {
+        const int i = tile + tid;
+        long long v[3] = {0, 0, 0};  // cost, peak, value
+        if (i < kmax) {
+            const int id = by_cost[i];
+            v[0] = cost_of(s[id], o[id], feas_mode);
+            v[1] = (long long)s[id] + o[id];
+            v[2] = (long long)ga * s[id] + (long long)gb * o[id];
+        }
+        scan3(v, carry);
+        if (i < kmax) {
+            cost[i + 1] = (int)v[0];
+            if (v[1] <= (long long)M && dp_better(v[2], i + 1, 0, bS, bk, bm, KVSCHED_TIE_LARGER)) bS = v[2], bk = i + 1;
+        }
+    }
+    if (tid == 0) cost[0] = 0;
+    reduce_best(KVSCHED_TIE_LARGER, L, bS, bk, bm);
+    // least k whose k smallest values (at least gb o + ga each) could do as well
+    if (tid == 0) L.sh[0] = kmax;
+    __syncthreads();
+    carry[0] = carry[1] = carry[2] = 0;
+    for (int tile = 0; tile < kmax; tile += DP_T) {
+        const int i = tile + tid;
+        long long v[3] = {0, 0, 0};
+        if (i < kmax) v[0] = (long long)gb * o[left_by_o[i]] + ga;
+        scan3(v, carry);
+        if (i < kmax && bk > 0 && dp_cmp_F(v[0], i + 1, bS, bk) <= 0) atomicMin(&L.sh[0], i + 1);
+    }
+    __syncthreads();
+    const int kmin = bk > 0 ? L.sh[0] : 1;
+    __syncthreads();
+    return kmin;
+}
+
+// The plan of a batch over the r requests proc[0 .. r) (DP_G more entries that join nothing).
+__device__ void plan_body(const int *proc, int r, int kmin, int kmax, const int32_t *s, const int32_t *o, int32_t M,
+                          int32_t ga, int32_t gb, int32_t feas_mode, const int *cost, int4 *req, int2 *range)
+{
+    for (int t = threadIdx.x; t < r + DP_G; t += DP_T) {
+        int4 q = make_int4(M + 1, 0, 0, 0);
+        if (t < r) {
+            const int id = proc[t], sv = s[id], ov = o[id];
+            q = make_int4(feas_mode ? sv : sv + ov, ov, ga * sv + gb * ov, 0);
+        }
+        req[t] = q;
+    }
+    for (int k = threadIdx.x; k <= kmax; k += DP_T) {
+        const int more = feas_mode ? k : 0;
+        range[k] = make_int2(cost[k] - more, M - more - (kmin > k ? cost[kmin - k] : 0));
+    }
+}
+
+// What the host waits for between batches.
+__device__ __forceinline__ void tell_host(int32_t *words, int32_t *host, int32_t seq, int r, int kmax, int kmin)
+{
+    words[KVS_W_REMAIN] = r;
+    words[KVS_W_KMAX] = kmax;
+    host[KVS_H_REMAIN] = r;
+    host[KVS_H_KMAX] = kmax;
+    host[KVS_H_KMIN] = kmin;
+    __threadfence_system();
+    __hip_atomic_store(&host[KVS_H_SEQ], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
+                                                          int32_t ga, int32_t gb, int32_t feas_mode, int *proc, int *by_o,
+                                                          int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o,
+                                                          int *cost, int4 *req, int2 *range, int32_t *words,
+                                                          int32_t *num_batches_out, int32_t *host, int32_t seq)
 {
     __shared__ HelperLds L;
-    int kept, kmax;
-    compact_body(proc, by_cost, tmp, r, nb, batch_of, s, o, feas_mode, M, L, kept, kmax);
-    if (threadIdx.x == 0) {  // the words the host reads
-        words[KVS_W_REMAIN] = kept;
-        words[KVS_W_KMAX] = kmax;
+    const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
+                                  num_batches_out, L);
+    if (kmax < 0) {
+        if (threadIdx.x == 0) tell_host(words, host, seq, 0, 0, 0);
+        return;
     }
+    for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
+    __threadfence_block();
+    __syncthreads();
+    const int kmin = bounds_body(by_cost, left_by_o, kmax, s, o, M, ga, gb, feas_mode, cost, L);
+    plan_body(proc, n, kmin, kmax, s, o, M, ga, gb, feas_mode, cost, req, range);
+    if (threadIdx.x == 0) tell_host(words, host, seq, n, kmax, kmin);
+}
+
+// The end of a batch: its best state from the rows' (partial[k - kmin]), its members, the remaining requests and the
+// bounds of the next batch.
+__global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long long *partial, const unsigned long long *bits,
+                                                         int *proc, int *by_cost, int *left_by_o, int *tmp, int *batch_of,
+                                                         int *cost, int4 *req, int2 *range, int r, int kmin, int kmax, int Mp, const int32_t *s,
+                                                         const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+                                                         int32_t feas_mode, int32_t tie_rule, int32_t done, int32_t nb,
+                                                         int32_t *batch_end_out, double *F_out, int32_t *words,
+                                                         int32_t *host, int32_t seq)
+{
+    __shared__ HelperLds L;
+    __shared__ int load[KVSCHED_EXACT_MAX_N];
+    long long bS = 0;
+    int bk = 0, bm = 0;
+    for (int k = kmin + threadIdx.x; k <= kmax; k += DP_T) {
+        const unsigned long long v = partial[k - kmin];
+        const unsigned S = (unsigned)(v >> 32);
+        if (S < DP_NONE && dp_better(S, k, (int)(unsigned)v, bS, bk, bm, tie_rule)) bS = S, bk = k, bm = (int)(unsigned)v;
+    }
+    for (int t = threadIdx.x; t < r; t += DP_T) load[t] = req[t].x;
+    reduce_best(tie_rule, L, bS, bk, bm);
+    if (threadIdx.x == 0) publish_batch(bS, bk, gb, done, nb, batch_end_out, F_out, words);
+    __syncthreads();
+    if (threadIdx.x < 64) walk_body(bits, proc, r, kmax, Mp, load, nb, batch_of, bk, bm);
+    __threadfence_block();
+    __syncthreads();
+    int kept, knext, next_min = 0;
+    compact_body(proc, by_cost, left_by_o, tmp, r, nb, batch_of, s, o, feas_mode, M, L, kept, knext);
+    if (kept > 0) {
+        next_min = bounds_body(by_cost, left_by_o, knext, s, o, M, ga, gb, feas_mode, cost, L);
+        plan_body(proc, kept, next_min, knext, s, o, M, ga, gb, feas_mode, cost, req, range);
+    }
+    if (threadIdx.x == 0) tell_host(words, host, seq, kept, knext, next_min);
 }
 
 // The (o, id)-sorted ids ordered by batch number (stable): each batch in nondecreasing o.
@@ -432,7 +605,7 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
     __shared__ HelperLds L;
     __shared__ int tab[2][DP_SMALL_STATES];
     __shared__ int req_o[DP_SMALL_N], req_load[DP_SMALL_N], req_g[DP_SMALL_N];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int Mp = 1 << lg;
     int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words, num_batches_out, L);
     if (kmax < 0) return;
@@ -488,11 +661,11 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
         if (bk < 1) break;  // uniform
         __threadfence_block();
         __syncthreads();
-        if (wave == 0) walk_body(bits, proc, r, kmax, Mp, s, o, feas_mode, nb, batch_of, bk, bm);
+        if (tid < 64) walk_body(bits, proc, r, kmax, Mp, req_load, nb, batch_of, bk, bm);
         __threadfence_block();
         __syncthreads();
         int kept, knext;
-        compact_body(proc, by_cost, buf0, r, nb, batch_of, s, o, feas_mode, M, L, kept, knext);
+        compact_body(proc, by_cost, nullptr, buf0, r, nb, batch_of, s, o, feas_mode, M, L, kept, knext);
         if (kept >= r) break;  // cannot happen: a batch has at least one member; never spin
         r = kept;
         kmax = knext;
@@ -506,64 +679,82 @@ bool launched() { return hipGetLastError() == hipSuccess; }
 
 }  // namespace
 
+// Lists of ids (and, last, the sums of the least costs) of a construction over n requests.
+struct DpLists {
+    int *proc, *by_o, *by_cost, *buf0, *buf1, *batch_of, *left_by_o, *cost;
+    int4 *req;
+    int2 *range;
+};
+
+static DpLists dp_lists(void *lists, int32_t n)
+{
+    const size_t np = ((size_t)n + 64) & ~(size_t)63;
+    int *p = (int *)lists;
+    return DpLists{p,          p + np,     p + 2 * np, p + 3 * np, p + 4 * np,
+                   p + 5 * np, p + 6 * np, p + 7 * np, (int4 *)(p + 8 * np), (int2 *)(p + 12 * np + 64)};
+}
+
+static int dp_row(int32_t M) { return (int)(((size_t)M + DP_STEP_M) & ~(size_t)(DP_STEP_M - 1)); }  // >= M + 1
+
 size_t kvs_exact_dp_list_bytes(int32_t n)
 {
     const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    return np * 6 * sizeof(int) + 256;
+    return np * 14 * sizeof(int) + 1024;
 }
 
 size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M)
 {
-    const size_t Mp = ((size_t)M + DP_STEP_T) & ~(size_t)(DP_STEP_T - 1);
-    return 2 * (size_t)(kmax + 1) * Mp * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (Mp / 8) +
-           3 * sizeof(long long) * DP_ARGMIN_BLOCKS + 256;
+    const size_t Mp = (size_t)dp_row(M);
+    return 2 * (size_t)(kmax + 1 + DP_G) * Mp * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (Mp / 8) +
+           sizeof(long long) * (size_t)(kmax + 1) + 256;
 }
 
-int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t feas_mode,
-                                void *lists, int32_t *d_words, int32_t *num_batches_out, hipStream_t st)
+int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+                                int32_t feas_mode, void *lists, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
+                                int32_t seq, hipStream_t st)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    int *proc = (int *)lists, *by_o = proc + np, *by_cost = by_o + np, *buf0 = by_cost + np, *buf1 = buf0 + np,
-        *batch_of = buf1 + np;
-    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, feas_mode, proc, by_o, by_cost, buf0,
-                       buf1, batch_of, d_words, num_batches_out);
+    const DpLists l = dp_lists(lists, n);
+    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, l.proc, l.by_o,
+                       l.by_cost, l.buf0, l.buf1, l.batch_of, l.left_by_o, l.cost, l.req, l.range, d_words,
+                       num_batches_out, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
 // One batch over the r remaining requests: tables, records, best state, members, compaction.
-int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmax, const int32_t *s, const int32_t *o, int32_t M,
-                              int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb, void *lists, void *tables,
-                              int32_t *batch_end_out, double *F_out, int32_t *d_words, hipStream_t st)
+int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
+                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
+                              void *lists, void *tables, int32_t *batch_end_out, double *F_out, int32_t *d_words,
+                              int32_t *host, int32_t seq, hipStream_t st)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    int *proc = (int *)lists, *by_cost = proc + 2 * np, *buf0 = by_cost + np, *batch_of = buf0 + 2 * np;
-    const int Mp = (int)(((size_t)M + DP_STEP_T) & ~(size_t)(DP_STEP_T - 1));
-    const size_t table = (size_t)(kmax + 1) * Mp;
-    int *dp[2] = {(int *)tables, (int *)tables + table};
-    unsigned long long *bits = (unsigned long long *)((int *)tables + 2 * table);
+    const DpLists l = dp_lists(lists, n);
+    const int Mp = dp_row(M);
+    const size_t table = (size_t)(kmax + 1 + DP_G) * Mp;
+    unsigned *dp[2] = {(unsigned *)tables, (unsigned *)tables + table};
+    unsigned long long *bits = (unsigned long long *)((unsigned *)tables + 2 * table);
     const size_t per_t = (size_t)(kmax + 1) * (Mp >> 6);
-    hipLaunchKernelGGL(dp_init_kernel, dim3((unsigned)((table + DP_STEP_T - 1) / DP_STEP_T)), dim3(DP_STEP_T), 0, st,
-                       dp[0], dp[1], table);
-    if (!launched()) return KVSCHED_EHIP;
-    for (int32_t t = 0; t < r; ++t) {
-        const int rows = t + 1 < kmax ? t + 1 : kmax;  // after t + 1 requests no set is larger
-        hipLaunchKernelGGL(dp_step_kernel, dim3((unsigned)(Mp / DP_STEP_T), (unsigned)rows), dim3(DP_STEP_T), 0, st,
-                           proc, t, s, o, M, ga, gb, feas_mode, dp[t & 1], dp[(t + 1) & 1], bits + (size_t)t * per_t, Mp);
-        if (!launched()) return KVSCHED_EHIP;
+    hipLaunchKernelGGL(dp_init_kernel, dim3((unsigned)((2 * table + DP_STEP_T - 1) / DP_STEP_T)), dim3(DP_STEP_T), 0, st,
+                       dp[0], 2 * table, table, Mp);
+    const DpPlan plan{l.req, l.range};
+    int at = 0;
+    for (int32_t t = 0; t < r; t += DP_G, at ^= 1) {
+        const int behind = t + DP_G < r ? t + DP_G : r;  // requests offered when this launch is done
+        const int top = behind < kmax ? behind : kmax;   // no set is larger
+        // the launch has to leave every row that a set of kmin can still be reached from, after each of its requests
+        const int first = kmin - (r - t) + 1 > 1 ? kmin - (r - t) + 1 : 1;
+        const dim3 grid((unsigned)(Mp / DP_STEP_M), (unsigned)(top - first + 1));
+        if (feas_mode)
+            hipLaunchKernelGGL((dp_step_kernel<1>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, dp[at], dp[at ^ 1], bits, per_t,
+                               Mp, first);
+        else
+            hipLaunchKernelGGL((dp_step_kernel<0>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, dp[at], dp[at ^ 1], bits, per_t,
+                               Mp, first);
     }
-    const int G = kmax < DP_ARGMIN_BLOCKS ? kmax : DP_ARGMIN_BLOCKS;
-    long long *partial = (long long *)(bits + (size_t)r * per_t);
-    hipLaunchKernelGGL(dp_argmin_rows_kernel, dim3((unsigned)G), dim3(DP_T), 0, st, dp[r & 1], kmax, M, Mp, tie_rule,
-                       partial);
-    if (!launched()) return KVSCHED_EHIP;
-    hipLaunchKernelGGL(dp_argmin_kernel, dim3(1), dim3(DP_T), 0, st, partial, G, tie_rule, gb, n - r, nb, batch_end_out,
-                       F_out, d_words);
-    if (!launched()) return KVSCHED_EHIP;
-    hipLaunchKernelGGL(dp_walk_kernel, dim3(1), dim3(64), 0, st, bits, proc, r, kmax, Mp, s, o, feas_mode, nb, batch_of,
-                       d_words);
-    if (!launched()) return KVSCHED_EHIP;
-    hipLaunchKernelGGL(dp_compact_kernel, dim3(1), dim3(DP_T), 0, st, proc, by_cost, buf0, r, nb, batch_of, s, o,
-                       feas_mode, M, d_words);
+    unsigned long long *partial = bits + (size_t)r * per_t;
+    hipLaunchKernelGGL(dp_argmin_rows_kernel, dim3((unsigned)(kmax - kmin + 1)), dim3(DP_T), 0, st, dp[at], kmin, Mp,
+                       plan, partial);
+    hipLaunchKernelGGL(dp_finish_kernel, dim3(1), dim3(DP_T), 0, st, partial, bits, l.proc, l.by_cost, l.left_by_o, l.buf0,
+                       l.batch_of, l.cost, l.req, l.range, r, kmin, kmax, Mp, s, o, M, ga, gb, feas_mode, tie_rule, n - r, nb, batch_end_out,
+                       F_out, d_words, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
@@ -588,11 +779,9 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
                               int32_t *batch_end_out, double *F_out, int32_t *num_batches_out, int32_t *d_words,
                               hipStream_t st)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    int *proc = (int *)lists, *by_o = proc + np, *by_cost = by_o + np, *buf0 = by_cost + np, *buf1 = buf0 + np,
-        *batch_of = buf1 + np;
-    hipLaunchKernelGGL(dp_small_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, proc, by_o,
-                       by_cost, buf0, buf1, batch_of, (unsigned long long *)records, order_out, batch_end_out, F_out,
+    const DpLists l = dp_lists(lists, n);
+    hipLaunchKernelGGL(dp_small_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
+                       l.by_cost, l.buf0, l.buf1, l.batch_of, (unsigned long long *)records, order_out, batch_end_out, F_out,
                        num_batches_out, d_words);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }
@@ -600,9 +789,8 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
 int kvs_launch_exact_dp_emit(int32_t n, int32_t nb, void *lists, int32_t *order_out, int32_t *num_batches_out,
                              hipStream_t st)
 {
-    const size_t np = ((size_t)n + 64) & ~(size_t)63;
-    int *proc = (int *)lists, *by_o = proc + np, *buf0 = proc + 3 * np, *buf1 = buf0 + np, *batch_of = buf1 + np;
-    hipLaunchKernelGGL(dp_emit_kernel, dim3(1), dim3(DP_T), 0, st, n, by_o, buf0, buf1, batch_of, nb, order_out,
+    const DpLists l = dp_lists(lists, n);
+    hipLaunchKernelGGL(dp_emit_kernel, dim3(1), dim3(DP_T), 0, st, n, l.by_o, l.buf0, l.buf1, l.batch_of, nb, order_out,
                        num_batches_out);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }

@@ -13,8 +13,6 @@ enum {
     KVS_W_MINPOS = 2,  // smallest position any move touches (best_neighbor)
     KVS_W_REMAIN = 3,  // exact DP: requests not yet in a batch
     KVS_W_KMAX = 4,    // exact DP: bound on the size of the next batch
-    KVS_W_BESTK = 5,   // exact DP: best state of the batch in hand
-    KVS_W_BESTM = 6,
     KVS_W_ESTMAX = 7,  // largest initial estimate (kvsched_simulate_predicted)
     KVS_W_MAXPOS = 8,  // largest position any move touches (best_neighbor), -1: none
     KVS_W_COUNT = 16,  // (what kvsched_device_status and the waits of kvsched_exact_dp read back)
@@ -32,7 +30,17 @@ enum {
 };
 
 // What the length scan leaves in pinned host memory for a call that waits for it.
-enum { KVS_H_OMAX = 0, KVS_H_MINPOS = 1, KVS_H_MAXPOS = 2, KVS_H_SEQ = 3, KVS_H_COUNT = 16 };
+// ... and what the exact DP leaves there between batches.
+enum {
+    KVS_H_OMAX = 0,
+    KVS_H_MINPOS = 1,
+    KVS_H_MAXPOS = 2,
+    KVS_H_SEQ = 3,  // number of the launch that has written the others
+    KVS_H_REMAIN = 4,
+    KVS_H_KMAX = 5,
+    KVS_H_KMIN = 6,
+    KVS_H_COUNT = 16
+};
 
 struct kvsched_ctx {
     int device;
@@ -165,12 +173,15 @@ int kvs_launch_neighbor_finish(const int64_t *tel, const int32_t *rejoin, const 
 // exactdp.hip
 size_t kvs_exact_dp_list_bytes(int32_t n);
 size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M);
-int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t feas_mode,
-                                void *lists, int32_t *d_words, int32_t *num_batches_out, hipStream_t st);
-// ga, gb: the metric's numerator sums ga s_i + gb o_i (0, 1: the F-metric; else G with alpha = ga / gb)
-int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmax, const int32_t *s, const int32_t *o, int32_t M,
-                              int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb, void *lists, void *tables,
-                              int32_t *batch_end_out, double *F_out, int32_t *d_words, hipStream_t st);
+// (host, seq: pinned words that receive the requests left and the bounds kmin..kmax on the next batch's size, then seq;
+// ga, gb: the metric's numerator sums ga s_i + gb o_i -- 0, 1: the F-metric; else G with alpha = ga / gb)
+int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+                                int32_t feas_mode, void *lists, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
+                                int32_t seq, hipStream_t st);
+int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
+                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
+                              void *lists, void *tables, int32_t *batch_end_out, double *F_out, int32_t *d_words,
+                              int32_t *host, int32_t seq, hipStream_t st);
 int kvs_exact_dp_small_lg(int32_t n, int32_t kmax_bound, int32_t M);
 size_t kvs_exact_dp_small_record_bytes(int32_t n, int32_t kmax_bound, int lg);
 int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
