@@ -2,10 +2,10 @@
 
 hipcc cross-compiles without a GPU, so this runs anywhere the ROCm toolchain is installed.
 
-timeline_reg.hip keeps per-timeline state in a block of physical VGPRs (v30 upward) that only
-its inline-assembly blocks touch.  That is sound only while everything the compiler allocates in those
-kernels (its own code and the operand registers it hands to the assembly statements) stays below v30,
-so the build emits the device assembly of that file and fails if a timeline_reg_kernel names a VGPR of
+timeline_reg.hip and predicted.hip keep per-timeline state in a block of physical VGPRs (v30 / v60 upward) that
+only their inline-assembly blocks touch.  That is sound only while everything the compiler allocates in those
+kernels (its own code and the operand registers it hands to the assembly statements) stays below the block,
+so the build emits the device assembly of these files and fails if such a kernel names a VGPR of
 the block anywhere but in the hand-written row code, or if it did not see every instantiation.
 """
 from __future__ import annotations
@@ -29,6 +29,7 @@ DEVICE_FLAGS = [
 ]
 FLAGS = DEVICE_FLAGS + ["-fPIC", "-shared", "-Wall", "-Wno-unused-function"]
 RESERVED_VGPR_BASE = 30  # KVS_PB in timeline_reg.hip
+PREDICTED_VGPR_BASE = 60  # KVP_PB in predicted.hip
 
 
 def lib_path() -> str:
@@ -52,8 +53,14 @@ def timeline_reg_instantiations() -> int:
     return launches * sizes
 
 
-def reserved_vgpr_scan(asm_text: str, base: int = RESERVED_VGPR_BASE) -> tuple[list[str], int]:
-    """(offending lines, kernel bodies scanned) for the timeline_reg_kernel bodies of a device assembly.
+def predicted_reg_instantiations() -> int:
+    src = open(os.path.join(CSRC, "predicted.hip")).read()
+    return len(re.findall(r"\(const void \*\)predicted_reg_kernel<\d+>", src))
+
+
+def reserved_vgpr_scan(asm_text: str, base: int = RESERVED_VGPR_BASE,
+                       kernel: str = "timeline_reg_kernel") -> tuple[list[str], int]:
+    """(offending lines, kernel bodies scanned) for the bodies of `kernel` in a device assembly.
 
     The profile block of an instantiation with NR rows (read off the kernel's mangled name) is
     v[base, base + NR).  It belongs to the hand-written assembly alone, which names it only as
@@ -70,7 +77,7 @@ def reserved_vgpr_scan(asm_text: str, base: int = RESERVED_VGPR_BASE) -> tuple[l
     top = base
     for line in asm_text.splitlines():
         s = line.strip()
-        m = re.match(r"^_Z\w*timeline_reg_kernelILi(\d+)E\w*:", s)
+        m = re.match(r"^_Z\w*" + kernel + r"ILi(\d+)E\w*:", s)
         if m:
             in_kernel, in_asm = True, False
             top = base + int(m.group(1))
@@ -101,24 +108,30 @@ def reserved_vgpr_violations(asm_text: str, base: int = RESERVED_VGPR_BASE) -> l
     return reserved_vgpr_scan(asm_text, base)[0]
 
 
-def emit_timeline_reg_assembly(hipcc: str) -> str:
+def emit_assembly(hipcc: str, source: str) -> str:
     with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "timeline_reg.s")
-        cmd = [hipcc, *DEVICE_FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "timeline_reg.hip"), "-o", out]
+        out = os.path.join(tmp, "device.s")
+        cmd = [hipcc, *DEVICE_FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", out]
         subprocess.check_call(cmd, stderr=subprocess.DEVNULL)
         return open(out).read()
 
 
+def emit_timeline_reg_assembly(hipcc: str) -> str:
+    return emit_assembly(hipcc, "timeline_reg.hip")
+
+
 def check_reserved_vgprs(hipcc: str, verbose: bool = False) -> None:
-    bad, bodies = reserved_vgpr_scan(emit_timeline_reg_assembly(hipcc))
-    want = timeline_reg_instantiations()
-    if bodies != want or want == 0:
-        raise RuntimeError(f"scanned {bodies} timeline_reg_kernel bodies, the launcher can reach {want}")
-    if bad:
-        raise RuntimeError("the reserved VGPR block (v%d..) is named outside the hand-written row code:\n  "
-                           % RESERVED_VGPR_BASE + "\n  ".join(bad[:10]))
-    if verbose:
-        print(f"reserved VGPR block untouched in all {bodies} timeline_reg_kernel bodies", flush=True)
+    for source, kernel, base, want in (
+            ("timeline_reg.hip", "timeline_reg_kernel", RESERVED_VGPR_BASE, timeline_reg_instantiations()),
+            ("predicted.hip", "predicted_reg_kernel", PREDICTED_VGPR_BASE, predicted_reg_instantiations())):
+        bad, bodies = reserved_vgpr_scan(emit_assembly(hipcc, source), base, kernel)
+        if bodies != want or want == 0:
+            raise RuntimeError(f"scanned {bodies} {kernel} bodies, the launcher can reach {want}")
+        if bad:
+            raise RuntimeError("the reserved VGPR block (v%d..) is named outside the hand-written row code:\n  "
+                               % base + "\n  ".join(bad[:10]))
+        if verbose:
+            print(f"reserved VGPR block untouched in all {bodies} {kernel} bodies", flush=True)
 
 
 def build(verbose: bool = False) -> str:

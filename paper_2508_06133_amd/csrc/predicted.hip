@@ -499,6 +499,587 @@ __global__ __launch_bounds__(PW) void predicted_kernel(PredParams p)
     }
 }
 
+// The same with the projected memory in vector registers (H <= 4096): row r of lane l is round b + 64 r + l, with b
+// kept at 64 floor((t + 1) / 64), so that round t + 1 lies in row 0 and every loop over rounds names its registers at
+// compile time; when t passes a multiple of 64 the rows move down by one.  Rounds at or before t keep stale values.
+//
+// What bounds the call is the number of candidates in flight times the chain of dependent instructions each is: with the
+// ring and entries of 14 bytes in LDS eight fit a compute unit (two wavefronts per SIMD, some nine cycles an
+// instruction).  Without the ring, and with s left to a table look-up when an entry is handled (10 bytes an entry), 10 KB
+// a candidate let sixteen in; the entries due in one round are handled lane by lane instead of one after the other.
+// 4096 candidates of n = 2000, M = 131072: 16.1 -> 9.4 ms.
+//
+// List entry: position | id << 16 and o | estimate << 16, and the low 16 bits of the round it next matters at.
+// The rows of projected memory live in physical vector registers (KVP_PB upward) that only the assembly statements
+// below touch: a C++ array of this size under this kernel's control flow becomes copies of the whole file at every way
+// out of a loop over rows.  The compiler's own registers have to stay below the block, which the build checks on the
+// emitted assembly (as for the timeline kernel).  Every statement waits out what the compiler may have issued just before
+// (an SGPR written by a vector instruction needs two instructions, as a lane select four, before it is used) and keeps two
+// instructions between a compare and the use of VCC.  A pass over rows ends when the rounds left run out.
+#define KVP_PB "60"
+#define KVP_CLOB_9 "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68"
+#define KVP_CLOB_17 KVP_CLOB_9, "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76"
+#define KVP_CLOB_33 KVP_CLOB_17, "v77", "v78", "v79", "v80", "v81", "v82", "v83", "v84", "v85", "v86", "v87", "v88", "v89", "v90",  \
+    "v91", "v92"
+#define KVP_CLOB_65 KVP_CLOB_33, "v93", "v94", "v95", "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105",  \
+    "v106", "v107", "v108", "v109", "v110", "v111", "v112", "v113", "v114", "v115", "v116", "v117",  \
+    "v118", "v119", "v120", "v121", "v122", "v123", "v124"
+
+#define KVP_FOR_NR(STMT)                                                                 \
+    do {                                                                                 \
+        static_assert(NR == 9 || NR == 17 || NR == 33 || NR == 65, "register files");    \
+        if constexpr (NR == 9) {                                                         \
+            STMT(KVP_CLOB_9);                                                            \
+        } else if constexpr (NR == 17) {                                                 \
+            STMT(KVP_CLOB_17);                                                           \
+        } else if constexpr (NR == 33) {                                                 \
+            STMT(KVP_CLOB_33);                                                           \
+        } else {                                                                         \
+            STMT(KVP_CLOB_65);                                                           \
+        }                                                                                \
+    } while (0)
+
+template <int NR>
+__device__ __forceinline__ void rows_clear()
+{
+#define KVP_STMT(CLOB)                                    \
+    asm volatile(".set kvs_r, 0\n"                        \
+                 ".rept %c[nr]\n"                         \
+                 "  v_mov_b32 v[" KVP_PB "+kvs_r], 0\n"   \
+                 "  .set kvs_r, kvs_r+1\n"                \
+                 ".endr\n"                                \
+                 :                                        \
+                 : [nr] "n"(NR)                           \
+                 : CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+}
+
+// every row takes the next one's place; an empty one enters
+template <int NR>
+__device__ __forceinline__ void rows_down()
+{
+#define KVP_STMT(CLOB)                                                          \
+    asm volatile(".set kvs_r, 0\n"                                              \
+                 ".rept %c[nr]-1\n"                                             \
+                 "  v_mov_b32 v[" KVP_PB "+kvs_r], v[" KVP_PB "+kvs_r+1]\n"     \
+                 "  .set kvs_r, kvs_r+1\n"                                      \
+                 ".endr\n"                                                      \
+                 "v_mov_b32 v[" KVP_PB "+%c[nr]-1], 0\n"                        \
+                 :                                                              \
+                 : [nr] "n"(NR)                                                 \
+                 : CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+}
+
+// Rows += first + j for the rounds with 0 <= j < count (j: the lane's in row 0); left >= 0: the last of those rounds as
+// row and lane.  Returns the most any row visited holds afterwards.
+template <int NR>
+__device__ __forceinline__ int rows_add(int left, int j, int count, int first)
+{
+    int most, y;
+#define KVP_STMT(CLOB)                                                              \
+    asm volatile("s_nop 4\n"                                                        \
+                 "v_mov_b32 %[most], 0\n"                                           \
+                 ".set kvs_r, 0\n"                                                  \
+                 ".rept %c[nr]\n"                                                   \
+                 "  v_cmp_gt_u32 vcc, %[count], %[j]\n"                             \
+                 "  v_add_u32 %[y], %[first], %[j]\n"                               \
+                 "  v_add_u32 %[j], 64, %[j]\n"                                     \
+                 "  v_cndmask_b32 %[y], 0, %[y], vcc\n"                             \
+                 "  v_add_u32 v[" KVP_PB "+kvs_r], %[y], v[" KVP_PB "+kvs_r]\n"     \
+                 "  v_max_i32 %[most], %[most], v[" KVP_PB "+kvs_r]\n"              \
+                 "  s_sub_u32 %[left], %[left], 64\n"                               \
+                 "  s_cbranch_scc1 9f\n"                                            \
+                 "  .set kvs_r, kvs_r+1\n"                                          \
+                 ".endr\n"                                                          \
+                 "9:\n"                                                             \
+                 : [most] "=&v"(most), [y] "=&v"(y), [j] "+v"(j), [left] "+s"(left) \
+                 : [count] "s"(count), [first] "s"(first), [nr] "n"(NR)             \
+                 : "vcc", "scc", CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+    return most;
+}
+
+// ... and the same taken off again.
+template <int NR>
+__device__ __forceinline__ void rows_take(int left, int j, int count, int first)
+{
+    int y;
+#define KVP_STMT(CLOB)                                                              \
+    asm volatile("s_nop 4\n"                                                        \
+                 ".set kvs_r, 0\n"                                                  \
+                 ".rept %c[nr]\n"                                                   \
+                 "  v_cmp_gt_u32 vcc, %[count], %[j]\n"                             \
+                 "  v_add_u32 %[y], %[first], %[j]\n"                               \
+                 "  v_add_u32 %[j], 64, %[j]\n"                                     \
+                 "  v_cndmask_b32 %[y], 0, %[y], vcc\n"                             \
+                 "  v_sub_u32 v[" KVP_PB "+kvs_r], v[" KVP_PB "+kvs_r], %[y]\n"     \
+                 "  s_sub_u32 %[left], %[left], 64\n"                               \
+                 "  s_cbranch_scc1 9f\n"                                            \
+                 "  .set kvs_r, kvs_r+1\n"                                          \
+                 ".endr\n"                                                          \
+                 "9:\n"                                                             \
+                 : [y] "=&v"(y), [j] "+v"(j), [left] "+s"(left)                     \
+                 : [count] "s"(count), [first] "s"(first), [nr] "n"(NR)             \
+                 : "vcc", "scc", CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+}
+
+// Per lane: the largest min(tq, row + bias + tq) over its rounds tq with 0 <= k <= span (k, tq: the lane's in row 0).
+template <int NR>
+__device__ __forceinline__ int rows_bound(int left, int k, int span, int tq, int bias)
+{
+    int acc, y, none;
+#define KVP_STMT(CLOB)                                                                       \
+    asm volatile("s_nop 4\n"                                                                 \
+                 "v_mov_b32 %[none], 0x80000001\n"                                           \
+                 "v_mov_b32 %[acc], %[none]\n"                                               \
+                 ".set kvs_r, 0\n"                                                           \
+                 ".rept %c[nr]\n"                                                            \
+                 "  v_cmp_ge_u32 vcc, %[span], %[k]\n"                                       \
+                 "  v_add_u32 %[y], %[bias], %[tq]\n"                                        \
+                 "  v_add_u32 %[y], %[y], v[" KVP_PB "+kvs_r]\n"                             \
+                 "  v_min_i32 %[y], %[tq], %[y]\n"                                           \
+                 "  v_cndmask_b32 %[y], %[none], %[y], vcc\n"                                \
+                 "  v_max_i32 %[acc], %[acc], %[y]\n"                                        \
+                 "  v_add_u32 %[k], 64, %[k]\n"                                              \
+                 "  v_add_u32 %[tq], 64, %[tq]\n"                                            \
+                 "  s_sub_u32 %[left], %[left], 64\n"                                        \
+                 "  s_cbranch_scc1 9f\n"                                                     \
+                 "  .set kvs_r, kvs_r+1\n"                                                   \
+                 ".endr\n"                                                                   \
+                 "9:\n"                                                                      \
+                 : [acc] "=&v"(acc), [y] "=&v"(y), [none] "=&v"(none), [k] "+v"(k), [tq] "+v"(tq), [left] "+s"(left) \
+                 : [span] "s"(span), [bias] "s"(bias), [nr] "n"(NR)                          \
+                 : "vcc", "scc", CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+    return acc;
+}
+
+// Lane `at` of row 0.
+template <int NR>
+__device__ __forceinline__ int row0_lane(int at)
+{
+    int v;
+#define KVP_STMT(CLOB)                                        \
+    asm volatile("s_nop 4\n"                                  \
+                 "v_readlane_b32 %[v], v[" KVP_PB "], %[at]\n" \
+                 : [v] "=s"(v)                                \
+                 : [at] "s"(at)                               \
+                 : CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+    return v;
+}
+
+// Row r, 0 <= r < NR (a computed jump to one of NR moves, eight bytes apart).
+template <int NR>
+__device__ __forceinline__ int row_of(int r)
+{
+    int v;
+#define KVP_STMT(CLOB)                                           \
+    asm volatile("s_lshl_b32 %[r], %[r], 3\n"                    \
+                 "s_getpc_b64 s[66:67]\n"                        \
+                 "8:\n"                                          \
+                 "s_add_u32 %[r], %[r], 7f-8b\n"                 \
+                 "s_add_u32 s66, s66, %[r]\n"                    \
+                 "s_addc_u32 s67, s67, 0\n"                      \
+                 "s_setpc_b64 s[66:67]\n"                        \
+                 "7:\n"                                          \
+                 ".set kvs_r, 0\n"                               \
+                 ".rept %c[nr]\n"                                \
+                 "  v_mov_b32 %[v], v[" KVP_PB "+kvs_r]\n"       \
+                 "  s_branch 9f\n"                               \
+                 "  .set kvs_r, kvs_r+1\n"                       \
+                 ".endr\n"                                       \
+                 "9:\n"                                          \
+                 : [v] "=v"(v), [r] "+s"(r)                      \
+                 : [nr] "n"(NR)                                  \
+                 : "scc", "s66", "s67", CLOB)
+    KVP_FOR_NR(KVP_STMT);
+#undef KVP_STMT
+    return v;
+}
+
+template <int NR>
+__global__ __launch_bounds__(PW) void predicted_reg_kernel(PredParams p)
+{
+    extern __shared__ int lds[];
+    const int lane = threadIdx.x;
+    const int cand = blockIdx.x;
+    if (p.second && p.retry[cand] == 0) return;
+    const int n = p.n, M = p.M, cap = p.cap;
+    constexpr int H = 64 * (NR - 1);  // longest estimate and decode length
+    const int stw = (n + 31) >> 5;
+    unsigned *WAIT = (unsigned *)lds;   // bit k & 31 of word k >> 5: position k waits (below the frontier)
+    int *LPI = (int *)(WAIT + stw);     // the running list
+    int *LOE = LPI + cap;
+    unsigned short *LDUE = (unsigned short *)(LOE + cap);
+    unsigned short *est_stopped = p.est_stopped + (size_t)cand * (size_t)n;
+
+    const int32_t *row = p.orders + (size_t)cand * (size_t)n;
+    const int32_t *est0 = p.est0 + (p.E > 1 ? (size_t)cand * (size_t)n : 0);
+    int32_t *crow = p.completion_out ? p.completion_out + (size_t)cand * (size_t)n : nullptr;
+
+    for (int i = lane; i < stw; i += PW) WAIT[i] = 0;  // nobody was stopped yet
+    int bad = 0;
+    for (int k = lane; k < n; k += PW) {
+        const int id = min(max(row[k], 0), n - 1);
+        const int sv = p.s[id], ov = p.o[id], ev = est0[id];
+        if (sv < 1 || ov < 1 || ev < 1 || ov > p.H || ev > p.H || (long long)sv + ov > (long long)M ||
+            (long long)sv + ev > (long long)M)
+            bad = 1;
+    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // cannot be scheduled: report, do not loop forever
+        if (lane == 0) {
+            p.tel_out[cand] = -1;
+            if (p.evictions_out) p.evictions_out[cand] = 0;
+            atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
+        }
+        return;
+    }
+    p_sync();
+
+    rows_clear<NR>();
+    int b = 0;
+
+    // the 64 positions [w_base, w_base + 64) of the order: lane l holds id, s, o of position w_base + l
+    int w_base = -PW, w_id = 0, w_s = 1, w_o = 1, w_e = 1;
+    int x_base = -PW, x_id = 0, x_s = 1, x_o = 1, x_e = 1;  // ... and the 64 behind them, fetched ahead of need
+    int frontier = 0;  // every position from here on waits and was never started
+    int c_pos = -1, c_s = 0, c_o = 0, c_id = 0, c_e = 0;  // the request stopped last: position, lengths, id, estimate kept
+
+    int t = 0;
+    int head = 0;      // no waiting position lies before it
+    int hpos = -1, hs = 0, he = 0, ho = 0, hid = 0;  // the waiting position the admission is stuck at, if any
+    int ring_start = 0;  // ... and a round before which the reservations rule out its start
+    int nact = 0;      // entries of the list
+    int done = 0;
+    int ov_cnt = 0;    // requests past their estimate ...
+    long long ov_sp = 0;  // ... and the sum of s_j - p_j over them
+    int next_due = INT_MAX;  // earliest round at which a running request reaches its estimate or its end
+    int evictions = 0;
+    long long tel = 0;
+    bool over_limit = false, overflow = false;
+
+    // rounds advance to `to` (> t): rows move down while row 0 ends before round to + 1
+    auto advance = [&](int to) __attribute__((always_inline)) {
+        t = to;
+        const int nb = p_uni((to + 1) & ~63);
+        if (nb - b >= 64 * NR) {
+            rows_clear<NR>();
+            b = nb;
+        }
+        for (; b < nb; b += 64) rows_down<NR>();
+    };
+    // take s + (tq - ps) off rounds tq = t + 1 .. last
+    auto release = [&](int sv, int ps, int last) __attribute__((always_inline)) {
+        rows_take<NR>(p_uni(last - b), b + lane - t - 1, p_uni(last - t), p_uni(sv + t + 1 - ps));
+    };
+    // the reservations of round t + 1
+    auto next_round = [&]() __attribute__((always_inline)) -> int { return row0_lane<NR>(p_uni((t + 1) & 63)); };
+
+    while (done < n) {
+        // (everything the loop carries is the same in all lanes; saying so keeps it on the scalar unit)
+        t = p_uni(t), head = p_uni(head), hpos = p_uni(hpos), hs = p_uni(hs), he = p_uni(he), ho = p_uni(ho), hid = p_uni(hid);
+        ring_start = p_uni(ring_start), nact = p_uni(nact), done = p_uni(done), ov_cnt = p_uni(ov_cnt), ov_sp = p_uni64(ov_sp);
+        next_due = p_uni(next_due), evictions = p_uni(evictions), tel = p_uni64(tel), frontier = p_uni(frontier), b = p_uni(b);
+        c_pos = p_uni(c_pos), c_s = p_uni(c_s), c_o = p_uni(c_o), c_id = p_uni(c_id), c_e = p_uni(c_e);
+        w_base = p_uni(w_base), x_base = p_uni(x_base);
+        if (t >= p.round_limit) { over_limit = true; break; }
+        // nothing waits, nobody outruns an estimate: nothing can happen before the next due round
+        if (head >= n && ov_cnt == 0 && next_due > t) advance(next_due);
+
+        // ---- 1. running requests that reach their estimate or their end at this round: the tiles of the list from the last
+        //         to the first (an entry that fills a hole has then been looked at), the due entries of a tile side by side.
+        if (t >= next_due) {
+            int wait_min = INT_MAX;  // per lane: rounds until its entries matter again
+            for (int a0 = (nact - 1) & ~(PW - 1); a0 >= 0; a0 -= PW) {
+                const int a = a0 + lane;
+                const bool in = a < nact;
+                const int wait = in ? (int)(short)(unsigned short)(LDUE[a] - t) : INT_MAX;  // due - t (at most 16384 ahead)
+                const bool now = wait <= 0;
+                if (!now) wait_min = min(wait_min, wait);
+                const unsigned long long due = __builtin_amdgcn_ballot_w64(now);
+                if (due == 0) continue;
+                // due now: it started min(estimate, o) rounds ago, o rounds ago if it had outrun its estimate
+                int pi = 0, oe = 0, sv = 0;
+                if (now) {
+                    pi = LPI[a];
+                    oe = LOE[a];
+                    sv = p.s[(unsigned)pi >> 16];
+                }
+                const int ol = oe & 0xffff, el = (int)((unsigned)oe >> 16);
+                const int ps = t - (el == EST_OVERRUN ? ol : min(el, ol));
+                const bool fin = now && t - ps == ol;
+                const bool on = now && !fin;  // goes on past its estimate: from now on it reserves the next round only
+                if (on) {
+                    LOE[a] = ol;  // (estimate field EST_OVERRUN)
+                    LDUE[a] = (unsigned short)(ps + ol);
+                    wait_min = min(wait_min, ps + ol - t);
+                }
+                if (crow && fin) crow[(unsigned)pi >> 16] = t;
+                const unsigned long long ends = __builtin_amdgcn_ballot_w64(fin), goes = due & ~ends;
+                const unsigned long long leaves = __builtin_amdgcn_ballot_w64(fin && el == EST_OVERRUN);
+                const int k = __popcll(ends);
+                done += k;
+                tel += (long long)t * k;
+                ov_cnt += __popcll(goes) - __popcll(leaves);
+                const int sp = sv - ps;  // (a running request started at most 16384 rounds ago, s < 2^30)
+                for (unsigned long long m = goes | leaves; m != 0; m &= m - 1) {
+                    const int l = __builtin_ctzll(m);
+                    const long long v = __builtin_amdgcn_readlane(sp, l);
+                    ov_sp += (goes >> l) & 1ull ? v : -v;
+                }
+                for (unsigned long long m = ends & ~leaves; m != 0; m &= m - 1) {
+                    // over-estimated (or exact: nothing left): rounds t+1 .. p + e were reserved for it
+                    const int l = __builtin_ctzll(m);
+                    const int ps_l = __builtin_amdgcn_readlane(ps, l), last = ps_l + __builtin_amdgcn_readlane(el, l);
+                    if (last > t) {
+                        release(__builtin_amdgcn_readlane(sv, l), ps_l, last);
+                        ring_start = 0;  // memory released: the blocked request may fit earlier
+                    }
+                }
+                if (k > 0) {
+                    // the entries behind the first nact - k places that stay fill the holes before them
+                    const int left = nact - k;
+                    const int mp = left + lane;  // a place that goes away
+                    const bool stays = lane < k && !(mp >= a0 && mp < a0 + PW && ((ends >> (mp - a0)) & 1ull));
+                    unsigned long long movers = __builtin_amdgcn_ballot_w64(stays);
+                    unsigned long long hm = __builtin_amdgcn_ballot_w64(fin && a < left);
+                    while (hm != 0) {  // (as many holes as movers)
+                        const int to = a0 + __builtin_ctzll(hm), from = left + __builtin_ctzll(movers);
+                        hm &= hm - 1;
+                        movers &= movers - 1;
+                        if (lane == 0) {
+                            const int e0 = LPI[from], e1 = LOE[from];
+                            const unsigned short e2 = LDUE[from];
+                            LPI[to] = e0, LOE[to] = e1, LDUE[to] = e2;
+                        }
+                    }
+                    nact = left;
+                    p_sync();
+                }
+            }
+            const int w = p_wave_min(wait_min);
+            next_due = w == INT_MAX ? INT_MAX : t + w;
+            p_sync();
+        }
+
+        // ---- 2. admission in the order's sequence
+        const int ov_next = (int)(ov_sp + (long long)ov_cnt * (t + 1));  // the overrunners' share of round t + 1
+        int t_skip = t + 1;  // the next round at which anything can happen
+        while (head < n) {
+            head = p_uni(head), hpos = p_uni(hpos), frontier = p_uni(frontier), nact = p_uni(nact), next_due = p_uni(next_due);
+            ring_start = p_uni(ring_start), t_skip = p_uni(t_skip);
+            if (hpos < 0) {  // first waiting position at or after head; kept while it stays blocked
+                if (head < frontier) {  // among the stopped ones: 32 positions a lane, 2048 a turn
+                    for (int w0 = head >> 5; w0 < stw && hpos < 0; w0 += PW) {
+                        const int wi = w0 + lane;
+                        unsigned wait = wi < stw ? WAIT[wi] : 0u;
+                        if (wi == (head >> 5)) wait &= ~0u << (head & 31);  // not before head
+                        const unsigned long long any = __builtin_amdgcn_ballot_w64(wait != 0);
+                        if (any != 0) {
+                            const int l = __builtin_ctzll(any);
+                            hpos = (w0 + l) * 32 + __builtin_ctz((unsigned)__builtin_amdgcn_readlane((int)wait, l));
+                        }
+                    }
+                    if (hpos < 0) hpos = frontier;  // none: the first position never started
+                } else {
+                    hpos = head;
+                }
+                hpos = p_uni(hpos);
+                if (hpos >= n) { hpos = -1; head = n; break; }
+                head = hpos;
+                if (hpos == c_pos) {
+                    // the request stopped last: what admission needs of it was at hand when it was stopped
+                    hs = c_s, ho = c_o, hid = c_id, he = c_e;
+                } else if (hpos < frontier) {
+                    // an older stopped one: fetched alone (two dependent loads), the window stays at the frontier
+                    hid = p_uni(min(max(row[hpos], 0), n - 1));
+                    hs = p_uni(p.s[hid]);
+                    ho = p_uni(p.o[hid]);
+                    he = p_uni((int)est_stopped[hpos]);  // a stopped request kept its estimate
+                } else {
+                    if (hpos < w_base || hpos >= w_base + PW) {  // the 64 positions around it
+                        const int base = hpos & ~(PW - 1);
+                        if (base == x_base) {  // fetched ahead
+                            w_id = x_id, w_s = x_s, w_o = x_o, w_e = x_e;
+                        } else {
+                            const int k = base + lane;
+                            w_id = 0, w_s = 1, w_o = 1, w_e = 1;
+                            if (k < n) {
+                                w_id = min(max(row[k], 0), n - 1);
+                                w_s = p.s[w_id];
+                                w_o = p.o[w_id];
+                                w_e = est0[w_id];
+                            }
+                        }
+                        w_base = base;
+                        x_base = base + PW;  // the loads for the next 64 are issued now and waited for when used
+                        const int k = x_base + lane;
+                        x_id = 0, x_s = 1, x_o = 1, x_e = 1;
+                        if (k < n) {
+                            x_id = min(max(row[k], 0), n - 1);
+                            x_s = p.s[x_id];
+                            x_o = p.o[x_id];
+                            x_e = est0[x_id];
+                        }
+                    }
+                    hs = __builtin_amdgcn_readlane(w_s, hpos - w_base);
+                    ho = __builtin_amdgcn_readlane(w_o, hpos - w_base);
+                    hid = __builtin_amdgcn_readlane(w_id, hpos - w_base);
+                    he = __builtin_amdgcn_readlane(w_e, hpos - w_base);  // one that never ran starts from est0
+                }
+                ring_start = 0;
+            }
+            if (t < ring_start) {  // the reservations rule this round out (nothing was released since that was found)
+                if (ov_cnt == 0) t_skip = min(ring_start, next_due);
+                break;
+            }
+            // The requests past their estimate hold round t + 1 as well; that test is one slot, so it
+            // goes first (when it fails no request starts this round, whatever the reservations say).
+            if (ov_cnt > 0 && next_round() + ov_next + hs + 1 > M) break;
+            if (nact == cap) { overflow = true; break; }  // (first launch only: the second one's list holds every position)
+            // A start at t against the reservations, the request's own entered in the same pass and
+            // taken back if some round cannot hold them (rare: the verdict is known for a blocked request).  No
+            // reservation exceeds M, so a round above M afterwards is one of the window.
+            const int most = rows_add<NR>(p_uni(t + he - b), b + lane - t - 1, p_uni(he), p_uni(hs + 1));
+            if (__builtin_amdgcn_ballot_w64(most > M) != 0) {
+                release(hs, t, t + he);
+                // Blocked by them.  They change only by admissions (none while this request is blocked)
+                // and releases, so they are searched once for the earliest start they allow: round tq
+                // rules out the starts t' < tq with t' < R(tq) + s + tq - M; rounds more than H ahead
+                // hold nothing.  Each turn moves the start to the largest bound seen and looks only at the
+                // rounds that entered the window (t', t' + e] since.
+                int start = t, lo = t + 1;
+                const int bias = hs - M;
+                for (;;) {
+                    start = p_uni(start), lo = p_uni(lo);
+                    const int hi = min(start + he, t + H);
+                    const int acc = rows_bound<NR>(p_uni(hi - b), b + lane - lo, p_uni(hi - lo), b + lane, p_uni(bias));
+                    const int bound = -p_wave_min(-acc);
+                    if (bound <= start) break;  // fits at `start`
+                    start = bound;
+                    lo = hi + 1;
+                    if (start >= next_due) break;  // the running set changes first
+                }
+                ring_start = start;  // (> t)
+                if (ov_cnt == 0) t_skip = min(start, next_due);  // nothing happens before
+                break;
+            }
+            ring_start = t;  // a start is allowed now
+            if (lane == 0) {
+                if (hpos < frontier) WAIT[hpos >> 5] &= ~(1u << (hpos & 31));  // a stopped one starts again
+                LPI[nact] = hpos | (hid << 16), LOE[nact] = ho | (he << 16);
+                LDUE[nact] = (unsigned short)(t + min(he, ho));
+            }
+            if (hpos >= frontier) frontier = hpos + 1;
+            ++nact;
+            next_due = min(next_due, t + min(he, ho));
+            head = hpos + 1;
+            hpos = -1;
+            p_sync();
+        }
+        if (overflow) break;
+
+        // ---- 3. eviction while round t + 1 is projected above M (only that round can be: the reservations
+        //         held a feasible projection and only the overrunners' are new)
+        if (ov_cnt > 0) {
+            p_sync();
+            while (next_round() + (int)(ov_sp + (long long)ov_cnt * (t + 1)) > M) {
+                nact = p_uni(nact), ov_cnt = p_uni(ov_cnt), ov_sp = p_uni64(ov_sp), head = p_uni(head), hpos = p_uni(hpos);
+                int best = INT_MAX, best_at = -1;  // (current estimate, id) of the running requests, least first, and its place
+                for (int a0 = 0; a0 < nact; a0 += PW) {
+                    const int a = a0 + lane;
+                    if (a < nact) {
+                        const int oe = LOE[a];
+                        const int ev = (int)((unsigned)oe >> 16);
+                        // past its estimate: it has run o - (due - t) rounds and needs one more
+                        const int cur = ev == EST_OVERRUN ? (oe & 0xffff) - (int)(unsigned short)(LDUE[a] - (unsigned short)t) + 1 : ev;
+                        const int key = (cur << 16) | (int)((unsigned)LPI[a] >> 16);
+                        if (key < best) best = key, best_at = a;
+                    }
+                }
+                const int least = p_wave_min(best);
+                if (least == INT_MAX) break;  // cannot happen: an empty system holds nothing
+                // ids of a permutation are distinct: one lane holds it
+                const unsigned long long holder = __builtin_amdgcn_ballot_w64(best == least);
+                const int slot = __builtin_amdgcn_readlane(best_at, __builtin_ctzll(holder));
+                if (slot < 0) break;
+                const int sv = p_uni(p.s[least & 0xffff]);
+                const int pi_r = p_uni(LPI[slot]), oe_r = p_uni(LOE[slot]), due16 = p_uni(LDUE[slot]);
+                const int vpos = pi_r & 0xffff;
+                const int ev = (int)((unsigned)oe_r >> 16), ov = oe_r & 0xffff;
+                const int due = t + (int)(unsigned short)((unsigned short)due16 - (unsigned short)t);
+                const int ps = due - (ev == EST_OVERRUN ? ov : min(ev, ov));
+                if (ev == EST_OVERRUN) {
+                    --ov_cnt;
+                    ov_sp -= (long long)sv - ps;
+                } else {
+                    release(sv, ps, ps + ev);
+                    ring_start = 0;  // memory released
+                }
+                p_sync();
+                c_pos = vpos, c_s = sv, c_o = ov, c_id = (int)((unsigned)pi_r >> 16);
+                c_e = ev == EST_OVERRUN ? t - ps + 1 : ev;  // what it is known to need
+                if (lane == 0) {
+                    est_stopped[vpos] = (unsigned short)c_e;
+                    WAIT[vpos >> 5] |= 1u << (vpos & 31);  // waits again
+                    const int e0 = LPI[nact - 1], e1 = LOE[nact - 1];
+                    const unsigned short e2 = LDUE[nact - 1];
+                    LPI[slot] = e0, LOE[slot] = e1, LDUE[slot] = e2;
+                }
+                --nact;
+                if (vpos < head) { head = vpos; hpos = -1; }
+                ++evictions;
+                p_sync();
+            }
+        }
+        // While requests outrun their estimates the projection of round t' + 1 grows by their count
+        // every round; until the next due round nothing else changes.  Round t' needs work only if
+        // that projection passes M (eviction) or, from the round on that the reservations allow the blocked
+        // request to start at, leaves room for its first token (both necessary for its admission):
+        // find the first such round.
+        if (ov_cnt > 0 && (hpos >= 0 || head >= n) && next_due > t + 1) {
+            const int room = hpos >= 0 ? hs + 1 : INT_MAX / 2;  // nothing waits: only the overflow matters
+            const int from = hpos >= 0 ? ring_start : INT_MAX;
+            int found = next_due;
+            for (int r = 0; b + 64 * r <= next_due; ++r) {
+                const int tr = b + 64 * r + lane - 1;  // the lane's round is tr + 1
+                const long long x = (long long)row_of<NR>(p_uni(r)) + ov_sp + (long long)ov_cnt * (tr + 1);
+                const bool hit = tr > t && tr < next_due && (x > (long long)M || (tr >= from && x + room <= (long long)M));
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+                if (m != 0) {
+                    found = b + 64 * r - 1 + __builtin_ctzll(m);
+                    break;
+                }
+            }
+            t_skip = found;
+        }
+        advance(p_uni(max(t_skip, t + 1)));  // rounds t + 1 .. t_skip - 1 change nothing
+    }
+
+    if (lane == 0) {
+        if (overflow) {
+            p.retry[cand] = 1;  // the second launch runs this candidate with a list of n entries
+        } else {
+            if (over_limit) {
+                p.tel_out[cand] = -1;
+                atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_ROUND_LIMIT);
+            } else {
+                p.tel_out[cand] = tel;
+            }
+            if (p.evictions_out) p.evictions_out[cand] = evictions;
+        }
+    }
+}
+
 __global__ void clear_retry_kernel(int32_t *retry, int32_t C)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -534,6 +1115,40 @@ static size_t predicted_lds_bytes(int32_t n, int32_t H, int32_t cap)
     return sizeof(int) * ((size_t)H + stw + 3 * (size_t)cap) + sizeof(unsigned short) * (size_t)cap;
 }
 
+// ... with the projection in registers.
+static size_t reg_lds_bytes(int32_t n, int32_t, int32_t cap)
+{
+    return sizeof(int) * (((size_t)n + 31) >> 5) + 10 * (size_t)cap;
+}
+
+// First launch: the longest list with which `per_unit` candidates share a compute unit's 160 KB (LDS is handed out in
+// whole KB); worth it when that is at least 128 entries and fewer than all.
+static int launch_variant(const void *kernel, PredParams p, int per_unit, size_t (*lds_bytes)(int32_t, int32_t, int32_t),
+                          hipStream_t st)
+{
+    const int32_t cap_all = (p.n + 1) & ~1;
+    const size_t bytes_all = lds_bytes(p.n, p.H, cap_all), fixed = lds_bytes(p.n, p.H, 0);
+    const size_t entry = (lds_bytes(p.n, p.H, 2) - fixed) / 2, budget = (160 / per_unit) * 1024;
+    const int32_t cap_first = fixed < budget ? (int32_t)((budget - fixed) / entry) & ~1 : 0;
+    // beyond 64 KB of dynamic LDS the kernel's limit has to be raised first
+    if (bytes_all > 64 * 1024 &&
+        hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes_all) != hipSuccess)
+        return KVSCHED_EHIP;
+    auto launch = [&](int32_t cap, int32_t second) {
+        p.cap = cap;
+        p.second = second;
+        void *args[] = {&p};
+        return hipLaunchKernel(kernel, dim3((unsigned)p.C), dim3(PW), args, lds_bytes(p.n, p.H, cap), st) == hipSuccess;
+    };
+    if (cap_first >= 128 && cap_first < cap_all && p.retry) {
+        hipLaunchKernelGGL(clear_retry_kernel, dim3((unsigned)((p.C + 255) / 256)), dim3(256), 0, st, p.retry, p.C);
+        if (!launch(cap_first, 0) || !launch(cap_all, 1)) return KVSCHED_EHIP;
+    } else if (!launch(cap_all, 0)) {
+        return KVSCHED_EHIP;
+    }
+    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+}
+
 // ... with a list that holds every position: what a candidate may need at worst.
 size_t kvs_predicted_lds_bytes(int32_t n, int32_t H) { return predicted_lds_bytes(n, H, (n + 1) & ~1); }
 
@@ -543,21 +1158,7 @@ int kvs_launch_predicted(const int32_t *orders, int32_t C, int32_t n, const int3
                          int32_t *d_words, hipStream_t st)
 {
     const int32_t cap_all = (n + 1) & ~1;
-    const size_t bytes_all = predicted_lds_bytes(n, H, cap_all);
-    if (bytes_all > KVS_PREDICTED_MAX_LDS || n > 65535) return KVSCHED_ERANGE;
-    // beyond 64 KB of dynamic LDS the kernel's limit has to be raised first; only as far as needed
-    static size_t lds_limit = 64 * 1024;
-    if (bytes_all > lds_limit) {
-        if (hipFuncSetAttribute((const void *)predicted_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)bytes_all) != hipSuccess)
-            return KVSCHED_EHIP;
-        lds_limit = bytes_all;
-    }
-    // First launch: the longest list with which eight candidates share a compute unit's 160 KB (LDS is
-    // handed out in whole KB); worth it when that is at least 128 entries and fewer than all.
-    const size_t budget = 20 * 1024;
-    const size_t fixed = predicted_lds_bytes(n, H, 0);
-    int32_t cap_first = fixed < budget ? (int32_t)((budget - fixed) / 14) & ~1 : 0;
+    if (predicted_lds_bytes(n, H, cap_all) > KVS_PREDICTED_MAX_LDS || n > 65535) return KVSCHED_ERANGE;
     PredParams p;
     p.orders = orders;
     p.C = C;
@@ -575,18 +1176,10 @@ int kvs_launch_predicted(const int32_t *orders, int32_t C, int32_t n, const int3
     p.completion_out = completion_out;
     p.evictions_out = evictions_out;
     p.d_words = d_words;
-    if (cap_first >= 128 && cap_first < cap_all && retry) {
-        hipLaunchKernelGGL(clear_retry_kernel, dim3((unsigned)((C + 255) / 256)), dim3(256), 0, st, retry, C);
-        p.cap = cap_first;
-        p.second = 0;
-        hipLaunchKernelGGL(predicted_kernel, dim3((unsigned)C), dim3(PW), predicted_lds_bytes(n, H, cap_first), st, p);
-        p.cap = cap_all;
-        p.second = 1;
-        hipLaunchKernelGGL(predicted_kernel, dim3((unsigned)C), dim3(PW), bytes_all, st, p);
-    } else {
-        p.cap = cap_all;
-        p.second = 0;
-        hipLaunchKernelGGL(predicted_kernel, dim3((unsigned)C), dim3(PW), bytes_all, st, p);
-    }
-    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+    // The projection in registers while its rows leave room for three wavefronts per SIMD, else in LDS.
+    if (H <= 512) return launch_variant((const void *)predicted_reg_kernel<9>, p, 16, reg_lds_bytes, st);
+    if (H <= 1024) return launch_variant((const void *)predicted_reg_kernel<17>, p, 16, reg_lds_bytes, st);
+    if (H <= 2048) return launch_variant((const void *)predicted_reg_kernel<33>, p, 16, reg_lds_bytes, st);
+    if (H <= 4096) return launch_variant((const void *)predicted_reg_kernel<65>, p, 12, reg_lds_bytes, st);
+    return launch_variant((const void *)predicted_kernel, p, 8, predicted_lds_bytes, st);
 }
