@@ -507,7 +507,7 @@ __global__ __launch_bounds__(PW) void predicted_kernel(PredParams p)
 // ring and entries of 14 bytes in LDS eight fit a compute unit (two wavefronts per SIMD, some nine cycles an
 // instruction).  Without the ring, and with s left to a table look-up when an entry is handled (10 bytes an entry), 10 KB
 // a candidate let sixteen in; the entries due in one round are handled lane by lane instead of one after the other.
-// 4096 candidates of n = 2000, M = 131072: 16.1 -> 9.4 ms.
+// 4096 candidates of n = 2000, M = 131072: 16.1 -> 9.4 ms (8.6 with the slowest candidates first).
 //
 // List entry: position | id << 16 and o | estimate << 16, and the low 16 bits of the round it next matters at.
 // The rows of projected memory live in physical vector registers (KVP_PB upward) that only the assembly statements
@@ -764,6 +764,7 @@ __global__ __launch_bounds__(PW) void predicted_reg_kernel(PredParams p)
     long long ov_sp = 0;  // ... and the sum of s_j - p_j over them
     int next_due = INT_MAX;  // earliest round at which a running request reaches its estimate or its end
     int evictions = 0;
+    int visited = 0;
     long long tel = 0;
     bool over_limit = false, overflow = false;
 
@@ -788,10 +789,16 @@ __global__ __launch_bounds__(PW) void predicted_reg_kernel(PredParams p)
         // (everything the loop carries is the same in all lanes; saying so keeps it on the scalar unit)
         t = p_uni(t), head = p_uni(head), hpos = p_uni(hpos), hs = p_uni(hs), he = p_uni(he), ho = p_uni(ho), hid = p_uni(hid);
         ring_start = p_uni(ring_start), nact = p_uni(nact), done = p_uni(done), ov_cnt = p_uni(ov_cnt), ov_sp = p_uni64(ov_sp);
-        next_due = p_uni(next_due), evictions = p_uni(evictions), tel = p_uni64(tel), frontier = p_uni(frontier), b = p_uni(b);
+        next_due = p_uni(next_due), evictions = p_uni(evictions), visited = p_uni(visited), tel = p_uni64(tel), frontier = p_uni(frontier), b = p_uni(b);
         c_pos = p_uni(c_pos), c_s = p_uni(c_s), c_o = p_uni(c_o), c_id = p_uni(c_id), c_e = p_uni(c_e);
         w_base = p_uni(w_base), x_base = p_uni(x_base);
         if (t >= p.round_limit) { over_limit = true; break; }
+        // A candidate that visits many rounds for each request it finishes (a random order: twice as many as the Sorted-F
+        // order's neighbours) runs longest, and the call lasts as long as it does: it goes first on its SIMD.
+        if ((++visited & 63) == 0) {
+            if (2 * visited > 3 * done) __builtin_amdgcn_s_setprio(3);
+            else __builtin_amdgcn_s_setprio(0);
+        }
         // nothing waits, nobody outruns an estimate: nothing can happen before the next due round
         if (head >= n && ov_cnt == 0 && next_due > t) advance(next_due);
 
