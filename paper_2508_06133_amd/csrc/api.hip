@@ -665,9 +665,7 @@ static int run_local_swap(kvsched_ctx *ctx, int32_t n, const int32_t *s, const i
     hipStream_t st = (hipStream_t)stream;
     rc = ensure_scratch(ctx, kvs_local_swap_scratch_bytes(n));
     if (rc != KVSCHED_OK) return rc;
-    rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
-    if (rc != KVSCHED_OK) return rc;
-    return kvs_launch_local_swap(n, s, o, (int32_t)M, ga, gb, order_out, batch_end_out, F_out, swaps_out,
+    return kvs_launch_local_swap(n, s, o, (int32_t)M, ga, gb, ctx->pad_outputs, order_out, batch_end_out, F_out, swaps_out,
                                  num_batches_out, ctx->d_scratch, ctx->d_words, st);
 }
 

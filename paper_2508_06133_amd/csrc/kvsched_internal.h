@@ -194,7 +194,7 @@ int kvs_launch_exact_dp_emit(int32_t n, int32_t nb, void *lists, int32_t *order_
 
 // localswap.hip
 size_t kvs_local_swap_scratch_bytes(int32_t n);
-int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb, int32_t pad,
                           int32_t *order_out,
                           int32_t *batch_end_out, double *F_out, int32_t *swaps_out, int32_t *num_batches_out,
                           void *scratch, int32_t *d_words, hipStream_t st);

@@ -20,7 +20,12 @@
 // LS_TABLE ub() is one read of a table rank[v] = number of remaining requests with w <= v (the
 // arrangement is fixed within a batch, so the table is built once per batch); otherwise ub() is a
 // binary search.
+//
+// Up to LSR_N - 1 requests of sizes below LS_TABLE (the second half of this file) the values are
+// replaced by their ranks beforehand, by a kernel over the whole chip, so that a whole backlog fits in
+// LDS, and the exchanges of a batch are made by a single wavefront where its places are few.
 #include "phase1_util.h"
+#include "sort_util.h"
 
 namespace {
 
@@ -38,6 +43,12 @@ constexpr unsigned long long LS_NO_KEY = ~0ull;
 
 typedef __attribute__((address_space(3))) int lds_int;
 typedef __attribute__((address_space(3))) const unsigned short lds_rank;
+
+// LDS words read and written at other widths than they are declared with
+typedef unsigned __attribute__((may_alias)) any_u32;
+typedef unsigned short __attribute__((may_alias)) any_u16;
+typedef unsigned any_u32x2 __attribute__((ext_vector_type(2), may_alias));
+typedef unsigned any_u32x4 __attribute__((ext_vector_type(4), may_alias));
 
 struct SwapLds {
     int wave_min[LS_NW];
@@ -504,11 +515,13 @@ __global__ __launch_bounds__(LS_T) void local_swap_kernel(int32_t n, const int32
                                                           int32_t ga, int32_t gb, int32_t *order_out, int32_t *batch_end_out, double *F_out,
                                                           int32_t *swaps_out, int32_t *num_batches_out, int *gw, int *go,
                                                           int *gid, int *alt_o, int *buf0, int *buf1, int *by_o,
-                                                          int *batch_of, int32_t *words)
+                                                          int *batch_of, int32_t *words, const int *ranked,
+                                                          int32_t pad)
 {
     __shared__ PhaseLds P;
     __shared__ SwapLds L;
     __shared__ int sh[4];
+    if (ranked && *ranked != 0) return;  // done by ranked_swap_kernel
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     // ---- well-formedness and key widths
@@ -536,6 +549,12 @@ __global__ __launch_bounds__(LS_T) void local_swap_kernel(int32_t n, const int32
             atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
             *num_batches_out = 0;
         }
+        if (pad)
+            for (int i = tid; i < n; i += LS_T) {
+                batch_end_out[i] = 0;
+                F_out[i] = 0.0;
+                if (swaps_out) swaps_out[i] = 0;
+            }
         return;
     }
 
@@ -662,6 +681,12 @@ __global__ __launch_bounds__(LS_T) void local_swap_kernel(int32_t n, const int32
         ++nb;
     }
     if (tid == 0) *num_batches_out = nb;
+    if (pad)
+        for (int i = nb + tid; i < n; i += LS_T) {
+            batch_end_out[i] = 0;
+            F_out[i] = 0.0;
+            if (swaps_out) swaps_out[i] = 0;
+        }
     __threadfence_block();
     __syncthreads();
 
@@ -677,7 +702,627 @@ __global__ __launch_bounds__(LS_T) void local_swap_kernel(int32_t n, const int32
     for (int i = tid; i < n; i += LS_T) order_out[i] = src[i];
 }
 
+// ---------------------------------------------------------------------------------------------
+// Fewer than LSR_N requests, all of sizes below LS_TABLE.
+//
+// Exchanges only compare values, so a value is replaced by the number of requests of smaller values
+// (equal ones stay equal).  Then size, value and membership of a request fit in one LDS word, and with
+// its rank by (o, id) two bytes more; nothing is read from memory between the batches.
+//
+// rank_requests_kernel sorts by counting: a request's place in an order is the number of requests
+// before it, three counts of n comparisons each, which the whole chip shares (2000 requests: 125
+// workgroups; the radix passes that one workgroup made took 95 us).
+//
+// What a step costs is the latency of its chain of dependent operations, not their number.  Up to
+// 1024 places it is therefore the work of ONE wavefront, without a barrier: lane l holds places E l ...
+// E l + E - 1 of the arrangement in registers.  Cycles per exchange, 4 / 8 / 16 places per lane: 710 / 1040 / 1700; by
+// eight wavefronts with four barriers, 4 / 16 places per lane: 2250 / 3650 (so 1024 places are the line:
+// with 2 places per lane the workgroup takes 2290).  The rest of the workgroup takes part between the exchanges
+// (greedy fill, table of ub(), closing up: three microseconds per batch) and writes the batch before out
+// during them.
+// 2000 requests, 29 batches, 769 exchanges: 1073 -> 410 us; 8000 requests, 6 batches, 1151 exchanges over up to
+// 6000 places: 4.0 -> 1.5 ms.
+
+constexpr int LSR_N = 8192;
+constexpr int LSR_T = 512;  // threads of the workgroup
+constexpr int LSR_NW = LSR_T / 64;
+constexpr int LSR_OWN = 16;        // requests ranked by a workgroup
+// The word of a place: LSR_IN for a member | value << 18 | size << 4 | (in registers only) number of the register.
+// Comparing words compares values, and a member's is larger than any non-member's.
+constexpr unsigned LSR_IN = 0x80000000u;
+constexpr unsigned LSR_VALUE = 0x7ffc0000u;  // as a word, a place without a request: larger than every value
+constexpr unsigned LSR_REST = 0x3ffffu;
+__device__ __forceinline__ int size_of(unsigned word) { return (int)(word >> 4) & (LS_TABLE - 1); }
+static_assert(LS_TABLE <= 1 << 14 && LSR_N <= 1 << 13, "words of RankedLds");
+
+// What the ranking kernel leaves behind.
+struct RankedArrays {
+    int *state;            // 1: the arrays hold the ranked requests; 0: a size does not fit; -1: malformed lengths
+    unsigned *word;        // [n] by (size, o, id): value rank << 18 | size << 4
+    unsigned short *by_w;  // [n] rank by (o, id) of the same requests
+    unsigned short *by_o;  // [n] id at a rank by (o, id)
+    int *value;            // [n] value of the request at a rank by (o, id)
+};
+
+// Each workgroup ranks LSR_OWN requests: lane 16 g + r of wavefront v compares request r with the keys of
+// part 4 v + g.  Keys of a quad that lies before the request count when equal, those behind it when
+// smaller; the quad that holds the request itself is corrected afterwards.
+__global__ __launch_bounds__(1024) void rank_requests_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
+                                                             int32_t ga, int32_t gb, RankedArrays r, int32_t *words,
+                                                             int32_t *num_batches_out)
+{
+    __shared__ __align__(16) unsigned key_w[LSR_N];  // size << 14 | o
+    __shared__ __align__(16) unsigned key_v[LSR_N];
+    __shared__ unsigned part[16][3][LSR_OWN];
+    __shared__ int sh[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < 3) sh[tid] = 0;
+    __syncthreads();
+    int omax = 0, wide = 0, bad = 0;
+    for (int j = tid; j < ((n + 3) & ~3); j += 1024) {
+        unsigned kw = ~0u, kv = ~0u;  // (padding: below no key, and o < size < 0x3fff)
+        if (j < n) {
+            const int sv = s[j], ov = o[j];
+            if (sv < 1 || ov < 1 || (long long)sv + ov > (long long)M) bad = 1;
+            else if (sv + ov >= LS_TABLE) wide = 1;
+            omax = max(omax, ov);
+            kw = ((unsigned)(sv + ov) << 14) | ((unsigned)ov & 0x3fffu);
+            kv = (unsigned)(ga * sv + gb * ov);
+        }
+        key_w[j] = kw;
+        key_v[j] = kv;
+    }
+    for (int d = 32; d > 0; d >>= 1) omax = max(omax, __shfl_xor(omax, d));
+    if (lane == 0) atomicMax(&sh[0], omax);
+    if (bad) atomicOr(&sh[1], 1);
+    if (wide) atomicOr(&sh[2], 1);
+    __syncthreads();
+    bad = sh[1];
+    wide = sh[2];
+    if (blockIdx.x == 0 && tid == 0) {
+        words[KVS_W_STATUS] = bad ? KVSCHED_DEV_BAD_LENGTH : 0;
+        words[KVS_W_OMAX] = sh[0];
+        words[KVS_W_MINPOS] = 0x7fffffff;
+        words[KVS_W_MAXPOS] = -1;
+        *r.state = bad ? -1 : (wide ? 0 : 1);
+        if (bad) *num_batches_out = 0;
+    }
+    if (bad || wide) return;
+
+    const int i = (int)blockIdx.x * LSR_OWN + (lane & 15);
+    const int ii = min(i, n - 1), group = 4 * wave + (lane >> 4);
+    const unsigned kw = key_w[ii], kv = key_v[ii], ko = kw & 0x3fffu;
+    const int quads = (n + 3) >> 2, per = (quads + 63) >> 6;
+    const int q1 = min(quads, (group + 1) * per);
+    unsigned cw = 0, co = 0, cv = 0;
+    for (int q = group * per; q < q1; ++q) {
+        const any_u32x4 a = reinterpret_cast<const any_u32x4 *>(key_w)[q], b = reinterpret_cast<const any_u32x4 *>(key_v)[q];
+        const unsigned tie = 4 * q + 3 < ii ? 1u : 0u, tw = kw + tie, to = ko + tie;
+        cw += (a.x < tw) + (a.y < tw) + (a.z < tw) + (a.w < tw);
+        co += ((a.x & 0x3fffu) < to) + ((a.y & 0x3fffu) < to) + ((a.z & 0x3fffu) < to) + ((a.w & 0x3fffu) < to);
+        cv += (b.x < kv) + (b.y < kv) + (b.z < kv) + (b.w < kv);
+    }
+    if (group == 0) {
+        for (int j = ii & ~3; j < ii; ++j) {
+            cw += key_w[j] == kw;
+            co += (key_w[j] & 0x3fffu) == ko;
+        }
+    }
+    for (int d = 16; d < 64; d <<= 1) {
+        cw += __shfl_xor((int)cw, d);
+        co += __shfl_xor((int)co, d);
+        cv += __shfl_xor((int)cv, d);
+    }
+    if (lane < LSR_OWN) {
+        part[wave][0][lane] = cw;
+        part[wave][1][lane] = co;
+        part[wave][2][lane] = cv;
+    }
+    __syncthreads();
+    if (tid < LSR_OWN && i < n) {
+        cw = co = cv = 0;
+        for (int u = 0; u < 16; ++u) {
+            cw += part[u][0][tid];
+            co += part[u][1][tid];
+            cv += part[u][2][tid];
+        }
+        r.word[cw] = (cv << 18) | ((kw >> 14) << 4);
+        r.by_w[cw] = (unsigned short)co;
+        r.by_o[co] = (unsigned short)i;
+        r.value[co] = (int)kv;
+    }
+}
+
+// (the two arrays of the dependent look-ups come first: their offsets fit in an LDS instruction)
+struct alignas(16) RankedLds {
+    unsigned short rank[LS_TABLE];   // twice the number of places of at most a size
+    unsigned short pm[LSR_N];        // upper half of the least word of a non-member before a place
+    unsigned word[LSR_N];            // by place
+    unsigned short by_w[LSR_N];      // by place: rank by (o, id)
+    unsigned short by_o[LSR_N];
+    int value[LSR_N];
+    unsigned bits[2][LSR_N / 32];    // a batch by rank by (o, id): a bit per request; two batches in turn
+    unsigned wave_sum[LSR_NW];
+    unsigned wave_top[LSR_NW];
+    unsigned wave_min[LSR_NW];
+    u64 first_out[2];                // alternating slots: place << 32 | word of the first member that has a partner
+    u64 first_in[2];                 //                    the same of its partner
+    int fill_end, fill_mem, fill_w;
+    int slack, hi, w_hi, swaps, done;
+    u64 S;                           // sum of values of the batch that is written out
+    int parts;                       // wavefronts that have added theirs
+};
+
+// x = from[e] of the least e with a[e] < b[e] (x if there is none), and from[at] = x: written out because a
+// comparison's mask may be read only two instructions later, and the compiler fills the gap with idle ones
+// when it takes one mask at a time (an exchange of four places per lane: 942 -> 740 cycles).
+template <int E>
+__device__ __forceinline__ void first_below(unsigned &x, const unsigned (&a)[E], const unsigned (&b)[E],
+                                            const unsigned (&from)[E])
+{
+    if constexpr (E == 2) {
+        const bool is0 = a[0] < b[0], is1 = a[1] < b[1];
+        x = is0 ? from[0] : is1 ? from[1] : x;
+    } else {
+        u64 m0, m1, m2, m3;
+#pragma unroll
+        for (int e = E - 4; e >= 0; e -= 4)
+            asm("v_cmp_lt_u32 %4, %8, %12\n\tv_cmp_lt_u32 %3, %7, %11\n\tv_cmp_lt_u32 %2, %6, %10\n\tv_cmp_lt_u32 %1, %5, %9\n\t"
+                "v_cndmask_b32 %0, %0, %16, %4\n\tv_cndmask_b32 %0, %0, %15, %3\n\tv_cndmask_b32 %0, %0, %14, %2\n\tv_cndmask_b32 %0, %0, %13, %1"
+                : "+&v"(x), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+                : "v"(a[e]), "v"(a[e + 1]), "v"(a[e + 2]), "v"(a[e + 3]), "v"(b[e]), "v"(b[e + 1]), "v"(b[e + 2]), "v"(b[e + 3]),
+                  "v"(from[e]), "v"(from[e + 1]), "v"(from[e + 2]), "v"(from[e + 3]));
+    }
+}
+
+template <int E>
+__device__ __forceinline__ void put(unsigned (&to)[E], int at, unsigned x)
+{
+    if constexpr (E == 2) {
+        const bool is0 = at == 0, is1 = at == 1;
+        to[0] = is0 ? x : to[0];
+        to[1] = is1 ? x : to[1];
+    } else {
+        u64 m0, m1, m2, m3;
+#pragma unroll
+        for (int e = 0; e < E; e += 4)
+            asm("v_cmp_eq_u32 %4, %8, %9\n\tv_cmp_eq_u32 %5, %8, %10\n\tv_cmp_eq_u32 %6, %8, %11\n\tv_cmp_eq_u32 %7, %8, %12\n\t"
+                "v_cndmask_b32 %0, %0, %13, %4\n\tv_cndmask_b32 %1, %1, %13, %5\n\tv_cndmask_b32 %2, %2, %13, %6\n\tv_cndmask_b32 %3, %3, %13, %7"
+                : "+&v"(to[e]), "+&v"(to[e + 1]), "+&v"(to[e + 2]), "+&v"(to[e + 3]), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+                : "v"(at), "n"(e), "n"(e + 1), "n"(e + 2), "n"(e + 3), "v"(x));
+    }
+}
+
+// State of a batch's exchanges, the same in every thread.  Places count from the batch's first group of eight.
+struct RankedState {
+    int slack, hi, w_hi, swaps;
+};
+
+// Exchanges of one batch while no place from NW 64 E - 1 on can fit, by NW wavefronts (1: without
+// barriers, called by one wavefront; or all of the workgroup).  Returns true when none is left.
+template <int NW, int E>
+__device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_last, int fill_from, int fill_to,
+                                             RankedState &st)
+{
+    static_assert(E >= 2 && E <= 16, "numbers of registers in the words");
+    constexpr int PLACES = NW * 64 * E;
+    const int lane = threadIdx.x & 63, wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int q = (wave * 64 + lane) * E;
+    asm volatile("" : "+v"(q));  // (keeps what each split derives from it out of the batches' loop, where it fills the registers)
+    unsigned v[E];  // the words of this thread's places
+    int w2[E];      // twice their sizes
+#pragma unroll
+    for (int e = 0; e < E; e += 2) {
+        const any_u32x2 x = *reinterpret_cast<const any_u32x2 *>(&L.word[min(p0 + q + e, LSR_N - 2)]);
+        v[e] = p0 + q + e < LSR_N ? x.x : LSR_VALUE;
+        v[e + 1] = p0 + q + e < LSR_N ? x.y : LSR_VALUE;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        w2[e] = 2 * size_of(v[e]);
+        v[e] |= (unsigned)e | ((q + e >= fill_from && q + e < fill_to) ? LSR_IN : 0u);
+    }
+    // no place from PLACES - 1 on fits against a member while w_hi + slack stays below this
+    const int w_limit = n - p0 < PLACES ? LS_INF : __builtin_amdgcn_readfirstlane(size_of(L.word[p0 + PLACES - 1]));
+    int slack = __builtin_amdgcn_readfirstlane(st.slack), hi = __builtin_amdgcn_readfirstlane(st.hi);
+    int w_hi = __builtin_amdgcn_readfirstlane(st.w_hi), swaps = __builtin_amdgcn_readfirstlane(st.swaps);
+    bool done = false;
+    if (NW > 1) {
+        if (threadIdx.x < 2) L.first_out[threadIdx.x] = L.first_in[threadIdx.x] = LS_NO_KEY;
+        __syncthreads();
+    }
+    for (int it = 0;; ++it) {
+        const int slot = it & 1;
+        if (w_hi + slack >= w_limit) break;  // uniform
+
+        // ---- how far each place would reach as a member (what non-members find is never used)
+        unsigned p[E];
+        const bool members = NW == 1 || wave * 64 * E < hi;  // (a wavefront behind all members looks nothing up)
+        if (members) {
+            const int reach = 2 * min(slack, w_last), top = 2 * w_last;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                p[e] = *reinterpret_cast<const any_u16 *>(reinterpret_cast<const char *>(L.rank) + min(w2[e] + reach, top));
+        }
+        // ---- least word of a non-member before each place (as unsigned numbers the members are the largest)
+        unsigned pm[E], run = LS_INF;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            pm[e] = run;
+            run = min(run, v[e]);
+        }
+        const int incl = wave_scan<false>((int)run);
+        unsigned before = (unsigned)wave_prev<false>(incl);
+        if (NW > 1) {
+            if (lane == 63) L.wave_min[wave] = (unsigned)incl;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NW - 1; ++u) before = u < wave ? min(before, L.wave_min[u]) : before;
+        }
+        {
+            any_u32 *to = reinterpret_cast<any_u32 *>(&L.pm[q]);
+            unsigned two[E / 2];
+#pragma unroll
+            for (int e = 0; e < E; e += 2)
+                two[e / 2] = __builtin_amdgcn_perm(min(pm[e + 1], before), min(pm[e], before), 0x07060302);
+#pragma unroll
+            for (int e = 0; e < E / 2; ++e) to[e] = two[e];
+        }
+        if (NW > 1) __syncthreads();
+
+        // ---- first member with an improving partner that fits
+        unsigned x_a = 0, x_b = ~0u;
+        if (members) {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                p[e] = *reinterpret_cast<const any_u16 *>(reinterpret_cast<const char *>(L.pm) + p[e]) << 16 | (LSR_IN | LSR_REST);
+            first_below<E>(x_a, p, v, v);
+        }
+        int a, b, l_a = 0;
+        u64 have = __builtin_amdgcn_ballot_w64(x_a != 0);
+        if (NW == 1) {
+            l_a = (int)__builtin_ctzll(have);
+            x_a = (unsigned)__builtin_amdgcn_readlane((int)x_a, l_a & 63);
+        } else {
+            if (have != 0) {
+                const int l = (int)__builtin_ctzll(have);
+                const unsigned x = (unsigned)__builtin_amdgcn_readlane((int)x_a, l);
+                if (lane == 0) atomicMin(&L.first_out[slot], (u64)((unsigned)(wave * 64 + l) * E + (x & 15)) << 32 | x);
+            }
+            __syncthreads();
+            const u64 k = L.first_out[slot];
+            x_a = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)k);
+            a = __builtin_amdgcn_readfirstlane((int)(k >> 32));
+            have = x_a != ~0u;
+        }
+
+        // ---- its partner: the first non-member of a smaller value
+        unsigned below[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) below[e] = x_a & LSR_VALUE;
+        first_below<E>(x_b, v, below, v);
+        u64 found;
+        if (NW == 1) {
+            a = l_a * E + (int)(x_a & 15);
+            found = __builtin_amdgcn_ballot_w64(x_b != ~0u);
+            const int l = (int)__builtin_ctzll(found);
+            x_b = (unsigned)__builtin_amdgcn_readlane((int)x_b, l & 63);
+            b = l * E + (int)(x_b & 15);
+        } else {
+            if (have != 0 && x_b != ~0u && before >= below[0]) L.first_in[slot] = (u64)(unsigned)(q + (int)(x_b & 15)) << 32 | x_b;
+            __syncthreads();
+            const u64 k = L.first_in[slot];
+            x_b = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)k);
+            b = __builtin_amdgcn_readfirstlane((int)(k >> 32));
+            found = x_b != ~0u;
+        }
+        if (have == 0 || found == 0) { done = true; break; }  // none left (a partner was seen if have != 0)
+
+        // ---- exchange
+        const int w_b = size_of(x_b);
+        slack -= w_b - size_of(x_a);
+        if (b >= hi) { hi = b + 1; w_hi = w_b; }
+        ++swaps;
+        put<E>(v, a - q, x_a ^ LSR_IN);
+        put<E>(v, b - q, x_b ^ LSR_IN);
+        if (NW > 1 && threadIdx.x == 0)  // the other slot was last read two barriers ago; ready it for the next step
+            L.first_out[slot ^ 1] = L.first_in[slot ^ 1] = LS_NO_KEY;
+    }
+#pragma unroll
+    for (int e = 0; e < E; e += 2)
+        if (p0 + q + e < LSR_N) *reinterpret_cast<any_u32x2 *>(&L.word[p0 + q + e]) = any_u32x2{v[e] & ~15u, v[e + 1] & ~15u};
+    st.slack = slack;
+    st.hi = hi;
+    st.w_hi = w_hi;
+    st.swaps = swaps;
+    return done;
+}
+
+// A batch that has left, from its bits, by four wavefronts (part 0 ... 3): the order, from place `first` on, and
+// its ratio.
+__device__ __forceinline__ void ranked_emit(RankedLds &L, int part, const unsigned *bits, int first, double scale,
+                                            int *order_out, double *F_out)
+{
+    static_assert(LSR_N / 32 == 4 * 64, "a word per lane");
+    const int lane = threadIdx.x & 63;
+    unsigned ahead = 0, mine = 0;
+    for (int u = 0; u < 4; ++u) {
+        const unsigned x = bits[64 * u + lane];
+        if (u < part) ahead += (unsigned)__popc(x);
+        if (u == part) mine = x;
+    }
+    const unsigned c = (unsigned)__popc(mine);
+    const unsigned incl = wave_scan_u32(c);
+    int at = first + (int)(incl - c) + (int)__builtin_amdgcn_readlane((int)wave_scan_u32(ahead), 63);
+    u64 S = 0;
+    while (mine != 0) {
+        const int k = 32 * (64 * part + lane) + __ffs((int)mine) - 1;
+        order_out[at++] = L.by_o[k];
+        S += (u64)(unsigned)L.value[k];
+        mine &= mine - 1;
+    }
+    S = wave_scan_u64(S);
+    if (lane == 63) {
+        atomicAdd(&L.S, S);
+        __threadfence_block();
+        if (atomicAdd(&L.parts, 1) == 3) *F_out = (double)(long long)atomicAdd(&L.S, 0ull) / scale;
+    }
+}
+
+__device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const RankedArrays &r, int *order_out,
+                                   int *batch_end_out, double *F_out, int *swaps_out, int *num_batches_out, int *words)
+{
+    constexpr int ROWS = (LS_TABLE / 512 + LSR_NW - 1) / LSR_NW;  // rows of the table per wavefront, at most
+    constexpr int OWN = LSR_N / (4 * LSR_T);                     // groups of four places per thread, at most
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < LSR_N; i += LSR_T) {
+        L.word[i] = i < n ? r.word[i] : LSR_VALUE;
+        if (i < n) {
+            L.by_w[i] = r.by_w[i];
+            L.by_o[i] = r.by_o[i];
+            L.value[i] = r.value[i];
+        }
+    }
+    for (int i = 8 * tid; i < LS_TABLE; i += 8 * LSR_T) *reinterpret_cast<any_u32x4 *>(&L.rank[i]) = any_u32x4{0, 0, 0, 0};
+    for (int i = tid; i < 2 * (LSR_N / 32); i += LSR_T) L.bits[0][i] = 0;
+    __syncthreads();
+    int a = 0, nb = 0;
+    int left = 0, left_K = 0;  // where the batch before starts, and its size
+    auto emit_left = [&](int part) {
+        if (nb == 0) return;
+        ranked_emit(L, part, L.bits[(nb - 1) & 1], left, (double)gb * (double)left_K * (double)left_K, order_out, F_out + nb - 1);
+    };
+    while (a < n) {
+        const int p0 = a & ~7;
+        const int groups = (n - p0 + 4 * LSR_T - 1) / (4 * LSR_T);  // of four places, per thread
+        const int i0 = p0 + 4 * groups * tid;
+
+        // ---- greedy fill (the longest run of places whose sizes add up to at most M) and the table of ub(), which is
+        //      zero here: the last place of each size enters its number, a running maximum fills the gaps
+        unsigned sum = 0;
+        for (int g = 0; g < groups; ++g) {
+            const int i = i0 + 4 * g;
+            const any_u32x4 y = *reinterpret_cast<const any_u32x4 *>(&L.word[min(i, LSR_N - 4)]);
+            const int next = size_of(L.word[min(i + 4, LSR_N - 1)]);
+            const int ws[5] = {size_of(y.x), size_of(y.y), size_of(y.z), size_of(y.w), i + 4 < n ? next : -1};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (i + e < n) {
+                    sum += (unsigned)ws[e];
+                    if (ws[e] != ws[e + 1]) L.rank[ws[e]] = (unsigned short)(2 * (i + e + 1 - p0));  // (past the last place: size 0)
+                }
+            }
+        }
+        const unsigned incl = wave_scan_u32(sum);
+        if (lane == 63) L.wave_sum[wave] = incl;
+        if (tid == 0) {
+            L.S = 0;
+            L.parts = 0;
+        }
+        const int w_last = __builtin_amdgcn_readfirstlane(size_of(L.word[n - 1]));
+        const int rows = (w_last >> 9) + 1, per = (rows + LSR_NW - 1) / LSR_NW;  // rows of 512 entries, eight per lane
+        const int r0 = wave * per, r1 = min(rows, r0 + per);
+        __syncthreads();
+        unsigned h[ROWS][8], top = 0;
+#pragma unroll
+        for (int k = 0; k < ROWS; ++k) {  // (rows past r1 are computed for nothing)
+            if (k >= per) break;
+            const any_u32x4 y = *reinterpret_cast<const any_u32x4 *>(&L.rank[512 * min(r0 + k, LS_TABLE / 512 - 1) + 8 * lane]);
+            h[k][0] = y.x & 0xffffu, h[k][1] = y.x >> 16, h[k][2] = y.y & 0xffffu, h[k][3] = y.y >> 16;
+            h[k][4] = y.z & 0xffffu, h[k][5] = y.z >> 16, h[k][6] = y.w & 0xffffu, h[k][7] = y.w >> 16;
+        }
+        unsigned pre = incl - sum;
+#pragma unroll
+        for (int u = 0; u < LSR_NW; ++u)
+            if (u < wave) pre += L.wave_sum[u];
+        // the one thread in whose places the run ends
+        if (pre <= (unsigned)M && i0 < n && (pre + sum > (unsigned)M || n <= i0 + 4 * groups)) {
+            int i = i0;
+            for (bool more = true; more;) {  // four places a turn; it ends in them or at n
+                const any_u32x4 y = *reinterpret_cast<const any_u32x4 *>(&L.word[i]);
+                const unsigned ws[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned next = pre + (unsigned)size_of(ws[e]);
+                    more = more && i < n && next <= (unsigned)M;
+                    pre = more ? next : pre;
+                    i += more;
+                }
+            }
+            L.fill_end = i;
+            L.fill_mem = (int)pre;
+            L.fill_w = size_of(L.word[max(i - 1, 0)]);
+        }
+#pragma unroll
+        for (int k = 0; k < ROWS; ++k) {
+            if (k >= per) break;
+#pragma unroll
+            for (int e = 1; e < 8; ++e) h[k][e] = max(h[k][e], h[k][e - 1]);
+            const int m = wave_scan<true>((int)h[k][7]);
+            const unsigned lower = (unsigned)max(wave_prev<true>(m), (int)top);
+            if (r0 + k < r1) top = (unsigned)max((int)top, __builtin_amdgcn_readlane(m, 63));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[k][e] = max(h[k][e], lower);
+        }
+        if (lane == 0) L.wave_top[wave] = top;
+        __syncthreads();
+        {
+            unsigned lower = 0;
+#pragma unroll
+            for (int u = 0; u < LSR_NW; ++u)
+                if (u < wave) lower = max(lower, L.wave_top[u]);
+#pragma unroll
+            for (int k = 0; k < ROWS; ++k) {
+                if (r0 + k < r1) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) h[k][e] = max(h[k][e], lower);
+                    *reinterpret_cast<any_u32x4 *>(&L.rank[512 * (r0 + k) + 8 * lane]) =
+                        any_u32x4{h[k][0] | h[k][1] << 16, h[k][2] | h[k][3] << 16, h[k][4] | h[k][5] << 16, h[k][6] | h[k][7] << 16};
+                }
+            }
+        }
+        RankedState st;
+        st.hi = __builtin_amdgcn_readfirstlane(L.fill_end);
+        st.slack = M - __builtin_amdgcn_readfirstlane(L.fill_mem);
+        st.w_hi = __builtin_amdgcn_readfirstlane(L.fill_w);
+        st.swaps = 0;
+        const int K = st.hi - a;
+        if (K < 1) {  // cannot happen for well-formed input; never spin
+            if (tid == 0) atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
+            break;
+        }
+        st.hi -= p0;
+        __syncthreads();
+
+        // ---- exchanges; meanwhile the batch before is written out
+        bool emitted = false;
+        const bool all = a + K == n;  // the batch has taken everything
+        int from = a - p0, to = a - p0 + K;  // places that become members when they are first read
+        while (!all) {
+            const int U = L.rank[min(st.w_hi + st.slack, w_last)] >> 1;  // places from U on fit against no member
+            bool done = false;
+            if (U < 1024) {
+                if (wave == 0) {
+                    done = U < 256   ? ranked_steps<1, 4>(L, p0, n, w_last, from, to, st)
+                           : U < 512 ? ranked_steps<1, 8>(L, p0, n, w_last, from, to, st)
+                                     : ranked_steps<1, 16>(L, p0, n, w_last, from, to, st);
+                    if (lane == 0) {
+                        L.slack = st.slack;
+                        L.hi = st.hi;
+                        L.w_hi = st.w_hi;
+                        L.swaps = st.swaps;
+                        L.done = done;
+                    }
+                } else if (wave <= 4 && !emitted) emit_left(wave - 1);
+                emitted = true;
+                __syncthreads();
+                st.slack = __builtin_amdgcn_readfirstlane(L.slack);
+                st.hi = __builtin_amdgcn_readfirstlane(L.hi);
+                st.w_hi = __builtin_amdgcn_readfirstlane(L.w_hi);
+                st.swaps = __builtin_amdgcn_readfirstlane(L.swaps);
+                done = __builtin_amdgcn_readfirstlane(L.done) != 0;
+            } else if (U < 2048) done = ranked_steps<LSR_NW, 2048 / LSR_T>(L, p0, n, w_last, from, to, st);
+            else if (U < 4096) done = ranked_steps<LSR_NW, 4096 / LSR_T>(L, p0, n, w_last, from, to, st);
+            else done = ranked_steps<LSR_NW, 8192 / LSR_T>(L, p0, n, w_last, from, to, st);
+            __syncthreads();
+            if (done) break;  // uniform
+            to = from;
+        }
+        if (!emitted && wave < 4) emit_left(wave);
+        if (tid == 0) {
+            batch_end_out[nb] = a + K;
+            if (swaps_out) swaps_out[nb] = st.swaps;
+        }
+        const int hi = p0 + st.hi;
+
+        // ---- members leave; non-members of [a, hi) close up behind the K removed places.  The table is zeroed.
+        unsigned x[OWN][4];
+        unsigned short at[OWN][4];
+        unsigned stay = 0;
+#pragma unroll
+        for (int g = 0; g < OWN; ++g) {
+            if (g < groups) {
+                const int i = i0 + 4 * g;
+                const int at_i = min(i, LSR_N - 4);
+                const any_u32x4 y = *reinterpret_cast<const any_u32x4 *>(&L.word[at_i]);
+                const any_u32x2 z = *reinterpret_cast<const any_u32x2 *>(&L.by_w[at_i]);
+                x[g][0] = y.x, x[g][1] = y.y, x[g][2] = y.z, x[g][3] = y.w;
+                at[g][0] = (unsigned short)z.x, at[g][1] = (unsigned short)(z.x >> 16);
+                at[g][2] = (unsigned short)z.y, at[g][3] = (unsigned short)(z.y >> 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (i + e >= a && i + e < hi) {
+                        if (all || (x[g][e] & LSR_IN)) atomicOr(&L.bits[nb & 1][at[g][e] >> 5], 1u << (at[g][e] & 31));
+                        else stay |= 1u << (4 * g + e);
+                    }
+                }
+            }
+        }
+        const unsigned count = (unsigned)__popc(stay);
+        const unsigned upto = wave_scan_u32(count);
+        if (lane == 63) L.wave_min[wave] = upto;
+        for (int i = 8 * tid; i <= w_last; i += 8 * LSR_T) *reinterpret_cast<any_u32x4 *>(&L.rank[i]) = any_u32x4{0, 0, 0, 0};
+        __syncthreads();
+        {
+            int place = a + K + (int)(upto - count);
+#pragma unroll
+            for (int u = 0; u < LSR_NW; ++u)
+                if (u < wave) place += (int)L.wave_min[u];
+            if (stay != 0) {
+#pragma unroll
+                for (int g = 0; g < OWN; ++g) {
+                    if (g < groups) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (stay & (1u << (4 * g + e))) {
+                                L.word[place] = x[g][e];
+                                L.by_w[place] = at[g][e];
+                                ++place;
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        left = a;
+        left_K = K;
+        a += K;
+        ++nb;
+        if (tid < 8 && (a & ~7) + tid < a) L.word[(a & ~7) + tid] = LSR_VALUE;
+        if (tid < LSR_N / 32) L.bits[nb & 1][tid] = 0;  // of the batch before the one that has just left
+        __syncthreads();
+    }
+    if (tid == 0) {
+        *num_batches_out = nb;
+        L.S = 0;
+        L.parts = 0;
+    }
+    __syncthreads();
+    if (wave < 4) emit_left(wave);
+    return nb;
+}
+
+__global__ __launch_bounds__(LSR_T) void ranked_swap_kernel(int32_t n, int32_t M, int32_t gb, RankedArrays r,
+                                                            int32_t *order_out, int32_t *batch_end_out, double *F_out,
+                                                            int32_t *swaps_out, int32_t *num_batches_out, int32_t pad,
+                                                            int32_t *words)
+{
+    __shared__ RankedLds L;
+    const int state = *r.state;
+    int nb = 0;
+    if (state == 1)
+        nb = ranked_construction(L, n, M, gb, r, order_out, batch_end_out, F_out, swaps_out, num_batches_out, words);
+    if (state != 0 && pad) {
+        for (int i = nb + (int)threadIdx.x; i < n; i += LSR_T) {
+            batch_end_out[i] = 0;
+            F_out[i] = 0.0;
+            if (swaps_out) swaps_out[i] = 0;
+        }
+    }
+}
+
 }  // namespace
+
 
 size_t kvs_local_swap_scratch_bytes(int32_t n)
 {
@@ -685,7 +1330,7 @@ size_t kvs_local_swap_scratch_bytes(int32_t n)
     return np * 8 * sizeof(int) + 256;
 }
 
-int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb, int32_t pad,
                           int32_t *order_out,
                           int32_t *batch_end_out, double *F_out, int32_t *swaps_out, int32_t *num_batches_out,
                           void *scratch, int32_t *d_words, hipStream_t st)
@@ -699,7 +1344,24 @@ int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t
     int *buf1 = buf0 + np;
     int *by_o = buf1 + np;
     int *batch_of = by_o + np;
+    int *state = nullptr;
+    if (n < LSR_N) {
+        RankedArrays r;
+        r.state = state = batch_of + np;
+        r.word = (unsigned *)gw;
+        r.value = go;
+        r.by_w = (unsigned short *)gid;
+        r.by_o = (unsigned short *)alt_o;
+        hipLaunchKernelGGL(rank_requests_kernel, dim3((unsigned)((n + LSR_OWN - 1) / LSR_OWN)), dim3(1024), 0, st, n, s, o,
+                           M, ga, gb, r, d_words, num_batches_out);
+        hipLaunchKernelGGL(ranked_swap_kernel, dim3(1), dim3(LSR_T), 0, st, n, M, gb, r, order_out, batch_end_out, F_out,
+                           swaps_out, num_batches_out, pad, d_words);
+        if (M < LS_TABLE) return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;  // then every size is below it
+    } else {
+        const int rc = kvs_launch_scan_lengths(s, o, n, M, 0, d_words, st);
+        if (rc != KVSCHED_OK) return rc;
+    }
     hipLaunchKernelGGL(local_swap_kernel, dim3(1), dim3(LS_T), 0, st, n, s, o, M, ga, gb, order_out, batch_end_out, F_out,
-                       swaps_out, num_batches_out, gw, go, gid, alt_o, buf0, buf1, by_o, batch_of, d_words);
+                       swaps_out, num_batches_out, gw, go, gid, alt_o, buf0, buf1, by_o, batch_of, d_words, state, pad);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

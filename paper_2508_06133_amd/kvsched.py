@@ -240,11 +240,12 @@ class Context:
         """Phase 1 with Local Swap Search -> (order [n], batch_end [n], F [n], swaps [n], num_batches [1])."""
         n = s.shape[0]
         dev = s.device
+        self._pad_outputs(True)
         order = torch.empty(n, dtype=torch.int32, device=dev)
-        ends = torch.zeros(n, dtype=torch.int32, device=dev)
-        F = torch.zeros(n, dtype=torch.float64, device=dev)
-        swaps = torch.zeros(n, dtype=torch.int32, device=dev)
-        nb = torch.zeros(1, dtype=torch.int32, device=dev)
+        ends = torch.empty(n, dtype=torch.int32, device=dev)
+        F = torch.empty(n, dtype=torch.float64, device=dev)
+        swaps = torch.empty(n, dtype=torch.int32, device=dev)
+        nb = torch.empty(1, dtype=torch.int32, device=dev)
         rc = _lib.kvsched_local_swap(self._h, n, _dev(s, torch.int32, "s"), _dev(o, torch.int32, "o"), int(M),
                                      order.data_ptr(), ends.data_ptr(), F.data_ptr(), swaps.data_ptr(),
                                      nb.data_ptr(), _stream())
@@ -289,11 +290,13 @@ class Context:
         -> (order [n], batch_end [n], G [n], swaps [n], num_batches [1])."""
         n = s.shape[0]
         dev = s.device
+        self._pad_outputs(True)
+        padded = torch.zeros if solver == SOLVER_EXACT_DP else torch.empty
         order = torch.empty(n, dtype=torch.int32, device=dev)
-        ends = torch.zeros(n, dtype=torch.int32, device=dev)
-        G = torch.zeros(n, dtype=torch.float64, device=dev)
-        swaps = torch.zeros(n, dtype=torch.int32, device=dev)
-        nb = torch.zeros(1, dtype=torch.int32, device=dev)
+        ends = padded(n, dtype=torch.int32, device=dev)
+        G = padded(n, dtype=torch.float64, device=dev)
+        swaps = (torch.empty if solver == SOLVER_LOCAL_SWAP else torch.zeros)(n, dtype=torch.int32, device=dev)
+        nb = torch.empty(1, dtype=torch.int32, device=dev)
         rc = _lib.kvsched_phase1_G(self._h, int(solver), n, _dev(s, torch.int32, "s"), _dev(o, torch.int32, "o"), int(M),
                                    int(alpha[0]), int(alpha[1]), int(tie_rule), int(feas_mode), order.data_ptr(),
                                    ends.data_ptr(), G.data_ptr(), swaps.data_ptr(), nb.data_ptr(), _stream())
