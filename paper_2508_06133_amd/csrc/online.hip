@@ -12,7 +12,7 @@
 // the first round at which it might, the next arrival and the next refresh that could change the
 // list (refreshes of an unchanged backlog reproduce the list and are only counted).
 //
-// A stream is a chain of small dependent steps (a refresh of the paper's setting is some
+// A stream is a chain of small dependent steps (a whole plan in the paper's setting is some
 // twenty batches and a hundred exchanges on fifty requests), so nothing is gained by putting
 // more lanes on one stream; the chip is filled by running thousands of streams side by side.
 // One wavefront per stream needs no workgroup barrier anywhere: every decision is a ballot or a
@@ -205,14 +205,21 @@ __device__ __forceinline__ int upper_bound_size(const u64 *wk, int n, int lim)
 
 // ------------------------------------------------- Sorted-F-Online's look-ahead window
 //
-// src[0..wn) are backlog keys in (s+o, o, id) order.  Phase 1 of Algorithm 1 with every batch
-// chosen by Local Swap Search over these wn requests alone (budget M): greedy fill in that
+// The window: backlog keys in (s+o, o, id) order.  Phase 1 of Algorithm 1 with every batch
+// chosen by Local Swap Search over these requests alone (budget M): greedy fill in that
 // order, then the first improving exchange (members and non-members scanned in the sorted
 // order; |X| is fixed, so F falls exactly when o_in < o_out) until none is left; the batch is
-// emitted by (o, id) and removed.  Writes the wn keys to list[0..wn) in priority order.
-// wk: WCAP keys of working storage; tmp: an idle array of >= max(wn + 1 ints, wn keys).
+// emitted by (o, id) and removed.
+//
+// The plan is made batch by batch, as far as admission asks for it: a batch depends on what the batches
+// before it left over (wk), not on anything that happens meanwhile, and at the next refresh
+// all that has not been asked for is planned anew (in the paper's setting twenty to thirty batches, of which
+// admission looks at one or two: 600 streams of it, 23.0 -> 4.9 ms).
+//
+// plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
+// tmp: an idle array of >= max(m + 1 ints, m keys).
 template <int WCAP>
-__device__ void plan_window(const u64 *src, int wn, int M, u64 *wk, u64 *tmp, u64 *list)
+__device__ int plan_batch(u64 *wk, int m, int M, u64 *tmp, u64 *list)
 {
     constexpr int RMAX = WCAP / 64;
     constexpr u64 LOW34 = (1ull << 34) - 1;  // (o, id) of a key
@@ -220,177 +227,170 @@ __device__ void plan_window(const u64 *src, int wn, int M, u64 *wk, u64 *tmp, u6
     int *pm = (int *)tmp;  // pm[j] = least o among non-members at places < j, j = 0..m
     u64 *bkey = tmp;       // the batch's keys (after the exchanges, pm is no longer needed)
 
-    for (int i = lane; i < wn; i += 64) wk[i] = src[i];
-    wave_sync();
-
-    int m = wn, outpos = 0;
-    while (m > 0) {
-        const int R = (m + 63) >> 6;
-        // this lane's places 64 r + lane
-        int wreg[RMAX], oreg[RMAX];
-        unsigned valid = 0, mem = 0;  // bit r: place exists / is in the batch
+    const int R = (m + 63) >> 6;
+    // this lane's places 64 r + lane
+    int wreg[RMAX], oreg[RMAX];
+    unsigned valid = 0, mem = 0;  // bit r: place exists / is in the batch
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            wreg[r] = 0;
-            oreg[r] = INT_MAX;
-            if (r < R && 64 * r + lane < m) {
-                const u64 k = wk[64 * r + lane];
-                wreg[r] = (int)(k >> 34);
-                oreg[r] = (int)((k >> 20) & 0x3fffu);
-                valid |= 1u << r;
-            }
+    for (int r = 0; r < RMAX; ++r) {
+        wreg[r] = 0;
+        oreg[r] = INT_MAX;
+        if (r < R && 64 * r + lane < m) {
+            const u64 k = wk[64 * r + lane];
+            wreg[r] = (int)(k >> 34);
+            oreg[r] = (int)((k >> 20) & 0x3fffu);
+            valid |= 1u << r;
         }
-        // greedy fill: sizes ascend, so "add while it fits" is the longest prefix within M
-        const unsigned cap = (unsigned)M + 1u;
-        unsigned carry = 0;
-        int K = 0, memsum = 0;
+    }
+    // greedy fill: sizes ascend, so "add while it fits" is the longest prefix within M
+    const unsigned cap = (unsigned)M + 1u;
+    unsigned carry = 0;
+    int K = 0, memsum = 0;
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            if (r < R) {
-                const unsigned incl = min(wave_incl_add_sat((unsigned)wreg[r], cap) + carry, cap);
-                const bool in = ((valid >> r) & 1u) && incl <= (unsigned)M;
-                if (in) mem |= 1u << r;
-                const u64 bal = __builtin_amdgcn_ballot_w64(in);
-                K += __popcll(bal);
-                memsum += wave_sum(in ? wreg[r] : 0);
-                carry = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
-            }
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const unsigned incl = min(wave_incl_add_sat((unsigned)wreg[r], cap) + carry, cap);
+            const bool in = ((valid >> r) & 1u) && incl <= (unsigned)M;
+            if (in) mem |= 1u << r;
+            const u64 bal = __builtin_amdgcn_ballot_w64(in);
+            K += __popcll(bal);
+            memsum += wave_sum(in ? wreg[r] : 0);
+            carry = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
         }
+    }
 
-        // Small batches in a window of at most two rows (the paper's online setting: a few requests
-        // per batch, some tens waiting) are searched as the pseudo-code scans: members in sorted
-        // order, each against all non-members at once from the registers.  Otherwise every member
-        // is tested at once through the prefix minimum of o over the non-members.
-        const bool by_member = R <= 2 && K <= 32;
-        for (;;) {  // one exchange per turn; every exchange lowers the batch's sum of o
-            const int slack = M - memsum;
-            int astar = -1, bstar = -1, wa = 0, wb = 0;
-            if (by_member) {
+    // Small batches in a window of at most two rows (the paper's online setting: a few requests
+    // per batch, some tens waiting) are searched as the pseudo-code scans: members in sorted
+    // order, each against all non-members at once from the registers.  Otherwise every member
+    // is tested at once through the prefix minimum of o over the non-members.
+    const bool by_member = R <= 2 && K <= 32;
+    for (;;) {  // one exchange per turn; every exchange lowers the batch's sum of o
+        const int slack = M - memsum;
+        int astar = -1, bstar = -1, wa = 0, wb = 0;
+        if (by_member) {
 #pragma unroll
-                for (int ra = 0; ra < 2; ++ra) {
-                    if (ra < R && astar < 0) {
-                        u64 todo = __builtin_amdgcn_ballot_w64((mem >> ra) & 1u);
-                        while (todo != 0 && astar < 0) {
-                            const int la = first_lane(todo);
-                            todo &= todo - 1;
-                            const int w_out = __builtin_amdgcn_readlane(wreg[ra], la);
-                            const int o_out = __builtin_amdgcn_readlane(oreg[ra], la);
+            for (int ra = 0; ra < 2; ++ra) {
+                if (ra < R && astar < 0) {
+                    u64 todo = __builtin_amdgcn_ballot_w64((mem >> ra) & 1u);
+                    while (todo != 0 && astar < 0) {
+                        const int la = first_lane(todo);
+                        todo &= todo - 1;
+                        const int w_out = __builtin_amdgcn_readlane(wreg[ra], la);
+                        const int o_out = __builtin_amdgcn_readlane(oreg[ra], la);
 #pragma unroll
-                            for (int rb = 0; rb < 2; ++rb) {
-                                if (rb < R && astar < 0) {
-                                    const bool ok = ((valid >> rb) & 1u) && !((mem >> rb) & 1u) &&
-                                                    wreg[rb] <= w_out + slack && oreg[rb] < o_out;
-                                    const u64 bal = __builtin_amdgcn_ballot_w64(ok);
-                                    if (bal != 0) {
-                                        astar = 64 * ra + la;
-                                        bstar = 64 * rb + first_lane(bal);
-                                        wa = w_out;
-                                        wb = __builtin_amdgcn_readlane(wreg[rb], first_lane(bal));
-                                    }
+                        for (int rb = 0; rb < 2; ++rb) {
+                            if (rb < R && astar < 0) {
+                                const bool ok = ((valid >> rb) & 1u) && !((mem >> rb) & 1u) &&
+                                                wreg[rb] <= w_out + slack && oreg[rb] < o_out;
+                                const u64 bal = __builtin_amdgcn_ballot_w64(ok);
+                                if (bal != 0) {
+                                    astar = 64 * ra + la;
+                                    bstar = 64 * rb + first_lane(bal);
+                                    wa = w_out;
+                                    wb = __builtin_amdgcn_readlane(wreg[rb], first_lane(bal));
                                 }
                             }
                         }
                     }
                 }
-                if (astar < 0) break;
-            } else {
-                int run = INT_MAX, oa = 0;
+            }
+            if (astar < 0) break;
+        } else {
+            int run = INT_MAX, oa = 0;
 #pragma unroll
-                for (int r = 0; r < RMAX; ++r) {
-                    if (r < R) {
-                        const bool out = ((valid >> r) & 1u) && !((mem >> r) & 1u);
-                        const int upto = wave_incl_min(out ? oreg[r] : INT_MAX);
-                        pm[64 * r + lane] = min(dpp<DPP_WAVE_SHR1>(INT_MAX, upto), run);  // lane 0: run alone
-                        run = min(run, __builtin_amdgcn_readlane(upto, 63));
-                    }
+            for (int r = 0; r < RMAX; ++r) {
+                if (r < R) {
+                    const bool out = ((valid >> r) & 1u) && !((mem >> r) & 1u);
+                    const int upto = wave_incl_min(out ? oreg[r] : INT_MAX);
+                    pm[64 * r + lane] = min(dpp<DPP_WAVE_SHR1>(INT_MAX, upto), run);  // lane 0: run alone
+                    run = min(run, __builtin_amdgcn_readlane(upto, 63));
                 }
-                if (lane == 0) pm[m] = run;
-                wave_sync();
-                // a member has a partner iff some non-member that still fits has a smaller o; those
-                // that fit are the places before the first size above w + slack
+            }
+            if (lane == 0) pm[m] = run;
+            wave_sync();
+            // a member has a partner iff some non-member that still fits has a smaller o; those
+            // that fit are the places before the first size above w + slack
 #pragma unroll
-                for (int r = 0; r < RMAX; ++r) {
-                    if (r < R && astar < 0) {
-                        const bool is_mem = (mem >> r) & 1u;
-                        if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
-                            bool has = false;
-                            if (is_mem) {
-                                const int ub = upper_bound_size(wk, m, wreg[r] + slack);
-                                has = pm[ub] < oreg[r];
-                            }
-                            const u64 bal = __builtin_amdgcn_ballot_w64(has);
-                            if (bal != 0) {
-                                astar = 64 * r + first_lane(bal);
-                                wa = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
-                                oa = __builtin_amdgcn_readlane(oreg[r], first_lane(bal));
-                            }
+            for (int r = 0; r < RMAX; ++r) {
+                if (r < R && astar < 0) {
+                    const bool is_mem = (mem >> r) & 1u;
+                    if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
+                        bool has = false;
+                        if (is_mem) {
+                            const int ub = upper_bound_size(wk, m, wreg[r] + slack);
+                            has = pm[ub] < oreg[r];
                         }
-                    }
-                }
-                wave_sync();
-                if (astar < 0) break;
-#pragma unroll
-                for (int r = 0; r < RMAX; ++r) {
-                    if (r < R && bstar < 0) {
-                        const bool ok = ((valid >> r) & 1u) && !((mem >> r) & 1u) && oreg[r] < oa;
-                        const u64 bal = __builtin_amdgcn_ballot_w64(ok);
+                        const u64 bal = __builtin_amdgcn_ballot_w64(has);
                         if (bal != 0) {
-                            bstar = 64 * r + first_lane(bal);
-                            wb = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
+                            astar = 64 * r + first_lane(bal);
+                            wa = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
+                            oa = __builtin_amdgcn_readlane(oreg[r], first_lane(bal));
                         }
                     }
                 }
-                if (bstar < 0) break;  // cannot happen: pm[] promised a partner before the bound
             }
-            memsum += wb - wa;
-            if (lane == (astar & 63)) mem &= ~(1u << (astar >> 6));
-            if (lane == (bstar & 63)) mem |= 1u << (bstar >> 6);
-        }
-
-        // the batch in nondecreasing o, ties by id: rank of each member among the members
-        int nmem = 0;
+            wave_sync();
+            if (astar < 0) break;
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            if (r < R) {
-                const bool is_mem = (mem >> r) & 1u;
-                const u64 bal = __builtin_amdgcn_ballot_w64(is_mem);
-                if (is_mem) bkey[nmem + __popcll(bal & lanes_below())] = wk[64 * r + lane];
-                nmem += __popcll(bal);
-            }
-        }
-        wave_sync();
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            if (r < R) {
-                const bool is_mem = (mem >> r) & 1u;
-                if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
-                    const u64 mine = wk[64 * r + lane];
-                    const u64 me = mine & LOW34;
-                    int rank = 0;
-                    for (int j = 0; j < K; ++j) rank += ((bkey[j] & LOW34) < me) ? 1 : 0;
-                    if (is_mem) list[outpos + rank] = mine;
+            for (int r = 0; r < RMAX; ++r) {
+                if (r < R && bstar < 0) {
+                    const bool ok = ((valid >> r) & 1u) && !((mem >> r) & 1u) && oreg[r] < oa;
+                    const u64 bal = __builtin_amdgcn_ballot_w64(ok);
+                    if (bal != 0) {
+                        bstar = 64 * r + first_lane(bal);
+                        wb = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
+                    }
                 }
             }
+            if (bstar < 0) break;  // cannot happen: pm[] promised a partner before the bound
         }
-        wave_sync();
-        // what remains closes up in place, still sorted: row by row, each row read before it is
-        // written, and never written beyond itself
-        int kept = 0;
+        memsum += wb - wa;
+        if (lane == (astar & 63)) mem &= ~(1u << (astar >> 6));
+        if (lane == (bstar & 63)) mem |= 1u << (bstar >> 6);
+    }
+
+    // the batch in nondecreasing o, ties by id: rank of each member among the members
+    int nmem = 0;
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            if (r < R) {
-                const bool keep = ((valid >> r) & 1u) && !((mem >> r) & 1u);
-                const u64 k = ((valid >> r) & 1u) ? wk[64 * r + lane] : 0;
-                const u64 bal = __builtin_amdgcn_ballot_w64(keep);
-                wave_sync();
-                if (keep) wk[kept + __popcll(bal & lanes_below())] = k;
-                kept += __popcll(bal);
-                wave_sync();
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const bool is_mem = (mem >> r) & 1u;
+            const u64 bal = __builtin_amdgcn_ballot_w64(is_mem);
+            if (is_mem) bkey[nmem + __popcll(bal & lanes_below())] = wk[64 * r + lane];
+            nmem += __popcll(bal);
+        }
+    }
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const bool is_mem = (mem >> r) & 1u;
+            if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
+                const u64 mine = wk[64 * r + lane];
+                const u64 me = mine & LOW34;
+                int rank = 0;
+                for (int j = 0; j < K; ++j) rank += ((bkey[j] & LOW34) < me) ? 1 : 0;
+                if (is_mem) list[rank] = mine;
             }
         }
-        outpos += K;
-        m -= K;
     }
+    wave_sync();
+    // what remains closes up in place, still sorted: row by row, each row read before it is
+    // written, and never written beyond itself
+    int kept = 0;
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const bool keep = ((valid >> r) & 1u) && !((mem >> r) & 1u);
+            const u64 k = ((valid >> r) & 1u) ? wk[64 * r + lane] : 0;
+            const u64 bal = __builtin_amdgcn_ballot_w64(keep);
+            wave_sync();
+            if (keep) wk[kept + __popcll(bal & lanes_below())] = k;
+            kept += __popcll(bal);
+            wave_sync();
+        }
+    }
+    return K;
 }
 
 // ------------------------------------------------------------------------ the stream kernel
@@ -484,6 +484,7 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
     int head = 0;          // list entries are list[(head + i) & QM], i < q
     int planned_left = 0;  // leading list entries that were placed by the last refresh
     int known = 0, started = 0;
+    int wn = 0, planned = 0;  // window of the last refresh, and how many of its entries are planned (list[0 ... planned))
     int t_plan = 0, backlog_at_plan = 0;
     long long refreshes = 0, sum_c = 0, sum_a = 0;  // sum_a: this lane's share
     int last_c = 0, max_backlog = 0;
@@ -548,16 +549,14 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
 
         // ---- 2. refresh of the cached order
         bool refreshed = false;
-        int wn = 0;
         if (q > 0) {
             const long long newly = q - planned_left;
             const bool due = planned_left == 0 || t - t_plan >= period ||
                              (rden > 0 && newly * rden >= (long long)rnum * backlog_at_plan);
             if (due) {
-                if (planner == KVSCHED_PLANNER_SORTED_F && window > 0) {
-                    wn = min(window, q);
-                    plan_window<Lds::WCAP>(cur, wn, M, L.wk, oth, L.list);
-                }
+                wn = planner == KVSCHED_PLANNER_SORTED_F ? min(window, q) : 0;
+                planned = 0;
+                for (int i = lane; i < wn; i += 64) L.wk[i] = cur[i];
                 for (int i = wn + lane; i < q; i += 64) L.list[i] = cur[i];
                 head = 0;
                 planned_left = q;
@@ -575,6 +574,8 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         int adm = 0;
         int wait_to = t + 1;  // when the loop stops at a request: a round before which it cannot start
         while (adm < q) {
+            if (head + adm == planned && planned < wn)  // (the window's entries are never wrapped: head counts from the refresh)
+                planned += plan_batch<Lds::WCAP>(L.wk, wn - planned, M, oth, L.list + planned);
             const u64 key = uni64(L.list[(head + adm) & QM]);
             const int oo = codec.decode(key), id = codec.id(key);
             const int sr = codec.size(key) - oo;
