@@ -981,8 +981,8 @@ __device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_
         int a, b, l_a = 0;
         u64 have = __builtin_amdgcn_ballot_w64(x_a != 0);
         if (NW == 1) {
-            l_a = (int)__builtin_ctzll(have);
-            x_a = (unsigned)__builtin_amdgcn_readlane((int)x_a, l_a & 63);
+            l_a = (__ffsll((long long)have) - 1) & 63;  // (any lane if there is none: the loop ends below)
+            x_a = (unsigned)__builtin_amdgcn_readlane((int)x_a, l_a);
         } else {
             if (have != 0) {
                 const int l = (int)__builtin_ctzll(have);
@@ -1005,8 +1005,8 @@ __device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_
         if (NW == 1) {
             a = l_a * E + (int)(x_a & 15);
             found = __builtin_amdgcn_ballot_w64(x_b != ~0u);
-            const int l = (int)__builtin_ctzll(found);
-            x_b = (unsigned)__builtin_amdgcn_readlane((int)x_b, l & 63);
+            const int l = (__ffsll((long long)found) - 1) & 63;
+            x_b = (unsigned)__builtin_amdgcn_readlane((int)x_b, l);
             b = l * E + (int)(x_b & 15);
         } else {
             if (have != 0 && x_b != ~0u && before >= below[0]) L.first_in[slot] = (u64)(unsigned)(q + (int)(x_b & 15)) << 32 | x_b;

@@ -127,15 +127,7 @@ constexpr int DPP_WAVE_SHR1 = 0x138;                      // every lane from the
     v = OP(v, dpp<DPP_HALF_MIRROR>(v, v));            \
     v = OP(v, dpp<DPP_MIRROR>(v, v));
 
-__device__ __forceinline__ int op_add(int a, int b) { return a + b; }
 __device__ __forceinline__ int op_max(int a, int b) { return max(a, b); }
-
-__device__ __forceinline__ int wave_sum(int v)
-{
-    KVS_ROW_BUTTERFLY(v, op_add)
-    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
-           __builtin_amdgcn_readlane(v, 48);
-}
 
 __device__ __forceinline__ long long wave_sum64(long long v)
 {
@@ -191,18 +183,6 @@ __device__ __forceinline__ int lower_bound_u64(const u64 *a, int n, u64 key)
     return lo;
 }
 
-// first index of wk[0..n) (keys ascending in s+o) whose s+o exceeds lim
-__device__ __forceinline__ int upper_bound_size(const u64 *wk, int n, int lim)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if ((int)(wk[mid] >> 34) <= lim) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
 // ------------------------------------------------- Sorted-F-Online's look-ahead window
 //
 // The window: backlog keys in (s+o, o, id) order.  Phase 1 of Algorithm 1 with every batch
@@ -216,137 +196,119 @@ __device__ __forceinline__ int upper_bound_size(const u64 *wk, int n, int lim)
 // all that has not been asked for is planned anew (in the paper's setting twenty to thirty batches, of which
 // admission looks at one or two: 600 streams of it, 23.0 -> 4.9 ms).
 //
+// The exchanges work from registers alone: the first non-member with a smaller o than a member's is always a
+// record, a non-member with less o than every non-member before it, and of some fifty requests four or five
+// are.  A member has a partner iff a record that still fits has less o than it, so all members are tested
+// against one record after the other (a prefix minimum in LDS with a binary search per member took three times as long).
+//
 // plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
-// tmp: an idle array of >= max(m + 1 ints, m keys).
-template <int WCAP>
-__device__ int plan_batch(u64 *wk, int m, int M, u64 *tmp, u64 *list)
+// bkey: an idle array of >= m keys, an even number.
+// m <= 64 RMAX (two rows, where the paper's backlogs fit, keep the whole state in scalar and vector registers
+// without a test per row).
+template <int RMAX>
+__device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 *list)
 {
-    constexpr int RMAX = WCAP / 64;
     constexpr u64 LOW34 = (1ull << 34) - 1;  // (o, id) of a key
+    constexpr unsigned IN = 0x80000000u, NONE = 0x7fffffffu;
+    constexpr int G = RMAX <= 2 ? 2 : 1;  // records tested at a time: what each waits for overlaps
     const int lane = lane_id();
-    int *pm = (int *)tmp;  // pm[j] = least o among non-members at places < j, j = 0..m
-    u64 *bkey = tmp;       // the batch's keys (after the exchanges, pm is no longer needed)
-
-    const int R = (m + 63) >> 6;
-    // this lane's places 64 r + lane
-    int wreg[RMAX], oreg[RMAX];
-    unsigned valid = 0, mem = 0;  // bit r: place exists / is in the batch
+    const int R = RMAX <= 2 ? RMAX : (m + 63) >> 6;
+    // this lane's places 64 r + lane: size, and o with the sign bit set in a member (no place: NONE)
+    int w[RMAX];
+    unsigned v[RMAX];
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
-        wreg[r] = 0;
-        oreg[r] = INT_MAX;
-        if (r < R && 64 * r + lane < m) {
-            const u64 k = wk[64 * r + lane];
-            wreg[r] = (int)(k >> 34);
-            oreg[r] = (int)((k >> 20) & 0x3fffu);
-            valid |= 1u << r;
+        if (r < R) {
+            const bool is = 64 * r + lane < m;
+            const u64 k = wk[min(64 * r + lane, m - 1)];
+            w[r] = is ? (int)(k >> 34) : 0;
+            v[r] = is ? (unsigned)(k >> 20) & 0x3fffu : NONE;
         }
     }
     // greedy fill: sizes ascend, so "add while it fits" is the longest prefix within M
     const unsigned cap = (unsigned)M + 1u;
     unsigned carry = 0;
-    int K = 0, memsum = 0;
+    int K = 0, slack = M;
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
-        if (r < R) {
-            const unsigned incl = min(wave_incl_add_sat((unsigned)wreg[r], cap) + carry, cap);
-            const bool in = ((valid >> r) & 1u) && incl <= (unsigned)M;
-            if (in) mem |= 1u << r;
-            const u64 bal = __builtin_amdgcn_ballot_w64(in);
-            K += __popcll(bal);
-            memsum += wave_sum(in ? wreg[r] : 0);
+        if (r < R && K == 64 * r) {
+            const unsigned incl = min(wave_incl_add_sat((unsigned)w[r], cap) + carry, cap);
+            const bool in = v[r] != NONE && incl <= (unsigned)M;
+            if (in) v[r] |= IN;
+            const int c = __popcll(__builtin_amdgcn_ballot_w64(in));
+            K += c;
+            if (c > 0) slack = M - __builtin_amdgcn_readlane((int)incl, c - 1);
             carry = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
         }
     }
 
-    // Small batches in a window of at most two rows (the paper's online setting: a few requests
-    // per batch, some tens waiting) are searched as the pseudo-code scans: members in sorted
-    // order, each against all non-members at once from the registers.  Otherwise every member
-    // is tested at once through the prefix minimum of o over the non-members.
-    const bool by_member = R <= 2 && K <= 32;
     for (;;) {  // one exchange per turn; every exchange lowers the batch's sum of o
-        const int slack = M - memsum;
-        int astar = -1, bstar = -1, wa = 0, wb = 0;
-        if (by_member) {
+        u64 has[RMAX], records[RMAX];
+        int upto[RMAX];
 #pragma unroll
-            for (int ra = 0; ra < 2; ++ra) {
-                if (ra < R && astar < 0) {
-                    u64 todo = __builtin_amdgcn_ballot_w64((mem >> ra) & 1u);
-                    while (todo != 0 && astar < 0) {
-                        const int la = first_lane(todo);
-                        todo &= todo - 1;
-                        const int w_out = __builtin_amdgcn_readlane(wreg[ra], la);
-                        const int o_out = __builtin_amdgcn_readlane(oreg[ra], la);
-#pragma unroll
-                        for (int rb = 0; rb < 2; ++rb) {
-                            if (rb < R && astar < 0) {
-                                const bool ok = ((valid >> rb) & 1u) && !((mem >> rb) & 1u) &&
-                                                wreg[rb] <= w_out + slack && oreg[rb] < o_out;
-                                const u64 bal = __builtin_amdgcn_ballot_w64(ok);
-                                if (bal != 0) {
-                                    astar = 64 * ra + la;
-                                    bstar = 64 * rb + first_lane(bal);
-                                    wa = w_out;
-                                    wb = __builtin_amdgcn_readlane(wreg[rb], first_lane(bal));
-                                }
-                            }
-                        }
-                    }
-                }
-            }
-            if (astar < 0) break;
-        } else {
-            int run = INT_MAX, oa = 0;
-#pragma unroll
-            for (int r = 0; r < RMAX; ++r) {
-                if (r < R) {
-                    const bool out = ((valid >> r) & 1u) && !((mem >> r) & 1u);
-                    const int upto = wave_incl_min(out ? oreg[r] : INT_MAX);
-                    pm[64 * r + lane] = min(dpp<DPP_WAVE_SHR1>(INT_MAX, upto), run);  // lane 0: run alone
-                    run = min(run, __builtin_amdgcn_readlane(upto, 63));
-                }
-            }
-            if (lane == 0) pm[m] = run;
-            wave_sync();
-            // a member has a partner iff some non-member that still fits has a smaller o; those
-            // that fit are the places before the first size above w + slack
-#pragma unroll
-            for (int r = 0; r < RMAX; ++r) {
-                if (r < R && astar < 0) {
-                    const bool is_mem = (mem >> r) & 1u;
-                    if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
-                        bool has = false;
-                        if (is_mem) {
-                            const int ub = upper_bound_size(wk, m, wreg[r] + slack);
-                            has = pm[ub] < oreg[r];
-                        }
-                        const u64 bal = __builtin_amdgcn_ballot_w64(has);
-                        if (bal != 0) {
-                            astar = 64 * r + first_lane(bal);
-                            wa = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
-                            oa = __builtin_amdgcn_readlane(oreg[r], first_lane(bal));
-                        }
-                    }
-                }
-            }
-            wave_sync();
-            if (astar < 0) break;
-#pragma unroll
-            for (int r = 0; r < RMAX; ++r) {
-                if (r < R && bstar < 0) {
-                    const bool ok = ((valid >> r) & 1u) && !((mem >> r) & 1u) && oreg[r] < oa;
-                    const u64 bal = __builtin_amdgcn_ballot_w64(ok);
-                    if (bal != 0) {
-                        bstar = 64 * r + first_lane(bal);
-                        wb = __builtin_amdgcn_readlane(wreg[r], first_lane(bal));
-                    }
-                }
-            }
-            if (bstar < 0) break;  // cannot happen: pm[] promised a partner before the bound
+        for (int r = 0; r < RMAX; ++r) {
+            has[r] = 0;
+            if (r < R) upto[r] = wave_incl_min((int)min(v[r], NONE));
         }
-        memsum += wb - wa;
-        if (lane == (astar & 63)) mem &= ~(1u << (astar >> 6));
-        if (lane == (bstar & 63)) mem |= 1u << (bstar >> 6);
+        unsigned low = NONE;  // least o of a non-member in the rows before
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r < R) {
+                records[r] = __builtin_amdgcn_ballot_w64(v[r] < min((unsigned)dpp<DPP_WAVE_SHR1>(INT_MAX, upto[r]), low));
+                low = min(low, (unsigned)__builtin_amdgcn_readlane(upto[r], 63));
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r < R) {
+                while (records[r] != 0) {
+                    int w_in[G];
+                    unsigned above[G];
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const bool is = records[r] != 0;
+                        const int l = first_lane(records[r]) & 63;
+                        w_in[u] = __builtin_amdgcn_readlane(w[r], l) - slack;  // members of at least this size have room for it
+                        above[u] = is ? (unsigned)__builtin_amdgcn_readlane((int)v[r], l) | IN : ~0u;
+                        records[r] &= records[r] - 1;
+                    }
+#pragma unroll
+                    for (int rr = 0; rr < RMAX; ++rr) {
+                        if (rr < R) {
+#pragma unroll
+                            for (int u = 0; u < G; ++u)
+                                has[rr] |= __builtin_amdgcn_ballot_w64(v[rr] > above[u]) & __builtin_amdgcn_ballot_w64(w[rr] >= w_in[u]);
+                        }
+                    }
+                }
+            }
+        }
+        int ra = -1, la = 0;
+        unsigned o_out = 0;
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r < R && ra < 0 && has[r] != 0) {
+                ra = r;
+                la = first_lane(has[r]);
+                o_out = (unsigned)__builtin_amdgcn_readlane((int)v[r], la) & ~IN;
+                slack += __builtin_amdgcn_readlane(w[r], la);
+            }
+        }
+        if (ra < 0) break;
+        bool found = false;
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r < R) {
+                const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < o_out);
+                if (r == ra && lane == la) v[r] ^= IN;
+                if (!found && bal != 0) {  // always met: a record said so
+                    found = true;
+                    const int lb = first_lane(bal);
+                    slack -= __builtin_amdgcn_readlane(w[r], lb);
+                    if (lane == lb) v[r] ^= IN;
+                }
+            }
+        }
     }
 
     // the batch in nondecreasing o, ties by id: rank of each member among the members
@@ -354,25 +316,21 @@ __device__ int plan_batch(u64 *wk, int m, int M, u64 *tmp, u64 *list)
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         if (r < R) {
-            const bool is_mem = (mem >> r) & 1u;
+            const bool is_mem = v[r] >= IN;
             const u64 bal = __builtin_amdgcn_ballot_w64(is_mem);
             if (is_mem) bkey[nmem + __popcll(bal & lanes_below())] = wk[64 * r + lane];
             nmem += __popcll(bal);
         }
     }
+    if ((nmem & 1) && lane == 0) bkey[nmem] = ~0ull;  // (the loop below takes them two by two)
     wave_sync();
-#pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-        if (r < R) {
-            const bool is_mem = (mem >> r) & 1u;
-            if (__builtin_amdgcn_ballot_w64(is_mem) != 0) {
-                const u64 mine = wk[64 * r + lane];
-                const u64 me = mine & LOW34;
-                int rank = 0;
-                for (int j = 0; j < K; ++j) rank += ((bkey[j] & LOW34) < me) ? 1 : 0;
-                if (is_mem) list[rank] = mine;
-            }
-        }
+    for (int i0 = 0; i0 < nmem; i0 += 64) {
+        const u64 mine = bkey[min(i0 + lane, nmem - 1)];
+        const u64 me = mine & LOW34;
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < nmem; j += 2) rank += ((bkey[j] & LOW34) < me ? 1 : 0) + ((bkey[j + 1] & LOW34) < me ? 1 : 0);
+        if (i0 + lane < nmem) list[rank] = mine;
     }
     wave_sync();
     // what remains closes up in place, still sorted: row by row, each row read before it is
@@ -381,8 +339,8 @@ __device__ int plan_batch(u64 *wk, int m, int M, u64 *tmp, u64 *list)
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         if (r < R) {
-            const bool keep = ((valid >> r) & 1u) && !((mem >> r) & 1u);
-            const u64 k = ((valid >> r) & 1u) ? wk[64 * r + lane] : 0;
+            const bool keep = v[r] < NONE;
+            const u64 k = wk[min(64 * r + lane, m - 1)];
             const u64 bal = __builtin_amdgcn_ballot_w64(keep);
             wave_sync();
             if (keep) wk[kept + __popcll(bal & lanes_below())] = k;
@@ -390,7 +348,7 @@ __device__ int plan_batch(u64 *wk, int m, int M, u64 *tmp, u64 *list)
             wave_sync();
         }
     }
-    return K;
+    return nmem;
 }
 
 // ------------------------------------------------------------------------ the stream kernel
@@ -486,9 +444,31 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
     int known = 0, started = 0;
     int wn = 0, planned = 0;  // window of the last refresh, and how many of its entries are planned (list[0 ... planned))
     int t_plan = 0, backlog_at_plan = 0;
+    u64 blocked = ~0ull;   // the last request that did not fit, and a round before which it cannot start
+    int blocked_to = 0;
     long long refreshes = 0, sum_c = 0, sum_a = 0;  // sum_a: this lane's share
     int last_c = 0, max_backlog = 0;
-    int next_a = uni(a[0]);
+    // the next up to 64 requests, one per lane (arrivals find them without waiting for memory)
+    struct { int a, s, o, bad; } ahead;
+    int ahead_at = 0;
+    auto read_ahead = [&]() {
+        ahead_at = known;
+        const int idx = known + lane;
+        ahead.a = INT_MAX;
+        ahead.s = ahead.o = 1;
+        ahead.bad = 0;
+        if (idx < count) {
+            ahead.a = a[idx];
+            ahead.s = s[idx];
+            ahead.o = o[idx];
+            const int earlier = idx > 0 ? a[idx - 1] : INT_MIN;
+            if (ahead.s < 1 || ahead.o < 1 || (long long)ahead.s + ahead.o > (long long)M) ahead.bad |= KVSCHED_DEV_BAD_LENGTH;
+            if (ahead.o > H) ahead.bad |= KVSCHED_DEV_O_MAX;
+            if (ahead.a < 0 || earlier > ahead.a) ahead.bad |= KVSCHED_DEV_BAD_ARRIVAL;
+        }
+    };
+    read_ahead();
+    int next_a = uni(ahead.a);
     int fault = 0;
     // No admission for H iterations in a row with a backlog is impossible (every running request
     // has left by then and a single request always fits), idle stretches are skipped in one step:
@@ -505,44 +485,47 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         }
         // ---- 1. arrivals, up to 64 at a time
         while (known < count && next_a <= t) {
-            const int idx = known + lane;
-            const int aj = idx < count ? a[idx] : INT_MAX;
-            const bool in = aj <= t;
-            int sj = 1, oj = 1, bad = 0;
-            if (in) {
-                sj = s[idx];
-                oj = o[idx];
-                if (sj < 1 || oj < 1 || (long long)sj + oj > (long long)M) bad |= KVSCHED_DEV_BAD_LENGTH;
-                if (oj > H) bad |= KVSCHED_DEV_O_MAX;
-                if (aj < 0 || (idx > 0 && a[idx - 1] > aj)) bad |= KVSCHED_DEV_BAD_ARRIVAL;
+            const int off = known - ahead_at;  // the newcomers are lanes off ... off + kc - 1 of the requests read ahead
+            const bool in = lane >= off && ahead.a <= t;
+            const u64 newly = __builtin_amdgcn_ballot_w64(in);
+            const int kc = __popcll(newly);
+            if (__builtin_amdgcn_ballot_w64(in && ahead.bad != 0) != 0) {
+                int bad = in ? ahead.bad : 0;
+                for (int dlt = 32; dlt >= 1; dlt >>= 1) bad |= __shfl_xor(bad, dlt);
+                fault = uni(bad);
             }
-            const int kc = __popcll(__builtin_amdgcn_ballot_w64(in));
-            for (int dlt = 32; dlt >= 1; dlt >>= 1) bad |= __shfl_xor(bad, dlt);
-            fault = uni(bad);
             if (q + kc > p.cap) fault |= KVSCHED_DEV_BACKLOG;
             if (fault) break;
             // merge: a newcomer lands at (entries of the backlog before it) + (newcomers before it);
             // an entry of the backlog moves up by the newcomers before it
-            const u64 key = in ? codec.make(sj + oj, oj, idx) : ~0ull;
-            int rank = 0;
-            for (int i = 0; i < kc; ++i) rank += (lane_u64(key, i) < key) ? 1 : 0;
-            if (in) {
-                oth[lower_bound_u64(cur, q, key) + rank] = key;
-                L.list[(head + q + lane) & QM] = key;  // arrival order
-                sum_a += aj;
-            }
+            const u64 key = in ? codec.make(ahead.s + ahead.o, ahead.o, ahead_at + lane) : ~0ull;
+            int at = 0;
+            for (int j = 0; j < kc; ++j) at += (lane_u64(key, off + j) < key) ? 1 : 0;
             for (int i0 = 0; i0 < q; i0 += 64) {
                 const int i = i0 + lane;
-                const u64 k = i < q ? cur[i] : 0;
+                const u64 k = i < q ? cur[i] : ~0ull;
                 int nb = 0;
-                for (int j = 0; j < kc; ++j) nb += (lane_u64(key, j) < k) ? 1 : 0;
+                for (int j = 0; j < kc; ++j) {
+                    const bool before = k < lane_u64(key, off + j);
+                    nb += before ? 0 : 1;
+                    const int c = __popcll(__builtin_amdgcn_ballot_w64(before));
+                    at += lane == off + j ? c : 0;
+                }
                 if (i < q) oth[i + nb] = k;
+            }
+            if (in) {
+                oth[at] = key;
+                L.list[(head + q + lane - off) & QM] = key;  // arrival order
+                sum_a += ahead.a;
             }
             wave_sync();
             u64 *sw = cur; cur = oth; oth = sw;
             q += kc;
             known += kc;
-            next_a = known < count ? uni(a[known]) : INT_MAX;
+            if (known < count) {
+                if (known - ahead_at == 64) read_ahead();
+                next_a = __builtin_amdgcn_readlane(ahead.a, known - ahead_at);
+            } else next_a = INT_MAX;
         }
         if (fault) break;
         max_backlog = max(max_backlog, q);
@@ -575,19 +558,40 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         int wait_to = t + 1;  // when the loop stops at a request: a round before which it cannot start
         while (adm < q) {
             if (head + adm == planned && planned < wn)  // (the window's entries are never wrapped: head counts from the refresh)
-                planned += plan_batch<Lds::WCAP>(L.wk, wn - planned, M, oth, L.list + planned);
+                planned += wn - planned <= 128 ? plan_batch<2>(L.wk, wn - planned, M, oth, L.list + planned)
+                                               : plan_batch<Lds::WCAP / 64>(L.wk, wn - planned, M, oth, L.list + planned);
             const u64 key = uni64(L.list[(head + adm) & QM]);
             const int oo = codec.decode(key), id = codec.id(key);
             const int sr = codec.size(key) - oo;
+            if (key == blocked && t < blocked_to) {  // found not to start before then (memory only grows by what is admitted)
+                wait_to = blocked_to;
+                break;
+            }
             // round t + j rules out every start before t + min(excess, j): started later the request is
             // smaller at that round by as much, or no longer overlaps it
             int excess = 0;
-            for (int j = lane + 1; j <= oo; j += 64) excess = max(excess, min(L.ring[(t + j) & HM] + sr + j - M, j));
+            for (int j0 = lane + 1; j0 <= oo; j0 += 256) {  // four reads at a time
+                int have[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u) & HM];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j0 + 64 * u <= oo) excess = max(excess, min(have[u] + sr + j0 + 64 * u - M, j0 + 64 * u));
+            }
             if (__builtin_amdgcn_ballot_w64(excess > 0) != 0) {
                 wait_to = t + wave_max(excess);
+                blocked = key;
+                blocked_to = wait_to;
                 break;
             }
-            for (int j = lane + 1; j <= oo; j += 64) L.ring[(t + j) & HM] += sr + j;
+            for (int j0 = lane + 1; j0 <= oo; j0 += 256) {
+                int have[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u) & HM];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j0 + 64 * u <= oo) L.ring[(t + j0 + 64 * u) & HM] = have[u] + sr + j0 + 64 * u;
+            }
             if (lane == 0) cout[id] = t + oo;
             sum_c += t + oo;
             last_c = max(last_c, t + oo);
@@ -597,21 +601,31 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         if (adm > 0) {
             wave_sync();
             if (adm < q) {
-                for (int j = lane; j < adm; j += 64) {
-                    const int pos = lower_bound_u64(cur, q, L.list[(head + j) & QM]);
-                    atomicOr(&L.dead[pos >> 5], 1u << (pos & 31));
+                // a few are looked for by comparing, many by a binary search for each
+                const bool few = adm <= 8;
+                const u64 gone = few ? L.list[(head + min(lane, adm - 1)) & QM] : 0;
+                if (!few) {
+                    for (int j = lane; j < adm; j += 64) {
+                        const int pos = lower_bound_u64(cur, q, L.list[(head + j) & QM]);
+                        atomicOr(&L.dead[pos >> 5], 1u << (pos & 31));
+                    }
+                    wave_sync();
                 }
-                wave_sync();
                 int kept = 0;
                 for (int i0 = 0; i0 < q; i0 += 64) {
                     const int i = i0 + lane;
-                    const bool alive = i < q && !((L.dead[i >> 5] >> (i & 31)) & 1u);
+                    bool alive = i < q;
+                    const u64 k = alive ? cur[i] : 0;
+                    if (few) {
+                        for (int j = 0; j < adm; ++j) alive = alive && k != lane_u64(gone, j);
+                    } else alive = alive && !((L.dead[i >> 5] >> (i & 31)) & 1u);
                     const u64 bal = __builtin_amdgcn_ballot_w64(alive);
-                    if (alive) oth[kept + __popcll(bal & lanes_below())] = cur[i];
+                    if (alive) oth[kept + __popcll(bal & lanes_below())] = k;
                     kept += __popcll(bal);
                 }
                 wave_sync();
-                for (int i = lane; i < (q + 31) / 32; i += 64) L.dead[i] = 0;
+                if (!few)
+                    for (int i = lane; i < (q + 31) / 32; i += 64) L.dead[i] = 0;
                 u64 *sw = cur; cur = oth; oth = sw;
                 wave_sync();
             }
@@ -631,8 +645,8 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
             t_next = min(wait_to, next_a);
             if (refreshed && (wn == 0 || adm == 0)) {
                 const int every = (rden > 0 && rnum == 0) ? 1 : period;
-                const int passed = (t_next - 1 - t) / every;
-                if (passed > 0) {
+                if (t_next - 1 - t >= every) {
+                    const int passed = every == 1 ? t_next - 1 - t : (t_next - 1 - t) / every;
                     refreshes += passed;
                     t_plan = t + passed * every;
                     backlog_at_plan = q;
