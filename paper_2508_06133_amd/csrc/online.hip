@@ -32,7 +32,7 @@
 //   * the look-ahead window of the Sorted-F-Online planner: Phase 1 of Algorithm 1 with Local
 //     Swap Search batches, sorted place 64 r + lane in row r of the lane's registers (greedy fill
 //     = longest prefix by a saturating wave scan; an exchange step = exclusive prefix minimum of
-//     o over non-members, one binary search per member of the first rows, two ballots).
+//     o over non-members, and its records against all members at once).
 #include "kvsched_internal.h"
 #include "phase1_util.h"
 
@@ -198,8 +198,8 @@ __device__ __forceinline__ int lower_bound_u64(const u64 *a, int n, u64 key)
 //
 // The exchanges work from registers alone: the first non-member with a smaller o than a member's is always a
 // record, a non-member with less o than every non-member before it, and of some fifty requests four or five
-// are.  A member has a partner iff a record that still fits has less o than it, so all members are tested
-// against one record after the other (a prefix minimum in LDS with a binary search per member took three times as long).
+// are, most of which are too large for every member or have more o than any.  A member has a partner iff a record that
+// still fits has less o than it, so all members are tested against one record after the other (a prefix minimum in LDS with a binary search per member took three times as long).
 //
 // plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
 // bkey: an idle array of >= m keys, an even number.
@@ -229,32 +229,42 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
     const unsigned cap = (unsigned)M + 1u;
     unsigned carry = 0;
     int K = 0, slack = M;
+    int w_most = 0;       // no member is larger than this, and none has more o than this
+    unsigned o_most = 0;
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         if (r < R && K == 64 * r) {
             const unsigned incl = min(wave_incl_add_sat((unsigned)w[r], cap) + carry, cap);
             const bool in = v[r] != NONE && incl <= (unsigned)M;
+            o_most = max(o_most, in ? v[r] : 0u);
             if (in) v[r] |= IN;
             const int c = __popcll(__builtin_amdgcn_ballot_w64(in));
             K += c;
-            if (c > 0) slack = M - __builtin_amdgcn_readlane((int)incl, c - 1);
+            if (c > 0) {
+                slack = M - __builtin_amdgcn_readlane((int)incl, c - 1);
+                w_most = __builtin_amdgcn_readlane(w[r], c - 1);
+            }
             carry = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
         }
     }
 
+    o_most = (unsigned)wave_max((int)o_most);
+
     for (;;) {  // one exchange per turn; every exchange lowers the batch's sum of o
-        u64 has[RMAX], records[RMAX];
+        u64 records[RMAX];
         int upto[RMAX];
+        unsigned least[RMAX];  // least o of a record for which this lane's member has room
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
-            has[r] = 0;
+            least[r] = ~0u;
             if (r < R) upto[r] = wave_incl_min((int)min(v[r], NONE));
         }
         unsigned low = NONE;  // least o of a non-member in the rows before
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
             if (r < R) {
-                records[r] = __builtin_amdgcn_ballot_w64(v[r] < min((unsigned)dpp<DPP_WAVE_SHR1>(INT_MAX, upto[r]), low));
+                const unsigned before = min(min((unsigned)dpp<DPP_WAVE_SHR1>(INT_MAX, upto[r]), low), o_most);
+                records[r] = __builtin_amdgcn_ballot_w64(v[r] < before) & __builtin_amdgcn_ballot_w64(w[r] <= w_most + slack);
                 low = min(low, (unsigned)__builtin_amdgcn_readlane(upto[r], 63));
             }
         }
@@ -263,52 +273,69 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
             if (r < R) {
                 while (records[r] != 0) {
                     int w_in[G];
-                    unsigned above[G];
+                    unsigned o_in[G];
 #pragma unroll
-                    for (int u = 0; u < G; ++u) {
-                        const bool is = records[r] != 0;
+                    for (int u = 0; u < G; ++u) {  // (past the last record: lane 63 or the record itself, taken for nothing)
                         const int l = first_lane(records[r]) & 63;
+                        const unsigned none = records[r] != 0 ? 0u : ~0u;
                         w_in[u] = __builtin_amdgcn_readlane(w[r], l) - slack;  // members of at least this size have room for it
-                        above[u] = is ? (unsigned)__builtin_amdgcn_readlane((int)v[r], l) | IN : ~0u;
+                        o_in[u] = (unsigned)__builtin_amdgcn_readlane((int)v[r], l) | none;
                         records[r] &= records[r] - 1;
                     }
 #pragma unroll
-                    for (int rr = 0; rr < RMAX; ++rr) {
-                        if (rr < R) {
+                    for (int u = 0; u < G; ++u) {
 #pragma unroll
-                            for (int u = 0; u < G; ++u)
-                                has[rr] |= __builtin_amdgcn_ballot_w64(v[rr] > above[u]) & __builtin_amdgcn_ballot_w64(w[rr] >= w_in[u]);
-                        }
+                        for (int rr = 0; rr < RMAX; ++rr)  // in vector registers: a mask in a scalar one would be waited for
+                            if (rr < R) least[rr] = min(least[rr], (unsigned)((w[rr] - w_in[u]) >> 31) | o_in[u]);
                     }
                 }
             }
         }
-        int ra = -1, la = 0;
-        unsigned o_out = 0;
+        int ra = -1;
+        u64 who = 0;
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            if (r < R && ra < 0 && has[r] != 0) {
-                ra = r;
-                la = first_lane(has[r]);
-                o_out = (unsigned)__builtin_amdgcn_readlane((int)v[r], la) & ~IN;
-                slack += __builtin_amdgcn_readlane(w[r], la);
+        for (int r = RMAX - 1; r >= 0; --r) {
+            if (r < R) {
+                const u64 has = __builtin_amdgcn_ballot_w64(v[r] > min(least[r], NONE) + IN);
+                ra = has != 0 ? r : ra;
+                who = has != 0 ? has : who;
             }
         }
         if (ra < 0) break;
-        bool found = false;
+        const int la = first_lane(who) & 63;
+        unsigned o_out = 0;
+        int w_out = 0;
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
             if (r < R) {
-                const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < o_out);
-                if (r == ra && lane == la) v[r] ^= IN;
-                if (!found && bal != 0) {  // always met: a record said so
-                    found = true;
-                    const int lb = first_lane(bal);
-                    slack -= __builtin_amdgcn_readlane(w[r], lb);
-                    if (lane == lb) v[r] ^= IN;
-                }
+                const unsigned x = (unsigned)__builtin_amdgcn_readlane((int)v[r], la) & ~IN;
+                const int y = __builtin_amdgcn_readlane(w[r], la);
+                o_out = r == ra ? x : o_out;
+                w_out = r == ra ? y : w_out;
             }
         }
+        int rb = -1;  // always found: a record said so
+#pragma unroll
+        for (int r = RMAX - 1; r >= 0; --r) {
+            if (r < R) {
+                const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < o_out);
+                rb = bal != 0 ? r : rb;
+                who = bal != 0 ? bal : who;
+            }
+        }
+        const int lb = first_lane(who) & 63;
+        slack += w_out;
+        int w_in = 0;
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r < R) {
+                const int y = __builtin_amdgcn_readlane(w[r], lb);
+                w_in = r == rb ? y : w_in;
+                v[r] ^= (lane == (r == ra ? la : -1)) != (lane == (r == rb ? lb : -1)) ? IN : 0u;
+            }
+        }
+        slack -= w_in;
+        w_most = max(w_most, w_in);
     }
 
     // the batch in nondecreasing o, ties by id: rank of each member among the members
