@@ -226,10 +226,10 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 #define KVS_SLOT_PAD(bytes) "  .fill (" #bytes "-(.-7b))/4, 4, 0xbf800000\n"
 
 template <int NR>
-__device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, int vmin, int M, int &t, int &b64)
+__device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, int vmin, int M, int &t, int &b64, int &hi)
 {
     int cv, acc, y, z, tl, vw;
-    int ns, oj, x64, off, u64, w, rs, ta, tb, tc, ql, qh, cl, ch, ul, uh, rl, rh;
+    int ns, oj, x64, off, u64, rs, ta, tb, tc, ql, qh, cl, ch, ul, uh, rl, rh;
     long long mk;
 #define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                                       \
     asm volatile(                                                                                       \
@@ -259,11 +259,11 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "    s_movk_i32 s[67+kvs_r], 192*kvs_r\n"                                                       \
         "    .set kvs_r, kvs_r+1\n"                                                                     \
         "  .endr\n"                                                                                     \
-        "  s_mov_b32 %[w], %[M]\n"                                                                      \
+        "  v_sub_u32 %[vw], %[M], %[tl]\n"                                                             \
         ".else\n"                                                                                       \
-        "  s_sub_u32 %[w], %[M], 64\n"                                                                  \
+        "  s_sub_u32 %[tc], %[M], 64\n"                                                                \
+        "  v_sub_u32 %[vw], %[tc], %[tl]\n" /* ramp in lane l of the window's last row: vw + (s - M) + 64 (re + 1) */ \
         ".endif\n"                                                                                      \
-        "v_sub_u32 %[vw], %[w], %[tl]\n"    /* ramp in lane l of the window's last row: vw + (s - M) + 64 (re + 1) */ \
         "v_mov_b32 %[cv], 0\n"                                                                          \
         "s_sub_u32 m0, %[cnt], 1\n"                                                                     \
         /* ---- next request (lane m0, counting down): is it blocked at all? */                         \
@@ -316,6 +316,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_cbranch_vccnz 52f\n"                                                                         \
         /* ---- admit at round t */                                                                     \
         "42:\n"                                                                                         \
+        "s_max_u32 %[hi], %[hi], %[off]\n"                                                              \
         ".if %c[nr] != 65\n"                                                                            \
         "  s_sub_u32 %[rs], %[off], %[ns]\n"                                                            \
         ".endif\n"                                                                                      \
@@ -441,7 +442,12 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_sub_u32 %[u64], %[tc], %[rs]\n"                                                              \
         "v_sub_u32 %[tl], %[u64], %[lane]\n"                                                            \
         "s_add_u32 %[u64], %[u64], 64\n"                                                                \
-        "v_sub_u32 %[vw], %[w], %[tl]\n"                                                                \
+        ".if %c[nr] == 65\n"                                                                            \
+        "  v_sub_u32 %[vw], %[M], %[tl]\n"                                                             \
+        ".else\n"                                                                                       \
+        "  s_sub_u32 %[tc], %[M], 64\n"                                                                \
+        "  v_sub_u32 %[vw], %[tc], %[tl]\n"                                                            \
+        ".endif\n"                                                                                      \
         "s_add_u32 %[x64], %[oj], %[u64]\n"                                                             \
         "s_lshl_b64 %[mk], -2, %[x64]\n"                                                                \
         "s_andn2_b32 %[off], %[x64], 63\n"                                                              \
@@ -452,10 +458,17 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "45:\n"                                                                                         \
         ".set kvs_r, 0\n"                                                                               \
         ".rept %c[nr]-1\n"                                                                              \
+        "  .if (kvs_r & 7) == 0\n"          /* nothing is committed from row hi / 64 on */              \
+        "    s_cmp_le_u32 %[hi], 64*kvs_r\n"                                                           \
+        "    s_cbranch_scc1 54f\n"                                                                     \
+        "  .endif\n"                                                                                    \
         "  v_subrev_u32 v[" KVS_PB "+kvs_r], 64, v[" KVS_PB "+kvs_r+1]\n"                               \
         "  .set kvs_r, kvs_r+1\n"                                                                       \
         ".endr\n"                                                                                       \
         "v_mov_b32 v[" KVS_PB "+%c[nr]-1], 64*(%c[nr]-1)\n"                                             \
+        "54:\n"                                                                                         \
+        "s_sub_u32 %[hi], %[hi], 64\n"                                                                  \
+        "s_max_i32 %[hi], %[hi], 0\n"                                                                   \
         "s_sub_u32 %[rs], %[rs], 1\n"                                                                   \
         "s_cmp_lg_u32 %[rs], 0\n"                                                                       \
         "s_cbranch_scc1 45b\n"                                                                          \
@@ -466,6 +479,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "  v_mov_b32 v[" KVS_PB "+kvs_r], 64*kvs_r\n"                                                   \
         "  .set kvs_r, kvs_r+1\n"                                                                       \
         ".endr\n"                                                                                       \
+        "s_mov_b32 %[hi], 0\n"                                                                          \
         "46:\n"                                                                                         \
         "s_cmp_ge_u32 %[tb], %[off]\n"       /* are all rounds not looked at yet in the window's last row? */ \
         "s_cbranch_scc0 48f\n"                                                                          \
@@ -520,9 +534,9 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "50:\n"                                                                                         \
         : [cv] "=&v"(cv), [acc] "=&v"(acc), [y] "=&v"(y), [z] "=&v"(z), [tl] "=&v"(tl), [vw] "=&v"(vw), \
           [ns] "=&s"(ns), [oj] "=&s"(oj), [x64] "=&s"(x64), [off] "=&s"(off), [u64] "=&s"(u64),         \
-          [w] "=&s"(w), [rs] "=&s"(rs), [ta] "=&s"(ta), [tb] "=&s"(tb), [tc] "=&s"(tc), [ql] "=&s"(ql), \
+          [rs] "=&s"(rs), [ta] "=&s"(ta), [tb] "=&s"(tb), [tc] "=&s"(tc), [ql] "=&s"(ql), \
           [qh] "=&s"(qh), [cl] "=&s"(cl), [ch] "=&s"(ch), [ul] "=&s"(ul), [uh] "=&s"(uh), [rl] "=&s"(rl), \
-          [rh] "=&s"(rh), [mk] "=&s"(mk), [t] "+s"(t), [b64] "+s"(b64)                  \
+          [rh] "=&s"(rh), [mk] "=&s"(mk), [t] "+s"(t), [b64] "+s"(b64), [hi] "+s"(hi)                  \
         : [cnt] "s"(cnt), [vns] "v"(vns), [vo] "v"(vo), [lane] "v"(lane), [vmin] "v"(vmin),             \
           [M] "s"(M), [nr] "n"(NR)                                                                      \
         : "scc", "vcc", SCLOB, CLOB)
@@ -543,24 +557,26 @@ __device__ __forceinline__ int scalar_read(const int32_t *base, int index)
     return v;
 }
 
-// Head of a saved timeline state: words 0, 1 = b64, t (every lane stores the same two values), then
+// Head of a saved timeline state: words 0, 1, 2 = b64, t, hi (every lane stores the same three values), then
 // the lanes' partial sums of completion rounds as 64 int64 at byte 256.  The profile rows follow
 // at byte 768 (prof_store).  Written in assembly so that no temporary can land in the profile block.
 template <int NR>
-__device__ __forceinline__ void state_head_store(int32_t *snap, int b64, int t, long long tel_lane, int lane)
+__device__ __forceinline__ void state_head_store(int32_t *snap, int b64, int t, int hi, long long tel_lane, int lane)
 {
-    int a, b, off;
+    int a, b, c, off;
 #define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                                        \
     asm volatile("v_mov_b32 %[a], %[b64]\n"                                                              \
                  "v_mov_b32 %[b], %[t]\n"                                                                \
+                 "v_mov_b32 %[c], %[hi]\n"                                                               \
                  "v_mov_b32 %[off], 0\n"                                                                 \
                  "global_store_dword %[off], %[a], %[base]\n"                                            \
                  "global_store_dword %[off], %[b], %[base] offset:4\n"                                   \
+                 "global_store_dword %[off], %[c], %[base] offset:8\n"                                   \
                  "v_lshlrev_b32 %[off], 3, %[lane]\n"                                                    \
                  "global_store_dwordx2 %[off], %[tel], %[base] offset:256\n"                             \
                  "s_waitcnt vmcnt(0)\n"                                                                  \
-                 : [a] "=&v"(a), [b] "=&v"(b), [off] "=&v"(off)                                          \
-                 : [base] "s"(snap), [b64] "s"(b64), [t] "s"(t), [tel] "v"(tel_lane), [lane] "v"(lane)   \
+                 : [a] "=&v"(a), [b] "=&v"(b), [c] "=&v"(c), [off] "=&v"(off)                             \
+                 : [base] "s"(snap), [b64] "s"(b64), [t] "s"(t), [hi] "s"(hi), [tel] "v"(tel_lane), [lane] "v"(lane)   \
                  : "memory", CLOB)
     KVS_FOR_NR(KVS_STMT);
 #undef KVS_STMT
@@ -701,6 +717,25 @@ __device__ __forceinline__ int snapshot_word(const int32_t *snap, int index)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// The three words of a saved state's head in one load (the same path as snapshot_word).
+template <int NR>
+__device__ __forceinline__ void state_head_load(const int32_t *snap, int lane, int &b64, int &t, int &hi)
+{
+    int off, v;
+#define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                \
+    asm volatile("v_lshlrev_b32 %[off], 2, %[lane]\n"                           \
+                 "global_load_dword %[v], %[off], %[base]\n"                    \
+                 "s_waitcnt vmcnt(0)\n"                                         \
+                 "v_readlane_b32 %[b64], %[v], 0\n"                             \
+                 "v_readlane_b32 %[t], %[v], 1\n"                               \
+                 "v_readlane_b32 %[hi], %[v], 2\n"                              \
+                 : [off] "=&v"(off), [v] "=&v"(v), [b64] "=&s"(b64), [t] "=&s"(t), [hi] "=&s"(hi) \
+                 : [base] "s"(snap), [lane] "v"(lane)                           \
+                 : "memory", CLOB)
+    KVS_FOR_NR(KVS_STMT);
+#undef KVS_STMT
+}
+
 // RES: the launch runs the candidates named by p.cand_list; the wave of candidate 0 saves its
 // state every 64 positions, candidates with a resume block start from such a snapshot.
 // ONE (with RES): both in the same launch, handed over through p.snap_flags.
@@ -799,11 +834,11 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
     }
     int b64 = 0;             // round of lane 0 of register 0: 64 * floor((t + 1) / 64)
+    int hi = 0;              // 64 x the number of rows that may hold committed memory
     int t = 0;               // start round of the previous request in the order
     long long tel_lane = 0;  // completion rounds summed per lane; added up over the lanes at the end
     if (state_in) {
-        b64 = snapshot_word<NR>(state_in, 0);
-        t = snapshot_word<NR>(state_in, 1);
+        state_head_load<NR>(state_in, lane, b64, t, hi);
         if (t < 0) {  // the shared prefix could not be scheduled
             if (lane == 0 && p.tel_out) p.tel_out[cand] = -1;
             return;
@@ -839,7 +874,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
         if (takes_snapshots && k0 > (CONT ? k_first : 0) && (k0 >> 6) <= p.snap_blocks) {  // the state after k0 positions
             int32_t *snap = p.snapshots + (size_t)((k0 >> 6) - 1) * (size_t)p.snap_stride;
-            state_head_store<NR>(snap, b64, t, tel_lane, lane);
+            state_head_store<NR>(snap, b64, t, hi, tel_lane, lane);
             prof_store<NR>(snap + KVS_STATE_HEAD_WORDS, lane);
             if (ONE) snapshot_publish<NR>(p.snap_flags, k0 >> 6, lane);
             if (LIMIT && p.t_limit && t > snapshot_word<NR>(p.t_limit, 0)) {  // nobody asked for what comes later
@@ -874,14 +909,14 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
         // the up to 64 requests of this block, one after the other (place_block returns the lanes' start
         // rounds); cv: completion round of this lane's position
-        const int pv = place_block<NR>(cnt, M - sv, ov, lane, vmin, M, t, b64);
+        const int pv = place_block<NR>(cnt, M - sv, ov, lane, vmin, M, t, b64, hi);
         const int cv = (k >= k0 ? ov : 0) + pv;
         tel_lane += cv;
         if (crow && k >= k0) crow[p.completion_by_position ? k : rq] = cv;
         if ((RES ? takes_snapshots : p.C == 1) && p.start0 && k >= k0) p.start0[k] = pv;  // (published with the next snapshot)
     }
     if (p.state_out) {
-        state_head_store<NR>(p.state_out, b64, t, tel_lane, lane);
+        state_head_store<NR>(p.state_out, b64, t, hi, tel_lane, lane);
         prof_store<NR>(p.state_out + KVS_STATE_HEAD_WORDS, lane);
     }
     for (int d = 32; d > 0; d >>= 1) tel_lane += __shfl_down(tel_lane, d);
