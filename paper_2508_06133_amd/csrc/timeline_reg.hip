@@ -237,8 +237,10 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* whole passes and single rows alike */                                                    \
         "s_getpc_b64 s[66:67]\n"                                                                        \
         "60:\n"                                                                                         \
-        "s_add_u32 %[ql], s66, 64f-60b-64\n"                                                            \
+        "s_add_u32 %[ql], s66, 64f-60b\n"                                                               \
         "s_addc_u32 %[qh], s67, 0\n"                                                                    \
+        "s_sub_u32 %[ql], %[ql], 256\n"                                                                 \
+        "s_subb_u32 %[qh], %[qh], 0\n"                                                                  \
         "s_add_u32 %[cl], s66, 61f-60b-64\n"                                                            \
         "s_addc_u32 %[ch], s67, 0\n"                                                                    \
         "s_add_u32 %[ul], s66, 62f-60b-64\n"                                                            \
@@ -273,30 +275,111 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_add_u32 %[x64], %[oj], %[u64]\n" /* (t + o - b64) + 64: row and lane of the window's last round */ \
         "s_lshl_b64 %[mk], -2, %[x64]\n"    /* the lanes behind it (the shift uses x64 mod 64) */       \
         "s_andn2_b32 %[off], %[x64], 63\n"  /* 64 (re + 1) */                                           \
-        "s_add_u32 s66, %[ql], %[off]\n"                                                                \
+        "s_lshl_b32 %[ta], %[off], 2\n"                                                                 \
+        "s_add_u32 s66, %[ql], %[ta]\n"                                                                 \
         "s_addc_u32 s67, %[qh], 0\n"                                                                    \
         "s_setpc_b64 s[66:67]\n"                                                                        \
         "64:\n"                                                                                         \
         ".irp r," ASC "\n"                                                                              \
         "7:\n"                                                                                          \
-        "  .if \\r == 0\n"                                                                              \
-        "    v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                    \
-        "    v_cndmask_b32_e64 %[acc], %[y], %[vmin], %[mk]\n"                                          \
-        "    s_branch 26f\n"                                                                            \
+        "  .if \\r <= 12\n" /* the whole request: check, ramp, next */                                  \
+        "    v_add_u32 %[z], %[ns], %[tl]\n"                                                            \
+        "    .if \\r == 0\n"                                                                            \
+        "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
+        "      v_cndmask_b32_e64 %[acc], %[y], %[vmin], %[mk]\n"                                        \
+        "    .else\n"                                                                                   \
+        "      v_cndmask_b32_e64 %[acc], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                           \
+        "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
+        "      .if \\r == 1\n"                                                                          \
+        "        v_max_i32 %[acc], %[acc], %[y]\n"                                                      \
+        "      .else\n"                                                                                 \
+        "        .set kvs_k, \\r\n"                                                                     \
+        "        .if (\\r & 1) == 1\n"                                                                  \
+        "          v_max_i32 %[acc], %[acc], v[" KVS_PB "+\\r-1]\n"                                     \
+        "          .set kvs_k, \\r-1\n"                                                                 \
+        "        .endif\n"                                                                              \
+        "        .rept kvs_k/2-1\n"                                                                     \
+        "          v_max3_i32 %[acc], %[acc], v[" KVS_PB "+kvs_k-1], v[" KVS_PB "+kvs_k-2]\n"           \
+        "          .set kvs_k, kvs_k-2\n"                                                               \
+        "        .endr\n"                                                                               \
+        "        v_max3_i32 %[acc], %[acc], v[" KVS_PB "+1], %[y]\n"                                    \
+        "      .endif\n"                                                                                \
+        "    .endif\n"                                                                                  \
+        "    v_cmp_gt_i32 vcc, %[acc], %[z]\n"                                                          \
+        "    s_cbranch_vccnz 55f\n"                                                                     \
+        "    s_max_u32 %[hi], %[hi], 64*(\\r+1)\n"                                                      \
+        "    .if %c[nr] == 65\n"                                                                        \
+        "      v_subrev_u32 %[z], %[ns], %[vw]\n"                                                       \
+        "      .if \\r == 0\n"                                                                          \
+        "        v_cndmask_b32_e64 %[y], %[z], 0, %[mk]\n"                                              \
+        "        v_add_u32 v[" KVS_PB "], %[y], v[" KVS_PB "]\n"                                        \
+        "      .else\n"                                                                                 \
+        "        v_add_u32 %[y], 64*\\r, %[z]\n"                                                        \
+        "        v_cndmask_b32_e64 %[y], %[y], 0, %[mk]\n"                                              \
+        "        v_add_u32 v[" KVS_PB "+\\r], %[y], v[" KVS_PB "+\\r]\n"                                \
+        "        .if \\r >= 2\n"                                                                        \
+        "          v_add_u32 %[acc], 64, %[z]\n"                                                        \
+        "        .endif\n"                                                                              \
+        "        .if \\r >= 3\n"                                                                        \
+        "          v_add_u32 %[y], 0x80, %[z]\n"                                                        \
+        "        .endif\n"                                                                              \
+        "        .set kvs_k, 0\n"                                                                       \
+        "        .rept \\r\n"                                                                           \
+        "          .if kvs_k == 0\n"                                                                    \
+        "            v_add_u32 v[" KVS_PB "], %[z], v[" KVS_PB "]\n"                                    \
+        "          .elseif kvs_k == 1\n"                                                                \
+        "            v_add_u32 v[" KVS_PB "+1], %[acc], v[" KVS_PB "+1]\n"                              \
+        "          .elseif kvs_k == 2\n"                                                                \
+        "            v_add_u32 v[" KVS_PB "+2], %[y], v[" KVS_PB "+2]\n"                                \
+        "          .elseif (kvs_k - 3*(kvs_k/3)) == 0\n"                                                \
+        "            v_add3_u32 v[" KVS_PB "+kvs_k], v[" KVS_PB "+kvs_k], %[z], s[67+kvs_k/3]\n"        \
+        "          .elseif (kvs_k - 3*(kvs_k/3)) == 1\n"                                                \
+        "            v_add3_u32 v[" KVS_PB "+kvs_k], v[" KVS_PB "+kvs_k], %[acc], s[67+kvs_k/3]\n"      \
+        "          .else\n"                                                                             \
+        "            v_add3_u32 v[" KVS_PB "+kvs_k], v[" KVS_PB "+kvs_k], %[y], s[67+kvs_k/3]\n"        \
+        "          .endif\n"                                                                            \
+        "          .set kvs_k, kvs_k+1\n"                                                               \
+        "        .endr\n"                                                                               \
+        "      .endif\n"                                                                                \
+        "    .else\n"                                                                                   \
+        "      s_sub_u32 %[rs], 64*(\\r+1), %[ns]\n"                                                    \
+        "      v_add_u32 %[y], %[rs], %[vw]\n"                                                          \
+        "      .if \\r >= 1\n"                                                                          \
+        "        .if (\\r & 1) == 1\n"                                                                  \
+        "          v_subrev_u32 %[z], 64, %[y]\n"                                                       \
+        "        .else\n"                                                                               \
+        "          v_add_u32 %[z], 0xffffff80, %[y]\n"                                                  \
+        "        .endif\n"                                                                              \
+        "      .endif\n"                                                                                \
+        "      v_cndmask_b32_e64 %[y], %[y], 0, %[mk]\n"                                                \
+        "      v_add_u32 v[" KVS_PB "+\\r], %[y], v[" KVS_PB "+\\r]\n"                                  \
+        "      .set kvs_k, \\r-1\n"                                                                     \
+        "      .rept \\r\n"                                                                             \
+        "        .if (kvs_k & 1) == 1\n"                                                                \
+        "          v_add3_u32 v[" KVS_PB "+kvs_k], v[" KVS_PB "+kvs_k], %[z], 64\n"                     \
+        "        .else\n"                                                                               \
+        "          v_add_u32 v[" KVS_PB "+kvs_k], %[z], v[" KVS_PB "+kvs_k]\n"                          \
+        "          .if kvs_k >= 2\n"                                                                    \
+        "            v_add_u32 %[z], 0xffffff80, %[z]\n"                                                \
+        "          .endif\n"                                                                            \
+        "        .endif\n"                                                                              \
+        "        .set kvs_k, kvs_k-1\n"                                                                 \
+        "      .endr\n"                                                                                 \
+        "    .endif\n"                                                                                  \
+        "    v_writelane_b32 %[cv], %[t], m0\n"                                                         \
+        "    s_sub_u32 m0, m0, 1\n"                                                                     \
+        "    s_cbranch_scc0 40b\n"                                                                      \
+        "    s_branch 50f\n"                                                                            \
         "  .else\n"                                                                                     \
         "    v_cndmask_b32_e64 %[acc], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                             \
-        "    .if \\r == 1\n"                                                                            \
-        "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
-        "      v_max_i32 %[acc], %[acc], %[y]\n"                                                        \
-        "      s_branch 26f\n"                                                                          \
-        "    .else\n"                                                                                   \
-        "      .if (\\r & 1) == 1\n"                                                                    \
-        "        v_max_i32 %[acc], %[acc], v[" KVS_PB "+\\r-1]\n"                                       \
-        "      .endif\n"                                                                                \
-        "      s_branch 25\\r\\()f\n"                                                                   \
+        "    .if (\\r & 1) == 1\n"                                                                      \
+        "      v_max_i32 %[acc], %[acc], v[" KVS_PB "+\\r-1]\n"                                         \
         "    .endif\n"                                                                                  \
-        "  .endif\n" KVS_SLOT_PAD(64)                                                                   \
+        "    s_branch 25\\r\\()f\n"                                                                     \
+        "  .endif\n"                                                                                    \
+        KVS_SLOT_PAD(256)                                                                               \
         ".endr\n"                                                                                       \
+        ".if %c[nr] > 13\n"                                                                             \
         /* entry 25r: the rows below those of stub r, two per instruction; y stands for row 0 */       \
         ".irp r," DESC "\n"                                                                             \
         "25\\r:\n"                                                                                      \
@@ -311,9 +394,9 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         ".endr\n"                                                                                       \
         "26:\n"                                                                                         \
         "v_subrev_u32 %[acc], %[ns], %[acc]\n"                                                          \
-        "41:\n"                                                                                         \
         "v_cmp_gt_i32 vcc, %[acc], %[tl]\n"                                                             \
         "s_cbranch_vccnz 52f\n"                                                                         \
+        ".endif\n"                                                                                      \
         /* ---- admit at round t */                                                                     \
         "42:\n"                                                                                         \
         "s_max_u32 %[hi], %[hi], %[off]\n"                                                              \
@@ -398,6 +481,8 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_branch 50f\n"                                                                                \
         /* ---- blocked.  The bounds found are exact unless one exceeds 64 in some lane (only then */   \
         /* can a row's limit 64 r, r >= 1, have mattered): then the pass with the limits */             \
+        "55:\n"                                                                                         \
+        "v_subrev_u32 %[acc], %[ns], %[acc]\n"                                                          \
         "52:\n"                                                                                         \
         "v_cmp_lt_i32 vcc, 64, %[acc]\n"                                                                \
         "s_cbranch_vccz 44f\n"                                                                          \
