@@ -67,7 +67,7 @@ namespace {
     "v233", "v234", "v235", "v236", "v237", "v238", "v239", "v240", "v241", "v242", "v243", "v244", "v245", \
     "v246", "v247", "v248", "v249", "v250", "v251", "v252", "v253", "v254"
 
-// Scalar registers of place_block: the pair it jumps through and, for the 65-row file, the row offsets 192 k.
+// Scalar registers of place_block: the pair it jumps through and, from the 65-row file on, the row offsets 192 k.
 #define KVS_SCLOB_PLAIN "s66", "s67"
 #define KVS_SCLOB_65 "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", \
     "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88"
@@ -99,9 +99,9 @@ namespace {
         } else if constexpr (NR == 65) {                                                         \
             STMT(KVS_CLOB_65, KVS_ASC_65, KVS_DESC_65, KVS_SCLOB_65);                                          \
         } else if constexpr (NR == 129) {                                                        \
-            STMT(KVS_CLOB_129, KVS_ASC_129, KVS_DESC_129, KVS_SCLOB_PLAIN);                                       \
+            STMT(KVS_CLOB_129, KVS_ASC_129, KVS_DESC_129, KVS_SCLOB_65);                                       \
         } else {                                                                                 \
-            STMT(KVS_CLOB_225, KVS_ASC_225, KVS_DESC_225, KVS_SCLOB_PLAIN);                                       \
+            STMT(KVS_CLOB_225, KVS_ASC_225, KVS_DESC_225, KVS_SCLOB_65);                                       \
         }                                                                                        \
     } while (0)
 
@@ -186,9 +186,19 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //            not known at compile time and VGPR index mode is avoided); blocked again: repeat;
 //   admit    rows 0..re get the ramp s + (tau - t) (by value zero beyond the window); the start
 //            round t goes to the request's lane of cv.
-// A pass over rows 0..re is entered by one computed jump (table base + 64 (re + 1), s_setpc) to a
-// 64-byte stub that handles the masked last row with constant register numbers and branches into a
-// descending chain of full rows re-1..0, which runs to its end without a compare or a branch.
+// A taken jump costs a lone wavefront some 40 cycles, so a window of at most thirteen rows (most requests
+// of a chat or a document: decodes up to 832) has its whole request in one 256-byte slot, entered by a computed jump
+// (table base + 256 re): check, ramp and the step to the next request.  For more rows the slot is the
+// beginning of a pass as all passes are: one computed jump to a stub that handles the masked last row with
+// constant register numbers and branches into a descending chain of full rows re-1..0, which runs to its end
+// without a compare or a branch.  (Reading the next request's lengths and computing its jump inside the slot,
+// 1 % faster with one wavefront per SIMD, was 12 % slower with eight.)
+//
+// Beyond 65 rows most of the time went into rows that hold nothing and into limits that bind nothing, hence
+//   * the file moves down only as far as memory is committed (hi, kept across blocks and in saved states);
+//   * a blocked request whose rows 4 and above stay below bound 256 takes the limits of rows 0..3 alone;
+//   * the ramp of a row is added in one instruction, as in the 65-row file, from 22 scalar offsets per 66 rows.
+// 8192 moves on 2000 requests with decodes up to 8192: 1511 -> 1270 us; 1025 bimodal orders of 100000: 32.5 -> 29.8 ms.
 //
 // Both the vector unit (one instruction per cycle and compute unit) and the scalar unit (the same,
 // shared by the four SIMDs) are close to saturated by this loop, so it is written to need few of
@@ -250,12 +260,12 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_sub_u32 %[u64], %[t], %[b64]\n"                                                              \
         "v_sub_u32 %[tl], %[u64], %[lane]\n" /* (t - b64) - lane */                                     \
         "s_add_u32 %[u64], %[u64], 64\n"     /* x64 of a request is its decode length plus this */      \
-        /* The 65-row file (long decodes, few wavefronts per SIMD) updates a row in one instruction: the */ \
+        /* Files of 65 rows and more (long decodes, few wavefronts per SIMD) update a row in one instruction: the */ \
         /* ramp of row r is that of row r mod 3 (three vectors) plus 192 floor(r / 3) from a scalar */    \
         /* register (s[67 + k] = 192 k); vw = M - (t - b64) + lane there, the ramp of row 0 is vw - (M - s). */ \
         /* The other files take rows in pairs from the ramp of the window's last row, */                  \
         /* vw + 64 (re + 1) - (M - s) with vw = M - 64 - (t - b64) + lane. */                             \
-        ".if %c[nr] == 65\n"                                                                            \
+        ".if %c[nr] >= 65\n"                                                                            \
         "  .set kvs_r, 1\n"                                                                             \
         "  .rept 21\n"                                                                                  \
         "    s_movk_i32 s[67+kvs_r], 192*kvs_r\n"                                                       \
@@ -308,7 +318,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "    v_cmp_gt_i32 vcc, %[acc], %[z]\n"                                                          \
         "    s_cbranch_vccnz 55f\n"                                                                     \
         "    s_max_u32 %[hi], %[hi], 64*(\\r+1)\n"                                                      \
-        "    .if %c[nr] == 65\n"                                                                        \
+        "    .if %c[nr] >= 65\n"                                                                        \
         "      v_subrev_u32 %[z], %[ns], %[vw]\n"                                                       \
         "      .if \\r == 0\n"                                                                          \
         "        v_cndmask_b32_e64 %[y], %[z], 0, %[mk]\n"                                              \
@@ -371,16 +381,16 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "    s_cbranch_scc0 40b\n"                                                                      \
         "    s_branch 50f\n"                                                                            \
         "  .else\n"                                                                                     \
-        "    v_cndmask_b32_e64 %[acc], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                             \
+        "    v_cndmask_b32_e64 %[z], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                             \
         "    .if (\\r & 1) == 1\n"                                                                      \
-        "      v_max_i32 %[acc], %[acc], v[" KVS_PB "+\\r-1]\n"                                         \
+        "      v_max_i32 %[z], %[z], v[" KVS_PB "+\\r-1]\n"                                         \
         "    .endif\n"                                                                                  \
         "    s_branch 25\\r\\()f\n"                                                                     \
         "  .endif\n"                                                                                    \
         KVS_SLOT_PAD(256)                                                                               \
         ".endr\n"                                                                                       \
         ".if %c[nr] > 13\n"                                                                             \
-        /* entry 25r: the rows below those of stub r, two per instruction; y stands for row 0 */       \
+        /* entry 25r: the rows below those of stub r, two per instruction; z: down to row 4, acc: all; y stands for row 0 */       \
         ".irp r," DESC "\n"                                                                             \
         "25\\r:\n"                                                                                      \
         "  .if (\\r & 1) == 0\n"                                                                        \
@@ -388,7 +398,11 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
         "      v_max3_i32 %[acc], %[acc], v[" KVS_PB "+1], %[y]\n"                                      \
         "    .else\n"                                                                                   \
-        "      v_max3_i32 %[acc], %[acc], v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-2]\n"                   \
+        "      .if \\r == 4\n"                                                                          \
+        "        v_max3_i32 %[acc], %[z], v[" KVS_PB "+3], v[" KVS_PB "+2]\n"                           \
+        "      .else\n"                                                                                 \
+        "        v_max3_i32 %[z], %[z], v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-2]\n"                     \
+        "      .endif\n"                                                                                \
         "    .endif\n"                                                                                  \
         "  .endif\n"                                                                                    \
         ".endr\n"                                                                                       \
@@ -400,7 +414,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* ---- admit at round t */                                                                     \
         "42:\n"                                                                                         \
         "s_max_u32 %[hi], %[hi], %[off]\n"                                                              \
-        ".if %c[nr] != 65\n"                                                                            \
+        ".if %c[nr] < 65\n"                                                                            \
         "  s_sub_u32 %[rs], %[off], %[ns]\n"                                                            \
         ".endif\n"                                                                                      \
         "s_add_u32 s66, %[ul], %[off]\n"                                                                \
@@ -409,7 +423,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "62:\n"                                                                                         \
         ".irp r," ASC "\n"                                                                              \
         "7:\n"                                                                                          \
-        "  .if %c[nr] == 65\n"                                                                          \
+        "  .if %c[nr] >= 65\n"                                                                          \
         /*   z, acc, y (once the masked row is done): the ramps of rows 0, 1, 2 */                      \
         "    v_subrev_u32 %[z], %[ns], %[vw]\n"                                                         \
         "    .if \\r == 0\n"                                                                            \
@@ -420,6 +434,9 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "      v_add_u32 %[y], 64*\\r, %[z]\n"                                                          \
         "      v_cndmask_b32_e64 %[y], %[y], 0, %[mk]\n"                                                \
         "      v_add_u32 v[" KVS_PB "+\\r], %[y], v[" KVS_PB "+\\r]\n"                                  \
+        "      .if (\\r-1)/66 >= 1\n"                                                                   \
+        "        v_add_u32 %[z], 4224*((\\r-1)/66), %[z]\n"                                             \
+        "      .endif\n"                                                                                \
         "      .if \\r >= 2\n"                                                                          \
         "        v_add_u32 %[acc], 64, %[z]\n"                                                          \
         "      .endif\n"                                                                                \
@@ -449,19 +466,25 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         ".endr\n"                                                                                       \
         ".irp r," DESC "\n"                                                                             \
         "30\\r:\n"                                                                                      \
-        "  .if %c[nr] == 65\n"                                                                          \
-        "    .if (\\r-1) == 0\n"                                                                        \
-        "      v_add_u32 v[" KVS_PB "], %[z], v[" KVS_PB "]\n"                                          \
-        "    .elseif (\\r-1) == 1\n"                                                                    \
-        "      v_add_u32 v[" KVS_PB "+1], %[acc], v[" KVS_PB "+1]\n"                                    \
-        "    .elseif (\\r-1) == 2\n"                                                                    \
-        "      v_add_u32 v[" KVS_PB "+2], %[y], v[" KVS_PB "+2]\n"                                      \
-        "    .elseif ((\\r-1) - 3*((\\r-1)/3)) == 0\n"                                                  \
-        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[z], s[67+(\\r-1)/3]\n"            \
-        "    .elseif ((\\r-1) - 3*((\\r-1)/3)) == 1\n"                                                  \
-        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[acc], s[67+(\\r-1)/3]\n"          \
+        "  .if %c[nr] >= 65\n"                                                                          \
+        "    .set kvs_k, \\r-1-66*((\\r-1)/66)\n"                                                       \
+        "    .if kvs_k == 0\n"                                                                          \
+        "      v_add_u32 v[" KVS_PB "+\\r-1], %[z], v[" KVS_PB "+\\r-1]\n"                              \
+        "      .if \\r > 1\n"                                                                           \
+        "        v_add_u32 %[z], 0xffffef80, %[z]\n"                                                    \
+        "        v_add_u32 %[acc], 0xffffef80, %[acc]\n"                                                \
+        "        v_add_u32 %[y], 0xffffef80, %[y]\n"                                                    \
+        "      .endif\n"                                                                                \
+        "    .elseif kvs_k == 1\n"                                                                      \
+        "      v_add_u32 v[" KVS_PB "+\\r-1], %[acc], v[" KVS_PB "+\\r-1]\n"                            \
+        "    .elseif kvs_k == 2\n"                                                                      \
+        "      v_add_u32 v[" KVS_PB "+\\r-1], %[y], v[" KVS_PB "+\\r-1]\n"                              \
+        "    .elseif (kvs_k - 3*(kvs_k/3)) == 0\n"                                                      \
+        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[z], s[67+kvs_k/3]\n"              \
+        "    .elseif (kvs_k - 3*(kvs_k/3)) == 1\n"                                                      \
+        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[acc], s[67+kvs_k/3]\n"            \
         "    .else\n"                                                                                   \
-        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[y], s[67+(\\r-1)/3]\n"            \
+        "      v_add3_u32 v[" KVS_PB "+\\r-1], v[" KVS_PB "+\\r-1], %[y], s[67+kvs_k/3]\n"              \
         "    .endif\n"                                                                                  \
         "  .else\n"                                                                                     \
         "    .if ((\\r-1) & 1) == 1\n"                                                                  \
@@ -483,9 +506,32 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* can a row's limit 64 r, r >= 1, have mattered): then the pass with the limits */             \
         "55:\n"                                                                                         \
         "v_subrev_u32 %[acc], %[ns], %[acc]\n"                                                          \
+        "v_cmp_lt_i32 vcc, 64, %[acc]\n"                                                                \
+        "s_cbranch_vccz 44f\n"                                                                          \
+        ".if %c[nr] > 13\n"                                                                             \
+        "s_branch 56f\n"                                                                                \
+        /* (a window of more than thirteen rows) no row from 4 on beyond 256: none of those reached its limit, */ \
+        /* and the others are four */                                                                   \
         "52:\n"                                                                                         \
         "v_cmp_lt_i32 vcc, 64, %[acc]\n"                                                                \
         "s_cbranch_vccz 44f\n"                                                                          \
+        "v_subrev_u32 %[z], %[ns], %[z]\n"                                                              \
+        "v_cmp_lt_i32 vcc, 0x100, %[z]\n"                                                               \
+        "s_cbranch_vccnz 56f\n"                                                                         \
+        "v_subrev_u32 %[y], %[ns], v[" KVS_PB "+3]\n"                                                   \
+        "v_min_i32 %[y], 0xc0, %[y]\n"                                                                  \
+        "v_max_i32 %[z], %[z], %[y]\n"                                                                  \
+        "v_subrev_u32 %[y], %[ns], v[" KVS_PB "+2]\n"                                                   \
+        "v_min_i32 %[y], 0x80, %[y]\n"                                                                  \
+        "v_subrev_u32 %[acc], %[ns], v[" KVS_PB "+1]\n"                                                 \
+        "v_min_i32 %[acc], 64, %[acc]\n"                                                                \
+        "v_max3_i32 %[z], %[z], %[y], %[acc]\n"                                                         \
+        "v_subrev_u32 %[y], %[ns], v[" KVS_PB "]\n"                                                     \
+        "v_min_i32 %[y], 0, %[y]\n"                                                                     \
+        "v_max_i32 %[acc], %[z], %[y]\n"                                                                \
+        "s_branch 44f\n"                                                                                \
+        "56:\n"                                                                                         \
+        ".endif\n"                                                                                      \
         "s_add_u32 s66, %[cl], %[off]\n"                                                                \
         "s_addc_u32 s67, %[ch], 0\n"                                                                    \
         "s_setpc_b64 s[66:67]\n"                                                                        \
@@ -527,7 +573,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_sub_u32 %[u64], %[tc], %[rs]\n"                                                              \
         "v_sub_u32 %[tl], %[u64], %[lane]\n"                                                            \
         "s_add_u32 %[u64], %[u64], 64\n"                                                                \
-        ".if %c[nr] == 65\n"                                                                            \
+        ".if %c[nr] >= 65\n"                                                                            \
         "  v_sub_u32 %[vw], %[M], %[tl]\n"                                                             \
         ".else\n"                                                                                       \
         "  s_sub_u32 %[tc], %[M], 64\n"                                                                \
