@@ -54,6 +54,7 @@ struct kvsched_ctx {
     void *static_scratch;  // this device's address of the library's fixed working array (never freed)
     void *d_tables;        // exact DP: tables and records, grows on demand
     size_t tables_bytes;
+    int32_t o_file;        // longest decode of the register file the last kvsched_simulate needed (0: unknown, or none)
     int pad_outputs;       // Phase-1 calls write zeros behind the last batch
     int timing;            // record events around the timeline kernel
     int timed;             // a pair of events has been recorded
@@ -161,6 +162,7 @@ int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st);
 constexpr int32_t KVS_REG_MAX_O = 14336;  // 224 rows of 64 rounds, and one more row for the window's offset
 int kvs_launch_simulate_reg(const SimParams &p, hipStream_t st);
 int32_t kvs_reg_state_words(int32_t o_bound);  // words of one snapshot for this decode bound
+int32_t kvs_reg_file_bound(int32_t o_bound);   // the longest decode its register file takes
 
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
                             hipStream_t st);

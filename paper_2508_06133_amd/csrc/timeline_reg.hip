@@ -1084,6 +1084,12 @@ static int reg_rows_for(int32_t o_bound)
 
 int32_t kvs_reg_state_words(int32_t o_bound) { return KVS_STATE_HEAD_WORDS + 64 * reg_rows_for(o_bound); }
 
+// The longest decode of the smallest register file that takes o_bound (0: none does).
+int32_t kvs_reg_file_bound(int32_t o_bound)
+{
+    return o_bound > KVS_REG_MAX_O ? 0 : 64 * (reg_rows_for(o_bound) - 1);
+}
+
 // o_bound <= KVS_REG_MAX_O.  Rows needed: ceil(o_bound / 64) + 1.  Wavefronts per SIMD by file size
 // (512 VGPRs per SIMD lane): 8 up to 33 rows, 5 at 65, 3 at 129, 2 at 225; a file cannot be larger
 // than that, vector instructions address 256 registers.

@@ -38,3 +38,25 @@ def test_rows_at_the_edges(ctx, o_max, crowded):
         assert int(tel[row].item()) == total
         assert (comp[row].cpu().numpy() == np.asarray(want)).all()
     assert ctx.device_status() == 0
+
+
+def test_lengths_that_change_from_call_to_call(ctx):
+    """No bound from the caller: a call may meet longer decodes than the one before, or shorter ones."""
+    import torch
+
+    ctx.set_o_max(0)
+    rng = np.random.default_rng(9)
+    n = 70
+    for o_max in (300, 300, 5000, 200, 14000, 16384, 16384, 40, 2048, 2049, 2048):
+        print(f"o_max={o_max}", flush=True)
+        o = rng.integers(1, o_max + 1, n).astype(np.int32)
+        o[11] = o_max
+        s = rng.integers(1, 400, n).astype(np.int32)
+        M = int((s + o).max()) + 900
+        orders = np.stack([rng.permutation(n) for _ in range(3)]).astype(np.int32)
+        tel, comp = ctx.simulate(torch.from_numpy(orders).cuda(), torch.from_numpy(s).cuda(), torch.from_numpy(o).cuda(), M)
+        for row in range(len(orders)):
+            _, want, total = oracle.simulate(s, o, M, orders[row], literal=False)[:3]
+            assert int(tel[row].item()) == total
+            assert (comp[row].cpu().numpy() == np.asarray(want)).all()
+        assert ctx.device_status() == 0
