@@ -109,8 +109,8 @@ const char *kvsched_strerror(int status);
  * the bound is reported as KVSCHED_DEV_O_MAX and the affected candidates get tel = -1. */
 int kvsched_set_o_max(kvsched_ctx *ctx, int32_t o_max_bound);
 
-/* With `on` != 0 kvsched_sortedF and kvsched_local_swap (and kvsched_phase1_G with those solvers) write zeros behind
- * the last batch of batch_end_out, F_out and swaps_out, so that a caller need not clear them; by default those entries
+/* With `on` != 0 the Phase 1 calls write zeros behind the last batch of batch_end_out and F_out (and Local Swap Search of
+ * swaps_out), so that a caller need not clear them; by default those entries
  * are not touched. */
 int kvsched_set_pad_outputs(kvsched_ctx *ctx, int on);
 

@@ -713,6 +713,12 @@ int kvsched_local_swap(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int3
     return run_local_swap(ctx, n, s, o, M, 0, 1, order_out, batch_end_out, F_out, swaps_out, num_batches_out, stream);
 }
 
+__global__ void kvs_zero_batches(int32_t *batch_end, double *F, int32_t n)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) batch_end[i] = 0, F[i] = 0.0;
+}
+
 static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int32_t *o, int64_t M, int32_t ga,
                         int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t *order_out, int32_t *batch_end_out,
                         double *F_out, int32_t *num_batches_out, void *stream)
@@ -726,8 +732,10 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
     hipStream_t st = (hipStream_t)stream;
     rc = ensure_scratch(ctx, kvs_exact_dp_list_bytes(n));
     if (rc != KVSCHED_OK) return rc;
-    rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
-    if (rc != KVSCHED_OK) return rc;
+    if (ctx->pad_outputs) {
+        hipLaunchKernelGGL(kvs_zero_batches, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, batch_end_out, F_out, n);
+        if (hipGetLastError() != hipSuccess) return KVSCHED_EHIP;
+    }
     // Small problems run in one workgroup with both tables in LDS; a batch holds at most M / 2
     // requests (each costs at least 2 of the budget), which may already show that they fit.
     const int32_t k_host = (int32_t)((M / 2 < n) ? M / 2 : n);

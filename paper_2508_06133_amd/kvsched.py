@@ -257,10 +257,11 @@ class Context:
         """Phase 1 with exact batches (Algorithm 2) -> (order [n], batch_end [n], F [n], num_batches [1])."""
         n = s.shape[0]
         dev = s.device
+        self._pad_outputs(True)
         order = torch.empty(n, dtype=torch.int32, device=dev)
-        ends = torch.zeros(n, dtype=torch.int32, device=dev)
-        F = torch.zeros(n, dtype=torch.float64, device=dev)
-        nb = torch.zeros(1, dtype=torch.int32, device=dev)
+        ends = torch.empty(n, dtype=torch.int32, device=dev)
+        F = torch.empty(n, dtype=torch.float64, device=dev)
+        nb = torch.empty(1, dtype=torch.int32, device=dev)
         rc = _lib.kvsched_exact_dp(self._h, n, _dev(s, torch.int32, "s"), _dev(o, torch.int32, "o"), int(M),
                                    int(feas_mode), int(tie_rule), order.data_ptr(), ends.data_ptr(), F.data_ptr(),
                                    nb.data_ptr(), _stream())
@@ -291,10 +292,9 @@ class Context:
         n = s.shape[0]
         dev = s.device
         self._pad_outputs(True)
-        padded = torch.zeros if solver == SOLVER_EXACT_DP else torch.empty
         order = torch.empty(n, dtype=torch.int32, device=dev)
-        ends = padded(n, dtype=torch.int32, device=dev)
-        G = padded(n, dtype=torch.float64, device=dev)
+        ends = torch.empty(n, dtype=torch.int32, device=dev)
+        G = torch.empty(n, dtype=torch.float64, device=dev)
         swaps = (torch.empty if solver == SOLVER_LOCAL_SWAP else torch.zeros)(n, dtype=torch.int32, device=dev)
         nb = torch.empty(1, dtype=torch.int32, device=dev)
         rc = _lib.kvsched_phase1_G(self._h, int(solver), n, _dev(s, torch.int32, "s"), _dev(o, torch.int32, "o"), int(M),
