@@ -198,7 +198,9 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //   * the file moves down only as far as memory is committed (hi, kept across blocks and in saved states);
 //   * a blocked request whose rows 4 and above stay below bound 256 takes the limits of rows 0..3 alone;
 //   * the ramp of a row is added in one instruction, as in the 65-row file, from 22 scalar offsets per 66 rows.
-// 8192 moves on 2000 requests with decodes up to 8192: 1511 -> 1270 us; 1025 bimodal orders of 100000: 32.5 -> 29.8 ms.
+//   * the 129-row file's slots are 512 bytes, which hold the whole request for up to 29 rows (decodes up to
+//     1856).  The smaller files keep 256: few of their windows are longer than thirteen rows.
+// 8192 moves on 2000 requests with decodes up to 8192: 1511 -> 1246 us (the slots: 1297 -> 1246); 1025 bimodal orders of 100000: 32.5 -> 29.8 ms.
 //
 // Both the vector unit (one instruction per cycle and compute unit) and the scalar unit (the same,
 // shared by the four SIMDs) are close to saturated by this loop, so it is written to need few of
@@ -247,9 +249,16 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* whole passes and single rows alike */                                                    \
         "s_getpc_b64 s[66:67]\n"                                                                        \
         "60:\n"                                                                                         \
+        ".if %c[nr] == 129\n"                                                                           \
+        "  .set kvs_one, 28\n"                                                                          \
+        "  .set kvs_slot, 9\n"                                                                          \
+        ".else\n"                                                                                       \
+        "  .set kvs_one, 12\n"                                                                          \
+        "  .set kvs_slot, 8\n"                                                                          \
+        ".endif\n"                                                                                      \
         "s_add_u32 %[ql], s66, 64f-60b\n"                                                               \
         "s_addc_u32 %[qh], s67, 0\n"                                                                    \
-        "s_sub_u32 %[ql], %[ql], 256\n"                                                                 \
+        "s_sub_u32 %[ql], %[ql], 1<<kvs_slot\n"                                                                 \
         "s_subb_u32 %[qh], %[qh], 0\n"                                                                  \
         "s_add_u32 %[cl], s66, 61f-60b-64\n"                                                            \
         "s_addc_u32 %[ch], s67, 0\n"                                                                    \
@@ -285,21 +294,22 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_add_u32 %[x64], %[oj], %[u64]\n" /* (t + o - b64) + 64: row and lane of the window's last round */ \
         "s_lshl_b64 %[mk], -2, %[x64]\n"    /* the lanes behind it (the shift uses x64 mod 64) */       \
         "s_andn2_b32 %[off], %[x64], 63\n"  /* 64 (re + 1) */                                           \
-        "s_lshl_b32 %[ta], %[off], 2\n"                                                                 \
+        "s_lshl_b32 %[ta], %[off], kvs_slot-6\n"                                                                 \
         "s_add_u32 s66, %[ql], %[ta]\n"                                                                 \
         "s_addc_u32 s67, %[qh], 0\n"                                                                    \
         "s_setpc_b64 s[66:67]\n"                                                                        \
         "64:\n"                                                                                         \
         ".irp r," ASC "\n"                                                                              \
         "7:\n"                                                                                          \
-        "  .if \\r <= 12\n" /* the whole request: check, ramp, next */                                  \
-        "    v_add_u32 %[z], %[ns], %[tl]\n"                                                            \
+        "  .if \\r <= kvs_one\n" /* the whole request: check, ramp, next */                                  \
+        "    .if \\r <= 12\n"                                                                           \
+        "      v_add_u32 %[z], %[ns], %[tl]\n"                                                          \
+        "    .endif\n"                                                                                  \
+        "    v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                    \
         "    .if \\r == 0\n"                                                                            \
-        "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
         "      v_cndmask_b32_e64 %[acc], %[y], %[vmin], %[mk]\n"                                        \
-        "    .else\n"                                                                                   \
+        "    .elseif \\r <= 12\n"                                                                       \
         "      v_cndmask_b32_e64 %[acc], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                           \
-        "      v_min_i32 %[y], %[ns], v[" KVS_PB "]\n"                                                  \
         "      .if \\r == 1\n"                                                                          \
         "        v_max_i32 %[acc], %[acc], %[y]\n"                                                      \
         "      .else\n"                                                                                 \
@@ -314,9 +324,28 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "        .endr\n"                                                                               \
         "        v_max3_i32 %[acc], %[acc], v[" KVS_PB "+1], %[y]\n"                                    \
         "      .endif\n"                                                                                \
+        "    .else\n" /* as in a pass: z down to row 4, acc all */                                      \
+        "      v_cndmask_b32_e64 %[z], v[" KVS_PB "+\\r], %[vmin], %[mk]\n"                             \
+        "      .set kvs_k, \\r\n"                                                                       \
+        "      .if (\\r & 1) == 1\n"                                                                    \
+        "        v_max_i32 %[z], %[z], v[" KVS_PB "+\\r-1]\n"                                           \
+        "        .set kvs_k, \\r-1\n"                                                                   \
+        "      .endif\n"                                                                                \
+        "      .rept kvs_k/2-2\n"                                                                       \
+        "        v_max3_i32 %[z], %[z], v[" KVS_PB "+kvs_k-1], v[" KVS_PB "+kvs_k-2]\n"                 \
+        "        .set kvs_k, kvs_k-2\n"                                                                 \
+        "      .endr\n"                                                                                 \
+        "      v_max3_i32 %[acc], %[z], v[" KVS_PB "+3], v[" KVS_PB "+2]\n"                             \
+        "      v_max3_i32 %[acc], %[acc], v[" KVS_PB "+1], %[y]\n"                                      \
         "    .endif\n"                                                                                  \
-        "    v_cmp_gt_i32 vcc, %[acc], %[z]\n"                                                          \
-        "    s_cbranch_vccnz 55f\n"                                                                     \
+        "    .if \\r <= 12\n"                                                                           \
+        "      v_cmp_gt_i32 vcc, %[acc], %[z]\n"                                                        \
+        "      s_cbranch_vccnz 55f\n"                                                                   \
+        "    .else\n"                                                                                   \
+        "      v_add_u32 %[y], %[ns], %[tl]\n"                                                          \
+        "      v_cmp_gt_i32 vcc, %[acc], %[y]\n"                                                        \
+        "      s_cbranch_vccnz 57f\n"                                                                   \
+        "    .endif\n"                                                                                  \
         "    s_max_u32 %[hi], %[hi], 64*(\\r+1)\n"                                                      \
         "    .if %c[nr] >= 65\n"                                                                        \
         "      v_subrev_u32 %[z], %[ns], %[vw]\n"                                                       \
@@ -387,7 +416,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "    .endif\n"                                                                                  \
         "    s_branch 25\\r\\()f\n"                                                                     \
         "  .endif\n"                                                                                    \
-        KVS_SLOT_PAD(256)                                                                               \
+        KVS_SLOT_PAD((1<<kvs_slot))                                                                               \
         ".endr\n"                                                                                       \
         ".if %c[nr] > 13\n"                                                                             \
         /* entry 25r: the rows below those of stub r, two per instruction; z: down to row 4, acc: all; y stands for row 0 */       \
@@ -512,6 +541,8 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_branch 56f\n"                                                                                \
         /* (a window of more than thirteen rows) no row from 4 on beyond 256: none of those reached its limit, */ \
         /* and the others are four */                                                                   \
+        "57:\n"                                                                                         \
+        "v_subrev_u32 %[acc], %[ns], %[acc]\n"                                                          \
         "52:\n"                                                                                         \
         "v_cmp_lt_i32 vcc, 64, %[acc]\n"                                                                \
         "s_cbranch_vccz 44f\n"                                                                          \
