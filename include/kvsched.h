@@ -280,7 +280,7 @@ int kvsched_local_swap(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int3
  *
  *   order_out, batch_end_out, F_out, num_batches_out   as for kvsched_sortedF
  * ERANGE: n > KVSCHED_EXACT_MAX_N, or tables beyond 16 GiB ((k_max + 1) (M + 1) (8 + n / 8) bytes,
- * k_max = the most requests that can share a batch).
+ * k_max = the most requests that can share a batch; loads counted in 256s).
  */
 int kvsched_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int32_t *o, int64_t M,
                      int32_t feas_mode, int32_t tie_rule, int32_t *order_out, int32_t *batch_end_out,

@@ -760,9 +760,8 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
         return kvs_launch_exact_dp_small(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, lg, ctx->d_scratch, ctx->d_tables,
                                          order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
     }
-    const size_t bytes = kvs_exact_dp_table_bytes(r, kmax, (int32_t)M);
-    if (bytes > kMaxExactTableBytes) return KVSCHED_ERANGE;
-    rc = ensure_tables(ctx, bytes);
+    if (kvs_exact_dp_counted_bytes(r, kmax, (int32_t)M) > kMaxExactTableBytes) return KVSCHED_ERANGE;
+    rc = ensure_tables(ctx, kvs_exact_dp_table_bytes(r, kmax, (int32_t)M));
     if (rc != KVSCHED_OK) return rc;
     int32_t nb = 0;
     while (r > 0) {  // r falls by at least one per batch

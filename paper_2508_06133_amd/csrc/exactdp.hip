@@ -178,11 +178,12 @@ __device__ int prepare_body(int32_t n, const int32_t *s, const int32_t *o, int32
     return prefix_fit(by_cost, n, s, o, feas_mode, M, L);
 }
 
-// Both tables, each with DP_G rows of "no set" in front of row 0.
-__global__ __launch_bounds__(DP_STEP_T) void dp_init_kernel(unsigned *a, size_t count, size_t table, int Mp)
+// The entry for "no set", which the states before row 0 and load 0 are read from (DP_FRONT words of it), and both tables.
+constexpr int DP_FRONT = 64;
+__global__ __launch_bounds__(DP_STEP_T) void dp_init_kernel(unsigned *a, size_t count, size_t table)
 {
     const size_t i = (size_t)blockIdx.x * DP_STEP_T + threadIdx.x;
-    if (i < count) a[i] = i % table == (size_t)DP_G * Mp ? 0u : DP_NONE;  // dp[0][0] = 0
+    if (i < count) a[i] = i >= DP_FRONT && (i - DP_FRONT) % table == 0 ? 0u : DP_NONE;  // dp[0][0] = 0
 }
 
 // What the step launches read, laid out so that one round trip brings it: per request in processing order its load,
@@ -196,9 +197,9 @@ struct DpPlan {
 // Bound by the launch and by L2 reads (16 per state and four requests, where one request a launch took 2 reads and a
 // write each): 200 requests, M = 16384: 497 launches of 4.5 us become 126 of 5.6 us (two dependent reads and a write take 4 of them).
 template <int MODE>
-__global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0, int r, int32_t M, const unsigned *src,
-                                                            unsigned *dst, unsigned long long *bits, size_t per_t, int Mp,
-                                                            int k_first)
+__global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0, int r, int32_t M, const unsigned *none,
+                                                            const unsigned *src, unsigned *dst, unsigned long long *bits,
+                                                            size_t per_t, int Mp, int k_first)
 {
     const int k = k_first + (int)blockIdx.y;
     const int lane = threadIdx.x & 63;
@@ -219,7 +220,12 @@ __global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0,
     off[0] = 0;
 #pragma unroll
     for (int h = 1; h < (1 << DP_G); ++h) off[h] = off[h & (h - 1)] + load[__builtin_ctz(h)];
-    const unsigned *row = src + (size_t)(k + DP_G) * Mp;
+    if (k < DP_G) {  // no set has fewer than no members: such a state reads as one of negative load does
+#pragma unroll
+        for (int h = 1; h < (1 << DP_G); ++h)
+            if (__builtin_popcount(h) > k) off[h] = ~0u;
+    }
+    const unsigned *row = src + (size_t)k * Mp;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int mc = m0 + 64 * c;
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0,
         unsigned f[1 << DP_G];  // f[h]: the state that lacks the requests of h, behind those below h's lowest
 #pragma unroll
         for (int h = 0; h < (1 << DP_G); ++h)
-            f[h] = *(off[h] <= m ? row + ((long long)m - off[h] - (long long)__builtin_popcount(h) * Mp) : src);  // (src[0]: no set)
+            f[h] = *(off[h] <= m ? row + ((long long)m - off[h] - (long long)__builtin_popcount(h) * Mp) : none);
         static_assert(DP_G == 4, "sixteen states");
         // all sixteen reads are in flight before the first is waited for
         asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]),
@@ -244,7 +250,7 @@ __global__ __launch_bounds__(DP_STEP_T) void dp_step_kernel(DpPlan plan, int t0,
                 f[h] = min(f[h], with);
             }
         }
-        dst[(size_t)(k + DP_G) * Mp + m] = f[0];
+        dst[(size_t)k * Mp + m] = f[0];
         if (lane == 0) {
             unsigned long long *b = bits + (size_t)t0 * per_t + (size_t)k * (Mp >> 6) + (mc >> 6);
 #pragma unroll
@@ -341,7 +347,7 @@ __global__ __launch_bounds__(DP_T) void dp_argmin_rows_kernel(const unsigned *dp
     const int lo = plan.range[k].x, hi = plan.range[k].y;
     unsigned long long best = ~0ull;
     for (int m = max(lo, 0) + threadIdx.x; m <= hi; m += DP_T) {
-        const unsigned v = dp[(size_t)(k + DP_G) * Mp + m];
+        const unsigned v = dp[(size_t)k * Mp + m];
         best = min(best, ((unsigned long long)v << 32) | (unsigned)m);
     }
     for (int d = 32; d > 0; d >>= 1) best = min(best, (unsigned long long)__shfl_xor((long long)best, d));
@@ -744,8 +750,17 @@ size_t kvs_exact_dp_list_bytes(int32_t n)
 size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M)
 {
     const size_t Mp = (size_t)dp_row(M);
-    return 2 * (size_t)(kmax + 1 + DP_G) * Mp * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (Mp / 8) +
+    return DP_FRONT * sizeof(int) + 2 * (size_t)(kmax + 1) * Mp * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (Mp / 8) +
            sizeof(long long) * (size_t)(kmax + 1) + 256;
+}
+
+// What the limit on the tables is compared with: two tables and the records with the loads counted in 256s, and 6400
+// bytes.  (Fixed, so that the sizes that are accepted do not move with the kernels' own rows and working memory: the
+// allocation may exceed it by the loads that fill a row of DP_STEP_M.)
+size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M)
+{
+    const size_t loads = ((size_t)M + 256) & ~(size_t)255;
+    return 2 * (size_t)(kmax + 1) * loads * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (loads / 8) + 6400;
 }
 
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
@@ -767,12 +782,13 @@ int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, 
 {
     const DpLists l = dp_lists(lists, n);
     const int Mp = dp_row(M);
-    const size_t table = (size_t)(kmax + 1 + DP_G) * Mp;
-    unsigned *dp[2] = {(unsigned *)tables, (unsigned *)tables + table};
-    unsigned long long *bits = (unsigned long long *)((unsigned *)tables + 2 * table);
+    const size_t table = (size_t)(kmax + 1) * Mp, words = DP_FRONT + 2 * table;
+    unsigned *none = (unsigned *)tables;
+    unsigned *dp[2] = {none + DP_FRONT, none + DP_FRONT + table};
+    unsigned long long *bits = (unsigned long long *)(none + words);
     const size_t per_t = (size_t)(kmax + 1) * (Mp >> 6);
-    hipLaunchKernelGGL(dp_init_kernel, dim3((unsigned)((2 * table + DP_STEP_T - 1) / DP_STEP_T)), dim3(DP_STEP_T), 0, st,
-                       dp[0], 2 * table, table, Mp);
+    hipLaunchKernelGGL(dp_init_kernel, dim3((unsigned)((words + DP_STEP_T - 1) / DP_STEP_T)), dim3(DP_STEP_T), 0, st,
+                       none, words, table);
     const DpPlan plan{l.req, l.range};
     int at = 0;
     for (int32_t t = 0; t < r; t += DP_G, at ^= 1) {
@@ -782,11 +798,11 @@ int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, 
         const int first = kmin - (r - t) + 1 > 1 ? kmin - (r - t) + 1 : 1;
         const dim3 grid((unsigned)(Mp / DP_STEP_M), (unsigned)(top - first + 1));
         if (feas_mode)
-            hipLaunchKernelGGL((dp_step_kernel<1>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, dp[at], dp[at ^ 1], bits, per_t,
-                               Mp, first);
+            hipLaunchKernelGGL((dp_step_kernel<1>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, none, dp[at], dp[at ^ 1],
+                               bits, per_t, Mp, first);
         else
-            hipLaunchKernelGGL((dp_step_kernel<0>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, dp[at], dp[at ^ 1], bits, per_t,
-                               Mp, first);
+            hipLaunchKernelGGL((dp_step_kernel<0>), grid, dim3(DP_STEP_T), 0, st, plan, t, r, M, none, dp[at], dp[at ^ 1],
+                               bits, per_t, Mp, first);
     }
     unsigned long long *partial = bits + (size_t)r * per_t;
     hipLaunchKernelGGL(dp_argmin_rows_kernel, dim3((unsigned)(kmax - kmin + 1)), dim3(DP_T), 0, st, dp[at], kmin, Mp,

@@ -175,6 +175,7 @@ int kvs_launch_neighbor_finish(const int64_t *tel, const int32_t *rejoin, const 
 // exactdp.hip
 size_t kvs_exact_dp_list_bytes(int32_t n);
 size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M);
+size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M);
 // (host, seq: pinned words that receive the requests left and the bounds kmin..kmax on the next batch's size, then seq;
 // ga, gb: the metric's numerator sums ga s_i + gb o_i -- 0, 1: the F-metric; else G with alpha = ga / gb)
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,

@@ -56,3 +56,25 @@ def test_g_metric(ctx, alpha, feas):
     assert ctx.device_status() == 0 and k == len(ends_o)
     assert (ends.cpu().numpy()[:k] == ends_o).all() and (order.cpu().numpy() == order_o).all()
     assert np.allclose(G.cpu().numpy()[:k], G_o, rtol=1e-12, atol=0.0)
+
+
+@pytest.mark.parametrize("n,M", [(4, 1 << 29), (20, 1 << 28)])
+def test_largest_tables(ctx, n, M):
+    """Tables just within the documented 16 GiB.  Batches are known without the oracle: up to k_max = 1 / 3 of any of the
+    requests share a batch, decodes are distinct and within a factor of two, so every batch is the k_max shortest that
+    are left (F = 1/9 of their sum is below any pair's and any single one's)."""
+    rng = np.random.default_rng(n)
+    k_max = 1 if n == 4 else 3
+    o = (4000 + rng.permutation(n) * 7).astype(np.int32)
+    s = (M // (k_max + 1) + 1 + rng.integers(0, 5000, n)).astype(np.int32)
+    assert (k_max + 1) * int((s + o).min()) > M and k_max * int((s + o).max()) <= M
+    assert 2 * (k_max + 1) * (M + 1) * (4 + n / 16) <= 16 << 30
+    print(f"exact_dp largest tables: n={n} M={M} k_max={k_max}", flush=True)
+    order, ends, F, nb = ctx.exact_dp(_dev(s), _dev(o), M)
+    k = int(nb.item())
+    want_ends = np.minimum(np.arange(k_max, n + k_max, k_max), n)
+    assert ctx.device_status() == 0 and k == len(want_ends)
+    assert (order.cpu().numpy() == np.argsort(o)).all() and (ends.cpu().numpy()[:k] == want_ends).all()
+    by_o = np.sort(o).astype(float)
+    want_F = [by_o[a:b].sum() / (b - a) ** 2 for a, b in zip(np.r_[0, want_ends[:-1]], want_ends)]
+    assert np.allclose(F.cpu().numpy()[:k], want_F, rtol=1e-12, atol=0.0)
