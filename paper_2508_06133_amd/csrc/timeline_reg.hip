@@ -186,9 +186,19 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //            not known at compile time and VGPR index mode is avoided); blocked again: repeat;
 //   admit    rows 0..re get the ramp s + (tau - t) (by value zero beyond the window); the start
 //            round t goes to the request's lane of cv.
-// A taken jump costs a lone wavefront some 40 cycles, so a window of at most thirteen rows (most requests
-// of a chat or a document: decodes up to 832) has its whole request in one 256-byte slot, entered by a computed jump
-// (table base + 256 re): check, ramp and the step to the next request.  For more rows the slot is the
+// A taken jump costs a lone wavefront some 40 cycles, so a window of at most kvs_one + 1 rows has its whole request
+// in one slot, entered by a computed jump (table base + slot size * re): check, ramp and the step to the next request.
+// Slot sizes by file:
+//   9 and 33 rows: 256 bytes, up to 13 rows (decodes up to 832: most requests of a chat or a document).  512 bytes (29 rows)
+//     in the 33-row file, 200 to 2000 requests with decodes lognormal around 200: 1 % less with one wavefront per SIMD, the
+//     same with eight; uniform decodes up to 2048: 4 % (256 orders) and 0 to 1 % (4000).  Not worth the longer code.
+//   65 rows and more: the largest power of two with which the branches of this statement (128 KB either way) still
+//     reach across the table, as long decodes are what these files are for: 1024 bytes in the 65-row file (every window
+//     fits), 512 in the 129-row file (37 rows; 640 measure the same), 256 in the 225-row file (its table is 57 KB with
+//     256, and not even 320 assemble).
+//     Against 256: 1025 bimodal orders of 100000 (65 rows) 29.1 -> 28.3 ms, 256 orders of 2000, decodes up to 4096,
+//     0.454 -> 0.438 ms; 129 rows, decodes up to 8192: 8191 moves 1.22 -> 1.19 ms, 256 orders 0.506 -> 0.484 ms.
+// For more rows the slot is the
 // beginning of a pass as all passes are: one computed jump to a stub that handles the masked last row with
 // constant register numbers and branches into a descending chain of full rows re-1..0, which runs to its end
 // without a compare or a branch.  (Reading the next request's lengths and computing its jump inside the slot,
@@ -198,9 +208,8 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //   * the file moves down only as far as memory is committed (hi, kept across blocks and in saved states);
 //   * a blocked request whose rows 4 and above stay below bound 256 takes the limits of rows 0..3 alone;
 //   * the ramp of a row is added in one instruction, as in the 65-row file, from 22 scalar offsets per 66 rows.
-//   * the 129-row file's slots are 512 bytes, which hold the whole request for up to 29 rows (decodes up to
-//     1856).  The smaller files keep 256: few of their windows are longer than thirteen rows.
-// 8192 moves on 2000 requests with decodes up to 8192: 1511 -> 1246 us (the slots: 1297 -> 1246); 1025 bimodal orders of 100000: 32.5 -> 29.8 ms.
+// With the slots above, 8191 moves on 2000 requests with decodes up to 8192: 1511 -> 1240 us; 1025 bimodal orders of
+// 100000: 32.5 -> 29.0 ms.
 //
 // Both the vector unit (one instruction per cycle and compute unit) and the scalar unit (the same,
 // shared by the four SIMDs) are close to saturated by this loop, so it is written to need few of
@@ -235,7 +244,8 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 
 // Pads the slot that began at the last label 7 to the given number of bytes (never executed: slots
 // end in a branch).
-#define KVS_SLOT_PAD(bytes) "  .fill (" #bytes "-(.-7b))/4, 4, 0xbf800000\n"
+// (The .org stops the build if the slot does not hold what was put into it.)
+#define KVS_SLOT_PAD(bytes) "  .fill (" #bytes "-(.-7b))/4, 4, 0xbf800000\n  .org 7b+" #bytes "\n"
 
 template <int NR>
 __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, int vmin, int M, int &t, int &b64, int &hi)
@@ -249,8 +259,11 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* whole passes and single rows alike */                                                    \
         "s_getpc_b64 s[66:67]\n"                                                                        \
         "60:\n"                                                                                         \
-        ".if %c[nr] == 129\n"                                                                           \
-        "  .set kvs_one, 28\n"                                                                          \
+        ".if %c[nr] == 65\n"                                                                            \
+        "  .set kvs_one, 64\n"                                                                          \
+        "  .set kvs_slot, 10\n"                                                                         \
+        ".elseif %c[nr] == 129\n"                                                                       \
+        "  .set kvs_one, 36\n"                                                                          \
         "  .set kvs_slot, 9\n"                                                                          \
         ".else\n"                                                                                       \
         "  .set kvs_one, 12\n"                                                                          \
