@@ -104,7 +104,10 @@ const char *kvsched_strerror(int status);
 
 /* The kernels size their future-memory ring from the largest decode length.  By default
  * every call first scans o[] on the device and waits for that one number (the only host
- * synchronisation a call makes).  A caller that knows an upper bound on o_i can set it here
+ * synchronisation a call makes).  A kvsched_simulate call of up to 2^20 positions in all (rows times n) waits
+ * behind its launches instead: they use the ring size of the context's last such call and do nothing if the
+ * scan finds longer decodes, in which case they are enqueued again with the right one (some 4 us; results, and
+ * outputs left alone on ERANGE, are the same).  A caller that knows an upper bound on o_i can set it here
  * (1..KVSCHED_MAX_O) to make calls fully asynchronous; 0 restores the scan.  A length above
  * the bound is reported as KVSCHED_DEV_O_MAX and the affected candidates get tel = -1. */
 int kvsched_set_o_max(kvsched_ctx *ctx, int32_t o_max_bound);

@@ -472,11 +472,13 @@ int kvsched_device_status(kvsched_ctx *ctx, void *stream, int32_t *status_out)
     return KVSCHED_OK;
 }
 
-// kvsched_simulate for decodes of at most o_bound.
+// kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
+// longer one (only where rows are not resumed and no prefix is placed ahead).
 static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, const int32_t *s,
-                           const int32_t *o, int64_t M, int32_t o_bound, int64_t *tel_out, int32_t *completion_out,
-                           int32_t common_prefix, hipStream_t st)
+                           const int32_t *o, int64_t M, int32_t o_bound, bool gated, int64_t *tel_out,
+                           int32_t *completion_out, int32_t common_prefix, hipStream_t st)
 {
+    const int32_t o_limit = gated ? o_bound : INT32_MAX;
     int rc;
     const int32_t H = ring_slots_for(o_bound);
     if ((int64_t)n * (int64_t)H >= kMaxM) return KVSCHED_ERANGE;  // rounds are int32
@@ -497,6 +499,7 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     p.completion_by_position = (completion_out && n <= KVS_PERMUTE_MAX_N) ? 1 : 0;
     p.d_words = ctx->d_words;
     p.o_bound = o_bound;
+    p.gate = gated ? ctx->d_words + KVS_W_OMAX : nullptr;
     // Declared common prefix: run it once (row 0), resume every row from its state.
     int32_t cp = 0;
     int32_t *prefix_comp = nullptr;
@@ -622,18 +625,24 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     }
     if (p.completion_by_position) {  // this pass over the rows checks them as well
         rc = kvs_launch_permute_rows(orders, C, n, completion_out, tel_out, ctx->d_words, resumed_blocks, resumed_row0,
-                                     resumed_row0 ? rejoined : nullptr, st);
+                                     resumed_row0 ? rejoined : nullptr, st, o_limit);
     } else {
-        rc = kvs_launch_check_orders(orders, C, n, tel_out, ctx->d_words, st);
+        rc = kvs_launch_check_orders(orders, C, n, tel_out, ctx->d_words, st, o_limit);
     }
     if (rc != KVSCHED_OK || cp == 0) return rc;
     return kvs_launch_check_prefix(orders, C, n, cp, tel_out, ctx->d_words, st);
 }
 
 // Without a bound from the caller the largest decode length has to be found before the kernel can be chosen.  A small
-// call does not let the GPU wait for the host meanwhile: it runs with the bound of the register file the last call
-// needed, and again only if the scan then reports a longer decode.  (Up to a million positions, 80 us of timelines, against
-// some 6 us of waiting in each call: 61 requests 36 -> 31 us, 4096 orders of 200: 86 -> 81 us.)
+// call does not let the GPU wait for the host meanwhile: its launches follow the scan at once, with the register file that
+// the last call needed, and do nothing if the scan has found a longer decode; the host, which reads the scan's result
+// while they run, then launches with the right file.  So a caller whose backlogs alternate pays for launches that end
+// at once, not for timelines.  Nor does it get a file that lets fewer of its timelines run side by side than its own:
+// the file has to be one of those with eight wavefronts per SIMD, or every timeline of the call in flight.
+// (Up to a million positions, some 100 us of timelines, against 10 us of waiting in each call.  One order of 61 requests:
+// 29 us with the wait, 18.5 without, 22 when two backlogs alternate; 4096 orders of 200, decodes up to 400 and up to 14000 in
+// turn: 114 with the wait, 102 now, 114 when the launches of a wrong guess ran to their end; up to 2000 and up to 14000: 118,
+// 105, 132.  4096 orders exceed what the 225-row file holds at once, so those of 14000 alone wait: 130.)
 constexpr int64_t kGuessMaxPositions = 1 << 20;
 
 int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, const int32_t *s,
@@ -647,11 +656,12 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
     int32_t guess = 0;
     if (ctx->o_max_bound == 0 && ctx->o_file > 0 && (int64_t)C * n <= kGuessMaxPositions &&
         common_prefix < kMinSharedPrefix && !resume_pays(ctx, C, n, ctx->o_file) &&
+        (C <= kvs_reg_wavefronts(ctx->o_file) || kvs_reg_wavefronts(ctx->o_file) == kvs_reg_wavefronts(1)) &&
         (int64_t)n * ring_slots_for(ctx->o_file) < kMaxM && !capturing(st))
         guess = ctx->o_file;
     if (guess > 0) {
         rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, next_seq(ctx));
-        if (rc == KVSCHED_OK) rc = simulate_within(ctx, orders, C, n, s, o, M, guess, tel_out, completion_out, common_prefix, st);
+        if (rc == KVSCHED_OK) rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, tel_out, completion_out, 0, st);
         if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);
         if (rc != KVSCHED_OK) return rc;
     }
@@ -660,7 +670,7 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
     if (rc != KVSCHED_OK) return rc;
     ctx->o_file = kvs_reg_file_bound(o_bound);
     if (guess >= o_bound) return KVSCHED_OK;
-    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, tel_out, completion_out, common_prefix, st);
+    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, false, tel_out, completion_out, common_prefix, st);
 }
 
 // The three Phase-1 solvers; (ga, gb) = (0, 1) is the F-metric.

@@ -54,7 +54,8 @@ struct kvsched_ctx {
     void *static_scratch;  // this device's address of the library's fixed working array (never freed)
     void *d_tables;        // exact DP: tables and records, grows on demand
     size_t tables_bytes;
-    int32_t o_file;        // longest decode of the register file the last kvsched_simulate needed (0: unknown, or none)
+    int32_t o_file;        // longest decode of the register file the last kvsched_simulate needed (0: unknown, or none): what a
+                           // small call starts with before its own is known
     int pad_outputs;       // Phase-1 calls write zeros behind the last batch
     int timing;            // record events around the timeline kernel
     int timed;             // a pair of events has been recorded
@@ -95,6 +96,8 @@ struct SimParams {
     int32_t completion_by_position;  // 1: row entry k = completion of position k (a later pass permutes)
     int32_t *d_words;
     int32_t o_bound;          // lengths above this are reported, not simulated
+    // Register kernel, explicit rows that are not resumed: the launch leaves everything as it is when *gate > o_bound
+    const int32_t *gate = nullptr;
     // Register kernel only: simulate positions [k_begin, k_end) (k_end == 0: up to n), starting
     // from / leaving behind a saved timeline state of KVS_STATE_HEAD_WORDS + 64 NR int32 words:
     // {b64, t, 62 unused, the 64 lanes' partial sums of completion rounds as int64, then the
@@ -163,9 +166,11 @@ constexpr int32_t KVS_REG_MAX_O = 14336;  // 224 rows of 64 rounds, and one more
 int kvs_launch_simulate_reg(const SimParams &p, hipStream_t st);
 int32_t kvs_reg_state_words(int32_t o_bound);  // words of one snapshot for this decode bound
 int32_t kvs_reg_file_bound(int32_t o_bound);   // the longest decode its register file takes
+int32_t kvs_reg_wavefronts(int32_t o_bound);   // timelines of this decode bound that the chip holds at once
 
+// (o_limit: the launch does nothing when the length scan before it found a longer decode)
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
-                            hipStream_t st);
+                            hipStream_t st, int32_t o_limit = INT32_MAX);
 int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t *d_words, hipStream_t st);
 // The end of a local-search step: latencies of timelines that stopped early completed from the base order's (rejoin or
 // NULL), malformed moves marked, latencies copied to tel_out (or NULL), best move, its latency and the base order's.
@@ -217,7 +222,7 @@ constexpr int32_t KVS_PERMUTE_MAX_N = 15872;  // one row and its bitmap must fit
 // completion rounds before them are row0[k], row 0's in position order
 int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t *completion, int64_t *tel_out,
                             int32_t *d_words, const int32_t *resume_block, const int32_t *row0,
-                            const int32_t *rejoin_block, hipStream_t st);
+                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit = INT32_MAX);
 
 // horizon.hip.  What the context keeps between horizon steps (one device buffer).
 enum {

@@ -22,8 +22,9 @@ namespace {
 __global__ __launch_bounds__(256) void permute_rows_kernel(const int32_t *orders, int32_t n, int32_t *completion,
                                                            int64_t *tel_out, int32_t *words,
                                                            const int32_t *resume_block, const int32_t *row0,
-                                                           const int32_t *rejoin_block)
+                                                           const int32_t *rejoin_block, int32_t o_limit)
 {
+    const int o_max = words[KVS_W_OMAX];
     extern __shared__ int row_by_id[];
     unsigned int *seen = (unsigned int *)(row_by_id + n);  // one bit per request id
     const int32_t *order = orders + (size_t)blockIdx.x * (size_t)n;
@@ -42,7 +43,9 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const int32_t *orders
         if (k < tail) row_by_id[r] = k < shared ? row0[k] : comp[k];
     }
     for (int k = tail + threadIdx.x; k < n; k += blockDim.x) row_by_id[min(max(orders[k], 0), n - 1)] = row0[k];
-    if (__syncthreads_or(bad) && threadIdx.x == 0) {  // the row is no permutation: its results are void
+    bad = __syncthreads_or(bad);
+    if (o_max > o_limit) return;  // the rows have not been placed (looked at this late: the other reads hide it)
+    if (bad && threadIdx.x == 0) {  // the row is no permutation: its results are void
         tel_out[blockIdx.x] = -1;
         atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
     }
@@ -54,8 +57,10 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const int32_t *orders
 // launch: 40321 such rows 31.5 us, so 4.2.)
 constexpr int kShortRow = 256, kShortEntries = 1024;
 __global__ __launch_bounds__(256) void permute_short_rows_kernel(const int32_t *orders, int32_t C, int32_t n, int32_t rows,
-                                                                 int32_t *completion, int64_t *tel_out, int32_t *words)
+                                                                 int32_t *completion, int64_t *tel_out, int32_t *words,
+                                                                 int32_t o_limit)
 {
+    const int o_max = words[KVS_W_OMAX];
     __shared__ int by_id[kShortEntries];
     __shared__ unsigned int seen[kShortEntries + kShortEntries / 32];
     __shared__ int bad[kShortEntries];
@@ -75,6 +80,7 @@ __global__ __launch_bounds__(256) void permute_short_rows_kernel(const int32_t *
         by_id[row * n + r] = comp[e];
     }
     __syncthreads();
+    if (o_max > o_limit) return;  // the rows have not been placed (looked at this late: the other reads hide it)
     for (int i = threadIdx.x; i < mine; i += 256) {
         if (bad[i]) {
             tel_out[row0 + i] = -1;
@@ -88,17 +94,17 @@ __global__ __launch_bounds__(256) void permute_short_rows_kernel(const int32_t *
 
 int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t *completion, int64_t *tel_out,
                             int32_t *d_words, const int32_t *resume_block, const int32_t *row0,
-                            const int32_t *rejoin_block, hipStream_t st)
+                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit)
 {
     if (n > KVS_PERMUTE_MAX_N) return KVSCHED_ERANGE;
     if (n <= kShortRow && !resume_block) {
         const int rows = kShortEntries / n;
         hipLaunchKernelGGL(permute_short_rows_kernel, dim3((unsigned)((C + rows - 1) / rows)), dim3(256), 0, st, orders, C, n,
-                           rows, completion, tel_out, d_words);
+                           rows, completion, tel_out, d_words, o_limit);
         return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
     }
     const size_t lds = sizeof(int32_t) * ((size_t)n + (((size_t)n + 31) >> 5));
     hipLaunchKernelGGL(permute_rows_kernel, dim3((unsigned)C), dim3(256), lds, st, orders, n, completion, tel_out,
-                       d_words, resume_block, row0, rejoin_block);
+                       d_words, resume_block, row0, rejoin_block, o_limit);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

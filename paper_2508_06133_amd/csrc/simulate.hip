@@ -182,9 +182,10 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
 // One wavefront per row: is it a permutation of 0..n-1?  Bitmap of n bits per wave in LDS.
 template <int WPB>
 __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *orders, int32_t C, int32_t n,
-                                                                 int64_t *tel_out, int32_t *words)
+                                                                 int64_t *tel_out, int32_t *words, int32_t o_limit)
 {
     extern __shared__ unsigned int bitmap_all[];
+    const int o_max = words[KVS_W_OMAX];
     const int lane = threadIdx.x & (WAVE - 1);
     const int cand = blockIdx.x * WPB + (threadIdx.x >> 6);
     if (cand >= C) return;
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *
             if (atomicOr(&bm[r >> 5], bit) & bit) bad = true;
         }
     }
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) {
+    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0 && o_max <= o_limit) {  // (else the rows have not been placed)
         tel_out[cand] = -1;
         atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
     }
@@ -212,9 +213,10 @@ __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *
 // The same for long rows: one workgroup of 1024 threads per row (a single wavefront would walk a row of
 // 100000 entries in 1563 dependent turns).
 __global__ __launch_bounds__(1024) void check_orders_wide_kernel(const int32_t *orders, int32_t C, int32_t n,
-                                                                 int64_t *tel_out, int32_t *words)
+                                                                 int64_t *tel_out, int32_t *words, int32_t o_limit)
 {
     extern __shared__ unsigned int bitmap_all[];
+    const int o_max = words[KVS_W_OMAX];
     const int cand = blockIdx.x;
     const int nw = (n + 31) >> 5;
     for (int i = threadIdx.x; i < nw; i += 1024) bitmap_all[i] = 0;
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(1024) void check_orders_wide_kernel(const int32_t *
             if (atomicOr(&bitmap_all[r >> 5], bit) & bit) bad = 1;
         }
     }
-    if (__syncthreads_or(bad) && threadIdx.x == 0) {
+    if (__syncthreads_or(bad) && threadIdx.x == 0 && o_max <= o_limit) {  // (else the rows have not been placed)
         tel_out[cand] = -1;
         atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
     }
@@ -362,20 +364,20 @@ int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st)
 }
 
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
-                            hipStream_t st)
+                            hipStream_t st, int32_t o_limit)
 {
     const size_t per_wave = (size_t)((n + 31) >> 5) * sizeof(unsigned int);
     if (per_wave > 65536) return KVSCHED_ERANGE;
     // long rows, not enough of them to fill the chip with a wavefront each (one row of 10000: 31 us by a wavefront)
     if ((n >= 16384 && C <= 8192) || (n >= 1024 && C <= 512)) {
         hipLaunchKernelGGL(check_orders_wide_kernel, dim3((unsigned)C), dim3(1024), per_wave, st, orders, C, n, tel_out,
-                           d_words);
+                           d_words, o_limit);
     } else if (per_wave * 4 <= 65536) {
         hipLaunchKernelGGL((check_orders_kernel<4>), dim3((unsigned)((C + 3) / 4)), dim3(256), per_wave * 4, st,
-                           orders, C, n, tel_out, d_words);
+                           orders, C, n, tel_out, d_words, o_limit);
     } else {
         hipLaunchKernelGGL((check_orders_kernel<1>), dim3((unsigned)C), dim3(64), per_wave, st, orders, C, n,
-                           tel_out, d_words);
+                           tel_out, d_words, o_limit);
     }
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

@@ -1037,6 +1037,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
             ov_n = p.o[rq_n];
         }
     }
+    if (!RES && !MOVES && p.gate && scalar_read(p.gate, 0) > p.o_bound) return;  // (while the lengths are on their way)
     if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = n;  // (unless it stops before)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
     for (int k0 = k_first; k0 < n_stop; k0 += WAVE) {
@@ -1132,6 +1133,13 @@ int32_t kvs_reg_state_words(int32_t o_bound) { return KVS_STATE_HEAD_WORDS + 64 
 int32_t kvs_reg_file_bound(int32_t o_bound)
 {
     return o_bound > KVS_REG_MAX_O ? 0 : 64 * (reg_rows_for(o_bound) - 1);
+}
+
+// 256 compute units of four SIMDs, each with 8 / 8 / 5 / 3 / 2 wavefronts of these files.
+int32_t kvs_reg_wavefronts(int32_t o_bound)
+{
+    const int rows = reg_rows_for(o_bound);
+    return 1024 * (rows <= 33 ? 8 : rows <= 65 ? 5 : rows <= 129 ? 3 : 2);
 }
 
 // o_bound <= KVS_REG_MAX_O.  Rows needed: ceil(o_bound / 64) + 1.  Wavefronts per SIMD by file size

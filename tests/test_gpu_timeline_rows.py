@@ -86,3 +86,60 @@ def test_rows_where_a_request_no_longer_is_one_piece(ctx, o_max, crowded):
         assert int(tel[row].item()) == total
         assert (comp[row].cpu().numpy() == np.asarray(want)).all()
     assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("n", [70, 300])
+@pytest.mark.parametrize("completions", [True, False])
+def test_a_call_that_starts_with_the_last_calls_register_file(ctx, n, completions):
+    """No bound from the caller, after a call with short decodes: too long a decode leaves the outputs as they are, a longer
+    one than that file takes gives the right results, a faulty row among them is found."""
+    import torch
+
+    from paper_2508_06133_amd import kvsched
+
+    print(f"n={n} completions={completions}", flush=True)
+    rng = np.random.default_rng(n)
+    ctx.set_o_max(0)
+    s = rng.integers(1, 300, n).astype(np.int32)
+    orders = np.stack([rng.permutation(n) for _ in range(5)]).astype(np.int32)
+
+    def call(orders, o, M):
+        tel = torch.full((5,), -7, dtype=torch.int64, device="cuda:0")
+        comp = torch.full((5, n), -7, dtype=torch.int32, device="cuda:0")
+        try:
+            ctx.simulate(torch.from_numpy(orders).cuda(), torch.from_numpy(s).cuda(), torch.from_numpy(o).cuda(), M,
+                         completions, tel_out=tel, completion_out=comp)
+            code = 0
+        except kvsched.KvschedError as e:
+            code = e.code
+        torch.cuda.synchronize()
+        return code, tel.cpu().numpy(), comp.cpu().numpy()
+
+    for o_max in (100, 5000, 14000, 100):
+        o = rng.integers(1, o_max + 1, n).astype(np.int32)
+        o[3] = o_max
+        short = np.minimum(o, 200)
+        assert call(orders, short, 4000)[0] == 0
+        long = o.copy()
+        long[5] = 20000
+        code, tel, comp = call(orders, long, 40000)
+        assert code == -2 and (tel == -7).all() and (comp == -7).all()
+        assert call(orders, short, 4000)[0] == 0
+        faulty = orders.copy()
+        faulty[2, 1] = faulty[2, 0]
+        code, tel, comp = call(faulty, o, 16000)
+        assert code == 0 and ctx.device_status() == kvsched.DEV_BAD_ORDER and tel[2] == -1
+        for row in (0, 1, 3, 4):
+            _, want, total = oracle.simulate(s, o, 16000, orders[row], literal=False)[:3]
+            assert tel[row] == total
+            assert not completions or (comp[row] == np.asarray(want)).all()
+    # as many positions as a round counter cannot count: refused before anything is written
+    m = 65600
+    assert call(orders, short, 4000)[0] == 0
+    o = np.full(m, 16384, np.int32)
+    tel = torch.full((1,), -7, dtype=torch.int64, device="cuda:0")
+    with pytest.raises(kvsched.KvschedError) as e:
+        ctx.simulate(torch.arange(m, dtype=torch.int32, device="cuda:0")[None], torch.ones(m, dtype=torch.int32, device="cuda:0"),
+                     torch.from_numpy(o).cuda(), 1 << 20, False, tel_out=tel)
+    torch.cuda.synchronize()
+    assert e.value.code == -2 and int(tel.item()) == -7
