@@ -235,22 +235,31 @@ HorizonKept horizon_kept(kvsched_ctx *ctx, int32_t n)
     return h;
 }
 
-// Room for n positions with saved states of `stride` words; growing it forgets what was kept.
-int ensure_horizon(kvsched_ctx *ctx, int32_t n, int32_t stride)
+// Room for n positions with saved states of `stride` words; growing it forgets what was kept, unless `carry`: what is
+// there moves along (its places depend on its own number of positions alone).
+int ensure_horizon(kvsched_ctx *ctx, int32_t n, int32_t stride, bool carry = false)
 {
     const size_t bytes = align256(sizeof(int32_t) * (KVS_HZ_WORDS + KVS_PROGRESS_WORDS)) +
                          5 * align256(sizeof(int32_t) * (size_t)n) +
                          sizeof(int32_t) * (size_t)((n - 1) / WAVE_POSITIONS) * (size_t)stride + 256;
     if (bytes <= ctx->horizon_bytes) return KVSCHED_OK;
-    ctx->hz_kept = ctx->hz_completion = 0;
-    if (ctx->d_horizon) {
-        if (hipDeviceSynchronize() != hipSuccess) return KVSCHED_EHIP;
+    if (ctx->d_horizon && hipDeviceSynchronize() != hipSuccess) return KVSCHED_EHIP;
+    if (!carry) {
+        ctx->hz_kept = ctx->hz_completion = 0;
         (void)hipFree(ctx->d_horizon);
         ctx->d_horizon = nullptr;
         ctx->horizon_bytes = 0;
     }
-    if (hipMalloc(&ctx->d_horizon, bytes) != hipSuccess) return KVSCHED_ENOMEM;
-    if (hipMemset(ctx->d_horizon, 0, sizeof(int32_t) * KVS_HZ_WORDS) != hipSuccess) return KVSCHED_EHIP;
+    void *buf = nullptr;
+    if (hipMalloc(&buf, bytes) != hipSuccess) return KVSCHED_ENOMEM;
+    if ((ctx->d_horizon ? hipMemcpy(buf, ctx->d_horizon, ctx->horizon_bytes, hipMemcpyDeviceToDevice)
+                        : hipMemset(buf, 0, sizeof(int32_t) * KVS_HZ_WORDS)) != hipSuccess ||
+        hipDeviceSynchronize() != hipSuccess) {  // (the copies may run behind the call; the steps' streams do not wait for them)
+        (void)hipFree(buf);
+        return KVSCHED_EHIP;
+    }
+    (void)hipFree(ctx->d_horizon);
+    ctx->d_horizon = buf;
     ctx->horizon_bytes = bytes;
     return KVSCHED_OK;
 }
@@ -384,7 +393,8 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
 {
     if (!ctx || rows < 0 || n < 1 || moves < 0) return KVSCHED_EINVAL;
     if (hipSetDevice(ctx->device) != hipSuccess) return KVSCHED_EHIP;
-    // the largest of what the calls named in the header ask of the scratch buffer at these sizes
+    // the largest of what the calls named in the header ask of the scratch buffer at these sizes, whatever the decode
+    // lengths (saved states of the largest kind: a bound set now may be lifted later)
     const size_t nblk = (size_t)((n - 1) / WAVE_POSITIONS);
     const size_t row_bytes = align256(sizeof(int32_t) * (size_t)n);
     size_t need = kvs_sortedF_scratch_bytes(n);
@@ -399,8 +409,10 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
         if (pre > need) need = pre;
     }
     if (moves > 0) {
-        const size_t hor = neighbor_scratch_bytes(moves, n, ctx->o_max_bound) + row_bytes + 256;
+        const size_t hor = neighbor_scratch_bytes(moves, n, 0) + row_bytes + 256;
         if (hor > need) need = hor;
+        const int rc = ensure_horizon(ctx, n, KVS_STATE_MAX_WORDS, true);  // what the horizon step keeps between steps
+        if (rc != KVSCHED_OK) return rc;
     }
     const int32_t keep = ctx->resume_rows;  // reserving is no call: the last resume plan stays readable unless the buffer moves
     const size_t keep_rejoin = ctx->rejoin_offset;

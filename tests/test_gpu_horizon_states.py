@@ -79,3 +79,64 @@ def test_a_malformed_order_leaves_nothing_behind(ctx):
         order_o, _, _, res_o = ohorizon.horizon_step(inst.s, inst.o, inst.M, base, moves, 0, 40)
         _, res = ctx.horizon_step(order, _dev(moves), s, o, inst.M, 0, 40)
         assert tuple(res.cpu().tolist()) == res_o and (order.cpu().numpy() == order_o).all() and ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("bound", [0, 512])
+def test_steps_within_a_reservation_do_not_allocate(bound):
+    """Short decodes first, then the longest: the states kept between steps grow, the memory the context holds does not."""
+    import torch
+    from paper_2508_06133_amd import kvsched
+
+    n, K = 12000, 40
+    rng = np.random.default_rng(3)
+    s = rng.integers(1, 300, n).astype(np.int32)
+    order = _dev(rng.permutation(n))
+    mv = _dev(workloads.window_moves(rng, K, 0, 200))
+
+    def steps(c, free):
+        for o_max in (200, 2000, 14000, 300):
+            o = rng.integers(1, 201, n).astype(np.int32)
+            o[rng.integers(0, n, 20)] = o_max
+            print(f"reserved horizon: bound={bound} o_max={o_max} check={free is not None}", flush=True)
+            c.set_o_max(0 if o_max > bound else bound)
+            for _ in range(2):
+                _, res = c.horizon_step(order, mv, _dev(s), _dev(o), 400000, 0, 50)
+            assert int(res[0].item()) >= 0 and c.device_status() == 0
+            assert free is None or torch.cuda.mem_get_info()[0] == free, o_max
+
+    for checked in (False, True):  # (once before: what the runtime and torch allocate on a first use)
+        c = kvsched.Context(0)
+        try:
+            c.set_o_max(bound)
+            c.reserve(1, n, K)
+            torch.cuda.synchronize()
+            steps(c, torch.cuda.mem_get_info()[0] if checked else None)
+        finally:
+            c.close()
+
+
+def test_reserving_between_a_step_and_its_completion_rounds(ctx):
+    import torch
+
+    inst = workloads.instance(4, n=700, M=20000)
+    base, _, _ = oracle.sortedF(inst.s, inst.o, inst.M)
+    s, o = _dev(inst.s), _dev(inst.o)
+    from paper_2508_06133_amd import kvsched
+
+    c = kvsched.Context(0)
+    try:
+        order_h, completed = base, 0
+        order = _dev(base)
+        for step in range(3):
+            moves = workloads.window_moves(np.random.default_rng(step), 60, 80 * step, 80 * step + 90)
+            order_h, comp_o, _, res_o = ohorizon.horizon_step(inst.s, inst.o, inst.M, order_h, moves, completed, 60)
+            _, res = c.horizon_step(order, _dev(moves), s, o, inst.M, completed, 60)
+            assert tuple(res.cpu().tolist()) == res_o
+            c.reserve(0, 1000 * (step + 1), 100)  # larger each time: the buffer moves
+            comp = c.horizon_completion(order, o, torch.full((700,), -1, dtype=torch.int32, device="cuda:0")).cpu().numpy()
+            placed = comp >= 0
+            assert (comp[placed] == comp_o[placed]).all() and placed[comp_o - inst.o <= res_o[5]].all()
+            completed = res_o[4]
+        assert c.device_status() == 0
+    finally:
+        c.close()
