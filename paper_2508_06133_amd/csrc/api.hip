@@ -415,10 +415,10 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
         if (rc != KVSCHED_OK) return rc;
     }
     const int32_t keep = ctx->resume_rows;  // reserving is no call: the last resume plan stays readable unless the buffer moves
-    const size_t keep_rejoin = ctx->rejoin_offset;
+    const size_t keep_rejoin = ctx->rejoin_offset, keep_neighbor = ctx->neighbor_stop_offset;
     const bool grows = need > ctx->scratch_bytes;
     const int rc = ensure_scratch(ctx, need);
-    if (!grows) ctx->resume_rows = keep, ctx->rejoin_offset = keep_rejoin;
+    if (!grows) ctx->resume_rows = keep, ctx->rejoin_offset = keep_rejoin, ctx->neighbor_stop_offset = keep_neighbor;
     return rc;
 }
 

@@ -264,6 +264,21 @@ def test_moves_that_only_reorder_requests_started_together_are_not_placed(ctx, c
     assert cut_short > K and placed_nothing > K // 2, (cut_short, placed_nothing)
 
 
+def test_stop_positions_survive_a_reservation_within_what_is_there(ctx):
+    import torch
+
+    n, K = 900, 400
+    inst = workloads.instance(3, n=n)
+    base, _, _ = oracle.sortedF(inst.s, inst.o, inst.M)
+    moves = workloads.window_moves(np.random.default_rng(4), K, 64, 200)
+    ctx.reserve(0, n, K)
+    _gpu_best(ctx, inst.s, inst.o, inst.M, base, moves)
+    before = ctx.neighbor_stop_positions(K, n).cpu().numpy()
+    ctx.reserve(0, n, K)  # nothing to do
+    after = ctx.neighbor_stop_positions(K, n).cpu().numpy()
+    assert (before < n).any() and (before == after).all()
+
+
 def test_best_neighbor_only_identity_moves(ctx):
     inst = workloads.instance(2, n=130)
     base, _, _ = oracle.sortedF(inst.s, inst.o, inst.M)
