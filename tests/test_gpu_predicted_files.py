@@ -68,3 +68,32 @@ def test_many_requests_that_finish_together(ctx):
         for M in (300 * 42, 130 * 42, 3000):
             print(f"predicted, finishing together: M={M} est {int(est[0])}", flush=True)
             _check(ctx, s, o, est.astype(np.int32), M, rows)
+
+
+@pytest.mark.parametrize("o_max", [5000, 8192, 16384])
+def test_rings(ctx, o_max):
+    """Beyond 4096 rounds: the projection as a ring; requests that run out together among long ones."""
+    inst = workloads.tight_instance(o_max, 50, o_max)
+    rng = np.random.default_rng(o_max)
+    s = np.concatenate([inst.s, np.full(40, 2, dtype=np.int32)]).astype(np.int32)
+    o = np.concatenate([inst.o, np.full(40, 40, dtype=np.int32)]).astype(np.int32)
+    o[0] = o_max
+    rows = np.stack([rng.permutation(len(o)) for _ in range(1 if o_max > 8192 else 3)]).astype(np.int32)
+    M = max(inst.M, int((s + o).max()))
+    lower, upper = workloads.prediction_intervals(o_max, s, o, M, 0.4)
+    upper = np.minimum(upper, 16384).astype(np.int32)
+    for what, est in (("lower", lower), ("upper", upper), ("exact", o)):
+        print(f"predicted, rings: o_max={o_max} M={M} {what}", flush=True)
+        _check(ctx, s, o, est, M, rows)
+
+
+@pytest.mark.parametrize("n", [1000, 1100, 1300])
+def test_long_lists_with_the_largest_register_file(ctx, n):
+    rng = np.random.default_rng(n)
+    s, o = np.ones(n, dtype=np.int32), rng.integers(1, 4001, n).astype(np.int32)
+    o[5] = 4000
+    lower = np.maximum(1, o // 2).astype(np.int32)
+    rows = rng.permutation(n)[None].astype(np.int32)
+    for M in (int(0.4 * n * 2000), 9000000):
+        print(f"predicted, long lists: n={n} M={M}", flush=True)
+        _check(ctx, s, o, lower, M, rows)
