@@ -468,7 +468,10 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
         w_base = p_uni(w_base), x_base = p_uni(x_base);
         if (t >= p.round_limit) { over_limit = true; break; }
         // A candidate that visits many rounds for each request it finishes (a random order: twice as many as the Sorted-F
-        // order's neighbours) runs longest, and the call lasts as long as it does: it goes first on its SIMD.
+        // order's neighbours) runs longest, and the call lasts as long as it does: it goes first on its SIMD.  Without / from
+        // 1.25 / 1.5 / 2 rounds a request on, 4096 candidates: mixed, lower bounds at gamma 0.6 9.4 / 8.4 to 9.2 / 8.3 / 9.4 ms,
+        // at 0.3 9.5 / 8.8 / 8.8 / 9.6, at 0.95 7.9 / 7.4 / 7.5 / 8.1; 400 chat requests 3.20 / 2.99 / 2.81 / 3.06; 300 mixed 1.82 /
+        // 1.81 / 1.82 / 1.76; 2000 chat requests, upper bounds, 1024 candidates: no difference.
         if ((++visited & 63) == 0) {
             if (2 * visited > 3 * done) __builtin_amdgcn_s_setprio(3);
             else __builtin_amdgcn_s_setprio(0);
@@ -811,12 +814,12 @@ static size_t lds_bytes(int32_t n, int32_t ring, int32_t cap, int32_t entry = 10
     return sizeof(int) * ((size_t)ring + (((size_t)n + 31) >> 5)) + (size_t)entry * (size_t)cap;
 }
 
-// The longest list of the first launch is the one with which `per_unit` candidates share a compute unit's 160 KB (LDS is
+// The longest list of the first launch is the one with which sixteen candidates share a compute unit's 160 KB (LDS is
 // handed out in whole KB); worth it when that is at least 128 entries and fewer than all.
-static int launch_rows(const void *kernel, PredParams p, int per_unit, hipStream_t st)
+static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
 {
     const int32_t cap_all = (p.n + 1) & ~1;
-    const size_t bytes_all = lds_bytes(p.n, 0, cap_all), fixed = lds_bytes(p.n, 0, 0), budget = (160 / per_unit) * 1024;
+    const size_t bytes_all = lds_bytes(p.n, 0, cap_all), fixed = lds_bytes(p.n, 0, 0), budget = 10 * 1024;
     const int32_t cap_first = fixed < budget ? (int32_t)((budget - fixed) / 10) & ~1 : 0;
     // beyond 64 KB of dynamic LDS the kernel's limit has to be raised first
     if (bytes_all > 64 * 1024 &&
@@ -877,10 +880,12 @@ int kvs_launch_predicted(const int32_t *orders, int32_t C, int32_t n, const int3
     p.completion_out = completion_out;
     p.evictions_out = evictions_out;
     p.d_words = d_words;
-    // The projection in registers while its rows leave room for three wavefronts per SIMD, else in LDS.
-    if (H <= 512) return launch_rows((const void *)predicted_reg_kernel<9>, p, 16, st);
-    if (H <= 1024) return launch_rows((const void *)predicted_reg_kernel<17>, p, 16, st);
-    if (H <= 2048) return launch_rows((const void *)predicted_reg_kernel<33>, p, 16, st);
-    if (H <= 4096) return launch_rows((const void *)predicted_reg_kernel<65>, p, 12, st);
+    // The projection in registers while its rows leave room for four wavefronts per SIMD (125 registers in the largest
+    // file), hence sixteen candidates per compute unit with every file; else in LDS.  65 rows, 4096 candidates of 2000 mixed
+    // requests with decodes up to 4096, eight / twelve / sixteen per unit: 21.0 / 19.3 / 12.3 ms, of 1000: 6.7 / 6.7 / 6.7.
+    if (H <= 512) return launch_rows((const void *)predicted_reg_kernel<9>, p, st);
+    if (H <= 1024) return launch_rows((const void *)predicted_reg_kernel<17>, p, st);
+    if (H <= 2048) return launch_rows((const void *)predicted_reg_kernel<33>, p, st);
+    if (H <= 4096) return launch_rows((const void *)predicted_reg_kernel<65>, p, st);
     return launch_ring((const void *)predicted_ring_kernel, p, st);
 }
