@@ -18,8 +18,9 @@
 //           nothing above t, so the dead lanes in front of the window need no mask.
 //   update  per row:  Q_r += s + (tau - t)
 //   Only the last row of a window is lane-masked (rounds beyond t + o), by value.
+// (Whether a request is blocked at all takes less: one maximum over the rows, see place_block.)
 //
-// The row loops are hand-written gfx950 assembly over a fixed block of physical VGPRs (v28
+// The row loops are hand-written gfx950 assembly over a fixed block of physical VGPRs (v30
 // upward) that only these assembly blocks touch, and the whole placement of up to 64 consecutive
 // requests is ONE assembly statement (place_block): the vector unit's issue slots are what bounds
 // the kernel, and the code a compiler wraps around separate check / update statements (copies for
@@ -27,12 +28,12 @@
 // a third of them.  A pass over rows 0..re is entered by one computed jump (s_getpc / s_setpc,
 // 64-byte slots) to a stub that handles the masked last row `re` with constant register numbers
 // and then branches into a descending chain of full rows re-1..0, which runs to its end without
-// a single compare or branch.  Rows are paired (five vector instructions per two rows in the
-// check, three in the update).
-// The compiler-generated part of the kernel and the operands of the assembly statements need
-// fewer than 28 VGPRs, so the block is never allocated (the build verifies that on the emitted
-// assembly of every instantiation); the clobber lists keep the block, s72, s73 and vcc out of the
-// compiler's hands across the assembly statements.
+// a single compare or branch; the first rows of a file have the whole request in one slot.  The check takes two rows per
+// vector instruction, the update two rows in three (files of 9 and 33 rows) or one (the larger ones).
+// The compiler-generated part of the kernel and the operands of the assembly statements stay
+// below v30, so the block is never allocated (the build verifies that on the emitted
+// assembly of every instantiation); the clobber lists keep the block, the scalar registers of KVS_SCLOB_* and vcc out of
+// the compiler's hands across the assembly statements.
 #include "kvsched_internal.h"
 #include "device_util.h"
 
