@@ -95,9 +95,10 @@ void kvsched_destroy(kvsched_ctx *ctx);
  * rows, kvsched_best_neighbor / kvsched_horizon_step with up to `moves` moves, and the Phase-1
  * calls (kvsched_sortedF, kvsched_local_swap, kvsched_phase1_G with those solvers), all on up to
  * `n` positions (0 rows / moves: that call is not planned).  Calls within these sizes then never
- * allocate, whatever the decode lengths, now and when they grow; with moves that covers the buffer which
- * kvsched_horizon_step keeps between steps, and takes up to 58 KB per 64 positions twice.  (kvsched_exact_dp sizes its tables from the data and kvsched_online from the number
- * of streams: not covered.)  ENOMEM if the device cannot provide the buffer. */
+ * allocate, whatever the decode lengths, now and when they grow; with moves that includes what
+ * kvsched_horizon_step keeps between steps (saved states of up to 58 KB per 64 positions are provided
+ * for twice).  (kvsched_exact_dp sizes its tables from the data and kvsched_online from the number
+ * of streams: not covered.)  ENOMEM if the device cannot provide the buffers. */
 int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves);
 
 /* Static description of a return code. */

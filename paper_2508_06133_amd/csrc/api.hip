@@ -174,14 +174,15 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
 
 constexpr int32_t kMinSharedPrefix = 64;  // shorter shared prefixes are not worth a launch
 // Resuming rows from snapshots of row 0 costs the plan (which rows share what with row 0, sorted:
-// some 60 us for 16384 rows) and the wait for row 0's wave; it pays when there is enough work to
+// some 50 us for 16384 rows) and the wait for row 0's wave; it pays when there is enough work to
 // skip.  Measured on random one-swap neighbours of a base order, whole call, no resume / resumed in
-// one launch: n = 2000: 4096 rows 1.02 / 0.96 ms, 8192 rows 1.63 / 1.33, 16384 rows 2.96 / 2.25;
-// n = 500: 8192 rows 0.42 / 0.41, 16384 rows 0.74 / 0.69; n = 200: never (0.33 / 0.40 at 16384 rows).
+// one launch / in two: n = 2000: 2048 rows 0.48 / 0.53 / 0.85 ms, 4096 rows 0.62 / 0.63 / 0.87, 6144 rows 0.78 / 0.75 / 0.96,
+// 16384 rows 1.71 / 1.34 / 1.66; n = 1000: 8192 rows 0.54 / 0.54 / 0.64, 16384 rows 0.98 / 0.86 / 0.99; n = 500: 8192 rows 0.32 /
+// 0.38 / 0.40, 16384 rows 0.57 / 0.58 / 0.62, 32768 rows 1.06 / 0.98 / 1.06; n = 200: never (16384 rows 0.37 / 0.51 / 0.45).
 // Hence, unless the caller sets a row threshold of his own: at least 4096 rows, 6 blocks of 64
 // positions and 8 million positions in all.  In two launches (the quarter of the rows that shares least,
 // at most half a chip's worth, from the start next to row 0, then the others) the first launch lasts
-// a whole timeline whatever it holds: that pays from 16384 rows on (n = 2000: 2.96 / 2.53 ms).
+// a whole timeline whatever it holds: that pays from 16384 rows on.
 constexpr int32_t kResumeAutoMinRows = 4096;
 constexpr int32_t kResumeAutoMinRowsTwoLaunches = 16384;
 constexpr int32_t kResumeAutoMinBlocks = 6;
