@@ -236,13 +236,17 @@ HorizonKept horizon_kept(kvsched_ctx *ctx, int32_t n)
     return h;
 }
 
-// Room for n positions with saved states of `stride` words; growing it forgets what was kept, unless `carry`: what is
-// there moves along (its places depend on its own number of positions alone).
-int ensure_horizon(kvsched_ctx *ctx, int32_t n, int32_t stride, bool carry = false)
+// ... for n positions with saved states of `stride` words.
+size_t horizon_bytes(int32_t n, int32_t stride)
 {
-    const size_t bytes = align256(sizeof(int32_t) * (KVS_HZ_WORDS + KVS_PROGRESS_WORDS)) +
-                         5 * align256(sizeof(int32_t) * (size_t)n) +
-                         sizeof(int32_t) * (size_t)((n - 1) / WAVE_POSITIONS) * (size_t)stride + 256;
+    return align256(sizeof(int32_t) * (KVS_HZ_WORDS + KVS_PROGRESS_WORDS)) + 5 * align256(sizeof(int32_t) * (size_t)n) +
+           sizeof(int32_t) * (size_t)((n - 1) / WAVE_POSITIONS) * (size_t)stride + 256;
+}
+
+// Growing it forgets what was kept, unless `carry`: what is there moves along (its places depend on its own number of
+// positions alone).
+int ensure_horizon(kvsched_ctx *ctx, size_t bytes, bool carry = false)
+{
     if (bytes <= ctx->horizon_bytes) return KVSCHED_OK;
     if (ctx->d_horizon && hipDeviceSynchronize() != hipSuccess) return KVSCHED_EHIP;
     if (!carry) {
@@ -394,8 +398,7 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
 {
     if (!ctx || rows < 0 || n < 1 || moves < 0) return KVSCHED_EINVAL;
     if (hipSetDevice(ctx->device) != hipSuccess) return KVSCHED_EHIP;
-    // the largest of what the calls named in the header ask of the scratch buffer at these sizes, whatever the decode
-    // lengths (saved states of the largest kind: a bound set now may be lifted later)
+    // the largest of what the calls named in the header ask of the scratch buffer at these sizes
     const size_t nblk = (size_t)((n - 1) / WAVE_POSITIONS);
     const size_t row_bytes = align256(sizeof(int32_t) * (size_t)n);
     size_t need = kvs_sortedF_scratch_bytes(n);
@@ -410,9 +413,18 @@ int kvsched_reserve(kvsched_ctx *ctx, int32_t rows, int32_t n, int32_t moves)
         if (pre > need) need = pre;
     }
     if (moves > 0) {
-        const size_t hor = neighbor_scratch_bytes(moves, n, 0) + row_bytes + 256;
-        if (hor > need) need = hor;
-        const int rc = ensure_horizon(ctx, n, KVS_STATE_MAX_WORDS, true);  // what the horizon step keeps between steps
+        // ... whatever the decode lengths (a bound set now may be lifted later): for the shortest decodes of each register
+        // file, the most positions that a call may have with them
+        size_t kept = 0;  // by the horizon step, between steps
+        for (const int32_t o_bound : {1, 513, 2049, 4097, 8193}) {
+            const int64_t most = (kMaxM - 1) / ring_slots_for(o_bound);
+            const int32_t m = (int32_t)(most < n ? most : n);
+            const size_t hor = neighbor_scratch_bytes(moves, m, o_bound) + align256(sizeof(int32_t) * (size_t)m) + 256;
+            if (hor > need) need = hor;
+            const size_t states = horizon_bytes(m, kvs_reg_state_words(o_bound));
+            if (states > kept) kept = states;
+        }
+        const int rc = ensure_horizon(ctx, kept, true);
         if (rc != KVSCHED_OK) return rc;
     }
     const int32_t keep = ctx->resume_rows;  // reserving is no call: the last resume plan stays readable unless the buffer moves
@@ -846,13 +858,17 @@ int kvsched_phase1_G(kvsched_ctx *ctx, int32_t solver, int32_t n, const int32_t 
 // and the plan for resuming each move's timeline from the base order's (three lists of K + 1 entries, a flag
 // and a saved state of the largest kind per 64 positions).
 namespace {
-// o_bound: the caller's bound on the decode lengths if there is one (it fixes the size of a saved state), else 0.
+// o_bound: the caller's bound on the decode lengths if there is one (it fixes the size of a saved state), else 0: the
+// longest that n positions allow (rounds are int32).
 size_t neighbor_scratch_bytes(int32_t K, int32_t n, int32_t o_bound)
 {
     const size_t nblk = (size_t)((n - 1) / WAVE_POSITIONS);
+    if (o_bound == 0) {
+        o_bound = KVS_REG_MAX_O;
+        while (o_bound > 512 && (int64_t)n * ring_slots_for(o_bound) >= kMaxM) o_bound = ring_slots_for(o_bound) / 2;
+    }
     const size_t words = o_bound > KVS_REG_MAX_O ? 0  // beyond the register kernel nothing is resumed
-                         : o_bound > 0           ? (size_t)kvs_reg_state_words(o_bound)
-                                                 : KVS_STATE_MAX_WORDS;
+                                                 : (size_t)kvs_reg_state_words(o_bound);
     return align256(sizeof(int64_t) * ((size_t)K + 1)) + state_bytes() +
            4 * align256(sizeof(int32_t) * ((size_t)K + 1)) + align256(sizeof(int32_t) * (size_t)n) +
            align256(sizeof(int32_t) * KVS_PROGRESS_WORDS) + align256(sizeof(int32_t) * nblk * words);
@@ -1072,7 +1088,7 @@ int kvsched_horizon_step(kvsched_ctx *ctx, int32_t *order, int32_t n, const int3
     const bool states_wanted = n > 2 * WAVE_POSITIONS && ctx->resume_wait_polls > 0 && ctx->resume_min_rows != 0;
     if (!(states_wanted && o_bound <= KVS_REG_MAX_O)) {  // short orders, and where saved states are ruled out: step by step
         ctx->hz_kept = 0;
-        rc = ensure_horizon(ctx, n, 0);
+        rc = ensure_horizon(ctx, horizon_bytes(n, 0));
         if (rc != KVSCHED_OK) return rc;
         return horizon_step_plain(ctx, order, n, moves, K, s, o, M, completed_in, complete_every, tel_out, completion_out,
                                   result_out, st);
@@ -1082,13 +1098,13 @@ int kvsched_horizon_step(kvsched_ctx *ctx, int32_t *order, int32_t n, const int3
     if ((int64_t)n * (int64_t)ring_slots_for(o_bound) >= kMaxM) return KVSCHED_ERANGE;
     if (o_bound > KVS_REG_MAX_O) {
         ctx->hz_kept = 0;
-        rc = ensure_horizon(ctx, n, 0);
+        rc = ensure_horizon(ctx, horizon_bytes(n, 0));
         if (rc != KVSCHED_OK) return rc;
         return horizon_step_plain(ctx, order, n, moves, K, s, o, M, completed_in, complete_every, tel_out, completion_out,
                                   result_out, st);
     }
     const int32_t stride = kvs_reg_state_words(o_bound), nblk = (n - 1) / WAVE_POSITIONS, C = K + 1;
-    rc = ensure_horizon(ctx, n, stride);
+    rc = ensure_horizon(ctx, horizon_bytes(n, stride));
     if (rc != KVSCHED_OK) return rc;
     const HorizonKept h = horizon_kept(ctx, n);
     // (a state holds the largest file's words or fewer: kept ones are of use only to the same file)
