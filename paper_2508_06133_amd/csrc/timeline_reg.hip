@@ -183,8 +183,7 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //   move on  t becomes the largest bound (six DPP steps), the register file moves down so that row 0
 //            holds round t + 1 again, and only the rounds that have entered the window since are
 //            looked at: nearly always the window's last row alone (one computed jump to a stub of
-//            that row), otherwise rows rs..re one by one (a computed jump per row: the row number is
-//            not known at compile time and VGPR index mode is avoided); blocked again: repeat;
+//            that row), otherwise the whole window once more, as at first; blocked again: repeat;
 //   admit    rows 0..re get the ramp s + (tau - t) (by value zero beyond the window); the start
 //            round t goes to the request's lane of cv.
 // A taken jump costs a lone wavefront some 40 cycles, so a window of at most kvs_one + 1 rows has its whole request
@@ -206,7 +205,10 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // 1 % faster with one wavefront per SIMD, was 12 % slower with eight.)
 //
 // Beyond 65 rows most of the time went into rows that hold nothing and into limits that bind nothing, hence
-//   * the file moves down only as far as memory is committed (hi, kept across blocks and in saved states);
+//   * the file moves down only as far as memory is committed (hi, kept across blocks and in saved states), by 16 and by 4
+//     rows at a time first: where long decodes end together the round moves by thousands (bimodal orders: 38 rows on
+//     average, 2470 instructions one row at a time, 290 now; with the whole window looked at again instead of its new rows one
+//     by one, 1025 orders of 100000: 29.1 -> 27.2 ms; 16384 of 2000, decodes up to 2048, where the latter counts: 1406 -> 1357 us);
 //   * a blocked request whose rows 4 and above stay below bound 256 takes the limits of rows 0..3 alone;
 //   * the ramp of a row is added in one instruction, as in the 65-row file, from 22 scalar offsets per 66 rows.
 // With the slots above, 8191 moves on 2000 requests with decodes up to 8192: 1511 -> 1240 us; 1025 bimodal orders of
@@ -242,6 +244,26 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
     "v_max_i32_dpp %[y], %[y], %[y] row_bcast:31 row_mask:0xc bank_mask:0xf\n"                  \
     "s_nop 1\n"                                                                                 \
     "v_readlane_b32 %[tc], %[y], 63\n"
+
+// The register file moves down by the given number of rows (of the %[rs] it has to).
+#define KVS_MOVE_DOWN(rows)                                                                      \
+    ".set kvs_r, 0\n"                                                                           \
+    ".rept %c[nr]-" rows "\n"                                                                   \
+    "  .if (kvs_r & 7) == 0\n" /* nothing is committed from row hi / 64 on */                   \
+    "    s_cmp_le_u32 %[hi], 64*kvs_r\n"                                                        \
+    "    s_cbranch_scc1 54f\n"                                                                  \
+    "  .endif\n"                                                                                \
+    "  v_subrev_u32 v[" KVS_PB "+kvs_r], 64*" rows ", v[" KVS_PB "+kvs_r+" rows "]\n"           \
+    "  .set kvs_r, kvs_r+1\n"                                                                   \
+    ".endr\n"                                                                                   \
+    ".rept " rows "\n"                                                                          \
+    "  v_mov_b32 v[" KVS_PB "+kvs_r], 64*kvs_r\n"                                               \
+    "  .set kvs_r, kvs_r+1\n"                                                                   \
+    ".endr\n"                                                                                   \
+    "54:\n"                                                                                     \
+    "s_sub_u32 %[hi], %[hi], 64*" rows "\n"                                                     \
+    "s_max_i32 %[hi], %[hi], 0\n"                                                               \
+    "s_sub_u32 %[rs], %[rs], " rows "\n"
 
 // Pads the slot that began at the last label 7 to the given number of bytes (never executed: slots
 // end in a branch).
@@ -631,24 +653,26 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_cbranch_scc0 46f\n"                                                                          \
         "s_cmp_ge_u32 %[rs], %c[nr]\n"                                                                  \
         "s_cbranch_scc1 47f\n"                                                                          \
+        ".if %c[nr] >= 65\n"                /* long decodes end far apart: 16 and 4 rows at a time */    \
+        "41:\n"                                                                                         \
+        "  s_cmp_lt_u32 %[rs], 16\n"                                                                    \
+        "  s_cbranch_scc1 58f\n"                                                                        \
+        KVS_MOVE_DOWN("16")                                                                             \
+        "  s_branch 41b\n"                                                                              \
+        "58:\n"                                                                                         \
+        "  s_cmp_lt_u32 %[rs], 4\n"                                                                     \
+        "  s_cbranch_scc1 59f\n"                                                                        \
+        KVS_MOVE_DOWN("4")                                                                              \
+        "  s_branch 58b\n"                                                                              \
+        "59:\n"                                                                                         \
+        "  s_cmp_eq_u32 %[rs], 0\n"                                                                     \
+        "  s_cbranch_scc1 46f\n"                                                                        \
+        ".endif\n"                                                                                     \
         "45:\n"                                                                                         \
-        ".set kvs_r, 0\n"                                                                               \
-        ".rept %c[nr]-1\n"                                                                              \
-        "  .if (kvs_r & 7) == 0\n"          /* nothing is committed from row hi / 64 on */              \
-        "    s_cmp_le_u32 %[hi], 64*kvs_r\n"                                                           \
-        "    s_cbranch_scc1 54f\n"                                                                     \
-        "  .endif\n"                                                                                    \
-        "  v_subrev_u32 v[" KVS_PB "+kvs_r], 64, v[" KVS_PB "+kvs_r+1]\n"                               \
-        "  .set kvs_r, kvs_r+1\n"                                                                       \
-        ".endr\n"                                                                                       \
-        "v_mov_b32 v[" KVS_PB "+%c[nr]-1], 64*(%c[nr]-1)\n"                                             \
-        "54:\n"                                                                                         \
-        "s_sub_u32 %[hi], %[hi], 64\n"                                                                  \
-        "s_max_i32 %[hi], %[hi], 0\n"                                                                   \
-        "s_sub_u32 %[rs], %[rs], 1\n"                                                                   \
-        "s_cmp_lg_u32 %[rs], 0\n"                                                                       \
-        "s_cbranch_scc1 45b\n"                                                                          \
-        "s_branch 46f\n"                                                                                \
+        KVS_MOVE_DOWN("1")                                                                              \
+        "s_cmp_lg_u32 %[rs], 0\n"                                                                      \
+        "s_cbranch_scc1 45b\n"                                                                         \
+        "s_branch 46f\n"                                                                               \
         "47:\n"                                                                                         \
         ".set kvs_r, 0\n"                                                                               \
         ".rept %c[nr]\n"                                                                                \
@@ -672,41 +696,12 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "  s_cbranch_vccz 42b\n"                                                                        \
         "  s_branch 44b\n" KVS_SLOT_PAD(64)                                                             \
         ".endr\n"                                                                                       \
-        /* rows tb..tc, the last of them masked */                                                      \
+        /* several rows are new: the whole window once more */                                          \
         "48:\n"                                                                                         \
-        "s_add_u32 %[tb], %[tb], 1\n"                                                                   \
-        "s_lshr_b32 %[tb], %[tb], 6\n"                                                                  \
-        "s_sub_u32 %[tb], %[tb], 1\n"                                                                   \
-        "s_lshr_b32 %[tc], %[x64], 6\n"                                                                 \
-        "s_sub_u32 %[tc], %[tc], 1\n"                                                                   \
-        "v_mov_b32 %[acc], %[vmin]\n"                                                                   \
-        "51:\n"                                                                                         \
-        "s_cmp_eq_u32 %[tb], %[tc]\n"                                                                   \
-        "s_cselect_b64 vcc, %[mk], 0\n"                                                                \
-        "s_add_u32 %[ta], %[tb], 1\n"                                                                   \
-        "s_lshl_b32 %[ta], %[ta], 4\n"       /* 16-byte slots, the first 16 bytes behind s_getpc's successor */ \
-        "s_getpc_b64 s[66:67]\n"                                                                        \
-        "s_add_u32 s66, s66, %[ta]\n"                                                                   \
-        "s_addc_u32 s67, s67, 0\n"                                                                      \
+        "s_lshl_b32 %[ta], %[off], kvs_slot-6\n"                                                        \
+        "s_add_u32 s66, %[ql], %[ta]\n"                                                                 \
+        "s_addc_u32 s67, %[qh], 0\n"                                                                    \
         "s_setpc_b64 s[66:67]\n"                                                                        \
-        ".fill 1, 4, 0xbf800000\n"                                                                      \
-        ".irp r," ASC "\n"                                                                              \
-        "7:\n"                                                                                          \
-        "  v_subrev_u32 %[y], %[ns], v[" KVS_PB "+\\r]\n"                                                  \
-        "  v_min_i32 %[y], 64*\\r, %[y]\n"                                                              \
-        "  s_branch 49f\n" KVS_SLOT_PAD(16)                                                             \
-        ".endr\n"                                                                                       \
-        "49:\n"                                                                                         \
-        "v_cndmask_b32_e32 %[y], %[y], %[vmin], vcc\n"                                                 \
-        "v_max_i32 %[acc], %[acc], %[y]\n"                                                              \
-        "s_add_u32 %[tb], %[tb], 1\n"                                                                   \
-        "s_cmp_le_u32 %[tb], %[tc]\n"                                                                   \
-        "s_cbranch_scc1 51b\n"                                                                          \
-        /* ---- the new rounds' bounds (exact): admitted now, or blocked once more */                   \
-        "53:\n"                                                                                         \
-        "v_cmp_gt_i32 vcc, %[acc], %[tl]\n"                                                             \
-        "s_cbranch_vccz 42b\n"                                                                          \
-        "s_branch 44b\n"                                                                                \
         "50:\n"                                                                                         \
         : [cv] "=&v"(cv), [acc] "=&v"(acc), [y] "=&v"(y), [z] "=&v"(z), [tl] "=&v"(tl), [vw] "=&v"(vw), \
           [ns] "=&s"(ns), [oj] "=&s"(oj), [x64] "=&s"(x64), [off] "=&s"(off), [u64] "=&s"(u64),         \
