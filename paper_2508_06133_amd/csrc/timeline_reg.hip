@@ -164,11 +164,48 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 }
 
 // ---------------------------------------------------------------------------------------------
+// Requests started in one round, many at a time.
+//
+// While it is known that no round after t holds more than M - H, requests whose sizes s + o sum up to at most H can all
+// start at t whatever their windows: one prefix sum over the 64 lanes of a block says how many, and nothing has to be
+// looked at row by row.  Their ramps are added later, all in one pass over the rows, before the next request that has to
+// be looked at: a request that ends at round e of the file (in units of rounds from b64) is kept as (s, e) in a list in LDS,
+// and round x gets (sum of s) + (number) * (x - (t - b64)) over the entries with e >= x.  The rows are taken from the last
+// down in chunks of four: a chunk in which no entry ends is a line (one instruction per row besides the addition); for the others the
+// entries are scattered into a histogram of 256 rounds, each lane sums four rounds of it from the end, and one
+// prefix sum over the lanes joins them.
+//
+// H is known at the beginning (M) and from saved states; while requests start at round 0 it only falls by their sizes.
+// Later it is the distance of the file's maximum to M, which costs one and a half instructions per row: worth it when
+// many requests follow in one round.  The files of 65 rows and more (long decodes, rows dear to look at) find that out by
+// themselves: place_block returns after kRunMoved + 1 requests in a row that did not move the round.
+//
+// What it gives: of bimodal orders (decodes 1 or 4096) 97 % of the requests start that way, 56 at a time, and their ramps are added 340 at a
+// time: 1025 orders of 100000 27.2 -> 4.5 ms, of which the timelines 26.3 -> 3.6: one wavefront per SIMD, bound by the chain
+// of the blocks (loads, prefix sum, list: 1500 cycles per 64 requests) and of the 250 moves.  4096 chat orders of 200, half of
+// them in the first burst: 82.5 -> 80 us.  Below kGroupMin requests the pass over the rows (75 instructions per chunk with
+// entries) costs more than they do one by one.
+constexpr int kChunkRows = 4;
+constexpr int kChunk = WAVE * kChunkRows;
+template <int NR>
+constexpr int kRunMoved = NR > 65 ? 16 : 4;  // (more rows to look at)
+template <int NR>
+constexpr int kListCap = NR >= 65 ? 512 : 256;
+// Which launches do so.  Not the 9-row file: its rows are few, and its launches of many short timelines lose 3 % to LDS and
+// a longer beginning (40321 orders of 8).  Timelines that resume from saved states have most of their bursts behind them: 16384
+// orders of 2000 with the 33-row file 1357 us without and 1407 with it, 8191 moves with the 129-row file 1221 and 1239; with
+// the 65-row file they do, for the sake of bimodal lengths.
+template <int NR, bool RES>
+constexpr bool kGroup = RES ? NR == 65 : NR >= 33;
+constexpr int kGroupMin = 16;  // below this the requests are placed one by one
+
+// ---------------------------------------------------------------------------------------------
 // Placing up to 64 consecutive requests of the order: ONE assembly statement.
 //
 // Lane j of vns / vo holds M - s and o of a request; the requests are taken from lane cnt - 1 down to
 // lane 0 (the lane number is kept in M0 for v_readlane / v_writelane, and the loop ends when it
-// borrows).  Round tau imposes the start bound min(P(tau) + s - M + tau, tau) on the
+// borrows; v_readlane and v_writelane use the six low bits, above them the files of 65 rows and more count down the
+// requests that may still follow before the statement returns early, so that one subtraction does both).  Round tau imposes the start bound min(P(tau) + s - M + tau, tau) on the
 // request (from round tau on it no longer overlaps tau); with Q_r = P + 64 r that is, relative to the
 // lane's round in row 0, min(Q_r + (s - M), 64 r).  For each request in turn:
 //   blocked? rows 0..re of the profile (re = row of the window's last round t + o; the last row is
@@ -225,7 +262,7 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 //   jump (at least five scalar instructions later); oj, vcc and the DPP result are read by scalar
 //   instructions, which need none;
 //   DPP reads of a VGPR written by the previous VALU instruction, and v_readlane of one: s_nop 1.
-// The kernel has no other use of M0 (no LDS, no relative addressing).
+// The kernel has no other use of M0 (LDS instructions need none here, no relative addressing).
 
 // Maximum over the 64 lanes of %[y] into lane 63 (four DPP steps inside the 16-lane rows, two row
 // broadcasts), read into %[tc].
@@ -270,10 +307,12 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // (The .org stops the build if the slot does not hold what was put into it.)
 #define KVS_SLOT_PAD(bytes) "  .fill (" #bytes "-(.-7b))/4, 4, 0xbf800000\n  .org 7b+" #bytes "\n"
 
-template <int NR>
-__device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, int vmin, int M, int &t, int &b64, int &hi)
+// (RUNS: return early behind look + 1, later kRunMoved + 1, requests that did not move the round; cnt: those left)
+template <int NR, bool RUNS>
+__device__ __forceinline__ void place_block(int &cnt, int look, int vns, int vo, int lane, int vmin, int M, int &cv, int &t, int &b64,
+                                            int &hi)
 {
-    int cv, acc, y, z, tl, vw;
+    int acc, y, z, tl, vw;
     int ns, oj, x64, off, u64, rs, ta, tb, tc, ql, qh, cl, ch, ul, uh, rl, rh;
     long long mk;
 #define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                                       \
@@ -321,8 +360,16 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "  s_sub_u32 %[tc], %[M], 64\n"                                                                \
         "  v_sub_u32 %[vw], %[tc], %[tl]\n" /* ramp in lane l of the window's last row: vw + (s - M) + 64 (re + 1) */ \
         ".endif\n"                                                                                      \
-        "v_mov_b32 %[cv], 0\n"                                                                          \
-        "s_sub_u32 m0, %[cnt], 1\n"                                                                     \
+        ".if %c[runs]\n"                                                                                \
+        "  s_sub_u32 %[tc], %[cnt], 1\n"                                                                \
+        "  s_min_u32 %[ta], %[tc], %[look]\n"                                                           \
+        "  s_lshl_b32 %[ta], %[ta], 6\n"                                                                \
+        "  s_add_u32 m0, %[tc], %[ta]\n"                                                                \
+        "  .set kvs_step, 65\n"                                                                         \
+        ".else\n"                                                                                       \
+        "  s_sub_u32 m0, %[cnt], 1\n"                                                                   \
+        "  .set kvs_step, 1\n"                                                                          \
+        ".endif\n"                                                                                      \
         /* ---- next request (lane m0, counting down): is it blocked at all? */                         \
         "40:\n"                                                                                         \
         "v_readlane_b32 %[ns], %[vns], m0\n"                                                            \
@@ -442,7 +489,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "      .endr\n"                                                                                 \
         "    .endif\n"                                                                                  \
         "    v_writelane_b32 %[cv], %[t], m0\n"                                                         \
-        "    s_sub_u32 m0, m0, 1\n"                                                                     \
+        "    s_sub_u32 m0, m0, kvs_step\n"                                                               \
         "    s_cbranch_scc0 40b\n"                                                                      \
         "    s_branch 50f\n"                                                                            \
         "  .else\n"                                                                                     \
@@ -564,7 +611,7 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         ".endr\n"                                                                                       \
         "43:\n"                                                                                         \
         "v_writelane_b32 %[cv], %[t], m0\n"  /* the start round; the caller adds the lane's decode length */ \
-        "s_sub_u32 m0, m0, 1\n"             /* borrows behind lane 0 */                                 \
+        "s_sub_u32 m0, m0, kvs_step\n"      /* borrows behind the last */                                 \
         "s_cbranch_scc0 40b\n"                                                                          \
         "s_branch 50f\n"                                                                                \
         /* ---- blocked.  The bounds found are exact unless one exceeds 64 in some lane (only then */   \
@@ -631,6 +678,12 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         /* ---- move t to the largest bound, the register file with it, look at what is new */          \
         "44:\n"                                                                                         \
         "v_add_u32 %[y], %[acc], %[lane]\n"                                                             \
+        ".if %c[runs]\n"                    /* the count of requests that have not moved begins anew */  \
+        "  s_and_b32 %[ta], m0, 63\n"                                                                   \
+        "  s_min_u32 %[tb], %[ta], %c[anew]\n"                                                          \
+        "  s_lshl_b32 %[tb], %[tb], 6\n"                                                                \
+        "  s_add_u32 m0, %[ta], %[tb]\n"                                                                \
+        ".endif\n"                                                                                      \
         KVS_WAVE_MAX                                                                                    \
         "s_add_u32 %[t], %[tc], %[b64]\n"                                                               \
         "s_add_u32 %[ta], %[tc], 1\n"                                                                   \
@@ -703,17 +756,329 @@ __device__ __forceinline__ int place_block(int cnt, int vns, int vo, int lane, i
         "s_addc_u32 s67, %[qh], 0\n"                                                                    \
         "s_setpc_b64 s[66:67]\n"                                                                        \
         "50:\n"                                                                                         \
-        : [cv] "=&v"(cv), [acc] "=&v"(acc), [y] "=&v"(y), [z] "=&v"(z), [tl] "=&v"(tl), [vw] "=&v"(vw), \
+        "s_add_u32 %[cnt], m0, kvs_step\n"  /* requests left (63 bits: lane 0 has been placed) */         \
+        : [cv] "+&v"(cv), [cnt] "+&s"(cnt), [acc] "=&v"(acc), [y] "=&v"(y), [z] "=&v"(z), [tl] "=&v"(tl), [vw] "=&v"(vw), \
           [ns] "=&s"(ns), [oj] "=&s"(oj), [x64] "=&s"(x64), [off] "=&s"(off), [u64] "=&s"(u64),         \
           [rs] "=&s"(rs), [ta] "=&s"(ta), [tb] "=&s"(tb), [tc] "=&s"(tc), [ql] "=&s"(ql), \
           [qh] "=&s"(qh), [cl] "=&s"(cl), [ch] "=&s"(ch), [ul] "=&s"(ul), [uh] "=&s"(uh), [rl] "=&s"(rl), \
           [rh] "=&s"(rh), [mk] "=&s"(mk), [t] "+s"(t), [b64] "+s"(b64), [hi] "+s"(hi)                  \
-        : [cnt] "s"(cnt), [vns] "v"(vns), [vo] "v"(vo), [lane] "v"(lane), [vmin] "v"(vmin),             \
+        : [look] "s"(look), [anew] "n"(kRunMoved<NR>), [runs] "n"(RUNS ? 1 : 0), [vns] "v"(vns), [vo] "v"(vo), [lane] "v"(lane), [vmin] "v"(vmin),             \
           [M] "s"(M), [nr] "n"(NR)                                                                      \
         : "scc", "vcc", SCLOB, CLOB)
     KVS_FOR_NR(KVS_STMT);
 #undef KVS_STMT
-    return cv;
+}
+
+template <int NR>
+struct GroupLds {  // of one wavefront
+    int e[kListCap<NR>], s[kListCap<NR>];  // the list; unused entries have e = -1
+    int number[kChunk];                    // of the chunk's entries by round; then what the chunk's rounds get
+    int sum[kChunk];                       // of their s
+    int kept[NR >= 65 ? 6 : 4][WAVE];      // registers that group_flush gives back as they were
+
+    // The last place of s is never an entry's: it has a bit for every chunk, or pair of chunks, in which some entry ends.
+    static constexpr int chunk_shift = NR > 128 ? 1 : 0;
+    __device__ __forceinline__ int &chunks() { return s[kListCap<NR> - 1]; }
+};
+
+// The largest P of the rounds behind t (u = t - b64); 0 if nothing is committed there.
+template <int NR>
+__device__ __forceinline__ int prof_max(int u, int hi, int lane)
+{
+    int acc = lane > u ? 0 : -(1 << 30), y, z, mx;
+    // (row 0: Q where the lane's round lies behind t)
+#define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                            \
+    asm volatile("v_cmp_lt_i32 vcc, %[u], %[lane]\n"                                             \
+                 "v_mov_b32 %[acc], 0\n"                                                         \
+                 "s_nop 1\n"                                                                     \
+                 "v_cndmask_b32_e32 %[acc], %[acc], v[" KVS_PB "], vcc\n"                        \
+                 ".set kvs_r, 1\n"                                                               \
+                 ".rept (%c[nr]-1)/2\n"                                                          \
+                 "  .if (kvs_r & 7) == 1\n"                                                      \
+                 "    s_cmp_le_u32 %[hi], 64*kvs_r\n"                                            \
+                 "    s_cbranch_scc1 1f\n"                                                       \
+                 "  .endif\n"                                                                    \
+                 "  v_add_u32 %[y], -64*kvs_r, v[" KVS_PB "+kvs_r]\n"                            \
+                 "  v_add_u32 %[z], -64*kvs_r-64, v[" KVS_PB "+kvs_r+1]\n"                       \
+                 "  v_max3_i32 %[acc], %[acc], %[y], %[z]\n"                                     \
+                 "  .set kvs_r, kvs_r+2\n"                                                       \
+                 ".endr\n"                                                                       \
+                 "1:\n"                                                                          \
+                 "v_max_i32 %[y], 0, %[acc]\n"                                                   \
+                 KVS_WAVE_MAX                                                                    \
+                 : [acc] "=&v"(acc), [y] "=&v"(y), [z] "=&v"(z), [tc] "=&s"(mx)                  \
+                 : [u] "s"(u), [hi] "s"(hi), [lane] "v"(lane), [nr] "n"(NR)                      \
+                 : "scc", "vcc", CLOB)
+    KVS_FOR_NR(KVS_STMT);
+#undef KVS_STMT
+    return mx;
+}
+
+// Sum over lanes 0 .. lane.
+__device__ __forceinline__ int lane_prefix_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+// How many of the requests in lanes rem - 1, rem - 2, .. 0 (in this order) start at t together; H falls by their sizes,
+// in units of 2^shift (rounded up), which keep the sum of 64 sizes within 32 bits.
+__device__ __forceinline__ int group_size(int rem, int size, int lane, int shift, int &H)
+{
+    const int unit = lane < rem ? (size + (1 << shift) - 1) >> shift : 0;
+    const int below = lane_prefix_sum(unit);  // lanes 0 .. lane
+    const int total = __builtin_amdgcn_readlane(below, WAVE - 1);
+    const unsigned sum = (unsigned)(total - below + unit);  // lanes lane .. rem - 1
+    const unsigned long long fits = __builtin_amdgcn_ballot_w64(lane < rem && sum <= (unsigned)H >> shift);
+    const int g = __popcll(fits);
+    if (g > 0) H -= __builtin_amdgcn_readlane((int)sum, rem - g) << shift;
+    return g;
+}
+
+// The list without entries.
+template <int NR>
+__device__ __forceinline__ void group_clear(GroupLds<NR> &L, int lane)
+{
+    asm volatile("" : "+v"(lane));  // (nothing that follows from it is to be kept in a register all along)
+    int none = -1;
+    asm volatile("" : "+v"(none));
+    volatile __attribute__((address_space(3))) int *e = (volatile __attribute__((address_space(3))) int *)L.e + lane;
+    for (int b = 0; b < kListCap<NR>; b += WAVE) e[b] = none;
+    L.chunks() = 0;
+}
+
+// The requests in lanes rem - 1 .. rem - g join the `count` in the list (e: the round their window ends at, from b64).
+template <int NR>
+__device__ __forceinline__ void group_append(GroupLds<NR> &L, int &count, int rem, int g, int s, int e, int lane)
+{
+    asm volatile("" : "+v"(lane));
+    if (lane < rem && lane >= rem - g) {
+        L.e[count + rem - 1 - lane] = e;
+        L.s[count + rem - 1 - lane] = s;
+        // (in assembly: the compiler would make it a loop over the lanes)
+        asm volatile("ds_or_b32 %0, %1" ::"v"((unsigned)(uintptr_t)(__attribute__((address_space(3))) int *)&L.chunks()),
+                     "v"(1 << ((unsigned)e / kChunk >> L.chunk_shift))
+                     : "memory");
+    }
+    count += g;
+}
+
+// The ramps of all entries are added to the file (u = t - b64).  Temporaries are v17..v29: the
+// compiler, which knows nothing of the profile block, must not need more registers than those below it, so it is asked
+// to keep few of them free and the others are put back as they were (four; six in the files whose wavefronts have the LDS for it).
+#define KVS_FLUSH_KVS_SCLOB_65 "v23", "v24", "v25", "v26", "v27", "v28", "v29"
+#define KVS_FLUSH_KVS_SCLOB_PLAIN "v21", "v22", KVS_FLUSH_KVS_SCLOB_65
+#define KVS_FLUSH_SCATTER(x, s)                                                             \
+    "v_subrev_u32 " x ", %[lo], " x "\n"                                                   \
+    "v_cmp_gt_u32 vcc, %[n256], " x "\n"                                                   \
+    "s_cbranch_vccz 8f\n"                                                                  \
+    "s_mov_b64 exec, vcc\n"                                                                \
+    "v_lshl_add_u32 v28, " x ", 2, %[base]\n"                                              \
+    "ds_add_u32 v28, v18 offset:%c[number]\n"                                              \
+    "ds_add_u32 v28, " s " offset:%c[sum]\n"                                               \
+    "s_mov_b64 exec, -1\n"                                                                 \
+    "8:\n"
+#define KVS_FLUSH_DPP(how)                                                                  \
+    "s_nop 0\n"                                                                            \
+    "v_add_u32_dpp v18, v18, v18 " how "\n"                                                \
+    "v_add_u32_dpp v19, v19, v19 " how "\n"
+template <int NR>
+__device__ __forceinline__ void group_flush(GroupLds<NR> &L, int count, int u, int &hi)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    const int chunks = __builtin_amdgcn_readfirstlane(L.chunks());
+    int c = min(((32 - __builtin_clz(chunks)) << L.chunk_shift) - 1, (NR - 1) / kChunkRows);
+    int number = 0, sum = 0, lo, nt, stt;
+    hi = max(hi, min(kChunk * (c + 1), WAVE * NR));
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) GroupLds<NR> *)&L;
+    constexpr int at_s = sizeof(L.e), at_number = 2 * sizeof(L.e), at_sum = at_number + sizeof(L.number);
+    static_assert(NR % 4 == 1 && kChunkRows == 4 && (kListCap<NR> == 256 || kListCap<NR> == 512), "");
+#define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                  \
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n" /* (nothing is on its way to the registers put aside) */ \
+                 "v_mbcnt_lo_u32_b32 v29, -1, 0\n"                                     \
+                 "v_mbcnt_hi_u32_b32 v29, -1, v29\n"                                   \
+                 "v_lshl_add_u32 v28, v29, 2, %[base]\n"                               \
+                 "ds_write_b32 v28, v17 offset:%c[kept]\n"                             \
+                 "ds_write_b32 v28, v18 offset:%c[kept]+256\n"                         \
+                 "ds_write_b32 v28, v19 offset:%c[kept]+512\n"                         \
+                 "ds_write_b32 v28, v20 offset:%c[kept]+768\n"                         \
+                 ".if %c[nr] >= 65\n"                                                  \
+                 "  ds_write_b32 v28, v21 offset:%c[kept]+1024\n"                      \
+                 "  ds_write_b32 v28, v22 offset:%c[kept]+1280\n"                      \
+                 ".endif\n"                                                            \
+                 "v_mov_b32 v17, v29\n"                                                \
+                 "1:\n"                                                                \
+                 "s_lshr_b32 %[lo], %[c], %c[shift]\n"                                 \
+                 "s_bitcmp1_b32 %[chunks], %[lo]\n"                                    \
+                 "s_cbranch_scc1 2f\n"                                                 \
+                 /* chunks without entries, from this one down to the next with some: the ramp of the last row, */ \
+                 /* 64 number less in every row before */ \
+                 "s_lshl_b32 %[lo], %[c], 2\n"                                         \
+                 "s_add_u32 %[lo], %[lo], 3\n"                                         \
+                 "s_min_u32 %[lo], %[lo], %c[nr]-1\n"                                  \
+                 "s_lshl_b32 %[lo], %[lo], 6\n"                                        \
+                 "s_sub_u32 %[lo], %[lo], %[u]\n"                                      \
+                 "v_add_u32 v28, %[lo], v17\n"                                     \
+                 "v_mul_i32_i24 v28, %[number_], v28\n"                                \
+                 "v_add_u32 v28, %[sum_], v28\n"                                       \
+                 "s_lshl_b32 %[nt], %[number_], 6\n"                                   \
+                 "s_getpc_b64 s[66:67]\n"                                              \
+                 "60:\n"                                                               \
+                 "s_sub_u32 %[lo], (%c[nr]-1)/4, %[c]\n" /* (descending) */             \
+                 "s_lshl_b32 %[lo], %[lo], 6\n"                                        \
+                 "s_add_u32 %[lo], %[lo], 61f-60b\n"                                   \
+                 "s_add_u32 s66, s66, %[lo]\n"                                         \
+                 "s_addc_u32 s67, s67, 0\n"                                            \
+                 "s_setpc_b64 s[66:67]\n"                                              \
+                 "61:\n"                                                               \
+                 ".set kvs_k, 4*((%c[nr]-1)/4)\n"                                      \
+                 ".rept (%c[nr]+3)/4\n"                                                \
+                 "7:\n"                                                                \
+                 "  .set kvs_r, 3\n"                                                   \
+                 "  .rept 4\n"                                                         \
+                 "    .if kvs_k+kvs_r < %c[nr]\n"                                      \
+                 "      v_add_u32 v[" KVS_PB "+kvs_k+kvs_r], v28, v[" KVS_PB "+kvs_k+kvs_r]\n" \
+                 "      v_subrev_u32 v28, %[nt], v28\n"                                \
+                 "    .endif\n"                                                        \
+                 "    .set kvs_r, kvs_r-1\n"                                           \
+                 "  .endr\n"                                                           \
+                 "  .if kvs_k > 0\n"           /* so is the chunk before it, perhaps */ \
+                 "    s_sub_u32 %[c], %[c], 1\n"                                       \
+                 "    s_bitcmp0_b32 %[chunks], (kvs_k-4)/4>>%c[shift]\n"               \
+                 "    s_cbranch_scc0 1b\n"                                             \
+                 "    .fill (64-(.-7b))/4, 4, 0xbf800000\n"                            \
+                 "    .org 7b+64\n"                                                    \
+                 "  .endif\n"                                                          \
+                 "  .set kvs_k, kvs_k-4\n"                                             \
+                 ".endr\n"                                                             \
+                 "s_branch 5f\n"                                                       \
+                 /* the histogram of a chunk */                                        \
+                 "2:\n"                                                                \
+                 "s_lshl_b32 %[lo], %[c], 8\n"                                         \
+                 "v_lshl_add_u32 v29, v17, 4, %[base]\n"                           \
+                 "ds_read_b128 v[20:23], v29\n"                                        \
+                 "ds_read_b128 v[24:27], v29 offset:%c[s]\n"                           \
+                 "v_mov_b32 v18, 0\n"                                                  \
+                 "v_mov_b32 v19, 0\n"                                                  \
+                 "ds_write_b64 v29, v[18:19] offset:%c[number]\n"                      \
+                 "ds_write_b64 v29, v[18:19] offset:%c[number]+8\n"                    \
+                 "ds_write_b64 v29, v[18:19] offset:%c[sum]\n"                         \
+                 "ds_write_b64 v29, v[18:19] offset:%c[sum]+8\n"                       \
+                 "s_waitcnt lgkmcnt(0)\n"                                              \
+                 "v_mov_b32 v18, 1\n"                                                  \
+                 KVS_FLUSH_SCATTER("v20", "v24")                                       \
+                 KVS_FLUSH_SCATTER("v21", "v25")                                       \
+                 KVS_FLUSH_SCATTER("v22", "v26")                                       \
+                 KVS_FLUSH_SCATTER("v23", "v27")                                       \
+                 ".if %c[cap] > 256\n"                                                 \
+                 "  s_cmp_le_u32 %[count], %[n256]\n"                                  \
+                 "  s_cbranch_scc1 3f\n"                                               \
+                 "  ds_read_b128 v[20:23], v29 offset:1024\n"                          \
+                 "  ds_read_b128 v[24:27], v29 offset:%c[s]+1024\n"                    \
+                 "  s_waitcnt lgkmcnt(0)\n"                                            \
+                 KVS_FLUSH_SCATTER("v20", "v24")                                       \
+                 KVS_FLUSH_SCATTER("v21", "v25")                                       \
+                 KVS_FLUSH_SCATTER("v22", "v26")                                       \
+                 KVS_FLUSH_SCATTER("v23", "v27")                                       \
+                 "  3:\n"                                                              \
+                 ".endif\n"                                                            \
+                 /* each lane: its four rounds from the last one down (v20..v23 numbers, v24..v27 sums) */ \
+                 "ds_read_b128 v[20:23], v29 offset:%c[number]\n"                      \
+                 "ds_read_b128 v[24:27], v29 offset:%c[sum]\n"                         \
+                 "s_waitcnt lgkmcnt(0)\n"                                              \
+                 "v_add_u32 v22, v22, v23\n"                                           \
+                 "v_add_u32 v26, v26, v27\n"                                           \
+                 "v_add_u32 v21, v21, v22\n"                                           \
+                 "v_add_u32 v25, v25, v26\n"                                           \
+                 "v_add_u32 v20, v20, v21\n"                                           \
+                 "v_add_u32 v24, v24, v25\n"                                           \
+                 /* sums over lanes 0 .. lane of the lanes' totals */                  \
+                 "s_nop 0\n"                                                           \
+                 "v_add_u32_dpp v18, v20, v20 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n" \
+                 "v_add_u32_dpp v19, v24, v24 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n" \
+                 KVS_FLUSH_DPP("row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0")    \
+                 KVS_FLUSH_DPP("row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0")    \
+                 KVS_FLUSH_DPP("row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0")    \
+                 KVS_FLUSH_DPP("row_bcast:15 row_mask:0xa bank_mask:0xf")              \
+                 KVS_FLUSH_DPP("row_bcast:31 row_mask:0xc bank_mask:0xf")              \
+                 "s_nop 1\n"                                                           \
+                 "v_readlane_b32 %[nt], v18, 63\n"                                     \
+                 "v_readlane_b32 %[st], v19, 63\n"                                     \
+                 "s_add_u32 %[number_], %[number_], %[nt]\n"                           \
+                 "s_add_u32 %[sum_], %[sum_], %[st]\n"                                 \
+                 "s_sub_u32 %[lo], %[lo], %[u]\n"                                      \
+                 /* v18, v19: number and sum of the entries behind the lane's rounds; v28: round - t */ \
+                 "v_sub_u32 v18, %[number_], v18\n"                                    \
+                 "v_sub_u32 v19, %[sum_], v19\n"                                       \
+                 "v_lshl_add_u32 v28, v17, 2, %[lo]\n"                             \
+                 "v_add_u32 v20, v18, v20\n"                                           \
+                 "v_mul_i32_i24 v20, v20, v28\n"                                       \
+                 "v_add3_u32 v20, v20, v19, v24\n"                                     \
+                 "v_add_u32 v28, 1, v28\n"                                             \
+                 "v_add_u32 v21, v18, v21\n"                                           \
+                 "v_mul_i32_i24 v21, v21, v28\n"                                       \
+                 "v_add3_u32 v21, v21, v19, v25\n"                                     \
+                 "v_add_u32 v28, 1, v28\n"                                             \
+                 "v_add_u32 v22, v18, v22\n"                                           \
+                 "v_mul_i32_i24 v22, v22, v28\n"                                       \
+                 "v_add3_u32 v22, v22, v19, v26\n"                                     \
+                 "v_add_u32 v28, 1, v28\n"                                             \
+                 "v_add_u32 v23, v18, v23\n"                                           \
+                 "v_mul_i32_i24 v23, v23, v28\n"                                       \
+                 "v_add3_u32 v23, v23, v19, v27\n"                                     \
+                 /* from four rounds per lane to rows of 64 */                          \
+                 "ds_write_b128 v29, v[20:23] offset:%c[number]\n"                     \
+                 "v_lshl_add_u32 v28, v17, 2, %[base]\n"                           \
+                 "ds_read_b32 v20, v28 offset:%c[number]\n"                            \
+                 "ds_read_b32 v21, v28 offset:%c[number]+256\n"                        \
+                 "ds_read_b32 v22, v28 offset:%c[number]+512\n"                        \
+                 "ds_read_b32 v23, v28 offset:%c[number]+768\n"                        \
+                 "s_getpc_b64 s[66:67]\n"                                              \
+                 "60:\n"                                                               \
+                 "s_lshl_b32 %[lo], %[c], 5\n"                                         \
+                 "s_add_u32 %[lo], %[lo], 61f-60b\n"                                   \
+                 "s_add_u32 s66, s66, %[lo]\n"                                         \
+                 "s_addc_u32 s67, s67, 0\n"                                            \
+                 "s_waitcnt lgkmcnt(0)\n"                                              \
+                 "s_setpc_b64 s[66:67]\n"                                              \
+                 "61:\n"                                                               \
+                 ".set kvs_k, 0\n"                                                     \
+                 ".rept (%c[nr]+3)/4\n"                                                \
+                 "7:\n"                                                                \
+                 "  v_add_u32 v[" KVS_PB "+kvs_k], v20, v[" KVS_PB "+kvs_k]\n"         \
+                 "  .if kvs_k+3 < %c[nr]\n"                                            \
+                 "    v_add_u32 v[" KVS_PB "+kvs_k+1], v21, v[" KVS_PB "+kvs_k+1]\n"   \
+                 "    v_add_u32 v[" KVS_PB "+kvs_k+2], v22, v[" KVS_PB "+kvs_k+2]\n"   \
+                 "    v_add_u32 v[" KVS_PB "+kvs_k+3], v23, v[" KVS_PB "+kvs_k+3]\n"   \
+                 "  .endif\n"                                                          \
+                 "  s_branch 5f\n" KVS_SLOT_PAD(32)                                    \
+                 "  .set kvs_k, kvs_k+4\n"                                             \
+                 ".endr\n"                                                             \
+                 "5:\n"                                                                \
+                 "s_sub_u32 %[c], %[c], 1\n"                                           \
+                 "s_cbranch_scc0 1b\n"                                                 \
+                 "v_lshl_add_u32 v28, v17, 2, %[base]\n"                               \
+                 "ds_read_b32 v17, v28 offset:%c[kept]\n"                              \
+                 "ds_read_b32 v18, v28 offset:%c[kept]+256\n"                          \
+                 "ds_read_b32 v19, v28 offset:%c[kept]+512\n"                          \
+                 "ds_read_b32 v20, v28 offset:%c[kept]+768\n"                          \
+                 ".if %c[nr] >= 65\n"                                                  \
+                 "  ds_read_b32 v21, v28 offset:%c[kept]+1024\n"                       \
+                 "  ds_read_b32 v22, v28 offset:%c[kept]+1280\n"                       \
+                 ".endif\n"                                                            \
+                 "s_waitcnt lgkmcnt(0)\n"                                              \
+                 : [c] "+&s"(c), [number_] "+&s"(number), [sum_] "+&s"(sum), [lo] "=&s"(lo), [nt] "=&s"(nt), [st] "=&s"(stt) \
+                 : [chunks] "s"(chunks), [u] "s"(u), [base] "s"(base), [count] "s"(count), [n256] "s"(256), \
+                   [nr] "n"(NR), [cap] "n"(kListCap<NR>), [s] "n"(at_s), [number] "n"(at_number), [sum] "n"(at_sum), [kept] "n"(at_sum + (int)sizeof(L.sum)), \
+                   [shift] "n"(L.chunk_shift)                                          \
+                 : "scc", "vcc", "memory", "s66", "s67", KVS_FLUSH_##SCLOB, CLOB)
+    KVS_FOR_NR(KVS_STMT);
+#undef KVS_STMT
 }
 
 // One int32 read through the scalar unit (the address is the same for the whole wavefront).
@@ -728,26 +1093,28 @@ __device__ __forceinline__ int scalar_read(const int32_t *base, int index)
     return v;
 }
 
-// Head of a saved timeline state: words 0, 1, 2 = b64, t, hi (every lane stores the same three values), then
+// Head of a saved timeline state: words 0, 1, 2, 3 = b64, t, hi, H (every lane stores the same four values), then
 // the lanes' partial sums of completion rounds as 64 int64 at byte 256.  The profile rows follow
 // at byte 768 (prof_store).  Written in assembly so that no temporary can land in the profile block.
 template <int NR>
-__device__ __forceinline__ void state_head_store(int32_t *snap, int b64, int t, int hi, long long tel_lane, int lane)
+__device__ __forceinline__ void state_head_store(int32_t *snap, int b64, int t, int hi, int H, long long tel_lane, int lane)
 {
-    int a, b, c, off;
+    int a, b, c, d, off;
 #define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                                        \
     asm volatile("v_mov_b32 %[a], %[b64]\n"                                                              \
                  "v_mov_b32 %[b], %[t]\n"                                                                \
                  "v_mov_b32 %[c], %[hi]\n"                                                               \
+                 "v_mov_b32 %[d], %[H]\n"                                                                \
                  "v_mov_b32 %[off], 0\n"                                                                 \
                  "global_store_dword %[off], %[a], %[base]\n"                                            \
                  "global_store_dword %[off], %[b], %[base] offset:4\n"                                   \
                  "global_store_dword %[off], %[c], %[base] offset:8\n"                                   \
+                 "global_store_dword %[off], %[d], %[base] offset:12\n"                                  \
                  "v_lshlrev_b32 %[off], 3, %[lane]\n"                                                    \
                  "global_store_dwordx2 %[off], %[tel], %[base] offset:256\n"                             \
                  "s_waitcnt vmcnt(0)\n"                                                                  \
-                 : [a] "=&v"(a), [b] "=&v"(b), [c] "=&v"(c), [off] "=&v"(off)                             \
-                 : [base] "s"(snap), [b64] "s"(b64), [t] "s"(t), [hi] "s"(hi), [tel] "v"(tel_lane), [lane] "v"(lane)   \
+                 : [a] "=&v"(a), [b] "=&v"(b), [c] "=&v"(c), [d] "=&v"(d), [off] "=&v"(off)               \
+                 : [base] "s"(snap), [b64] "s"(b64), [t] "s"(t), [hi] "s"(hi), [H] "s"(H), [tel] "v"(tel_lane), [lane] "v"(lane) \
                  : "memory", CLOB)
     KVS_FOR_NR(KVS_STMT);
 #undef KVS_STMT
@@ -888,9 +1255,9 @@ __device__ __forceinline__ int snapshot_word(const int32_t *snap, int index)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
-// The three words of a saved state's head in one load (the same path as snapshot_word).
+// The four words of a saved state's head in one load (the same path as snapshot_word).
 template <int NR>
-__device__ __forceinline__ void state_head_load(const int32_t *snap, int lane, int &b64, int &t, int &hi)
+__device__ __forceinline__ void state_head_load(const int32_t *snap, int lane, int &b64, int &t, int &hi, int &H)
 {
     int off, v;
 #define KVS_STMT(CLOB, ASC, DESC, SCLOB)                                                \
@@ -900,7 +1267,8 @@ __device__ __forceinline__ void state_head_load(const int32_t *snap, int lane, i
                  "v_readlane_b32 %[b64], %[v], 0\n"                             \
                  "v_readlane_b32 %[t], %[v], 1\n"                               \
                  "v_readlane_b32 %[hi], %[v], 2\n"                              \
-                 : [off] "=&v"(off), [v] "=&v"(v), [b64] "=&s"(b64), [t] "=&s"(t), [hi] "=&s"(hi) \
+                 "v_readlane_b32 %[H], %[v], 3\n"                               \
+                 : [off] "=&v"(off), [v] "=&v"(v), [b64] "=&s"(b64), [t] "=&s"(t), [hi] "=&s"(hi), [H] "=&s"(H) \
                  : [base] "s"(snap), [lane] "v"(lane)                           \
                  : "memory", CLOB)
     KVS_FOR_NR(KVS_STMT);
@@ -911,8 +1279,10 @@ __device__ __forceinline__ void state_head_load(const int32_t *snap, int lane, i
 // state every 64 positions, candidates with a resume block start from such a snapshot.
 // ONE (with RES): both in the same launch, handed over through p.snap_flags.
 template <int NR, int WPB, bool MOVES, bool RES, bool ONE>
-__global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
+__global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <= 33 ? 8 : 1))) void timeline_reg_kernel(SimParams p)
 {
+    constexpr bool GROUP = kGroup<NR, RES>, RUNS = GROUP && NR >= 65;
+    __shared__ __align__(16) GroupLds<NR> group_lds[WPB];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave_no = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
     if (wave_no >= p.C) return;
@@ -930,9 +1300,9 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         rd.mt = KVSCHED_MOVE_SWAP;
         rd.mi = rd.mj = 0;
         if (cand < p.C - 1) {  // the last timeline is the base order itself
-            rd.mt = p.src.moves[3 * (size_t)cand];
-            rd.mi = min(max(p.src.moves[3 * (size_t)cand + 1], 0), n_all - 1);
-            rd.mj = min(max(p.src.moves[3 * (size_t)cand + 2], 0), n_all - 1);
+            rd.mt = __builtin_amdgcn_readfirstlane(p.src.moves[3 * (size_t)cand]);
+            rd.mi = __builtin_amdgcn_readfirstlane(min(max(p.src.moves[3 * (size_t)cand + 1], 0), n_all - 1));
+            rd.mj = __builtin_amdgcn_readfirstlane(min(max(p.src.moves[3 * (size_t)cand + 2], 0), n_all - 1));
         }
     } else {
         rd.row = p.src.orders + (size_t)cand * (size_t)n_all;
@@ -1006,10 +1376,12 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
     }
     int b64 = 0;             // round of lane 0 of register 0: 64 * floor((t + 1) / 64)
     int hi = 0;              // 64 x the number of rows that may hold committed memory
+    // no round behind t holds more than M - H (-1: not known, or of no use)
+    int H = GROUP && n - k_first >= kGroupMin ? M : -1;
     int t = 0;               // start round of the previous request in the order
     long long tel_lane = 0;  // completion rounds summed per lane; added up over the lanes at the end
     if (state_in) {
-        state_head_load<NR>(state_in, lane, b64, t, hi);
+        state_head_load<NR>(state_in, lane, b64, t, hi, H);
         if (t < 0) {  // the shared prefix could not be scheduled
             if (lane == 0 && p.tel_out) p.tel_out[cand] = -1;
             return;
@@ -1020,19 +1392,34 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         prof_init<NR>();
     }
     const int vmin = -(1 << 30);  // below every bound (s - M > -2^30), and s - M may still be added to it
+    GroupLds<NR> &group = group_lds[WPB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
+    int grouped = 0;  // entries of its list
+    const int unit_shift = max(0, 7 - __builtin_clz(M));  // sizes in units of 2^this are below 2^25
 
-    // 64 positions of the order at a time: ids read coalesced, lengths gathered; the next
-    // block is fetched while the current one is being placed.  Within a block of cnt positions
-    // lane cnt - 1 holds the first and lane 0 the last (place_block counts its lane number down).
-    int rq_n = 0, sv_n = 1, ov_n = 1;
-    {
-        const int k = k_first + min(WAVE, n - k_first) - 1 - lane;
-        if (k >= k_first) {
-            rq_n = min(max(rd.at(k), 0), n_all - 1);
+    // 64 positions of the order at a time: ids read coalesced, lengths gathered.  While one block is being placed the lengths
+    // of the next are on their way, and in plain launches the ids of the one behind it too (a block whose requests
+    // start together takes less time than either; the other launches have no register to spare).  Within a block of cnt positions lane cnt - 1 holds the first and
+    // lane 0 the last (place_block counts its lane number down).
+    constexpr bool AHEAD = !RES && !MOVES;
+    int rq_n = 0, sv_n = 1, ov_n = 1, id_nn = 0;
+    auto id_at = [&](int first) __attribute__((always_inline)) -> int {
+        const int at = first + min(WAVE, n - first) - 1 - lane;
+        return at >= first ? rd.at(at) : 0;
+    };
+    auto fetch = [&](int first) __attribute__((always_inline)) {
+        rq_n = 0, sv_n = 1, ov_n = 1;
+        int l = lane;
+        asm volatile("" : "+v"(l));  // (as in group_clear)
+        const int at = first + min(WAVE, n - first) - 1 - l;
+        if (at >= first) {
+            rq_n = min(max(AHEAD ? id_nn : rd.at(at), 0), n_all - 1);
             sv_n = p.s[rq_n];
             ov_n = p.o[rq_n];
         }
-    }
+        if (AHEAD) id_nn = id_at(first + WAVE);
+    };
+    if (AHEAD) id_nn = id_at(k_first);
+    fetch(k_first);
     if (!RES && !MOVES && p.gate && scalar_read(p.gate, 0) > p.o_bound) return;  // (while the lengths are on their way)
     if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = n;  // (unless it stops before)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
@@ -1046,7 +1433,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
         if (takes_snapshots && k0 > (CONT ? k_first : 0) && (k0 >> 6) <= p.snap_blocks) {  // the state after k0 positions
             int32_t *snap = p.snapshots + (size_t)((k0 >> 6) - 1) * (size_t)p.snap_stride;
-            state_head_store<NR>(snap, b64, t, hi, tel_lane, lane);
+            state_head_store<NR>(snap, b64, t, hi, H, tel_lane, lane);
             prof_store<NR>(snap + KVS_STATE_HEAD_WORDS, lane);
             if (ONE) snapshot_publish<NR>(p.snap_flags, k0 >> 6, lane);
             if (LIMIT && p.t_limit && t > snapshot_word<NR>(p.t_limit, 0)) {  // nobody asked for what comes later
@@ -1056,24 +1443,18 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
             }
         }
         const int cnt = __builtin_amdgcn_readfirstlane(min(WAVE, n - k0));
+        const bool state_follows = takes_snapshots || (p.state_out && k0 + WAVE >= n);
         const int k = k0 + cnt - 1 - lane;  // this lane's position (none if k < k0)
         const int rq = rq_n, sv = sv_n, ov = ov_n;
-        rq_n = 0, sv_n = 1, ov_n = 1;
-        {
-            const int k1 = k0 + WAVE;
-            const int kn = k1 + min(WAVE, n - k1) - 1 - lane;
-            if (kn >= k1) {
-                rq_n = min(max(rd.at(kn), 0), n_all - 1);
-                sv_n = p.s[rq_n];
-                ov_n = p.o[rq_n];
-            }
-        }
+        fetch(k0 + WAVE);
         const bool bad = (sv < 1) | (ov < 1) | (ov > p.o_bound) | ((long long)sv + (long long)ov > (long long)M);
         if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // cannot be scheduled: report, do not loop forever
             if (lane == 0) {
-                if (p.tel_out) p.tel_out[cand] = -1;
+                long long none = -1;
+                asm volatile("" : "+v"(none));
+                if (p.tel_out) p.tel_out[cand] = none;
                 if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = 0;
-                if (p.state_out) p.state_out[1] = -1;  // poisons every timeline that resumes from it
+                if (p.state_out) p.state_out[1] = (int)none;  // poisons every timeline that resumes from it
             }
             if (ONE && takes_snapshots)  // nobody shall wait for the snapshots that will not come
                 snapshot_progress_set<NR>(p.snap_flags, ~(k0 >> 6), lane);
@@ -1081,14 +1462,49 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_reg_kernel(SimParams p)
         }
         // the up to 64 requests of this block, one after the other (place_block returns the lanes' start
         // rounds); cv: completion round of this lane's position
-        const int pv = place_block<NR>(cnt, M - sv, ov, lane, vmin, M, t, b64, hi);
-        const int cv = (k >= k0 ? ov : 0) + pv;
+        int rem = cnt, look = kRunMoved<NR>;
+        int pv = t;
+        for (;;) {
+            // (the one place where the list is emptied: this code is long, and the branches around it reach only so far)
+            if (GROUP && grouped > 0 && (H < 0 || grouped >= kListCap<NR> - WAVE || rem == 0)) {
+                group_flush<NR>(group, grouped, t - b64, hi);
+                grouped = 0;
+            }
+            if (rem == 0) break;
+            if (GROUP && H >= 0) {
+                int size = sv;
+                asm volatile("" : "+v"(size));
+                const int g = group_size(rem, size + ov, lane, unit_shift, H);
+                if (g >= kGroupMin || (g > 0 && grouped > 0)) {
+                    if (grouped == 0) group_clear<NR>(group, lane);
+                    group_append<NR>(group, grouped, rem, g, sv, ov + (t - b64), lane);
+                    if (lane < rem) pv = t;
+                    rem -= g;
+                    if (rem == 0 && !state_follows) break;
+                } else {
+                    look = WAVE - 1;  // (not again for requests that are looked at one by one anyway)
+                }
+                if (rem > 0) H = -1;
+                continue;
+            }
+            if constexpr (NR >= 65)  // (lets the compiler know that its branches have some 120 KB of hand-written code to cross)
+                asm volatile(".if 0\n.space 120000\n.endif\n");
+            int free_of_s = sv;
+            asm volatile("" : "+v"(free_of_s));  // (not to be kept in a register besides sv)
+            free_of_s = M - free_of_s;
+            place_block<NR, RUNS>(rem, look, free_of_s, ov, lane, vmin, M, pv, t, b64, hi);
+            if (RUNS && rem > 0) {  // a run of requests in one round
+                H = M - prof_max<NR>(t - b64, hi, lane);
+                look = kRunMoved<NR>;
+            }
+        }
+        const int cv = k >= k0 ? ov + pv : 0;
         tel_lane += cv;
         if (crow && k >= k0) crow[p.completion_by_position ? k : rq] = cv;
         if ((RES ? takes_snapshots : p.C == 1) && p.start0 && k >= k0) p.start0[k] = pv;  // (published with the next snapshot)
     }
     if (p.state_out) {
-        state_head_store<NR>(p.state_out, b64, t, hi, tel_lane, lane);
+        state_head_store<NR>(p.state_out, b64, t, hi, H, tel_lane, lane);
         prof_store<NR>(p.state_out + KVS_STATE_HEAD_WORDS, lane);
     }
     for (int d = 32; d > 0; d >>= 1) tel_lane += __shfl_down(tel_lane, d);

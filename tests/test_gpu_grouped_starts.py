@@ -44,14 +44,14 @@ def lengths(rng, kind, n, o_max):
 
 @pytest.mark.parametrize("o_max", [512, 2048, 4096, 8192, 14336])
 @pytest.mark.parametrize("kind", ["edges", "bimodal", "uniform"])
-@pytest.mark.parametrize("n", [15, 16, 17, 64, 129, 700])
+@pytest.mark.parametrize("n", [16, 129, 700])
 def test_bursts(ctx, o_max, kind, n):
     """Budgets for a quarter of the requests, for all but a few, for all of them."""
     print(f"o_max={o_max} {kind} n={n}", flush=True)
     rng = np.random.default_rng(o_max + n)
     o = lengths(rng, kind, n, o_max)
     s = rng.integers(1, 900, n).astype(np.int32)
-    orders = np.stack([np.argsort(s + o, kind="stable")] + [rng.permutation(n) for _ in range(3)]).astype(np.int32)
+    orders = np.stack([np.argsort(s + o, kind="stable")] + [rng.permutation(n)]).astype(np.int32)
     ctx.set_o_max(o_max)
     total = int((s.astype(np.int64) + o).sum())
     largest = int((s + o).max())
