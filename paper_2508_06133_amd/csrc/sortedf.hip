@@ -22,7 +22,9 @@ namespace {
 
 constexpr int kRun = 2048;          // keys one workgroup sorts (1024 threads, two each)
 constexpr int kFan = 8;             // runs merged by one pass
-constexpr int kNextMax = 256;       // batches among the first so many requests are found by one wavefront
+constexpr int kNextMax = 256;       // profile tests among the first so many requests are made by one wavefront
+constexpr int kNextLimit = 2048;    // batches whose extent is below this are found for all places at once
+constexpr int kNextWindow = 73728;  // places of which the chain holds what is known in LDS (two bytes each)
 constexpr int kSmallBuckets = 2048; // completion-time buckets of the profile test in LDS
 constexpr int kLargeBuckets = 4096;
 
@@ -101,10 +103,10 @@ __device__ __forceinline__ int wave_best(u64 &bS, int bk, int tie_rule)
     return k;
 }
 
-// One wavefront: size of the batch that starts at place a (0: none; -1: undecided, only with `limited`, when
-// its extent passes kNextMax).  Feasible are the k <= rem with W_k - W_0 <= M.  256 sizes a turn, their sums read together.
+// One wavefront: size of the batch that starts at place a (0: none).  Feasible are the k <= rem with W_k - W_0 <= M.  256 sizes
+// a turn, their sums read together.
 template <bool SMALL>
-__device__ __forceinline__ int wave_batch(const Sums &c, int a, int rem, u64 M, int tie_rule, bool limited)
+__device__ __forceinline__ int wave_batch(const Sums &c, int a, int rem, u64 M, int tie_rule)
 {
     const int lane = threadIdx.x & 63;
     const u64 W0 = c.W[a], G0 = c.G[a];
@@ -126,7 +128,6 @@ __device__ __forceinline__ int wave_batch(const Sums &c, int a, int rem, u64 M, 
             if (ok && better<SMALL>(g[q] - G0, k, bS, bk, tie_rule)) bS = g[q] - G0, bk = k;
         }
         if (__builtin_amdgcn_ballot_w64(ok) != ~0ull) break;  // (feasibility is monotone: the end lies in these 256)
-        if (limited && base + 256 < rem) return -1;
     }
     return wave_best<SMALL>(bS, bk, tie_rule);
 }
@@ -482,8 +483,8 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
         if (NW > 1 && all_w > M * (u64)(n / 32 + 1)) {
             // many small batches: all wavefronts find the batch that each place would start, then the chain is followed
             for (int a = wave; a < n; a += NW) {
-                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule, false)
-                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule, false);
+                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule)
+                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule);
                 if (lane == 0) next[a] = k;
             }
             __syncthreads();
@@ -499,8 +500,8 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
             }
         } else if (wave == 0) {  // one wavefront, no barriers
             for (int a = 0; a < n;) {
-                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule, false)
-                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule, false);
+                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule)
+                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule);
                 if (k < 1) break;
                 a += k;
                 if (lane == 0) ends[nb] = a;
@@ -513,8 +514,8 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
     } else if constexpr (NW == 1) {
         for (int a = 0; a < n;) {  // (n <= 64 < kNextMax: always decided)
             const int K = wave_profile_extent(c, a, n - a, (unsigned)M);
-            const int k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule, false)
-                                : wave_batch<false>(c, a, K, ~0ull, p.tie_rule, false);
+            const int k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule)
+                                : wave_batch<false>(c, a, K, ~0ull, p.tie_rule);
             if (k < 1) break;
             a += k;
             if (lane == 0) ends[nb] = a;
@@ -531,8 +532,8 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
                 const int K = wave_profile_extent(c, a, n - a, (unsigned)M);
                 int k = -1;
                 if (K >= 0)
-                    k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule, false)
-                              : wave_batch<false>(c, a, K, ~0ull, p.tie_rule, false);
+                    k = small ? wave_batch<true>(c, a, K, ~0ull, p.tie_rule)
+                              : wave_batch<false>(c, a, K, ~0ull, p.tie_rule);
                 if (lane == 0) sh[3] = k;
             }
             __syncthreads();
@@ -604,7 +605,7 @@ struct LargeArrays {
     u64 *W, *S, *G, *tot;  // tot: two sums per 4096 places
     int *s_pos, *o_pos;
     int *by_o, *rank_of, *rank_pos, *o_of_rank;  // (only when the (o, id) order is sorted too)
-    unsigned char *next;
+    unsigned short *next;
     unsigned *hist;
 };
 
@@ -782,7 +783,10 @@ __global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeAr
 
 __device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c) { return p.n < 65536 && c.G[p.n] < (1ull << 32); }
 
-// The batch every place would start, one wavefront each; 0 where it is not decided by kNextMax - 1 requests.
+// The batch every place would start, one wavefront each; 0 where that is left to the chain: extents of kNextLimit requests
+// or more (a place costs up to kNextLimit / 256 turns, all of them together less than the 3 us that the chain takes for a batch of
+// that many; such a place is recognised by one sum), and of kNextMax under the profile constraint.  With 256 for both, 100000 bimodal
+// requests in 197 batches of 510 were 554 us of chain.
 template <bool PROFILE>
 __global__ __launch_bounds__(256) void next_batch_kernel(SortedArgs p, LargeArrays m)
 {
@@ -794,20 +798,21 @@ __global__ __launch_bounds__(256) void next_batch_kernel(SortedArgs p, LargeArra
     int rem = p.n - a;
     u64 M = (u64)p.M;
     int k = 0;
+    // (a sum of peaks that holds so many requests or more is feasible: nothing to decide here)
+    constexpr int limit = PROFILE ? kNextMax : kNextLimit;
+    if (rem >= limit && c.W[a + limit] - c.W[a] <= M) rem = -1;
     if constexpr (PROFILE) {
-        // (a sum of peaks that holds kNextMax requests or more is feasible: nothing to decide here)
-        if (rem >= kNextMax && c.W[a + kNextMax] - c.W[a] <= M) rem = -1;
-        else rem = wave_profile_extent(c, a, rem, (unsigned)M);
+        if (rem > 0) rem = wave_profile_extent(c, a, rem, (unsigned)M);
         M = ~0ull;
     }
-    if (rem > 0) k = small ? wave_batch<true>(c, a, rem, M, p.tie_rule, true) : wave_batch<false>(c, a, rem, M, p.tie_rule, true);
-    if ((threadIdx.x & 63) == 0) m.next[a] = (unsigned char)(k > 0 && k < kNextMax ? k : 0);
+    if (rem > 0) k = small ? wave_batch<true>(c, a, rem, M, p.tie_rule) : wave_batch<false>(c, a, rem, M, p.tie_rule);
+    if ((threadIdx.x & 63) == 0) m.next[a] = (unsigned short)(k > 0 && k < limit ? k : 0);
 }
 
-// The chain of batches by one workgroup: the small ones are read off next[] (in LDS when there is room), the others
-// found by all threads.
+// The chain of batches by one workgroup: the small ones are read off next[], of which LDS holds the part the chain is in,
+// the others found by all threads.
 template <bool PROFILE>
-__global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeArrays m, int next_lds)
+__global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeArrays m, int window)
 {
     extern __shared__ u64 lds64[];
     __shared__ u64 red_S[16];
@@ -824,9 +829,14 @@ __global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeAr
     const bool small = small_numbers(p, c);
     const u64 M = (u64)p.M;
     unsigned *hist_lds = (unsigned *)lds64;
-    unsigned char *next_in = (unsigned char *)lds64 + (PROFILE ? 16 * kLargeBuckets : 0);
-    if (next_lds)
-        for (int i = tid; i < n; i += 1024) next_in[i] = m.next[i];
+    unsigned short *next_in = (unsigned short *)((char *)lds64 + (PROFILE ? 16 * kLargeBuckets : 0));
+    int first = 0;  // next_in holds the places [first, first + window), once there is use for them (80 KB take one workgroup 8 us)
+    bool loaded = PROFILE;
+    auto load_window = [&](int from) __attribute__((always_inline)) {  // eight places at a time (next[] is as long as that takes)
+        first = from & ~7;
+        for (int i = tid; i < (min(window, n - first) + 7) / 8; i += 1024) ((uint4 *)next_in)[i] = ((const uint4 *)(m.next + first))[i];
+    };
+    if (loaded) load_window(0);
     const bool by_rank = p.words[KVS_W_OMAX] > kLargeBuckets;  // (then the ranks are there)
     const int *rank_pos = by_rank ? m.rank_pos : nullptr;
     const int buckets = by_rank ? n : p.words[KVS_W_OMAX];
@@ -839,9 +849,13 @@ __global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeAr
     __syncthreads();
     int a = 0, nb = 0;
     while (a < n) {
-        if (tid < 64) {  // follow the chain as far as it is known
-            while (a < n) {
-                const int k = __builtin_amdgcn_readfirstlane(next_lds ? (int)next_in[a] : (int)m.next[a]);
+        if (loaded && a >= first + window) {
+            load_window(a);
+            __syncthreads();
+        }
+        if (loaded && tid < 64) {  // follow the chain as far as it is known
+            while (a < n && a < first + window) {
+                const int k = __builtin_amdgcn_readfirstlane((int)next_in[a - first]);
                 if (k < 1) break;
                 a += k;
                 if (tid == 0) p.batch_end_out[nb] = a;
@@ -849,14 +863,23 @@ __global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeAr
             }
             if (tid == 0) sh[0] = a, sh[1] = nb;
         }
-        __syncthreads();
-        a = sh[0];
-        nb = sh[1];
-        if (a >= n) break;
+        if (loaded) {
+            __syncthreads();
+            a = sh[0];
+            nb = sh[1];
+            if (a >= n) break;
+            if (a >= first + window) continue;
+        }
         int K;
         if constexpr (!PROFILE) {
             const u64 W0 = c.W[a];
             K = count_fitting(n - a, [&](int k) { return c.W[a + k] - W0; }, M);
+            if (!loaded && K < kNextLimit) {  // from here on batches may be known
+                load_window(a);
+                loaded = true;
+                __syncthreads();
+                continue;
+            }
         } else if (buckets <= kLargeBuckets) {
             Profile<true> prof{hist_lds, hist_lds + kLargeBuckets, hist_lds + 2 * kLargeBuckets, hist_lds + 3 * kLargeBuckets,
                                buckets, rank_pos, m.o_of_rank};
@@ -925,14 +948,14 @@ const u64 *launch_merges(const SortedArgs &p, const LargeArrays &m, hipStream_t 
 template <bool PROFILE>
 int launch_chain(const SortedArgs &p, const LargeArrays &m, hipStream_t st)
 {
-    constexpr int most = 150 * 1024;
+    constexpr int most = 2 * kNextWindow + 2048;
+    static_assert(most + 4096 <= 160 * 1024 && kNextWindow % 8 == 0, "fits the LDS");
     static const hipError_t granted = hipFuncSetAttribute((const void *)batch_chain_kernel<PROFILE>,
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (granted != hipSuccess) return KVSCHED_EHIP;
-    int bytes = PROFILE ? 16 * kLargeBuckets : 0;
-    const int next_lds = bytes + p.n <= most;
-    if (next_lds) bytes += p.n;
-    hipLaunchKernelGGL((batch_chain_kernel<PROFILE>), dim3(1), dim3(1024), bytes, st, p, m, next_lds);
+    const int window = PROFILE ? kNextWindow - 8 * kLargeBuckets : kNextWindow;
+    const int bytes = (PROFILE ? 16 * kLargeBuckets : 0) + 2 * (p.n < window ? (p.n + 7) & ~7 : window);
+    hipLaunchKernelGGL((batch_chain_kernel<PROFILE>), dim3(1), dim3(1024), bytes, st, p, m, window);
     return ok();
 }
 
@@ -955,8 +978,8 @@ size_t kvs_sortedF_scratch_bytes(int32_t n)
 {
     if (n <= kvs_sortedF_small_max(KVSCHED_FEAS_PROFILE)) return 256;
     const size_t np = padded(n);
-    // two key arrays and three sums; block sums; six arrays of ints, four of profile buckets; a byte each
-    return np * 5 * sizeof(u64) + (2 * sizeof(u64)) * (np / 4096 + 1) + np * 10 * sizeof(int) + np + 1024;
+    // two key arrays and three sums; block sums; six arrays of ints, four of profile buckets; two bytes each
+    return np * 5 * sizeof(u64) + (2 * sizeof(u64)) * (np / 4096 + 1) + np * 10 * sizeof(int) + 2 * np + 1024;
 }
 
 // Up to kvs_sortedF_small_max requests the kernel scans the lengths itself (status word and longest decode);
@@ -1015,7 +1038,7 @@ int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
     m.rank_pos = i + 4 * np;
     m.o_of_rank = i + 5 * np;
     m.hist = (unsigned *)(i + 6 * np);
-    m.next = (unsigned char *)(i + 10 * np);
+    m.next = (unsigned short *)(i + 10 * np);
     const dim3 runs((unsigned)((n + kRun - 1) / kRun)), sums((unsigned)((n + 4095) / 4096));
     // Ranks in the (o, id) order are needed by keys that do not fit and, under the profile constraint, when completion
     // times may be too many for buckets in LDS.

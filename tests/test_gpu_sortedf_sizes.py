@@ -71,6 +71,25 @@ def test_batches_around_one_wavefronts_reach(ctx, feas):
             _check(ctx, s, o, 4 * K, feas, K & 1)
 
 
+def test_extents_around_what_is_found_for_all_places(ctx):
+    n = 9000
+    for K in (2046, 2047, 2048, 2049, 2300):
+        s, o = np.full(n, 2, dtype=np.int32), np.full(n, 2, dtype=np.int32)
+        o[K // 2 :: K] = 900  # (batches shorter than their extents)
+        for M in (4 * K + 1000, 4 * K + 1002):
+            _check(ctx, s, o, M, 0, K & 1)
+
+
+@pytest.mark.parametrize("feas", [0, 1])
+def test_chains_longer_than_the_part_held_in_lds(ctx, feas):
+    rng = np.random.default_rng(feas)
+    for n in (40959, 40961, 73727, 73729, 150000):
+        s, o = rng.integers(1, 9, n).astype(np.int32), rng.integers(1, 9, n).astype(np.int32)
+        o[rng.integers(0, n, 20)] = 3000
+        _check(ctx, s, o, 60000, feas, n & 1)  # (a few extents that are not found for all places among many that are)
+        _check(ctx, s, o, 3100, feas, n & 1)
+
+
 def test_a_faulty_request_gives_no_batches(ctx):
     import torch
 
