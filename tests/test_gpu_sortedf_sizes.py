@@ -90,6 +90,27 @@ def test_chains_longer_than_the_part_held_in_lds(ctx, feas):
         _check(ctx, s, o, 3100, feas, n & 1)
 
 
+@pytest.mark.parametrize("kind,per,n", [("bimodal", 60, 20000), ("chat", 8, 9000), ("chat", 75, 2049), ("chat", 79, 30000),
+                                        ("tiny", 1, 5000), ("same", 1, 6000), ("mixed", 100, 12000), ("uniform", 300, 7000)])
+def test_profile_extents_found_for_all_places(ctx, kind, per, n):
+    """Completion times of one row, of 2048, 2049 and 4096; many requests that join where few leave; ties of both kinds."""
+    rng = np.random.default_rng(n)
+    if kind == "mixed":
+        s, o = _lengths(rng, "chat", n)
+        long = rng.random(n) < 0.3
+        s, o = np.where(long, rng.integers(2048, 8193, n), s), np.where(long, rng.integers(100, 501, n), o)
+    elif kind == "uniform":
+        s, o = rng.integers(1, 1000, n), rng.integers(1, 4097, n)
+    else:
+        s, o = _lengths(rng, kind, n)
+    s, o = s.astype(np.int32), o.astype(np.int32)
+    M = max(int((s.astype(np.int64) + o).max()), int(per * n))
+    for o_max in (int(o.max()), 2048, 2049, 4096, 4097):
+        if o_max >= o.max() and o_max + s[5] <= M:
+            o[5] = o_max
+            _check(ctx, s, o, M, 1, n & 1)
+
+
 def test_a_faulty_request_gives_no_batches(ctx):
     import torch
 
