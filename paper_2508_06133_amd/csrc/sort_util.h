@@ -78,70 +78,77 @@ __device__ __forceinline__ u64 lane_xor64(u64 v)
     return (u64)lane_xor<X>((unsigned)v) | ((u64)lane_xor<X>((unsigned)(v >> 32)) << 32);
 }
 
-// One step of the bitonic network over N = TPB * E keys: element i = 64 E wave + 64 e + lane is kept in k[e]
-// of its thread.  Partners STRIDE apart: in the same wavefront by lane moves, in the same thread, or (the
+// Steps of the bitonic network over N = TPB * E keys: element i = 64 E wave + 64 e + lane is kept in k[e]
+// of its thread.  Partners a stride apart: in the same wavefront by lane moves, in the same thread, or (the
 // larger strides) through LDS; two buffers alternate so that one barrier serves an exchange.
-template <int TPB, int E, int SIZE, int STRIDE>
-__device__ __forceinline__ void bitonic_step(u64 (&k)[E], u64 *lds, int &buf)
+__device__ __forceinline__ u64 keep_one(u64 mine, u64 other, bool least) { return (other < mine) == least ? other : mine; }
+
+// Strides below 64 (only those below `size`).
+template <int E, int STRIDE>
+__device__ __forceinline__ void bitonic_lanes(u64 (&k)[E], int i0, int size)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if constexpr (STRIDE >= 64 * E) {
-        u64 *b = lds + (buf ? TPB * E : 0);
-        buf ^= 1;
-        const int i0 = 64 * E * wave + lane;
-#pragma unroll
-        for (int e = 0; e < E; ++e) b[i0 + 64 * e] = k[e];
-        __syncthreads();
+    if (STRIDE < size) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int i = i0 + 64 * e;
-            const u64 o = b[i ^ STRIDE];
-            const bool keep_min = ((i & SIZE) == 0) == ((i & STRIDE) == 0);
-            k[e] = keep_min ? (o < k[e] ? o : k[e]) : (o < k[e] ? k[e] : o);
+            k[e] = keep_one(k[e], lane_xor64<STRIDE>(k[e]), ((i & size) == 0) == ((i & STRIDE) == 0));
         }
-    } else if constexpr (STRIDE >= 64) {
-        constexpr int S = STRIDE / 64;
+    }
+    if constexpr (STRIDE > 1) bitonic_lanes<E, STRIDE / 2>(k, i0, size);
+}
+
+// Strides 64 STEP inside a thread.
+template <int E, int STEP>
+__device__ __forceinline__ void bitonic_thread(u64 (&k)[E], int i0, int size)
+{
+    if constexpr (STEP >= 1) {
+        if (64 * STEP < size) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            if ((e & S) == 0) {
-                const bool asc = ((64 * E * wave + 64 * e) & SIZE) == 0;
-                const u64 x = k[e], y = k[e | S];
-                const bool sw = (x > y) == asc;
-                k[e] = sw ? y : x;
-                k[e | S] = sw ? x : y;
+            for (int e = 0; e < E; ++e) {
+                if ((e & STEP) == 0) {
+                    const bool asc = ((i0 + 64 * e) & size) == 0;
+                    const u64 x = k[e], y = k[e | STEP];
+                    const bool sw = (x > y) == asc;
+                    k[e] = sw ? y : x;
+                    k[e | STEP] = sw ? x : y;
+                }
             }
         }
-    } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int i = 64 * E * wave + 64 * e + lane;
-            const u64 o = lane_xor64<STRIDE>(k[e]);
-            const bool keep_min = ((i & SIZE) == 0) == ((i & STRIDE) == 0);
-            k[e] = keep_min ? (o < k[e] ? o : k[e]) : (o < k[e] ? k[e] : o);
-        }
+        bitonic_thread<E, STEP / 2>(k, i0, size);
     }
 }
 
-template <int TPB, int E, int SIZE, int STRIDE>
-__device__ __forceinline__ void bitonic_merge(u64 (&k)[E], u64 *lds, int &buf)
-{
-    bitonic_step<TPB, E, SIZE, STRIDE>(k, lds, buf);
-    if constexpr (STRIDE > 1) bitonic_merge<TPB, E, SIZE, STRIDE / 2>(k, lds, buf);
-}
-
-template <int TPB, int E, int SIZE = 2>
-__device__ __forceinline__ void bitonic_stages(u64 (&k)[E], u64 *lds, int &buf)
-{
-    bitonic_merge<TPB, E, SIZE, SIZE / 2>(k, lds, buf);
-    if constexpr (SIZE < TPB * E) bitonic_stages<TPB, E, SIZE * 2>(k, lds, buf);
-}
-
-// Ascending sort of TPB * E keys.  lds: 2 TPB E keys; the caller separates its own use of it by barriers.
+// Ascending sort of TPB * E keys.  lds: 2 TPB E keys; the caller separates its own use of it by barriers.  From 1024 threads on the
+// stages are a loop over one piece of code of some 1.5 KB: unrolled, a sort of 2048 keys is 11 KB of instructions that run once and
+// have to be fetched (Sorted-F order of 2000 requests 53 -> 47 us).  Few keys are quicker unrolled (61 requests 6.0 us, 6.9 as a loop).
 template <int TPB, int E>
 __device__ __forceinline__ void block_sort(u64 (&k)[E], u64 *lds)
 {
-    int buf = 0;
-    bitonic_stages<TPB, E>(k, lds, buf);
+    constexpr int N = TPB * E;
+    const int i0 = 64 * E * (threadIdx.x >> 6) + (threadIdx.x & 63);
+    u64 *b = lds, *other = lds + N;
+    constexpr int kStages = TPB < 1024 ? 16 : 1;  // (to unroll)
+#pragma unroll kStages
+    for (int size = 2; size <= N; size <<= 1) {
+        if constexpr (TPB > 64) {
+#pragma unroll kStages
+            for (int stride = size >> 1; stride >= 64 * E; stride >>= 1) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) b[i0 + 64 * e] = k[e];
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int i = i0 + 64 * e;
+                    k[e] = keep_one(k[e], b[i ^ stride], ((i & size) == 0) == ((i & stride) == 0));
+                }
+                u64 *const t = b;
+                b = other;
+                other = t;
+            }
+        }
+        bitonic_thread<E, E / 2>(k, i0, size);
+        bitonic_lanes<E, 32>(k, i0, size);
+    }
 }
 
 }  // namespace
