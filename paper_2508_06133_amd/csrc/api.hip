@@ -781,39 +781,41 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
                                          order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
     }
     if (capturing(st)) return KVSCHED_EHIP;
-    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, ga, gb, feas_mode, ctx->d_scratch, ctx->d_words, num_batches_out,
-                                     ctx->h_scan, next_seq(ctx), st);
+    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, kMaxExactTableBytes, ctx->d_scratch, order_out,
+                                     batch_end_out, F_out, ctx->d_words, num_batches_out, ctx->h_scan, next_seq(ctx), st);
     if (rc != KVSCHED_OK) return rc;
     rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;
-    int32_t r = ctx->h_scan[KVS_H_REMAIN], kmax = ctx->h_scan[KVS_H_KMAX], kmin = ctx->h_scan[KVS_H_KMIN];
-    if (r == 0) return KVSCHED_OK;  // malformed lengths: reported in the device status, no batches
-    if (r != n || kmax < 1 || kmax > n || kmin < 1 || kmin > kmax) return KVSCHED_EHIP;
-    if (const int lg = kvs_exact_dp_small_lg(n, kmax, (int32_t)M)) {  // fits after all, with the true bound
-        rc = ensure_tables(ctx, kvs_exact_dp_small_record_bytes(n, kmax, lg));
-        if (rc != KVSCHED_OK) return rc;
-        return kvs_launch_exact_dp_small(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, lg, ctx->d_scratch, ctx->d_tables,
-                                         order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
+    int32_t r = ctx->h_scan[KVS_H_REMAIN], kmax = ctx->h_scan[KVS_H_KMAX], kmin = ctx->h_scan[KVS_H_KMIN], nb = ctx->h_scan[KVS_H_BATCHES];
+    if (r == 0) return KVSCHED_OK;  // all batches are found (or malformed lengths: reported in the device status, no batches)
+    if (r < 0 || r > n || kmax < 1 || kmax > r || kmin < 1 || kmin > kmax || nb < 0 || nb > n - r) return KVSCHED_EHIP;
+    if (r == n) {  // nothing found yet
+        if (const int lg = kvs_exact_dp_small_lg(n, kmax, (int32_t)M)) {  // fits after all, with the true bound
+            rc = ensure_tables(ctx, kvs_exact_dp_small_record_bytes(n, kmax, lg));
+            if (rc != KVSCHED_OK) return rc;
+            return kvs_launch_exact_dp_small(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, lg, ctx->d_scratch, ctx->d_tables,
+                                             order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
+        }
+        if (kvs_exact_dp_counted_bytes(r, kmax, (int32_t)M) > kMaxExactTableBytes) return KVSCHED_ERANGE;
     }
-    if (kvs_exact_dp_counted_bytes(r, kmax, (int32_t)M) > kMaxExactTableBytes) return KVSCHED_ERANGE;
     rc = ensure_tables(ctx, kvs_exact_dp_table_bytes(r, kmax, (int32_t)M));
     if (rc != KVSCHED_OK) return rc;
-    int32_t nb = 0;
     while (r > 0) {  // r falls by at least one per batch
         rc = kvs_launch_exact_dp_batch(n, r, kmin, kmax, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, nb, ctx->d_scratch,
-                                       ctx->d_tables, batch_end_out, F_out, ctx->d_words, ctx->h_scan, next_seq(ctx), st);
+                                       ctx->d_tables, order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, ctx->h_scan,
+                                       next_seq(ctx), st);
         if (rc != KVSCHED_OK) return rc;
         rc = wait_for_scan(ctx, st);
         if (rc != KVSCHED_OK) return rc;
         const int32_t r_next = ctx->h_scan[KVS_H_REMAIN], k_next = ctx->h_scan[KVS_H_KMAX], min_next = ctx->h_scan[KVS_H_KMIN];
-        ++nb;
         if (r_next < 0 || r_next >= r || k_next > kmax || (r_next > 0 && (k_next < 1 || min_next < 1 || min_next > k_next)))
             return KVSCHED_EHIP;
         r = r_next;
         kmax = k_next;
         kmin = min_next;
+        nb = ctx->h_scan[KVS_H_BATCHES];
     }
-    return kvs_launch_exact_dp_emit(n, nb, ctx->d_scratch, order_out, num_batches_out, st);
+    return KVSCHED_OK;
 }
 
 int kvsched_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int32_t *o, int64_t M, int32_t feas_mode,

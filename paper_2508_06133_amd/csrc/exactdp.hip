@@ -25,6 +25,7 @@
 //   join k - 1 others only if load + o_j k <= M (j then has the least o, so this is the memory at
 //   its completion; the constraints at later completions are not touched by j).
 #include "phase1_util.h"
+#include "sort_util.h"
 
 namespace {
 
@@ -87,7 +88,7 @@ __device__ int prefix_fit(const int *list, int r, const int *s, const int *o, in
 }
 
 // out = the ids of in[0..n) in ascending (key, place), n <= DP_T: a thread counts the keys before its own.  (200 ids:
-// 1 us where the two passes of a radix sort take 11; 1024: 4 us.)
+// 11 us less than the two passes of a radix sort.  Up to a quarter of DP_T ids have four threads each: 3 us less again.)
 template <class KeyFn>
 __device__ void rank_sort(const int *in, int *out, int n, KeyFn key, HelperLds &L)
 {
@@ -100,14 +101,22 @@ __device__ void rank_sort(const int *in, int *out, int n, KeyFn key, HelperLds &
     __syncthreads();
     k[tid] = mine;
     __syncthreads();
+    // (parts: threads for each id, which share the quads; their counts are added up)
+    const int parts = 4 * n <= DP_T ? 4 : 1, at = tid / parts, part = tid % parts;
+    const int own = parts == 1 ? mine : k[at];
     int rank = 0;
-    for (int q = 0; 4 * q < n; ++q) {
+    for (int q = part; 4 * q < n; q += parts) {
         const keys4 v = reinterpret_cast<const keys4 *>(k)[q];
-        const int limit = 4 * q + 3 < tid && tid < n ? mine + 1 : mine;  // equal keys count when the whole quad lies before this one
+        const int limit = 4 * q + 3 < at && at < n ? own + 1 : own;  // equal keys count when the whole quad lies before this one
         rank += (v.x < limit) + (v.y < limit) + (v.z < limit) + (v.w < limit);
     }
-    for (int j = tid & ~3; j < tid; ++j) rank += k[j] == mine;
-    if (tid < n) out[rank] = id;
+    if (part == 0)
+        for (int j = at & ~3; j < at; ++j) rank += k[j] == own;
+    if (parts == 4) {
+        rank += __shfl_xor(rank, 1);
+        rank += __shfl_xor(rank, 2);
+    }
+    if (at < n && part == 0) out[rank] = parts == 1 ? id : in[at];
     __syncthreads();
 }
 
@@ -408,7 +417,7 @@ __device__ void walk_body(const unsigned long long *bits, const int *proc, int r
 
 // Members leave proc[], by_cost[] and left_by_o[] (or NULL; all keep their order); kept = the new count, kmax = the new
 // bound on the batch size.
-__device__ void compact_body(int *proc, int *by_cost, int *left_by_o, int *tmp, int r, int32_t nb, const int *batch_of, const int32_t *s,
+__device__ void compact_body(int *proc, int *by_cost, int *left_by_o, int *tmp, int r, const int *batch_of, const int32_t *s,
                              const int32_t *o, int32_t feas_mode, int32_t M, HelperLds &L, int &kept, int &kmax)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -421,7 +430,7 @@ __device__ void compact_body(int *proc, int *by_cost, int *left_by_o, int *tmp, 
             int id = 0, keep = 0;
             if (i < r) {
                 id = list[i];
-                keep = batch_of[id] != nb;
+                keep = batch_of[id] < 0;
             }
             int c = keep;
             for (int d = 1; d < 64; d <<= 1) {
@@ -535,8 +544,9 @@ __device__ void plan_body(const int *proc, int r, int kmin, int kmax, const int3
 }
 
 // What the host waits for between batches.
-__device__ __forceinline__ void tell_host(int32_t *words, int32_t *host, int32_t seq, int r, int kmax, int kmin)
+__device__ __forceinline__ void tell_host(int32_t *words, int32_t *host, int32_t seq, int r, int kmax, int kmin, int nb)
 {
+    host[KVS_H_BATCHES] = nb;
     words[KVS_W_REMAIN] = r;
     words[KVS_W_KMAX] = kmax;
     host[KVS_H_REMAIN] = r;
@@ -544,62 +554,6 @@ __device__ __forceinline__ void tell_host(int32_t *words, int32_t *host, int32_t
     host[KVS_H_KMIN] = kmin;
     __threadfence_system();
     __hip_atomic_store(&host[KVS_H_SEQ], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-__global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
-                                                          int32_t ga, int32_t gb, int32_t feas_mode, int *proc, int *by_o,
-                                                          int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o,
-                                                          int *cost, int4 *req, int2 *range, int32_t *words,
-                                                          int32_t *num_batches_out, int32_t *host, int32_t seq)
-{
-    __shared__ HelperLds L;
-    const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
-                                  num_batches_out, L);
-    if (kmax < 0) {
-        if (threadIdx.x == 0) tell_host(words, host, seq, 0, 0, 0);
-        return;
-    }
-    for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
-    __threadfence_block();
-    __syncthreads();
-    const int kmin = bounds_body(by_cost, left_by_o, kmax, s, o, M, ga, gb, feas_mode, cost, L);
-    plan_body(proc, n, kmin, kmax, s, o, M, ga, gb, feas_mode, cost, req, range);
-    if (threadIdx.x == 0) tell_host(words, host, seq, n, kmax, kmin);
-}
-
-// The end of a batch: its best state from the rows' (partial[k - kmin]), its members, the remaining requests and the
-// bounds of the next batch.
-__global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long long *partial, const unsigned long long *bits,
-                                                         int *proc, int *by_cost, int *left_by_o, int *tmp, int *batch_of,
-                                                         int *cost, int4 *req, int2 *range, int r, int kmin, int kmax, int Mp, const int32_t *s,
-                                                         const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                                                         int32_t feas_mode, int32_t tie_rule, int32_t done, int32_t nb,
-                                                         int32_t *batch_end_out, double *F_out, int32_t *words,
-                                                         int32_t *host, int32_t seq)
-{
-    __shared__ HelperLds L;
-    __shared__ int load[KVSCHED_EXACT_MAX_N];
-    long long bS = 0;
-    int bk = 0, bm = 0;
-    for (int k = kmin + threadIdx.x; k <= kmax; k += DP_T) {
-        const unsigned long long v = partial[k - kmin];
-        const unsigned S = (unsigned)(v >> 32);
-        if (S < DP_NONE && dp_better(S, k, (int)(unsigned)v, bS, bk, bm, tie_rule)) bS = S, bk = k, bm = (int)(unsigned)v;
-    }
-    for (int t = threadIdx.x; t < r; t += DP_T) load[t] = req[t].x;
-    reduce_best(tie_rule, L, bS, bk, bm);
-    if (threadIdx.x == 0) publish_batch(bS, bk, gb, done, nb, batch_end_out, F_out, words);
-    __syncthreads();
-    if (threadIdx.x < 64) walk_body(bits, proc, r, kmax, Mp, load, nb, batch_of, bk, bm);
-    __threadfence_block();
-    __syncthreads();
-    int kept, knext, next_min = 0;
-    compact_body(proc, by_cost, left_by_o, tmp, r, nb, batch_of, s, o, feas_mode, M, L, kept, knext);
-    if (kept > 0) {
-        next_min = bounds_body(by_cost, left_by_o, knext, s, o, M, ga, gb, feas_mode, cost, L);
-        plan_body(proc, kept, next_min, knext, s, o, M, ga, gb, feas_mode, cost, req, range);
-    }
-    if (threadIdx.x == 0) tell_host(words, host, seq, kept, knext, next_min);
 }
 
 // The (o, id)-sorted ids ordered by batch number (stable): each batch in nondecreasing o.
@@ -625,12 +579,531 @@ __device__ void emit_body(int32_t n, const int *by_o, int *buf0, int *buf1, cons
     if (tid == 0) *num_batches_out = nb;
 }
 
-__global__ __launch_bounds__(DP_T) void dp_emit_kernel(int32_t n, const int *by_o, int *buf0, int *buf1,
-                                                       const int *batch_of, int32_t nb, int32_t *order_out,
-                                                       int32_t *num_batches_out)
+// ---------------------------------------------------------------------------------------------
+// Batches decided without a table (sum of peaks, up to CORE_N requests left).
+//
+// For a price p >= 0 of load and a size k, the k least values of (value + p load) added up, less p M, are a lower bound on the
+// value of every set of k requests that fits ("load <= M" relaxed).  With a good set known, of metric F, a size is out of
+// the question when its bound exceeds F k^2.  A request is out when for every size left the bound with it forced in does,
+// and it is in when the bound without it does.  Bounds come from 16 prices at a time, a wavefront each (one sort gives
+// those of all sizes): a coarse grid, a finer one around the best price of the best size, and one over the best prices of the
+// sizes that are left.  The good set is the best prefix of any of these orders, bettered by one request more or
+// exchanged and by all choices from the CORE_WINDOW requests about the end of a prefix.  The requests that remain undecided are
+// tried in all combinations if they are CORE_MAX or fewer.  Of 300 backlogs of 200 chat requests and of others down to 30,
+// 8 to 20 % of the batches leave more than 8 undecided, 1 % more than 16, none of 645 more than 18 (without the choices
+// about the end: up to 26, and 1 % more than 20).
+//
+// The batch is the one the tables would give: all sets as good as the best are among those tried, and of those of one
+// size and load the tables keep the one whose latest request is the earliest, then whose second latest is, and so on
+// (a state's record is the last request that improved it): the least as a binary number, the earliest request its lowest bit.
+// Sums are exact; bounds are in double precision, and a request or size is given up only beyond one part in 10^9.
+//
+// Bound by the instructions of one workgroup and their chain (a batch of 200 requests left takes 43 us, of 40 or fewer 22:
+// three sorts of 0.6 to 1.3 us, 2.5 to 5 for what the prefixes of their orders give, 2 to 3 for better sets, the combinations 1 to 6).
+// 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.19 this way, and 0.1 for each batch that needs tables after
+// all (one of 200).
+constexpr int CORE_N = 256;
+constexpr int CORE_MAX = 20;
+constexpr int CORE_SIZES = 16;
+constexpr int CORE_WINDOW = 14;
+
+struct CoreLds {
+    int id[CORE_N], value[CORE_N], load[CORE_N];  // the remaining requests in processing order
+    unsigned char at[DP_NW][CORE_N];              // by wavefront: the request at a place of its order
+    double bound[DP_NW][CORE_N];                  // by wavefront: the bound for size place + 1
+    double price[DP_NW], step[DP_NW];
+    double best_bound[CORE_N], best_price[CORE_N], per_square[CORE_N];
+    unsigned char best_wave[CORE_N];
+    // of one wavefront's order, with as many places before the first (nothing) and behind the last (never fits)
+    long long sum_load[CORE_N], sum_value[CORE_N];
+    int2 sorted[64 + CORE_N + 64];  // (load, value)
+    unsigned char out[CORE_SIZES][CORE_N], in[CORE_SIZES][CORE_N];  // by size: is the request out of, or in, every set?
+    int size[CORE_SIZES], dead[CORE_SIZES];
+    unsigned long long best_of[CORE_SIZES];
+    int2 undecided[CORE_MAX];  // (load, value)
+    int over[CORE_MAX / 2 + 1][CORE_MAX / 2 + 2];  // [b][j]: b over j
+    int first[CORE_MAX / 2 + 2];                   // place of the first combination of j members of the lower half
+    int2 low[1 << CORE_MAX / 2];                   // (load, value)
+    unsigned short low_set[1 << CORE_MAX / 2];
+    unsigned long long best_key, total[2];
+    int fits, prefix, subset, most[2];
+    int sure[3];  // requests in every set: number, value, load
+    int wave_count[2][CORE_N / 64];
+};
+
+// Places of the threads whose flag is set, in thread order (tid < CORE_N); count receives how many.  (slot: two calls in a row differ.)
+__device__ __forceinline__ int place_of(bool flag, CoreLds &C, int slot, int &count)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned long long set = __builtin_amdgcn_ballot_w64(flag && tid < CORE_N);
+    if (lane == 0 && wave < CORE_N / 64) C.wave_count[slot][wave] = __popcll(set);
+    __syncthreads();
+    int before = 0;
+    count = 0;
+    for (int w = 0; w < CORE_N / 64; ++w) {
+        if (w < wave) before += C.wave_count[slot][w];
+        count += C.wave_count[slot][w];
+    }
+    return before + __popcll(set & ((1ull << lane) - 1ull));
+}
+
+// Metric and size of a set as a key that orders by the metric (to one part in 10^12).
+__device__ __forceinline__ unsigned long long set_key(double value, int k, double per_square)
+{
+    return ((unsigned long long)__double_as_longlong(value * per_square) & ~4095ull) | (unsigned)k;
+}
+
+// What does not change from batch to batch.
+__device__ __forceinline__ void core_start(CoreLds &C)
+{
+    const int tid = threadIdx.x;
+    if (tid < CORE_N) C.per_square[tid] = 1.0 / ((double)(tid + 1) * (double)(tid + 1));
+    if (tid < 64) {  // Pascal's triangle, a column a lane
+        int above = tid == 0;
+#pragma unroll 1
+        for (int b = 0; b <= CORE_MAX / 2; ++b) {
+            if (tid <= CORE_MAX / 2 + 1) C.over[b][tid] = above;
+            const int left = __shfl_up(above, 1);
+            above += tid == 0 ? 0 : left;
+        }
+    }
+}
+
+// One batch of the r <= CORE_N requests in C.id ..; its members are marked and leave the lists.  False: not decided, nothing has
+// changed.
+__device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_t tie_rule, int32_t n, int32_t nb, int *batch_of,
+                                           int32_t *batch_end_out, double *F_out, int32_t *words, CoreLds &C)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const double margin = 1e-9;
+    if (tid < 2) C.total[tid] = 0, C.most[tid] = 0;
+    if (tid < 3) C.sure[tid] = 0;
+    if (tid == 0) C.best_key = ~0ull, C.subset = INT_MAX;
+    if (tid < CORE_SIZES) C.dead[tid] = 0, C.best_of[tid] = ~0ull;
+    __syncthreads();
+    const int value = tid < r ? C.value[tid] : 0, load = tid < r ? C.load[tid] : 0;
+    if (tid < CORE_N) {
+        const u64 v = wave_scan_u64((u64)value), w = wave_scan_u64((u64)load);
+        const unsigned most_v = ~wave_min_u32(~(unsigned)value), most_w = ~wave_min_u32(~(unsigned)load);
+        if (lane == 63) {
+            atomicAdd(&C.total[0], v);
+            atomicAdd(&C.total[1], w);
+            atomicMax(&C.most[0], (int)most_v);
+            atomicMax(&C.most[1], (int)most_w);
+        }
+        C.best_bound[tid] = -1e300;
+        C.best_price[tid] = 0.0;
+    }
+    __syncthreads();
+    const double scale = (double)C.total[0] / (double)C.total[1];
+    const bool wide = ((C.total[0] | C.total[1]) >> 32) != 0;
+    double centre = scale, low = 0.0, ratio = 0.0, F = 0.0;
+    int sizes = 0, bk = 0;
+    if (r <= CORE_MAX / 2) {  // all combinations at once
+        sizes = r;
+        if (tid < r) C.size[tid] = tid + 1;
+    }
+#pragma unroll 1
+    for (int turn = 0; turn < 3 && sizes != r; ++turn) {
+        // the price of this wavefront (turn 0: none, a grid over four orders of magnitude, and load alone)
+        double price;
+        if (turn == 0) price = wave == 0 ? 0.0 : scale * (double)exp2f(0.7655f * (float)(wave - 10));
+        else if (turn == 1) price = centre * (double)exp2f(0.7655f * ((float)wave - 7.5f) / 7.5f);
+        else price = low * (double)exp2f((float)ratio * (float)wave / 15.0f);
+        const bool by_load = turn == 0 && wave == DP_NW - 1;
+        // sorted by their sums in steps of 2^-24 of the greatest
+        const double most = by_load ? (double)C.most[1] : (double)C.most[0] + price * (double)C.most[1];
+        const double step = most * (1.0 / 16776000.0), per_step = 16777000.0 / most;
+        unsigned key[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 64 * e + lane;
+            key[e] = ~0u;
+            if (i < r) {
+                const double c = by_load ? (double)C.load[i] : (double)C.value[i] + price * (double)C.load[i];
+                key[e] = ((unsigned)(c * per_step) << 8) | (unsigned)i;
+            }
+        }
+        if (r > 128) wave_sort<4>(key);
+        else wave_sort<2>(key);
+        if (lane == 0) C.price[wave] = price, C.step[wave] = step;
+        // prefixes of the order
+        u64 sum_w[4], sum_v[4], cw = 0, cv = 0, best = ~0ull;
+        int fits = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (64 * e < r) {
+                const int i = 64 * e + lane, who = (int)(key[e] & (CORE_N - 1));
+                const unsigned own_w = i < r ? C.load[who] : 0, own_v = i < r ? C.value[who] : 0;
+                double v, w;
+                if (wide) {
+                    sum_w[e] = wave_scan_u64((u64)own_w) + cw;
+                    sum_v[e] = wave_scan_u64((u64)own_v) + cv;
+                    w = (double)sum_w[e], v = (double)sum_v[e];
+                    cw = lane_value_u64(sum_w[e], 63);
+                    cv = lane_value_u64(sum_v[e], 63);
+                } else {
+                    const unsigned w32 = wave_scan_u32(own_w) + (unsigned)cw, v32 = wave_scan_u32(own_v) + (unsigned)cv;
+                    w = (double)w32, v = (double)v32;
+                    sum_w[e] = w32, sum_v[e] = v32;
+                    cw = (unsigned)__builtin_amdgcn_readlane((int)w32, 63);
+                    cv = (unsigned)__builtin_amdgcn_readlane((int)v32, 63);
+                }
+                const bool fit = i < r && sum_w[e] <= (u64)M;
+                fits += __popcll(__builtin_amdgcn_ballot_w64(fit));
+                if (i < r) {
+                    C.at[wave][i] = (unsigned char)who;
+                    C.bound[wave][i] = by_load ? -1e300 : v + price * (w - (double)M) - margin * (v + price * w) - step * (double)(i + 1);
+                    if (fit) best = min(best, set_key(v, i + 1, C.per_square[i]));
+                }
+            }
+        }
+        best = wave_min_u64(best);
+        if (lane == 0) {
+            atomicMin(&C.best_key, best);
+            if (by_load) C.fits = fits;
+        }
+        __syncthreads();
+        if (tid < r) {
+            double b = C.best_bound[tid];
+            int from = -1;
+#pragma unroll
+            for (int w = 0; w < DP_NW; ++w) {
+                const double x = C.bound[w][tid];
+                if (x > b) b = x, from = w;
+            }
+            if (from >= 0) {
+                C.best_bound[tid] = b;
+                C.best_price[tid] = C.price[from];
+            }
+            C.best_wave[tid] = (unsigned char)max(from, 0);
+        }
+        __syncthreads();
+        bk = (int)(C.best_key & 4095);
+        if (bk < 1 || bk > r) return false;  // cannot happen: a single request fits
+        if (turn == 0) {
+            centre = C.best_price[bk - 1];
+            if (!(centre > 0.0)) centre = scale * (double)exp2f(0.7655f * -10.0f);
+            __syncthreads();
+            continue;
+        }
+        // Better sets from the prefixes of one order about the longest that fits.  First of the order whose bound is the best:
+        // one request more, or one exchanged (a lane for each of the 64 requests behind, four wavefronts for the 64 before).  Then of
+        // one between the sizes' best: any choice from the CORE_WINDOW requests about its end.
+        if (wave == (turn == 1 ? C.best_wave[bk - 1] : DP_NW / 2)) {
+            C.sorted[lane] = make_int2(-1, -1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = 64 * e + lane;
+                if (i < r) {
+                    C.sum_load[i] = (long long)sum_w[e];
+                    C.sum_value[i] = (long long)sum_v[e];
+                    C.sorted[64 + i] = make_int2(C.load[key[e] & (CORE_N - 1)], C.value[key[e] & (CORE_N - 1)]);
+                }
+            }
+            C.sorted[64 + r + lane] = make_int2(INT_MAX, INT_MAX);
+            if (lane == 0) C.prefix = fits;
+        }
+        __syncthreads();
+        best = ~0ull;
+        if (turn == 1) {
+            const int k = C.prefix - 1 + (wave >> 2);
+            if (k >= 1 && k <= r) {
+                const long long room = (long long)M - C.sum_load[k - 1], sum = C.sum_value[k - 1];
+                const int2 more = C.sorted[64 + k + lane];
+                if (more.x <= room) best = set_key((double)(sum + more.y), k + 1, C.per_square[k]);  // (k < r here)
+                const int need = (int)min((long long)INT_MAX, (long long)more.x - room);
+                int dearest = -1;  // value of the dearest request that makes room
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int2 less = C.sorted[k + 16 * (wave & 3) + i];
+                    if (less.x >= need) dearest = max(dearest, less.y);
+                }
+                if (more.x != INT_MAX && dearest >= 0) best = min(best, set_key((double)(sum + more.y - dearest), k, C.per_square[k - 1]));
+            }
+        } else {
+            const int a = max(0, min(C.prefix - CORE_WINDOW / 2, r - CORE_WINDOW)), members = a + __popc(tid);
+            double w = a > 0 ? (double)C.sum_load[a - 1] : 0.0, v = a > 0 ? (double)C.sum_value[a - 1] : 0.0;
+#pragma unroll
+            for (int b = 0; b < 10; ++b) {
+                const int2 q = C.sorted[64 + a + CORE_WINDOW - 10 + b];
+                if ((tid >> b) & 1) w += (double)q.x, v += (double)q.y;
+            }
+            double few_w[1 << (CORE_WINDOW - 10)], few_v[1 << (CORE_WINDOW - 10)];
+            few_w[0] = w, few_v[0] = v;
+#pragma unroll
+            for (int g = 0; g < 1 << (CORE_WINDOW - 10); ++g) {
+                if (g > 0) {
+                    const int2 q = C.sorted[64 + a + __builtin_ctz(g)];
+                    few_w[g] = few_w[g & (g - 1)] + (double)q.x;
+                    few_v[g] = few_v[g & (g - 1)] + (double)q.y;
+                }
+                const int k = members + __builtin_popcount(g);
+                if (k > 0 && k <= r && few_w[g] <= (double)M) best = min(best, set_key(few_v[g], k, C.per_square[k - 1]));
+            }
+        }
+        best = wave_min_u64(best);
+        if (lane == 0) atomicMin(&C.best_key, best);
+        __syncthreads();
+        best = C.best_key;
+        bk = (int)(best & 4095);
+        F = __longlong_as_double((long long)(best | 4095)) * (1.0 + margin);
+        if (turn == 1) {
+            // sizes left, and the range of their prices
+            const bool left = tid < r && tid < C.fits && C.best_bound[tid] <= F * (double)(tid + 1) * (double)(tid + 1);
+            const int at = place_of(left, C, 0, sizes);
+            if (sizes > CORE_SIZES) return false;
+            if (left) C.size[at] = tid + 1;
+#pragma unroll 1
+            for (int i = tid; i < CORE_SIZES * CORE_N / 8; i += DP_T)
+                reinterpret_cast<u64 *>(&C.out[0][0])[i] = reinterpret_cast<u64 *>(&C.in[0][0])[i] = 0;
+            __syncthreads();
+            double lo = C.best_price[bk - 1], hi = lo;
+#pragma unroll 1
+            for (int a = 0; a < sizes; ++a) {
+                lo = fmin(lo, C.best_price[C.size[a] - 1]);
+                hi = fmax(hi, C.best_price[C.size[a] - 1]);
+            }
+            if (!(hi > 0.0)) hi = centre;
+            lo = fmax(lo, hi * 0.125);
+            low = lo * 0.93;
+            ratio = (double)__log2f((float)(hi * 1.08 / low));
+            continue;
+        }
+        // requests that are in or out, by this wavefront's price
+        double c[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (64 * e + lane < r) c[e] = (double)C.value[64 * e + lane] + price * (double)C.load[64 * e + lane];
+#pragma unroll 1
+        for (int a = 0; a < sizes; ++a) {
+            const int k = C.size[a];
+            const double limit = F * (double)k * (double)k, b = C.bound[wave][k - 1];
+            const int last = C.at[wave][k - 1];
+            const double c_last = (double)C.value[last] + price * (double)C.load[last];
+            double c_next = 1e300;
+            if (k < r) {
+                const int next = C.at[wave][k];
+                c_next = (double)C.value[next] + price * (double)C.load[next];
+            }
+            if (lane == 0 && b > limit) C.dead[a] = 1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = 64 * e + lane;
+                if (i < r) {
+                    if (b + fmax(0.0, c[e] - c_last - step) * (1.0 - margin) > limit) C.out[a][i] = 1;
+                    if (c[e] <= c_last && b + fmax(0.0, c_next - c[e] - step) * (1.0 - margin) > limit) C.in[a][i] = 1;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // ---- what is decided
+    bool out = sizes != r, in = out;
+#pragma unroll 1
+    for (int a = 0; a < sizes; ++a) {
+        if (C.dead[a]) continue;
+        if (tid < r) out &= C.out[a][tid] != 0, in &= C.in[a][tid] != 0;
+    }
+    const bool sure = tid < r && in && !out, open = tid < r && !out && !in;
+    if (tid < CORE_N) {
+        const int members = __popcll(__builtin_amdgcn_ballot_w64(sure));
+        const u64 v = wave_scan_u64(sure ? (u64)value : 0), w = wave_scan_u64(sure ? (u64)load : 0);
+        if (lane == 63) {
+            atomicAdd(&C.sure[0], members);
+            atomicAdd(&C.sure[1], (int)(unsigned)v);
+            atomicAdd(&C.sure[2], (int)(unsigned)w);
+        }
+    }
+    int undecided;
+    const int bit = place_of(open, C, 1, undecided);
+    if (undecided > CORE_MAX) return false;
+    if (open) C.undecided[bit] = make_int2(load, value);
+    const int hi_bits = min(undecided, CORE_MAX / 2), lo_bits = undecided - hi_bits;
+    if (tid <= CORE_MAX / 2 + 1) {
+        int first = 0;
+        for (int j = 0; j < tid; ++j) first += C.over[lo_bits][j];
+        C.first[tid] = first;
+    }
+    __syncthreads();
+    const int k0 = C.sure[0], v0 = C.sure[1], room = M - C.sure[2];
+    if (room < 0) return false;  // cannot happen
+    // ---- all combinations of the rest: a thread for each of its ten last requests', the others' from a table by number of
+    // members and in ascending order.
+    // Loads stop at room + 1 (M < 2^30, or the tables would be refused).
+    if (tid < (1 << lo_bits)) {
+        int w = 0, rank = 0, j = 0;
+        unsigned v = 0;
+#pragma unroll 1
+        for (int b = 0; b < lo_bits; ++b) {
+            if ((tid >> b) & 1) {
+                w = min(w + C.undecided[b].x, room + 1);
+                v += (unsigned)C.undecided[b].y;
+                rank += C.over[b][++j];
+            }
+        }
+        const int at = C.first[j] + rank;
+        C.low[at] = make_int2(w, (int)v);
+        C.low_set[at] = (unsigned short)tid;
+    }
+    int hi_load = 0;
+    unsigned hi_value = 0;
+    const int hi_members = __popc(tid);
+#pragma unroll
+    for (int b = 0; b < CORE_MAX / 2; ++b) {
+        const int2 q = C.undecided[min(lo_bits + b, CORE_MAX - 1)];
+        if (b < hi_bits && ((tid >> b) & 1)) {
+            hi_load = min(hi_load + q.x, room + 1);
+            hi_value += (unsigned)q.y;
+        }
+    }
+    __syncthreads();
+    // The best key (value, load) of each size; then, of the best size, the least combination that has it.
+    auto combinations = [&](int size, auto &&use) {
+        const int low_members = size - k0 - hi_members;
+        if (tid < (1 << hi_bits) && low_members >= 0 && low_members <= lo_bits) {
+            const int behind = C.first[low_members + 1];
+#pragma unroll 2
+            for (int x = C.first[low_members]; x < behind; ++x) {
+                const int w = hi_load + C.low[x].x;
+                if (w <= room) use(x, ((unsigned long long)(hi_value + (unsigned)C.low[x].y) << 32) | (unsigned)w);
+            }
+        }
+    };
+#pragma unroll 1
+    for (int a = 0; a < sizes; ++a) {
+        if (C.dead[a] || 64 * wave >= (1 << hi_bits)) continue;
+        unsigned long long best = ~0ull;
+        combinations(C.size[a], [&](int, unsigned long long key) { best = min(best, key); });
+        best = wave_min_u64(best);
+        if (lane == 0) atomicMin(&C.best_of[a], best);
+    }
+    __syncthreads();
+    long long S = 0;
+    int k = 0, m = 0;
+    unsigned long long least = 0;
+#pragma unroll 1
+    for (int a = 0; a < sizes; ++a) {
+        const unsigned long long key = C.best_of[a];
+        if (key == ~0ull) continue;
+        const long long total = (long long)v0 + (long long)(key >> 32);
+        if (dp_better(total, C.size[a], (int)(unsigned)key, S, k, m, tie_rule)) S = total, k = C.size[a], m = (int)(unsigned)key, least = key;
+    }
+    if (k < 1) return false;  // cannot happen
+    int own = INT_MAX;
+    combinations(k, [&](int x, unsigned long long key) {
+        if (key == least && own == INT_MAX) own = (tid << lo_bits) | C.low_set[x];
+    });
+    if (own != INT_MAX) atomicMin(&C.subset, own);
+    __syncthreads();
+    // ---- members
+    const bool member = sure || (open && ((C.subset >> bit) & 1));
+    const int id = tid < r ? C.id[tid] : 0;
+    int kept;
+    const int to = place_of(tid < r && !member, C, 0, kept);
+    if (r - kept != k) return false;  // cannot happen
+    if (member) batch_of[id] = nb;
+    if (tid == 0) publish_batch(S, k, gb, n - r, nb, batch_end_out, F_out, words);
+    if (tid < r && !member) C.id[to] = id, C.value[to] = value, C.load[to] = load;
+    r = kept;
+    __syncthreads();
+    return true;
+}
+
+// The batches from number nb on, as far as no table is needed: lists as left by the kernels below.  What remains is planned and reported to the
+// host; behind the last batch the order is written.
+__device__ __forceinline__ void go_on(int32_t n, int r, int kmax, int32_t nb, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+                      int32_t feas_mode, int32_t tie_rule, bool search, int *proc, int *by_o, int *by_cost, int *buf0, int *buf1,
+                      int *batch_of, int *left_by_o, int *cost, int4 *req, int2 *range, int32_t *order_out,
+                      int32_t *batch_end_out, double *F_out, int32_t *num_batches_out, int32_t *words, int32_t *host, int32_t seq,
+                      HelperLds &L, CoreLds &C)
+{
+    const int tid = threadIdx.x, before = r;
+    if (search && feas_mode == 0 && r > 0 && r <= CORE_N) {
+        if (tid < r) {
+            const int id = proc[tid], sv = s[id], ov = o[id];
+            C.id[tid] = id;
+            C.value[tid] = ga * sv + gb * ov;
+            C.load[tid] = sv + ov;
+        }
+        core_start(C);
+        __syncthreads();
+        while (r > 0 && core_batch(r, M, gb, tie_rule, n, nb, batch_of, batch_end_out, F_out, words, C)) ++nb;
+        __threadfence_block();
+        __syncthreads();
+    }
+    int kmin = 0;
+    if (r == 0) {
+        kmax = 0;
+        emit_body(n, by_o, buf0, buf1, batch_of, nb, order_out, num_batches_out, L);
+    } else {
+        if (r < before) compact_body(proc, by_cost, left_by_o, buf0, before, batch_of, s, o, feas_mode, M, L, r, kmax);
+        kmin = bounds_body(by_cost, left_by_o, kmax, s, o, M, ga, gb, feas_mode, cost, L);
+        plan_body(proc, r, kmin, kmax, s, o, M, ga, gb, feas_mode, cost, req, range);
+    }
+    __syncthreads();
+    if (tid == 0) tell_host(words, host, seq, r, kmax, kmin, nb);
+}
+
+__host__ __device__ __forceinline__ size_t counted_bytes(int32_t r, int32_t kmax, int32_t M)
+{
+    const size_t loads = ((size_t)M + 256) & ~(size_t)255;
+    return 2 * (size_t)(kmax + 1) * loads * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (loads / 8) + 6400;
+}
+
+__global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
+                                                          int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int *proc, int *by_o,
+                                                          int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o,
+                                                          int *cost, int4 *req, int2 *range, size_t most_bytes, int32_t *order_out,
+                                                          int32_t *batch_end_out, double *F_out, int32_t *words,
+                                                          int32_t *num_batches_out, int32_t *host, int32_t seq)
 {
     __shared__ HelperLds L;
-    emit_body(n, by_o, buf0, buf1, batch_of, nb, order_out, num_batches_out, L);
+    __shared__ CoreLds C;
+    const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
+                                  num_batches_out, L);
+    if (kmax < 0) {
+        if (threadIdx.x == 0) tell_host(words, host, seq, 0, 0, 0, 0);
+        return;
+    }
+    for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
+    __threadfence_block();
+    __syncthreads();
+    // (sizes that are refused are refused whether or not a table would have been needed)
+    go_on(n, n, kmax, 0, s, o, M, ga, gb, feas_mode, tie_rule, counted_bytes(n, kmax, M) <= most_bytes, proc, by_o, by_cost, buf0, buf1,
+          batch_of, left_by_o, cost, req, range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, C);
+}
+
+// The end of a batch: its best state from the rows' (partial[k - kmin]), its members, and how it goes on.
+__global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long long *partial, const unsigned long long *bits,
+                                                         int *proc, int *by_o, int *by_cost, int *left_by_o, int *buf0, int *buf1, int *batch_of,
+                                                         int *cost, int4 *req, int2 *range, int32_t n, int r, int kmin, int kmax, int Mp, const int32_t *s,
+                                                         const int32_t *o, int32_t M, int32_t ga, int32_t gb,
+                                                         int32_t feas_mode, int32_t tie_rule, int32_t nb, int32_t *order_out,
+                                                         int32_t *batch_end_out, double *F_out, int32_t *num_batches_out, int32_t *words,
+                                                         int32_t *host, int32_t seq)
+{
+    __shared__ HelperLds L;
+    __shared__ CoreLds C;
+    __shared__ int load[KVSCHED_EXACT_MAX_N];
+    long long bS = 0;
+    int bk = 0, bm = 0;
+    for (int k = kmin + threadIdx.x; k <= kmax; k += DP_T) {
+        const unsigned long long v = partial[k - kmin];
+        const unsigned S = (unsigned)(v >> 32);
+        if (S < DP_NONE && dp_better(S, k, (int)(unsigned)v, bS, bk, bm, tie_rule)) bS = S, bk = k, bm = (int)(unsigned)v;
+    }
+    for (int t = threadIdx.x; t < r; t += DP_T) load[t] = req[t].x;
+    reduce_best(tie_rule, L, bS, bk, bm);
+    if (threadIdx.x == 0) publish_batch(bS, bk, gb, n - r, nb, batch_end_out, F_out, words);
+    __syncthreads();
+    if (threadIdx.x < 64) walk_body(bits, proc, r, kmax, Mp, load, nb, batch_of, bk, bm);
+    __threadfence_block();
+    __syncthreads();
+    int kept, knext;
+    compact_body(proc, by_cost, left_by_o, buf0, r, batch_of, s, o, feas_mode, M, L, kept, knext);
+    go_on(n, kept, knext, nb + 1, s, o, M, ga, gb, feas_mode, tie_rule, true, proc, by_o, by_cost, buf0, buf1, batch_of, left_by_o, cost, req,
+          range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, C);
 }
 
 // The whole Phase 1 in one workgroup when both tables fit in LDS (the settings Algorithm 2 is meant
@@ -710,7 +1183,7 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
         __threadfence_block();
         __syncthreads();
         int kept, knext;
-        compact_body(proc, by_cost, nullptr, buf0, r, nb, batch_of, s, o, feas_mode, M, L, kept, knext);
+        compact_body(proc, by_cost, nullptr, buf0, r, batch_of, s, o, feas_mode, M, L, kept, knext);
         if (kept >= r) break;  // cannot happen: a batch has at least one member; never spin
         r = kept;
         kmax = knext;
@@ -757,28 +1230,26 @@ size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M)
 // What the limit on the tables is compared with: two tables and the records with the loads counted in 256s, and 6400
 // bytes.  (Fixed, so that the sizes that are accepted do not move with the kernels' own rows and working memory: the
 // allocation may exceed it by the loads that fill a row of DP_STEP_M.)
-size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M)
-{
-    const size_t loads = ((size_t)M + 256) & ~(size_t)255;
-    return 2 * (size_t)(kmax + 1) * loads * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (loads / 8) + 6400;
-}
+size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M) { return counted_bytes(r, kmax, M); }
 
+// (most_bytes: what counted bytes are compared with)
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                                int32_t feas_mode, void *lists, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
+                                int32_t feas_mode, int32_t tie_rule, size_t most_bytes, void *lists, int32_t *order_out,
+                                int32_t *batch_end_out, double *F_out, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
                                 int32_t seq, hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, l.proc, l.by_o,
-                       l.by_cost, l.buf0, l.buf1, l.batch_of, l.left_by_o, l.cost, l.req, l.range, d_words,
-                       num_batches_out, host, seq);
+    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, l.proc, l.by_o,
+                       l.by_cost, l.buf0, l.buf1, l.batch_of, l.left_by_o, l.cost, l.req, l.range, most_bytes, order_out, batch_end_out,
+                       F_out, d_words, num_batches_out, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
 // One batch over the r remaining requests: tables, records, best state, members, compaction.
 int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
                               int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
-                              void *lists, void *tables, int32_t *batch_end_out, double *F_out, int32_t *d_words,
-                              int32_t *host, int32_t seq, hipStream_t st)
+                              void *lists, void *tables, int32_t *order_out, int32_t *batch_end_out, double *F_out,
+                              int32_t *num_batches_out, int32_t *d_words, int32_t *host, int32_t seq, hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
     const int Mp = dp_row(M);
@@ -807,9 +1278,9 @@ int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, 
     unsigned long long *partial = bits + (size_t)r * per_t;
     hipLaunchKernelGGL(dp_argmin_rows_kernel, dim3((unsigned)(kmax - kmin + 1)), dim3(DP_T), 0, st, dp[at], kmin, Mp,
                        plan, partial);
-    hipLaunchKernelGGL(dp_finish_kernel, dim3(1), dim3(DP_T), 0, st, partial, bits, l.proc, l.by_cost, l.left_by_o, l.buf0,
-                       l.batch_of, l.cost, l.req, l.range, r, kmin, kmax, Mp, s, o, M, ga, gb, feas_mode, tie_rule, n - r, nb, batch_end_out,
-                       F_out, d_words, host, seq);
+    hipLaunchKernelGGL(dp_finish_kernel, dim3(1), dim3(DP_T), 0, st, partial, bits, l.proc, l.by_o, l.by_cost, l.left_by_o, l.buf0, l.buf1,
+                       l.batch_of, l.cost, l.req, l.range, n, r, kmin, kmax, Mp, s, o, M, ga, gb, feas_mode, tie_rule, nb, order_out,
+                       batch_end_out, F_out, num_batches_out, d_words, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
@@ -838,14 +1309,5 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
     hipLaunchKernelGGL(dp_small_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
                        l.by_cost, l.buf0, l.buf1, l.batch_of, (unsigned long long *)records, order_out, batch_end_out, F_out,
                        num_batches_out, d_words);
-    return launched() ? KVSCHED_OK : KVSCHED_EHIP;
-}
-
-int kvs_launch_exact_dp_emit(int32_t n, int32_t nb, void *lists, int32_t *order_out, int32_t *num_batches_out,
-                             hipStream_t st)
-{
-    const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(dp_emit_kernel, dim3(1), dim3(DP_T), 0, st, n, l.by_o, l.buf0, l.buf1, l.batch_of, nb, order_out,
-                       num_batches_out);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
 }

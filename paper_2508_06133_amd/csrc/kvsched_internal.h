@@ -39,6 +39,7 @@ enum {
     KVS_H_REMAIN = 4,
     KVS_H_KMAX = 5,
     KVS_H_KMIN = 6,
+    KVS_H_BATCHES = 7,
     KVS_H_COUNT = 16
 };
 
@@ -181,15 +182,17 @@ int kvs_launch_neighbor_finish(const int64_t *tel, const int32_t *rejoin, const 
 size_t kvs_exact_dp_list_bytes(int32_t n);
 size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M);
 size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M);
-// (host, seq: pinned words that receive the requests left and the bounds kmin..kmax on the next batch's size, then seq;
+// (host, seq: pinned words that receive the batches found, the requests left and the bounds kmin..kmax on the next batch's size, then seq;
 // ga, gb: the metric's numerator sums ga s_i + gb o_i -- 0, 1: the F-metric; else G with alpha = ga / gb)
+// The batches that need no table are found on the way; behind the last one the order is written.
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                                int32_t feas_mode, void *lists, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
+                                int32_t feas_mode, int32_t tie_rule, size_t most_bytes, void *lists, int32_t *order_out,
+                                int32_t *batch_end_out, double *F_out, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
                                 int32_t seq, hipStream_t st);
 int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
                               int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
-                              void *lists, void *tables, int32_t *batch_end_out, double *F_out, int32_t *d_words,
-                              int32_t *host, int32_t seq, hipStream_t st);
+                              void *lists, void *tables, int32_t *order_out, int32_t *batch_end_out, double *F_out,
+                              int32_t *num_batches_out, int32_t *d_words, int32_t *host, int32_t seq, hipStream_t st);
 int kvs_exact_dp_small_lg(int32_t n, int32_t kmax_bound, int32_t M);
 size_t kvs_exact_dp_small_record_bytes(int32_t n, int32_t kmax_bound, int lg);
 int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
@@ -197,9 +200,6 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
                               int32_t tie_rule, int lg, void *lists, void *records, int32_t *order_out,
                               int32_t *batch_end_out, double *F_out, int32_t *num_batches_out, int32_t *d_words,
                               hipStream_t st);
-int kvs_launch_exact_dp_emit(int32_t n, int32_t nb, void *lists, int32_t *order_out, int32_t *num_batches_out,
-                             hipStream_t st);
-
 // localswap.hip
 size_t kvs_local_swap_scratch_bytes(int32_t n);
 int kvs_launch_local_swap(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb, int32_t pad,

@@ -151,4 +151,72 @@ __device__ __forceinline__ void block_sort(u64 (&k)[E], u64 *lds)
     }
 }
 
+// The same network for 32-bit keys of one wavefront, element i = 64 e + lane in k[e]: three instructions an exchange (least,
+// greatest, choice by a mask that is a constant), partners 16 and 32 lanes apart by swaps of rows.
+template <int STRIDE>
+__device__ __forceinline__ unsigned exchanged(unsigned v, u64 least_in)
+{
+    unsigned a = v, b;
+    if constexpr (STRIDE == 16) {
+        const auto x = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = x[0], b = x[1];
+    } else if constexpr (STRIDE == 32) {
+        const auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = x[0], b = x[1];
+    } else if constexpr (STRIDE == 4) {  // mirrored in eights, then in fours
+        b = (unsigned)__builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+    } else {
+        b = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, STRIDE == 1 ? 0xB1 : STRIDE == 2 ? 0x4E : 0x128, 0xf, 0xf, true);
+    }
+    unsigned r;
+    asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(max(a, b)), "v"(min(a, b)), "s"(least_in));
+    return r;
+}
+
+// Lanes that keep the lesser of two elements STRIDE apart in the stage of `size`, row e.
+__device__ constexpr u64 least_lanes(int size, int stride, int e)
+{
+    u64 m = 0;
+    for (int lane = 0; lane < 64; ++lane)
+        if ((((64 * e + lane) & size) == 0) == ((lane & stride) == 0)) m |= 1ull << lane;
+    return m;
+}
+
+template <int E, int SIZE, int STRIDE>
+__device__ __forceinline__ void wave_sort_stage(unsigned (&k)[4])
+{
+    if constexpr (STRIDE >= 64) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if ((e & (STRIDE / 64)) == 0) {
+                const unsigned lo = min(k[e], k[e + STRIDE / 64]), hi = max(k[e], k[e + STRIDE / 64]);
+                const bool asc = ((64 * e) & SIZE) == 0;
+                k[e] = asc ? lo : hi;
+                k[e + STRIDE / 64] = asc ? hi : lo;
+            }
+        }
+    } else {
+        constexpr u64 even = least_lanes(SIZE, STRIDE, 0), odd = least_lanes(SIZE, STRIDE, 1), two = least_lanes(SIZE, STRIDE, 2),
+                      three = least_lanes(SIZE, STRIDE, 3);
+#pragma unroll
+        for (int e = 0; e < E; ++e) k[e] = exchanged<STRIDE>(k[e], e == 0 ? even : e == 1 ? odd : e == 2 ? two : three);
+    }
+    if constexpr (STRIDE > 1) wave_sort_stage<E, SIZE, STRIDE / 2>(k);
+    else if constexpr (SIZE < 64 * E) wave_sort_stage<E, SIZE * 2, SIZE>(k);
+}
+
+// Ascending sort of the first 64 E of 256 keys of a wavefront (those behind stay).
+template <int E>
+__device__ __forceinline__ void wave_sort(unsigned (&k)[4]) { wave_sort_stage<E, 2, 1>(k); }
+
+__device__ __forceinline__ u64 wave_min_u64(u64 v)
+{
+    v = min(v, lane_xor64<1>(v));
+    v = min(v, lane_xor64<2>(v));
+    v = min(v, (u64)(unsigned)__builtin_amdgcn_update_dpp((int)(unsigned)v, (int)(unsigned)v, 0x141, 0xf, 0xf, false) |
+                   ((u64)(unsigned)__builtin_amdgcn_update_dpp((int)(v >> 32), (int)(v >> 32), 0x141, 0xf, 0xf, false) << 32));
+    v = min(v, lane_xor64<8>(v));
+    return min(min(lane_value_u64(v, 0), lane_value_u64(v, 16)), min(lane_value_u64(v, 32), lane_value_u64(v, 48)));
+}
+
 }  // namespace
