@@ -203,8 +203,10 @@ __device__ __forceinline__ int lower_bound_u64(const u64 *a, int n, u64 key)
 //
 // plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
 // bkey: an idle array of >= m keys, an even number.
-// m <= 64 RMAX (two rows, where the paper's backlogs fit, keep the whole state in scalar and vector registers
-// without a test per row).
+// m <= 64 RMAX.  One and two rows, where the paper's backlogs fit, keep the whole state in scalar and vector registers
+// without a test per row: an exchange on one row takes 960 cycles, on two 1250 (a longest stream of 457 requests has 1580 of them;
+// 600 streams 2.75 -> 2.56 ms with a variant of its own for one row).  They are a chain of moves between lanes, scalars
+// and masks, ten cycles an instruction: four records at a time or masks in place of the vector minima are slower.
 template <int RMAX>
 __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 *list)
 {
@@ -585,7 +587,8 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         int wait_to = t + 1;  // when the loop stops at a request: a round before which it cannot start
         while (adm < q) {
             if (head + adm == planned && planned < wn)  // (the window's entries are never wrapped: head counts from the refresh)
-                planned += wn - planned <= 128 ? plan_batch<2>(L.wk, wn - planned, M, oth, L.list + planned)
+                planned += wn - planned <= 64 ? plan_batch<1>(L.wk, wn - planned, M, oth, L.list + planned)
+                           : wn - planned <= 128 ? plan_batch<2>(L.wk, wn - planned, M, oth, L.list + planned)
                                                : plan_batch<Lds::WCAP / 64>(L.wk, wn - planned, M, oth, L.list + planned);
             const u64 key = uni64(L.list[(head + adm) & QM]);
             const int oo = codec.decode(key), id = codec.id(key);
@@ -594,16 +597,21 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
                 wait_to = blocked_to;
                 break;
             }
+            // (The rounds last read are written from registers when the request is admitted, mostly all of them: a second
+            // reading was a third of an admission, 600 streams 2.56 -> 2.39 ms.)
             // round t + j rules out every start before t + min(excess, j): started later the request is
             // smaller at that round by as much, or no longer overlaps it
             int excess = 0;
-            for (int j0 = lane + 1; j0 <= oo; j0 += 256) {  // four reads at a time
-                int have[4];
+            int have[4];  // four reads at a time; those of the last ones are kept
+            for (int from = 0; from < oo; from += 256) {
+                const int j0 = from + lane + 1;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u) & HM];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (j0 + 64 * u <= oo) excess = max(excess, min(have[u] + sr + j0 + 64 * u - M, j0 + 64 * u));
+                for (int u = 0; u < 4; ++u) {
+                    have[u] += sr + j0 + 64 * u;
+                    if (j0 + 64 * u <= oo) excess = max(excess, min(have[u] - M, j0 + 64 * u));
+                }
             }
             if (__builtin_amdgcn_ballot_w64(excess > 0) != 0) {
                 wait_to = t + wave_max(excess);
@@ -611,13 +619,14 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
                 blocked_to = wait_to;
                 break;
             }
-            for (int j0 = lane + 1; j0 <= oo; j0 += 256) {
-                int have[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u) & HM];
+            for (int from = (oo - 1) & ~255; ; from -= 256) {
+                const int j0 = from + lane + 1;
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (j0 + 64 * u <= oo) L.ring[(t + j0 + 64 * u) & HM] = have[u] + sr + j0 + 64 * u;
+                    if (j0 + 64 * u <= oo) L.ring[(t + j0 + 64 * u) & HM] = have[u];
+                if (from == 0) break;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u - 256) & HM] + sr + j0 + 64 * u - 256;
             }
             if (lane == 0) cout[id] = t + oo;
             sum_c += t + oo;
