@@ -86,8 +86,16 @@ def _dev(t: torch.Tensor, dtype, what: str) -> int:
     return t.data_ptr()
 
 
+# (torch.cuda.current_stream() builds an object around the handle, 2.9 us of a call that takes 12 before it returns;
+# the two functions below it take 0.2.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 class Context:
