@@ -767,22 +767,22 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
     hipStream_t st = (hipStream_t)stream;
     rc = ensure_scratch(ctx, kvs_exact_dp_list_bytes(n));
     if (rc != KVSCHED_OK) return rc;
-    if (ctx->pad_outputs) {
-        hipLaunchKernelGGL(kvs_zero_batches, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, batch_end_out, F_out, n);
-        if (hipGetLastError() != hipSuccess) return KVSCHED_EHIP;
-    }
     // Small problems run in one workgroup with both tables in LDS; a batch holds at most M / 2
     // requests (each costs at least 2 of the budget), which may already show that they fit.
     const int32_t k_host = (int32_t)((M / 2 < n) ? M / 2 : n);
     if (const int lg = kvs_exact_dp_small_lg(n, k_host, (int32_t)M)) {
         rc = ensure_tables(ctx, kvs_exact_dp_small_record_bytes(n, k_host, lg));
         if (rc != KVSCHED_OK) return rc;
+        if (ctx->pad_outputs) {
+            hipLaunchKernelGGL(kvs_zero_batches, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, batch_end_out, F_out, n);
+            if (hipGetLastError() != hipSuccess) return KVSCHED_EHIP;
+        }
         return kvs_launch_exact_dp_small(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, lg, ctx->d_scratch, ctx->d_tables,
                                          order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, st);
     }
     if (capturing(st)) return KVSCHED_EHIP;
-    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, kMaxExactTableBytes, ctx->d_scratch, order_out,
-                                     batch_end_out, F_out, ctx->d_words, num_batches_out, ctx->h_scan, next_seq(ctx), st);
+    rc = kvs_launch_exact_dp_prepare(n, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, ctx->pad_outputs, kMaxExactTableBytes, ctx->d_scratch,
+                                     order_out, batch_end_out, F_out, ctx->d_words, num_batches_out, ctx->h_scan, next_seq(ctx), st);
     if (rc != KVSCHED_OK) return rc;
     rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;

@@ -122,10 +122,11 @@ __device__ void rank_sort(const int *in, int *out, int n, KeyFn key, HelperLds &
 
 // Validation, the three orders of the ids (emission order (o, id); processing order; ascending
 // cost), the first bound on the batch size.
-// Returns that bound, or -1 for malformed lengths (reported; no batches).
+// Returns that bound, or -1 for malformed lengths (reported; no batches).  costs: without it neither the order by cost nor
+// the bound are made (0 is returned).
 __device__ int prepare_body(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t feas_mode, int *proc,
                             int *by_o, int *by_cost, int *buf0, int *buf1, int *batch_of, int32_t *words,
-                            int32_t *num_batches_out, HelperLds &L)
+                            int32_t *num_batches_out, HelperLds &L, bool costs = true)
 {
     const int tid = threadIdx.x;
     int omax = 0, cmax = 0, bad = 0;
@@ -180,6 +181,11 @@ __device__ int prepare_body(int32_t n, const int32_t *s, const int32_t *o, int32
     else {
         for (int i = tid; i < n; i += DP_T) proc[i] = i;
         __syncthreads();
+    }
+    if (!costs) {
+        __threadfence_block();
+        __syncthreads();
+        return 0;
     }
     sort_by(by_cost, [s, o, feas_mode](int id) { return cost_of(s[id], o[id], feas_mode); }, cmax);
     __threadfence_block();
@@ -600,7 +606,7 @@ __device__ void emit_body(int32_t n, const int *by_o, int *buf0, int *buf1, cons
 //
 // Bound by the instructions of one workgroup and their chain (a batch of 200 requests left takes 43 us, of 40 or fewer 22:
 // three sorts of 0.6 to 1.3 us, 2.5 to 5 for what the prefixes of their orders give, 2 to 3 for better sets, the combinations 1 to 6).
-// 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.19 this way, and 0.1 for each batch that needs tables after
+// 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.18 this way, and 0.1 for each batch that needs tables after
 // all (one of 200).
 constexpr int CORE_N = 256;
 constexpr int CORE_MAX = 20;
@@ -922,7 +928,11 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
     const int hi_bits = min(undecided, CORE_MAX / 2), lo_bits = undecided - hi_bits;
     if (tid <= CORE_MAX / 2 + 1) {
         int first = 0;
-        for (int j = 0; j < tid; ++j) first += C.over[lo_bits][j];
+#pragma unroll
+        for (int j = 0; j <= CORE_MAX / 2; ++j) {
+            const int c = C.over[lo_bits][j];
+            first += j < tid ? c : 0;
+        }
         C.first[tid] = first;
     }
     __syncthreads();
@@ -1010,13 +1020,15 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
     return true;
 }
 
-// The batches from number nb on, as far as no table is needed: lists as left by the kernels below.  What remains is planned and reported to the
-// host; behind the last batch the order is written.
-__device__ __forceinline__ void go_on(int32_t n, int r, int kmax, int32_t nb, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                      int32_t feas_mode, int32_t tie_rule, bool search, int *proc, int *by_o, int *by_cost, int *buf0, int *buf1,
-                      int *batch_of, int *left_by_o, int *cost, int4 *req, int2 *range, int32_t *order_out,
-                      int32_t *batch_end_out, double *F_out, int32_t *num_batches_out, int32_t *words, int32_t *host, int32_t seq,
-                      HelperLds &L, CoreLds &C)
+// The batches from number nb on, as far as no table is needed: lists as left by the kernels below (listed: otherwise those
+// by cost and by o of what remains are still to be made).  What remains is planned and reported to the host; behind the
+// last batch the order is written.
+__device__ __forceinline__ void go_on(int32_t n, int r, int kmax, bool listed, int32_t nb, const int32_t *s, const int32_t *o, int32_t M,
+                                      int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, bool search, int *proc, int *by_o,
+                                      int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o, int *cost, int4 *req,
+                                      int2 *range, int32_t *order_out, int32_t *batch_end_out, double *F_out,
+                                      int32_t *num_batches_out, int32_t *words, int32_t *host, int32_t seq, HelperLds &L,
+                                      CoreLds &C)
 {
     const int tid = threadIdx.x, before = r;
     if (search && feas_mode == 0 && r > 0 && r <= CORE_N) {
@@ -1037,7 +1049,18 @@ __device__ __forceinline__ void go_on(int32_t n, int r, int kmax, int32_t nb, co
         kmax = 0;
         emit_body(n, by_o, buf0, buf1, batch_of, nb, order_out, num_batches_out, L);
     } else {
-        if (r < before) compact_body(proc, by_cost, left_by_o, buf0, before, batch_of, s, o, feas_mode, M, L, r, kmax);
+        if (!listed) {  // (of up to CORE_N requests, in which case none had left before this call)
+            for (int i = tid; i < before; i += DP_T) {
+                buf0[i] = i;
+                left_by_o[i] = by_o[i];
+            }
+            __threadfence_block();
+            __syncthreads();
+            rank_sort(buf0, by_cost, before, [s, o, feas_mode](int id) { return cost_of(s[id], o[id], feas_mode); }, L);
+            __threadfence_block();
+            __syncthreads();
+        }
+        if (!listed || r < before) compact_body(proc, by_cost, left_by_o, buf0, before, batch_of, s, o, feas_mode, M, L, r, kmax);
         kmin = bounds_body(by_cost, left_by_o, kmax, s, o, M, ga, gb, feas_mode, cost, L);
         plan_body(proc, r, kmin, kmax, s, o, M, ga, gb, feas_mode, cost, req, range);
     }
@@ -1051,27 +1074,34 @@ __host__ __device__ __forceinline__ size_t counted_bytes(int32_t r, int32_t kmax
     return 2 * (size_t)(kmax + 1) * loads * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (loads / 8) + 6400;
 }
 
+// (pad: zeros in all of batch_end_out and F_out first)
 __global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
-                                                          int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int *proc, int *by_o,
-                                                          int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o,
-                                                          int *cost, int4 *req, int2 *range, size_t most_bytes, int32_t *order_out,
-                                                          int32_t *batch_end_out, double *F_out, int32_t *words,
-                                                          int32_t *num_batches_out, int32_t *host, int32_t seq)
+                                                          int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t pad,
+                                                          int *proc, int *by_o, int *by_cost, int *buf0, int *buf1, int *batch_of,
+                                                          int *left_by_o, int *cost, int4 *req, int2 *range, size_t most_bytes,
+                                                          int32_t *order_out, int32_t *batch_end_out, double *F_out,
+                                                          int32_t *words, int32_t *num_batches_out, int32_t *host, int32_t seq)
 {
     __shared__ HelperLds L;
     __shared__ CoreLds C;
+    if (pad)
+        for (int i = threadIdx.x; i < n; i += DP_T) batch_end_out[i] = 0, F_out[i] = 0.0;
+    // Sizes that are refused are refused whether or not a table would have been needed: where no bound on the batch size
+    // leads to a refusal, it and the lists it takes are made when a table is needed (5 us of 200 requests).
+    const bool listed = feas_mode != 0 || n > CORE_N || counted_bytes(n, n, M) > most_bytes;
     const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
-                                  num_batches_out, L);
+                                  num_batches_out, L, listed);
     if (kmax < 0) {
         if (threadIdx.x == 0) tell_host(words, host, seq, 0, 0, 0, 0);
         return;
     }
-    for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
+    if (listed)
+        for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
     __threadfence_block();
     __syncthreads();
-    // (sizes that are refused are refused whether or not a table would have been needed)
-    go_on(n, n, kmax, 0, s, o, M, ga, gb, feas_mode, tie_rule, counted_bytes(n, kmax, M) <= most_bytes, proc, by_o, by_cost, buf0, buf1,
-          batch_of, left_by_o, cost, req, range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, C);
+    go_on(n, n, kmax, listed, 0, s, o, M, ga, gb, feas_mode, tie_rule, !listed || counted_bytes(n, kmax, M) <= most_bytes, proc, by_o,
+          by_cost, buf0, buf1, batch_of, left_by_o, cost, req, range, order_out, batch_end_out, F_out, num_batches_out, words, host,
+          seq, L, C);
 }
 
 // The end of a batch: its best state from the rows' (partial[k - kmin]), its members, and how it goes on.
@@ -1102,7 +1132,7 @@ __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long lon
     __syncthreads();
     int kept, knext;
     compact_body(proc, by_cost, left_by_o, buf0, r, batch_of, s, o, feas_mode, M, L, kept, knext);
-    go_on(n, kept, knext, nb + 1, s, o, M, ga, gb, feas_mode, tie_rule, true, proc, by_o, by_cost, buf0, buf1, batch_of, left_by_o, cost, req,
+    go_on(n, kept, knext, true, nb + 1, s, o, M, ga, gb, feas_mode, tie_rule, true, proc, by_o, by_cost, buf0, buf1, batch_of, left_by_o, cost, req,
           range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, C);
 }
 
@@ -1234,12 +1264,12 @@ size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M) { return c
 
 // (most_bytes: what counted bytes are compared with)
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
-                                int32_t feas_mode, int32_t tie_rule, size_t most_bytes, void *lists, int32_t *order_out,
-                                int32_t *batch_end_out, double *F_out, int32_t *d_words, int32_t *num_batches_out, int32_t *host,
-                                int32_t seq, hipStream_t st)
+                                int32_t feas_mode, int32_t tie_rule, int pad, size_t most_bytes, void *lists,
+                                int32_t *order_out, int32_t *batch_end_out, double *F_out, int32_t *d_words,
+                                int32_t *num_batches_out, int32_t *host, int32_t seq, hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, l.proc, l.by_o,
+    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, pad, l.proc, l.by_o,
                        l.by_cost, l.buf0, l.buf1, l.batch_of, l.left_by_o, l.cost, l.req, l.range, most_bytes, order_out, batch_end_out,
                        F_out, d_words, num_batches_out, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
