@@ -606,7 +606,7 @@ __device__ void emit_body(int32_t n, const int *by_o, int *buf0, int *buf1, cons
 //
 // Bound by the instructions of one workgroup and their chain (a batch of 200 requests left takes 43 us, of 40 or fewer 22:
 // three sorts of 0.6 to 1.3 us, 2.5 to 5 for what the prefixes of their orders give, 2 to 3 for better sets, the combinations 1 to 6).
-// 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.18 this way, and 0.1 for each batch that needs tables after
+// 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.17 this way, and 0.1 for each batch that needs tables after
 // all (one of 200).
 constexpr int CORE_N = 256;
 constexpr int CORE_MAX = 20;
@@ -617,9 +617,10 @@ struct CoreLds {
     int id[CORE_N], value[CORE_N], load[CORE_N];  // the remaining requests in processing order
     unsigned char at[DP_NW][CORE_N];              // by wavefront: the request at a place of its order
     double bound[DP_NW][CORE_N];                  // by wavefront: the bound for size place + 1
-    double price[DP_NW], step[DP_NW];
-    double best_bound[CORE_N], best_price[CORE_N], per_square[CORE_N];
-    unsigned char best_wave[CORE_N];
+    double price[3 * DP_NW];                       // by turn and wavefront
+    // by size: the best bound (a double of no sign compares as a whole number), in its last six bits the price it comes from
+    unsigned long long best_bound[CORE_N];
+    double per_square[CORE_N];
     // of one wavefront's order, with as many places before the first (nothing) and behind the last (never fits)
     long long sum_load[CORE_N], sum_value[CORE_N];
     int2 sorted[64 + CORE_N + 64];  // (load, value)
@@ -697,8 +698,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
             atomicMax(&C.most[0], (int)most_v);
             atomicMax(&C.most[1], (int)most_w);
         }
-        C.best_bound[tid] = -1e300;
-        C.best_price[tid] = 0.0;
+        C.best_bound[tid] = 0;
     }
     __syncthreads();
     const double scale = (double)C.total[0] / (double)C.total[1];
@@ -732,7 +732,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
         }
         if (r > 128) wave_sort<4>(key);
         else wave_sort<2>(key);
-        if (lane == 0) C.price[wave] = price, C.step[wave] = step;
+        if (lane == 0) C.price[turn * DP_NW + wave] = price;
         // prefixes of the order
         u64 sum_w[4], sum_v[4], cw = 0, cv = 0, best = ~0ull;
         int fits = 0;
@@ -759,7 +759,10 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
                 fits += __popcll(__builtin_amdgcn_ballot_w64(fit));
                 if (i < r) {
                     C.at[wave][i] = (unsigned char)who;
-                    C.bound[wave][i] = by_load ? -1e300 : v + price * (w - (double)M) - margin * (v + price * w) - step * (double)(i + 1);
+                    const double b = v + price * (w - (double)M) - margin * (v + price * w) - step * (double)(i + 1);
+                    C.bound[wave][i] = b;
+                    if (b > 0.0 && !by_load)
+                        atomicMax(&C.best_bound[i], ((u64)__double_as_longlong(b) & ~63ull) | (unsigned)(turn * DP_NW + wave));
                     if (fit) best = min(best, set_key(v, i + 1, C.per_square[i]));
                 }
             }
@@ -770,25 +773,11 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
             if (by_load) C.fits = fits;
         }
         __syncthreads();
-        if (tid < r) {
-            double b = C.best_bound[tid];
-            int from = -1;
-#pragma unroll
-            for (int w = 0; w < DP_NW; ++w) {
-                const double x = C.bound[w][tid];
-                if (x > b) b = x, from = w;
-            }
-            if (from >= 0) {
-                C.best_bound[tid] = b;
-                C.best_price[tid] = C.price[from];
-            }
-            C.best_wave[tid] = (unsigned char)max(from, 0);
-        }
-        __syncthreads();
         bk = (int)(C.best_key & 4095);
         if (bk < 1 || bk > r) return false;  // cannot happen: a single request fits
+        const int from = (int)(C.best_bound[bk - 1] & 63);
         if (turn == 0) {
-            centre = C.best_price[bk - 1];
+            centre = C.price[from];
             if (!(centre > 0.0)) centre = scale * (double)exp2f(0.7655f * -10.0f);
             __syncthreads();
             continue;
@@ -796,7 +785,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
         // Better sets from the prefixes of one order about the longest that fits.  First of the order whose bound is the best:
         // one request more, or one exchanged (a lane for each of the 64 requests behind, four wavefronts for the 64 before).  Then of
         // one between the sizes' best: any choice from the CORE_WINDOW requests about its end.
-        if (wave == (turn == 1 ? C.best_wave[bk - 1] : DP_NW / 2)) {
+        if (wave == (from >= DP_NW && turn == 1 ? from - DP_NW : DP_NW / 2)) {
             C.sorted[lane] = make_int2(-1, -1);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -856,7 +845,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
         F = __longlong_as_double((long long)(best | 4095)) * (1.0 + margin);
         if (turn == 1) {
             // sizes left, and the range of their prices
-            const bool left = tid < r && tid < C.fits && C.best_bound[tid] <= F * (double)(tid + 1) * (double)(tid + 1);
+            const bool left = tid < r && tid < C.fits && __longlong_as_double((long long)(C.best_bound[tid] & ~63ull)) <= F * (double)(tid + 1) * (double)(tid + 1);
             const int at = place_of(left, C, 0, sizes);
             if (sizes > CORE_SIZES) return false;
             if (left) C.size[at] = tid + 1;
@@ -864,11 +853,12 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
             for (int i = tid; i < CORE_SIZES * CORE_N / 8; i += DP_T)
                 reinterpret_cast<u64 *>(&C.out[0][0])[i] = reinterpret_cast<u64 *>(&C.in[0][0])[i] = 0;
             __syncthreads();
-            double lo = C.best_price[bk - 1], hi = lo;
+            double lo = C.price[C.best_bound[bk - 1] & 63], hi = lo;
 #pragma unroll 1
             for (int a = 0; a < sizes; ++a) {
-                lo = fmin(lo, C.best_price[C.size[a] - 1]);
-                hi = fmax(hi, C.best_price[C.size[a] - 1]);
+                const double p = C.price[C.best_bound[C.size[a] - 1] & 63];
+                lo = fmin(lo, p);
+                hi = fmax(hi, p);
             }
             if (!(hi > 0.0)) hi = centre;
             lo = fmax(lo, hi * 0.125);
