@@ -81,11 +81,12 @@ int read_words(kvsched_ctx *ctx, hipStream_t st)
 }
 
 // The timeline kernel, bracketed by the context's events when timing is on.
-int run_timelines(kvsched_ctx *ctx, const SimParams &p, int32_t H, hipStream_t st)
+int run_timelines(kvsched_ctx *ctx, const SimParams &p, int32_t H, hipStream_t st, bool short_rows = false, int32_t o_limit = INT32_MAX)
 {
     if (ctx->timing && hipEventRecord(ctx->ev0, st) != hipSuccess) return KVSCHED_EHIP;
     // profile in registers when the longest decode fits there, else the LDS ring
-    int rc = p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st) : kvs_launch_simulate(p, H, st);
+    int rc = short_rows ? kvs_launch_short_rows(p, o_limit, st)
+             : p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st) : kvs_launch_simulate(p, H, st);
     if (rc != KVSCHED_OK) return rc;
     if (ctx->timing) {
         if (hipEventRecord(ctx->ev1, st) != hipSuccess) return KVSCHED_EHIP;
@@ -641,8 +642,9 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
         ctx->resume_rows = C;
         ctx->resume_first = first;
     } else {
-        rc = run_timelines(ctx, p, H, st);
-        if (rc != KVSCHED_OK) return rc;
+        const bool short_rows = cp == 0 && kvs_short_rows(C, n);
+        rc = run_timelines(ctx, p, H, st, short_rows, o_limit);
+        if (rc != KVSCHED_OK || short_rows) return rc;  // (which checks the orders and writes by request id)
     }
     if (prefix_comp) {
         rc = kvs_launch_broadcast_prefix(prefix_comp, cp, C, n, completion_out, st);
