@@ -643,8 +643,12 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
         ctx->resume_first = first;
     } else {
         const bool short_rows = cp == 0 && kvs_short_rows(C, n);
+        if (cp == 0 && n <= WAVE_POSITIONS && o_bound <= KVS_REG_MAX_O) {
+            p.check_rows = 1;
+            p.completion_by_position = 0;
+        }
         rc = run_timelines(ctx, p, H, st, short_rows, o_limit);
-        if (rc != KVSCHED_OK || short_rows) return rc;  // (which checks the orders and writes by request id)
+        if (rc != KVSCHED_OK || short_rows || p.check_rows) return rc;  // (these check the orders and write by request id)
     }
     if (prefix_comp) {
         rc = kvs_launch_broadcast_prefix(prefix_comp, cp, C, n, completion_out, st);

@@ -97,6 +97,8 @@ struct SimParams {
     int32_t completion_by_position;  // 1: row entry k = completion of position k (a later pass permutes)
     int32_t *d_words;
     int32_t o_bound;          // lengths above this are reported, not simulated
+    // Register kernel, explicit rows of up to 64 positions placed in full: rows that are no permutations are reported
+    int32_t check_rows = 0;
     // Register kernel, explicit rows that are not resumed: the launch leaves everything as it is when *gate > o_bound
     const int32_t *gate = nullptr;
     // Register kernel only: simulate positions [k_begin, k_end) (k_end == 0: up to n), starting
