@@ -643,7 +643,7 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
         ctx->resume_first = first;
     } else {
         const bool short_rows = cp == 0 && kvs_short_rows(C, n);
-        if (cp == 0 && n <= WAVE_POSITIONS && o_bound <= KVS_REG_MAX_O) {
+        if (cp == 0 && n <= KVS_CHECKED_ROW && o_bound <= KVS_REG_MAX_O) {
             p.check_rows = 1;
             p.completion_by_position = 0;
         }

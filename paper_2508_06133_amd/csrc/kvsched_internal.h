@@ -85,6 +85,8 @@ struct OrderSource {
     const int32_t *moves;   // [K][3]; candidate K (one past the last move) is the base itself
 };
 
+constexpr int KVS_CHECKED_ROW = 1024;  // (a bit each has room in the LDS of the smallest file, and a word per lane of 32)
+
 struct SimParams {
     OrderSource src;
     int32_t C;  // number of timelines to run
@@ -97,7 +99,7 @@ struct SimParams {
     int32_t completion_by_position;  // 1: row entry k = completion of position k (a later pass permutes)
     int32_t *d_words;
     int32_t o_bound;          // lengths above this are reported, not simulated
-    // Register kernel, explicit rows of up to 64 positions placed in full: rows that are no permutations are reported
+    // Register kernel, explicit rows of up to KVS_CHECKED_ROW positions placed in full: rows that are no permutations are reported
     int32_t check_rows = 0;
     // Register kernel, explicit rows that are not resumed: the launch leaves everything as it is when *gate > o_bound
     const int32_t *gate = nullptr;

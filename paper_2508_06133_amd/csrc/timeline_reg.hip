@@ -1286,7 +1286,11 @@ template <int NR, int WPB, bool MOVES, bool RES, bool ONE>
 __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <= 33 ? 8 : 1))) void timeline_reg_kernel(SimParams p)
 {
     constexpr bool GROUP = kGroup<NR, RES>, RUNS = GROUP && NR >= 65;
-    __shared__ __align__(16) GroupLds<NR> group_lds[WPB];
+    union WaveLds {
+        GroupLds<NR> group;
+        unsigned met[RES || MOVES ? 1 : KVS_CHECKED_ROW / 32];
+    };
+    __shared__ __align__(16) WaveLds wave_lds[WPB];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave_no = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
     if (wave_no >= p.C) return;
@@ -1396,7 +1400,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         prof_init<NR>();
     }
     const int vmin = -(1 << 30);  // below every bound (s - M > -2^30), and s - M may still be added to it
-    GroupLds<NR> &group = group_lds[WPB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
+    GroupLds<NR> &group = wave_lds[WPB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0].group;
     int grouped = 0;  // entries of its list
     const int unit_shift = max(0, 7 - __builtin_clz(M));  // sizes in units of 2^this are below 2^25
 
@@ -1424,17 +1428,27 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
     };
     if (AHEAD) id_nn = id_at(k_first);
     fetch(k_first);
-    int raw = lane;
-    if (!RES && !MOVES && p.check_rows && lane < n_all) raw = rd.at(lane);
     if (!RES && !MOVES && p.gate && scalar_read(p.gate, 0) > p.o_bound) return;  // (while the lengths are on their way)
-    // A row of one block is checked here (every lane names another one, itself behind the row's end), and its completion rounds are
-    // written by request id, whole lines of one store: no second pass over it.  (One order of 61 requests 15.3 ->
-    // 13.6 us a call, 1024 22.9 -> 19.2, 32768 110.9 -> 104.6.)
+    // A row of up to KVS_CHECKED_ROW positions is checked here (in the room of the list, which is not in use yet), and its
+    // completion rounds are written by request id, while the whole row is in the L2 cache: no second pass over it.  (One order of 61
+    // requests 15.3 -> 13.6 us a call; 4096 orders of 61 / 200 / 300 / 1000 33.2 / 63.1 / 101 / 203 -> 29 / 58 / 92 / 196,
+    // 32768 of 61 111 -> 104, 40000 of 300 461 -> 411, of 1000 no difference.)
     bool is_order = true;
     if (!RES && !MOVES && p.check_rows) {
-        const bool named = __builtin_amdgcn_ds_permute((int)(4u * (unsigned)raw), 1) != 0;
-        is_order = __builtin_amdgcn_ballot_w64(named && (unsigned)raw < WAVE && (lane >= n_all || raw < n_all)) == ~0ull;
+        unsigned *met = wave_lds[WPB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0].met;
+        if (lane < KVS_CHECKED_ROW / 32) met[lane] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        bool fits = true;
+        for (int k = lane; k < n_all; k += WAVE) {
+            const int raw = rd.at(k), r = min(max(raw, 0), n_all - 1);
+            const unsigned bit = 1u << (r & 31);
+            fits &= raw == r && (atomicOr(&met[r >> 5], bit) & bit) == 0;
+        }
+        is_order = __builtin_amdgcn_ballot_w64(!fits) == 0;
         if (!is_order && lane == 0) atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = n;  // (unless it stops before)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)

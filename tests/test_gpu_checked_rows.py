@@ -1,6 +1,6 @@
-"""GPU parity with the CPU oracle of orders of up to 64 requests, which the timeline kernel checks and writes by request id
-itself: sizes around the block, one and many rows, every register file, with and without a bound from the caller, and
-orders that are no permutations beside lengths that cannot be scheduled."""
+"""GPU parity with the CPU oracle of orders of up to 1024 requests, which the timeline kernel checks and writes by request id
+itself: sizes around a block and the limit, one and many rows, every register file, with and without a bound from the
+caller, and orders that are no permutations beside lengths that cannot be scheduled."""
 import numpy as np
 import pytest
 
@@ -9,8 +9,9 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("longest", [100, 500, 2000, 4000, 8000, 14000, 15000])
-@pytest.mark.parametrize("n,rows", [(9, 1), (31, 5), (63, 1), (64, 1), (64, 300), (65, 3)])
+@pytest.mark.parametrize("n,rows,longest", [(n, rows, longest) for longest in (100, 500, 2000, 4000, 8000, 14000, 15000)
+                                            for n, rows in ((9, 1), (31, 5), (63, 1), (64, 1), (64, 300), (65, 3))]
+                         + [(130, 3, 2000), (256, 40, 100), (1023, 2, 100), (1024, 70, 500), (1024, 3, 1500), (1025, 2, 500)])
 def test_rows(n, rows, longest):
     import torch
     from paper_2508_06133_amd import kvsched
@@ -39,7 +40,7 @@ def test_rows(n, rows, longest):
             assert ctx.device_status() == kvsched.DEV_BAD_ORDER
             tel = tel.cpu().numpy()
             assert tel[rows // 2] == -1
-            if rows > 1:
+            if rows > 2:
                 assert tel[rows - 1] == tel_o[-1] and (comp[rows - 1].cpu().numpy() == comp_o[-1]).all()
         wrong = s.copy()
         wrong[n // 2] = M
