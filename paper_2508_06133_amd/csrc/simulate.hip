@@ -210,28 +210,37 @@ __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *
     }
 }
 
-// The same for long rows: one workgroup of 1024 threads per row (a single wavefront would walk a row of
-// 100000 entries in 1563 dependent turns).
-__global__ __launch_bounds__(1024) void check_orders_wide_kernel(const int32_t *orders, int32_t C, int32_t n,
-                                                                 int64_t *tel_out, int32_t *words, int32_t o_limit)
+// The same for long rows: a workgroup per row (a single wavefront would walk a row of 100000 entries in 1563
+// dependent turns), of 1024 threads up to 512 rows, which then run at a time, and of 256 beyond, of which a compute unit takes eight.
+// n entries in range set n bits exactly if none is there twice, so nothing is read back before the end, and eight
+// reads of a thread are in flight.  1025 rows of 100000: 184 us by 1024 threads a row, which take three turns, 139 so; one of 10000 4.7.
+template <int TPB>
+__global__ __launch_bounds__(TPB) void check_orders_wide_kernel(const int32_t *orders, int32_t C, int32_t n,
+                                                                int64_t *tel_out, int32_t *words, int32_t o_limit)
 {
     extern __shared__ unsigned int bitmap_all[];
+    constexpr int E = 8;
     const int o_max = words[KVS_W_OMAX];
     const int cand = blockIdx.x;
     const int nw = (n + 31) >> 5;
-    for (int i = threadIdx.x; i < nw; i += 1024) bitmap_all[i] = 0;
+    for (int i = threadIdx.x; i < nw; i += TPB) bitmap_all[i] = 0;
     __syncthreads();
     const int32_t *row = orders + (size_t)cand * (size_t)n;
     int bad = 0;
-    for (int k = threadIdx.x; k < n; k += 1024) {
-        const int r = row[k];
-        if (r < 0 || r >= n) {
-            bad = 1;
-        } else {
-            const unsigned int bit = 1u << (r & 31);
-            if (atomicOr(&bitmap_all[r >> 5], bit) & bit) bad = 1;
+    for (int k = threadIdx.x; k < n; k += TPB * E) {
+        int r[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) r[e] = row[min(k + TPB * e, n - 1)];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (k + TPB * e >= n) continue;
+            if ((unsigned)r[e] >= (unsigned)n) bad = 1;
+            else atomicOr(&bitmap_all[r[e] >> 5], 1u << (r[e] & 31));
         }
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nw; i += TPB)
+        if (bitmap_all[i] != (32 * i + 32 <= n ? ~0u : (1u << (n & 31)) - 1u)) bad = 1;
     if (__syncthreads_or(bad) && threadIdx.x == 0 && o_max <= o_limit) {  // (else the rows have not been placed)
         tel_out[cand] = -1;
         atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
@@ -370,8 +379,12 @@ int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t
     if (per_wave > 65536) return KVSCHED_ERANGE;
     // long rows, not enough of them to fill the chip with a wavefront each (one row of 10000: 31 us by a wavefront)
     if ((n >= 16384 && C <= 8192) || (n >= 1024 && C <= 512)) {
-        hipLaunchKernelGGL(check_orders_wide_kernel, dim3((unsigned)C), dim3(1024), per_wave, st, orders, C, n, tel_out,
-                           d_words, o_limit);
+        if (C <= 512)
+            hipLaunchKernelGGL(check_orders_wide_kernel<1024>, dim3((unsigned)C), dim3(1024), per_wave, st, orders, C, n,
+                               tel_out, d_words, o_limit);
+        else
+            hipLaunchKernelGGL(check_orders_wide_kernel<256>, dim3((unsigned)C), dim3(256), per_wave, st, orders, C, n,
+                               tel_out, d_words, o_limit);
     } else if (per_wave * 4 <= 65536) {
         hipLaunchKernelGGL((check_orders_kernel<4>), dim3((unsigned)((C + 3) / 4)), dim3(256), per_wave * 4, st,
                            orders, C, n, tel_out, d_words, o_limit);
