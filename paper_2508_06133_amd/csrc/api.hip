@@ -806,8 +806,12 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
     }
     rc = ensure_tables(ctx, kvs_exact_dp_table_bytes(r, kmax, (int32_t)M));
     if (rc != KVSCHED_OK) return rc;
+    // Requests of a few lengths leave most of a backlog undecided: once that has happened twice more than the search has found
+    // a batch it is not tried again (150 requests of lengths up to 8: tried for every batch it cost 45 us of 970).
+    int32_t tables = 0, failed = r <= KVS_EXACT_SEARCH_N ? 1 : 0;
     while (r > 0) {  // r falls by at least one per batch
-        rc = kvs_launch_exact_dp_batch(n, r, kmin, kmax, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, nb, ctx->d_scratch,
+        const bool search = failed <= 1 + nb - tables++;
+        rc = kvs_launch_exact_dp_batch(n, r, kmin, kmax, s, o, (int32_t)M, ga, gb, feas_mode, tie_rule, nb, search, ctx->d_scratch,
                                        ctx->d_tables, order_out, batch_end_out, F_out, num_batches_out, ctx->d_words, ctx->h_scan,
                                        next_seq(ctx), st);
         if (rc != KVSCHED_OK) return rc;
@@ -820,6 +824,7 @@ static int run_exact_dp(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int
         kmax = k_next;
         kmin = min_next;
         nb = ctx->h_scan[KVS_H_BATCHES];
+        if (search && r > 0 && r <= KVS_EXACT_SEARCH_N) ++failed;
     }
     return KVSCHED_OK;
 }

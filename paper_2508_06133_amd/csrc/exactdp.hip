@@ -608,7 +608,7 @@ __device__ void emit_body(int32_t n, const int *by_o, int *buf0, int *buf1, cons
 // three sorts of 0.6 to 1.3 us, 2.5 to 5 for what the prefixes of their orders give, 2 to 3 for better sets, the combinations 1 to 6).
 // 200 chat requests, M = 16384: 1.06 ms with tables (126 launches), 0.17 this way, and 0.1 for each batch that needs tables after
 // all (one of 200).
-constexpr int CORE_N = 256;
+constexpr int CORE_N = KVS_EXACT_SEARCH_N;
 constexpr int CORE_MAX = 20;
 constexpr int CORE_SIZES = 16;
 constexpr int CORE_WINDOW = 14;
@@ -1013,26 +1013,30 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
 // The batches from number nb on, as far as no table is needed: lists as left by the kernels below (listed: otherwise those
 // by cost and by o of what remains are still to be made).  What remains is planned and reported to the host; behind the
 // last batch the order is written.
+template <bool SEARCH>
 __device__ __forceinline__ void go_on(int32_t n, int r, int kmax, bool listed, int32_t nb, const int32_t *s, const int32_t *o, int32_t M,
                                       int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, bool search, int *proc, int *by_o,
                                       int *by_cost, int *buf0, int *buf1, int *batch_of, int *left_by_o, int *cost, int4 *req,
                                       int2 *range, int32_t *order_out, int32_t *batch_end_out, double *F_out,
                                       int32_t *num_batches_out, int32_t *words, int32_t *host, int32_t seq, HelperLds &L,
-                                      CoreLds &C)
+                                      CoreLds *core)
 {
     const int tid = threadIdx.x, before = r;
-    if (search && feas_mode == 0 && r > 0 && r <= CORE_N) {
-        if (tid < r) {
-            const int id = proc[tid], sv = s[id], ov = o[id];
-            C.id[tid] = id;
-            C.value[tid] = ga * sv + gb * ov;
-            C.load[tid] = sv + ov;
+    if constexpr (SEARCH) {
+        if (search && r > 0 && r <= CORE_N) {
+            CoreLds &C = *core;
+            if (tid < r) {
+                const int id = proc[tid], sv = s[id], ov = o[id];
+                C.id[tid] = id;
+                C.value[tid] = ga * sv + gb * ov;
+                C.load[tid] = sv + ov;
+            }
+            core_start(C);
+            __syncthreads();
+            while (r > 0 && core_batch(r, M, gb, tie_rule, n, nb, batch_of, batch_end_out, F_out, words, C)) ++nb;
+            __threadfence_block();
+            __syncthreads();
         }
-        core_start(C);
-        __syncthreads();
-        while (r > 0 && core_batch(r, M, gb, tie_rule, n, nb, batch_of, batch_end_out, F_out, words, C)) ++nb;
-        __threadfence_block();
-        __syncthreads();
     }
     int kmin = 0;
     if (r == 0) {
@@ -1064,7 +1068,9 @@ __host__ __device__ __forceinline__ size_t counted_bytes(int32_t r, int32_t kmax
     return 2 * (size_t)(kmax + 1) * loads * sizeof(int) + (size_t)r * (size_t)(kmax + 1) * (loads / 8) + 6400;
 }
 
-// (pad: zeros in all of batch_end_out and F_out first)
+// (pad: zeros in all of batch_end_out and F_out first.  SEARCH: with the batches that need no table, under the sum of peaks; the code of
+// the search is five times that of the rest, which costs the profile constraint, where there is none, 6 % of a call.)
+template <bool SEARCH>
 __global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
                                                           int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t pad,
                                                           int *proc, int *by_o, int *by_cost, int *buf0, int *buf1, int *batch_of,
@@ -1073,12 +1079,12 @@ __global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32
                                                           int32_t *words, int32_t *num_batches_out, int32_t *host, int32_t seq)
 {
     __shared__ HelperLds L;
-    __shared__ CoreLds C;
+    __shared__ char core[SEARCH ? sizeof(CoreLds) : 1] __attribute__((aligned(16)));
     if (pad)
         for (int i = threadIdx.x; i < n; i += DP_T) batch_end_out[i] = 0, F_out[i] = 0.0;
     // Sizes that are refused are refused whether or not a table would have been needed: where no bound on the batch size
     // leads to a refusal, it and the lists it takes are made when a table is needed (5 us of 200 requests).
-    const bool listed = feas_mode != 0 || n > CORE_N || counted_bytes(n, n, M) > most_bytes;
+    const bool listed = !SEARCH || n > CORE_N || counted_bytes(n, n, M) > most_bytes;
     const int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words,
                                   num_batches_out, L, listed);
     if (kmax < 0) {
@@ -1089,12 +1095,13 @@ __global__ __launch_bounds__(DP_T) void dp_prepare_kernel(int32_t n, const int32
         for (int i = threadIdx.x; i < n; i += DP_T) left_by_o[i] = by_o[i];
     __threadfence_block();
     __syncthreads();
-    go_on(n, n, kmax, listed, 0, s, o, M, ga, gb, feas_mode, tie_rule, !listed || counted_bytes(n, kmax, M) <= most_bytes, proc, by_o,
+    go_on<SEARCH>(n, n, kmax, listed, 0, s, o, M, ga, gb, feas_mode, tie_rule, !listed || counted_bytes(n, kmax, M) <= most_bytes, proc, by_o,
           by_cost, buf0, buf1, batch_of, left_by_o, cost, req, range, order_out, batch_end_out, F_out, num_batches_out, words, host,
-          seq, L, C);
+          seq, L, reinterpret_cast<CoreLds *>(core));
 }
 
 // The end of a batch: its best state from the rows' (partial[k - kmin]), its members, and how it goes on.
+template <bool SEARCH>
 __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long long *partial, const unsigned long long *bits,
                                                          int *proc, int *by_o, int *by_cost, int *left_by_o, int *buf0, int *buf1, int *batch_of,
                                                          int *cost, int4 *req, int2 *range, int32_t n, int r, int kmin, int kmax, int Mp, const int32_t *s,
@@ -1104,7 +1111,7 @@ __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long lon
                                                          int32_t *host, int32_t seq)
 {
     __shared__ HelperLds L;
-    __shared__ CoreLds C;
+    __shared__ char core[SEARCH ? sizeof(CoreLds) : 1] __attribute__((aligned(16)));
     __shared__ int load[KVSCHED_EXACT_MAX_N];
     long long bS = 0;
     int bk = 0, bm = 0;
@@ -1122,8 +1129,8 @@ __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long lon
     __syncthreads();
     int kept, knext;
     compact_body(proc, by_cost, left_by_o, buf0, r, batch_of, s, o, feas_mode, M, L, kept, knext);
-    go_on(n, kept, knext, true, nb + 1, s, o, M, ga, gb, feas_mode, tie_rule, true, proc, by_o, by_cost, buf0, buf1, batch_of, left_by_o, cost, req,
-          range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, C);
+    go_on<SEARCH>(n, kept, knext, true, nb + 1, s, o, M, ga, gb, feas_mode, tie_rule, true, proc, by_o, by_cost, buf0, buf1, batch_of, left_by_o, cost, req,
+          range, order_out, batch_end_out, F_out, num_batches_out, words, host, seq, L, reinterpret_cast<CoreLds *>(core));
 }
 
 // The whole Phase 1 in one workgroup when both tables fit in LDS (the settings Algorithm 2 is meant
@@ -1259,7 +1266,7 @@ int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, i
                                 int32_t *num_batches_out, int32_t *host, int32_t seq, hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(dp_prepare_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, pad, l.proc, l.by_o,
+    hipLaunchKernelGGL(feas_mode == KVSCHED_FEAS_SUM_OF_PEAKS ? dp_prepare_kernel<true> : dp_prepare_kernel<false>, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, pad, l.proc, l.by_o,
                        l.by_cost, l.buf0, l.buf1, l.batch_of, l.left_by_o, l.cost, l.req, l.range, most_bytes, order_out, batch_end_out,
                        F_out, d_words, num_batches_out, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
@@ -1267,7 +1274,7 @@ int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, i
 
 // One batch over the r remaining requests: tables, records, best state, members, compaction.
 int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
-                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
+                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb, bool search,
                               void *lists, void *tables, int32_t *order_out, int32_t *batch_end_out, double *F_out,
                               int32_t *num_batches_out, int32_t *d_words, int32_t *host, int32_t seq, hipStream_t st)
 {
@@ -1298,7 +1305,7 @@ int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, 
     unsigned long long *partial = bits + (size_t)r * per_t;
     hipLaunchKernelGGL(dp_argmin_rows_kernel, dim3((unsigned)(kmax - kmin + 1)), dim3(DP_T), 0, st, dp[at], kmin, Mp,
                        plan, partial);
-    hipLaunchKernelGGL(dp_finish_kernel, dim3(1), dim3(DP_T), 0, st, partial, bits, l.proc, l.by_o, l.by_cost, l.left_by_o, l.buf0, l.buf1,
+    hipLaunchKernelGGL(search && feas_mode == KVSCHED_FEAS_SUM_OF_PEAKS ? dp_finish_kernel<true> : dp_finish_kernel<false>, dim3(1), dim3(DP_T), 0, st, partial, bits, l.proc, l.by_o, l.by_cost, l.left_by_o, l.buf0, l.buf1,
                        l.batch_of, l.cost, l.req, l.range, n, r, kmin, kmax, Mp, s, o, M, ga, gb, feas_mode, tie_rule, nb, order_out,
                        batch_end_out, F_out, num_batches_out, d_words, host, seq);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;

@@ -193,13 +193,14 @@ size_t kvs_exact_dp_table_bytes(int32_t r, int32_t kmax, int32_t M);
 size_t kvs_exact_dp_counted_bytes(int32_t r, int32_t kmax, int32_t M);
 // (host, seq: pinned words that receive the batches found, the requests left and the bounds kmin..kmax on the next batch's size, then seq;
 // ga, gb: the metric's numerator sums ga s_i + gb o_i -- 0, 1: the F-metric; else G with alpha = ga / gb)
-// The batches that need no table are found on the way; behind the last one the order is written.
+constexpr int32_t KVS_EXACT_SEARCH_N = 256;
+// Of up to KVS_EXACT_SEARCH_N requests the batches that need no table are found on the way (search: also behind this one); behind the last one the order is written.
 int kvs_launch_exact_dp_prepare(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
                                 int32_t feas_mode, int32_t tie_rule, int pad, size_t most_bytes, void *lists,
                                 int32_t *order_out, int32_t *batch_end_out, double *F_out, int32_t *d_words,
                                 int32_t *num_batches_out, int32_t *host, int32_t seq, hipStream_t st);
 int kvs_launch_exact_dp_batch(int32_t n, int32_t r, int32_t kmin, int32_t kmax, const int32_t *s, const int32_t *o,
-                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb,
+                              int32_t M, int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int32_t nb, bool search,
                               void *lists, void *tables, int32_t *order_out, int32_t *batch_end_out, double *F_out,
                               int32_t *num_batches_out, int32_t *d_words, int32_t *host, int32_t seq, hipStream_t st);
 int kvs_exact_dp_small_lg(int32_t n, int32_t kmax_bound, int32_t M);
