@@ -458,6 +458,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
     long long tel = 0;
     bool over_limit = false, overflow = false;
 
+    const int first_last = p.C - 4096;  // no other takes the place of the candidates from here on
     while (done < n) {
         // (everything the loop carries is the same in all lanes; saying so keeps it on the scalar unit)
         t = p_uni(t), head = p_uni(head), hpos = p_uni(hpos), hs = p_uni(hs), he = p_uni(he), ho = p_uni(ho), hid = p_uni(hid);
@@ -476,9 +477,12 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
         // ones a SIMD serves the oldest, and of its four the youngest took 20.3 M cycles where the oldest took 12.2 M, the last
         // third of the time with fewer than four.  4096 mixed candidates 8.28 -> 7.58 ms (lines at a half and a quarter 7.66, a
         // third and two thirds done 7.75, turns of 64 visits 7.79), of 1000 requests 4.39 -> 4.06, 2000 chat requests 19.0 -> 19.2.
+        // Those whose place another candidate takes (all but the last 4096) step back in their last eighth only: 6000 / 8192 / 16384
+        // candidates 13.25 / 16.9 / 31.1 -> 13.0 / 15.6 / 31.0 ms (with the lines of the others 13.4 / 15.5 / 29.7, but 9000 of 1000
+        // requests 10.1 -> 10.8 instead of 10.4; never 13.1 / 16.1 / 31.4).
         if ((++visited & 63) == 0) {
             if (2 * visited > 3 * done) __builtin_amdgcn_s_setprio(3);
-            else if (4 * done < 3 * n) __builtin_amdgcn_s_setprio(2);
+            else if (cand < first_last ? 8 * done < 7 * n : 4 * done < 3 * n) __builtin_amdgcn_s_setprio(2);
             else if (8 * done < 7 * n) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
         }
