@@ -602,7 +602,8 @@ __device__ void emit_body(int32_t n, const int *by_o, int *buf0, int *buf1, cons
 // The batch is the one the tables would give: all sets as good as the best are among those tried, and of those of one
 // size and load the tables keep the one whose latest request is the earliest, then whose second latest is, and so on
 // (a state's record is the last request that improved it): the least as a binary number, the earliest request its lowest bit.
-// Sums are exact; bounds are in double precision, and a request or size is given up only beyond one part in 10^9.
+// Sums are exact; bounds are in double precision, and a request or size is given up only beyond one part in 10^9.  Orders are
+// by keys of 24 bits, which tell sums apart that differ by a step: bounds, sizes that fit and requests have that much room.
 //
 // Bound by the instructions of one workgroup and their chain (a batch of 200 requests left takes 43 us, of 40 or fewer 22:
 // three sorts of 0.6 to 1.3 us, 2.5 to 5 for what the prefixes of their orders give, 2 to 3 for better sets, the combinations 1 to 6).
@@ -733,7 +734,9 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
         if (r > 128) wave_sort<4>(key);
         else wave_sort<2>(key);
         if (lane == 0) C.price[turn * DP_NW + wave] = price;
-        // prefixes of the order
+        // Prefixes of the order.  Loads that share a key lie in any order: the sum of the k first is that of the k least but for
+        // less than k steps, and with r steps more room no size that fits is lost (less than 1 while r loads are below 2^24).
+        const u64 room_sizes = (u64)M + (by_load ? (u64)(step * (double)r) : 0);
         u64 sum_w[4], sum_v[4], cw = 0, cv = 0, best = ~0ull;
         int fits = 0;
 #pragma unroll
@@ -756,7 +759,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
                     cv = (unsigned)__builtin_amdgcn_readlane((int)v32, 63);
                 }
                 const bool fit = i < r && sum_w[e] <= (u64)M;
-                fits += __popcll(__builtin_amdgcn_ballot_w64(fit));
+                fits += __popcll(__builtin_amdgcn_ballot_w64(i < r && sum_w[e] <= room_sizes));
                 if (i < r) {
                     C.at[wave][i] = (unsigned char)who;
                     const double b = v + price * (w - (double)M) - margin * (v + price * w) - step * (double)(i + 1);
@@ -990,6 +993,7 @@ __device__ __forceinline__ bool core_batch(int &r, int32_t M, int32_t gb, int32_
         if (dp_better(total, C.size[a], (int)(unsigned)key, S, k, m, tie_rule)) S = total, k = C.size[a], m = (int)(unsigned)key, least = key;
     }
     if (k < 1) return false;  // cannot happen
+    if (F > 0.0 && (double)S * C.per_square[k - 1] > F) return false;  // cannot happen: a set that was met is better
     int own = INT_MAX;
     combinations(k, [&](int x, unsigned long long key) {
         if (key == least && own == INT_MAX) own = (tid << lo_bits) | C.low_set[x];
