@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
         int s = len_s[id], o = len_o[id];
         if (s < 1 || o < 1 || o > p.o_bound || (long long)s + o > (long long)M) {  // cannot be scheduled
             valid = false;
-            s = o = 1;
+            s = o = 0;  // ends where it starts and holds nothing: the look below moves no start for it
         }
         for (;;) {
             const int end = t + o;

@@ -1,0 +1,68 @@
+"""Orders placed a lane each that cannot be scheduled: a budget of one token, which no request fits, and requests that hold more
+than any budget beside others that wait for one another.  The CPU oracle refuses such requests; the rows report -1."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1), (1, 130), (2, 64), (8, 65), (9, 8192), (16, 8200), (17, 32768), (32, 32770)]  # (requests, orders)
+
+
+def _run(s, o, M, orders, bound=0):
+    import torch
+    from paper_2508_06133_amd import kvsched
+
+    ctx = kvsched.Context(0)
+    try:
+        ctx.set_o_max(bound)
+        d = [torch.from_numpy(np.ascontiguousarray(x, dtype=np.int32)).to("cuda:0") for x in (orders, s, o)]
+        tel, comp = ctx.simulate(d[0], d[1], d[2], M)
+        status = ctx.device_status()
+        return tel.cpu().numpy(), comp.cpu().numpy(), status
+    finally:
+        ctx.close()
+
+
+def _orders(rng, n, rows):
+    return np.argsort(rng.random((rows, n)), axis=1).astype(np.int32)
+
+
+@pytest.mark.parametrize("bound", [0, 4])
+@pytest.mark.parametrize("n,rows", SIZES)
+def test_budget_of_one_token(n, rows, bound):
+    rng = np.random.default_rng(n)
+    s, o = rng.integers(1, 5, n), rng.integers(1, 5, n)
+    print(f"short rows, M=1: n={n} rows={rows} bound={bound}", flush=True)
+    tel, _, status = _run(s, o, 1, _orders(rng, n, rows), bound)
+    assert status == 1 and (tel == -1).all()
+
+
+@pytest.mark.parametrize("n,rows", SIZES)
+def test_budget_of_two_tokens(n, rows):
+    """The least budget that holds a request: one runs after the other."""
+    rng = np.random.default_rng(n)
+    orders = _orders(rng, n, rows)
+    print(f"short rows, M=2: n={n} rows={rows}", flush=True)
+    tel, comp, status = _run(np.ones(n), np.ones(n), 2, orders)
+    assert status == 0 and (tel == n * (n + 1) // 2).all()
+    assert (np.take_along_axis(comp, orders.astype(np.int64), axis=1) == np.arange(1, n + 1)).all()
+
+
+@pytest.mark.parametrize("n,rows", SIZES[2:])
+def test_unschedulable_among_others(n, rows):
+    rng = np.random.default_rng(n)
+    s, o = rng.integers(1, 3000, n), rng.integers(1, 2048, n)
+    M = int((s + o).max()) + 100
+    orders = _orders(rng, n, rows)
+    for value in (0, -2**31, M, 2**31 - 1):
+        bad = s.copy()
+        bad[rng.integers(0, n)] = value
+        print(f"short rows, unschedulable: n={n} rows={rows} s={value}", flush=True)
+        tel, _, status = _run(bad, o, M, orders)
+        assert status == 1 and (tel == -1).all()
+    few = orders[:4]
+    tel, comp, status = _run(s, o, M, orders)
+    tel_o, comp_o = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), M, few)
+    assert status == 0 and (tel[:4] == tel_o).all() and (comp[:4] == comp_o).all()
