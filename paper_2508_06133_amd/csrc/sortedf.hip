@@ -303,9 +303,17 @@ __device__ int group_argmin(const Sums &c, int a, int K, int tie_rule, u64 *red_
     const u64 G0 = c.G[a];
     u64 bS = 0;
     int bk = 0;
-    for (int k = tid + 1; k <= K; k += 1024) {
-        const u64 Sk = c.G[a + k] - G0;
-        if (better<SMALL>(Sk, k, bS, bk, tie_rule)) bS = Sk, bk = k;
+    // Four reads in flight, where one a turn left the loop to their latency (0.35 us each): 20000 sizes 7.8 -> 5.0 us; 40000 chat
+    // requests in 3 / 5 batches 142 -> 137 / 148 -> 144 us a call, under the profile constraint in 3 batches 242 -> 235.
+    for (int k0 = tid + 1; k0 <= K; k0 += 4096) {
+        u64 g[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = c.G[a + min(k0 + 1024 * q, K)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = k0 + 1024 * q;
+            if (k <= K && better<SMALL>(g[q] - G0, k, bS, bk, tie_rule)) bS = g[q] - G0, bk = k;
+        }
     }
     bk = wave_best<SMALL>(bS, bk, tie_rule);
     if (lane == 0) red_S[wave] = bS, red_k[wave] = bk;
@@ -1081,8 +1089,9 @@ __global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeAr
             __syncthreads();
             continue;
         }
-        const int k = small ? group_argmin<true>(c, a, K, p.tie_rule, red_S, red_k)
-                            : group_argmin<false>(c, a, K, p.tie_rule, red_S, red_k);
+        int k;  // (likely, so that the other form's code lies behind the loop: 100000 bimodal requests in 197 batches 241 us without)
+        if (__builtin_expect(small, 1)) k = group_argmin<true>(c, a, K, p.tie_rule, red_S, red_k);
+        else k = group_argmin<false>(c, a, K, p.tie_rule, red_S, red_k);
         if (k < 1) {  // cannot happen for well-formed input; never spin
             if (tid == 0) atomicOr(&p.words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
             break;
