@@ -797,8 +797,9 @@ __device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c
 // places that a wavefront takes; the chain takes some 20 us for each batch, if the extents are beyond kNextMax.  Hence ahead if
 // there are six budgets' worth of requests or more, and if the extents are on average beyond 64, or kNextMax where completion
 // times are beyond 2048.  Whole call, before -> now: 10000 mixed requests in 17 batches 256 -> 157 us, 44 batches 273 -> 162; 40000 in 43
-// 823 -> 312; 10000 chat requests in 9 375 -> 151; 40000 bimodal ones in 69 1878 -> 486.  The other side: 40000 chat requests in 3 batches 239
-// (270 with it), 10000 bimodal ones in 213 138 (191), in 70 171 (181).
+// 823 -> 312; 10000 chat requests in 9 375 -> 151; 40000 bimodal ones in 69 1878 -> 486.  The other side: 40000 chat requests in 3 batches 236
+// (270 with it), 10000 bimodal ones in 213 138 (191), in 70 171 (181).  Where they are not, two launches end at once: 5000 mixed
+// requests in 5 batches 186 -> 191, 10000 chat ones in 3 118 -> 120.
 __device__ __forceinline__ bool extents_ahead(const SortedArgs &p, const LargeArrays &m)
 {
     const int omax = p.words[KVS_W_OMAX];
@@ -982,7 +983,7 @@ __global__ __launch_bounds__(64) void profile_extents_kernel(SortedArgs p, Large
 // The batch every place would start, one wavefront each; 0 where that is left to the chain: extents of kNextLimit requests
 // or more (a place costs up to kNextLimit / 256 turns, all of them together less than the 3 us that the chain takes for a batch of
 // that many; such a place is recognised by one sum), and of kNextMax where the profile test is made here.  With 256 for both, 100000 bimodal
-// requests in 197 batches of 510 were 554 us of chain.
+// requests in 197 batches of 510 were 554 us of chain.  (100000 chat requests in 16 batches, all but two beyond the limit: 261 -> 267.)
 template <bool PROFILE>
 __global__ __launch_bounds__(256) void next_batch_kernel(SortedArgs p, LargeArrays m)
 {
