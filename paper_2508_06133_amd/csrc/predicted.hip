@@ -61,6 +61,7 @@ struct PredParams {
     int32_t second;       // 0: every candidate, overflow sets retry[c]; 1: only candidates with retry[c] != 0
     int32_t *retry;       // [C]
     unsigned short *est_stopped;  // [C][n]: estimate kept by a stopped request, by position
+    int32_t step_back;    // candidates that run at a time, if they give way near their ends (0: they do not)
     int32_t round_limit;  // a run that lasts longer is reported, not continued
     int64_t *tel_out;         // [C]
     int32_t *completion_out;  // [C][n] by request id, or NULL
@@ -458,7 +459,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
     long long tel = 0;
     bool over_limit = false, overflow = false;
 
-    const int first_last = p.C - 4096;  // no other takes the place of the candidates from here on
+    const int first_last = p.C - p.step_back;  // no other takes the place of the candidates from here on
     while (done < n) {
         // (everything the loop carries is the same in all lanes; saying so keeps it on the scalar unit)
         t = p_uni(t), head = p_uni(head), hpos = p_uni(hpos), hs = p_uni(hs), he = p_uni(he), ho = p_uni(ho), hid = p_uni(hid);
@@ -476,12 +477,13 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
         // The others go first while they have a quarter of their requests before them, then while they have an eighth: of equal
         // ones a SIMD serves the oldest, and of its four the youngest took 20.3 M cycles where the oldest took 12.2 M, the last
         // third of the time with fewer than four.  4096 mixed candidates 8.28 -> 7.58 ms (lines at a half and a quarter 7.66, a
-        // third and two thirds done 7.75, turns of 64 visits 7.79), of 1000 requests 4.39 -> 4.06, 2000 chat requests 19.0 -> 19.2.
-        // Those whose place another candidate takes (all but the last 4096) step back in their last eighth only: 6000 / 8192 / 16384
-        // candidates 13.25 / 16.9 / 31.1 -> 13.0 / 15.6 / 31.0 ms (with the lines of the others 13.4 / 15.5 / 29.7, but 9000 of 1000
-        // requests 10.1 -> 10.8 instead of 10.4; never 13.1 / 16.1 / 31.4).
+        // third and two thirds done 7.75, turns of 64 visits 7.79), of 1000 requests 4.87 -> 4.48, 2000 chat requests 10.6 -> 9.8.
+        // Those whose place another candidate takes (all but as many as run at a time) step back in their last eighth only: 6000 /
+        // 8192 / 16384 candidates 13.25 / 16.9 / 31.1 -> 13.0 / 15.6 / 31.0 ms (with the lines of the others 13.4 / 15.5 / 29.7, but
+        // 9000 of 1000 requests 10.6 -> 11.2 ms; never 13.1 / 16.1 / 31.4).  Which calls have these lines: may_step_back.
         if ((++visited & 63) == 0) {
             if (2 * visited > 3 * done) __builtin_amdgcn_s_setprio(3);
+            else if (p.step_back == 0) __builtin_amdgcn_s_setprio(0);
             else if (cand < first_last ? 8 * done < 7 * n : 4 * done < 3 * n) __builtin_amdgcn_s_setprio(2);
             else if (8 * done < 7 * n) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
@@ -824,6 +826,20 @@ static size_t lds_bytes(int32_t n, int32_t ring, int32_t cap, int32_t entry = 10
     return sizeof(int) * ((size_t)ring + (((size_t)n + 31) >> 5)) + (size_t)entry * (size_t)cap;
 }
 
+// For C candidates of `bytes` of LDS each: how many run at a time on 256 compute units if they step back near their ends, or 0.
+// Sixteen per unit is the most that counts: with short lists a few more fit, but 6000 / 7000 candidates of 400 chat requests take
+// 3.92 / 4.30 ms with 4096, 4.00 / 4.35 with the 5120 that run.  The second launch has whole lists; which of its candidates
+// run is not known here, and it goes by the case that all do (as if others took the places of all of them: up to 1 % slower).
+// Not where the last ones are a quarter or fewer, one for each SIMD: they start when the first end, and equal progress
+// ends all the others at once and late.  1000 mixed requests, 4200 / 5000 / 9000 candidates with the lines 7.05 / 7.23 / 10.86 ms,
+// without 6.68 / 6.97 / 10.60; 5300 / 6000 / 9800 the other way, 7.40 / 7.56 / 11.25 and 7.47 / 7.83 / 11.36.
+static int32_t may_step_back(int32_t C, size_t bytes)
+{
+    const int32_t by_lds = (int32_t)((160 * 1024) / ((bytes + 1023) & ~(size_t)1023));
+    const int32_t at_a_time = 256 * (by_lds < 16 ? by_lds : 16), last = C % at_a_time;
+    return C > at_a_time && last > 0 && 4 * last <= at_a_time ? 0 : at_a_time;
+}
+
 // The longest list of the first launch is the one with which sixteen candidates share a compute unit's 160 KB (LDS is
 // handed out in whole KB); worth it when that is at least 128 entries and fewer than all.
 static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
@@ -838,6 +854,7 @@ static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
     auto launch = [&](int32_t cap, int32_t second) {
         p.cap = cap;
         p.second = second;
+        p.step_back = may_step_back(p.C, lds_bytes(p.n, 0, cap));
         void *args[] = {&p};
         return hipLaunchKernel(kernel, dim3((unsigned)p.C), dim3(PW), args, lds_bytes(p.n, 0, cap), st) == hipSuccess;
     };
@@ -850,11 +867,13 @@ static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
-// One launch with the whole list (a ring is 32 KB or more: a short list lets no further candidate in).
+// One launch with the whole list (a ring is 32 KB or more: a short list lets no further candidate in).  Its candidates have a
+// SIMD each and do not step back: 512 of 2000 requests 22.2 -> 21.7 ms without, 1024 of 800 with the largest ring 57.6 -> 56.2.
 static int launch_ring(const void *kernel, PredParams p, hipStream_t st)
 {
     p.cap = (p.n + 1) & ~1;
     p.second = 0;
+    p.step_back = 0;
     const size_t bytes = lds_bytes(p.n, p.H, p.cap);
     if (bytes > 64 * 1024 &&
         hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
