@@ -87,6 +87,9 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
         p.tel_out[first + lane] = permutation && valid ? (int64_t)tel : -1;
     }
     if (!p.completion_out) return;
+    if (!permutation)  // requests that do not occur
+        for (int i = 0; i < n; ++i)
+            if (((met >> i) & 1) == 0) done[lane * PITCH + i] = -1;
     __syncthreads();
     int32_t *out = p.completion_out + (size_t)first * (size_t)n;
     for (int e = lane; e < entries; e += 64) out[e] = done[(e / n) * PITCH + e % n];

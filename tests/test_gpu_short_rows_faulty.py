@@ -1,5 +1,6 @@
-"""Orders placed a lane each that cannot be scheduled: a budget of one token, which no request fits, and requests that hold more
-than any budget beside others that wait for one another.  The CPU oracle refuses such requests; the rows report -1."""
+"""Orders placed a lane each that cannot be scheduled: a budget of one token, which no request fits, requests that hold more
+than any budget beside others that wait for one another, and rows that are no permutations.  The CPU oracle refuses them; the
+rows report -1."""
 import numpy as np
 import pytest
 
@@ -66,3 +67,22 @@ def test_unschedulable_among_others(n, rows):
     tel, comp, status = _run(s, o, M, orders)
     tel_o, comp_o = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), M, few)
     assert status == 0 and (tel[:4] == tel_o).all() and (comp[:4] == comp_o).all()
+
+
+@pytest.mark.parametrize("n,rows", SIZES[2:])
+def test_requests_that_do_not_occur(n, rows):
+    """A row that names one request twice, or one that does not exist: the completion round of those it leaves out is -1."""
+    rng = np.random.default_rng(n)
+    s, o = rng.integers(1, 9, n), rng.integers(1, 9, n)
+    orders = _orders(rng, n, rows)
+    left_out = {0: orders[0, 0], rows // 2: orders[rows // 2, n - 1], rows - 1: orders[rows - 1, 1]}
+    orders[0, 0], orders[rows // 2, n - 1], orders[rows - 1, 1] = orders[0, 1], orders[rows // 2, 0], 2**31 - 1
+    left_out[rows - 1] = None if left_out[rows - 1] == n - 1 else left_out[rows - 1]  # (read as request n - 1)
+    print(f"short rows, requests left out: n={n} rows={rows}", flush=True)
+    tel, comp, status = _run(s, o, 40, orders)
+    assert status == 2 and (tel[list(left_out)] == -1).all() and (tel == -1).sum() == 3
+    for row, request in left_out.items():
+        assert (comp[row] == -1).sum() == (request is not None) and (request is None or comp[row, request] == -1)
+    whole = np.setdiff1d(np.arange(rows), list(left_out))[:4]
+    tel_o, comp_o = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), 40, orders[whole])
+    assert (tel[whole] == tel_o).all() and (comp[whole] == comp_o).all()
