@@ -49,6 +49,9 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const int32_t *orders
         tel_out[blockIdx.x] = -1;
         atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
     }
+    if (bad)  // (-1 for requests that do not occur)
+        for (int i = threadIdx.x; i < n; i += blockDim.x)
+            if (((seen[i >> 5] >> (i & 31)) & 1u) == 0) row_by_id[i] = -1;
     for (int i = threadIdx.x; i < n; i += blockDim.x) comp[i] = row_by_id[i];
 }
 
@@ -70,6 +73,7 @@ __global__ __launch_bounds__(256) void permute_short_rows_kernel(const int32_t *
     int32_t *comp = completion + (size_t)row0 * (size_t)n;
     for (int i = threadIdx.x; i < mine * nw; i += 256) seen[i] = 0;
     for (int i = threadIdx.x; i < mine; i += 256) bad[i] = 0;
+    for (int e = threadIdx.x; e < entries; e += 256) by_id[e] = -1;  // (what requests that do not occur are left with)
     __syncthreads();
     for (int e = threadIdx.x; e < entries; e += 256) {
         const int row = e / n;
