@@ -6,16 +6,22 @@
 // reserved for round c_i is then the sum of the first i + 1 second parts plus (i + 1) c_i, a running sum with
 // factors known at compile time.  Memory rises from one completion to the next, so a request (s, o) may start in round t
 // iff the completion rounds among t + 1 .. t + o, and round t + o, have room for it.  Round tau rules out every start
-// before min(tau, memory(tau) + s + tau - M): the start moves to the largest of these until none is behind it.
+// before min(tau, memory(tau) + s + tau - M): the start moves to the largest of these until none is behind it.  If round t + o
+// has no room, no start has whose last round comes before the next completion or with it, as memory only rises until then.
+// (Without that a request of one round, which looks at the round ahead only, went through every round it waited: 8192 orders
+// of 16 requests of 1 or 4096 tokens and rounds, M = 8192, 17 ms instead of 25 us.)  Every turn that moves the
+// start settles a completion round for good, so there is at most one more turn than there are completions.
 //
 // The ids are read as whole rows and the completion rounds written by request id through LDS; that an order is a
 // permutation comes out on the way.  So there is no second pass over the rows.
 //
 // Bound by the chain of its vector instructions, ten for each place of the arrays in each look at a start round: a call of
-// 65536 orders of 4 or 8 chat requests takes 11 us where two launches of a wavefront an order took 35 and 42, of 16 requests
-// 20 (63), of 24 39 (74), of 32 50 (89).  The chain grows with the square of the requests and does not shrink with the orders, so
-// longer orders need more of them: 4096 / 16384 orders of 16 requests 17.6 / 18.1 us (14.9 / 23.7), 16384 of 24 35 (29),
-// of 32 56 (40).  The lines lie where the two meet.
+// 65536 orders of 4 or 8 chat requests takes 11 us where the timeline kernel takes 36 and 44, of 16 requests 20 (55), of 24 40 (79),
+// of 32 58 (103).  The chain grows with the square of the requests and does not shrink with the orders, so longer orders
+// need more of them: 8192 orders of 9 requests 12.1 us (12.4), of 12 14.6 (12.4), of 16 17.8 (13.0), 16384 of 16 18.1 (18.5), of
+// 24 37 (26), 32768 of 17 / 24 / 32 27 / 39 / 55 (36 / 44 / 57).  Where many short requests wait for long ones the timeline kernel
+// looks at many more rounds: 16 requests of 1 or 4096 tokens and rounds, 8192 orders at M = 8192 25 us (4400), 16384 at M = 16384
+// 24 (73).  So orders of 9 to 16 requests take this way from 8192 on, where the chat ones alone would have it at 16384.
 #include "kvsched_internal.h"
 
 namespace {
@@ -66,7 +72,13 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
                 const int bound = min(c[i], sum + (int)__umul24((unsigned)c[i], i + 2));
                 start = (unsigned)(c[i] - t - 1) < (unsigned)o ? max(start, bound) : start;
             }
-            start = max(start, min(end, at_end + (int)__umul24((unsigned)end, (unsigned)behind)));
+            const int free_end = at_end + (int)__umul24((unsigned)end, (unsigned)behind);
+            if (__builtin_amdgcn_ballot_w64(free_end > t && o > 0) != 0) {
+                int next = 0;  // the first completion round at or behind `end` (there is one)
+#pragma unroll
+                for (int i = 0; i < N; ++i) next = c[i] >= end ? c[i] : next;
+                if (free_end > t && o > 0) start = max(start, max(min(end, free_end), next - o + 1));
+            }
             const bool moved = start > t;
             t = start;
             if (__builtin_amdgcn_ballot_w64(moved) == 0) break;
