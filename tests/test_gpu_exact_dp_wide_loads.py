@@ -6,7 +6,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _phase1(s, o, M, tie):
+def _phase1(s, o, M, tie, alpha=(0, 1)):
     """(order, batch ends, F) with every batch the best subset: least F, then the size, then the least load, then the set
     whose latest request is the earliest, then whose second latest is (the least as a binary number)."""
     left, order, ends, F = list(range(len(s))), [], [], []
@@ -14,7 +14,7 @@ def _phase1(s, o, M, tie):
         w = np.zeros(1, dtype=np.int64)
         v, k = w.copy(), w.copy()
         for i in left:  # bit b of a subset's number: the b-th of those left
-            w, v, k = np.concatenate([w, w + s[i] + o[i]]), np.concatenate([v, v + o[i]]), np.concatenate([k, k + 1])
+            w, v, k = np.concatenate([w, w + s[i] + o[i]]), np.concatenate([v, v + alpha[0] * s[i] + alpha[1] * o[i]]), np.concatenate([k, k + 1])
         ok = np.flatnonzero((w <= M) & (k > 0))
         best = None
         for size in np.unique(k[ok]):
@@ -28,7 +28,7 @@ def _phase1(s, o, M, tie):
         members = [i for b, i in enumerate(left) if best[2] >> b & 1]
         order += sorted(members, key=lambda i: (o[i], i))
         ends.append(len(order))
-        F.append(best[1] / best[0] ** 2)
+        F.append(best[1] / (alpha[1] * best[0] ** 2))
         left = [i for i in left if i not in members]
     return order, ends, F
 
@@ -43,14 +43,18 @@ def _near_ties(rng, n, largest):
     return (load - o).astype(np.int32), o.astype(np.int32), int(np.sort(load)[:k].sum())
 
 
-def _check(ctx, s, o, M):
+def _check(ctx, s, o, M, alpha=(0, 1)):
     import torch
+    from paper_2508_06133_amd import kvsched
 
     ds, do = torch.from_numpy(s).to("cuda:0"), torch.from_numpy(o).to("cuda:0")
     s, o = s.astype(np.int64), o.astype(np.int64)
     for tie in (0, 1):
-        order_r, ends_r, F_r = _phase1(s, o, M, tie)
-        order, ends, F, nb = ctx.exact_dp(ds, do, M, 0, tie)
+        order_r, ends_r, F_r = _phase1(s, o, M, tie, alpha)
+        if alpha[0]:
+            order, ends, F, _, nb = ctx.phase1_G(kvsched.SOLVER_EXACT_DP, ds, do, M, alpha, tie, 0)
+        else:
+            order, ends, F, nb = ctx.exact_dp(ds, do, M, 0, tie)
         k = int(nb.item())
         assert ctx.device_status() == 0 and k == len(ends_r)
         assert ends.cpu().numpy()[:k].tolist() == ends_r and order.cpu().numpy().tolist() == order_r
@@ -82,3 +86,13 @@ def test_near_ties(ctx, n, largest):
         s, o, M = _near_ties(rng, n, largest)
         print(f"exact_dp, wide loads: n={n} largest={largest} case={case} M={M}", flush=True)
         _check(ctx, s, o, M)
+
+
+@pytest.mark.parametrize("alpha", [(1, 1), (1, 50), (7, 2)])
+def test_near_ties_weighted(ctx, alpha):
+    """Values above 2^24 as well as loads."""
+    rng = np.random.default_rng(alpha[0] + alpha[1])
+    for n in (11, 14):
+        s, o, M = _near_ties(rng, n, 20999999)
+        print(f"exact_dp, wide loads: n={n} M={M} alpha={alpha}", flush=True)
+        _check(ctx, s, o, M, alpha)
