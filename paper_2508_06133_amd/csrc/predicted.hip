@@ -28,12 +28,17 @@
 //     matters: it reaches its estimate or its true length, start + min(estimate, o), or start + o
 //     once it has outrun its estimate.  The start round follows from that (a running request
 //     started at most o <= 16384 rounds ago, so 16 bits and the current round give the round
-//     itself), s from the length table when an entry is handled.  The pass that finds the due entries and the next due
-//     round reads that array alone; an entry that finishes leaves a hole that the list's last entry fills.
+//     itself), s from the length table when an entry is handled.  Entries that finish leave holes, which the others of
+//     their tile of 64 and the list's last entries fill.
 // Lengths and ids of the waiting positions are not kept at all: admission walks the order from the
 // front, so the 64 positions around the first waiting one sit in registers (one position per lane,
 // fetched from the order row and the length tables when the walk leaves the window).
-// What bounds the call is the number of candidates in flight times the chain of dependent instructions each is, so the
+// What bounds the call is the number of candidates in flight times the chain of dependent instructions each is (2000 mixed
+// requests: 400 k vector and 525 k scalar instructions; four candidates share a SIMD, whose scalar unit is 65 % busy, and wait for
+// memory, LDS and branches a third of the time).  Hence no branch of the loop over rounds depends on the lane (see
+// put_entry), tiles of the list are read two at a time, and what scalars would add up entry by entry is added up a lane each:
+// 613 k and 759 k instructions before; 4096 / 256 / 16 candidates 7.58 / 6.42 / 5.10 -> 4.75 / 3.79 / 2.98 ms, 1024 of 2000
+// chat requests 7.94 -> 4.81.  And the
 // list decides how many candidates fit a compute unit: a first launch runs every candidate with a list of at
 // most `cap` entries (launch_variant); a candidate whose list overflows gives up and is run again by a second launch
 // whose list holds all n positions.
@@ -87,12 +92,25 @@ __device__ __forceinline__ void p_sync()
 // 16 lanes, two row broadcasts; lane 63 ends up with the result).
 __device__ __forceinline__ int p_wave_min(int v)
 {
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false));  // row_half_mirror
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false));  // row_mirror
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+    // (lanes that receive nothing compare with the largest number, which lets the exchange be part of the comparison)
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x141, 0xf, 0xf, false));  // row_half_mirror
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x140, 0xf, 0xf, false));  // row_mirror
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Sum over the 64 lanes (modulo 2^32).
+__device__ __forceinline__ int p_wave_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return __builtin_amdgcn_readlane(v, 63);
 }
 
@@ -400,6 +418,56 @@ struct Ring {
     __device__ __forceinline__ int tile(int base, int r) const { return slot[(base + 64 * r + lane + 1) & mask]; }
 };
 
+// A running request: position | id << 16 and o | estimate << 16.
+struct Entry {
+    int pi, oe;
+};
+
+// The LDS address of p (what a ds instruction takes).
+__device__ __forceinline__ unsigned lds_at(const void *p)
+{
+    return (unsigned)(size_t)(const __attribute__((address_space(3))) void *)p;
+}
+
+// Stores of the lanes of `mask`.  A branch that depends on the lane, anywhere in the loop over rounds, makes the compiler
+// carry every way out of the loops around it as flags in scalar registers, and the scalar unit is what the candidates
+// of a SIMD wait for; so lanes are masked here and every branch of the loop is the same for all of them.
+__device__ __forceinline__ void put_entry(unsigned long long mask, const Entry *e, const unsigned short *d, int pi, int oe, int due)
+{
+    unsigned long long all;
+    const unsigned long long v = (unsigned long long)(unsigned)pi | ((unsigned long long)(unsigned)oe << 32);
+    asm volatile("s_and_saveexec_b64 %[all], %[mask]\n"
+                 "ds_write_b64 %[e], %[v]\n"
+                 "ds_write_b16 %[d], %[due]\n"
+                 "s_mov_b64 exec, %[all]\n"
+                 : [all] "=&s"(all)
+                 : [mask] "s"(mask), [e] "v"(lds_at(e)), [v] "v"(v), [d] "v"(lds_at(d)), [due] "v"(due)
+                 : "memory", "scc");
+}
+
+__device__ __forceinline__ void put_word(unsigned long long mask, const unsigned *w, unsigned v)
+{
+    unsigned long long all;
+    asm volatile("s_and_saveexec_b64 %[all], %[mask]\n"
+                 "ds_write_b32 %[w], %[v]\n"
+                 "s_mov_b64 exec, %[all]\n"
+                 : [all] "=&s"(all)
+                 : [mask] "s"(mask), [w] "v"(lds_at(w)), [v] "v"(v)
+                 : "memory", "scc");
+}
+
+__device__ __forceinline__ void put_global(unsigned long long mask, int32_t *base, unsigned byte, int v)
+{
+    unsigned long long all;
+    asm volatile("s_and_saveexec_b64 %[all], %[mask]\n"
+                 "s_nop 4\n"
+                 "global_store_dword %[byte], %[v], %[base]\n"
+                 "s_mov_b64 exec, %[all]\n"
+                 : [all] "=&s"(all)
+                 : [mask] "s"(mask), [base] "s"(base), [byte] "v"(byte), [v] "v"(v)
+                 : "memory", "scc");
+}
+
 template <class Projection>
 __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
 {
@@ -409,9 +477,8 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
     const int n = p.n, M = p.M, cap = p.cap;
     const int stw = (n + 31) >> 5;
     unsigned *WAIT = (unsigned *)(lds + Projection::lds_words(p.H));  // bit k & 31 of word k >> 5: position k waits (below the frontier)
-    int *LPI = (int *)(WAIT + stw);     // the running list
-    int *LOE = LPI + cap;
-    unsigned short *LDUE = (unsigned short *)(LOE + cap);
+    Entry *LE = (Entry *)(WAIT + ((stw + 1) & ~1));  // the running list
+    unsigned short *LDUE = (unsigned short *)(LE + cap);
     unsigned short *est_stopped = p.est_stopped + (size_t)cand * (size_t)n;
 
     const int32_t *row = p.orders + (size_t)cand * (size_t)n;
@@ -452,35 +519,25 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
     int nact = 0;      // entries of the list
     int done = 0;
     int ov_cnt = 0;    // requests past their estimate ...
-    long long ov_sp = 0;  // ... and the sum of s_j - p_j over them
+    unsigned ov_sp = 0;  // ... and the sum of s_j - p_j over them, modulo 2^32 (what they hold together is at most M < 2^30)
     int next_due = INT_MAX;  // earliest round at which a running request reaches its estimate or its end
     int evictions = 0;
     int visited = 0;
-    long long tel = 0;
+    long long tel = 0;  // per lane: completion rounds of the entries it has seen end
     bool over_limit = false, overflow = false;
 
     const int first_last = p.C - p.step_back;  // no other takes the place of the candidates from here on
     while (done < n) {
-        // (everything the loop carries is the same in all lanes; saying so keeps it on the scalar unit)
-        t = p_uni(t), head = p_uni(head), hpos = p_uni(hpos), hs = p_uni(hs), he = p_uni(he), ho = p_uni(ho), hid = p_uni(hid);
-        ring_start = p_uni(ring_start), nact = p_uni(nact), done = p_uni(done), ov_cnt = p_uni(ov_cnt), ov_sp = p_uni64(ov_sp);
-        next_due = p_uni(next_due), evictions = p_uni(evictions), visited = p_uni(visited), tel = p_uni64(tel), frontier = p_uni(frontier);
-        proj.uniform();
-        c_pos = p_uni(c_pos), c_s = p_uni(c_s), c_o = p_uni(c_o), c_id = p_uni(c_id), c_e = p_uni(c_e);
-        w_base = p_uni(w_base), x_base = p_uni(x_base);
         if (t >= p.round_limit) { over_limit = true; break; }
         // A candidate that visits many rounds for each request it finishes (a random order: twice as many as the Sorted-F
-        // order's neighbours) runs longest, and the call lasts as long as it does: it goes first on its SIMD.  Without / from
-        // 1.25 / 1.5 / 2 rounds a request on, 4096 candidates: mixed, lower bounds at gamma 0.6 9.4 / 8.4 to 9.2 / 8.3 / 9.4 ms,
-        // at 0.3 9.5 / 8.8 / 8.8 / 9.6, at 0.95 7.9 / 7.4 / 7.5 / 8.1; 400 chat requests 3.20 / 2.99 / 2.81 / 3.06; 300 mixed 1.82 /
-        // 1.81 / 1.82 / 1.76; 2000 chat requests, upper bounds, 1024 candidates: no difference.
-        // The others go first while they have a quarter of their requests before them, then while they have an eighth: of equal
-        // ones a SIMD serves the oldest, and of its four the youngest took 20.3 M cycles where the oldest took 12.2 M, the last
-        // third of the time with fewer than four.  4096 mixed candidates 8.28 -> 7.58 ms (lines at a half and a quarter 7.66, a
-        // third and two thirds done 7.75, turns of 64 visits 7.79), of 1000 requests 4.87 -> 4.48, 2000 chat requests 10.6 -> 9.8.
-        // Those whose place another candidate takes (all but as many as run at a time) step back in their last eighth only: 6000 /
-        // 8192 / 16384 candidates 13.25 / 16.9 / 31.1 -> 13.0 / 15.6 / 31.0 ms (with the lines of the others 13.4 / 15.5 / 29.7, but
-        // 9000 of 1000 requests 10.6 -> 11.2 ms; never 13.1 / 16.1 / 31.4).  Which calls have these lines: may_step_back.
+        // order's neighbours) runs longest, and the call lasts as long as it does: it goes first on its SIMD.  The others go
+        // first while they have a quarter of their requests before them, then while they have an eighth: of equal ones a SIMD
+        // serves the oldest, and the last third of the time would see fewer than four.  4096 candidates of 2000 mixed requests
+        // without any priority / without the two lines / with them: 5.82 / 5.17 / 4.73 ms, of 1000 3.15 / 2.85 / 2.62, of 300
+        // chat requests 1.66 / 1.64 / 1.64.
+        // Those whose place another candidate takes (all but as many as run at a time) step back in their last eighth only: 6000
+        // of 1000 requests 4.92 / 4.76 / 4.53 ms, 8192 / 16384 of 2000 10.9 / 10.3 / 9.4 and 19.6 / 19.0 / 19.0.  Which calls
+        // have these lines: may_step_back.
         if ((++visited & 63) == 0) {
             if (2 * visited > 3 * done) __builtin_amdgcn_s_setprio(3);
             else if (p.step_back == 0) __builtin_amdgcn_s_setprio(0);
@@ -489,112 +546,114 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
             else __builtin_amdgcn_s_setprio(0);
         }
         // nothing waits, nobody outruns an estimate: nothing can happen before the next due round
-        if (head >= n && ov_cnt == 0 && next_due > t) {
-            proj.advance(t, next_due);
-            t = next_due;
+        if (__builtin_expect(head >= n, 0)) {
+            asm volatile("");  // (three branches, of which the first is hardly ever taken, and not one on all three)
+            if (ov_cnt == 0 && next_due > t) {
+                proj.advance(t, next_due);
+                t = next_due;
+            }
         }
 
         // ---- 1. running requests that reach their estimate or their end at this round: the tiles of the list from the last
         //         to the first (an entry that fills a hole has then been looked at), the due entries of a tile side by side.
         if (t >= next_due) {
-            int wait_min = INT_MAX;  // per lane: rounds until its entries matter again
-            for (int a0 = (nact - 1) & ~(PW - 1); a0 >= 0; a0 -= PW) {
-                const int a = a0 + lane;
-                const bool in = a < nact;
-                const int wait = in ? (int)(short)(unsigned short)(LDUE[a] - t) : INT_MAX;  // due - t (at most 16384 ahead)
-                const bool now = wait <= 0;
-                if (!now) wait_min = min(wait_min, wait);
-                const unsigned long long due = __builtin_amdgcn_ballot_w64(now);
-                if (due == 0) continue;
+            unsigned wait_min = 0x7fffffffu;  // per lane: rounds from t + 1 until its entries matter again
+            unsigned sp_sum = 0;              // per lane: what its entries change ov_sp by
+            // the due entries `due` of the tile at a0; e and wait (rounds from t + 1 until it is due) of the lane's entry
+            auto handle = [&](int a0, unsigned long long in, unsigned long long due, const Entry e, int wait) __attribute__((always_inline)) {
                 // due now: it started min(estimate, o) rounds ago, o rounds ago if it had outrun its estimate
-                int pi = 0, oe = 0, sv = 0;
-                if (now) {
-                    pi = LPI[a];
-                    oe = LOE[a];
-                    sv = p.s[(unsigned)pi >> 16];
+                const int id = (int)((unsigned)e.pi >> 16);
+                const int sv = p.s[__builtin_amdgcn_inverse_ballot_w64(due) ? id : 0];
+                const unsigned ol = e.oe & 0xffff, el = (unsigned)e.oe >> 16;
+                static_assert(EST_OVERRUN == 0, "an estimate of 0 less 1 is the largest");
+                const int ran = (int)min(el - 1u, ol - 1u) + 1;
+                const unsigned long long ends = __builtin_amdgcn_ballot_w64(el - 1u >= ol - 1u) & due;
+                // goes on past its estimate: from now on it reserves the next round only
+                const unsigned long long goes = due & ~ends;
+                const bool on = __builtin_amdgcn_inverse_ballot_w64(goes);
+                const int more = (int)ol - ran;  // (of one that goes on)
+                wait_min = on ? min(wait_min, (unsigned)(more - 1)) : wait_min;
+                const unsigned sp = (unsigned)(sv - t + ran);  // (a running request started at most 16384 rounds ago, s < 2^30)
+                ov_cnt += __popcll(goes);
+                if (ends == 0) {
+                    put_entry(goes, LE + a0 + lane, LDUE + a0 + lane, e.pi, (int)ol, t + more);
+                    sp_sum += on ? sp : 0u;
+                    return;
                 }
-                const int ol = oe & 0xffff, el = (int)((unsigned)oe >> 16);
-                const int ps = t - (el == EST_OVERRUN ? ol : min(el, ol));
-                const bool fin = now && t - ps == ol;
-                const bool on = now && !fin;  // goes on past its estimate: from now on it reserves the next round only
-                if (on) {
-                    LOE[a] = ol;  // (estimate field EST_OVERRUN)
-                    LDUE[a] = (unsigned short)(ps + ol);
-                    wait_min = min(wait_min, ps + ol - t);
-                }
-                if (crow && fin) crow[(unsigned)pi >> 16] = t;
-                const unsigned long long ends = __builtin_amdgcn_ballot_w64(fin), goes = due & ~ends;
-                const unsigned long long leaves = __builtin_amdgcn_ballot_w64(fin && el == EST_OVERRUN);
+                const unsigned long long leaves = ends & __builtin_amdgcn_ballot_w64(el == EST_OVERRUN);
                 const int k = __popcll(ends);
+                tel += __builtin_amdgcn_inverse_ballot_w64(ends) ? t : 0;
                 done += k;
-                tel += (long long)t * k;
-                ov_cnt += __popcll(goes) - __popcll(leaves);
-                const int sp = sv - ps;  // (a running request started at most 16384 rounds ago, s < 2^30)
-                for (unsigned long long m = goes | leaves; m != 0; m &= m - 1) {
+                ov_cnt -= __popcll(leaves);
+                if (crow) put_global(ends, crow, (unsigned)id * 4u, t);
+                // the entries that stay move together within the tile, the list's last ones behind them
+                const unsigned long long stay = in & ~ends;
+                const int to = a0 + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(stay >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)stay, 0));
+                put_entry(stay, LE + to, LDUE + to, e.pi, on ? (int)ol : e.oe, on ? t + more : wait + t + 1);
+                const int tail = min(k, nact - (a0 + PW));
+                if (tail > 0) {
+                    const int from = min(nact - tail + lane, nact - 1), hole = a0 + PW - k + lane;
+                    const Entry f = LE[from];
+                    put_entry(~0ull >> (PW - tail), LE + hole, LDUE + hole, f.pi, f.oe, LDUE[from]);
+                }
+                nact -= k;
+                // over-estimated: rounds t+1 .. p + e were reserved for it
+                for (unsigned long long m = ends & __builtin_amdgcn_ballot_w64(el > ol); m != 0; m &= m - 1) {
                     const int l = __builtin_ctzll(m);
-                    const long long v = __builtin_amdgcn_readlane(sp, l);
-                    ov_sp += (goes >> l) & 1ull ? v : -v;
+                    const int ps_l = t - __builtin_amdgcn_readlane((int)ol, l);
+                    proj.take(t, __builtin_amdgcn_readlane(sv, l), ps_l, ps_l + __builtin_amdgcn_readlane((int)el, l));
+                    ring_start = 0;  // memory released: the blocked request may fit earlier
                 }
-                for (unsigned long long m = ends & ~leaves; m != 0; m &= m - 1) {
-                    // over-estimated (or exact: nothing left): rounds t+1 .. p + e were reserved for it
-                    const int l = __builtin_ctzll(m);
-                    const int ps_l = __builtin_amdgcn_readlane(ps, l), last = ps_l + __builtin_amdgcn_readlane(el, l);
-                    if (last > t) {
-                        proj.take(t, __builtin_amdgcn_readlane(sv, l), ps_l, last);
-                        ring_start = 0;  // memory released: the blocked request may fit earlier
-                    }
-                }
-                if (k > 0) {
-                    // the entries behind the first nact - k places that stay fill the holes before them
-                    const int left = nact - k;
-                    const int mp = left + lane;  // a place that goes away
-                    const bool stays = lane < k && !(mp >= a0 && mp < a0 + PW && ((ends >> (mp - a0)) & 1ull));
-                    unsigned long long movers = __builtin_amdgcn_ballot_w64(stays);
-                    unsigned long long hm = __builtin_amdgcn_ballot_w64(fin && a < left);
-                    while (hm != 0) {  // (as many holes as movers)
-                        const int to = a0 + __builtin_ctzll(hm), from = left + __builtin_ctzll(movers);
-                        hm &= hm - 1;
-                        movers &= movers - 1;
-                        if (lane == 0) {
-                            const int e0 = LPI[from], e1 = LOE[from];
-                            const unsigned short e2 = LDUE[from];
-                            LPI[to] = e0, LOE[to] = e1, LDUE[to] = e2;
-                        }
-                    }
-                    nact = left;
-                    p_sync();
-                }
+                sp_sum += on ? sp : 0u;
+                sp_sum -= __builtin_amdgcn_inverse_ballot_w64(leaves) ? sp : 0u;
+            };
+            // two tiles a turn, all their reads in flight together (a tile takes longer to read than to look at)
+            unsigned long long in1 = ~0ull >> (63 - ((nact - 1) & 63));  // the lanes of the tile that hold an entry
+            for (int a1 = (nact - 1) & ~(PW - 1); a1 >= 0; a1 -= 2 * PW, in1 = ~0ull) {
+                const int i1 = min(a1 + lane, nact - 1), i0 = max(a1 - PW, 0) + lane;
+                const unsigned short d1 = LDUE[i1], d0 = LDUE[min(i0, nact - 1)];
+                Entry e1 = LE[i1], e0 = LE[min(i0, nact - 1)];
+                asm volatile("" : "+v"(e1.pi), "+v"(e1.oe), "+v"(e0.pi), "+v"(e0.oe));  // (read now, needed or not)
+                const int w1 = (int)(short)(unsigned short)(d1 - (unsigned short)(t + 1));  // due - t - 1 (at most 16383)
+                const int w0 = (int)(short)(unsigned short)(d0 - (unsigned short)(t + 1));
+                wait_min = min(wait_min, min((unsigned)w1, (unsigned)w0));  // (-1, due now: the largest)
+                const unsigned long long due1 = __builtin_amdgcn_ballot_w64(w1 < 0) & in1;
+                const unsigned long long due0 = __builtin_amdgcn_ballot_w64(w0 < 0) & (a1 > 0 ? ~0ull : 0ull);
+                if (due1 != 0) handle(a1, in1, due1, e1, w1);
+                if (due0 != 0) handle(a1 - PW, ~0ull, due0, e0, w0);
             }
-            const int w = p_wave_min(wait_min);
-            next_due = w == INT_MAX ? INT_MAX : t + w;
-            p_sync();
+            const int w = p_wave_min((int)wait_min);
+            next_due = w == INT_MAX ? INT_MAX : t + 1 + w;
+            ov_sp += (unsigned)p_wave_sum((int)sp_sum);
         }
 
         // ---- 2. admission in the order's sequence
-        const int ov_next = (int)(ov_sp + (long long)ov_cnt * (t + 1));  // the overrunners' share of round t + 1
+        int room = 0;  // of round t + 1 (while some are past their estimate: without them the reservations alone decide)
+        if (ov_cnt > 0) room = M - proj.next_round(t) - (int)(ov_sp + (unsigned)ov_cnt * (unsigned)(t + 1));
         int t_skip = t + 1;  // the next round at which anything can happen
         while (head < n) {
-            head = p_uni(head), hpos = p_uni(hpos), frontier = p_uni(frontier), nact = p_uni(nact), next_due = p_uni(next_due);
-            ring_start = p_uni(ring_start), t_skip = p_uni(t_skip);
             if (hpos < 0) {  // first waiting position at or after head; kept while it stays blocked
+                hpos = head;
                 if (head < frontier) {  // among the stopped ones: 32 positions a lane, 2048 a turn
-                    for (int w0 = head >> 5; w0 < stw && hpos < 0; w0 += PW) {
+                    hpos = frontier;  // none: the first position never started
+                    for (int w0 = head >> 5; w0 < stw; w0 += PW) {
                         const int wi = w0 + lane;
-                        unsigned wait = wi < stw ? WAIT[wi] : 0u;
-                        if (wi == (head >> 5)) wait &= ~0u << (head & 31);  // not before head
+                        unsigned wait = WAIT[min(wi, stw - 1)];
+                        wait = wi < stw ? wait : 0u;
+                        wait &= wi == (head >> 5) ? ~0u << (head & 31) : ~0u;  // not before head
                         const unsigned long long any = __builtin_amdgcn_ballot_w64(wait != 0);
                         if (any != 0) {
                             const int l = __builtin_ctzll(any);
                             hpos = (w0 + l) * 32 + __builtin_ctz((unsigned)__builtin_amdgcn_readlane((int)wait, l));
+                            break;
                         }
                     }
-                    if (hpos < 0) hpos = frontier;  // none: the first position never started
-                } else {
-                    hpos = head;
                 }
-                hpos = p_uni(hpos);
-                if (hpos >= n) { hpos = -1; head = n; break; }
                 head = hpos;
+                if (hpos >= n) {
+                    hpos = -1;
+                    break;
+                }
                 if (hpos == c_pos) {
                     // the request stopped last: what admission needs of it was at hand when it was stopped
                     hs = c_s, ho = c_o, hid = c_id, he = c_e;
@@ -605,30 +664,22 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                     ho = p_uni(p.o[hid]);
                     he = p_uni((int)est_stopped[hpos]);  // a stopped request kept its estimate
                 } else {
-                    if (hpos < w_base || hpos >= w_base + PW) {  // the 64 positions around it
+                    if ((unsigned)(hpos - w_base) >= (unsigned)PW) {  // the 64 positions around it
                         const int base = hpos & ~(PW - 1);
                         if (base == x_base) {  // fetched ahead
                             w_id = x_id, w_s = x_s, w_o = x_o, w_e = x_e;
                         } else {
-                            const int k = base + lane;
-                            w_id = 0, w_s = 1, w_o = 1, w_e = 1;
-                            if (k < n) {
-                                w_id = min(max(row[k], 0), n - 1);
-                                w_s = p.s[w_id];
-                                w_o = p.o[w_id];
-                                w_e = est0[w_id];
-                            }
+                            w_id = min(max(row[min(base + lane, n - 1)], 0), n - 1);
+                            w_s = p.s[w_id];
+                            w_o = p.o[w_id];
+                            w_e = est0[w_id];
                         }
                         w_base = base;
                         x_base = base + PW;  // the loads for the next 64 are issued now and waited for when used
-                        const int k = x_base + lane;
-                        x_id = 0, x_s = 1, x_o = 1, x_e = 1;
-                        if (k < n) {
-                            x_id = min(max(row[k], 0), n - 1);
-                            x_s = p.s[x_id];
-                            x_o = p.o[x_id];
-                            x_e = est0[x_id];
-                        }
+                        x_id = min(max(row[min(x_base + lane, n - 1)], 0), n - 1);
+                        x_s = p.s[x_id];
+                        x_o = p.o[x_id];
+                        x_e = est0[x_id];
                     }
                     hs = __builtin_amdgcn_readlane(w_s, hpos - w_base);
                     ho = __builtin_amdgcn_readlane(w_o, hpos - w_base);
@@ -643,7 +694,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
             }
             // The requests past their estimate hold round t + 1 as well; that test is one slot, so it
             // goes first (when it fails no request starts this round, whatever the reservations say).
-            if (ov_cnt > 0 && proj.next_round(t) + ov_next + hs + 1 > M) break;
+            if (ov_cnt > 0 && hs >= room) break;
             if (nact == cap) { overflow = true; break; }  // (first launch only: the second one's list holds every position)
             // A start at t against the reservations, the request's own entered in the same pass and
             // taken back if some round cannot hold them (rare: the verdict is known for a blocked request).
@@ -657,7 +708,6 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                 int start = t, lo = t + 1;
                 const int bias = hs - M;
                 for (;;) {
-                    start = p_uni(start), lo = p_uni(lo);
                     const int hi = min(start + he, t + proj.longest());
                     const int bound = -p_wave_min(-proj.bound(lo, hi, bias));
                     if (bound <= start) break;  // fits at `start`
@@ -670,100 +720,110 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                 break;
             }
             ring_start = t;  // a start is allowed now
-            if (lane == 0) {
-                if (hpos < frontier) WAIT[hpos >> 5] &= ~(1u << (hpos & 31));  // a stopped one starts again
-                LPI[nact] = hpos | (hid << 16), LOE[nact] = ho | (he << 16);
-                LDUE[nact] = (unsigned short)(t + min(he, ho));
+            room -= hs + 1;
+            if (hpos < frontier) {  // a stopped one starts again
+                const unsigned *w = WAIT + (hpos >> 5);
+                put_word(1, w, *w & ~(1u << (hpos & 31)));
             }
-            if (hpos >= frontier) frontier = hpos + 1;
+            const int until = t + min(he, ho);
+            put_entry(1, LE + nact, LDUE + nact, hpos | (hid << 16), ho | (he << 16), until);
+            frontier = max(frontier, hpos + 1);
             ++nact;
-            next_due = min(next_due, t + min(he, ho));
+            next_due = min(next_due, until);
             head = hpos + 1;
             hpos = -1;
-            p_sync();
         }
         if (overflow) break;
 
         // ---- 3. eviction while round t + 1 is projected above M (only that round can be: the reservations
         //         held a feasible projection and only the overrunners' are new)
         if (ov_cnt > 0) {
-            p_sync();
-            while (proj.next_round(t) + (int)(ov_sp + (long long)ov_cnt * (t + 1)) > M) {
-                nact = p_uni(nact), ov_cnt = p_uni(ov_cnt), ov_sp = p_uni64(ov_sp), head = p_uni(head), hpos = p_uni(hpos);
+            while (room < 0) {
                 int best = INT_MAX, best_at = -1;  // (current estimate, id) of the running requests, least first, and its place
-                for (int a0 = 0; a0 < nact; a0 += PW) {
-                    const int a = a0 + lane;
-                    if (a < nact) {
-                        const int oe = LOE[a];
-                        const int ev = (int)((unsigned)oe >> 16);
+                for (int a0 = 0; a0 < nact; a0 += 2 * PW) {  // two tiles a turn, as above
+                    int at[2];
+                    Entry e[2];
+                    unsigned short due[2];
+                    for (int h = 0; h < 2; ++h) {
+                        at[h] = min(a0 + h * PW + lane, nact - 1);
+                        e[h] = LE[at[h]];
+                        due[h] = LDUE[at[h]];
+                    }
+                    for (int h = 0; h < 2; ++h) {
+                        const int ev = (int)((unsigned)e[h].oe >> 16);
                         // past its estimate: it has run o - (due - t) rounds and needs one more
-                        const int cur = ev == EST_OVERRUN ? (oe & 0xffff) - (int)(unsigned short)(LDUE[a] - (unsigned short)t) + 1 : ev;
-                        const int key = (cur << 16) | (int)((unsigned)LPI[a] >> 16);
-                        if (key < best) best = key, best_at = a;
+                        const int out = (e[h].oe & 0xffff) - (int)(unsigned short)(due[h] - (unsigned short)t) + 1;
+                        const int key = ((ev == EST_OVERRUN ? out : ev) << 16) | (int)((unsigned)e[h].pi >> 16);
+                        best_at = key < best ? at[h] : best_at;
+                        best = min(best, key);
                     }
                 }
                 const int least = p_wave_min(best);
                 if (least == INT_MAX) break;  // cannot happen: an empty system holds nothing
-                // ids of a permutation are distinct: one lane holds it
+                // ids of a permutation are distinct: one entry holds it
                 const unsigned long long holder = __builtin_amdgcn_ballot_w64(best == least);
                 const int slot = __builtin_amdgcn_readlane(best_at, __builtin_ctzll(holder));
                 if (slot < 0) break;
                 const int sv = p_uni(p.s[least & 0xffff]);
-                const int pi_r = p_uni(LPI[slot]), oe_r = p_uni(LOE[slot]), due16 = p_uni(LDUE[slot]);
+                const Entry er = LE[slot];
+                const int pi_r = p_uni(er.pi), oe_r = p_uni(er.oe), due16 = p_uni(LDUE[slot]);
                 const int vpos = pi_r & 0xffff;
                 const int ev = (int)((unsigned)oe_r >> 16), ov = oe_r & 0xffff;
                 const int due = t + (int)(unsigned short)((unsigned short)due16 - (unsigned short)t);
                 const int ps = due - (ev == EST_OVERRUN ? ov : min(ev, ov));
+                room += sv + t + 1 - ps;
                 if (ev == EST_OVERRUN) {
                     --ov_cnt;
-                    ov_sp -= (long long)sv - ps;
+                    ov_sp -= (unsigned)(sv - ps);
                 } else {
                     proj.take(t, sv, ps, ps + ev);
                     ring_start = 0;  // memory released
                 }
-                p_sync();
                 c_pos = vpos, c_s = sv, c_o = ov, c_id = (int)((unsigned)pi_r >> 16);
                 c_e = ev == EST_OVERRUN ? t - ps + 1 : ev;  // what it is known to need
-                if (lane == 0) {
-                    est_stopped[vpos] = (unsigned short)c_e;
-                    WAIT[vpos >> 5] |= 1u << (vpos & 31);  // waits again
-                    const int e0 = LPI[nact - 1], e1 = LOE[nact - 1];
-                    const unsigned short e2 = LDUE[nact - 1];
-                    LPI[slot] = e0, LOE[slot] = e1, LDUE[slot] = e2;
-                }
+                est_stopped[vpos] = (unsigned short)c_e;
+                const unsigned *w = WAIT + (vpos >> 5);
+                put_word(1, w, *w | 1u << (vpos & 31));  // waits again
                 --nact;
+                const Entry last = LE[nact];
+                put_entry(1, LE + slot, LDUE + slot, last.pi, last.oe, LDUE[nact]);
                 if (vpos < head) { head = vpos; hpos = -1; }
                 ++evictions;
-                p_sync();
             }
         }
         // While requests outrun their estimates the projection of round t' + 1 grows by their count
         // every round; until the next due round nothing else changes.  Round t' needs work only if
         // that projection passes M (eviction) or, from the round on that the reservations allow the blocked
         // request to start at, leaves room for its first token (both necessary for its admission):
-        // find the first such round.
+        // find the first such round.  (They hold at most M < 2^30 now and 65535 * 16384 more at the next due round.)
         if (ov_cnt > 0 && (hpos >= 0 || head >= n) && next_due > t + 1) {
-            const int room = hpos >= 0 ? hs + 1 : INT_MAX / 2;  // nothing waits: only the overflow matters
-            const int from = hpos >= 0 ? ring_start : INT_MAX;
-            int found = next_due;
+            const unsigned first = hpos >= 0 ? hs + 1 : 1;
+            const int from = hpos >= 0 ? ring_start : INT_MAX;  // (nothing waits: only the overflow matters)
+            t_skip = next_due;
             const int base = proj.first_tile(t);
+            int tr = base + lane;
+            unsigned held = ov_sp + (unsigned)ov_cnt * (unsigned)(tr + 1);
             for (int r = 0; base + 64 * r < next_due; ++r) {
-                const int tr = base + 64 * r + lane;
-                const long long x = (long long)proj.tile(base, r) + ov_sp + (long long)ov_cnt * (tr + 1);
-                const bool hit = tr > t && tr < next_due && (x > (long long)M || (tr >= from && x + room <= (long long)M));
-                const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+                const unsigned left = (unsigned)(M - proj.tile(base, r));
+                const unsigned long long out = __builtin_amdgcn_ballot_w64(held > left);
+                const unsigned long long fits = __builtin_amdgcn_ballot_w64(held + first <= left) & __builtin_amdgcn_ballot_w64(tr >= from);
+                const unsigned long long m = (out | fits) & __builtin_amdgcn_ballot_w64((unsigned)(tr - t - 1) < (unsigned)(next_due - t - 1));
                 if (m != 0) {
-                    found = base + 64 * r + __builtin_ctzll(m);
+                    t_skip = base + 64 * r + __builtin_ctzll(m);
                     break;
                 }
+                tr += 64;
+                held += 64u * (unsigned)ov_cnt;
             }
-            t_skip = found;
         }
-        const int to = p_uni(max(t_skip, t + 1));  // rounds t + 1 .. to - 1 change nothing
+        const int to = max(t_skip, t + 1);  // rounds t + 1 .. to - 1 change nothing
         proj.advance(t, to);
         t = to;
     }
 
+    // the lanes' completion rounds, 21 bits at a time (64 lanes of 2^21 - 1 stay below 2^31)
+    long long total = 0;
+    for (int bit = 42; bit >= 0; bit -= 21) total = (total << 21) + p_wave_sum((int)((unsigned long long)tel >> bit) & 0x1fffff);
     if (lane == 0) {
         if (overflow) {
             p.retry[cand] = 1;  // the second launch runs this candidate with a list of n entries
@@ -772,7 +832,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                 p.tel_out[cand] = -1;
                 atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_ROUND_LIMIT);
             } else {
-                p.tel_out[cand] = tel;
+                p.tel_out[cand] = total;
             }
             if (p.evictions_out) p.evictions_out[cand] = evictions;
         }
@@ -826,13 +886,16 @@ static size_t lds_bytes(int32_t n, int32_t ring, int32_t cap, int32_t entry = 10
     return sizeof(int) * ((size_t)ring + (((size_t)n + 31) >> 5)) + (size_t)entry * (size_t)cap;
 }
 
+// ... as launched: the entries lie at a multiple of eight bytes.
+static size_t lds_taken(int32_t n, int32_t ring, int32_t cap) { return lds_bytes((n + 63) & ~63, ring, cap); }
+
 // For C candidates of `bytes` of LDS each: how many run at a time on 256 compute units if they step back near their ends, or 0.
-// Sixteen per unit is the most that counts: with short lists a few more fit, but 6000 / 7000 candidates of 400 chat requests take
-// 3.92 / 4.30 ms with 4096, 4.00 / 4.35 with the 5120 that run.  The second launch has whole lists; which of its candidates
+// Sixteen per unit is the most that counts: with short lists a few more fit, but with the kernel of the time 6000 / 7000 candidates of
+// 400 chat requests took 3.92 / 4.30 ms with 4096, 4.00 / 4.35 with the 5120 that run.  The second launch has whole lists; which of its candidates
 // run is not known here, and it goes by the case that all do (as if others took the places of all of them: up to 1 % slower).
 // Not where the last ones are a quarter or fewer, one for each SIMD: they start when the first end, and equal progress
-// ends all the others at once and late.  1000 mixed requests, 4200 / 5000 / 9000 candidates with the lines 7.05 / 7.23 / 10.86 ms,
-// without 6.68 / 6.97 / 10.60; 5300 / 6000 / 9800 the other way, 7.40 / 7.56 / 11.25 and 7.47 / 7.83 / 11.36.
+// ends all the others at once and late.  1000 mixed requests, 4200 / 5000 / 9000 candidates with the lines 4.18 / 4.33 / 6.73 ms,
+// without 3.95 / 4.15 / 6.37; 6000 the other way, 4.53 and 4.76.
 static int32_t may_step_back(int32_t C, size_t bytes)
 {
     const int32_t by_lds = (int32_t)((160 * 1024) / ((bytes + 1023) & ~(size_t)1023));
@@ -845,7 +908,7 @@ static int32_t may_step_back(int32_t C, size_t bytes)
 static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
 {
     const int32_t cap_all = (p.n + 1) & ~1;
-    const size_t bytes_all = lds_bytes(p.n, 0, cap_all), fixed = lds_bytes(p.n, 0, 0), budget = 10 * 1024;
+    const size_t bytes_all = lds_taken(p.n, 0, cap_all), fixed = lds_taken(p.n, 0, 0), budget = 10 * 1024;
     const int32_t cap_first = fixed < budget ? (int32_t)((budget - fixed) / 10) & ~1 : 0;
     // beyond 64 KB of dynamic LDS the kernel's limit has to be raised first
     if (bytes_all > 64 * 1024 &&
@@ -854,9 +917,9 @@ static int launch_rows(const void *kernel, PredParams p, hipStream_t st)
     auto launch = [&](int32_t cap, int32_t second) {
         p.cap = cap;
         p.second = second;
-        p.step_back = may_step_back(p.C, lds_bytes(p.n, 0, cap));
+        p.step_back = may_step_back(p.C, lds_taken(p.n, 0, cap));
         void *args[] = {&p};
-        return hipLaunchKernel(kernel, dim3((unsigned)p.C), dim3(PW), args, lds_bytes(p.n, 0, cap), st) == hipSuccess;
+        return hipLaunchKernel(kernel, dim3((unsigned)p.C), dim3(PW), args, lds_taken(p.n, 0, cap), st) == hipSuccess;
     };
     if (cap_first >= 128 && cap_first < cap_all && p.retry) {
         hipLaunchKernelGGL(clear_retry_kernel, dim3((unsigned)((p.C + 255) / 256)), dim3(256), 0, st, p.retry, p.C);
@@ -874,7 +937,7 @@ static int launch_ring(const void *kernel, PredParams p, hipStream_t st)
     p.cap = (p.n + 1) & ~1;
     p.second = 0;
     p.step_back = 0;
-    const size_t bytes = lds_bytes(p.n, p.H, p.cap);
+    const size_t bytes = lds_taken(p.n, p.H, p.cap);
     if (bytes > 64 * 1024 &&
         hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
         return KVSCHED_EHIP;
