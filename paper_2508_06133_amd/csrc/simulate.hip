@@ -170,6 +170,7 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
     words[KVS_W_OMAX] = mx;
     words[KVS_W_MINPOS] = lowest;
     words[KVS_W_MAXPOS] = top;
+    words[KVS_W_ESTMAX] = 0;
     if (host) {
         host[KVS_H_OMAX] = mx;
         host[KVS_H_MINPOS] = lowest;
