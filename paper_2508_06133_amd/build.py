@@ -31,7 +31,8 @@ DEVICE_FLAGS = [
 # Branches that all lanes of a wavefront take together stay branches: by default every way out of a loop becomes a flag in
 # scalar registers, tested later.  For the kernels whose main loop has no other branches (4096 candidates of
 # predicted.hip 5.9 ms without, 5.1 with it); elsewhere it makes no difference.
-SOURCE_FLAGS = {"predicted.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+UNIFORM_BRANCHES = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
+SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES}
 FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall", "-Wno-unused-function"]
 RESERVED_VGPR_BASE = 30  # KVS_PB in timeline_reg.hip
 PREDICTED_VGPR_BASE = 60  # KVP_PB in predicted.hip

@@ -34,6 +34,7 @@
 //     = longest prefix by a saturating wave scan; an exchange step = exclusive prefix minimum of
 //     o over non-members, and its records against all members at once).
 #include "kvsched_internal.h"
+#include "lane_mask.h"
 #include "phase1_util.h"
 
 #include <limits.h>
@@ -120,14 +121,17 @@ constexpr int DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, 
 constexpr int DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;  // last lane of a row -> the next row(s)
 constexpr int DPP_WAVE_SHR1 = 0x138;                      // every lane from the lane below, across rows
 
-// After these four steps every lane of a 16-lane row holds the row's total.
-#define KVS_ROW_BUTTERFLY(v, OP)                      \
-    v = OP(v, dpp<DPP_QUAD_1032>(v, v));              \
-    v = OP(v, dpp<DPP_QUAD_2301>(v, v));              \
-    v = OP(v, dpp<DPP_HALF_MIRROR>(v, v));            \
-    v = OP(v, dpp<DPP_MIRROR>(v, v));
-
-__device__ __forceinline__ int op_max(int a, int b) { return max(a, b); }
+// (lanes that receive nothing take the operation's neutral value, which lets the exchange be part of the operation)
+__device__ __forceinline__ int wave_min(int v)
+{
+    v = min(v, dpp<DPP_QUAD_1032>(INT_MAX, v));
+    v = min(v, dpp<DPP_QUAD_2301>(INT_MAX, v));
+    v = min(v, dpp<DPP_HALF_MIRROR>(INT_MAX, v));
+    v = min(v, dpp<DPP_MIRROR>(INT_MAX, v));
+    v = min(v, dpp<DPP_BCAST15, 0xa>(INT_MAX, v));
+    v = min(v, dpp<DPP_BCAST31, 0xc>(INT_MAX, v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
 
 __device__ __forceinline__ long long wave_sum64(long long v)
 {
@@ -137,9 +141,13 @@ __device__ __forceinline__ long long wave_sum64(long long v)
 
 __device__ __forceinline__ int wave_max(int v)
 {
-    KVS_ROW_BUTTERFLY(v, op_max)
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+    v = max(v, dpp<DPP_QUAD_1032>(INT_MIN, v));
+    v = max(v, dpp<DPP_QUAD_2301>(INT_MIN, v));
+    v = max(v, dpp<DPP_HALF_MIRROR>(INT_MIN, v));
+    v = max(v, dpp<DPP_MIRROR>(INT_MIN, v));
+    v = max(v, dpp<DPP_BCAST15, 0xa>(INT_MIN, v));
+    v = max(v, dpp<DPP_BCAST31, 0xc>(INT_MIN, v));
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Inclusive prefix scans over the 64 lanes: within rows by shifts of 1, 2, 4, 8, then the last
@@ -171,16 +179,22 @@ __device__ __forceinline__ int wave_incl_min(int v)
 
 __device__ __forceinline__ int first_lane(u64 ballot) { return __ffsll((long long)ballot) - 1; }
 
-// number of entries of the ascending array a[0..n) that are < key
+// number of entries of the ascending array a[0..n) that are < key (n >= 1; the same number of steps in every lane)
 __device__ __forceinline__ int lower_bound_u64(const u64 *a, int n, u64 key)
 {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1;
-        else hi = mid;
+    int lo = 0;
+    for (int w = 1 << (31 - __builtin_clz(n)); w > 0; w >>= 1) {
+        const bool less = lo + w <= n && a[min(lo + w, n) - 1] < key;
+        lo = less ? lo + w : lo;
     }
     return lo;
+}
+
+__device__ __forceinline__ u64 lanes_from(int first) { return first >= 64 ? 0ull : ~0ull << first; }
+__device__ __forceinline__ u64 lanes_upto(int count) { return count >= 64 ? ~0ull : ~(~0ull << count); }  // count >= 0
+__device__ __forceinline__ int rank_in(u64 mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
 }
 
 // ------------------------------------------------- Sorted-F-Online's look-ahead window
@@ -202,13 +216,36 @@ __device__ __forceinline__ int lower_bound_u64(const u64 *a, int n, u64 key)
 // still fits has less o than it, so all members are tested against one record after the other (a prefix minimum in LDS with a binary search per member took three times as long).
 //
 // plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
-// bkey: an idle array of >= m keys, an even number.
+// bkey: an idle array of >= m keys, an even number.  With one row the batch stays where it is, in the lanes (`batch`): admission
+// mostly takes one or two requests of a batch before the next refresh, so the batch is not sorted but the least (o, id) looked for
+// when it is asked for, and wk is closed up when a next batch is.
 // m <= 64 RMAX.  One and two rows, where the paper's backlogs fit, keep the whole state in scalar and vector registers
 // without a test per row: an exchange on one row takes 960 cycles, on two 1250 (a longest stream of 457 requests has 1580 of them;
 // 600 streams 2.75 -> 2.56 ms with a variant of its own for one row).  They are a chain of moves between lanes, scalars
 // and masks, ten cycles an instruction: four records at a time or masks in place of the vector minima are slower.
+struct Batch {
+    u64 key;     // this lane's request of the window ...
+    unsigned o;  // ... and its o while it is in the batch and has not been asked for (else NO_O)
+    u64 others;  // the lanes whose requests are not in the batch
+};
+constexpr unsigned NO_O = 0x7fffffffu;
+
+// The batch's next request: least (o, id) of those not asked for yet (there is one).
+__device__ __forceinline__ u64 take_next(Batch &b)
+{
+    const unsigned least = (unsigned)wave_min((int)b.o);
+    u64 who = __builtin_amdgcn_ballot_w64(b.o == least);
+    if ((who & (who - 1)) != 0) {
+        const int id = __builtin_amdgcn_inverse_ballot_w64(who) ? (int)(b.key & 0xfffffu) : INT_MAX;
+        who = __builtin_amdgcn_ballot_w64(id == wave_min(id)) & who;
+    }
+    const int l = first_lane(who) & 63;
+    b.o = lane_id() == l ? NO_O : b.o;
+    return lane_u64(b.key, l);
+}
+
 template <int RMAX>
-__device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 *list)
+__device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 *list, Batch &batch)
 {
     constexpr u64 LOW34 = (1ull << 34) - 1;  // (o, id) of a key
     constexpr unsigned IN = 0x80000000u, NONE = 0x7fffffffu;
@@ -223,6 +260,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         if (r < R) {
             const bool is = 64 * r + lane < m;
             const u64 k = wk[min(64 * r + lane, m - 1)];
+            if (RMAX == 1) batch.key = k;
             w[r] = is ? (int)(k >> 34) : 0;
             v[r] = is ? (unsigned)(k >> 20) & 0x3fffu : NONE;
         }
@@ -239,7 +277,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
             const unsigned incl = min(wave_incl_add_sat((unsigned)w[r], cap) + carry, cap);
             const bool in = v[r] != NONE && incl <= (unsigned)M;
             o_most = max(o_most, in ? v[r] : 0u);
-            if (in) v[r] |= IN;
+            v[r] |= in ? IN : 0u;
             const int c = __popcll(__builtin_amdgcn_ballot_w64(in));
             K += c;
             if (c > 0) {
@@ -340,18 +378,23 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         w_most = max(w_most, w_in);
     }
 
+    if (RMAX == 1) {
+        const u64 members = __builtin_amdgcn_ballot_w64(v[0] >= IN);
+        batch.o = v[0] >= IN ? v[0] & ~IN : NO_O;
+        batch.others = __builtin_amdgcn_ballot_w64(v[0] < NONE);
+        return __popcll(members);
+    }
     // the batch in nondecreasing o, ties by id: rank of each member among the members
     int nmem = 0;
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         if (r < R) {
-            const bool is_mem = v[r] >= IN;
-            const u64 bal = __builtin_amdgcn_ballot_w64(is_mem);
-            if (is_mem) bkey[nmem + __popcll(bal & lanes_below())] = wk[64 * r + lane];
+            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] >= IN);
+            put_b64(bal, bkey + nmem + rank_in(bal), wk[min(64 * r + lane, m - 1)]);
             nmem += __popcll(bal);
         }
     }
-    if ((nmem & 1) && lane == 0) bkey[nmem] = ~0ull;  // (the loop below takes them two by two)
+    if (nmem & 1) put_b64(1, bkey + nmem, ~0ull);  // (the loop below takes them two by two)
     wave_sync();
     for (int i0 = 0; i0 < nmem; i0 += 64) {
         const u64 mine = bkey[min(i0 + lane, nmem - 1)];
@@ -359,7 +402,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         int rank = 0;
 #pragma unroll 4
         for (int j = 0; j < nmem; j += 2) rank += ((bkey[j] & LOW34) < me ? 1 : 0) + ((bkey[j + 1] & LOW34) < me ? 1 : 0);
-        if (i0 + lane < nmem) list[rank] = mine;
+        put_b64(lanes_upto(nmem - i0), list + rank, mine);
     }
     wave_sync();
     // what remains closes up in place, still sorted: row by row, each row read before it is
@@ -368,11 +411,10 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         if (r < R) {
-            const bool keep = v[r] < NONE;
             const u64 k = wk[min(64 * r + lane, m - 1)];
-            const u64 bal = __builtin_amdgcn_ballot_w64(keep);
+            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < NONE);
             wave_sync();
-            if (keep) wk[kept + __popcll(bal & lanes_below())] = k;
+            put_b64(bal, wk + kept + rank_in(bal), k);
             kept += __popcll(bal);
             wave_sync();
         }
@@ -456,12 +498,10 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         if (lane == 0) stats[0] = stats[1] = stats[2] = stats[3] = 0;
         return;
     }
-    const int H = p.H, HM = H - 1, M = p.M;
-    const int32_t *a = p.a + begin, *s = p.s + begin, *o = p.o + begin;
-    int32_t *cout = p.completion_out + outb;
+    const int H = p.H, HM = max(H, 256) - 1, M = p.M;  // (the ring has 256 slots or more)
     const Codec codec(planner);
 
-    for (int i = lane; i < H; i += 64) L.ring[i] = 0;
+    for (int i = lane; i <= HM; i += 64) L.ring[i] = 0;
     for (int i = lane; i < QCAP / 32; i += 64) L.dead[i] = 0;
     wave_sync();
 
@@ -471,146 +511,186 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
     int head = 0;          // list entries are list[(head + i) & QM], i < q
     int planned_left = 0;  // leading list entries that were placed by the last refresh
     int known = 0, started = 0;
-    int wn = 0, planned = 0;  // window of the last refresh, and how many of its entries are planned (list[0 ... planned))
+    int wn = 0, planned = 0;  // window of the last refresh, and how many of its entries are planned ...
+    int listed = 0;           // ... and of these in list[0 ... listed); the others are still in `batch`
+    Batch batch = {0, NO_O, 0};
     int t_plan = 0, backlog_at_plan = 0;
     u64 blocked = ~0ull;   // the last request that did not fit, and a round before which it cannot start
     int blocked_to = 0;
-    long long refreshes = 0, sum_c = 0, sum_a = 0;  // sum_a: this lane's share
-    int last_c = 0, max_backlog = 0;
+    // What is seldom looked at lives in vector registers, though it is the same in all lanes: there are not scalar registers enough
+    // for everything, and the compiler would move others to and fro.
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    long long refreshes = zero, sum_c = zero, sum_a = zero;  // sum_a: this lane's share
+    int last_c = zero, max_backlog = zero;
+    const int32_t *a = p.a + begin + zero, *s = p.s + begin + zero, *o = p.o + begin + zero;
+    int32_t *cout = p.completion_out + outb + zero;
     // the next up to 64 requests, one per lane (arrivals find them without waiting for memory)
-    struct { int a, s, o, bad; } ahead;
+    struct { int a, bad; u64 key; } ahead;
     int ahead_at = 0;
-    auto read_ahead = [&]() {
+    auto read_ahead = [&]() __attribute__((always_inline)) {
         ahead_at = known;
-        const int idx = known + lane;
-        ahead.a = INT_MAX;
-        ahead.s = ahead.o = 1;
-        ahead.bad = 0;
-        if (idx < count) {
-            ahead.a = a[idx];
-            ahead.s = s[idx];
-            ahead.o = o[idx];
-            const int earlier = idx > 0 ? a[idx - 1] : INT_MIN;
-            if (ahead.s < 1 || ahead.o < 1 || (long long)ahead.s + ahead.o > (long long)M) ahead.bad |= KVSCHED_DEV_BAD_LENGTH;
-            if (ahead.o > H) ahead.bad |= KVSCHED_DEV_O_MAX;
-            if (ahead.a < 0 || earlier > ahead.a) ahead.bad |= KVSCHED_DEV_BAD_ARRIVAL;
-        }
+        const int idx = known + lane, at = min(idx, count - 1);
+        const int av = a[at], earlier = a[max(at - 1, 0)], sv = s[at], ov = o[at];
+        ahead.bad = sv < 1 || ov < 1 || (long long)sv + ov > (long long)M ? KVSCHED_DEV_BAD_LENGTH : 0;
+        ahead.bad |= ov > H ? KVSCHED_DEV_O_MAX : 0;
+        ahead.bad |= av < 0 || (idx > 0 && earlier > av) ? KVSCHED_DEV_BAD_ARRIVAL : 0;
+        ahead.a = idx < count ? av : INT_MAX;
+        ahead.key = codec.make(sv + ov, ov, idx);  // (of a request with a fault: not looked at)
     };
     read_ahead();
     int next_a = uni(ahead.a);
     int fault = 0;
+    // has the backlog grown since the last refresh so much that the list is due?  (Mostly in 32 bits: q <= 4096.)
+    const bool short_ratio = (rnum | rden) < (1 << 18);
+    auto grown = [&]() __attribute__((always_inline)) {
+        if (short_ratio) return (q - planned_left) * rden >= rnum * backlog_at_plan;
+        return (long long)(q - planned_left) * rden >= (long long)rnum * backlog_at_plan;
+    };
+    const float per_round = 1.0f / (float)period;
     // No admission for H iterations in a row with a backlog is impossible (every running request
     // has left by then and a single request always fits), idle stretches are skipped in one step:
     // the budget below is never reached by well-formed input and bounds the loop otherwise.
-    long long budget = (long long)count * (H + 2) + 16;
+    // (An iteration passes a round, and rounds are 32-bit numbers.)
+    int budget = (int)min((long long)count * (H + 2) + 16, (long long)INT_MAX);
+    t = max(next_a, 0);  // nothing waits before (the ring is empty)
 
     while (started < count) {
         if (--budget < 0) { fault = KVSCHED_DEV_BAD_STREAM; break; }
-        if (q == 0 && next_a > t) {  // nothing waits: jump to the next arrival, retiring the rounds passed
-            const int span = min(next_a - t, H);
-            for (int i = lane; i < span; i += 64) L.ring[(t + i) & HM] = 0;
-            t = next_a;
-            wave_sync();
-        }
         // ---- 1. arrivals, up to 64 at a time
         while (known < count && next_a <= t) {
             const int off = known - ahead_at;  // the newcomers are lanes off ... off + kc - 1 of the requests read ahead
-            const bool in = lane >= off && ahead.a <= t;
-            const u64 newly = __builtin_amdgcn_ballot_w64(in);
+            const u64 newly = __builtin_amdgcn_ballot_w64(ahead.a <= t) & lanes_from(off) & lanes_upto(count - ahead_at);
             const int kc = __popcll(newly);
-            if (__builtin_amdgcn_ballot_w64(in && ahead.bad != 0) != 0) {
-                int bad = in ? ahead.bad : 0;
+            if ((__builtin_amdgcn_ballot_w64(ahead.bad != 0) & newly) != 0) {
+                int bad = __builtin_amdgcn_inverse_ballot_w64(newly) ? ahead.bad : 0;
                 for (int dlt = 32; dlt >= 1; dlt >>= 1) bad |= __shfl_xor(bad, dlt);
                 fault = uni(bad);
             }
             if (q + kc > p.cap) fault |= KVSCHED_DEV_BACKLOG;
             if (fault) break;
-            // merge: a newcomer lands at (entries of the backlog before it) + (newcomers before it);
-            // an entry of the backlog moves up by the newcomers before it
-            const u64 key = in ? codec.make(ahead.s + ahead.o, ahead.o, ahead_at + lane) : ~0ull;
-            int at = 0;
-            for (int j = 0; j < kc; ++j) at += (lane_u64(key, off + j) < key) ? 1 : 0;
-            for (int i0 = 0; i0 < q; i0 += 64) {
-                const int i = i0 + lane;
-                const u64 k = i < q ? cur[i] : ~0ull;
-                int nb = 0;
+            put_b64(newly, L.list + ((head + q + lane - off) & QM), ahead.key);  // arrival order
+            sum_a += __builtin_amdgcn_inverse_ballot_w64(newly) ? ahead.a : 0;
+            if (kc <= 2) {
+                // each newcomer moves the entries behind it up by one, the last tile first
                 for (int j = 0; j < kc; ++j) {
-                    const bool before = k < lane_u64(key, off + j);
-                    nb += before ? 0 : 1;
-                    const int c = __popcll(__builtin_amdgcn_ballot_w64(before));
-                    at += lane == off + j ? c : 0;
+                    const u64 key = lane_u64(ahead.key, off + j);
+                    int at = 0;
+                    for (int i0 = (q - 1) & ~63; i0 >= 0; i0 -= 64) {
+                        const u64 k = cur[min(i0 + lane, q - 1)];
+                        const u64 there = lanes_upto(q - i0);
+                        const u64 up = __builtin_amdgcn_ballot_w64(key < k) & there;
+                        put_b64(up, cur + i0 + lane + 1, k);
+                        if (up != there) {
+                            at = i0 + __popcll(there & ~up);
+                            break;
+                        }
+                    }
+                    put_b64(1, cur + at, key);
+                    ++q;
                 }
-                if (i < q) oth[i + nb] = k;
+            } else {
+                // merge: a newcomer lands at (entries of the backlog before it) + (newcomers before it);
+                // an entry of the backlog moves up by the newcomers before it
+                const u64 key = ahead.key;
+                int at = 0;
+                for (int j = 0; j < kc; ++j) at += (lane_u64(key, off + j) < key) ? 1 : 0;
+                for (int i0 = 0; i0 < q; i0 += 64) {
+                    const u64 there = lanes_upto(q - i0);
+                    const u64 k = cur[min(i0 + lane, q - 1)];
+                    int nb = 0;
+                    for (int j = 0; j < kc; ++j) {
+                        const u64 before = __builtin_amdgcn_ballot_w64(k < lane_u64(key, off + j)) & there;
+                        nb += __builtin_amdgcn_inverse_ballot_w64(before) ? 0 : 1;
+                        at += lane == off + j ? __popcll(before) : 0;
+                    }
+                    put_b64(there, oth + i0 + lane + nb, k);
+                }
+                put_b64(newly, oth + at, key);
+                u64 *sw = cur; cur = oth; oth = sw;
+                q += kc;
             }
-            if (in) {
-                oth[at] = key;
-                L.list[(head + q + lane - off) & QM] = key;  // arrival order
-                sum_a += ahead.a;
-            }
-            wave_sync();
-            u64 *sw = cur; cur = oth; oth = sw;
-            q += kc;
             known += kc;
+            next_a = INT_MAX;
             if (known < count) {
                 if (known - ahead_at == 64) read_ahead();
                 next_a = __builtin_amdgcn_readlane(ahead.a, known - ahead_at);
-            } else next_a = INT_MAX;
+            }
         }
         if (fault) break;
         max_backlog = max(max_backlog, q);
 
         // ---- 2. refresh of the cached order
         bool refreshed = false;
-        if (q > 0) {
-            const long long newly = q - planned_left;
-            const bool due = planned_left == 0 || t - t_plan >= period ||
-                             (rden > 0 && newly * rden >= (long long)rnum * backlog_at_plan);
-            if (due) {
-                wn = planner == KVSCHED_PLANNER_SORTED_F ? min(window, q) : 0;
-                planned = 0;
-                for (int i = lane; i < wn; i += 64) L.wk[i] = cur[i];
-                for (int i = wn + lane; i < q; i += 64) L.list[i] = cur[i];
-                head = 0;
-                planned_left = q;
-                t_plan = t;
-                backlog_at_plan = q;
-                ++refreshes;
-                refreshed = true;
-                wave_sync();
-            }
+        if (q > 0 && (planned_left == 0 || t - t_plan >= period || (rden > 0 && grown()))) {
+            wn = planner == KVSCHED_PLANNER_SORTED_F ? min(window, q) : 0;
+            planned = listed = 0;
+            if (wn > 64)  // (a window of one row is read from the backlog itself, below)
+                for (int i0 = 0; i0 < wn; i0 += 64) put_b64(lanes_upto(wn - i0), L.wk + i0 + lane, cur[min(i0 + lane, q - 1)]);
+            for (int i0 = wn; i0 < q; i0 += 64) put_b64(lanes_upto(q - i0), L.list + i0 + lane, cur[min(i0 + lane, q - 1)]);
+            head = 0;
+            planned_left = q;
+            t_plan = t;
+            backlog_at_plan = q;
+            ++refreshes;
+            refreshed = true;
         }
 
-        // ---- 3. admission of the longest feasible prefix of the list
-        if (lane == 0) L.ring[t & HM] = 0;  // round t is behind every check from now on
-        wave_sync();
+        // ---- 3. admission of the longest feasible prefix of the list (the ring's slot of round t is empty)
         int adm = 0;
+        u64 taken = 0;  // the request admitted last
         int wait_to = t + 1;  // when the loop stops at a request: a round before which it cannot start
         while (adm < q) {
-            if (head + adm == planned && planned < wn)  // (the window's entries are never wrapped: head counts from the refresh)
-                planned += wn - planned <= 64 ? plan_batch<1>(L.wk, wn - planned, M, oth, L.list + planned)
-                           : wn - planned <= 128 ? plan_batch<2>(L.wk, wn - planned, M, oth, L.list + planned)
-                                               : plan_batch<Lds::WCAP / 64>(L.wk, wn - planned, M, oth, L.list + planned);
-            const u64 key = uni64(L.list[(head + adm) & QM]);
-            const int oo = codec.decode(key), id = codec.id(key);
-            const int sr = codec.size(key) - oo;
+            // (the window's entries are never wrapped: head counts from the refresh)
+            if (head + adm == planned && planned < wn) {
+                const int left = wn - planned;
+                u64 *from = L.wk;
+                if (planned == 0 && left <= 64) from = cur;  // (in the iteration of the refresh)
+                else if (planned > 0 && batch.others != 0)  // behind a batch in lanes
+                    put_b64(batch.others, L.wk + rank_in(batch.others), batch.key);
+                batch.others = 0;
+                if (left <= 64) planned += plan_batch<1>(from, left, M, oth, L.list + planned, batch);
+                else {
+                    planned += left <= 128 ? plan_batch<2>(L.wk, left, M, oth, L.list + planned, batch)
+                                           : plan_batch<Lds::WCAP / 64>(L.wk, left, M, oth, L.list + planned, batch);
+                    listed = planned;
+                }
+            }
+            u64 key;
+            if (head + adm == listed && listed < planned) {
+                key = take_next(batch);
+                put_b64(1, L.list + listed, key);
+                ++listed;
+            } else {
+                key = uni64(L.list[(head + adm) & QM]);
+            }
             if (key == blocked && t < blocked_to) {  // found not to start before then (memory only grows by what is admitted)
                 wait_to = blocked_to;
                 break;
             }
+            const int oo = codec.decode(key), id = codec.id(key);
+            const int sr = codec.size(key) - oo;
             // (The rounds last read are written from registers when the request is admitted, mostly all of them: a second
             // reading was a third of an admission, 600 streams 2.56 -> 2.39 ms.)
             // round t + j rules out every start before t + min(excess, j): started later the request is
             // smaller at that round by as much, or no longer overlaps it
             int excess = 0;
-            int have[4];  // four reads at a time; those of the last ones are kept
-            for (int from = 0; from < oo; from += 256) {
-                const int j0 = from + lane + 1;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u) & HM];
+            int have[4], *at[4];  // four reads at a time; those of the last ones are kept
+            const int peak = sr + lane + 1, limit = oo - lane - 1;
+            auto read4 = [&](int from) __attribute__((always_inline)) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    have[u] += sr + j0 + 64 * u;
-                    if (j0 + 64 * u <= oo) excess = max(excess, min(have[u] - M, j0 + 64 * u));
+                    at[u] = L.ring + ((t + lane + 1 + from + 64 * u) & HM);
+                    have[u] = *at[u];
+                }
+            };
+            for (int from = 0; from < oo; from += 256) {
+                read4(from);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = from + 64 * u;  // (less lane + 1)
+                    const int over = min(have[u] + (peak + j) - M, j + lane + 1);
+                    excess = max(excess, j <= limit ? over : 0);
                 }
             }
             if (__builtin_amdgcn_ballot_w64(excess > 0) != 0) {
@@ -619,51 +699,58 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
                 blocked_to = wait_to;
                 break;
             }
-            for (int from = (oo - 1) & ~255; ; from -= 256) {
-                const int j0 = from + lane + 1;
+            // (all 256 rounds of a turn are written, those behind the last with what they hold: the ring has 256 slots or more)
+            for (int from = (oo - 1) & ~255; ; from -= 256, read4(from)) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (j0 + 64 * u <= oo) L.ring[(t + j0 + 64 * u) & HM] = have[u];
+                for (int u = 0; u < 4; ++u) {
+                    const int j = from + 64 * u;
+                    *at[u] = have[u] + (j <= limit ? peak + j : 0);
+                }
                 if (from == 0) break;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) have[u] = L.ring[(t + j0 + 64 * u - 256) & HM] + sr + j0 + 64 * u - 256;
             }
-            if (lane == 0) cout[id] = t + oo;
+            put_global(1, cout + id, t + oo);
             sum_c += t + oo;
             last_c = max(last_c, t + oo);
+            taken = key;
             ++adm;
         }
         // ---- the admitted requests leave the backlog
         if (adm > 0) {
-            wave_sync();
             if (adm < q) {
-                // a few are looked for by comparing, many by a binary search for each
-                const bool few = adm <= 8;
-                const u64 gone = few ? L.list[(head + min(lane, adm - 1)) & QM] : 0;
-                if (!few) {
-                    for (int j = lane; j < adm; j += 64) {
-                        const int pos = lower_bound_u64(cur, q, L.list[(head + j) & QM]);
-                        atomicOr(&L.dead[pos >> 5], 1u << (pos & 31));
+                if (adm == 1) {
+                    for (int i0 = 0; i0 < q; i0 += 64) {
+                        const u64 k = cur[min(i0 + lane, q - 1)];
+                        put_b64(__builtin_amdgcn_ballot_w64(taken < k) & lanes_upto(q - i0), cur + i0 + lane - 1, k);
                     }
-                    wave_sync();
+                } else if (adm <= 8) {  // (in place: an entry moves down by as many as went before it)
+                    const u64 gone = L.list[(head + min(lane, adm - 1)) & QM];
+                    for (int i0 = 0; i0 < q; i0 += 64) {
+                        const u64 k = cur[min(i0 + lane, q - 1)];
+                        u64 stay = lanes_upto(q - i0);
+                        int before = 0;
+                        for (int j = 0; j < adm; ++j) {
+                            const u64 g = lane_u64(gone, j);
+                            before += g < k ? 1 : 0;
+                            stay &= ~__builtin_amdgcn_ballot_w64(k == g);
+                        }
+                        put_b64(stay, cur + i0 + lane - before, k);
+                    }
+                } else {
+                    for (int j0 = 0; j0 < adm; j0 += 64) {
+                        const u64 g = L.list[(head + min(j0 + lane, adm - 1)) & QM];
+                        const int pos = lower_bound_u64(cur, q, g);
+                        or_b32(lanes_upto(adm - j0), L.dead + (pos >> 5), 1u << (pos & 31));
+                    }
+                    int kept = 0;
+                    for (int i0 = 0; i0 < q; i0 += 64) {
+                        const int i = min(i0 + lane, q - 1);
+                        const u64 k = cur[i];
+                        const u64 stay = __builtin_amdgcn_ballot_w64(((L.dead[i >> 5] >> (i & 31)) & 1u) == 0) & lanes_upto(q - i0);
+                        put_b64(stay, cur + kept + rank_in(stay), k);
+                        kept += __popcll(stay);
+                    }
+                    for (int i0 = 0; i0 < QCAP / 32; i0 += 64) put_b32(lanes_upto(QCAP / 32 - i0), L.dead + i0 + lane, 0);
                 }
-                int kept = 0;
-                for (int i0 = 0; i0 < q; i0 += 64) {
-                    const int i = i0 + lane;
-                    bool alive = i < q;
-                    const u64 k = alive ? cur[i] : 0;
-                    if (few) {
-                        for (int j = 0; j < adm; ++j) alive = alive && k != lane_u64(gone, j);
-                    } else alive = alive && !((L.dead[i >> 5] >> (i & 31)) & 1u);
-                    const u64 bal = __builtin_amdgcn_ballot_w64(alive);
-                    if (alive) oth[kept + __popcll(bal & lanes_below())] = k;
-                    kept += __popcll(bal);
-                }
-                wave_sync();
-                if (!few)
-                    for (int i = lane; i < (q + 31) / 32; i += 64) L.dead[i] = 0;
-                u64 *sw = cur; cur = oth; oth = sw;
-                wave_sync();
             }
             head = (head + adm) & QM;
             q -= adm;
@@ -680,20 +767,29 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         if (q > 0) {
             t_next = min(wait_to, next_a);
             if (refreshed && (wn == 0 || adm == 0)) {
-                const int every = (rden > 0 && rnum == 0) ? 1 : period;
-                if (t_next - 1 - t >= every) {
-                    const int passed = every == 1 ? t_next - 1 - t : (t_next - 1 - t) / every;
+                const bool each = rden > 0 && rnum == 0;
+                const int rounds = t_next - 1 - t;  // (fewer than 2^14: wait_to lies within the ring)
+                if (rounds >= (each ? 1 : period)) {
+                    int passed = rounds;
+                    if (!each) {  // rounds / period, the quotient in fp32 off by one at most
+                        passed = uni((int)((float)rounds * per_round));
+                        passed += (passed + 1) * period <= rounds ? 1 : 0;
+                        passed -= passed * period > rounds ? 1 : 0;
+                    }
                     refreshes += passed;
-                    t_plan = t + passed * every;
+                    t_plan = t + passed * (each ? 1 : period);
                     backlog_at_plan = q;
                 }
             } else {
-                const bool grown = rden > 0 && (long long)(q - planned_left) * rden >= (long long)rnum * backlog_at_plan;
-                const long long due_at = (planned_left == 0 || grown) ? t + 1 : max((long long)t + 1, (long long)t_plan + period);
-                t_next = (int)min((long long)t_next, due_at);
+                const bool now = planned_left == 0 || (rden > 0 && grown());
+                t_next = now ? t + 1 : (int)min((long long)t_next, max((long long)t + 1, (long long)t_plan + period));
             }
-            for (int u = t + 1 + lane; u < t_next; u += 64) L.ring[u & HM] = 0;
+        } else if (known < count) {
+            t_next = max(t_next, next_a);  // nothing waits: on to the next arrival
         }
+        // the rounds up to t_next are behind every check from now on: their slots stand for the rounds H later
+        const int span = min(t_next - t, H);
+        for (int i0 = 1; i0 <= span; i0 += 64) put_b32(lanes_upto(span + 1 - i0), L.ring + ((t + i0 + lane) & HM), 0);
         t = t_next;
     }
 

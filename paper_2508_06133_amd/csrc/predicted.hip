@@ -36,7 +36,7 @@
 // What bounds the call is the number of candidates in flight times the chain of dependent instructions each is (2000 mixed
 // requests: 400 k vector and 525 k scalar instructions; four candidates share a SIMD, whose scalar unit is 65 % busy, and wait for
 // memory, LDS and branches a third of the time).  Hence no branch of the loop over rounds depends on the lane (see
-// put_entry), tiles of the list are read two at a time, and what scalars would add up entry by entry is added up a lane each:
+// lane_mask.h), tiles of the list are read two at a time, and what scalars would add up entry by entry is added up a lane each:
 // 613 k and 759 k instructions before; 4096 / 256 / 16 candidates 7.58 / 6.42 / 5.10 -> 4.75 / 3.79 / 2.98 ms, 1024 of 2000
 // chat requests 7.94 -> 4.81.  And the
 // list decides how many candidates fit a compute unit: a first launch runs every candidate with a list of at
@@ -46,6 +46,7 @@
 // start its reservations allow, and that bound holds until memory is released (an eviction, or a
 // request that finishes before its estimate), whoever outruns an estimate meanwhile.
 #include "kvsched_internal.h"
+#include "lane_mask.h"
 
 #include <limits.h>
 
@@ -423,15 +424,7 @@ struct Entry {
     int pi, oe;
 };
 
-// The LDS address of p (what a ds instruction takes).
-__device__ __forceinline__ unsigned lds_at(const void *p)
-{
-    return (unsigned)(size_t)(const __attribute__((address_space(3))) void *)p;
-}
-
-// Stores of the lanes of `mask`.  A branch that depends on the lane, anywhere in the loop over rounds, makes the compiler
-// carry every way out of the loops around it as flags in scalar registers, and the scalar unit is what the candidates
-// of a SIMD wait for; so lanes are masked here and every branch of the loop is the same for all of them.
+// An entry and the round it is due, by the lanes of `mask`.
 __device__ __forceinline__ void put_entry(unsigned long long mask, const Entry *e, const unsigned short *d, int pi, int oe, int due)
 {
     unsigned long long all;
@@ -442,29 +435,6 @@ __device__ __forceinline__ void put_entry(unsigned long long mask, const Entry *
                  "s_mov_b64 exec, %[all]\n"
                  : [all] "=&s"(all)
                  : [mask] "s"(mask), [e] "v"(lds_at(e)), [v] "v"(v), [d] "v"(lds_at(d)), [due] "v"(due)
-                 : "memory", "scc");
-}
-
-__device__ __forceinline__ void put_word(unsigned long long mask, const unsigned *w, unsigned v)
-{
-    unsigned long long all;
-    asm volatile("s_and_saveexec_b64 %[all], %[mask]\n"
-                 "ds_write_b32 %[w], %[v]\n"
-                 "s_mov_b64 exec, %[all]\n"
-                 : [all] "=&s"(all)
-                 : [mask] "s"(mask), [w] "v"(lds_at(w)), [v] "v"(v)
-                 : "memory", "scc");
-}
-
-__device__ __forceinline__ void put_global(unsigned long long mask, int32_t *base, unsigned byte, int v)
-{
-    unsigned long long all;
-    asm volatile("s_and_saveexec_b64 %[all], %[mask]\n"
-                 "s_nop 4\n"
-                 "global_store_dword %[byte], %[v], %[base]\n"
-                 "s_mov_b64 exec, %[all]\n"
-                 : [all] "=&s"(all)
-                 : [mask] "s"(mask), [base] "s"(base), [byte] "v"(byte), [v] "v"(v)
                  : "memory", "scc");
 }
 
@@ -585,7 +555,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                 tel += __builtin_amdgcn_inverse_ballot_w64(ends) ? t : 0;
                 done += k;
                 ov_cnt -= __popcll(leaves);
-                if (crow) put_global(ends, crow, (unsigned)id * 4u, t);
+                if (crow) put_global(ends, crow + id, t);
                 // the entries that stay move together within the tile, the list's last ones behind them
                 const unsigned long long stay = in & ~ends;
                 const int to = a0 + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(stay >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)stay, 0));
@@ -723,7 +693,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
             room -= hs + 1;
             if (hpos < frontier) {  // a stopped one starts again
                 const unsigned *w = WAIT + (hpos >> 5);
-                put_word(1, w, *w & ~(1u << (hpos & 31)));
+                put_b32(1, w, *w & ~(1u << (hpos & 31)));
             }
             const int until = t + min(he, ho);
             put_entry(1, LE + nact, LDUE + nact, hpos | (hid << 16), ho | (he << 16), until);
@@ -783,7 +753,7 @@ __device__ __forceinline__ void run_candidate(const PredParams &p, int *lds)
                 c_e = ev == EST_OVERRUN ? t - ps + 1 : ev;  // what it is known to need
                 est_stopped[vpos] = (unsigned short)c_e;
                 const unsigned *w = WAIT + (vpos >> 5);
-                put_word(1, w, *w | 1u << (vpos & 31));  // waits again
+                put_b32(1, w, *w | 1u << (vpos & 31));  // waits again
                 --nact;
                 const Entry last = LE[nact];
                 put_entry(1, LE + slot, LDUE + slot, last.pi, last.oe, LDUE[nact]);
