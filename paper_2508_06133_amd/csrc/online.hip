@@ -766,6 +766,7 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
         int t_next = t + 1;
         if (q > 0) {
             t_next = min(wait_to, next_a);
+            bool quiet = short_ratio;
             if (refreshed && (wn == 0 || adm == 0)) {
                 const bool each = rden > 0 && rnum == 0;
                 const int rounds = t_next - 1 - t;  // (fewer than 2^14: wait_to lies within the ring)
@@ -780,9 +781,24 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
                     t_plan = t + passed * (each ? 1 : period);
                     backlog_at_plan = q;
                 }
+                quiet = quiet && !each;
+            } else if (planned_left == 0 || (rden > 0 && grown())) {
+                t_next = t + 1;
+                quiet = false;
             } else {
-                const bool now = planned_left == 0 || (rden > 0 && grown());
-                t_next = now ? t + 1 : (int)min((long long)t_next, max((long long)t + 1, (long long)t_plan + period));
+                t_next = (int)min((long long)t_next, max((long long)t + 1, (long long)t_plan + period));
+            }
+            // Nor does an arrival change anything but the backlog and the list's end, until the one that makes the backlog grown
+            // enough for a refresh: arrivals before it wait for the next iteration there is (as far as they have been read).  600
+            // streams 2.10 -> 1.90 ms.
+            if (quiet && t_next == next_a && __builtin_amdgcn_ballot_w64(ahead.bad != 0) == 0) {
+                const int off = known - ahead_at;
+                const u64 enough = rden > 0 ? __builtin_amdgcn_ballot_w64((q - planned_left + lane - off + 1) * rden >= rnum * backlog_at_plan) & lanes_from(off) : 0;
+                const int last = min(count - 1 - ahead_at, 63);  // (read so far; behind the last request of all none arrives)
+                const int l = min(enough != 0 ? first_lane(enough) : 64, last);
+                int grows = __builtin_amdgcn_readlane(ahead.a, l);
+                if (enough == 0 && ahead_at + last == count - 1) grows = INT_MAX;
+                t_next = (int)min((long long)min(wait_to, grows), max((long long)t + 1, (long long)t_plan + period));
             }
         } else if (known < count) {
             t_next = max(t_next, next_a);  // nothing waits: on to the next arrival
