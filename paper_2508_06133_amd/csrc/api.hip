@@ -334,6 +334,7 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     ctx->hz_M = 0;
     ctx->pad_outputs = 0;
     ctx->o_file = 0;
+    ctx->status_turn = 0;
     ctx->timing = 0;
     ctx->timed = 0;
     ctx->resume_rows = 0;
@@ -494,14 +495,31 @@ int kvsched_device_status(kvsched_ctx *ctx, void *stream, int32_t *status_out)
         hipSuccess)
         return KVSCHED_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return KVSCHED_EHIP;
-    *status_out = ctx->h_words[KVS_W_STATUS];
+    const int32_t at = ctx->h_words[KVS_W_STATUS_AT];
+    *status_out = ctx->h_words[at == KVS_W_STATUS_TURN || at == KVS_W_STATUS_TURN + 1 ? at : KVS_W_STATUS];
     return KVSCHED_OK;
 }
 
+// May a simulate call whose timelines take the register file of o_bound do without a length scan ahead of it?  Its timelines look
+// the lengths over themselves where those are few: rows that are placed in full and checked by their own wavefronts.  Not while
+// the stream is captured, as a replay would find the status word of the replay before.  (A launch between others that
+// depend on each other takes 4.7 us: 40321 rows of 8 11.6 -> 9.3 us a call, 4096 rows of 200 51.8 -> 48.6, with a bound 47.4 -> 46.1; one
+// order of 61 requests 14.2 -> 14.4, which waits for the scan's result either way.)
+static bool scans_here(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bound, int32_t common_prefix, hipStream_t st)
+{
+    return n <= KVS_SCANNED_HERE && o_bound <= KVS_REG_MAX_O && !(common_prefix >= kMinSharedPrefix && C > 1) &&
+           !resume_pays(ctx, C, n, o_bound) && !capturing(st);
+}
+
+// The status word of the next such call, which clears the other one for the call after it.
+static int32_t next_status_word(kvsched_ctx *ctx) { return KVS_W_STATUS_TURN + (ctx->status_turn ^= 1); }
+
 // kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
-// longer one (only where rows are not resumed and no prefix is placed ahead).
+// longer one (only where rows are not resumed and no prefix is placed ahead).  scan: no length scan is enqueued before
+// (scans_here), the launch does it and, if gated, leaves its result in pinned memory under number ctx->scan_seq.
+// status_word: where faulty rows are reported.
 static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, const int32_t *s,
-                           const int32_t *o, int64_t M, int32_t o_bound, bool gated, int64_t *tel_out,
+                           const int32_t *o, int64_t M, int32_t o_bound, bool gated, bool scan, int32_t status_word, int64_t *tel_out,
                            int32_t *completion_out, int32_t common_prefix, hipStream_t st)
 {
     const int32_t o_limit = gated ? o_bound : INT32_MAX;
@@ -525,7 +543,17 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     p.completion_by_position = (completion_out && n <= KVS_PERMUTE_MAX_N) ? 1 : 0;
     p.d_words = ctx->d_words;
     p.o_bound = o_bound;
-    p.gate = gated ? ctx->d_words + KVS_W_OMAX : nullptr;
+    p.gate = gated && !scan ? ctx->d_words + KVS_W_OMAX : nullptr;
+    p.status_word = status_word;
+    if (scan) {
+        p.scan_here = 1;
+        p.scan_limit = o_limit;
+        p.scan_bound = ctx->o_max_bound;
+        if (gated) {
+            p.host = ctx->h_scan;
+            p.seq = ctx->scan_seq;
+        }
+    }
     // Declared common prefix: run it once (row 0), resume every row from its state.
     int32_t cp = 0;
     int32_t *prefix_comp = nullptr;
@@ -684,24 +712,38 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
     if (rc != KVSCHED_OK) return rc;
     if (!orders || !tel_out || C < 1 || common_prefix < 0 || common_prefix > n) return KVSCHED_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    int32_t guess = 0;
+    int32_t guess = 0, status_word = KVS_W_STATUS;
+    bool scan = false;
     if (ctx->o_max_bound == 0 && ctx->o_file > 0 && (int64_t)C * n <= kGuessMaxPositions &&
         common_prefix < kMinSharedPrefix && !resume_pays(ctx, C, n, ctx->o_file) &&
         (C <= kvs_reg_wavefronts(ctx->o_file) || kvs_reg_wavefronts(ctx->o_file) == kvs_reg_wavefronts(1)) &&
         (int64_t)n * ring_slots_for(ctx->o_file) < kMaxM && !capturing(st))
         guess = ctx->o_file;
     if (guess > 0) {
-        rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, next_seq(ctx));
-        if (rc == KVSCHED_OK) rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, tel_out, completion_out, 0, st);
+        next_seq(ctx);
+        scan = scans_here(ctx, C, n, guess, common_prefix, st);
+        if (scan) status_word = next_status_word(ctx);
+        else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq);
+        if (rc == KVSCHED_OK)
+            rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, scan, status_word, tel_out, completion_out, 0, st);
         if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);
         if (rc != KVSCHED_OK) return rc;
+    } else if (ctx->o_max_bound > 0 && scans_here(ctx, C, n, ctx->o_max_bound, common_prefix, st)) {
+        ctx->o_file = kvs_reg_file_bound(ctx->o_max_bound);
+        return simulate_within(ctx, orders, C, n, s, o, M, ctx->o_max_bound, false, true, next_status_word(ctx), tel_out,
+                               completion_out, common_prefix, st);
     }
     int32_t o_bound = 0;
     rc = guess > 0 ? scanned_bound(ctx, &o_bound) : scan_and_bound(ctx, s, o, n, M, st, &o_bound);
     if (rc != KVSCHED_OK) return rc;
     ctx->o_file = kvs_reg_file_bound(o_bound);
     if (guess >= o_bound) return KVSCHED_OK;
-    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, false, tel_out, completion_out, common_prefix, st);
+    if (scan && o_bound > KVS_REG_MAX_O) {  // (whose kernels report in the scan's word)
+        status_word = KVS_W_STATUS;
+        rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
+        if (rc != KVSCHED_OK) return rc;
+    }
+    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, false, false, status_word, tel_out, completion_out, common_prefix, st);
 }
 
 // The three Phase-1 solvers; (ga, gb) = (0, 1) is the F-metric.

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/kvsched.h"
+#include "kvsched_internal.h"
 
 namespace {
 
@@ -37,6 +38,32 @@ __device__ __forceinline__ int wave_max_i32(int v)
 // sees them, so this is all that has to separate them from the atomic that announces them; a device-scope fence would
 // write the whole L2 back as well (5 us behind a kernel that has just stored a few megabytes).
 __device__ __forceinline__ void device_writes_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// What a length scan leaves behind, by one lane of a launch that has had none ahead of it (SimParams::scan_here).
+template <class Params>
+__device__ __forceinline__ void report_lengths(const Params &p, int longest, int flags)
+{
+    p.d_words[2 * KVS_W_STATUS_TURN + 1 - p.status_word] = 0;  // (the other one)
+    p.d_words[KVS_W_STATUS_AT] = p.status_word;
+    if (flags) atomicOr(&p.d_words[p.status_word], flags);
+    p.d_words[KVS_W_OMAX] = longest;
+    p.d_words[KVS_W_MINPOS] = 0x7fffffff;
+    p.d_words[KVS_W_MAXPOS] = -1;
+    if (p.host) {
+        p.host[KVS_H_OMAX] = longest;
+        p.host[KVS_H_MINPOS] = 0x7fffffff;
+        p.host[KVS_H_MAXPOS] = -1;
+        __threadfence_system();
+        __hip_atomic_store(&p.host[KVS_H_SEQ], p.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// The flags that one request's lengths give (bound: the caller's on the decode lengths, or 0).
+__device__ __forceinline__ int length_flags(int s, int o, int M, int bound)
+{
+    return (s < 1 || o < 1 || (long long)s + (long long)o > (long long)M ? KVSCHED_DEV_BAD_LENGTH : 0) |
+           (bound > 0 && o > bound ? KVSCHED_DEV_O_MAX : 0);
+}
 
 // Position k of candidate order -> request id.
 template <bool MOVES>

@@ -149,6 +149,7 @@ __device__ int prepare_body(int32_t n, const int32_t *s, const int32_t *o, int32
     cmax = L.sh[1];
     if (tid == 0) {  // (the first kernel of the call: as the length scan leaves them)
         words[KVS_W_STATUS] = L.sh[2] != 0 ? KVSCHED_DEV_BAD_LENGTH : 0;
+        words[KVS_W_STATUS_AT] = KVS_W_STATUS;
         words[KVS_W_OMAX] = omax;
         words[KVS_W_MINPOS] = INT_MAX;
         words[KVS_W_MAXPOS] = -1;

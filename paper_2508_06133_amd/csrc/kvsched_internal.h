@@ -15,6 +15,8 @@ enum {
     KVS_W_KMAX = 4,    // exact DP: bound on the size of the next batch
     KVS_W_ESTMAX = 7,  // largest initial estimate (kvsched_simulate_predicted)
     KVS_W_MAXPOS = 8,  // largest position any move touches (best_neighbor), -1: none
+    KVS_W_STATUS_AT = 9,     // which word holds the status of the last call: KVS_W_STATUS (or 0), or one of the following two,
+    KVS_W_STATUS_TURN = 10,  // which calls without a length scan use in turn, each clearing the other (SimParams::scan_here)
     KVS_W_COUNT = 16,  // (what kvsched_device_status and the waits of kvsched_exact_dp read back)
     // Behind them, working words of kernels that split one pass over several workgroups: what they have gathered so
     // far and how many are done.  The workgroup that is done last takes the results and leaves the neutral values.
@@ -58,6 +60,7 @@ struct kvsched_ctx {
     int32_t o_file;        // longest decode of the register file the last kvsched_simulate needed (0: unknown, or none): what a
                            // small call starts with before its own is known
     int pad_outputs;       // Phase-1 calls write zeros behind the last batch
+    int32_t status_turn;   // which of the two words at KVS_W_STATUS_TURN the last call without a length scan used
     int timing;            // record events around the timeline kernel
     int timed;             // a pair of events has been recorded
     int32_t resume_rows;   // rows of the last kvsched_simulate call if it resumed rows from snapshots, else 0
@@ -85,6 +88,7 @@ struct OrderSource {
     const int32_t *moves;   // [K][3]; candidate K (one past the last move) is the base itself
 };
 
+constexpr int KVS_SCANNED_HERE = 256;   // (see SimParams::scan_here)
 constexpr int KVS_CHECKED_ROW = 1024;  // (a bit each has room in the LDS of the smallest file, and a word per lane of 32)
 
 struct SimParams {
@@ -103,6 +107,16 @@ struct SimParams {
     int32_t check_rows = 0;
     // Register kernel, explicit rows that are not resumed: the launch leaves everything as it is when *gate > o_bound
     const int32_t *gate = nullptr;
+    // Plain launches of the register kernel, and orders placed a lane each: the launch looks the lengths over itself, every wavefront
+    // for the longest decode (above scan_limit: everything is left as it is) and the first one for what a scan ahead of it would
+    // have left: longest and flags (scan_bound: the caller's bound or 0) in d_words and, with seq, in host.  Nothing has cleared a
+    // status word just before it, so there are two in turn: the launch reports in status_word and clears the other.
+    int32_t scan_here = 0;
+    int32_t scan_limit = 0;
+    int32_t scan_bound = 0;
+    int32_t status_word = KVS_W_STATUS;  // (with or without a scan: where rows that are no permutations are reported)
+    int32_t *host = nullptr;
+    int32_t seq = 0;
     // Register kernel only: simulate positions [k_begin, k_end) (k_end == 0: up to n), starting
     // from / leaving behind a saved timeline state of KVS_STATE_HEAD_WORDS + 64 NR int32 words:
     // {b64, t, 62 unused, the 64 lanes' partial sums of completion rounds as int64, then the

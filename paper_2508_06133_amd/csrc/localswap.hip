@@ -781,6 +781,7 @@ __global__ __launch_bounds__(1024) void rank_requests_kernel(int32_t n, const in
     wide = sh[2];
     if (blockIdx.x == 0 && tid == 0) {
         words[KVS_W_STATUS] = bad ? KVSCHED_DEV_BAD_LENGTH : 0;
+        words[KVS_W_STATUS_AT] = KVS_W_STATUS;
         words[KVS_W_OMAX] = sh[0];
         words[KVS_W_MINPOS] = 0x7fffffff;
         words[KVS_W_MAXPOS] = -1;

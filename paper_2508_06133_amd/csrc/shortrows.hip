@@ -23,6 +23,7 @@
 // looks at many more rounds: 16 requests of 1 or 4096 tokens and rounds, 8192 orders at M = 8192 25 us (4400), 16384 at M = 16384
 // 24 (73).  So orders of 9 to 16 requests take this way from 8192 on, where the chat ones alone would have it at 16384.
 #include "kvsched_internal.h"
+#include "device_util.h"
 
 namespace {
 
@@ -35,11 +36,21 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
     const int first = (int)blockIdx.x * 64, mine = min(64, p.C - first);
     const int32_t *orders = p.src.orders + (size_t)first * (size_t)n;
     const int entries = mine * n;
-    const int o_max = p.d_words[KVS_W_OMAX];
+    int o_max = p.scan_here ? 0 : p.d_words[KVS_W_OMAX];
     for (int e = lane; e < entries; e += 64) row[(e / n) * PITCH + e % n] = orders[e];
+    const int s_mine = lane < n ? p.s[lane] : 1, o_mine = lane < n ? p.o[lane] : 1;
     if (lane < N) {
-        len_s[lane] = lane < n ? p.s[lane] : 1;
-        len_o[lane] = lane < n ? p.o[lane] : 1;
+        len_s[lane] = s_mine;
+        len_o[lane] = o_mine;
+    }
+    if (p.scan_here) {
+        o_max = wave_max_i32(lane < n ? o_mine : 0);
+        o_limit = p.scan_limit;
+        if (blockIdx.x == 0) {
+            const int flags = lane < n ? length_flags(s_mine, o_mine, M, p.scan_bound) : 0;
+            const int all = wave_max_i32(flags & KVSCHED_DEV_BAD_LENGTH) | wave_max_i32(flags & KVSCHED_DEV_O_MAX);
+            if (lane == 0) report_lengths(p, o_max, all);
+        }
     }
     __syncthreads();
     if (o_max > o_limit) return;  // (the rows are placed by a later launch)
@@ -95,7 +106,7 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
         }
     }
     if (lane < mine) {
-        if (!permutation) atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
+        if (!permutation) atomicOr(&p.d_words[p.status_word], KVSCHED_DEV_BAD_ORDER);
         p.tel_out[first + lane] = permutation && valid ? (int64_t)tel : -1;
     }
     if (!p.completion_out) return;

@@ -167,6 +167,7 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
         atomicExch(&words[KVS_W_SCAN_DONE], 0);
     }
     words[KVS_W_STATUS] = flag;
+    words[KVS_W_STATUS_AT] = KVS_W_STATUS;
     words[KVS_W_OMAX] = mx;
     words[KVS_W_MINPOS] = lowest;
     words[KVS_W_MAXPOS] = top;

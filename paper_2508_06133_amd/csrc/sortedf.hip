@@ -385,6 +385,7 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
     omax = sh[1];
     if (tid == 0) {
         p.words[KVS_W_STATUS] = bad ? KVSCHED_DEV_BAD_LENGTH : 0;
+        p.words[KVS_W_STATUS_AT] = KVS_W_STATUS;
         p.words[KVS_W_OMAX] = omax;
         p.words[KVS_W_MINPOS] = 0x7fffffff;
         p.words[KVS_W_MAXPOS] = -1;

@@ -1429,6 +1429,20 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
     if (AHEAD) id_nn = id_at(k_first);
     fetch(k_first);
     if (!RES && !MOVES && p.gate && scalar_read(p.gate, 0) > p.o_bound) return;  // (while the lengths are on their way)
+    if (!RES && !MOVES && p.scan_here) {
+        int longest = 0, flags = 0;
+        for (int k = lane; k < n_all; k += WAVE) {
+            const int o = p.o[k];
+            longest = max(longest, o);
+            if (wave_no == 0) flags |= length_flags(p.s[k], o, M, p.scan_bound);
+        }
+        longest = wave_max_i32(longest);
+        if (wave_no == 0) {
+            const int all = wave_max_i32(flags & KVSCHED_DEV_BAD_LENGTH) | wave_max_i32(flags & KVSCHED_DEV_O_MAX);
+            if (lane == 0) report_lengths(p, longest, all);
+        }
+        if (longest > p.scan_limit) return;
+    }
     // A row of up to KVS_CHECKED_ROW positions is checked here (in the room of the list, which is not in use yet), and its
     // completion rounds are written by request id, while the whole row is in the L2 cache: no second pass over it.  (One order of 61
     // requests 15.3 -> 13.6 us a call; 4096 orders of 61 / 200 / 300 / 1000 33.2 / 63.1 / 101 / 203 -> 29 / 58 / 92 / 196,
@@ -1446,7 +1460,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
             fits &= raw == r && (atomicOr(&met[r >> 5], bit) & bit) == 0;
         }
         is_order = __builtin_amdgcn_ballot_w64(!fits) == 0;
-        if (!is_order && lane == 0) atomicOr(&p.d_words[KVS_W_STATUS], KVSCHED_DEV_BAD_ORDER);
+        if (!is_order && lane == 0) atomicOr(&p.d_words[p.status_word], KVSCHED_DEV_BAD_ORDER);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }

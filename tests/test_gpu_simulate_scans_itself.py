@@ -1,0 +1,98 @@
+"""Calls of kvsched_simulate that have no length scan ahead of their timelines (orders of up to 256 requests): the status they
+leave is their own, whatever the calls before and after left, and a wrong guess of the longest decode changes nothing."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to("cuda:0")
+
+
+def _rows(rng, n, C, faulty):
+    rows = np.stack([rng.permutation(n) for _ in range(C)]).astype(np.int32)
+    if faulty:
+        rows[C // 2, 0] = rows[C // 2, n - 1] if n > 1 else 5
+    return rows
+
+
+@pytest.mark.parametrize("n,C", [(1, 3), (8, 70), (63, 5), (64, 1), (65, 9), (255, 6), (256, 6), (257, 6), (20, 8200)])
+@pytest.mark.parametrize("bound", [0, 300])
+def test_status_is_that_of_the_last_call(n, C, bound):
+    from paper_2508_06133_amd import kvsched
+
+    rng = np.random.default_rng(n + C)
+    s, o = rng.integers(1, 100, n).astype(np.int32), rng.integers(1, 301, n).astype(np.int32)
+    M = 1500
+    ctx = kvsched.Context(0)
+    try:
+        ctx.set_o_max(bound)
+        print(f"simulate without a scan: n={n} C={C} bound={bound}", flush=True)
+        check = min(C, 6)
+        # a good call, faulty rows, faulty lengths, decodes above the bound, a call with a scan between them
+        for what in ("good", "row", "good", "length", "good", "row", "long", "sorted", "row", "good", "good"):
+            rows = _rows(rng, n, C, what == "row")
+            s1, o1 = s.copy(), o.copy()
+            if what == "length":
+                s1[n // 2] = 0
+            if what == "long":
+                o1[n // 2] = 310
+            if what == "sorted":
+                ctx.sortedF(_dev(s1), _dev(o1), M)
+                assert ctx.device_status() == 0
+                continue
+            tel, comp = ctx.simulate(_dev(rows), _dev(s1), _dev(o1), M)
+            status = ctx.device_status()
+            tel, comp = tel.cpu().numpy(), comp.cpu().numpy()
+            want = {"good": 0, "row": kvsched.DEV_BAD_ORDER, "length": kvsched.DEV_BAD_LENGTH,
+                    "long": kvsched.DEV_O_MAX if bound else 0}[what]
+            assert status == want, what
+            if what in ("length",) or (what == "long" and bound):
+                assert (tel == -1).all()
+                continue
+            good = [c for c in range(C) if what != "row" or c != C // 2][:check]
+            if good:
+                tel_o, comp_o = oracle.simulate_many(s1, o1, M, rows[good], literal=False)
+                assert (tel[good] == tel_o).all() and (comp[good] == comp_o).all(), what
+            if what == "row":
+                assert tel[C // 2] == -1
+    finally:
+        ctx.close()
+
+
+def test_wrong_guesses():
+    """Backlogs whose longest decodes need other register files, the ring, or are out of range, in turn."""
+    import torch
+    from paper_2508_06133_amd import kvsched
+
+    rng = np.random.default_rng(3)
+    ctx = kvsched.Context(0)
+    try:
+        for longest in (40, 600, 40, 3000, 5000, 600, 15000, 40, 14336, 17000, 40, 17000, 15000):
+            n, C = 40, 20
+            s, o = rng.integers(1, 50, n).astype(np.int32), rng.integers(1, 30, n).astype(np.int32)
+            o[7] = longest
+            M = 18000
+            rows = _rows(rng, n, C, longest == 15000)
+            print(f"simulate without a scan: longest decode {longest}", flush=True)
+            tel = torch.full((C,), -9, dtype=torch.int64, device="cuda:0")
+            comp = torch.full((C, n), -9, dtype=torch.int32, device="cuda:0")
+            call = lambda: ctx.simulate(_dev(rows), _dev(s), _dev(o), M, tel_out=tel, completion_out=comp)
+            if longest > 16384:
+                with pytest.raises(kvsched.KvschedError) as e:
+                    call()
+                torch.cuda.synchronize()
+                assert e.value.code == -2 and (tel == -9).all() and (comp == -9).all()
+                continue
+            call()
+            assert ctx.device_status() == (kvsched.DEV_BAD_ORDER if longest == 15000 else 0)
+            good = [c for c in range(C) if longest != 15000 or c != C // 2]
+            tel_o, comp_o = oracle.simulate_many(s, o, M, rows[good], literal=False)
+            assert (tel.cpu().numpy()[good] == tel_o).all() and (comp.cpu().numpy()[good] == comp_o).all()
+    finally:
+        ctx.close()
