@@ -15,6 +15,7 @@
 // Up to 4096 requests (2048 under the profile constraint) one workgroup does everything in LDS and
 // registers; beyond that the sorts and scans are launches over the whole chip and only step 3, a chain
 // by nature, is one workgroup's.
+#include "device_util.h"
 #include "phase1_util.h"
 #include "sort_util.h"
 
@@ -103,16 +104,20 @@ __device__ __forceinline__ int wave_best(u64 &bS, int bk, int tie_rule)
     return k;
 }
 
-// One wavefront: size of the batch that starts at place a (0: none).  Feasible are the k <= rem with W_k - W_0 <= M.  256 sizes
-// a turn, their sums read together.
+// One wavefront: size of the batch that starts at place a (0: none).  Feasible are the k <= rem with W_k - W_0 <= M.  First the sizes
+// up to 64, where most batches end, then 256 a turn, their sums read together.
 template <bool SMALL>
 __device__ __forceinline__ int wave_batch(const Sums &c, int a, int rem, u64 M, int tie_rule)
 {
     const int lane = threadIdx.x & 63;
     const u64 W0 = c.W[a], G0 = c.G[a];
-    u64 bS = 0;
-    int bk = 0;
-    for (int base = 0; base < rem; base += 256) {
+    const int k1 = min(lane + 1, rem);
+    const u64 w1 = c.W[a + k1], g1 = c.G[a + k1];
+    const bool ok1 = lane < rem && w1 - W0 <= M;
+    u64 bS = ok1 ? g1 - G0 : 0;
+    int bk = ok1 ? lane + 1 : 0;
+    if (__builtin_amdgcn_ballot_w64(ok1) != ~0ull) return wave_best<SMALL>(bS, bk, tie_rule);
+    for (int base = 64; base < rem; base += 256) {
         u64 w[4], g[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -354,8 +359,7 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
     int *ends = (int *)(lds64 + (PROFILE ? 3 : 2) * (N + 2));
     int *by_o = ends + N;  // id at a rank of the (o, id) order, and the inverse (only when ranks are needed)
     int *rank_of = by_o + N;
-    int *next = rank_of + N;  // size of the batch a place would start (when found for all places)
-    int *s_pos = next;        // PROFILE: lengths by sorted position, rank by sorted position
+    int *s_pos = rank_of + N;  // PROFILE: lengths by sorted position, rank by sorted position
     int *o_pos = s_pos + N, *rank_pos = o_pos + N, *o_of_rank = rank_pos + N;
     unsigned *hist = (unsigned *)(o_of_rank + N);
     __shared__ u64 tot_w[NW], tot_q[NW], red_S[16];
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
         if (sv[e] < 1 || ov[e] < 1 || (long long)sv[e] + ov[e] > (long long)p.M) bad = 1;
         if (i < n) omax = max(omax, ov[e]);
     }
-    for (int d = 32; d > 0; d >>= 1) omax = max(omax, __shfl_xor(omax, d));
+    omax = wave_max_i32(omax);
     if (lane == 0) atomicMax(&sh[1], omax);
     if (bad) atomicOr(&sh[0], 1);
     __syncthreads();
@@ -489,29 +493,13 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
     const bool small = all_g < (1ull << 32);
     int nb = 0;
     if constexpr (!PROFILE) {
-        if (NW > 1 && all_w > M * (u64)(n / 32 + 1)) {
-            // many small batches: all wavefronts find the batch that each place would start, then the chain is followed
-            for (int a = wave; a < n; a += NW) {
-                const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule)
-                                    : wave_batch<false>(c, a, n - a, M, p.tie_rule);
-                if (lane == 0) next[a] = k;
-            }
-            __syncthreads();
-            if (wave == 0) {
-                for (int a = 0; a < n;) {
-                    const int k = __builtin_amdgcn_readfirstlane(next[a]);
-                    if (k < 1) break;  // cannot happen for well-formed input; never spin
-                    a += k;
-                    if (lane == 0) ends[nb] = a;
-                    ++nb;
-                }
-                if (lane == 0) sh[2] = nb;
-            }
-        } else if (wave == 0) {  // one wavefront, no barriers
+        // One wavefront, no barriers, 0.4 us a batch.  (The batches of all places at once, by all wavefronts, were 49 us for 256 mixed
+        // requests whether in 12 batches or 59, now 11 and 30, and 149 for 2000 in 81, now 57.)
+        if (wave == 0) {
             for (int a = 0; a < n;) {
                 const int k = small ? wave_batch<true>(c, a, n - a, M, p.tie_rule)
                                     : wave_batch<false>(c, a, n - a, M, p.tie_rule);
-                if (k < 1) break;
+                if (k < 1) break;  // cannot happen for well-formed input; never spin
                 a += k;
                 if (lane == 0) ends[nb] = a;
                 ++nb;
@@ -602,7 +590,7 @@ __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
 // Words of dynamic LDS of the kernel above.
 constexpr size_t small_lds_bytes(int N, bool profile)
 {
-    return (size_t)(profile ? 3 : 2) * 8 * (N + 2) + (size_t)(profile ? 7 : 4) * 4 * N + (profile ? 16 * kSmallBuckets : 0);
+    return (size_t)(profile ? 3 : 2) * 8 * (N + 2) + (size_t)(profile ? 7 : 3) * 4 * N + (profile ? 16 * kSmallBuckets : 0);
 }
 static_assert(small_lds_bytes(4096, false) >= 16 * 4096 && small_lds_bytes(2048, true) + 2048 <= 160 * 1024, "fits the LDS");
 
