@@ -759,10 +759,6 @@ static int run_sortedF(kvsched_ctx *ctx, int32_t n, const int32_t *s, const int3
     hipStream_t st = (hipStream_t)stream;
     rc = ensure_scratch(ctx, kvs_sortedF_scratch_bytes(n));
     if (rc != KVSCHED_OK) return rc;
-    if (n > kvs_sortedF_small_max(feas_mode)) {
-        rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
-        if (rc != KVSCHED_OK) return rc;
-    }
     return kvs_launch_sortedF(n, s, o, (int32_t)M, ga, gb, tie_rule, feas_mode, ctx->pad_outputs, order_out, batch_end_out, F_out,
                               num_batches_out, ctx->d_scratch, ctx->d_words, st);
 }

@@ -120,7 +120,7 @@ __device__ __forceinline__ void bitonic_thread(u64 (&k)[E], int i0, int size)
 
 // Ascending sort of TPB * E keys.  lds: 2 TPB E keys; the caller separates its own use of it by barriers.  From 1024 threads on the
 // stages are a loop over one piece of code of some 1.5 KB: unrolled, a sort of 2048 keys is 11 KB of instructions that run once and
-// have to be fetched (Sorted-F order of 2000 requests 53 -> 47 us).  Few keys are quicker unrolled (61 requests 6.0 us, 6.9 as a loop).
+// have to be fetched (two such sorts 53 -> 47 us).  Few keys are quicker unrolled (61 requests 6.0 us, 6.9 as a loop).
 template <int TPB, int E>
 __device__ __forceinline__ void block_sort(u64 (&k)[E], u64 *lds)
 {

@@ -12,17 +12,23 @@
 //   3. per batch: the feasible extent K (sum of peaks <= M; or the simultaneous-start memory profile),
 //      then the argmin over k <= K of G_k / k^2 compared in exact integers, tie rule applied
 //   4. sort (batch, o, id): each batch in nondecreasing o; the metric as one fp64 division
-// Up to 4096 requests (2048 under the profile constraint) one workgroup does everything in LDS and
+// Up to 1024 requests (128 under the profile constraint) one workgroup does everything in LDS and
 // registers; beyond that the sorts and scans are launches over the whole chip and only step 3, a chain
 // by nature, is one workgroup's.
 #include "device_util.h"
 #include "phase1_util.h"
 #include "sort_util.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int kRun = 2048;          // keys one workgroup sorts (1024 threads, two each)
 constexpr int kFan = 8;             // runs merged by one pass
+constexpr int kSmallSum = 1024, kSmallProfile = 128;  // requests that one workgroup takes (kvs_sortedF_small_max)
+constexpr int kCountMax = 12288;    // requests whose places are found by counting the keys before them
+constexpr int kSumsHere = 16384;    // requests up to which the prefix sums need no sums ahead
+constexpr int kOrderTile = 6144;    // keys held at a time when the places within batches are counted
 constexpr int kNextMax = 256;       // profile tests among the first so many requests are made by one wavefront
 constexpr int kNextLimit = 2048;    // batches whose extent is below this are found for all places at once
 constexpr int kNextWindow = 73728;  // places of which the chain holds what is known in LDS (two bytes each)
@@ -592,14 +598,15 @@ constexpr size_t small_lds_bytes(int N, bool profile)
 {
     return (size_t)(profile ? 3 : 2) * 8 * (N + 2) + (size_t)(profile ? 7 : 3) * 4 * N + (profile ? 16 * kSmallBuckets : 0);
 }
-static_assert(small_lds_bytes(4096, false) >= 16 * 4096 && small_lds_bytes(2048, true) + 2048 <= 160 * 1024, "fits the LDS");
+static_assert(small_lds_bytes(2048, false) >= 16 * 2048 && small_lds_bytes(1024, true) + 2048 <= 160 * 1024 && kSmallSum <= 2048 &&
+                  kSmallProfile <= 1024, "fits the LDS");
 
 // ------------------------------------------------------------------------- many workgroups
 
 // What the launches of a large construction share (arrays in the context's scratch).
 struct LargeArrays {
     u64 *key[2];
-    u64 *W, *S, *G, *tot;  // tot: two sums per 4096 places
+    u64 *W, *S, *G, *tot;  // tot: two sums per 4096 places (beyond kSumsHere)
     int *s_pos, *o_pos;
     int *by_o, *rank_of, *rank_pos, *o_of_rank;  // (only when the (o, id) order is sorted too)
     unsigned short *next;
@@ -613,34 +620,232 @@ __device__ __forceinline__ bool ranks_needed(const SortedArgs &p) { return !p.pa
 
 __device__ __forceinline__ bool faulty(const SortedArgs &p) { return (p.words[KVS_W_STATUS] & KVSCHED_DEV_BAD_LENGTH) != 0; }
 
-enum { KEYS_BY_O, KEYS_BY_SIZE, KEYS_BY_BATCH };
+enum { KEYS_BY_O, KEYS_BY_SIZE };
 
-// Keys of kRun consecutive requests (places, for KEYS_BY_BATCH), sorted.
+__device__ __forceinline__ u64 request_key(const SortedArgs &p, const LargeArrays &m, int what, int i, int s, int o)
+{
+    if (what == KEYS_BY_O) return ((u64)o << p.id_bits) | (u64)i;
+    const u64 w = (u64)s + (u64)o;
+    return p.packed ? (((w << p.o_bits) | (u64)o) << p.id_bits) | (u64)i : (w << p.id_bits) | (u64)m.rank_of[i];
+}
+
+// What a length scan leaves (one thread): status, longest decode.
+__device__ __forceinline__ void lengths_seen(const SortedArgs &p, bool bad, int omax)
+{
+    p.words[KVS_W_STATUS] = bad ? KVSCHED_DEV_BAD_LENGTH : 0;
+    p.words[KVS_W_STATUS_AT] = KVS_W_STATUS;
+    p.words[KVS_W_OMAX] = omax;
+    p.words[KVS_W_MINPOS] = 0x7fffffff;
+    p.words[KVS_W_MAXPOS] = -1;
+}
+
+// ------------------------------------------------ up to kCountMax requests: places by counting
+//
+// A request's place in an order is the number of smaller keys.  Every workgroup holds all keys in LDS and counts them for OWN
+// requests, 64 / OWN lanes of each wavefront a request and a 16 OWN / 64-th of the keys each; so the whole chip works, where sorted runs of 2048 keys
+// keep five compute units busy and have to be merged.  The first launch of a call is its length scan too, as every workgroup reads all
+// lengths.  Bound by vector issue, 2.5 instructions a comparison of 64 pairs, in three
+// fifths of the compute units: 10000 requests 18.4 us where scan, sorted runs and merges took 28 (and two launches, for the order by
+// (o, id), that found nothing to do 8), 5000 7.5, 2000 6.
+template <int OWN>
+__global__ __launch_bounds__(1024) void count_places_kernel(SortedArgs p, LargeArrays m, int what, int scan, u64 *out)
+{
+    extern __shared__ __align__(16) u64 keys[];
+    __shared__ int count[OWN], sh_omax;
+    constexpr int GROUPS = 1024 / OWN;
+    const int tid = threadIdx.x, lane = tid & 63, n = p.n;
+    if (!scan && faulty(p)) return;
+    if (blockIdx.y == 1) what = KEYS_BY_O;  // (beside the order by size)
+    if (tid < OWN) count[tid] = 0;
+    if (tid == 0) sh_omax = 0;
+    __syncthreads();
+    const int padded = (n + 8 * GROUPS - 1) / (8 * GROUPS) * (8 * GROUPS);
+    int omax = 0, bad = 0;
+    for (int i = tid; i < padded; i += 1024) {
+        u64 key = ~0ull;
+        if (i < n) {
+            const int s = p.s[i], o = p.o[i];
+            bad |= s < 1 || o < 1 || (long long)s + o > (long long)p.M;
+            omax = max(omax, o);
+            key = request_key(p, m, what, i, s, o);
+        }
+        keys[i] = key;
+    }
+    omax = wave_max_i32(omax);
+    if (lane == 0) atomicMax(&sh_omax, omax);
+    bad = __syncthreads_or(bad);
+    omax = sh_omax;
+    if (scan && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) lengths_seen(p, bad, omax);
+    if (bad || (blockIdx.y == 1 && omax <= kLargeBuckets)) return;  // (no ranks needed)
+
+    const int el = lane & (OWN - 1), i = OWN * blockIdx.x + el;
+    const u64 mine = keys[min(i, padded - 1)];
+    unsigned c = 0;
+    const ulonglong2 *two = (const ulonglong2 *)keys + tid / OWN;
+    for (int q = 0; q < padded / 2; q += 4 * GROUPS) {  // (four reads in flight)
+        ulonglong2 x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = two[q + r * GROUPS];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            c += x[r].x < mine ? 1u : 0u;
+            c += x[r].y < mine ? 1u : 0u;
+        }
+    }
+    atomicAdd(&count[el], (int)c);
+    __syncthreads();
+    if (tid >= OWN || i >= n) return;
+    const int place = count[tid];
+    if (what == KEYS_BY_SIZE) {
+        out[place] = mine;
+    } else {
+        const int id = (int)(mine & field_mask(p.id_bits));
+        m.by_o[place] = id;
+        m.rank_of[id] = place;
+        m.o_of_rank[place] = (int)(mine >> p.id_bits);
+    }
+}
+
+// The order: the requests of a batch, which lie together by size, in nondecreasing (o, id).  (10000 mixed requests, 5500 of them in one
+// batch, 22.8 us, sorted runs and merges 26; 5000 12.7.)  A workgroup counts for 64
+// places how many of their batch come before each; what lies to the left of the 64 places concerns the first's batch alone, what lies
+// to the right the last's.  NARROW: the keys (o, id), or the ranks that stand for them, fit in 32 bits.
+template <bool NARROW>
+__device__ __forceinline__ void order_of_places(const SortedArgs &p, const LargeArrays &m, const u64 *by_place, int lo_all, int hi_all,
+                                                int lo, int hi, u64 *tile, int *count)
+{
+    typedef typename std::conditional<NARROW, unsigned, u64>::type Key;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n, first = 64 * blockIdx.x, i = min(first + lane, n - 1);
+    const u64 low = p.packed ? field_mask(p.o_bits + p.id_bits) : field_mask(p.id_bits);
+    Key *const keys = (Key *)tile;
+    const Key mine = (Key)(by_place[i] & low);
+    const bool one = __builtin_amdgcn_ballot_w64(lo != lo_all || hi != hi_all) == 0;  // (one batch has all 64 places, mostly)
+    unsigned c = 0;
+    for (int j0 = lo_all; j0 < hi_all; j0 += kOrderTile) {
+        const int held = min(kOrderTile, hi_all - j0), all = (held + 127) & ~127;
+        __syncthreads();
+        for (int j = tid; j < all; j += 1024) keys[j] = j < held ? (Key)(by_place[j0 + j] & low) : ~(Key)0;
+        __syncthreads();
+        // (sixteen wavefronts, four keys each in turn)
+        if (one) {
+            for (int j = 4 * wave; j < all; j += 128) {
+                Key x[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) x[q] = keys[j + (q & 3) + 16 * (q & 4)];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) c += x[q] < mine ? 1u : 0u;
+            }
+        } else {
+            for (int j = 4 * wave; j < all; j += 64) {
+                const Key x[4] = {keys[j], keys[j + 1], keys[j + 2], keys[j + 3]};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c += x[q] < mine && (unsigned)(j0 + j + q - lo) < (unsigned)(hi - lo) ? 1u : 0u;
+            }
+        }
+    }
+    atomicAdd(&count[lane], (int)c);
+    __syncthreads();
+    if (tid >= 64 || first + lane >= n) return;
+    const int v = (int)(by_place[i] & field_mask(p.id_bits));
+    p.order_out[lo + count[lane]] = p.packed ? v : m.by_o[v];
+}
+
+__global__ __launch_bounds__(1024) void order_batches_kernel(SortedArgs p, LargeArrays m, const u64 *by_place)
+{
+    __shared__ __align__(16) u64 tile[kOrderTile];
+    __shared__ int count[64], ends[64];
+    const int nb = *p.num_batches_out;
+    if (faulty(p) || nb < 1) return;
+    const int tid = threadIdx.x, lane = tid & 63, n = p.n, first = 64 * blockIdx.x;
+    // the batch of the first place, by counting the ends before it, and the next 64 ends
+    int before = 0;
+    for (int b0 = 0; b0 < nb; b0 += 1024) before += __syncthreads_count(b0 + tid < nb && p.batch_end_out[min(b0 + tid, nb - 1)] <= first);
+    if (tid < 64) {
+        count[tid] = 0;
+        ends[tid] = p.batch_end_out[min(before + tid, nb - 1)];
+    }
+    __syncthreads();
+    const int i = min(first + lane, n - 1), last = min(first + 63, n - 1);
+    int lo = before > 0 ? p.batch_end_out[before - 1] : 0, hi = ends[0];
+    const int lo_all = lo;
+    int hi_all = hi;
+    for (int b = 0; b < 63 && ends[b] <= last; ++b) {  // (the same in all lanes; at most 64 batches touch 64 places)
+        if (ends[b] <= i) lo = ends[b], hi = ends[b + 1];
+        hi_all = ends[b + 1];
+    }
+    const int bits = p.packed ? 32 - __builtin_clz(max(p.words[KVS_W_OMAX], 1)) + p.id_bits : p.id_bits;
+    if (bits < 32) order_of_places<true>(p, m, by_place, lo_all, hi_all, lo, hi, tile, count);
+    else order_of_places<false>(p, m, by_place, lo_all, hi_all, lo, hi, tile, count);
+}
+
+// ------------------------------------------------ beyond: sorted runs and merges
+
+// Keys of kRun consecutive requests, sorted.  scan: the launch is the call's length scan as well (the workgroup that is done last takes
+// what the others have seen).  The second row of workgroups, if there is one, sorts by (o, id).
 template <int WHAT>
-__global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArrays m, const u64 *by_place, u64 *out)
+__global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArrays m, int scan, u64 *out, u64 *out_by_o)
 {
     __shared__ u64 buf[2 * kRun];
-    if (faulty(p) || (WHAT == KEYS_BY_O && !ranks_needed(p))) return;
+    __shared__ int sh_omax;
+    if (!scan && faulty(p)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const u64 id_mask = field_mask(p.id_bits);
-    const int nb = WHAT == KEYS_BY_BATCH ? *p.num_batches_out : 0;
+    const bool beside = blockIdx.y == 1;
+    if (threadIdx.x == 0) sh_omax = 0;
+    __syncthreads();
+    u64 key[2];
+    int omax = 0, bad = 0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int i = kRun * blockIdx.x + 128 * wave + 64 * e + lane;
+        key[e] = ~0ull;
+        if (i < p.n) {
+            const int s = p.s[i], o = p.o[i];
+            bad |= s < 1 || o < 1 || (long long)s + o > (long long)p.M;
+            omax = max(omax, o);
+            key[e] = request_key(p, m, beside ? KEYS_BY_O : WHAT, i, s, o);
+        }
+    }
+    if (scan && !beside) {
+        omax = wave_max_i32(omax);
+        if (lane == 0) atomicMax(&sh_omax, omax);
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) {
+            atomicMax(&p.words[KVS_W_SCAN_OMAX], sh_omax);
+            atomicOr(&p.words[KVS_W_SCAN_FLAGS], bad ? KVSCHED_DEV_BAD_LENGTH : 0);
+            device_writes_done();
+            if (atomicAdd(&p.words[KVS_W_SCAN_DONE], 1) == (int)gridDim.x - 1) {
+                omax = atomicExch(&p.words[KVS_W_SCAN_OMAX], 0);
+                lengths_seen(p, atomicExch(&p.words[KVS_W_SCAN_FLAGS], 0) != 0, omax);
+                atomicExch(&p.words[KVS_W_SCAN_DONE], 0);
+            }
+        }
+    }
+    block_sort<1024, 2>(key, buf);
+    u64 *const to = beside ? out_by_o : out;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int i = kRun * blockIdx.x + 128 * wave + 64 * e + lane;
+        if (i < p.n) to[i] = key[e];
+    }
+}
+
+// Keys (batch, o, id) of kRun consecutive places, sorted.
+__global__ __launch_bounds__(1024) void sort_batch_runs_kernel(SortedArgs p, const u64 *by_place, u64 *out)
+{
+    __shared__ u64 buf[2 * kRun];
+    if (faulty(p)) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nb = *p.num_batches_out;
     u64 key[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
         const int i = kRun * blockIdx.x + 128 * wave + 64 * e + lane;
         key[e] = ~0ull;
         if (i < p.n) {
-            if constexpr (WHAT == KEYS_BY_O) {
-                key[e] = ((u64)p.o[i] << p.id_bits) | (u64)i;
-            } else if constexpr (WHAT == KEYS_BY_SIZE) {
-                const u64 o = (u64)p.o[i], w = (u64)p.s[i] + o;
-                key[e] = p.packed ? (((w << p.o_bits) | o) << p.id_bits) | (u64)i : (w << p.id_bits) | (u64)m.rank_of[i];
-            } else {
-                const u64 old = by_place[i];
-                const u64 b = (u64)batch_of_place(p.batch_end_out, nb, i);
-                const u64 low = p.packed ? old & field_mask(p.o_bits + p.id_bits) : old & id_mask;
-                key[e] = (b << (p.packed ? p.o_bits + p.id_bits : p.id_bits)) | low;
-            }
+            const u64 old = by_place[i];
+            const u64 b = (u64)batch_of_place(p.batch_end_out, nb, i);
+            const int low = p.packed ? p.o_bits + p.id_bits : p.id_bits;
+            key[e] = (b << low) | (old & field_mask(low));
         }
     }
     block_sort<1024, 2>(key, buf);
@@ -654,12 +859,15 @@ __global__ __launch_bounds__(1024) void sort_runs_kernel(SortedArgs p, LargeArra
 // One pass of merging sorted runs of `run` keys, kFan at a time: the keys are distinct, so a key's place is its place
 // in its own run plus the number of smaller keys in the others, found by binary searches that advance together.
 // The last pass may emit what the key stands for: MERGE_IDS the request ids (the order), MERGE_RANKS the (o, id)
-// order and its inverse.
+// order and its inverse.  The second row of workgroups, if there is one, merges the runs by (o, id) (its last pass emits ranks).
 enum { MERGE_KEYS, MERGE_IDS, MERGE_RANKS };
 template <int EMIT>
-__global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArrays m, const u64 *in, u64 *out, int run, int of_ranks)
+__global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArrays m, const u64 *in, u64 *out, int run, int of_ranks,
+                                                         const u64 *in_by_o, u64 *out_by_o)
 {
-    if (faulty(p) || (of_ranks && !ranks_needed(p))) return;
+    const bool beside = blockIdx.y == 1;
+    if (faulty(p) || ((of_ranks || beside) && !ranks_needed(p))) return;
+    if (beside) in = in_by_o, out = out_by_o;
     const int g = blockIdx.x * 256 + threadIdx.x, n = p.n;
     if (g >= n) return;
     const u64 key = in[g];
@@ -684,48 +892,39 @@ __global__ __launch_bounds__(256) void merge_runs_kernel(SortedArgs p, LargeArra
 #pragma unroll
     for (int q = 0; q < kFan - 1; ++q) place += below[q];
     const int v = (int)(key & field_mask(p.id_bits));
-    if constexpr (EMIT == MERGE_KEYS) {
-        out[place] = key;
-    } else if constexpr (EMIT == MERGE_IDS) {
-        p.order_out[place] = p.packed ? v : m.by_o[v];
-    } else {
+    const bool last = (long long)run * kFan >= n;
+    if (EMIT == MERGE_RANKS || (beside && last)) {
         m.by_o[place] = v;
         m.rank_of[v] = place;
         m.o_of_rank[place] = (int)(key >> p.id_bits);
+    } else if (EMIT == MERGE_IDS && !beside) {
+        p.order_out[place] = p.packed ? v : m.by_o[v];
+    } else {
+        out[place] = key;
     }
 }
 
-// Lengths by sorted place, and the sums of s+o and o over each 4096 places.
-__global__ __launch_bounds__(1024) void place_lengths_kernel(SortedArgs p, LargeArrays m, const u64 *sorted, int ranks)
+// s + o and o of a sorted key.
+__device__ __forceinline__ void key_lengths(const SortedArgs &p, const LargeArrays &m, u64 key, u64 &w, u64 &o)
+{
+    w = p.packed ? key >> (p.id_bits + p.o_bits) : key >> p.id_bits;
+    o = p.packed ? (key >> p.id_bits) & field_mask(p.o_bits) : (u64)m.o_of_rank[(int)(key & field_mask(p.id_bits))];
+}
+
+// The sums of s + o and o over each 4096 places.
+__global__ __launch_bounds__(1024) void place_sums_kernel(SortedArgs p, LargeArrays m, const u64 *sorted)
 {
     if (faulty(p)) return;
-    ranks = ranks && ranks_needed(p);
     __shared__ u64 tw[16], tq[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const u64 id_mask = field_mask(p.id_bits);
     u64 aw = 0, aq = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
-        if (i < p.n) {
-            const u64 key = sorted[i];
-            u64 w, o;
-            int rank = 0;
-            if (p.packed) {
-                o = (key >> p.id_bits) & field_mask(p.o_bits);
-                w = key >> (p.id_bits + p.o_bits);
-                if (ranks) rank = m.rank_of[(int)(key & id_mask)];
-            } else {
-                rank = (int)(key & id_mask);
-                o = (u64)m.o_of_rank[rank];
-                w = key >> p.id_bits;
-            }
-            m.s_pos[i] = (int)(w - o);
-            m.o_pos[i] = (int)o;
-            if (ranks) m.rank_pos[i] = rank;
-            aw += w;
-            aq += o;
-        }
+        const int i = 4096 * blockIdx.x + 1024 * e + threadIdx.x;
+        u64 w = 0, o = 0;
+        if (i < p.n) key_lengths(p, m, sorted[i], w, o);
+        aw += w;
+        aq += o;
     }
     aw = lane_value_u64(wave_scan_u64(aw), 63);
     aq = lane_value_u64(wave_scan_u64(aq), 63);
@@ -738,13 +937,39 @@ __global__ __launch_bounds__(1024) void place_lengths_kernel(SortedArgs p, Large
     }
 }
 
-__global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeArrays m)
+// Lengths by sorted place and their prefix sums, 4096 places a workgroup.  What lies before its own comes from the sums that a launch
+// ahead has left (summed), or is added up here: up to kSumsHere requests that costs less than the launch (4.7 us; 100000 requests 19 us
+// against 8 and 5).
+__global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeArrays m, const u64 *sorted, int ranks, int summed)
 {
     if (faulty(p)) return;
+    ranks = ranks && ranks_needed(p);
     __shared__ u64 tw[16], tq[16], bw[16], bq[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const u64 id_mask = field_mask(p.id_bits);
+    u64 key[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
+        key[e] = sorted[min(i, p.n - 1)];
+    }
     u64 fw = 0, fq = 0;  // everything before this block
-    for (int b = threadIdx.x; b < (int)blockIdx.x; b += 1024) fw += m.tot[2 * b], fq += m.tot[2 * b + 1];
+    if (summed) {
+        for (int b = threadIdx.x; b < (int)blockIdx.x; b += 1024) fw += m.tot[2 * b], fq += m.tot[2 * b + 1];
+    } else {
+        for (int i0 = threadIdx.x; i0 < 4096 * (int)blockIdx.x; i0 += 4096) {
+            u64 k[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) k[e] = sorted[i0 + 1024 * e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u64 w, o;
+                key_lengths(p, m, k[e], w, o);
+                fw += w;
+                fq += o;
+            }
+        }
+    }
     fw = lane_value_u64(wave_scan_u64(fw), 63);
     fq = lane_value_u64(wave_scan_u64(fq), 63);
     if (lane == 0) bw[wave] = fw, bq[wave] = fq;
@@ -752,8 +977,14 @@ __global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeAr
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int i = 4096 * blockIdx.x + 256 * wave + 64 * e + lane;
-        const u64 o = i < p.n ? (u64)m.o_pos[i] : 0, s = i < p.n ? (u64)m.s_pos[i] : 0;
-        w[e] = wave_scan_u64(s + o) + cw;
+        u64 wi = 0, o = 0;
+        if (i < p.n) {
+            key_lengths(p, m, key[e], wi, o);
+            m.s_pos[i] = (int)(wi - o);
+            m.o_pos[i] = (int)o;
+            if (ranks) m.rank_pos[i] = p.packed ? m.rank_of[(int)(key[e] & id_mask)] : (int)(key[e] & id_mask);
+        }
+        w[e] = wave_scan_u64(wi) + cw;
         q[e] = wave_scan_u64(o) + cq;
         cw = lane_value_u64(w[e], 63);
         cq = lane_value_u64(q[e], 63);
@@ -823,14 +1054,24 @@ __device__ __forceinline__ int wave_count_fitting(int rem, G g, u64 M)
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-template <int ROWS>  // completion times up to 64 ROWS, and beyond those of a smaller launch
-__global__ __launch_bounds__(64) void profile_extents_kernel(SortedArgs p, LargeArrays m, int per, int above)
+// Words of LDS that completion times up to 64 `rows` take.
+constexpr int extent_words(int rows) { return 64 * rows + 2 * 64 * (rows + 2); }
+
+// Two wavefronts a workgroup, each with half of its LDS, where completion times are up to 2048; beyond, the first one has all of it.
+__global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, LargeArrays m)
 {
-    __shared__ __align__(16) unsigned held[64 * ROWS];     // at time b + 1
-    __shared__ __align__(16) u64 slot[64 * (ROWS + 2)];    // (number, sum of s) of the requests that join, by their time
+    constexpr int kRows = kLargeBuckets / 64;
+    __shared__ __align__(16) unsigned lds[2 * extent_words(kRows / 2)];
+    static_assert(2 * extent_words(kRows / 2) >= extent_words(kRows), "");
     const int omax = p.words[KVS_W_OMAX];
-    if (faulty(p) || omax > 64 * ROWS || omax <= above || !extents_ahead(p, m)) return;
-    const int lane = threadIdx.x, n = p.n, a0 = blockIdx.x * per, a1 = min(a0 + per, n);
+    if (faulty(p) || !extents_ahead(p, m)) return;
+    const bool pairs = omax <= kLargeBuckets / 2;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (wave == 1 && !pairs) return;
+    unsigned *const held = lds + wave * extent_words(kRows / 2);           // at time b + 1
+    u64 *const slot = (u64 *)(held + 64 * (pairs ? kRows / 2 : kRows));    // (number, sum of s) of the requests that join, by their time
+    const int waves = pairs ? 2 * (int)gridDim.x : (int)gridDim.x, mine_no = pairs ? 2 * (int)blockIdx.x + wave : (int)blockIdx.x;
+    const int lane = threadIdx.x & 63, n = p.n, per = (n + waves - 1) / waves, a0 = mine_no * per, a1 = min(a0 + per, n);
     if (a0 >= a1) return;
     const unsigned M = (unsigned)p.M;
     // Times four to a lane, 256 a turn; while those of a join are summed lane l has the times rows l + 1 .. rows l + rows (rows a
@@ -1122,19 +1363,63 @@ int launch_small(const SortedArgs &p, hipStream_t st)
 }
 
 // Merge sorted runs of kRun keys of m.key[0] (through m.key[1] and back) to the end; returns where the keys are
-// (EMIT other than MERGE_KEYS: the last pass emits instead and the result is void).
+// (EMIT other than MERGE_KEYS: the last pass emits instead and the result is void).  by_o: two arrays with the runs by (o, id) in
+// the first, merged beside them, or null.
 template <int EMIT>
-const u64 *launch_merges(const SortedArgs &p, const LargeArrays &m, hipStream_t st)
+const u64 *launch_merges(const SortedArgs &p, const LargeArrays &m, u64 *const *by_o, hipStream_t st)
 {
-    const dim3 grid((unsigned)((p.n + 255) / 256)), block(256);
+    const dim3 grid((unsigned)((p.n + 255) / 256), by_o ? 2u : 1u), block(256);
     int at = 0;
     for (long long run = kRun; run < p.n; run *= kFan) {
         const bool last = run * kFan >= p.n;
-        if (last) hipLaunchKernelGGL((merge_runs_kernel<EMIT>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS);
-        else hipLaunchKernelGGL((merge_runs_kernel<MERGE_KEYS>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS);
+        const u64 *const from = by_o ? by_o[at] : nullptr;
+        u64 *const to = by_o ? by_o[at ^ 1] : nullptr;
+        if (last) hipLaunchKernelGGL((merge_runs_kernel<EMIT>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS, from, to);
+        else hipLaunchKernelGGL((merge_runs_kernel<MERGE_KEYS>), grid, block, 0, st, p, m, m.key[at], m.key[at ^ 1], (int)run, EMIT == MERGE_RANKS, from, to);
         at ^= 1;
     }
     return m.key[at];
+}
+
+template <int OWN>
+int launch_count(const SortedArgs &p, const LargeArrays &m, int what, bool beside, bool scan, u64 *out, hipStream_t st)
+{
+    static const hipError_t granted = hipFuncSetAttribute((const void *)count_places_kernel<OWN>,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 8 * kCountMax);
+    if (granted != hipSuccess) return KVSCHED_EHIP;
+    constexpr int turn = 8 * 1024 / OWN;
+    static_assert(kCountMax % turn == 0 && 8 * kCountMax + 1024 <= 160 * 1024, "fits the LDS");
+    const int padded = (p.n + turn - 1) / turn * turn;
+    hipLaunchKernelGGL(count_places_kernel<OWN>, dim3((unsigned)((p.n + OWN - 1) / OWN), beside ? 2u : 1u), dim3(1024), 8 * padded, st, p, m,
+                       what, scan ? 1 : 0, out);
+    return ok();
+}
+
+// The sorted keys by size (and the ranks in the (o, id) order where they may be needed); returns where they are.
+int launch_places(const SortedArgs &p, LargeArrays &m, bool ranks, const u64 **sorted, hipStream_t st)
+{
+    const bool beside = ranks && p.packed;  // (otherwise the keys by size hold ranks)
+    if (p.n <= kCountMax) {
+        // 32 requests a workgroup up to as many workgroups as compute units
+        auto count = [&](int what, bool both, bool scan) {
+            return p.n <= 32 * 256 ? launch_count<32>(p, m, what, both, scan, m.key[0], st)
+                                   : launch_count<64>(p, m, what, both, scan, m.key[0], st);
+        };
+        int rc = KVSCHED_OK;
+        if (ranks && !beside) rc = count(KEYS_BY_O, false, true);
+        if (rc == KVSCHED_OK) rc = count(KEYS_BY_SIZE, beside, !ranks || beside);
+        *sorted = m.key[0];
+        return rc;
+    }
+    const dim3 runs((unsigned)((p.n + kRun - 1) / kRun)), both(runs.x, 2);
+    u64 *const by_o[2] = {m.W, m.S};  // (not in use yet)
+    if (ranks && !beside) {
+        hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_O>), runs, dim3(1024), 0, st, p, m, 1, m.key[0], (u64 *)nullptr);
+        (void)launch_merges<MERGE_RANKS>(p, m, nullptr, st);
+    }
+    hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_SIZE>), beside ? both : runs, dim3(1024), 0, st, p, m, !ranks || beside ? 1 : 0, m.key[0], by_o[0]);
+    *sorted = launch_merges<MERGE_KEYS>(p, m, beside ? by_o : nullptr, st);
+    return ok();
 }
 
 template <bool PROFILE>
@@ -1151,13 +1436,6 @@ int launch_chain(const SortedArgs &p, const LargeArrays &m, hipStream_t st)
     return ok();
 }
 
-template <int ROWS>
-void launch_extents(const SortedArgs &p, const LargeArrays &m, int waves, int above, hipStream_t st)
-{
-    const int per = (p.n + waves - 1) / waves;
-    hipLaunchKernelGGL(profile_extents_kernel<ROWS>, dim3((unsigned)((p.n + per - 1) / per)), dim3(64), 0, st, p, m, per, above);
-}
-
 int bits_for(long long v)  // bits that hold 0..v
 {
     int b = 1;
@@ -1169,9 +1447,13 @@ size_t padded(int32_t n) { return ((size_t)n + 64) & ~(size_t)63; }
 
 }  // namespace
 
-// Largest construction done by one workgroup: n = 4096 takes 4 keys a thread; the profile test's arrays leave room
-// for 2048.
-int32_t kvs_sortedF_small_max(int32_t feas_mode) { return feas_mode == KVSCHED_FEAS_PROFILE ? 2048 : 4096; }
+// Largest construction done by one workgroup.  Its sorts and the chain grow with the requests and batches, most of the chip's launches
+// do not.  Mixed requests in 6 / 20 / 40 batches, one workgroup and the chip: 700 17 / 22 / 30 us against 26 for all; 1025 (two keys a
+// thread) 30 / 38 / 87 before the chain was one wavefront's, 27 / 27 / 29 by the chip; 2000 31 / 34 / 40 and 32 / 30 / 31; 4000 55 / 59 /
+// 63 and 43 / 38 / 37.  2000 chat requests in 3 batches, the other way: 29 and 34.  Under the profile constraint, where one
+// workgroup finds one extent after the other and the chip those of all places: 100 mixed requests in 5 / 10 / 25 batches 27 / 32 / 46 and
+// 29 / 31 / 32, 256 in 6 / 22 / 55 40 / 55 / 89 and 38 / 40 / 42, 200 chat requests in 3 / 14 33 / 43 and 38 / 30.
+int32_t kvs_sortedF_small_max(int32_t feas_mode) { return feas_mode == KVSCHED_FEAS_PROFILE ? kSmallProfile : kSmallSum; }
 
 size_t kvs_sortedF_scratch_bytes(int32_t n)
 {
@@ -1181,8 +1463,7 @@ size_t kvs_sortedF_scratch_bytes(int32_t n)
     return np * 5 * sizeof(u64) + (2 * sizeof(u64)) * (np / 4096 + 1) + np * 10 * sizeof(int) + 2 * np + 1024;
 }
 
-// Up to kvs_sortedF_small_max requests the kernel scans the lengths itself (status word and longest decode);
-// beyond, the caller has launched the length scan before.
+// (The first launch scans the lengths as well: status word and longest decode.)
 int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M, int32_t ga, int32_t gb,
                        int32_t tie_rule, int32_t feas_mode, int32_t pad, int32_t *order_out, int32_t *batch_end_out,
                        double *F_out, int32_t *num_batches_out, void *scratch, int32_t *d_words, hipStream_t st)
@@ -1211,14 +1492,11 @@ int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
     if (n <= kvs_sortedF_small_max(feas_mode)) {
         if (profile) {
             if (n <= 64) return launch_small<64, 1, true>(p, st);
-            if (n <= 1024) return launch_small<1024, 1, true>(p, st);
-            return launch_small<1024, 2, true>(p, st);
+            return launch_small<1024, 1, true>(p, st);
         }
         if (n <= 64) return launch_small<64, 1, false>(p, st);
         if (n <= 256) return launch_small<256, 1, false>(p, st);
-        if (n <= 1024) return launch_small<1024, 1, false>(p, st);
-        if (n <= 2048) return launch_small<1024, 2, false>(p, st);
-        return launch_small<1024, 4, false>(p, st);
+        return launch_small<1024, 1, false>(p, st);
     }
     const size_t np = padded(n);
     LargeArrays m;
@@ -1239,32 +1517,31 @@ int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
     m.hist = (unsigned *)(i + 6 * np);
     m.extent = (int *)m.hist;
     m.next = (unsigned short *)(i + 10 * np);
-    const dim3 runs((unsigned)((n + kRun - 1) / kRun)), sums((unsigned)((n + 4095) / 4096));
     // Ranks in the (o, id) order are needed by keys that do not fit and, under the profile constraint, when completion
     // times may be too many for buckets in LDS.
-    const int ranks = !p.packed || (profile && M > kLargeBuckets);
-    if (ranks) {
-        hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_O>), runs, dim3(1024), 0, st, p, m, (const u64 *)nullptr, m.key[0]);
-        (void)launch_merges<MERGE_RANKS>(p, m, st);
-    }
-    hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_SIZE>), runs, dim3(1024), 0, st, p, m, (const u64 *)nullptr, m.key[0]);
-    const u64 *sorted = launch_merges<MERGE_KEYS>(p, m, st);
+    const bool ranks = !p.packed || (profile && M > kLargeBuckets);
+    const u64 *sorted = nullptr;
+    int rc = launch_places(p, m, ranks, &sorted, st);
+    if (rc != KVSCHED_OK) return rc;
     if (sorted != m.key[1]) {  // (the batches' keys are written beside them)
         m.key[0] = m.key[1];
         m.key[1] = (u64 *)sorted;
     }
-    hipLaunchKernelGGL(place_lengths_kernel, sums, dim3(1024), 0, st, p, m, sorted, ranks);
-    hipLaunchKernelGGL(prefix_sums_kernel, sums, dim3(1024), 0, st, p, m);
+    const dim3 sums((unsigned)((n + 4095) / 4096));
+    if (n > kSumsHere) hipLaunchKernelGGL(place_sums_kernel, sums, dim3(1024), 0, st, p, m, sorted);
+    hipLaunchKernelGGL(prefix_sums_kernel, sums, dim3(1024), 0, st, p, m, sorted, ranks ? 1 : 0, n > kSumsHere ? 1 : 0);
     const dim3 waves((unsigned)((n + 3) / 4));
-    if (profile) {  // (the one whose times do not match ends at once; wavefronts: what the LDS of 256 compute units holds)
-        launch_extents<32>(p, m, 6 * 256, 0, st);
-        launch_extents<kLargeBuckets / 64>(p, m, 3 * 256, 2048, st);
-    }
+    // (as many workgroups as the LDS of 256 compute units holds)
+    if (profile) hipLaunchKernelGGL(profile_extents_kernel, dim3((unsigned)(n < 3 * 256 ? n : 3 * 256)), dim3(128), 0, st, p, m);
     if (profile) hipLaunchKernelGGL((next_batch_kernel<true>), waves, dim3(256), 0, st, p, m);
     else hipLaunchKernelGGL((next_batch_kernel<false>), waves, dim3(256), 0, st, p, m);
-    const int rc = profile ? launch_chain<true>(p, m, st) : launch_chain<false>(p, m, st);
+    rc = profile ? launch_chain<true>(p, m, st) : launch_chain<false>(p, m, st);
     if (rc != KVSCHED_OK) return rc;
-    hipLaunchKernelGGL((sort_runs_kernel<KEYS_BY_BATCH>), runs, dim3(1024), 0, st, p, m, sorted, m.key[0]);
-    (void)launch_merges<MERGE_IDS>(p, m, st);
+    if (n <= kCountMax) {
+        hipLaunchKernelGGL(order_batches_kernel, dim3((unsigned)((n + 63) / 64)), dim3(1024), 0, st, p, m, sorted);
+    } else {
+        hipLaunchKernelGGL(sort_batch_runs_kernel, dim3((unsigned)((n + kRun - 1) / kRun)), dim3(1024), 0, st, p, sorted, m.key[0]);
+        (void)launch_merges<MERGE_IDS>(p, m, nullptr, st);
+    }
     return ok();
 }
