@@ -354,7 +354,7 @@ __device__ __forceinline__ int batch_of_place(const int *ends, int nb, int place
 
 // Everything in one workgroup: n <= TPB * E requests, element 64 E wave + 64 e + lane of an order in k[e].
 // Also the length scan of the call (status word, longest decode).  What bounds it is latency, a chain of short
-// steps: 61 requests 22 -> 7 us (one wavefront, no barrier waits for anyone), 200 30 -> 12 us, 2000 92 -> 56 us.
+// steps: 61 requests 22 -> 7 us (one wavefront, no barrier waits for anyone), 200 30 -> 12 us.
 template <int TPB, int E, bool PROFILE>
 __global__ __launch_bounds__(TPB) void sortedF_small_kernel(SortedArgs p)
 {
@@ -598,8 +598,7 @@ constexpr size_t small_lds_bytes(int N, bool profile)
 {
     return (size_t)(profile ? 3 : 2) * 8 * (N + 2) + (size_t)(profile ? 7 : 3) * 4 * N + (profile ? 16 * kSmallBuckets : 0);
 }
-static_assert(small_lds_bytes(2048, false) >= 16 * 2048 && small_lds_bytes(1024, true) + 2048 <= 160 * 1024 && kSmallSum <= 2048 &&
-                  kSmallProfile <= 1024, "fits the LDS");
+static_assert(small_lds_bytes(1024, true) + 2048 <= 160 * 1024 && kSmallSum <= 1024 && kSmallProfile <= 1024, "fits the LDS");
 
 // ------------------------------------------------------------------------- many workgroups
 
@@ -1018,8 +1017,7 @@ __device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c
 // there are six budgets' worth of requests or more, and if the extents are on average beyond 64, or kNextMax where completion
 // times are beyond 2048.  Whole call, before -> now: 10000 mixed requests in 17 batches 256 -> 157 us, 44 batches 273 -> 162; 40000 in 43
 // 823 -> 312; 10000 chat requests in 9 375 -> 151; 40000 bimodal ones in 69 1878 -> 486.  The other side: 40000 chat requests in 3 batches 236
-// (270 with it), 10000 bimodal ones in 213 138 (191), in 70 171 (181).  Where they are not, two launches end at once: 5000 mixed
-// requests in 5 batches 186 -> 191, 10000 chat ones in 3 118 -> 120.
+// (270 with it), 10000 bimodal ones in 213 138 (191), in 70 171 (181).  Where they are not, the launch ends at once.
 __device__ __forceinline__ bool extents_ahead(const SortedArgs &p, const LargeArrays &m)
 {
     const int omax = p.words[KVS_W_OMAX];
@@ -1487,8 +1485,7 @@ int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
     p.packed = 2 * p.o_bits + p.id_bits <= 63 && p.o_bits + 2 * p.id_bits <= 63;
     p.pad = pad;
     const bool profile = feas_mode == KVSCHED_FEAS_PROFILE;
-    // One workgroup: as few wavefronts as hold the keys one each (a barrier costs by the wavefront), two or four each
-    // beyond 1024.
+    // One workgroup: as few wavefronts as hold the keys one each (a barrier costs by the wavefront).
     if (n <= kvs_sortedF_small_max(feas_mode)) {
         if (profile) {
             if (n <= 64) return launch_small<64, 1, true>(p, st);
