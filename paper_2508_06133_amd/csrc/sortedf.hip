@@ -1012,17 +1012,22 @@ __global__ __launch_bounds__(1024) void prefix_sums_kernel(SortedArgs p, LargeAr
 __device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c) { return p.n < 65536 && c.G[p.n] < (1ull << 32); }
 
 // Under the profile constraint: are the extents of all places found ahead (profile_extents_kernel), or each where the chain
-// needs it?  The former costs what one extent costs, 30 to 60 us, and then some microseconds for each of the 6 (40000 requests) to 50
-// places that a wavefront takes; the chain takes some 20 us for each batch, if the extents are beyond kNextMax.  Hence ahead if
-// there are six budgets' worth of requests or more, and if the extents are on average beyond 64, or kNextMax where completion
-// times are beyond 2048.  Whole call, before -> now: 10000 mixed requests in 17 batches 256 -> 157 us, 44 batches 273 -> 162; 40000 in 43
-// 823 -> 312; 10000 chat requests in 9 375 -> 151; 40000 bimodal ones in 69 1878 -> 486.  The other side: 40000 chat requests in 3 batches 236
-// (270 with it), 10000 bimodal ones in 213 138 (191), in 70 171 (181).  Where they are not, the launch ends at once.
+// needs it?  The former costs what one extent costs, 15 to 45 us, and then a microsecond or two for each of the 1 (up to 1536 requests) to
+// 26 (40000) places that a wavefront takes; the chain takes some 20 us for each batch, if the extents are beyond kNextMax, and the
+// launch before it some time for each place if they are below.  Completion times up to 2048, the chain and ahead: 5000 mixed
+// requests in 6 batches 170 and 75 us, in 73 213 and 80, in 240 175 and 91; 1000 chat requests in 3 73 and 56, 10000 143 and 130; 400
+// mixed ones in 5 64 and 41.  The other side: extents of 16 requests and fewer, 300 chat requests in 23 batches 32 and 39, 2000 in 37 47
+// and 53; and those beyond some 10000, which every wavefront reads through, 40000 chat requests in 3 batches 219 and 240.  Beyond 2048 an
+// extent costs twice and more and half as many wavefronts find them: 400 bimodal requests in 12 batches 36 and 56, 10000 in 42
+// 145 and 193, 2000 in 11 91 and 127.
+constexpr u64 kAheadMost = 10000;
+
 __device__ __forceinline__ bool extents_ahead(const SortedArgs &p, const LargeArrays &m)
 {
     const int omax = p.words[KVS_W_OMAX];
-    const u64 all = m.W[p.n], M = (u64)p.M;
-    return omax <= kLargeBuckets && all >= 6 * M && (u64)p.n * M >= (omax > 2048 ? kNextMax : 64) * all;
+    const u64 all = m.W[p.n], M = (u64)p.M, some = (u64)p.n * M;  // (some / all requests an extent, on average)
+    if (omax <= kLargeBuckets / 2) return all >= M && some >= 16 * all && some <= kAheadMost * all;
+    return omax <= kLargeBuckets && all >= 6 * M && some >= kNextMax * all;
 }
 
 // The longest feasible prefix at every place under the simultaneous-start profile, where extents_ahead.  A
@@ -1032,8 +1037,10 @@ __device__ __forceinline__ bool extents_ahead(const SortedArgs &p, const LargeAr
 // leaves, those behind the end join as long as they fit (a prefix without its first request stays feasible, so
 // the end never moves back).  What bounds it is latency, the first extent's chain of some five joins of 3 us and the wavefront
 // whose end moves most; the loops over times are kept rolled and everything in LDS, because the code is run once: with the times in
-// registers and the loops unrolled, 19 KB of code, 10000 requests took 120 us instead of 66.
-constexpr int kJoinMin = 16;  // fewer requests are added one by one
+// registers and the loops unrolled, 19 KB of code, 10000 requests took 120 us instead of 66.  One request costs a pass over the times up
+// to its own, which adds it and finds whether it fits (if not, a second pass takes it away again; with a pass to look and one to
+// add, and every time compared with the request's, the whole call took 135 us instead of 120, 40000 bimodal requests in 11 batches 1690
+// instead of 1360).
 
 // The largest k in [0, rem] with g(k) <= M, for g increasing in k, by one wavefront.
 template <class G>
@@ -1069,6 +1076,9 @@ __global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, Larg
     unsigned *const held = lds + wave * extent_words(kRows / 2);           // at time b + 1
     u64 *const slot = (u64 *)(held + 64 * (pairs ? kRows / 2 : kRows));    // (number, sum of s) of the requests that join, by their time
     const int waves = pairs ? 2 * (int)gridDim.x : (int)gridDim.x, mine_no = pairs ? 2 * (int)blockIdx.x + wave : (int)blockIdx.x;
+    // Fewer requests are added one by one (10000 mixed requests in 17 batches 120 -> 115 us with 8 instead of 16; of completion times beyond
+    // 2048, a join of which costs twice as much, 40000 bimodal ones in 11 1340 -> 1760).
+    const int join_min = pairs ? 8 : 16;
     const int lane = threadIdx.x & 63, n = p.n, per = (n + waves - 1) / waves, a0 = mine_no * per, a1 = min(a0 + per, n);
     if (a0 >= a1) return;
     const unsigned M = (unsigned)p.M;
@@ -1136,19 +1146,31 @@ __global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, Larg
         }
         return all;
     };
-    // what a request adds to the lane's times of turn r
-    auto ramp = [&](int s, int o, int r) __attribute__((always_inline)) {
-        const int b = 256 * r + 4 * lane;
-        const unsigned v = (unsigned)(s + b + 1);
-        return (u32x4){b < o ? v : 0u, b + 1 < o ? v + 1 : 0u, b + 2 < o ? v + 2 : 0u, b + 3 < o ? v + 3 : 0u};
-    };
-    // the most that any time it touches holds with one more request
-    auto most_with = [&](int s, int o) __attribute__((always_inline)) -> unsigned {
+    // One request more (sign 1), and the most that any time it touches holds then, or one less (sign -1).  Turns that lie in its times
+    // as a whole need no choice by the time.
+    auto change = [&](int s, int o, auto sign) __attribute__((always_inline)) -> unsigned {
+        constexpr unsigned kSign = (unsigned)decltype(sign)::value;
         u32x4 most = (u32x4)0u;
+        unsigned v = kSign * (unsigned)(s + 4 * lane + 1);
+        const int whole = o >> 8;
 #pragma unroll 4
-        for (int r = 0; r < (o + 255) >> 8; ++r) most = __builtin_elementwise_max(most, mine[64 * r] + ramp(s, o, r));
+        for (int r = 0; r < whole; ++r) {
+            const u32x4 x = mine[64 * r] + (u32x4){v, v + kSign, v + 2 * kSign, v + 3 * kSign};
+            mine[64 * r] = x;
+            most = __builtin_elementwise_max(most, x);
+            v += 256 * kSign;
+        }
+        if ((o & 255) != 0) {
+            const int left = (o & 255) - 4 * lane;
+            const u32x4 x = mine[64 * whole] +
+                            (u32x4){left > 0 ? v : 0u, left > 1 ? v + kSign : 0u, left > 2 ? v + 2 * kSign : 0u, left > 3 ? v + 3 * kSign : 0u};
+            mine[64 * whole] = x;
+            most = __builtin_elementwise_max(most, x);
+        }
         return ~wave_min_u32(~max(max(most.x, most.y), max(most.z, most.w)));
     };
+    const std::integral_constant<int, 1> joins;
+    const std::integral_constant<int, -1> leaves;
 
     // the sum of peaks bounds the memory of the first place's prefixes from above, sum (s_i + 1) that of every place's from below
     const u64 W0 = m.W[a0];
@@ -1160,7 +1182,7 @@ __global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, Larg
     for (;;) {
         bool failed = false;
         while (e < n && over <= 0) {
-            if (step >= kJoinMin) {
+            if (step >= join_min) {
                 step = min(step, min(1 << 18, n - e));
                 const u64 Pa = m.W[a] - m.S[a];
                 unsigned most = ~0u;
@@ -1183,12 +1205,12 @@ __global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, Larg
                 ov = m.o_pos[i];
             }
             const int s = __builtin_amdgcn_readlane(sv, e - base), o = __builtin_amdgcn_readlane(ov, e - base);
-            over = (int)(most_with(s, o) - M);
-            if (over <= 0) {
-#pragma unroll 4
-                for (int r = 0; r < (o + 255) >> 8; ++r) mine[64 * r] += ramp(s, o, r);
+            over = (int)(change(s, o, joins) - M);
+            if (over > 0) {
+                change(s, o, leaves);
+            } else {
                 ++e;
-                if (!failed && ++step == 4) step = 2 * kJoinMin;  // (a few in a row: many may follow)
+                if (!failed && ++step == 4) step = 2 * join_min;  // (a few in a row: many may follow)
             }
         }
         step = 0;
@@ -1201,8 +1223,7 @@ __global__ __launch_bounds__(128) void profile_extents_kernel(SortedArgs p, Larg
             oa = m.o_pos[i];
         }
         const int s = __builtin_amdgcn_readlane(sa, a - first), o = __builtin_amdgcn_readlane(oa, a - first);
-#pragma unroll 4
-        for (int r = 0; r < (o + 255) >> 8; ++r) mine[64 * r] -= ramp(s, o, r);
+        change(s, o, leaves);
         over -= s + o;  // (no time loses more)
         ++a;
     }

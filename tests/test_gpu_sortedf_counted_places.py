@@ -73,3 +73,15 @@ def test_a_faulty_request_and_a_good_call_after_it(ctx):
                 assert int(nb.item()) == 0 and ctx.device_status() == 1
                 assert (ends == 0).all() and (F == 0).all()
         _check(ctx, s, o, max(4200, 60 * n), 1, 0)
+
+
+@pytest.mark.parametrize("n,omax", [(150, 2048), (1200, 2047), (1200, 255), (3000, 2049), (24000, 2048), (24000, 256)])
+def test_extents_found_ahead_or_by_the_chain(ctx, n, omax):
+    """One batch and more, extents around 16 and around 10000 requests, longest decodes around 2048 and full turns of 256 times."""
+    rng = np.random.default_rng(n + omax)
+    s, o = rng.integers(1, 400, n), rng.integers(1, omax + 1, n)
+    o[: n // 8] = np.minimum(omax, 256 * rng.integers(1, 9, n // 8))
+    o[n // 2] = omax
+    total = int((s + o).sum())
+    for M in (total, total - 1, total // 2, total // 7, 16 * total // n, 16 * total // n - 1, 10000 * total // n, 10000 * total // n + 1):
+        _check(ctx, s, o, min(max(M, 400 + omax), (1 << 30) - 1), 1, n & 1)
