@@ -181,8 +181,8 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // themselves: place_block returns after kRunMoved + 1 requests in a row that did not move the round.
 //
 // What it gives: of bimodal orders (decodes 1 or 4096) 97 % of the requests start that way, 56 at a time, and their ramps are added 340 at a
-// time: 1025 orders of 100000 27.2 -> 4.5 ms, of which the timelines 26.3 -> 3.6: one wavefront per SIMD, bound by the chain
-// of the blocks (loads, prefix sum, list: 1500 cycles per 64 requests) and of the 250 moves.  4096 chat orders of 200, half of
+// time: 1025 orders of 100000 27.2 -> 4.5 ms (3.4 now), of which the timelines 26.3 -> 3.6 (3.0): one wavefront per SIMD, bound by the chain
+// of the blocks (prefix sum, list: 1200 cycles per 64 requests) and of the 250 moves.  4096 chat orders of 200, half of
 // them in the first burst: 82.5 -> 80 us.  Below kGroupMin requests the pass over the rows (75 instructions per chunk with
 // entries) costs more than they do one by one.
 constexpr int kChunkRows = 4;
@@ -834,7 +834,7 @@ __device__ __forceinline__ int group_size(int rem, int size, int lane, int shift
     const int below = lane_prefix_sum(unit);  // lanes 0 .. lane
     const int total = __builtin_amdgcn_readlane(below, WAVE - 1);
     const unsigned sum = (unsigned)(total - below + unit);  // lanes lane .. rem - 1
-    const unsigned long long fits = __builtin_amdgcn_ballot_w64(lane < rem && sum <= (unsigned)H >> shift);
+    const unsigned long long fits = __builtin_amdgcn_ballot_w64(lane < rem) & __builtin_amdgcn_ballot_w64(sum <= (unsigned)H >> shift);
     const int g = __popcll(fits);
     if (g > 0) H -= __builtin_amdgcn_readlane((int)sum, rem - g) << shift;
     return g;
@@ -1410,20 +1410,20 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
     // lane 0 the last (place_block counts its lane number down).
     constexpr bool AHEAD = !RES && !MOVES;
     int rq_n = 0, sv_n = 1, ov_n = 1, id_nn = 0;
+    // (lanes without a position take the last one there is)
     auto id_at = [&](int first) __attribute__((always_inline)) -> int {
-        const int at = first + min(WAVE, n - first) - 1 - lane;
-        return at >= first ? rd.at(at) : 0;
-    };
-    auto fetch = [&](int first) __attribute__((always_inline)) {
-        rq_n = 0, sv_n = 1, ov_n = 1;
         int l = lane;
         asm volatile("" : "+v"(l));  // (as in group_clear)
-        const int at = first + min(WAVE, n - first) - 1 - l;
-        if (at >= first) {
-            rq_n = min(max(AHEAD ? id_nn : rd.at(at), 0), n_all - 1);
-            sv_n = p.s[rq_n];
-            ov_n = p.o[rq_n];
-        }
+        return rd.at(max(min(first + WAVE, n) - 1 - l, min(first, n - 1)));
+    };
+    // (byte offsets of 32 bits: there are fewer than 2^21 requests)
+    auto gathered = [&](const int32_t *from, int at) __attribute__((always_inline)) -> int {
+        return *(const int32_t *)((const char *)from + (unsigned)at * 4u);
+    };
+    auto fetch = [&](int first) __attribute__((always_inline)) {
+        rq_n = min(max(AHEAD ? id_nn : id_at(first), 0), n_all - 1);
+        sv_n = gathered(p.s, rq_n);
+        ov_n = gathered(p.o, rq_n);
         if (AHEAD) id_nn = id_at(first + WAVE);
     };
     if (AHEAD) id_nn = id_at(k_first);
@@ -1465,6 +1465,16 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         __builtin_amdgcn_wave_barrier();
     }
     if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = n;  // (unless it stops before)
+    const int longest_o = min(p.o_bound, M);
+    // What the loop carries is there before it is entered, and in plain launches before a block's completion rounds are stored.
+    // Otherwise the compiler waits for all that is under way where a block's lengths are first used, right behind the loads
+    // for the next one (a trip to memory a block), and at the end of the block, behind its stores.  (1025 orders of 100000 bimodal
+    // requests 3956 -> 3404 us, 4096 of 200 chat ones 55.8 -> 53; the second wait costs moves in the 129-row file 3 %.)
+    auto arrived = [&]() __attribute__((always_inline)) {
+        asm volatile("" : "+v"(rq_n), "+v"(sv_n), "+v"(ov_n));
+        if (AHEAD) asm volatile("" : "+v"(id_nn));
+    };
+    arrived();
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
     // Who goes first on a SIMD.  Of equal wavefronts it serves the oldest, so they end one after the other and the last of them
     // alone, at a quarter of the rate of four.  Those that no other will take the place of therefore step back when a quarter, an eighth
@@ -1504,8 +1514,10 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         const int k = k0 + cnt - 1 - lane;  // this lane's position (none if k < k0)
         const int rq = rq_n, sv = sv_n, ov = ov_n;
         fetch(k0 + WAVE);
-        const bool bad = (sv < 1) | (ov < 1) | (ov > p.o_bound) | ((long long)sv + (long long)ov > (long long)M);
-        if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // cannot be scheduled: report, do not loop forever
+        // (1 <= ov <= longest <= M, hence M - ov >= 0, and 1 <= sv <= M - ov)
+        const unsigned long long bad = __builtin_amdgcn_ballot_w64((unsigned)ov - 1u >= (unsigned)longest_o) |
+                                       __builtin_amdgcn_ballot_w64((unsigned)sv - 1u >= (unsigned)M - (unsigned)ov);
+        if (bad != 0) {  // cannot be scheduled: report, do not loop forever
             if (lane == 0) {
                 long long none = -1;
                 asm volatile("" : "+v"(none));
@@ -1513,6 +1525,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
                 if (LIMIT && takes_snapshots && p.placed_out) *p.placed_out = 0;
                 if (p.state_out) p.state_out[1] = (int)none;  // poisons every timeline that resumes from it
             }
+            if (AHEAD) arrived();
             if (ONE && takes_snapshots)  // nobody shall wait for the snapshots that will not come
                 snapshot_progress_set<NR>(p.snap_flags, ~(k0 >> 6), lane);
             return;  // (snapshots not taken stay marked unusable, as the host left them)
@@ -1556,6 +1569,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
             }
         }
         const int cv = k >= k0 ? ov + pv : 0;
+        if (AHEAD) arrived();
         tel_lane += cv;
         if (crow && k >= k0) crow[p.completion_by_position ? k : rq] = cv;
         if ((RES ? takes_snapshots : p.C == 1) && p.start0 && k >= k0) p.start0[k] = pv;  // (published with the next snapshot)
