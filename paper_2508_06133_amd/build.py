@@ -1,4 +1,4 @@
-"""Compile libkvsched.so (hand-written HIP, gfx950 only) next to this file.
+"""Compile libkvsched.so (hand-written HIP, gfx950 only) and the Python module over it next to this file.
 
 hipcc cross-compiles without a GPU, so this runs anywhere the ROCm toolchain is installed.
 
@@ -10,16 +10,19 @@ the block anywhere but in the hand-written row code, or if it did not see every 
 """
 from __future__ import annotations
 
+import importlib.util
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvsched.so")
+HOST = os.path.join(HERE, "kvsched_host.so")  # csrc/host.cpp, a Python module over the library and torch
 SOURCES = ["api.hip", "simulate.hip", "timeline_reg.hip", "sortedf.hip", "localswap.hip", "exactdp.hip", "horizon.hip", "permute.hip", "prefix.hip", "shortrows.hip", "online.hip", "predicted.hip"]
 DEVICE_FLAGS = [
     "--offload-arch=gfx950",
@@ -43,7 +46,7 @@ def lib_path() -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(HOST):
         return True
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "kvsched.h")]
@@ -140,6 +143,17 @@ def check_reserved_vgprs(hipcc: str, verbose: bool = False) -> None:
             print(f"reserved VGPR block untouched in all {bodies} {kernel} bodies", flush=True)
 
 
+def build_host(run) -> None:
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    tmp = HOST + f".tmp{os.getpid()}"
+    run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "host.cpp"), "-o", tmp,
+         "-isystem", os.path.join(torch, "include"), "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+         "-I", sysconfig.get_paths()["include"],
+         "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10",
+         "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, HOST)
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + f".tmp{os.getpid()}"
@@ -160,6 +174,7 @@ def build(verbose: bool = False) -> str:
         os.remove(tmp)
         raise
     os.replace(tmp, LIB)
+    build_host(run)
     return LIB
 
 

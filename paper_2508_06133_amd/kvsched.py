@@ -1,4 +1,4 @@
-"""ctypes binding over libkvsched.so -- argument marshalling only.
+"""Binding over libkvsched.so -- argument marshalling only: ctypes, and a native module for the calls of a planning step.
 
 Same names as the C ABI (see include/kvsched.h).  Inputs and outputs are torch tensors on
 the context's GPU; torch is used for device memory and the current stream, nothing else.
@@ -75,6 +75,8 @@ def _load() -> ctypes.CDLL:
 
 _lib = _load()
 
+from . import kvsched_host as _host  # noqa: E402  (it is linked to the library; no fallback if it is missing)
+
 
 def strerror(code: int) -> str:
     return _lib.kvsched_strerror(int(code)).decode()
@@ -108,11 +110,13 @@ class Context:
         rc = _lib.kvsched_create(ctypes.byref(self._h), self.device)
         if rc != OK:
             raise KvschedError(rc, "kvsched_create")
+        self._address = self._h.value
 
     def close(self):
         if getattr(self, "_h", None) and self._h.value and _lib is not None:
             _lib.kvsched_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._address = 0
 
     def __del__(self):  # at interpreter exit the module globals may already be gone
         try:
@@ -145,6 +149,12 @@ class Context:
 
     def argmin(self, tel, result_out=None):
         """tel [C] int64 -> result [2] int64 = {index of the least valid entry, its value}."""
+        if result_out is None:
+            done = _host.argmin(self._address, tel, _stream())
+            if done is not None:
+                if done[0] != OK:
+                    raise KvschedError(done[0], "kvsched_argmin")
+                return done[1]
         res = torch.empty(2, dtype=torch.int64, device=tel.device) if result_out is None else result_out
         rc = _lib.kvsched_argmin(self._h, _dev(tel, torch.int64, "tel"), tel.shape[0], _dev(res, torch.int64, "result"),
                                  _stream())
@@ -162,6 +172,12 @@ class Context:
     def simulate(self, orders, s, o, M, completions: bool = True, common_prefix: int = 0, tel_out=None,
                  completion_out=None):
         """orders [C, n] -> (tel [C] int64, completion [C, n] int32 by request id or None)."""
+        if tel_out is None and completion_out is None:
+            done = _host.simulate(self._address, orders, s, o, int(M), completions, int(common_prefix), _stream())
+            if done is not None:
+                if done[0] != OK:
+                    raise KvschedError(done[0], "kvsched_simulate")
+                return done[1:]
         C, n = orders.shape
         dev = orders.device
         tel = torch.empty(C, dtype=torch.int64, device=dev) if tel_out is None else tel_out
@@ -227,6 +243,11 @@ class Context:
         dev = s.device
         self._pad_outputs(out is None)
         if out is None:
+            done = _host.sortedF(self._address, s, o, int(M), int(tie_rule), int(feas_mode), _stream())
+            if done is not None:
+                if done[0] != OK:
+                    raise KvschedError(done[0], "kvsched_sortedF")
+                return done[1:]
             order = torch.empty(n, dtype=torch.int32, device=dev)
             ends = torch.empty(n, dtype=torch.int32, device=dev)
             F = torch.empty(n, dtype=torch.float64, device=dev)
