@@ -4,7 +4,7 @@
 // Bound by the host: for a short backlog the calls' kernels take less time than their arguments.  Of the 9.8 / 8.4 / 5.6 us the three
 // took before the Python code returned, 3.3 are the launch; the rest was one tensor after the other made through Python (1.25 us
 // each), checked there (0.25) and passed through ctypes (1.2): 6.6 / 5.0 / 4.1 us now, and an order of 61 requests with its timeline 24.6 ->
-// 18.5 us.  Whatever is not the plain case (another type, a view, a subclass of Tensor, output tensors of the caller's) gets None here
+// 18.5 us.  Whatever is not the plain case (another type, not contiguous, a subclass of Tensor, output tensors of the caller's) gets None here
 // and takes the Python path, which also says what is wrong with an argument.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>

@@ -184,8 +184,7 @@ int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st);
 constexpr int32_t KVS_REG_MAX_O = 14336;  // 224 rows of 64 rounds, and one more row for the window's offset
 int kvs_launch_simulate_reg(const SimParams &p, hipStream_t st);
 
-// shortrows.hip: orders of up to 32 requests, a lane each, from these numbers of orders on
-constexpr int32_t KVS_SHORT_ROWS_8 = 1, KVS_SHORT_ROWS_16 = 8192, KVS_SHORT_ROWS_32 = 32768;
+// shortrows.hip: orders of up to 32 requests, a lane each
 bool kvs_short_rows(int32_t rows, int32_t n);
 int kvs_launch_short_rows(const SimParams &p, int32_t o_limit, hipStream_t st);
 int32_t kvs_reg_state_words(int32_t o_bound);  // words of one snapshot for this decode bound

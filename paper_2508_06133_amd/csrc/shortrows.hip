@@ -2,28 +2,33 @@
 //
 // A wavefront per order (timeline_reg.hip) is made for profiles of many rounds; an order of eight requests costs it
 // its start, two dependent rounds of loads and a turn for each request, all of which 64 lanes share here.  A lane keeps
-// the requests it has placed as pairs (completion round c_i, s_i - start) in registers, latest completion first.  The memory
-// reserved for round c_i is then the sum of the first i + 1 second parts plus (i + 1) c_i, a running sum with
-// factors known at compile time.  Memory rises from one completion to the next, so a request (s, o) may start in round t
-// iff the completion rounds among t + 1 .. t + o, and round t + o, have room for it.  Round tau rules out every start
-// before min(tau, memory(tau) + s + tau - M): the start moves to the largest of these until none is behind it.  If round t + o
-// has no room, no start has whose last round comes before the next completion or with it, as memory only rises until then.
-// (Without that a request of one round, which looks at the round ahead only, went through every round it waited: 8192 orders
-// of 16 requests of 1 or 4096 tokens and rounds, M = 8192, 17 ms instead of 25 us.)  Every turn that moves the
-// start settles a completion round for good, so there is at most one more turn than there are completions.
+// the completion rounds c_i of the requests it has placed in registers, latest first, and with each the memory reserved for that
+// round and the round once more, b_i: as request k holds s_k - start_k + tau in round tau, b_i is the sum of the first i + 1 of s_k -
+// start_k, plus (i + 2) c_i.  Memory rises from one completion to the next, so a request (s, o) may start in round t
+// iff the completion rounds among t + 1 .. t + o, and round t + o, have room for it.
+//
+// One pass over the completions, from the earliest on, finds the start.  Where c_i lies within t + 1 .. t + o it rules out every start
+// before min(c_i, b_i + s - M).  Where it is the first behind that, the last round t + o has to have room beside the first i + 1
+// requests; if it has not, no start has whose last round comes before c_i or with it, as memory only rises until then, and the
+// start moves to c_i + 1 - o, where c_i is within its rounds and rules out what it does (no less than round t + o did).  Later
+// completions find more room in that round, as fewer requests are left, so none of them moves a start that fits; and a start that an
+// earlier one has been passed for does not come back to it.  With x = c_i - o one comparison serves all cases: the room that round t + o
+// has beside the first i + 1 requests, also where c_i comes before it (it only seems less then, and max(x + 1, min(c_i, b_i + s - M)) is
+// beyond t only if that completion is in the way).
 //
 // The ids are read as whole rows and the completion rounds written by request id through LDS; that an order is a
 // permutation comes out on the way.  So there is no second pass over the rows.
 //
-// Bound by the chain of its vector instructions, ten for each place of the arrays in each look at a start round: a call of
-// 65536 orders of 4 or 8 chat requests takes 11 us where the timeline kernel takes 36 and 44, of 16 requests 20 (55), of 24 40 (79),
-// of 32 58 (103).  The chain grows with the square of the requests and does not shrink with the orders, so longer orders
-// need more of them: 8192 orders of 9 requests 12.1 us (12.4), of 12 14.6 (12.4), of 16 17.8 (13.0), 16384 of 16 18.1 (18.5), of
-// 24 37 (26), 32768 of 17 / 24 / 32 27 / 39 / 55 (36 / 44 / 57).  Where many short requests wait for long ones the timeline kernel
-// looks at many more rounds: 16 requests of 1 or 4096 tokens and rounds, 8192 orders at M = 8192 25 us (4400), 16384 at M = 16384
-// 24 (73).  So orders of 9 to 16 requests take this way from 8192 on, where the chat ones alone would have it at 16384.
+// Bound by the chain of its vector instructions: ten for each completion, three of them behind the one before, and seven to keep
+// them in order.  With a look at all completions after each move of the start, and one more (as many as there are completions, if the
+// memory is tight), 8 and 16 requests a row and 65536 rows were 7.7 and 17.0 us a call, 7.0 and 14.5 now, 24 and 32 34.6 and 59.0, now 28.0
+// and 41.2; 16384 rows of 16 that wait more 26.5, now 13.1; every order of 8 in a budget of 3 requests 7.8, now 6.4 (the launch alone takes 6).
+// The time hardly depends on the lengths.  Where many short requests wait for long ones the timeline kernel
+// looks at many more rounds: 16 requests of 1 or 4096 tokens and rounds, 8192 orders 13 us (2116).
 #include "kvsched_internal.h"
 #include "device_util.h"
+
+#include <climits>
 
 namespace {
 
@@ -55,54 +60,55 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
     __syncthreads();
     if (o_max > o_limit) return;  // (the rows are placed by a later launch)
 
-    int c[N], a[N];
+    int c[N];       // completion rounds placed so far, latest first
+    unsigned b[N];  // the memory reserved for round c[i], and c[i] once more
 #pragma unroll
-    for (int i = 0; i < N; ++i) c[i] = -1, a[i] = 0;  // none placed
+    for (int i = 0; i < N; ++i) c[i] = -1, b[i] = 0;  // none placed
     int t = 0, tel = 0, met = 0;
     bool permutation = true, valid = true;
     const int *ids = row + lane * PITCH;  // (lanes without an order place what is there, of no account)
+    const int longest = min(p.o_bound, M);
+    int raw = ids[0], id = min(max(raw, 0), n - 1), s_next = len_s[id], o_next = len_o[id];
     for (int k = 0; k < n; ++k) {
-        const int raw = lane < mine ? ids[k] : 0;
-        const int id = min(max(raw, 0), n - 1);
         permutation &= raw == id && ((met >> id) & 1) == 0;
         met |= 1 << id;
-        int s = len_s[id], o = len_o[id];
-        if (s < 1 || o < 1 || o > p.o_bound || (long long)s + o > (long long)M) {  // cannot be scheduled
-            valid = false;
-            s = o = 0;  // ends where it starts and holds nothing: the look below moves no start for it
-        }
-        for (;;) {
-            const int end = t + o;
-            int start = t, sum = s - M, at_end = sum, behind = 1;
+        const int here = id;
+        // (1 <= o <= longest <= M, hence M - o >= 0, and 1 <= s <= M - o)
+        const bool good = (unsigned)o_next - 1u < (unsigned)longest && (unsigned)s_next - 1u < (unsigned)M - (unsigned)o_next;
+        valid &= good;  // a request that cannot be scheduled ends where it starts and holds nothing: no completion moves it
+        const int s = good ? s_next : 0, o = good ? o_next : 0;
+        raw = ids[min(k + 1, n - 1)];  // (the next one's lengths are on their way meanwhile)
+        id = min(max(raw, 0), n - 1);
+        s_next = len_s[id];
+        o_next = len_o[id];
+        const unsigned over = (unsigned)(s - M);
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                sum += a[i];
-                const bool holds = c[i] >= end;
-                at_end = holds ? sum : at_end;
-                behind = holds ? i + 2 : behind;
-                const int bound = min(c[i], sum + (int)__umul24((unsigned)c[i], i + 2));
-                start = (unsigned)(c[i] - t - 1) < (unsigned)o ? max(start, bound) : start;
-            }
-            const int free_end = at_end + (int)__umul24((unsigned)end, (unsigned)behind);
-            if (__builtin_amdgcn_ballot_w64(free_end > t && o > 0) != 0) {
-                int next = 0;  // the first completion round at or behind `end` (there is one)
+        for (int f = N - 4; f >= 0; f -= 4) {
+            if (k <= f) continue;  // (uniform: four places that are empty yet)
 #pragma unroll
-                for (int i = 0; i < N; ++i) next = c[i] >= end ? c[i] : next;
-                if (free_end > t && o > 0) start = max(start, max(min(end, free_end), next - o + 1));
+            for (int i = f + 3; i >= f; --i) {
+                const int bound = (int)(b[i] + over), x = c[i] - o;
+                const int least = max(x + 1, min(c[i], bound));
+                const int at_x = bound - __mul24(x, i + 2);
+                t = at_x + __mul24(t, i + 2) > t ? max(t, least) : t;
             }
-            const bool moved = start > t;
-            t = start;
-            if (__builtin_amdgcn_ballot_w64(moved) == 0) break;
         }
-        const int c_new = t + o, a_new = s - t;
+        const int c_new = t + o;
+        const unsigned a_new = (unsigned)(s - t);
         tel += c_new;
-        done[lane * PITCH + id] = c_new;
+        done[lane * PITCH + here] = c_new;
 #pragma unroll
-        for (int i = N - 1; i >= 0; --i) {  // to its place among the completions
-            const bool keep = c[i] >= c_new, here = i == 0 || c[i > 0 ? i - 1 : 0] >= c_new;
-            const int from_c = here ? c_new : c[i > 0 ? i - 1 : 0], from_a = here ? a_new : a[i > 0 ? i - 1 : 0];
-            c[i] = keep ? c[i] : from_c;
-            a[i] = keep ? a[i] : from_a;
+        for (int f = N - 4; f >= 0; f -= 4) {  // to its place among the completions
+            if (k < f) continue;
+#pragma unroll
+            for (int i = f + 3; i >= f; --i) {
+                const bool keep = c[i] >= c_new;
+                const int c_left = i > 0 ? c[i > 0 ? i - 1 : 0] : INT_MAX;
+                const unsigned b_in = i > 0 ? b[i > 0 ? i - 1 : 0] + (unsigned)c_left + a_new + (unsigned)__mul24(min(c_new - c_left, 0), i + 2)
+                                            : a_new + 2u * (unsigned)c_new;
+                c[i] = keep ? c[i] : min(c_left, c_new);
+                b[i] = keep ? b[i] : b_in;
+            }
         }
     }
     if (lane < mine) {
@@ -120,10 +126,12 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
 
 }  // namespace
 
-// Are `rows` orders of n requests placed a lane each?  (The lines are measured at the top of the file.)
+// Are `rows` orders of n requests placed a lane each?  The chain grows with the square of the requests and does not shrink with the
+// orders: 9 chat requests 7.2 us (timeline kernel: 4096 orders 6.8, 8192 8.8), 12 9.3 (8.2, 11.4), 16 13 (10.7, 15.3), 24 24 (8192 18.5,
+// 16384 31.1), 32 36 (21.7, 36.4).
 bool kvs_short_rows(int32_t rows, int32_t n)
 {
-    return n <= 8 ? rows >= KVS_SHORT_ROWS_8 : n <= 16 ? rows >= KVS_SHORT_ROWS_16 : n <= 32 && rows >= KVS_SHORT_ROWS_32;
+    return n <= 32 && (n <= 8 || rows >= 512 * n);
 }
 
 // p.tel_out and p.completion_out (by request id) of every row, checked; nothing is written if words[KVS_W_OMAX] > o_limit.
