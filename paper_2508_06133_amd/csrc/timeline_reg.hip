@@ -178,17 +178,21 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // H is known at the beginning (M) and from saved states; while requests start at round 0 it only falls by their sizes.
 // Later it is the distance of the file's maximum to M, which costs one and a half instructions per row: worth it when
 // many requests follow in one round.  The files of 65 rows and more (long decodes, rows dear to look at) find that out by
-// themselves: place_block returns after kRunMoved + 1 requests in a row that did not move the round.
+// themselves: place_block returns after `patience` + 1 requests in a row that did not move the round, 2 where the last measurement
+// was worth it, up to 16 after some that were not.  (With 5 in the 65-row file and 17 in the others, always: 1025 orders of 100000 bimodal
+// requests, decodes of 1 or 4096, 3180 -> 2809 us, 3000 of 30000 2014 -> 1710, 1000 of 20000 of twelve thousand rounds 3929 -> 2065;
+// chat requests of twice the length, 4096 orders of 2000 425 -> 394, 64 of 6000 616 -> 542.  Always 2: 661 for the latter.  Without an
+// upper end: the bimodal ones 14600, as they are then placed 64 at a time one by one.)
+//
 //
 // What it gives: of bimodal orders (decodes 1 or 4096) 97 % of the requests start that way, 56 at a time, and their ramps are added 340 at a
-// time: 1025 orders of 100000 27.2 -> 4.5 ms (3.4 now), of which the timelines 26.3 -> 3.6 (3.0): one wavefront per SIMD, bound by the chain
+// time: 1025 orders of 100000 27.2 -> 4.5 ms (3.0 now), of which the timelines 26.3 -> 3.6 (2.6): one wavefront per SIMD, bound by the chain
 // of the blocks (prefix sum, list: 1200 cycles per 64 requests) and of the 250 moves.  4096 chat orders of 200, half of
 // them in the first burst: 82.5 -> 80 us.  Below kGroupMin requests the pass over the rows (75 instructions per chunk with
 // entries) costs more than they do one by one.
+constexpr int kMostPatience = 15;
 constexpr int kChunkRows = 4;
 constexpr int kChunk = WAVE * kChunkRows;
-template <int NR>
-constexpr int kRunMoved = NR > 65 ? 16 : 4;  // (more rows to look at)
 template <int NR>
 constexpr int kListCap = NR >= 65 ? 512 : 256;
 // Which launches do so.  Not the 9-row file: its rows are few, and its launches of many short timelines lose 3 % to LDS and
@@ -197,7 +201,10 @@ constexpr int kListCap = NR >= 65 ? 512 : 256;
 // the 65-row file they do, for the sake of bimodal lengths.
 template <int NR, bool RES>
 constexpr bool kGroup = RES ? NR == 65 : NR >= 33;
-constexpr int kGroupMin = 16;  // below this the requests are placed one by one
+// Fewer requests are placed one by one.  (With 16 in all files 8000 orders of 3000 bimodal requests 2979 us, with 4 2139, with 2 2143; the
+// rows of the smaller files are cheaper to look at than a list to empty.)
+template <int NR>
+constexpr int kGroupMin = NR >= 65 ? 4 : 16;
 
 // ---------------------------------------------------------------------------------------------
 // Placing up to 64 consecutive requests of the order: ONE assembly statement.
@@ -307,9 +314,9 @@ constexpr int kGroupMin = 16;  // below this the requests are placed one by one
 // (The .org stops the build if the slot does not hold what was put into it.)
 #define KVS_SLOT_PAD(bytes) "  .fill (" #bytes "-(.-7b))/4, 4, 0xbf800000\n  .org 7b+" #bytes "\n"
 
-// (RUNS: return early behind look + 1, later kRunMoved + 1, requests that did not move the round; cnt: those left)
+// (RUNS: return early behind look + 1, later anew + 1, requests that did not move the round; cnt: those left)
 template <int NR, bool RUNS>
-__device__ __forceinline__ void place_block(int &cnt, int look, int vns, int vo, int lane, int vmin, int M, int &cv, int &t, int &b64,
+__device__ __forceinline__ void place_block(int &cnt, int look, int anew, int vns, int vo, int lane, int vmin, int M, int &cv, int &t, int &b64,
                                             int &hi)
 {
     int acc, y, z, tl, vw;
@@ -680,7 +687,7 @@ __device__ __forceinline__ void place_block(int &cnt, int look, int vns, int vo,
         "v_add_u32 %[y], %[acc], %[lane]\n"                                                             \
         ".if %c[runs]\n"                    /* the count of requests that have not moved begins anew */  \
         "  s_and_b32 %[ta], m0, 63\n"                                                                   \
-        "  s_min_u32 %[tb], %[ta], %c[anew]\n"                                                          \
+        "  s_min_u32 %[tb], %[ta], %[anew]\n"                                                          \
         "  s_lshl_b32 %[tb], %[tb], 6\n"                                                                \
         "  s_add_u32 m0, %[ta], %[tb]\n"                                                                \
         ".endif\n"                                                                                      \
@@ -762,7 +769,7 @@ __device__ __forceinline__ void place_block(int &cnt, int look, int vns, int vo,
           [rs] "=&s"(rs), [ta] "=&s"(ta), [tb] "=&s"(tb), [tc] "=&s"(tc), [ql] "=&s"(ql), \
           [qh] "=&s"(qh), [cl] "=&s"(cl), [ch] "=&s"(ch), [ul] "=&s"(ul), [uh] "=&s"(uh), [rl] "=&s"(rl), \
           [rh] "=&s"(rh), [mk] "=&s"(mk), [t] "+s"(t), [b64] "+s"(b64), [hi] "+s"(hi)                  \
-        : [look] "s"(look), [anew] "n"(kRunMoved<NR>), [runs] "n"(RUNS ? 1 : 0), [vns] "v"(vns), [vo] "v"(vo), [lane] "v"(lane), [vmin] "v"(vmin),             \
+        : [look] "s"(look), [anew] "s"(anew), [runs] "n"(RUNS ? 1 : 0), [vns] "v"(vns), [vo] "v"(vo), [lane] "v"(lane), [vmin] "v"(vmin),             \
           [M] "s"(M), [nr] "n"(NR)                                                                      \
         : "scc", "vcc", SCLOB, CLOB)
     KVS_FOR_NR(KVS_STMT);
@@ -1385,7 +1392,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
     int b64 = 0;             // round of lane 0 of register 0: 64 * floor((t + 1) / 64)
     int hi = 0;              // 64 x the number of rows that may hold committed memory
     // no round behind t holds more than M - H (-1: not known, or of no use)
-    int H = GROUP && n - k_first >= kGroupMin ? M : -1;
+    int H = GROUP && n - k_first >= kGroupMin<NR> ? M : -1;
     int t = 0;               // start round of the previous request in the order
     long long tel_lane = 0;  // completion rounds summed per lane; added up over the lanes at the end
     if (state_in) {
@@ -1475,6 +1482,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         if (AHEAD) asm volatile("" : "+v"(id_nn));
     };
     arrived();
+    int patience = 1;  // (RUNS)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
     // Who goes first on a SIMD.  Of equal wavefronts it serves the oldest, so they end one after the other and the last of them
     // alone, at a quarter of the rate of four.  Those that no other will take the place of therefore step back when a quarter, an eighth
@@ -1532,7 +1540,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         }
         // the up to 64 requests of this block, one after the other (place_block returns the lanes' start
         // rounds); cv: completion round of this lane's position
-        int rem = cnt, look = kRunMoved<NR>;
+        int rem = cnt, look = patience;
         int pv = t;
         for (;;) {
             // (the one place where the list is emptied: this code is long, and the branches around it reach only so far)
@@ -1545,14 +1553,16 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
                 int size = sv;
                 asm volatile("" : "+v"(size));
                 const int g = group_size(rem, size + ov, lane, unit_shift, H);
-                if (g >= kGroupMin || (g > 0 && grouped > 0)) {
+                if (g >= kGroupMin<NR> || (g > 0 && grouped > 0)) {
+                    patience = 1;
                     if (grouped == 0) group_clear<NR>(group, lane);
                     group_append<NR>(group, grouped, rem, g, sv, ov + (t - b64), lane);
                     if (lane < rem) pv = t;
                     rem -= g;
                     if (rem == 0 && !state_follows) break;
                 } else {
-                    look = WAVE - 1;  // (not again for requests that are looked at one by one anyway)
+                    look = WAVE - 1;  // (not again before the round moves)
+                    patience = min(2 * patience + 1, kMostPatience);
                 }
                 if (rem > 0) H = -1;
                 continue;
@@ -1562,10 +1572,10 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
             int free_of_s = sv;
             asm volatile("" : "+v"(free_of_s));  // (not to be kept in a register besides sv)
             free_of_s = M - free_of_s;
-            place_block<NR, RUNS>(rem, look, free_of_s, ov, lane, vmin, M, pv, t, b64, hi);
+            place_block<NR, RUNS>(rem, look, patience, free_of_s, ov, lane, vmin, M, pv, t, b64, hi);
             if (RUNS && rem > 0) {  // a run of requests in one round
                 H = M - prof_max<NR>(t - b64, hi, lane);
-                look = kRunMoved<NR>;
+                look = patience;
             }
         }
         const int cv = k >= k0 ? ov + pv : 0;
