@@ -180,9 +180,10 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // many requests follow in one round.  The files of 65 rows and more (long decodes, rows dear to look at) find that out by
 // themselves: place_block returns after `patience` + 1 requests in a row that did not move the round, 2 where the last measurement
 // was worth it, up to 16 after some that were not.  (With 5 in the 65-row file and 17 in the others, always: 1025 orders of 100000 bimodal
-// requests, decodes of 1 or 4096, 3180 -> 2809 us, 3000 of 30000 2014 -> 1710, 1000 of 20000 of twelve thousand rounds 3929 -> 2065;
-// chat requests of twice the length, 4096 orders of 2000 425 -> 394, 64 of 6000 616 -> 542.  Always 2: 661 for the latter.  Without an
-// upper end: the bimodal ones 14600, as they are then placed 64 at a time one by one.)
+// requests, decodes of 1 or 4096, 3180 -> 2830 us, 3000 of 30000 2014 -> 1730, 1000 of 20000 of twelve thousand rounds 4079 -> 2234;
+// chat requests of twice the length, 4096 orders of 2000 425 -> 394, 64 of 6000 616 -> 548.  Always 2: 661 for the latter.  Without an
+// upper end: the bimodal ones 14600, as they are then placed 64 at a time one by one.)  The files of 129 rows and more, where a measurement
+// costs most, begin with 16 and go below only where it was for the sake of long ones.
 //
 //
 // What it gives: of bimodal orders (decodes 1 or 4096) 97 % of the requests start that way, 56 at a time, and their ramps are added 340 at a
@@ -201,10 +202,15 @@ constexpr int kListCap = NR >= 65 ? 512 : 256;
 // the 65-row file they do, for the sake of bimodal lengths.
 template <int NR, bool RES>
 constexpr bool kGroup = RES ? NR == 65 : NR >= 33;
-// Fewer requests are placed one by one.  (With 16 in all files 8000 orders of 3000 bimodal requests 2979 us, with 4 2139, with 2 2143; the
-// rows of the smaller files are cheaper to look at than a list to empty.)
+// Fewer requests are placed one by one, but for the long ones in the files of 65 rows and more: so many of so many rounds cost more
+// than a list to empty.  (8000 orders of 3000 bimodal requests 3229 us without them, 2119 with, 2000 of 2000 of twice the length 1120 and
+// 657.  4 of any length at a time, in the file of 129 rows: 545 moves in an order of 111 mixed requests of four times the length 54.1 us,
+// 49.8 without, 50.3 so.)
+constexpr int kGroupMin = 16;
 template <int NR>
-constexpr int kGroupMin = NR >= 65 ? 4 : 16;
+constexpr int kLongRounds = NR > 65 ? 4095 : 2048;
+template <int NR>
+constexpr int kLongMin = NR > 65 ? 2 : 3;
 
 // ---------------------------------------------------------------------------------------------
 // Placing up to 64 consecutive requests of the order: ONE assembly statement.
@@ -1392,7 +1398,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
     int b64 = 0;             // round of lane 0 of register 0: 64 * floor((t + 1) / 64)
     int hi = 0;              // 64 x the number of rows that may hold committed memory
     // no round behind t holds more than M - H (-1: not known, or of no use)
-    int H = GROUP && n - k_first >= kGroupMin<NR> ? M : -1;
+    int H = GROUP && n - k_first >= kGroupMin ? M : -1;
     int t = 0;               // start round of the previous request in the order
     long long tel_lane = 0;  // completion rounds summed per lane; added up over the lanes at the end
     if (state_in) {
@@ -1482,7 +1488,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         if (AHEAD) asm volatile("" : "+v"(id_nn));
     };
     arrived();
-    int patience = 1;  // (RUNS)
+    int patience = NR > 65 ? kMostPatience : 1;  // (RUNS)
     int n_stop = n;  // (the loop has one way out: the kernel's assembly operands stay scalar that way)
     // Who goes first on a SIMD.  Of equal wavefronts it serves the oldest, so they end one after the other and the last of them
     // alone, at a quarter of the rate of four.  Those that no other will take the place of therefore step back when a quarter, an eighth
@@ -1521,7 +1527,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         const bool state_follows = takes_snapshots || (p.state_out && k0 + WAVE >= n);
         const int k = k0 + cnt - 1 - lane;  // this lane's position (none if k < k0)
         const int rq = rq_n, sv = sv_n, ov = ov_n;
-        fetch(k0 + WAVE);
+        fetch(k0 + WAVE);  // (past the end too: a branch here brings the waits back, 2830 -> 3020 us)
         // (1 <= ov <= longest <= M, hence M - ov >= 0, and 1 <= sv <= M - ov)
         const unsigned long long bad = __builtin_amdgcn_ballot_w64((unsigned)ov - 1u >= (unsigned)longest_o) |
                                        __builtin_amdgcn_ballot_w64((unsigned)sv - 1u >= (unsigned)M - (unsigned)ov);
@@ -1553,8 +1559,14 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
                 int size = sv;
                 asm volatile("" : "+v"(size));
                 const int g = group_size(rem, size + ov, lane, unit_shift, H);
-                if (g >= kGroupMin<NR> || (g > 0 && grouped > 0)) {
-                    patience = 1;
+                bool worth = g >= kGroupMin || (g > 0 && grouped > 0);
+                if (RUNS && g > 0 && !worth) {
+                    const unsigned long long those = (~0ull >> (WAVE - rem)) & (~0ull << (rem - g));
+                    worth = __popcll(__builtin_amdgcn_ballot_w64(ov > kLongRounds<NR>) & those) >= kLongMin<NR>;
+                    if (NR > 65 && worth) patience = 1;
+                }
+                if (worth) {
+                    if (NR == 65) patience = 1;
                     if (grouped == 0) group_clear<NR>(group, lane);
                     group_append<NR>(group, grouped, rem, g, sv, ov + (t - b64), lane);
                     if (lane < rem) pv = t;
@@ -1562,7 +1574,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
                     if (rem == 0 && !state_follows) break;
                 } else {
                     look = WAVE - 1;  // (not again before the round moves)
-                    patience = min(2 * patience + 1, kMostPatience);
+                    patience = min(NR > 65 ? 4 * patience + 3 : 2 * patience + 1, kMostPatience);
                 }
                 if (rem > 0) H = -1;
                 continue;
