@@ -75,7 +75,8 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
         const int here = id;
         // (1 <= o <= longest <= M, hence M - o >= 0, and 1 <= s <= M - o)
         const bool good = (unsigned)o_next - 1u < (unsigned)longest && (unsigned)s_next - 1u < (unsigned)M - (unsigned)o_next;
-        valid &= good;  // a request that cannot be scheduled ends where it starts and holds nothing: no completion moves it
+        valid &= good;  // a request that cannot be scheduled ends in the round it is reached in and holds nothing
+        const int reached = t;
         const int s = good ? s_next : 0, o = good ? o_next : 0;
         raw = ids[min(k + 1, n - 1)];  // (the next one's lengths are on their way meanwhile)
         id = min(max(raw, 0), n - 1);
@@ -93,6 +94,7 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
                 t = at_x + __mul24(t, i + 2) > t ? max(t, least) : t;
             }
         }
+        t = good ? t : reached;  // (the test takes a completion in round t itself as in the way of a request of no rounds)
         const int c_new = t + o;
         const unsigned a_new = (unsigned)(s - t);
         tel += c_new;

@@ -86,3 +86,38 @@ def test_requests_that_do_not_occur(n, rows):
     whole = np.setdiff1d(np.arange(rows), list(left_out))[:4]
     tel_o, comp_o = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), 40, orders[whole])
     assert (tel[whole] == tel_o).all() and (comp[whole] == comp_o).all()
+
+
+def _placed(s, o, M, order):
+    """Completion rounds by request, round by round; a request that cannot be scheduled ends where it is reached."""
+    memory, t, done = np.zeros(1 + int(np.maximum(o, 0).sum()), dtype=np.int64), 0, np.zeros(len(order), dtype=np.int64)
+    for i in order:
+        good = s[i] >= 1 and o[i] >= 1 and s[i] + o[i] <= M
+        held = int(s[i]) + 1 + np.arange(o[i]) if good else np.zeros(0, dtype=np.int64)
+        while (memory[t + 1 : t + 1 + len(held)] + held > M).any():
+            t += 1
+        memory[t + 1 : t + 1 + len(held)] += held
+        done[i] = t + len(held)
+    return done
+
+
+@pytest.mark.parametrize("n,rows", [(3, 70), (8, 130), (16, 8192), (32, 16384)])
+def test_unschedulable_takes_no_rounds(n, rows):
+    """Budgets that a request or two fill, so that others start where one completes: those behind an unschedulable request are placed
+    as if it were not there."""
+    rng = np.random.default_rng(n)
+    orders = _orders(rng, n, rows)
+    some = np.r_[0:12, rows - 12:rows]
+    for turn in range(6):
+        s, o = rng.integers(1, 10, n), rng.integers(1, 7, n)
+        M = 14 if turn % 2 else 16
+        if n == 3:
+            s, o, M = np.array([5, 8, 1]), np.array([5, 4, 1]), 14
+            orders[0] = 0, 1, 2
+        bad = n - 1 if n == 3 else rng.integers(0, n)
+        s[bad] = M + turn
+        print(f"short rows, placed around an unschedulable one: n={n} rows={rows} M={M} turn={turn}", flush=True)
+        tel, comp, status = _run(s, o, M, orders)
+        assert status == 1 and (tel == -1).all()
+        for row in some:
+            assert (comp[row] == _placed(s, o, M, orders[row])).all(), (turn, row)
