@@ -88,6 +88,7 @@ int run_timelines(kvsched_ctx *ctx, const SimParams &p, int32_t H, hipStream_t s
     int rc = short_rows ? kvs_launch_short_rows(p, o_limit, st)
              : p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st) : kvs_launch_simulate(p, H, st);
     if (rc != KVSCHED_OK) return rc;
+    if (p.scan_here) ctx->status_turn = p.status_word - KVS_W_STATUS_TURN;  // (only now: a launch that failed has cleared nothing)
     if (ctx->timing) {
         if (hipEventRecord(ctx->ev1, st) != hipSuccess) return KVSCHED_EHIP;
         ctx->timed = 1;
@@ -511,8 +512,8 @@ static bool scans_here(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_b
            !resume_pays(ctx, C, n, o_bound) && !capturing(st);
 }
 
-// The status word of the next such call, which clears the other one for the call after it.
-static int32_t next_status_word(kvsched_ctx *ctx) { return KVS_W_STATUS_TURN + (ctx->status_turn ^= 1); }
+// The status word of the next such call, whose launch clears the other one for the call after it.
+static int32_t next_status_word(const kvsched_ctx *ctx) { return KVS_W_STATUS_TURN + (ctx->status_turn ^ 1); }
 
 // kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
 // longer one (only where rows are not resumed and no prefix is placed ahead).  scan: no length scan is enqueued before

@@ -60,7 +60,7 @@ struct kvsched_ctx {
     int32_t o_file;        // longest decode of the register file the last kvsched_simulate needed (0: unknown, or none): what a
                            // small call starts with before its own is known
     int pad_outputs;       // Phase-1 calls write zeros behind the last batch
-    int32_t status_turn;   // which of the two words at KVS_W_STATUS_TURN the last call without a length scan used
+    int32_t status_turn;   // which of the two words at KVS_W_STATUS_TURN the last launch without a length scan ahead used
     int timing;            // record events around the timeline kernel
     int timed;             // a pair of events has been recorded
     int32_t resume_rows;   // rows of the last kvsched_simulate call if it resumed rows from snapshots, else 0

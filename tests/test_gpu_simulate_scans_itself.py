@@ -96,3 +96,35 @@ def test_wrong_guesses():
             assert (tel.cpu().numpy()[good] == tel_o).all() and (comp.cpu().numpy()[good] == comp_o).all()
     finally:
         ctx.close()
+
+
+def test_status_behind_a_launch_that_fails():
+    """A grid of 2^32 lanes is more than a launch takes.  Whatever the call gives, the next one's status is its own, not that of the
+    call before the one that failed."""
+    import torch
+    from paper_2508_06133_amd import kvsched
+
+    n, C = 33, 1 << 26  # (the buffers are there in full: a launch that is taken after all stays within them)
+    rng = np.random.default_rng(5)
+    s, o = _dev(rng.integers(1, 50, n)), _dev(rng.integers(1, 30, n))
+    good, faulty = _dev(_rows(rng, n, 6, False)), _dev(_rows(rng, n, 6, True))
+    many = torch.zeros((C, n), dtype=torch.int32, device="cuda:0")
+    tel = torch.empty(C, dtype=torch.int64, device="cuda:0")
+    ctx = kvsched.Context(0)
+    try:
+        ctx.set_o_max(30)
+        for between in range(2):
+            ctx.simulate(faulty, s, o, 400)
+            assert ctx.device_status() == kvsched.DEV_BAD_ORDER
+            print(f"simulate without a scan: {C} rows of {n}", flush=True)
+            try:
+                ctx.simulate(many, s, o, 400, completions=False, tel_out=tel)
+                torch.cuda.synchronize()
+            except kvsched.KvschedError as e:
+                assert e.code == -3
+            ctx.simulate(good, s, o, 400)
+            assert ctx.device_status() == 0
+            if between == 0:
+                ctx.simulate(good, s, o, 400)
+    finally:
+        ctx.close()
