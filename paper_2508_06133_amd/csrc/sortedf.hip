@@ -1017,13 +1017,16 @@ __device__ __forceinline__ bool small_numbers(const SortedArgs &p, const Sums &c
 // launch before it some time for each place if they are below.  Completion times up to 2048, the chain and ahead: 5000 mixed
 // requests in 6 batches 170 and 75 us, in 73 213 and 80, in 240 175 and 91; 1000 chat requests in 3 73 and 56, 10000 143 and 130; 400
 // mixed ones in 5 64 and 41.  The other side: extents of 16 requests and fewer, 300 chat requests in 23 batches 32 and 39, 2000 in 37 47
-// and 53; and those beyond some 10000, which every wavefront reads through, 40000 chat requests in 3 batches 219 and 240.  Beyond 2048 an
+// and 53; those beyond some 10000 on average, which every wavefront reads through, 40000 chat requests in 3 batches 219 and 240; and
+// constructions of up to kNextMax requests, none of whose extents is beyond what one wavefront tests (no launch is made for them): 129
+// chat requests in 3 / 6 / 25 batches 32 / 28 / 29 and 41 / 39 / 32, 256 in 3 / 6 / 29 40 / 33 / 30 and 45 / 42 / 34.  Beyond 2048 an
 // extent costs twice and more and half as many wavefronts find them: 400 bimodal requests in 12 batches 36 and 56, 10000 in 42
 // 145 and 193, 2000 in 11 91 and 127.
 constexpr u64 kAheadMost = 10000;
 
 __device__ __forceinline__ bool extents_ahead(const SortedArgs &p, const LargeArrays &m)
 {
+    if (p.n <= kNextMax) return false;
     const int omax = p.words[KVS_W_OMAX];
     const u64 all = m.W[p.n], M = (u64)p.M, some = (u64)p.n * M;  // (some / all requests an extent, on average)
     if (omax <= kLargeBuckets / 2) return all >= M && some >= 16 * all && some <= kAheadMost * all;
@@ -1469,9 +1472,11 @@ size_t padded(int32_t n) { return ((size_t)n + 64) & ~(size_t)63; }
 // Largest construction done by one workgroup.  Its sorts and the chain grow with the requests and batches, most of the chip's launches
 // do not.  Mixed requests in 6 / 20 / 40 batches, one workgroup and the chip: 700 17 / 22 / 30 us against 26 for all; 1025 (two keys a
 // thread) 30 / 38 / 87 before the chain was one wavefront's, 27 / 27 / 29 by the chip; 2000 31 / 34 / 40 and 32 / 30 / 31; 4000 55 / 59 /
-// 63 and 43 / 38 / 37.  2000 chat requests in 3 batches, the other way: 29 and 34.  Under the profile constraint, where one
-// workgroup finds one extent after the other and the chip those of all places: 100 mixed requests in 5 / 10 / 25 batches 27 / 32 / 46 and
-// 29 / 31 / 32, 256 in 6 / 22 / 55 40 / 55 / 89 and 38 / 40 / 42, 200 chat requests in 3 / 14 33 / 43 and 38 / 30.
+// 63 and 43 / 38 / 37.  The other way, chat requests in 4 batches: 1100 28.3 and 29.2, 2000 30.3 and 32.2.  Under the profile constraint,
+// where one workgroup finds one extent after the other and the chip those of all places: 129 chat requests in 3 / 6 / 25 batches 28 / 30 /
+// 48 and 32 / 28 / 29, 200 in 3 / 4 / 14 34 / 34 / 43 and 37 / 33 / 29, 256 mixed ones in 8 / 16 / 67 41 / 49 / 100 and 37 / 37 / 40.  100
+// chat requests in 2 / 4 / 17 batches 23.5 / 25 / 38 and 27 / 24 / 24, 65 in 3 / 6 / 13 22 / 25 / 32 and 23 / 22 / 23: from some 4 batches
+// on the line could be as low as 64.
 int32_t kvs_sortedF_small_max(int32_t feas_mode) { return feas_mode == KVSCHED_FEAS_PROFILE ? kSmallProfile : kSmallSum; }
 
 size_t kvs_sortedF_scratch_bytes(int32_t n)
@@ -1550,7 +1555,7 @@ int kvs_launch_sortedF(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
     hipLaunchKernelGGL(prefix_sums_kernel, sums, dim3(1024), 0, st, p, m, sorted, ranks ? 1 : 0, n > kSumsHere ? 1 : 0);
     const dim3 waves((unsigned)((n + 3) / 4));
     // (as many workgroups as the LDS of 256 compute units holds)
-    if (profile) hipLaunchKernelGGL(profile_extents_kernel, dim3((unsigned)(n < 3 * 256 ? n : 3 * 256)), dim3(128), 0, st, p, m);
+    if (profile && n > kNextMax) hipLaunchKernelGGL(profile_extents_kernel, dim3((unsigned)(n < 3 * 256 ? n : 3 * 256)), dim3(128), 0, st, p, m);
     if (profile) hipLaunchKernelGGL((next_batch_kernel<true>), waves, dim3(256), 0, st, p, m);
     else hipLaunchKernelGGL((next_batch_kernel<false>), waves, dim3(256), 0, st, p, m);
     rc = profile ? launch_chain<true>(p, m, st) : launch_chain<false>(p, m, st);

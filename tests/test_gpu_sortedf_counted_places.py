@@ -85,3 +85,15 @@ def test_extents_found_ahead_or_by_the_chain(ctx, n, omax):
     total = int((s + o).sum())
     for M in (total, total - 1, total // 2, total // 7, 16 * total // n, 16 * total // n - 1, 10000 * total // n, 10000 * total // n + 1):
         _check(ctx, s, o, min(max(M, 400 + omax), (1 << 30) - 1), 1, n & 1)
+
+
+@pytest.mark.parametrize("n,omax", [(129, 700), (200, 2048), (255, 2049), (256, 2048), (256, 9000), (257, 2048), (257, 5000)])
+def test_no_extent_beyond_the_tests_of_one_wavefront(ctx, n, omax):
+    """Up to 256 requests under the profile constraint, and one more: all in one batch, a few batches, one request each."""
+    rng = np.random.default_rng(n + omax)
+    s, o = rng.integers(1, 400, n), rng.integers(1, omax + 1, n)
+    o[n // 2] = omax
+    total = int((s + o).sum())
+    for M in ((1 << 30) - 1, total, total - 1, total // 2, total // 3, total // 6, total // 20, 0):
+        for tie in (0, 1):
+            _check(ctx, s, o, max(M, 400 + omax), 1, tie)
