@@ -13,6 +13,7 @@ from __future__ import annotations
 import importlib.util
 import os
 import re
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -22,7 +23,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvsched.so")
-HOST = os.path.join(HERE, "kvsched_host.so")  # csrc/host.cpp, a Python module over the library and torch
+# csrc/host.cpp, a Python module over the library and torch (its name says for which interpreter, so that another one leaves it alone)
+HOST = os.path.join(HERE, "kvsched_host" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["api.hip", "simulate.hip", "timeline_reg.hip", "sortedf.hip", "localswap.hip", "exactdp.hip", "horizon.hip", "permute.hip", "prefix.hip", "shortrows.hip", "online.hip", "predicted.hip"]
 DEVICE_FLAGS = [
     "--offload-arch=gfx950",
@@ -48,8 +50,8 @@ def lib_path() -> str:
 def is_stale() -> bool:
     if not os.path.exists(LIB) or not os.path.exists(HOST):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "kvsched.h")]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(HOST))
+    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "kvsched.h"), os.path.abspath(__file__)]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -143,38 +145,36 @@ def check_reserved_vgprs(hipcc: str, verbose: bool = False) -> None:
             print(f"reserved VGPR block untouched in all {bodies} {kernel} bodies", flush=True)
 
 
-def build_host(run) -> None:
+def build_host(run, lib: str, out: str) -> None:
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
-    tmp = HOST + f".tmp{os.getpid()}"
-    run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "host.cpp"), "-o", tmp,
+    run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", os.path.join(CSRC, "host.cpp"), "-o", out,
          "-isystem", os.path.join(torch, "include"), "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"),
          "-I", sysconfig.get_paths()["include"],
          "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10",
-         "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"])
-    os.replace(tmp, HOST)
+         "-L", os.path.dirname(lib), "-l:" + os.path.basename(lib), "-Wl,-rpath,$ORIGIN"])
 
 
 def build(verbose: bool = False) -> str:
+    """Both files, put in place together once everything has been built and checked."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB + f".tmp{os.getpid()}"
 
     def run(cmd):
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
 
-    with tempfile.TemporaryDirectory() as objects, ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
-        built = [os.path.join(objects, f + ".o") for f in SOURCES]
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
+        built = [os.path.join(tmp, f + ".o") for f in SOURCES]
+        lib, host = os.path.join(tmp, os.path.basename(LIB)), os.path.join(tmp, os.path.basename(HOST))
         list(pool.map(run, [[hipcc, *FLAGS, *SOURCE_FLAGS.get(f, []), "-c", os.path.join(CSRC, f), "-o", o]
                             for f, o in zip(SOURCES, built)]))
-        run([hipcc, *DEVICE_FLAGS[:1], "-fPIC", "-shared", *built, "-o", tmp])
-    try:
+        run([hipcc, *DEVICE_FLAGS[:1], "-fPIC", "-shared", *built, "-o", lib])
         check_reserved_vgprs(hipcc, verbose)
-    except Exception:
-        os.remove(tmp)
-        raise
-    os.replace(tmp, LIB)
-    build_host(run)
+        build_host(run, lib, host)
+        for new, place in ((lib, LIB), (host, HOST)):
+            beside = place + f".tmp{os.getpid()}"
+            shutil.copy(new, beside)
+            os.replace(beside, place)
     return LIB
 
 

@@ -11,6 +11,7 @@
 
 #include <ATen/ops/empty.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <utility>
 
@@ -150,4 +151,9 @@ PyModuleDef definition = {PyModuleDef_HEAD_INIT, "kvsched_host", nullptr, -1, me
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_kvsched_host() { return PyModule_Create(&definition); }
+PyMODINIT_FUNC PyInit_kvsched_host()
+{
+    PyObject *m = PyModule_Create(&definition);
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) Py_CLEAR(m);  // (whose layouts are compiled in)
+    return m;
+}

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -75,7 +76,15 @@ def _load() -> ctypes.CDLL:
 
 _lib = _load()
 
-from . import kvsched_host as _host  # noqa: E402  (it is linked to the library; no fallback if it is missing)
+try:  # csrc/host.cpp, built for one Python and one torch
+    from . import kvsched_host as _host  # noqa: E402
+
+    if _host.torch_version != torch.__version__.split("+")[0]:
+        raise ImportError(f"built for torch {_host.torch_version}, this is {torch.__version__}")
+except ImportError as e:
+    _host = None
+    warnings.warn(f"kvsched_host: {e}; the calls of a planning step go through ctypes, some 3 us slower each "
+                  "(`python -m paper_2508_06133_amd.build` builds it)", RuntimeWarning)
 
 
 def strerror(code: int) -> str:
@@ -149,7 +158,7 @@ class Context:
 
     def argmin(self, tel, result_out=None):
         """tel [C] int64 -> result [2] int64 = {index of the least valid entry, its value}."""
-        if result_out is None:
+        if _host and result_out is None:
             done = _host.argmin(self._address, tel, _stream())
             if done is not None:
                 if done[0] != OK:
@@ -172,7 +181,7 @@ class Context:
     def simulate(self, orders, s, o, M, completions: bool = True, common_prefix: int = 0, tel_out=None,
                  completion_out=None):
         """orders [C, n] -> (tel [C] int64, completion [C, n] int32 by request id or None)."""
-        if tel_out is None and completion_out is None:
+        if _host and tel_out is None and completion_out is None:
             done = _host.simulate(self._address, orders, s, o, int(M), completions, int(common_prefix), _stream())
             if done is not None:
                 if done[0] != OK:
@@ -243,7 +252,7 @@ class Context:
         dev = s.device
         self._pad_outputs(out is None)
         if out is None:
-            done = _host.sortedF(self._address, s, o, int(M), int(tie_rule), int(feas_mode), _stream())
+            done = _host.sortedF(self._address, s, o, int(M), int(tie_rule), int(feas_mode), _stream()) if _host else None
             if done is not None:
                 if done[0] != OK:
                     raise KvschedError(done[0], "kvsched_sortedF")
