@@ -128,3 +128,66 @@ def test_status_behind_a_launch_that_fails():
                 ctx.simulate(good, s, o, 400)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("n,C", [(8, 70), (40, 20), (256, 6)])
+def test_status_of_faulty_rows_after_a_wrong_guess(n, C):
+    """Decodes longer than the register file of the call before: the first launch leaves everything but the status words as it is, and the
+    second reports faulty rows where that one has said the status is.  Then a good call, whose guess is right."""
+    from paper_2508_06133_amd import kvsched
+
+    rng = np.random.default_rng(n)
+    ctx = kvsched.Context(0)
+    try:
+        for longest in (40, 600, 3000, 5000, 9000, 40, 3000, 14336, 40, 9000):
+            s, o = rng.integers(1, 50, n).astype(np.int32), rng.integers(1, 30, n).astype(np.int32)
+            o[n // 2] = longest
+            for faulty in (True, False, False):
+                rows = _rows(rng, n, C, faulty)
+                print(f"simulate without a scan: n={n} C={C} longest decode {longest} faulty={faulty}", flush=True)
+                tel, comp = ctx.simulate(_dev(rows), _dev(s), _dev(o), 18000)
+                assert ctx.device_status() == (kvsched.DEV_BAD_ORDER if faulty else 0)
+                good = [c for c in range(C) if not faulty or c != C // 2][:8]
+                tel_o, comp_o = oracle.simulate_many(s, o, 18000, rows[good], literal=False)
+                tel, comp = tel.cpu().numpy(), comp.cpu().numpy()
+                assert (tel[good] == tel_o).all() and (comp[good] == comp_o).all()
+                assert (tel == -1).sum() == (1 if faulty else 0)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("n,C", [(8, 70), (40, 20)])
+def test_status_of_replays(n, C):
+    """A captured call has its scan ahead: every replay leaves its own status, between eager calls that have none ahead."""
+    import torch
+    from paper_2508_06133_amd import kvsched
+
+    rng = np.random.default_rng(n)
+    s, o = rng.integers(1, 50, n).astype(np.int32), rng.integers(1, 30, n).astype(np.int32)
+    ds, do, M = _dev(s), _dev(o), 300
+    rows = _dev(_rows(rng, n, C, False))
+    tel = torch.empty(C, dtype=torch.int64, device="cuda:0")
+    comp = torch.empty((C, n), dtype=torch.int32, device="cuda:0")
+    ctx = kvsched.Context(0)
+    try:
+        ctx.set_o_max(30)
+        ctx.simulate(rows, ds, do, M, tel_out=tel, completion_out=comp)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ctx.simulate(rows, ds, do, M, tel_out=tel, completion_out=comp)
+        for turn, faulty in enumerate((True, False, False, True, True, False)):
+            if turn % 2:
+                ctx.simulate(_dev(_rows(rng, n, C, turn == 3)), ds, do, M)
+                assert ctx.device_status() == (kvsched.DEV_BAD_ORDER if turn == 3 else 0)
+            new = _rows(rng, n, C, faulty)
+            rows.copy_(_dev(new))
+            print(f"captured simulate: n={n} C={C} replay {turn} faulty={faulty}", flush=True)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert ctx.device_status() == (kvsched.DEV_BAD_ORDER if faulty else 0)
+            good = [c for c in range(C) if not faulty or c != C // 2]
+            tel_o, comp_o = oracle.simulate_many(s, o, M, new[good], literal=False)
+            assert (tel.cpu().numpy()[good] == tel_o).all() and (comp.cpu().numpy()[good] == comp_o).all()
+    finally:
+        ctx.close()
