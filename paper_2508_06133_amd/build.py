@@ -38,7 +38,7 @@ DEVICE_FLAGS = [
 # predicted.hip 5.9 ms without, 5.1 with it); elsewhere it makes no difference.
 UNIFORM_BRANCHES = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
 SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES}
-FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall", "-Wno-unused-function"]
+FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall"]
 RESERVED_VGPR_BASE = 30  # KVS_PB in timeline_reg.hip
 PREDICTED_VGPR_BASE = 60  # KVP_PB in predicted.hip
 

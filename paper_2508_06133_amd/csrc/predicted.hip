@@ -77,12 +77,6 @@ struct PredParams {
 
 __device__ __forceinline__ int p_uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-__device__ __forceinline__ long long p_uni64(long long v)
-{
-    const int lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
-    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
 __device__ __forceinline__ void p_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -328,7 +322,6 @@ struct Rows {
     static __device__ __forceinline__ int lds_words(int) { return 0; }
     __device__ __forceinline__ Rows(int *, int, int lane_) : lane(lane_), b(0) { rows_clear<NR>(); }
     __device__ __forceinline__ int longest() const { return H; }
-    __device__ __forceinline__ void uniform() { b = p_uni(b); }
     // the present round goes on from t to `to`: rows move down while row 0 ends before round to + 1
     __device__ __forceinline__ void advance(int, int to)
     {
@@ -377,7 +370,6 @@ struct Ring {
         p_sync();
     }
     __device__ __forceinline__ int longest() const { return mask + 1; }
-    __device__ __forceinline__ void uniform() {}
     __device__ __forceinline__ void advance(int t, int to)
     {
         const int span = min(to - t, mask + 1);

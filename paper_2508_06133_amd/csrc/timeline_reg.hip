@@ -185,7 +185,6 @@ __device__ __forceinline__ void prof_load(const int32_t *rows, int lane)
 // upper end: the bimodal ones 14600, as they are then placed 64 at a time one by one.)  The files of 129 rows and more, where a measurement
 // costs most, begin with 16 and go below only where it was for the sake of long ones.
 //
-//
 // What it gives: of bimodal orders (decodes 1 or 4096) 97 % of the requests start that way, 56 at a time, and their ramps are added 340 at a
 // time: 1025 orders of 100000 27.2 -> 4.5 ms (3.0 now), of which the timelines 26.3 -> 3.6 (2.6): one wavefront per SIMD, bound by the chain
 // of the blocks (prefix sum, list: 1200 cycles per 64 requests) and of the 250 moves.  4096 chat orders of 200, half of
@@ -1429,7 +1428,7 @@ __global__ __launch_bounds__(WAVE *WPB) __attribute__((amdgpu_waves_per_eu(NR <=
         asm volatile("" : "+v"(l));  // (as in group_clear)
         return rd.at(max(min(first + WAVE, n) - 1 - l, min(first, n - 1)));
     };
-    // (byte offsets of 32 bits: there are fewer than 2^21 requests)
+    // (byte offsets of 32 bits: there are fewer than 2^24 requests, as rounds are 32-bit numbers)
     auto gathered = [&](const int32_t *from, int at) __attribute__((always_inline)) -> int {
         return *(const int32_t *)((const char *)from + (unsigned)at * 4u);
     };
