@@ -34,8 +34,9 @@ DEVICE_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 # Branches that all lanes of a wavefront take together stay branches: by default every way out of a loop becomes a flag in
-# scalar registers, tested later.  For the kernels whose main loop has no other branches (4096 candidates of
-# predicted.hip 5.9 ms without, 5.1 with it); elsewhere it makes no difference.
+# scalar registers, tested later.  For the files whose kernels have main loops without other branches (4096 candidates of
+# predicted_reg_kernel 5.9 ms without, 5.1 with it; predicted_ring_kernel, whose passes over the ring do branch by the lane, has it too);
+# elsewhere it makes no difference.
 UNIFORM_BRANCHES = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
 SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES}
 FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall"]

@@ -88,7 +88,12 @@ struct OrderSource {
     const int32_t *moves;   // [K][3]; candidate K (one past the last move) is the base itself
 };
 
-constexpr int KVS_SCANNED_HERE = 256;   // (see SimParams::scan_here)
+// Positions up to which the launch scans the lengths itself (SimParams::scan_here).  A launch ahead takes 2 us with a bound on the decodes, 3
+// to 4 without, at any size; here every wavefront reads all lengths.  2048 chat orders, scan ahead and here, without a bound 40 13.2
+// and 11.8 us, 256 58.7 and 54.8, 512 96.1 and 92.3, 768 137.9 and 137.6, 1024 167.4 and 167.2; with one 11.7 and 9.4, 54.1 and 51.8, 91.4 and 89.4,
+// 130.3 and 128.3, 160.2 and 158.3; one order of 256 49.0 and 46.9.  No size measured loses: up to 512 the line leaves 2 to 6 %, beyond it
+// nothing to 1 %.
+constexpr int KVS_SCANNED_HERE = 256;
 constexpr int KVS_CHECKED_ROW = 1024;  // (a bit each has room in the LDS of the smallest file, and a word per lane of 32)
 
 struct SimParams {

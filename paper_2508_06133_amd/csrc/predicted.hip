@@ -34,11 +34,12 @@
 // front, so the 64 positions around the first waiting one sit in registers (one position per lane,
 // fetched from the order row and the length tables when the walk leaves the window).
 // What bounds the call is the number of candidates in flight times the chain of dependent instructions each is (2000 mixed
-// requests: 400 k vector and 525 k scalar instructions; four candidates share a SIMD, whose scalar unit is 65 % busy, and wait for
-// memory, LDS and branches a third of the time).  Hence no branch of the loop over rounds depends on the lane (see
-// lane_mask.h), tiles of the list are read two at a time, and what scalars would add up entry by entry is added up a lane each:
-// 613 k and 759 k instructions before; 4096 / 256 / 16 candidates 7.58 / 6.42 / 5.10 -> 4.75 / 3.79 / 2.98 ms, 1024 of 2000
-// chat requests 7.94 -> 4.81.  And the
+// requests: 380 k vector and 475 k scalar instructions; four candidates share a SIMD, whose scalar unit is 65 % busy, and wait for
+// memory, LDS and branches a third of the time).  Hence no branch of the loop over rounds depends on the lane with Rows (see
+// lane_mask.h; the passes over a Ring are loops from the lane's round on), tiles of the list are read two at a time, and what scalars would
+// add up entry by entry is added up a lane each: 613 k and 759 k instructions before; 4096 / 256 / 16 candidates 7.58 / 6.42 / 5.10 ->
+// 4.75 / 3.79 / 2.98 ms, 1024 of 2000 chat requests 7.94 -> 4.81; with a Ring (decodes four times as long) 2048 / 512 / 16 of 2000 mixed
+// requests 65.7 / 22.3 / 21.3 -> 50.2 / 16.8 / 16.0, 1024 of 500 chat requests 5.7 -> 4.7.  And the
 // list decides how many candidates fit a compute unit: a first launch runs every candidate with a list of at
 // most `cap` entries (launch_variant); a candidate whose list overflows gives up and is run again by a second launch
 // whose list holds all n positions.
@@ -358,7 +359,7 @@ struct Rows {
 
 // A ring of H slots in LDS for longer estimates; one launch, 10 bytes an entry as above (with s in the list, 14 bytes, the
 // same time for few candidates and fewer of them side by side: 2048 candidates of n = 2000 with decodes up to 8192
-// 65 ms, 52 without; 512 of them 21.1 and 21.5).  The slots of rounds at or before t are empty and stand for the rounds H later.
+// 65 ms, 52 without, as the loop over rounds was then; 512 of them 21.1 and 21.5).  The slots of rounds at or before t are empty and stand for the rounds H later.
 struct Ring {
     int lane, mask;
     int *slot;
