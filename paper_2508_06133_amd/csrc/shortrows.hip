@@ -76,25 +76,26 @@ __global__ __launch_bounds__(64) void short_rows_kernel(SimParams p, int32_t o_l
         // (1 <= o <= longest <= M, hence M - o >= 0, and 1 <= s <= M - o)
         const bool good = (unsigned)o_next - 1u < (unsigned)longest && (unsigned)s_next - 1u < (unsigned)M - (unsigned)o_next;
         valid &= good;  // a request that cannot be scheduled ends in the round it is reached in and holds nothing
-        const int reached = t;
         const int s = good ? s_next : 0, o = good ? o_next : 0;
         raw = ids[min(k + 1, n - 1)];  // (the next one's lengths are on their way meanwhile)
         id = min(max(raw, 0), n - 1);
         s_next = len_s[id];
         o_next = len_o[id];
-        const unsigned over = (unsigned)(s - M);
+        // (it is looked at as one round without a token, s + 1 = 0, which no completion moves; as no rounds a completion in round t
+        // itself could be in its way)
+        const int rounds = good ? o : 1;
+        const unsigned over = (unsigned)((good ? s : -1) - M);
 #pragma unroll
         for (int f = N - 4; f >= 0; f -= 4) {
             if (k <= f) continue;  // (uniform: four places that are empty yet)
 #pragma unroll
             for (int i = f + 3; i >= f; --i) {
-                const int bound = (int)(b[i] + over), x = c[i] - o;
+                const int bound = (int)(b[i] + over), x = c[i] - rounds;
                 const int least = max(x + 1, min(c[i], bound));
                 const int at_x = bound - __mul24(x, i + 2);
                 t = at_x + __mul24(t, i + 2) > t ? max(t, least) : t;
             }
         }
-        t = good ? t : reached;  // (the test takes a completion in round t itself as in the way of a request of no rounds)
         const int c_new = t + o;
         const unsigned a_new = (unsigned)(s - t);
         tel += c_new;
