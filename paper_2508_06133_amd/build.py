@@ -25,7 +25,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvsched.so")
 # csrc/host.cpp, a Python module over the library and torch (its name says for which interpreter, so that another one leaves it alone)
 HOST = os.path.join(HERE, "kvsched_host" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
-SOURCES = ["api.hip", "simulate.hip", "timeline_reg.hip", "sortedf.hip", "localswap.hip", "exactdp.hip", "horizon.hip", "permute.hip", "prefix.hip", "shortrows.hip", "online.hip", "predicted.hip"]
+SOURCES = ["api.hip", "simulate.hip", "timeline_reg.hip", "sortedf.hip", "localswap.hip", "exactdp.hip", "horizon.hip", "permute.hip", "prefix.hip", "shortrows.hip", "eventrows.hip", "online.hip", "predicted.hip"]
 DEVICE_FLAGS = [
     "--offload-arch=gfx950",
     "-O3",
@@ -38,7 +38,7 @@ DEVICE_FLAGS = [
 # predicted_reg_kernel 5.9 ms without, 5.1 with it; predicted_ring_kernel, whose passes over the ring do branch by the lane, has it too);
 # elsewhere it makes no difference.
 UNIFORM_BRANCHES = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
-SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES}
+SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES, "eventrows.hip": UNIFORM_BRANCHES}
 FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall"]
 RESERVED_VGPR_BASE = 30  # KVS_PB in timeline_reg.hip
 PREDICTED_VGPR_BASE = 60  # KVP_PB in predicted.hip

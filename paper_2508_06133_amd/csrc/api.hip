@@ -81,12 +81,24 @@ int read_words(kvsched_ctx *ctx, hipStream_t st)
 }
 
 // The timeline kernel, bracketed by the context's events when timing is on.
-int run_timelines(kvsched_ctx *ctx, const SimParams &p, int32_t H, hipStream_t st, bool short_rows = false, int32_t o_limit = INT32_MAX)
+// events: by the event kernel (o_bound <= KVS_REG_MAX_O), and what it leaves, if it may leave any, by the register kernel.
+int run_timelines(kvsched_ctx *ctx, const SimParams &p, int32_t H, hipStream_t st, bool short_rows = false, int32_t o_limit = INT32_MAX,
+                  bool events = false)
 {
     if (ctx->timing && hipEventRecord(ctx->ev0, st) != hipSuccess) return KVSCHED_EHIP;
-    // profile in registers when the longest decode fits there, else the LDS ring
-    int rc = short_rows ? kvs_launch_short_rows(p, o_limit, st)
+    int rc;
+    if (events) {
+        rc = kvs_launch_event_rows(p, st);
+        if (rc == KVSCHED_OK && p.todo) {
+            SimParams rest = p;
+            rest.scan_here = 0;  // (if the lengths have been looked over: with decodes above the limit no row is left)
+            rc = kvs_launch_simulate_reg(rest, st);
+        }
+    } else {
+        // profile in registers when the longest decode fits there, else the LDS ring
+        rc = short_rows ? kvs_launch_short_rows(p, o_limit, st)
              : p.o_bound <= KVS_REG_MAX_O ? kvs_launch_simulate_reg(p, st) : kvs_launch_simulate(p, H, st);
+    }
     if (rc != KVSCHED_OK) return rc;
     if (p.scan_here) ctx->status_turn = p.status_word - KVS_W_STATUS_TURN;  // (only now: a launch that failed has cleared nothing)
     if (ctx->timing) {
@@ -151,12 +163,13 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
     if (min_position_out) *min_position_out = 0;
     if (ctx->o_max_bound > 0) {
         *o_bound_out = ctx->o_max_bound;
-        return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st, moves, K);
+        return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st, moves, K, nullptr, 0,
+                                       moves ? nullptr : ctx->h_scan + KVS_H_FEW);
     }
     if (capturing(st)) return KVSCHED_EHIP;
     // (the first and last position the moves touch come with it)
     int rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, moves, K, ctx->h_scan,
-                                     next_seq(ctx));
+                                     next_seq(ctx), moves ? nullptr : ctx->h_scan + KVS_H_FEW);
     if (rc != KVSCHED_OK) return rc;
     rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;
@@ -515,6 +528,24 @@ static bool scans_here(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_b
 // The status word of the next such call, whose launch clears the other one for the call after it.
 static int32_t next_status_word(const kvsched_ctx *ctx) { return KVS_W_STATUS_TURN + (ctx->status_turn ^ 1); }
 
+// Are timelines of n positions, no prefix shared, placed by the event kernel (eventrows.hip)?  Where the decodes are few, which the kernel
+// sees for itself, and may be long: with decodes up to 2048 the timeline kernel's 33 rows are as fast (1000 orders of 10000 with four
+// lengths 2260 us, 2660 here).  If they are not few, or a row has too many completions ahead, the timeline kernel's launch behind it
+// places the rows; so a launch is wasted, 3 us.  From 8192 positions on that is next to nothing beside a timeline (700 us and more); for shorter
+// ones what the context has seen last of the lengths decides, which may be out of date and then costs that launch, or the time
+// of the other kernel.  Not while the stream is captured, as the list of rows left lies in memory that later calls may replace
+// (orders of up to 64 have none); not where the caller asks for rows to be resumed, nor where they are by themselves unless the lengths are known to be few.
+constexpr int32_t kEventsUnasked = 8192;
+constexpr int32_t kEventsFrom = 2048;
+static bool by_events(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bound, bool few, hipStream_t st)
+{
+    if (o_bound <= kEventsFrom || o_bound > KVS_REG_MAX_O || n > KVS_EVENTS_MAX_N) return false;
+    const bool resume = resume_pays(ctx, C, n, o_bound);
+    if (ctx->resume_min_rows != KVSCHED_RESUME_AUTO && resume) return false;
+    if (!few && (resume || n < kEventsUnasked)) return false;
+    return n <= WAVE_POSITIONS || !capturing(st);
+}
+
 // kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
 // longer one (only where rows are not resumed and no prefix is placed ahead).  scan: no length scan is enqueued before
 // (scans_here), the launch does it and, if gated, leaves its result in pinned memory under number ctx->scan_seq.
@@ -575,7 +606,10 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     ctx->resume_rows = 0;
     ctx->rejoin_offset = 0;
     const int32_t *resumed_blocks = nullptr, *resumed_row0 = nullptr, *rejoined = nullptr;
-    if (cp == 0 && resume_pays(ctx, C, n, o_bound)) {
+    p.few_out = ctx->h_scan + KVS_H_FEW;
+    p.few_known = __atomic_load_n(p.few_out, __ATOMIC_RELAXED);
+    const bool events = cp == 0 && by_events(ctx, C, n, o_bound, p.few_known != 0, st);
+    if (cp == 0 && !events && resume_pays(ctx, C, n, o_bound)) {
         const int32_t nblk = (n - 1) / WAVE_POSITIONS;
         const int32_t stride = kvs_reg_state_words(o_bound);
         const size_t list_bytes = align256(sizeof(int32_t) * (size_t)C);
@@ -672,11 +706,16 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
         ctx->resume_first = first;
     } else {
         const bool short_rows = cp == 0 && kvs_short_rows(C, n);
+        if (events && n > WAVE_POSITIONS) {
+            rc = ensure_scratch(ctx, sizeof(int32_t) * (size_t)C);
+            if (rc != KVSCHED_OK) return rc;
+            p.todo = (int32_t *)ctx->d_scratch;
+        }
         if (cp == 0 && n <= KVS_CHECKED_ROW && o_bound <= KVS_REG_MAX_O) {
             p.check_rows = 1;
             p.completion_by_position = 0;
         }
-        rc = run_timelines(ctx, p, H, st, short_rows, o_limit);
+        rc = run_timelines(ctx, p, H, st, short_rows, o_limit, events && !short_rows);
         if (rc != KVSCHED_OK || short_rows || p.check_rows) return rc;  // (these check the orders and write by request id)
     }
     if (prefix_comp) {
@@ -685,9 +724,9 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     }
     if (p.completion_by_position) {  // this pass over the rows checks them as well
         rc = kvs_launch_permute_rows(orders, C, n, completion_out, tel_out, ctx->d_words, resumed_blocks, resumed_row0,
-                                     resumed_row0 ? rejoined : nullptr, st, o_limit);
+                                     resumed_row0 ? rejoined : nullptr, st, o_limit, p.todo);
     } else {
-        rc = kvs_launch_check_orders(orders, C, n, tel_out, ctx->d_words, st, o_limit);
+        rc = kvs_launch_check_orders(orders, C, n, tel_out, ctx->d_words, st, o_limit, p.todo);
     }
     if (rc != KVSCHED_OK || cp == 0) return rc;
     return kvs_launch_check_prefix(orders, C, n, cp, tel_out, ctx->d_words, st);
@@ -724,7 +763,7 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
         next_seq(ctx);
         scan = scans_here(ctx, C, n, guess, common_prefix, st);
         if (scan) status_word = next_status_word(ctx);
-        else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq);
+        else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq, ctx->h_scan + KVS_H_FEW);
         if (rc == KVSCHED_OK)
             rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, scan, status_word, tel_out, completion_out, 0, st);
         if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);

@@ -58,6 +58,25 @@ __device__ __forceinline__ void report_lengths(const Params &p, int longest, int
     }
 }
 
+// Are there at most KVS_FEW_LENGTHS different ones among the lanes' decode lengths?
+__device__ __forceinline__ bool few_lengths(int o)
+{
+    unsigned long long others = ~0ull;
+    for (int k = 0; k < KVS_FEW_LENGTHS && others != 0; ++k)
+        others &= ~__builtin_amdgcn_ballot_w64(o == __builtin_amdgcn_readlane(o, __builtin_ctzll(others)));
+    return others == 0;
+}
+
+// The request whose decode length is a lane's part of that sample.
+__device__ __forceinline__ int sampled(int lane, int n) { return (int)(((long long)lane * n) >> 6); }
+
+// (only what the host did not know: the end of a launch waits for the store, half a microsecond)
+template <class Params>
+__device__ __forceinline__ void report_few(const Params &p, bool few)
+{
+    if (few != (p.few_known != 0)) __hip_atomic_store(p.few_out, few ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The flags that one request's lengths give (bound: the caller's on the decode lengths, or 0).
 __device__ __forceinline__ int length_flags(int s, int o, int M, int bound)
 {

@@ -42,6 +42,7 @@ enum {
     KVS_H_KMAX = 5,
     KVS_H_KMIN = 6,
     KVS_H_BATCHES = 7,
+    KVS_H_FEW = 8,  // 1: the last backlog looked over had few decode lengths (few_lengths); nobody waits for it
     KVS_H_COUNT = 16
 };
 
@@ -122,6 +123,11 @@ struct SimParams {
     int32_t status_word = KVS_W_STATUS;  // (with or without a scan: where rows that are no permutations are reported)
     int32_t *host = nullptr;
     int32_t seq = 0;
+    int32_t *few_out = nullptr;  // pinned: whether the decode lengths are few, by a launch that looks them over
+    int32_t few_known = 0;       // ... and what it held before
+    // Rows of more than 64 positions: the event kernel sets todo[c] = 0 for the rows it has placed and 1 for those it has not, and
+    // the register kernel's plain launch behind it (which has it set too) places those.
+    int32_t *todo = nullptr;
     // Register kernel only: simulate positions [k_begin, k_end) (k_end == 0: up to n), starting
     // from / leaving behind a saved timeline state of KVS_STATE_HEAD_WORDS + 64 NR int32 words:
     // {b64, t, 62 unused, the 64 lanes' partial sums of completion rounds as int64, then the
@@ -183,7 +189,7 @@ constexpr size_t KVS_STATE_MAX_WORDS = KVS_STATE_HEAD_WORDS + 225 * 64;
 // (moves: the positions they touch are scanned along; host: pinned words that receive the results and then seq)
 int kvs_launch_scan_lengths(const int32_t *s, const int32_t *o, int32_t n, int32_t M, int32_t o_bound,
                             int32_t *d_words, hipStream_t st, const int32_t *moves = nullptr, int32_t K = 0,
-                            int32_t *host = nullptr, int32_t seq = 0);
+                            int32_t *host = nullptr, int32_t seq = 0, int32_t *few_out = nullptr);
 int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st);
 // timeline_reg.hip (decode lengths up to KVS_REG_MAX_O)
 constexpr int32_t KVS_REG_MAX_O = 14336;  // 224 rows of 64 rounds, and one more row for the window's offset
@@ -192,13 +198,18 @@ int kvs_launch_simulate_reg(const SimParams &p, hipStream_t st);
 // shortrows.hip: orders of up to 32 requests, a lane each
 bool kvs_short_rows(int32_t rows, int32_t n);
 int kvs_launch_short_rows(const SimParams &p, int32_t o_limit, hipStream_t st);
+
+// eventrows.hip: a lane per completion round
+constexpr int KVS_FEW_LENGTHS = 4;
+constexpr int32_t KVS_EVENTS_MAX_N = 400000;  // (a bit per request beside what a chunk takes, within 64 KB of LDS)
+int kvs_launch_event_rows(const SimParams &p, hipStream_t st);
 int32_t kvs_reg_state_words(int32_t o_bound);  // words of one snapshot for this decode bound
 int32_t kvs_reg_file_bound(int32_t o_bound);   // the longest decode its register file takes
 int32_t kvs_reg_wavefronts(int32_t o_bound);   // timelines of this decode bound that the chip holds at once
 
-// (o_limit: the launch does nothing when the length scan before it found a longer decode)
+// (o_limit: the launch does nothing when the length scan before it found a longer decode; todo: nor for rows with todo[c] = 0)
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
-                            hipStream_t st, int32_t o_limit = INT32_MAX);
+                            hipStream_t st, int32_t o_limit = INT32_MAX, const int32_t *todo = nullptr);
 int kvs_launch_argmin(const int64_t *tel, int32_t K, int64_t *result_out, int32_t *d_words, hipStream_t st);
 // The end of a local-search step: latencies of timelines that stopped early completed from the base order's (rejoin or
 // NULL), malformed moves marked, latencies copied to tel_out (or NULL), best move, its latency and the base order's.
@@ -250,7 +261,7 @@ constexpr int32_t KVS_PERMUTE_MAX_N = 15872;  // one row and its bitmap must fit
 // completion rounds before them are row0[k], row 0's in position order
 int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t *completion, int64_t *tel_out,
                             int32_t *d_words, const int32_t *resume_block, const int32_t *row0,
-                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit = INT32_MAX);
+                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit = INT32_MAX, const int32_t *todo = nullptr);
 
 // horizon.hip.  What the context keeps between horizon steps (one device buffer).
 enum {

@@ -22,8 +22,9 @@ namespace {
 __global__ __launch_bounds__(256) void permute_rows_kernel(const int32_t *orders, int32_t n, int32_t *completion,
                                                            int64_t *tel_out, int32_t *words,
                                                            const int32_t *resume_block, const int32_t *row0,
-                                                           const int32_t *rejoin_block, int32_t o_limit)
+                                                           const int32_t *rejoin_block, int32_t o_limit, const int32_t *todo)
 {
+    if (todo && todo[blockIdx.x] == 0) return;
     const int o_max = words[KVS_W_OMAX];
     extern __shared__ int row_by_id[];
     unsigned int *seen = (unsigned int *)(row_by_id + n);  // one bit per request id
@@ -98,10 +99,10 @@ __global__ __launch_bounds__(256) void permute_short_rows_kernel(const int32_t *
 
 int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t *completion, int64_t *tel_out,
                             int32_t *d_words, const int32_t *resume_block, const int32_t *row0,
-                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit)
+                            const int32_t *rejoin_block, hipStream_t st, int32_t o_limit, const int32_t *todo)
 {
     if (n > KVS_PERMUTE_MAX_N) return KVSCHED_ERANGE;
-    if (n <= kShortRow && !resume_block) {
+    if (n <= kShortRow && !resume_block && !todo) {
         const int rows = kShortEntries / n;
         hipLaunchKernelGGL(permute_short_rows_kernel, dim3((unsigned)((C + rows - 1) / rows)), dim3(256), 0, st, orders, C, n,
                            rows, completion, tel_out, d_words, o_limit);
@@ -109,6 +110,6 @@ int kvs_launch_permute_rows(const int32_t *orders, int32_t C, int32_t n, int32_t
     }
     const size_t lds = sizeof(int32_t) * ((size_t)n + (((size_t)n + 31) >> 5));
     hipLaunchKernelGGL(permute_rows_kernel, dim3((unsigned)C), dim3(256), lds, st, orders, n, completion, tel_out,
-                       d_words, resume_block, row0, rejoin_block, o_limit);
+                       d_words, resume_block, row0, rejoin_block, o_limit, todo);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_kernel(SimParams p)
 // memory) finds them there: the wait is one store across the bus instead of a copy and a stream synchronisation.
 __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, const int32_t *o, int32_t n, int32_t M,
                                                             int32_t o_bound, const int32_t *moves, int32_t K,
-                                                            int32_t *words, int32_t *host, int32_t seq)
+                                                            int32_t *words, int32_t *host, int32_t seq, int32_t *few_out)
 {
     __shared__ int sh_max[16], sh_flag[16], sh_min[16], sh_top[16];
     const int first = blockIdx.x * 1024 + threadIdx.x, stride = gridDim.x * 1024;
@@ -134,6 +134,11 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
         if (!ok) lowest = 0;
         else if (i != j) lowest = min(lowest, min(i, j));
         top = max(top, min(max(max(i, j), 0), n - 1));  // (as the timeline kernel clamps)
+    }
+    if (few_out && first < WAVE) {
+        const bool few = few_lengths(o[sampled(first, n)]);
+        if (first == 0)  // (has left this thread when it says that it is done)
+            __hip_atomic_store(few_out, few ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     mx = wave_max_i32(mx);
     flag = wave_max_i32(flag & 1) | wave_max_i32(flag & KVSCHED_DEV_O_MAX);
@@ -184,13 +189,13 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
 // One wavefront per row: is it a permutation of 0..n-1?  Bitmap of n bits per wave in LDS.
 template <int WPB>
 __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *orders, int32_t C, int32_t n,
-                                                                 int64_t *tel_out, int32_t *words, int32_t o_limit)
+                                                                 int64_t *tel_out, int32_t *words, int32_t o_limit, const int32_t *todo)
 {
     extern __shared__ unsigned int bitmap_all[];
     const int o_max = words[KVS_W_OMAX];
     const int lane = threadIdx.x & (WAVE - 1);
     const int cand = blockIdx.x * WPB + (threadIdx.x >> 6);
-    if (cand >= C) return;
+    if (cand >= C || (todo && todo[cand] == 0)) return;
     const int nw = (n + 31) >> 5;
     unsigned int *bm = bitmap_all + (size_t)(threadIdx.x >> 6) * nw;
     for (int i = lane; i < nw; i += WAVE) bm[i] = 0;
@@ -218,10 +223,11 @@ __global__ __launch_bounds__(WAVE *WPB) void check_orders_kernel(const int32_t *
 // reads of a thread are in flight.  1025 rows of 100000: 184 us by 1024 threads a row, which take three turns, 139 so; one of 10000 4.7.
 template <int TPB>
 __global__ __launch_bounds__(TPB) void check_orders_wide_kernel(const int32_t *orders, int32_t C, int32_t n,
-                                                                int64_t *tel_out, int32_t *words, int32_t o_limit)
+                                                                int64_t *tel_out, int32_t *words, int32_t o_limit, const int32_t *todo)
 {
     extern __shared__ unsigned int bitmap_all[];
     constexpr int E = 8;
+    if (todo && todo[blockIdx.x] == 0) return;
     const int o_max = words[KVS_W_OMAX];
     const int cand = blockIdx.x;
     const int nw = (n + 31) >> 5;
@@ -349,12 +355,12 @@ int launch_timeline(const SimParams &p, hipStream_t st)
 
 int kvs_launch_scan_lengths(const int32_t *s, const int32_t *o, int32_t n, int32_t M, int32_t o_bound,
                             int32_t *d_words, hipStream_t st, const int32_t *moves, int32_t K, int32_t *host,
-                            int32_t seq)
+                            int32_t seq, int32_t *few_out)
 {
     const int32_t most = moves && K > n ? K : n;
     const unsigned blocks = most <= 4096 ? 1u : most < 64 * 4096 ? (unsigned)((most + 4095) / 4096) : 64u;
     hipLaunchKernelGGL(scan_lengths_kernel, dim3(blocks), dim3(1024), 0, st, s, o, n, M, o_bound, moves, moves ? K : 0,
-                       d_words, host, seq);
+                       d_words, host, seq, few_out);
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
 
@@ -375,7 +381,7 @@ int kvs_launch_simulate(const SimParams &p, int32_t ring_slots, hipStream_t st)
 }
 
 int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t *tel_out, int32_t *d_words,
-                            hipStream_t st, int32_t o_limit)
+                            hipStream_t st, int32_t o_limit, const int32_t *todo)
 {
     const size_t per_wave = (size_t)((n + 31) >> 5) * sizeof(unsigned int);
     if (per_wave > 65536) return KVSCHED_ERANGE;
@@ -383,16 +389,16 @@ int kvs_launch_check_orders(const int32_t *orders, int32_t C, int32_t n, int64_t
     if ((n >= 16384 && C <= 8192) || (n >= 1024 && C <= 512)) {
         if (C <= 512)
             hipLaunchKernelGGL(check_orders_wide_kernel<1024>, dim3((unsigned)C), dim3(1024), per_wave, st, orders, C, n,
-                               tel_out, d_words, o_limit);
+                               tel_out, d_words, o_limit, todo);
         else
             hipLaunchKernelGGL(check_orders_wide_kernel<256>, dim3((unsigned)C), dim3(256), per_wave, st, orders, C, n,
-                               tel_out, d_words, o_limit);
+                               tel_out, d_words, o_limit, todo);
     } else if (per_wave * 4 <= 65536) {
         hipLaunchKernelGGL((check_orders_kernel<4>), dim3((unsigned)((C + 3) / 4)), dim3(256), per_wave * 4, st,
-                           orders, C, n, tel_out, d_words, o_limit);
+                           orders, C, n, tel_out, d_words, o_limit, todo);
     } else {
         hipLaunchKernelGGL((check_orders_kernel<1>), dim3((unsigned)C), dim3(64), per_wave, st, orders, C, n,
-                           tel_out, d_words, o_limit);
+                           tel_out, d_words, o_limit, todo);
     }
     return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
 }
