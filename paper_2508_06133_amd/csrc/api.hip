@@ -371,6 +371,7 @@ int kvsched_create(kvsched_ctx **out, int device_id)
     }
     ctx->h_scan = ctx->h_words + KVS_W_COUNT;
     ctx->h_scan[KVS_H_SEQ] = 0;
+    ctx->h_scan[KVS_H_FEW] = 0;
     // devices beyond the table simply cannot use kvsched_best_neighbor_static
     if (device_id < kMaxDevices) {
         const int rc = static_scratch_of_current_device(device_id, &ctx->static_scratch);

@@ -34,10 +34,10 @@ enum {
 // What the length scan leaves in pinned host memory for a call that waits for it.
 // ... and what the exact DP leaves there between batches.
 enum {
-    KVS_H_OMAX = 0,
-    KVS_H_MINPOS = 1,
-    KVS_H_MAXPOS = 2,
-    KVS_H_SEQ = 3,  // number of the launch that has written the others
+    KVS_H_OMAX = 0,  // (it and the number are one word of 64 bits)
+    KVS_H_SEQ = 1,   // number of the launch that has written the others
+    KVS_H_MINPOS = 2,
+    KVS_H_MAXPOS = 3,
     KVS_H_REMAIN = 4,
     KVS_H_KMAX = 5,
     KVS_H_KMIN = 6,

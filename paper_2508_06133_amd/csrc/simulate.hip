@@ -137,8 +137,7 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
     }
     if (few_out && first < WAVE) {
         const bool few = few_lengths(o[sampled(first, n)]);
-        if (first == 0)  // (has left this thread when it says that it is done)
-            __hip_atomic_store(few_out, few ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (first == 0) to_host(few_out, few ? 1 : 0);
     }
     mx = wave_max_i32(mx);
     flag = wave_max_i32(flag & 1) | wave_max_i32(flag & KVSCHED_DEV_O_MAX);
@@ -178,11 +177,12 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
     words[KVS_W_MAXPOS] = top;
     words[KVS_W_ESTMAX] = 0;
     if (host) {
-        host[KVS_H_OMAX] = mx;
-        host[KVS_H_MINPOS] = lowest;
-        host[KVS_H_MAXPOS] = top;
-        __threadfence_system();
-        __hip_atomic_store(&host[KVS_H_SEQ], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (moves) {
+            to_host(&host[KVS_H_MINPOS], lowest);
+            to_host(&host[KVS_H_MAXPOS], top);
+            device_writes_done();
+        }
+        longest_to_host(host, mx, seq);
     }
 }
 
