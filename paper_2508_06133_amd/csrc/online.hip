@@ -239,10 +239,120 @@ __device__ __forceinline__ u64 take_next(Batch &b)
     return lane_u64(b.key, l);
 }
 
+// Four more bits of a mask, those of lanes B + 3 ... B: does the lane have less o than this one?  (Written out because a scalar that a
+// vector instruction has written may be read by one only two instructions later, and so may its mask.)
+template <int B>
+__device__ __forceinline__ void four_below(unsigned &mask, unsigned o)
+{
+    unsigned r0, r1, r2, r3;
+    u64 m0, m1, m2, m3;
+    asm("s_nop 1\n"
+        "v_readlane_b32 %1, %9, %10\n"
+        "v_readlane_b32 %2, %9, %11\n"
+        "v_readlane_b32 %3, %9, %12\n"
+        "v_readlane_b32 %4, %9, %13\n"
+        "v_cmp_lt_u32 %5, %1, %9\n"
+        "v_cmp_lt_u32 %6, %2, %9\n"
+        "v_cmp_lt_u32 %7, %3, %9\n"
+        "v_cmp_lt_u32 %8, %4, %9\n"
+        "v_addc_co_u32 %0, vcc, %0, %0, %5\n"
+        "v_addc_co_u32 %0, vcc, %0, %0, %6\n"
+        "v_addc_co_u32 %0, vcc, %0, %0, %7\n"
+        "v_addc_co_u32 %0, vcc, %0, %0, %8\n"
+        : "+&v"(mask), "=&s"(r0), "=&s"(r1), "=&s"(r2), "=&s"(r3), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(o), "n"(B + 3), "n"(B + 2), "n"(B + 1), "n"(B)
+        : "vcc");
+}
+
+// Lanes B + 31 ... B, of which `count` hold a request at most.
+template <int B>
+__device__ __forceinline__ unsigned below(unsigned o, int count)
+{
+    unsigned mask = 0;
+    if (count > 24) four_below<B + 28>(mask, o), four_below<B + 24>(mask, o);
+    if (count > 16) four_below<B + 20>(mask, o), four_below<B + 16>(mask, o);
+    if (count > 8) four_below<B + 12>(mask, o), four_below<B + 8>(mask, o);
+    four_below<B + 4>(mask, o);
+    four_below<B>(mask, o);
+    return mask;
+}
+
+// The exchanges of a batch among the lanes' requests, as long as no request from w_limit on (the size of the first that `count` lanes do
+// not cover) has room: w_most + slack, what the largest member could be exchanged for, tells.  Returns whether none is left.
+// Who has less o than whom does not change with an exchange, so each lane keeps that as a mask of 64 bits; its first partner is then the
+// lowest bit of it that is no member's, one lane move brings that one's size, and a ballot says which members have a
+// partner with room: 300 cycles an exchange, and up to 850 for the masks of a batch.
+__device__ __forceinline__ bool exchange_in_lanes(int w, unsigned o, int count, int w_limit, int &slack, int &w_most, u64 &members,
+                                                  u64 &others)
+{
+    const unsigned less_lo = below<0>(o, count), less_hi = count > 32 ? below<32>(o, count - 32) : 0u;
+    while (w_most + slack < w_limit) {
+        const unsigned lo = less_lo & (unsigned)others, hi = less_hi & (unsigned)(others >> 32);
+        // (no bit: all ones, which is no lane)
+        const unsigned first_lo = lo != 0 ? (unsigned)__builtin_ctz(lo) : ~0u, first_hi = hi != 0 ? (unsigned)__builtin_ctz(hi) | 32u : ~0u;
+        const unsigned partner = min(first_lo, first_hi);
+        const int w_in = __builtin_amdgcn_ds_bpermute((int)(partner << 2), w);
+        const u64 has = __builtin_amdgcn_ballot_w64(w_in - w <= slack) & __builtin_amdgcn_ballot_w64((lo | hi) != 0) & members;
+        if (has == 0) return true;
+        const int a = __builtin_ctzll(has);
+        const int b = __builtin_amdgcn_readlane((int)partner, a), w_b = __builtin_amdgcn_readlane(w_in, a);
+        slack -= w_b - __builtin_amdgcn_readlane(w, a);
+        w_most = max(w_most, w_b);
+        const u64 both = 1ull << a | 1ull << b;
+        members ^= both;
+        others ^= both;
+    }
+    return false;
+}
+
+// The batch (members: v with the sign bit) goes to list[0..), in nondecreasing (o, id), and out of wk[0..m); returns its size.
+template <int RMAX>
+__device__ __forceinline__ int emit_batch(u64 *wk, int m, int R, const unsigned (&v)[RMAX], u64 *bkey, u64 *list)
+{
+    constexpr u64 LOW34 = (1ull << 34) - 1;  // (o, id) of a key
+    constexpr unsigned IN = 0x80000000u, NONE = 0x7fffffffu;
+    const int lane = lane_id();
+    // the batch in nondecreasing o, ties by id: rank of each member among the members
+    int nmem = 0;
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] >= IN);
+            put_b64(bal, bkey + nmem + rank_in(bal), wk[min(64 * r + lane, m - 1)]);
+            nmem += __popcll(bal);
+        }
+    }
+    if (nmem & 1) put_b64(1, bkey + nmem, ~0ull);  // (the loop below takes them two by two)
+    wave_sync();
+    for (int i0 = 0; i0 < nmem; i0 += 64) {
+        const u64 mine = bkey[min(i0 + lane, nmem - 1)];
+        const u64 me = mine & LOW34;
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < nmem; j += 2) rank += ((bkey[j] & LOW34) < me ? 1 : 0) + ((bkey[j + 1] & LOW34) < me ? 1 : 0);
+        put_b64(lanes_upto(nmem - i0), list + rank, mine);
+    }
+    wave_sync();
+    // what remains closes up in place, still sorted: row by row, each row read before it is
+    // written, and never written beyond itself
+    int kept = 0;
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        if (r < R) {
+            const u64 k = wk[min(64 * r + lane, m - 1)];
+            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < NONE);
+            wave_sync();
+            put_b64(bal, wk + kept + rank_in(bal), k);
+            kept += __popcll(bal);
+            wave_sync();
+        }
+    }
+    return nmem;
+}
+
 template <int RMAX>
 __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 *list, Batch &batch)
 {
-    constexpr u64 LOW34 = (1ull << 34) - 1;  // (o, id) of a key
     constexpr unsigned IN = 0x80000000u, NONE = 0x7fffffffu;
     constexpr int G = RMAX <= 2 ? 2 : 1;  // records tested at a time: what each waits for overlaps
     const int lane = lane_id();
@@ -283,6 +393,25 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         }
     }
 
+    // Mostly members and all that they could be exchanged for lie in the first row.
+    if (RMAX == 1 || K <= 64) {
+        const unsigned of = v[0] & ~IN;
+        u64 members = __builtin_amdgcn_ballot_w64(v[0] >= IN), others = __builtin_amdgcn_ballot_w64(v[0] < NONE);
+        const int reach = __popcll(__builtin_amdgcn_ballot_w64(w[0] <= w_most + slack) & (members | others));
+        const int behind = RMAX > 1 && m > 64 ? __builtin_amdgcn_readlane(w[RMAX > 1 ? 1 : 0], 0) : INT_MAX;  // the next row's first
+        bool none_left = false;
+        for (int count = max((reach + 7) & ~7, 8); !none_left && count <= 64; count = count < 64 ? 64 : 65)
+            none_left = exchange_in_lanes(w[0], of, count, count >= 64 ? behind : count < m ? __builtin_amdgcn_readlane(w[0], count & 63) : INT_MAX,
+                                          slack, w_most, members, others);
+        if constexpr (RMAX == 1) {
+            batch.o = __builtin_amdgcn_inverse_ballot_w64(members) ? of : NO_O;
+            batch.others = others;
+            return K;
+        }
+        v[0] = __builtin_amdgcn_inverse_ballot_w64(members) ? of | IN : of;
+        if (none_left) return emit_batch<RMAX>(wk, m, R, v, bkey, list);
+        o_most = __builtin_amdgcn_inverse_ballot_w64(members) ? of : 0u;  // (K <= 64: of all members)
+    }
     o_most = (unsigned)wave_max((int)o_most);
 
     for (;;) {  // one exchange per turn; every exchange lowers the batch's sum of o
@@ -373,48 +502,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         w_most = max(w_most, w_in);
     }
 
-    if (RMAX == 1) {
-        const u64 members = __builtin_amdgcn_ballot_w64(v[0] >= IN);
-        batch.o = v[0] >= IN ? v[0] & ~IN : NO_O;
-        batch.others = __builtin_amdgcn_ballot_w64(v[0] < NONE);
-        return __popcll(members);
-    }
-    // the batch in nondecreasing o, ties by id: rank of each member among the members
-    int nmem = 0;
-#pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-        if (r < R) {
-            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] >= IN);
-            put_b64(bal, bkey + nmem + rank_in(bal), wk[min(64 * r + lane, m - 1)]);
-            nmem += __popcll(bal);
-        }
-    }
-    if (nmem & 1) put_b64(1, bkey + nmem, ~0ull);  // (the loop below takes them two by two)
-    wave_sync();
-    for (int i0 = 0; i0 < nmem; i0 += 64) {
-        const u64 mine = bkey[min(i0 + lane, nmem - 1)];
-        const u64 me = mine & LOW34;
-        int rank = 0;
-#pragma unroll 4
-        for (int j = 0; j < nmem; j += 2) rank += ((bkey[j] & LOW34) < me ? 1 : 0) + ((bkey[j + 1] & LOW34) < me ? 1 : 0);
-        put_b64(lanes_upto(nmem - i0), list + rank, mine);
-    }
-    wave_sync();
-    // what remains closes up in place, still sorted: row by row, each row read before it is
-    // written, and never written beyond itself
-    int kept = 0;
-#pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-        if (r < R) {
-            const u64 k = wk[min(64 * r + lane, m - 1)];
-            const u64 bal = __builtin_amdgcn_ballot_w64(v[r] < NONE);
-            wave_sync();
-            put_b64(bal, wk + kept + rank_in(bal), k);
-            kept += __popcll(bal);
-            wave_sync();
-        }
-    }
-    return nmem;
+    return emit_batch<RMAX>(wk, m, R, v, bkey, list);
 }
 
 // ------------------------------------------------------------------------ the stream kernel
