@@ -222,6 +222,7 @@ struct Batch {
     u64 key;     // this lane's request of the window ...
     unsigned o;  // ... and its o while it is in the batch and has not been asked for (else NO_O)
     u64 others;  // the lanes whose requests are not in the batch
+    bool here;   // the batch is in the lanes (else in the list)
 };
 constexpr unsigned NO_O = 0x7fffffffu;
 
@@ -365,7 +366,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         if (r < R) {
             const bool is = 64 * r + lane < m;
             const u64 k = wk[min(64 * r + lane, m - 1)];
-            if (RMAX == 1) batch.key = k;
+            if (r == 0) batch.key = k;
             w[r] = is ? (int)(k >> 34) : 0;
             v[r] = is ? (unsigned)(k >> 20) & 0x3fffu : NONE;
         }
@@ -403,13 +404,13 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         for (int count = max((reach + 7) & ~7, 8); !none_left && count <= 64; count = count < 64 ? 64 : 65)
             none_left = exchange_in_lanes(w[0], of, count, count >= 64 ? behind : count < m ? __builtin_amdgcn_readlane(w[0], count & 63) : INT_MAX,
                                           slack, w_most, members, others);
-        if constexpr (RMAX == 1) {
+        if (RMAX == 1 || none_left) {
             batch.o = __builtin_amdgcn_inverse_ballot_w64(members) ? of : NO_O;
             batch.others = others;
+            batch.here = true;
             return K;
         }
         v[0] = __builtin_amdgcn_inverse_ballot_w64(members) ? of | IN : of;
-        if (none_left) return emit_batch<RMAX>(wk, m, R, v, bkey, list);
         o_most = __builtin_amdgcn_inverse_ballot_w64(members) ? of : 0u;  // (K <= 64: of all members)
     }
     o_most = (unsigned)wave_max((int)o_most);
@@ -502,6 +503,7 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
         w_most = max(w_most, w_in);
     }
 
+    batch.here = false;
     return emit_batch<RMAX>(wk, m, R, v, bkey, list);
 }
 
@@ -596,7 +598,8 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
     int known = 0, started = 0;
     int wn = 0, planned = 0;  // window of the last refresh, and how many of its entries are planned ...
     int listed = 0;           // ... and of these in list[0 ... listed); the others are still in `batch`
-    Batch batch = {0, NO_O, 0};
+    int rows = 0;             // lanes of it that hold a request of the window
+    Batch batch = {0, NO_O, 0, false};
     int t_plan = 0, backlog_at_plan = 0;
     u64 blocked = ~0ull;   // the last request that did not fit, and a round before which it cannot start
     int blocked_to = 0;
@@ -728,16 +731,23 @@ __global__ __launch_bounds__(64) void online_kernel(OnlineParams p)
             if (head + adm == planned && planned < wn) {
                 const int left = wn - planned;
                 u64 *from = L.wk;
-                if (planned == 0 && left <= 64) from = cur;  // (in the iteration of the refresh)
-                else if (planned > 0 && batch.others != 0)  // behind a batch in lanes
+                if (planned == 0) {
+                    if (left <= 64) from = cur;  // (in the iteration of the refresh)
+                } else if (batch.here) {  // what the batch has left in the lanes, and the rows behind, close up
                     put_b64(batch.others, L.wk + rank_in(batch.others), batch.key);
-                batch.others = 0;
-                if (left <= 64) planned += plan_batch<1>(from, left, M, oth, L.list + planned, batch);
-                else {
-                    planned += left <= 128 ? plan_batch<2>(L.wk, left, M, oth, L.list + planned, batch)
-                                           : plan_batch<Lds::WCAP / 64>(L.wk, left, M, oth, L.list + planned, batch);
-                    listed = planned;
+                    const int kept = __popcll(batch.others), gone = rows - kept;
+                    for (int i0 = rows; i0 < left + gone; i0 += 64) {
+                        const u64 k = L.wk[min(i0 + lane, left + gone - 1)];
+                        wave_sync();
+                        put_b64(lanes_upto(left + gone - i0), L.wk + i0 - gone + lane, k);
+                        wave_sync();
+                    }
                 }
+                rows = min(left, 64);
+                if (left <= 64) planned += plan_batch<1>(from, left, M, oth, L.list + planned, batch);
+                else planned += left <= 128 ? plan_batch<2>(L.wk, left, M, oth, L.list + planned, batch)
+                                            : plan_batch<Lds::WCAP / 64>(L.wk, left, M, oth, L.list + planned, batch);
+                if (!batch.here) listed = planned;
             }
             u64 key;
             if (head + adm == listed && listed < planned) {
