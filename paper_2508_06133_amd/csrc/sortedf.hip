@@ -26,7 +26,7 @@ namespace {
 constexpr int kRun = 2048;          // keys one workgroup sorts (1024 threads, two each)
 constexpr int kFan = 8;             // runs merged by one pass
 constexpr int kSmallSum = 1024, kSmallProfile = 128;  // requests that one workgroup takes (kvs_sortedF_small_max)
-constexpr int kCountMax = 12288;    // requests whose places are found by counting the keys before them
+constexpr int kCountMax = 16384;    // requests whose places are found by counting the keys before them
 constexpr int kSumsHere = 16384;    // requests up to which the prefix sums need no sums ahead
 constexpr int kOrderTile = 6144;    // keys held at a time when the places within batches are counted
 constexpr int kNextMax = 256;       // profile tests among the first so many requests are made by one wavefront
@@ -644,8 +644,9 @@ __device__ __forceinline__ void lengths_seen(const SortedArgs &p, bool bad, int 
 // requests, 64 / OWN lanes of each wavefront a request and a 16 OWN / 64-th of the keys each; so the whole chip works, where sorted runs of 2048 keys
 // keep five compute units busy and have to be merged.  The first launch of a call is its length scan too, as every workgroup reads all
 // lengths.  Bound by vector issue, 2.5 instructions a comparison of 64 pairs, in three
-// fifths of the compute units: 10000 requests 18.4 us where scan, sorted runs and merges took 28 (and two launches, for the order by
-// (o, id), that found nothing to do 8), 5000 7.5, 2000 6.
+// fifths of the compute units (all up to 16384): 10000 requests 18.4 us where scan, sorted runs and merges took 28 (and two launches, for the order by
+// (o, id), that found nothing to do 8), 5000 7.5, 2000 6; the whole construction of 16000 requests 102 -> 95.  (Keys of 32 bits, the
+// id told by the place in LDS and two instructions a comparison written out, took 17.6 to 18.6 for 10000.)
 template <int OWN>
 __global__ __launch_bounds__(1024) void count_places_kernel(SortedArgs p, LargeArrays m, int what, int scan, u64 *out)
 {
@@ -711,19 +712,27 @@ __global__ __launch_bounds__(1024) void count_places_kernel(SortedArgs p, LargeA
 // to the right the last's.  NARROW: the keys (o, id), or the ranks that stand for them, fit in 32 bits.
 template <bool NARROW>
 __device__ __forceinline__ void order_of_places(const SortedArgs &p, const LargeArrays &m, const u64 *by_place, int lo_all, int hi_all,
-                                                int lo, int hi, u64 *tile, int *count)
+                                                int lo, int hi, u64 own, u64 *tile, int *count)
 {
     typedef typename std::conditional<NARROW, unsigned, u64>::type Key;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n, first = 64 * blockIdx.x, i = min(first + lane, n - 1);
     const u64 low = p.packed ? field_mask(p.o_bits + p.id_bits) : field_mask(p.id_bits);
     Key *const keys = (Key *)tile;
-    const Key mine = (Key)(by_place[i] & low);
+    const Key mine = (Key)(own & low);
     const bool one = __builtin_amdgcn_ballot_w64(lo != lo_all || hi != hi_all) == 0;  // (one batch has all 64 places, mostly)
     unsigned c = 0;
     for (int j0 = lo_all; j0 < hi_all; j0 += kOrderTile) {
         const int held = min(kOrderTile, hi_all - j0), all = (held + 127) & ~127;
         __syncthreads();
-        for (int j = tid; j < all; j += 1024) keys[j] = j < held ? (Key)(by_place[j0 + j] & low) : ~(Key)0;
+        u64 x[kOrderTile / 1024];  // (a trip to memory together)
+#pragma unroll
+        for (int r = 0; r < kOrderTile / 1024; ++r)
+            if (1024 * r < all) x[r] = by_place[j0 + min(1024 * r + tid, held - 1)];
+#pragma unroll
+        for (int r = 0; r < kOrderTile / 1024; ++r) {
+            const int j = 1024 * r + tid;
+            if (j < all) keys[j] = j < held ? (Key)(x[r] & low) : ~(Key)0;
+        }
         __syncthreads();
         // (sixteen wavefronts, four keys each in turn)
         if (one) {
@@ -745,7 +754,7 @@ __device__ __forceinline__ void order_of_places(const SortedArgs &p, const Large
     atomicAdd(&count[lane], (int)c);
     __syncthreads();
     if (tid >= 64 || first + lane >= n) return;
-    const int v = (int)(by_place[i] & field_mask(p.id_bits));
+    const int v = (int)(own & field_mask(p.id_bits));
     p.order_out[lo + count[lane]] = p.packed ? v : m.by_o[v];
 }
 
@@ -753,28 +762,41 @@ __global__ __launch_bounds__(1024) void order_batches_kernel(SortedArgs p, Large
 {
     __shared__ __align__(16) u64 tile[kOrderTile];
     __shared__ int count[64], ends[64];
-    const int nb = *p.num_batches_out;
-    if (faulty(p) || nb < 1) return;
     const int tid = threadIdx.x, lane = tid & 63, n = p.n, first = 64 * blockIdx.x;
-    // the batch of the first place, by counting the ends before it, and the next 64 ends
-    int before = 0;
-    for (int b0 = 0; b0 < nb; b0 += 1024) before += __syncthreads_count(b0 + tid < nb && p.batch_end_out[min(b0 + tid, nb - 1)] <= first);
-    if (tid < 64) {
-        count[tid] = 0;
-        ends[tid] = p.batch_end_out[min(before + tid, nb - 1)];
-    }
-    __syncthreads();
     const int i = min(first + lane, n - 1), last = min(first + 63, n - 1);
-    int lo = before > 0 ? p.batch_end_out[before - 1] : 0, hi = ends[0];
-    const int lo_all = lo;
-    int hi_all = hi;
-    for (int b = 0; b < 63 && ends[b] <= last; ++b) {  // (the same in all lanes; at most 64 batches touch 64 places)
-        if (ends[b] <= i) lo = ends[b], hi = ends[b + 1];
-        hi_all = ends[b + 1];
+    const int nb = *p.num_batches_out;
+    const u64 own = by_place[i];
+    const int end = p.batch_end_out[lane];  // (n > 64)
+    if (faulty(p) || nb < 1) return;
+    if (tid < 64) count[tid] = 0;
+    int lo, hi, lo_all, hi_all;
+    if (nb <= 64) {  // (each end in a lane, read together with the rest: 5000 requests 10.8 -> 9.9 us, 1100 5.8 -> 5.2)
+        const u64 there = ~0ull >> (64 - nb);
+        int b = __popcll(__builtin_amdgcn_ballot_w64(end <= first) & there);
+        lo = lo_all = b > 0 ? __builtin_amdgcn_readlane(end, max(b - 1, 0)) : 0;
+        hi = hi_all = __builtin_amdgcn_readlane(end, b);
+        while (hi_all <= last && b + 1 < nb) {
+            const int next = __builtin_amdgcn_readlane(end, ++b);
+            if (hi_all <= i) lo = hi_all, hi = next;
+            hi_all = next;
+        }
+        __syncthreads();
+    } else {
+        // the batch of the first place, by counting the ends before it, and the next 64 ends
+        int before = 0;
+        for (int b0 = 0; b0 < nb; b0 += 1024) before += __syncthreads_count(b0 + tid < nb && p.batch_end_out[min(b0 + tid, nb - 1)] <= first);
+        if (tid < 64) ends[tid] = p.batch_end_out[min(before + tid, nb - 1)];
+        __syncthreads();
+        lo = lo_all = before > 0 ? p.batch_end_out[before - 1] : 0;
+        hi = hi_all = ends[0];
+        for (int b = 0; b < 63 && ends[b] <= last; ++b) {  // (the same in all lanes; at most 64 batches touch 64 places)
+            if (ends[b] <= i) lo = ends[b], hi = ends[b + 1];
+            hi_all = ends[b + 1];
+        }
     }
     const int bits = p.packed ? 32 - __builtin_clz(max(p.words[KVS_W_OMAX], 1)) + p.id_bits : p.id_bits;
-    if (bits < 32) order_of_places<true>(p, m, by_place, lo_all, hi_all, lo, hi, tile, count);
-    else order_of_places<false>(p, m, by_place, lo_all, hi_all, lo, hi, tile, count);
+    if (bits < 32) order_of_places<true>(p, m, by_place, lo_all, hi_all, lo, hi, own, tile, count);
+    else order_of_places<false>(p, m, by_place, lo_all, hi_all, lo, hi, own, tile, count);
 }
 
 // ------------------------------------------------ beyond: sorted runs and merges
