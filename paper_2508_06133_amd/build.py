@@ -38,7 +38,7 @@ DEVICE_FLAGS = [
 # predicted_reg_kernel 5.9 ms without, 5.1 with it; predicted_ring_kernel, whose passes over the ring do branch by the lane, has it too);
 # elsewhere it makes no difference.
 UNIFORM_BRANCHES = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
-SOURCE_FLAGS = {"predicted.hip": UNIFORM_BRANCHES, "online.hip": UNIFORM_BRANCHES, "eventrows.hip": UNIFORM_BRANCHES}
+SOURCE_FLAGS = {name: UNIFORM_BRANCHES for name in ("localswap.hip", "predicted.hip", "online.hip", "eventrows.hip")}
 FLAGS = DEVICE_FLAGS + ["-fPIC", "-Wall"]
 RESERVED_VGPR_BASE = 30  # KVS_PB in timeline_reg.hip
 PREDICTED_VGPR_BASE = 60  # KVP_PB in predicted.hip

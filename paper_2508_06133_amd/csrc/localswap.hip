@@ -713,15 +713,20 @@ __global__ __launch_bounds__(LS_T) void local_swap_kernel(int32_t n, const int32
 // before it, three counts of n comparisons each, which the whole chip shares (2000 requests: 125
 // workgroups; the radix passes that one workgroup made took 95 us).
 //
-// What a step costs is the latency of its chain of dependent operations, not their number.  Up to
+// What a step costs is its chain of dependent operations and, to a lone wavefront, some 7 cycles an instruction.  Up to
 // 1024 places it is therefore the work of ONE wavefront, without a barrier: lane l holds places E l ...
-// E l + E - 1 of the arrangement in registers.  Cycles per exchange, 4 / 8 / 16 places per lane: 710 / 1040 / 1700; by
-// eight wavefronts with four barriers, 4 / 16 places per lane: 2250 / 3650 (so 1024 places are the line:
+// E l + E - 1 of the arrangement in registers, and which of them are members in the bits of one more.  Cycles per
+// exchange, 2 / 4 / 8 / 16 places per lane: 700 / 800 / 1050 / 1700 (with a flag put into two of the registers for each exchange, the
+// lanes looked up with a case for none, and the last member's place kept up: 4 / 8 / 16 places 880 / 1150 / 1880); by
+// eight wavefronts with four barriers, 4 / 16 places per lane: 2100 / 4000 (so 1024 places are the line:
 // with 2 places per lane the workgroup takes 2290).  The rest of the workgroup takes part between the exchanges
 // (greedy fill, table of ub(), closing up: three microseconds per batch) and writes the batch before out
 // during them.
-// 2000 requests, 29 batches, 769 exchanges: 1073 -> 410 us; 8000 requests, 6 batches, 1151 exchanges over up to
-// 6000 places: 4.0 -> 1.5 ms.
+// 2000 mixed requests, 31 batches, 848 exchanges: 460 -> 427 us a call; 8000 chat requests, 8 batches, 1720 exchanges over up to
+// 6000 places: 1.99 -> 1.83 ms; 600 mixed ones 217 -> 193.
+// A bound for each member on its partner's size instead of the table, kept up with every exchange, is no gain: the exchange takes as many
+// instructions, and a fifth to a third of the members that a bound does not rule out have no partner after all (2000 mixed
+// requests 506 us; 64 places, a lane each, no difference).
 
 constexpr int LSR_N = 8192;
 constexpr int LSR_T = 512;  // threads of the workgroup
@@ -846,57 +851,62 @@ struct alignas(16) RankedLds {
     unsigned wave_sum[LSR_NW];
     unsigned wave_top[LSR_NW];
     unsigned wave_min[LSR_NW];
-    u64 first_out[2];                // alternating slots: place << 32 | word of the first member that has a partner
-    u64 first_in[2];                 //                    the same of its partner
+    unsigned out[LSR_NW], in[LSR_NW];  // each wavefront's first member that has a partner, and first one of a smaller value
     int fill_end, fill_mem, fill_w;
-    int slack, hi, w_hi, swaps, done;
+    int slack, w_hi, swaps, done;
+    int hi;                          // no member lies behind this place, from the batch's first group of eight on
     u64 S;                           // sum of values of the batch that is written out
     int parts;                       // wavefronts that have added theirs
 };
 
-// x = from[e] of the least e with a[e] < b[e] (x if there is none), and from[at] = x: written out because a
+// x = from[e] of the least e with a[e] < b[e], or with from[e] < below (x if there is none): written out because a
 // comparison's mask may be read only two instructions later, and the compiler fills the gap with idle ones
 // when it takes one mask at a time (an exchange of four places per lane: 942 -> 740 cycles).
 template <int E>
-__device__ __forceinline__ void first_below(unsigned &x, const unsigned (&a)[E], const unsigned (&b)[E],
-                                            const unsigned (&from)[E])
+__device__ __forceinline__ void first_less(unsigned &x, const unsigned (&a)[E], const unsigned (&b)[E])
 {
+    u64 m0, m1, m2, m3;
     if constexpr (E == 2) {
-        const bool is0 = a[0] < b[0], is1 = a[1] < b[1];
-        x = is0 ? from[0] : is1 ? from[1] : x;
+        asm("v_cmp_lt_u32 %2, %4, %6\n\tv_cmp_lt_u32 %1, %3, %5\n\ts_nop 0\n\tv_cndmask_b32 %0, %0, %6, %2\n\tv_cndmask_b32 %0, %0, %5, %1"
+            : "+&v"(x), "=&s"(m0), "=&s"(m1) : "v"(a[0]), "v"(a[1]), "v"(b[0]), "v"(b[1]));
     } else {
-        u64 m0, m1, m2, m3;
 #pragma unroll
         for (int e = E - 4; e >= 0; e -= 4)
             asm("v_cmp_lt_u32 %4, %8, %12\n\tv_cmp_lt_u32 %3, %7, %11\n\tv_cmp_lt_u32 %2, %6, %10\n\tv_cmp_lt_u32 %1, %5, %9\n\t"
-                "v_cndmask_b32 %0, %0, %16, %4\n\tv_cndmask_b32 %0, %0, %15, %3\n\tv_cndmask_b32 %0, %0, %14, %2\n\tv_cndmask_b32 %0, %0, %13, %1"
+                "v_cndmask_b32 %0, %0, %12, %4\n\tv_cndmask_b32 %0, %0, %11, %3\n\tv_cndmask_b32 %0, %0, %10, %2\n\tv_cndmask_b32 %0, %0, %9, %1"
                 : "+&v"(x), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-                : "v"(a[e]), "v"(a[e + 1]), "v"(a[e + 2]), "v"(a[e + 3]), "v"(b[e]), "v"(b[e + 1]), "v"(b[e + 2]), "v"(b[e + 3]),
-                  "v"(from[e]), "v"(from[e + 1]), "v"(from[e + 2]), "v"(from[e + 3]));
+                : "v"(a[e]), "v"(a[e + 1]), "v"(a[e + 2]), "v"(a[e + 3]), "v"(b[e]), "v"(b[e + 1]), "v"(b[e + 2]), "v"(b[e + 3]));
     }
 }
 
 template <int E>
-__device__ __forceinline__ void put(unsigned (&to)[E], int at, unsigned x)
+__device__ __forceinline__ void first_below(unsigned &x, unsigned below, const unsigned (&from)[E])
 {
+    u64 m0, m1, m2, m3;
     if constexpr (E == 2) {
-        const bool is0 = at == 0, is1 = at == 1;
-        to[0] = is0 ? x : to[0];
-        to[1] = is1 ? x : to[1];
+        asm("v_cmp_gt_u32 %2, %3, %5\n\tv_cmp_gt_u32 %1, %3, %4\n\ts_nop 0\n\tv_cndmask_b32 %0, %0, %5, %2\n\tv_cndmask_b32 %0, %0, %4, %1"
+            : "+&v"(x), "=&s"(m0), "=&s"(m1) : "s"(below), "v"(from[0]), "v"(from[1]));
     } else {
-        u64 m0, m1, m2, m3;
 #pragma unroll
-        for (int e = 0; e < E; e += 4)
-            asm("v_cmp_eq_u32 %4, %8, %9\n\tv_cmp_eq_u32 %5, %8, %10\n\tv_cmp_eq_u32 %6, %8, %11\n\tv_cmp_eq_u32 %7, %8, %12\n\t"
-                "v_cndmask_b32 %0, %0, %13, %4\n\tv_cndmask_b32 %1, %1, %13, %5\n\tv_cndmask_b32 %2, %2, %13, %6\n\tv_cndmask_b32 %3, %3, %13, %7"
-                : "+&v"(to[e]), "+&v"(to[e + 1]), "+&v"(to[e + 2]), "+&v"(to[e + 3]), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-                : "v"(at), "n"(e), "n"(e + 1), "n"(e + 2), "n"(e + 3), "v"(x));
+        for (int e = E - 4; e >= 0; e -= 4)
+            asm("v_cmp_gt_u32 %4, %5, %9\n\tv_cmp_gt_u32 %3, %5, %8\n\tv_cmp_gt_u32 %2, %5, %7\n\tv_cmp_gt_u32 %1, %5, %6\n\t"
+                "v_cndmask_b32 %0, %0, %9, %4\n\tv_cndmask_b32 %0, %0, %8, %3\n\tv_cndmask_b32 %0, %0, %7, %2\n\tv_cndmask_b32 %0, %0, %6, %1"
+                : "+&v"(x), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+                : "s"(below), "v"(from[e]), "v"(from[e + 1]), "v"(from[e + 2]), "v"(from[e + 3]));
     }
+}
+
+// The lowest lane of a mask (some lane, if there is none).
+__device__ __forceinline__ int first_lane(u64 mask)
+{
+    int l;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(l) : "s"(mask));
+    return l & 63;
 }
 
 // State of a batch's exchanges, the same in every thread.  Places count from the batch's first group of eight.
 struct RankedState {
-    int slack, hi, w_hi, swaps;
+    int slack, w_hi, swaps;  // (w_hi: no member is larger)
 };
 
 // Exchanges of one batch while no place from NW 64 E - 1 on can fit, by NW wavefronts (1: without
@@ -923,22 +933,18 @@ __device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_
         w2[e] = 2 * size_of(v[e]);
         v[e] |= (unsigned)e | ((q + e >= fill_from && q + e < fill_to) ? LSR_IN : 0u);
     }
+    unsigned in = 0;  // which of them are members, the first one highest
+#pragma unroll
+    for (int e = 0; e < E; ++e) in |= (v[e] & LSR_IN) >> e;
     // no place from PLACES - 1 on fits against a member while w_hi + slack stays below this
     const int w_limit = n - p0 < PLACES ? LS_INF : __builtin_amdgcn_readfirstlane(size_of(L.word[p0 + PLACES - 1]));
-    int slack = __builtin_amdgcn_readfirstlane(st.slack), hi = __builtin_amdgcn_readfirstlane(st.hi);
-    int w_hi = __builtin_amdgcn_readfirstlane(st.w_hi), swaps = __builtin_amdgcn_readfirstlane(st.swaps);
+    int slack = __builtin_amdgcn_readfirstlane(st.slack), w_hi = __builtin_amdgcn_readfirstlane(st.w_hi);
+    int swaps = __builtin_amdgcn_readfirstlane(st.swaps);
     bool done = false;
-    if (NW > 1) {
-        if (threadIdx.x < 2) L.first_out[threadIdx.x] = L.first_in[threadIdx.x] = LS_NO_KEY;
-        __syncthreads();
-    }
-    for (int it = 0;; ++it) {
-        const int slot = it & 1;
-        if (w_hi + slack >= w_limit) break;  // uniform
-
+    while (w_hi + slack < w_limit) {
         // ---- how far each place would reach as a member (what non-members find is never used)
         unsigned p[E];
-        const bool members = NW == 1 || wave * 64 * E < hi;  // (a wavefront behind all members looks nothing up)
+        const bool members = NW == 1 || __builtin_amdgcn_ballot_w64(in != 0) != 0;  // (without members nothing is looked up)
         if (members) {
             const int reach = 2 * min(slack, w_last), top = 2 * w_last;
 #pragma unroll
@@ -965,7 +971,7 @@ __device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_
             unsigned two[E / 2];
 #pragma unroll
             for (int e = 0; e < E; e += 2)
-                two[e / 2] = __builtin_amdgcn_perm(min(pm[e + 1], before), min(pm[e], before), 0x07060302);
+                two[e / 2] = __builtin_amdgcn_perm(min(pm[e + 1], before), e == 0 ? before : min(pm[e], before), 0x07060302);
 #pragma unroll
             for (int e = 0; e < E / 2; ++e) to[e] = two[e];
         }
@@ -977,63 +983,55 @@ __device__ __forceinline__ bool ranked_steps(RankedLds &L, int p0, int n, int w_
 #pragma unroll
             for (int e = 0; e < E; ++e)
                 p[e] = *reinterpret_cast<const any_u16 *>(reinterpret_cast<const char *>(L.pm) + p[e]) << 16 | (LSR_IN | LSR_REST);
-            first_below<E>(x_a, p, v, v);
+            first_less<E>(x_a, p, v);
         }
-        int a, b, l_a = 0;
-        u64 have = __builtin_amdgcn_ballot_w64(x_a != 0);
-        if (NW == 1) {
-            l_a = (__ffsll((long long)have) - 1) & 63;  // (any lane if there is none: the loop ends below)
-            x_a = (unsigned)__builtin_amdgcn_readlane((int)x_a, l_a);
-        } else {
-            if (have != 0) {
-                const int l = (int)__builtin_ctzll(have);
-                const unsigned x = (unsigned)__builtin_amdgcn_readlane((int)x_a, l);
-                if (lane == 0) atomicMin(&L.first_out[slot], (u64)((unsigned)(wave * 64 + l) * E + (x & 15)) << 32 | x);
-            }
+        int l_a = first_lane(__builtin_amdgcn_ballot_w64(x_a != 0)), l_b;  // their lanes, elsewhere none
+        x_a = (unsigned)__builtin_amdgcn_readlane((int)x_a, l_a);
+        if (NW > 1) {
+            if (lane == 0) L.out[wave] = x_a;  // (0: none)
             __syncthreads();
-            const u64 k = L.first_out[slot];
-            x_a = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)k);
-            a = __builtin_amdgcn_readfirstlane((int)(k >> 32));
-            have = x_a != ~0u;
+            const unsigned each = L.out[lane & (NW - 1)];
+            const int u = first_lane(__builtin_amdgcn_ballot_w64(each != 0));
+            x_a = (unsigned)__builtin_amdgcn_readlane((int)each, u);
+            l_a = u == wave ? l_a : 64;
+        }
+        if (x_a == 0) {  // none left
+            done = true;
+            break;
         }
 
         // ---- its partner: the first non-member of a smaller value
-        unsigned below[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) below[e] = x_a & LSR_VALUE;
-        first_below<E>(x_b, v, below, v);
-        u64 found;
-        if (NW == 1) {
-            a = l_a * E + (int)(x_a & 15);
-            found = __builtin_amdgcn_ballot_w64(x_b != ~0u);
-            const int l = (__ffsll((long long)found) - 1) & 63;
-            x_b = (unsigned)__builtin_amdgcn_readlane((int)x_b, l);
-            b = l * E + (int)(x_b & 15);
-        } else {
-            if (have != 0 && x_b != ~0u && before >= below[0]) L.first_in[slot] = (u64)(unsigned)(q + (int)(x_b & 15)) << 32 | x_b;
+        first_below<E>(x_b, x_a & LSR_VALUE, v);
+        l_b = first_lane(__builtin_amdgcn_ballot_w64(x_b != ~0u));
+        x_b = (unsigned)__builtin_amdgcn_readlane((int)x_b, l_b);
+        if (NW > 1) {
+            if (lane == 0) L.in[wave] = x_b;  // (~0: none)
             __syncthreads();
-            const u64 k = L.first_in[slot];
-            x_b = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)k);
-            b = __builtin_amdgcn_readfirstlane((int)(k >> 32));
-            found = x_b != ~0u;
+            const unsigned each = L.in[lane & (NW - 1)];
+            const int u = first_lane(__builtin_amdgcn_ballot_w64(each != ~0u));
+            x_b = (unsigned)__builtin_amdgcn_readlane((int)each, u);
+            l_b = u == wave ? l_b : 64;
         }
-        if (have == 0 || found == 0) { done = true; break; }  // none left (a partner was seen if have != 0)
 
         // ---- exchange
         const int w_b = size_of(x_b);
         slack -= w_b - size_of(x_a);
-        if (b >= hi) { hi = b + 1; w_hi = w_b; }
+        w_hi = max(w_hi, w_b);
         ++swaps;
-        put<E>(v, a - q, x_a ^ LSR_IN);
-        put<E>(v, b - q, x_b ^ LSR_IN);
-        if (NW > 1 && threadIdx.x == 0)  // the other slot was last read two barriers ago; ready it for the next step
-            L.first_out[slot ^ 1] = L.first_in[slot ^ 1] = LS_NO_KEY;
+        in ^= lane == l_a ? LSR_IN >> (x_a & 15) : 0u;
+        in ^= lane == l_b ? LSR_IN >> (x_b & 15) : 0u;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const unsigned up = in << e;
+            asm("v_bfi_b32 %0, %1, %0, %2" : "+v"(v[e]) : "s"(~LSR_IN), "v"(up));
+        }
     }
 #pragma unroll
     for (int e = 0; e < E; e += 2)
         if (p0 + q + e < LSR_N) *reinterpret_cast<any_u32x2 *>(&L.word[p0 + q + e]) = any_u32x2{v[e] & ~15u, v[e + 1] & ~15u};
+    const u64 with = __builtin_amdgcn_ballot_w64(in != 0);  // lanes with members
+    if (with != 0 && lane == 63 - __clzll((long long)with)) atomicMax(&L.hi, q + 33 - __ffs((int)in));
     st.slack = slack;
-    st.hi = hi;
     st.w_hi = w_hi;
     st.swaps = swaps;
     return done;
@@ -1119,10 +1117,13 @@ __device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const Ran
         if (tid == 0) {
             L.S = 0;
             L.parts = 0;
+            L.hi = 0;
         }
         const int w_last = __builtin_amdgcn_readfirstlane(size_of(L.word[n - 1]));
-        const int rows = (w_last >> 9) + 1, per = (rows + LSR_NW - 1) / LSR_NW;  // rows of 512 entries, eight per lane
-        const int r0 = wave * per, r1 = min(rows, r0 + per);
+        // (rows of 512 entries, eight per lane, from the first size on)
+        const int first_row = __builtin_amdgcn_readfirstlane(size_of(L.word[a])) >> 9;
+        const int rows = (w_last >> 9) + 1, per = (rows - first_row + LSR_NW - 1) / LSR_NW;
+        const int r0 = first_row + wave * per, r1 = min(rows, r0 + per);
         __syncthreads();
         unsigned h[ROWS][8], top = 0;
 #pragma unroll
@@ -1183,16 +1184,14 @@ __device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const Ran
             }
         }
         RankedState st;
-        st.hi = __builtin_amdgcn_readfirstlane(L.fill_end);
         st.slack = M - __builtin_amdgcn_readfirstlane(L.fill_mem);
         st.w_hi = __builtin_amdgcn_readfirstlane(L.fill_w);
         st.swaps = 0;
-        const int K = st.hi - a;
+        const int K = __builtin_amdgcn_readfirstlane(L.fill_end) - a;
         if (K < 1) {  // cannot happen for well-formed input; never spin
             if (tid == 0) atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
             break;
         }
-        st.hi -= p0;
         __syncthreads();
 
         // ---- exchanges; meanwhile the batch before is written out
@@ -1204,12 +1203,12 @@ __device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const Ran
             bool done = false;
             if (U < 1024) {
                 if (wave == 0) {
-                    done = U < 256   ? ranked_steps<1, 4>(L, p0, n, w_last, from, to, st)
+                    done = U < 128   ? ranked_steps<1, 2>(L, p0, n, w_last, from, to, st)
+                           : U < 256 ? ranked_steps<1, 4>(L, p0, n, w_last, from, to, st)
                            : U < 512 ? ranked_steps<1, 8>(L, p0, n, w_last, from, to, st)
                                      : ranked_steps<1, 16>(L, p0, n, w_last, from, to, st);
                     if (lane == 0) {
                         L.slack = st.slack;
-                        L.hi = st.hi;
                         L.w_hi = st.w_hi;
                         L.swaps = st.swaps;
                         L.done = done;
@@ -1218,7 +1217,6 @@ __device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const Ran
                 emitted = true;
                 __syncthreads();
                 st.slack = __builtin_amdgcn_readfirstlane(L.slack);
-                st.hi = __builtin_amdgcn_readfirstlane(L.hi);
                 st.w_hi = __builtin_amdgcn_readfirstlane(L.w_hi);
                 st.swaps = __builtin_amdgcn_readfirstlane(L.swaps);
                 done = __builtin_amdgcn_readfirstlane(L.done) != 0;
@@ -1234,7 +1232,7 @@ __device__ int ranked_construction(RankedLds &L, int n, int M, int gb, const Ran
             batch_end_out[nb] = a + K;
             if (swaps_out) swaps_out[nb] = st.swaps;
         }
-        const int hi = p0 + st.hi;
+        const int hi = all ? n : p0 + L.hi;
 
         // ---- members leave; non-members of [a, hi) close up behind the K removed places.  The table is zeroed.
         unsigned x[OWN][4];
