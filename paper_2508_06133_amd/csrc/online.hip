@@ -31,8 +31,9 @@
 //     a time and ends in one ballot;
 //   * the look-ahead window of the Sorted-F-Online planner: Phase 1 of Algorithm 1 with Local
 //     Swap Search batches, sorted place 64 r + lane in row r of the lane's registers (greedy fill
-//     = longest prefix by a saturating wave scan; an exchange step = exclusive prefix minimum of
-//     o over non-members, and its records against all members at once).
+//     = longest prefix by a saturating wave scan; an exchange step = each member's first partner from a
+//     mask of who has less o, or, beyond 64 requests, the records of the prefix minimum of o over non-members
+//     against all members at once).
 #include "kvsched_internal.h"
 #include "lane_mask.h"
 #include "phase1_util.h"
@@ -205,19 +206,21 @@ __device__ __forceinline__ int rank_in(u64 mask)
 // all that has not been asked for is planned anew (in the paper's setting twenty to thirty batches, of which
 // admission looks at one or two: 600 streams of it, 23.0 -> 4.9 ms).
 //
-// The exchanges work from registers alone: the first non-member with a smaller o than a member's is always a
+// Mostly the members and all that they could be exchanged for are the window's first 64 requests, a lane each: exchange_in_lanes makes the
+// exchanges there from masks of who has less o than whom, and the batch stays in the lanes (`batch`): admission takes one or two
+// requests of a batch before the next refresh, so the batch is not sorted but the least (o, id) looked for when it is asked for,
+// and wk is closed up when a next batch is.  (The listed grid of 600 streams 1.72 -> 1.45 ms with masks instead of records, below, and
+// 1.41 with the batches of windows beyond 64 requests in the lanes too.)
+//
+// Beyond, all rows of the window take part, from registers alone: the first non-member with a smaller o than a member's is always a
 // record, a non-member with less o than every non-member before it, and of some fifty requests four or five
 // are, most of which are too large for every member or have more o than any.  A member has a partner iff a record that
-// still fits has less o than it, so all members are tested against one record after the other (a prefix minimum in LDS with a binary search per member took three times as long).
+// still fits has less o than it, so all members are tested against one record after the other (a prefix minimum in LDS with a binary search per
+// member took three times as long).  An exchange on two rows takes 1250 cycles so.
 //
-// plan_batch chooses the next batch among wk[0..m), removes it there and writes it to list[0..K); returns K.
-// bkey: an idle array of >= m keys, an even number.  With one row the batch stays where it is, in the lanes (`batch`): admission
-// mostly takes one or two requests of a batch before the next refresh, so the batch is not sorted but the least (o, id) looked for
-// when it is asked for, and wk is closed up when a next batch is.
-// m <= 64 RMAX.  One and two rows, where the paper's backlogs fit, keep the whole state in scalar and vector registers
-// without a test per row: an exchange on one row takes 960 cycles, on two 1250 (a longest stream of 457 requests has 1580 of them;
-// 600 streams 2.75 -> 2.56 ms with a variant of its own for one row).  They are a chain of moves between lanes, scalars
-// and masks, ten cycles an instruction: four records at a time or masks in place of the vector minima are slower.
+// plan_batch chooses the next batch among wk[0..m); it is in the lanes or, removed from wk, in list[0..K).  Returns K.
+// bkey: an idle array of >= m keys, an even number.  m <= 64 RMAX.  One and two rows, where the paper's backlogs fit, keep the whole state
+// in scalar and vector registers without a test per row.
 struct Batch {
     u64 key;     // this lane's request of the window ...
     unsigned o;  // ... and its o while it is in the batch and has not been asked for (else NO_O)
