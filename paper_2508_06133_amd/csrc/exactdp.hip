@@ -31,7 +31,6 @@ namespace {
 
 constexpr int DP_T = 1024;  // threads of the single-workgroup helper kernels
 constexpr int DP_NW = DP_T / 64;
-constexpr int DP_INF = 0x7fffffff;        // (one-workgroup kernel)
 constexpr unsigned DP_NONE = 0x80000000u; // no set: above every value (< 2^31), and still below 2^32 with one more added
 constexpr int DP_STEP_T = 256;
 constexpr int DP_STEP_M = 512;            // loads per workgroup of a step launch, two per thread
@@ -307,14 +306,16 @@ __device__ void reduce_best(int32_t tie_rule, HelperLds &L, long long &bS, int &
     __syncthreads();  // the reduction slots may still be read from an earlier call
     if (lane == 0) { L.red_S[wave] = bS; L.red_k[wave] = bk; L.red_m[wave] = bm; }
     __syncthreads();
-    if (tid == 0) {
-        for (int v = 1; v < DP_NW; ++v)
-            if (dp_better(L.red_S[v], L.red_k[v], L.red_m[v], bS, bk, bm, tie_rule)) {
-                bS = L.red_S[v]; bk = L.red_k[v]; bm = L.red_m[v];
-            }
-        L.red_S[0] = bS;
-        L.red_k[0] = bk;
-        L.red_m[0] = bm;
+    if (wave == 0) {  // (a total order)
+        bS = L.red_S[lane & (DP_NW - 1)];
+        bk = L.red_k[lane & (DP_NW - 1)];
+        bm = L.red_m[lane & (DP_NW - 1)];
+        for (int d = DP_NW / 2; d > 0; d >>= 1) {
+            const long long oS = __shfl_xor(bS, d);
+            const int ok = __shfl_xor(bk, d), om = __shfl_xor(bm, d);
+            if (dp_better(oS, ok, om, bS, bk, bm, tie_rule)) { bS = oS; bk = ok; bm = om; }
+        }
+        if (lane == 0) { L.red_S[0] = bS; L.red_k[0] = bk; L.red_m[0] = bm; }
     }
     __syncthreads();
     bS = L.red_S[0];
@@ -322,21 +323,17 @@ __device__ void reduce_best(int32_t tie_rule, HelperLds &L, long long &bS, int &
     bm = L.red_m[0];
 }
 
-// Best final state among rows k_first, k_first + k_step, ... <= kmax of a table (global or LDS);
-// every thread receives it (bk = 0: none).
-template <class TablePtr>
-__device__ void argmin_body(TablePtr dp, int k_first, int k_step, int kmax, int32_t M, int Mp, int32_t tie_rule,
-                            HelperLds &L, long long &bS, int &bk, int &bm)
+// Best final state among rows 1 ... kmax of a table of rows of 2^lg loads; every thread receives it (bk = 0: none).
+__device__ void argmin_body(const unsigned *dp, int kmax, int32_t M, int lg, int32_t tie_rule, HelperLds &L, long long &bS, int &bk,
+                            int &bm)
 {
-    const int tid = threadIdx.x;
     bS = 0;
     bk = 0;
     bm = 0;
-    for (int k = k_first; k <= kmax; k += k_step) {
-        for (int m = tid; m <= M; m += DP_T) {
-            const int v = dp[(size_t)k * Mp + m];
-            if (v != DP_INF && dp_better(v, k, m, bS, bk, bm, tie_rule)) { bS = v; bk = k; bm = m; }
-        }
+    for (int i = threadIdx.x; i < kmax << lg; i += DP_T) {
+        const int k = 1 + (i >> lg), m = i & ((1 << lg) - 1);
+        const unsigned v = dp[i + (1 << lg)];
+        if (m <= M && v != DP_NONE && dp_better(v, k, m, bS, bk, bm, tie_rule)) { bS = v; bk = k; bm = m; }
     }
     reduce_best(tie_rule, L, bS, bk, bm);
 }
@@ -1142,9 +1139,37 @@ __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long lon
 // for: about a hundred requests, M of a few hundred to a few thousand): no launch per request and
 // no host round trip per batch.  Row length Mp = 2^lg >= M + 1; the records still go to global
 // memory.  Same arithmetic and the same order of updates as the kernels above.
+//
+// Bound by the instructions of one compute unit, whose sixteen wavefronts take 64 states a turn: so two requests are offered at a
+// time (four states read, one written, for each state; four requests would read sixteen), a wavefront's row and part of it
+// are scalars that step from turn to turn, only parts that hold loads up to M are visited, and a turn's records wait in a lane each
+// until the step's end, where one store takes all.  The barrier of a step is for LDS alone.  1620 cycles for two requests of 30 rows
+// of 101 loads (2320 with one request a step, every state computing its place); of a batch of 105 requests the walk back takes a
+// third as long as all steps, the best state and the lists 9 % each.  200 requests of lengths up to 8, M = 100 1303 -> 995 us; 100 of
+// them 382 -> 300, under the profile 423 -> 369; 60 176 -> 142 and 179 -> 157; 30, M = 60 94 -> 85.
 constexpr int DP_SMALL_STATES = 12288;  // (kmax + 1) * Mp at most; two int tables = 96 KB of LDS
 constexpr int DP_SMALL_N = 1024;
+static_assert(DP_SMALL_STATES / 64 <= 64 * DP_NW, "a lane per turn");
 
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// A barrier for what is in LDS alone: the records on their way to memory are not waited for.
+__device__ __forceinline__ void tables_written() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Lane l of the four becomes a's and b's halves (the same in all lanes; M0 and one scalar are what the instruction takes, two
+// instructions after a vector instruction has written it).
+__device__ __forceinline__ void keep(unsigned (&to)[4], unsigned long long a, unsigned long long b, int l)
+{
+    asm("s_mov_b32 m0, %8\n\ts_nop 1\n\tv_writelane_b32 %0, %4, m0\n\tv_writelane_b32 %1, %5, m0\n\t"
+        "v_writelane_b32 %2, %6, m0\n\tv_writelane_b32 %3, %7, m0"
+        : "+v"(to[0]), "+v"(to[1]), "+v"(to[2]), "+v"(to[3])
+        : "s"((unsigned)a), "s"((unsigned)(a >> 32)), "s"((unsigned)b), "s"((unsigned)(b >> 32)), "s"(l)
+        : "m0");
+}
+
+typedef __attribute__((address_space(3))) const unsigned lds_word;
+
+template <bool PROFILE>
 __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
                                                         int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int lg, int *proc, int *by_o,
                                                         int *by_cost, int *buf0, int *buf1, int *batch_of,
@@ -1153,24 +1178,27 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
                                                         int32_t *words)
 {
     __shared__ HelperLds L;
-    __shared__ int tab[2][DP_SMALL_STATES];
+    __shared__ unsigned tab[2][DP_SMALL_STATES + 1];  // (the last entry says "no set")
     __shared__ int req_o[DP_SMALL_N], req_load[DP_SMALL_N], req_g[DP_SMALL_N];
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int Mp = 1 << lg;
     int kmax = prepare_body(n, s, o, M, feas_mode, proc, by_o, by_cost, buf0, buf1, batch_of, words, num_batches_out, L);
     if (kmax < 0) return;
     int r = n, nb = 0;
     while (r > 0) {
+        kmax = uniform(kmax);
+        r = uniform(r);
         if (((kmax + 1) << lg) > DP_SMALL_STATES) {  // excluded by the host's choice of this kernel
             if (tid == 0) atomicOr(&words[KVS_W_STATUS], KVSCHED_DEV_BAD_LENGTH);
             break;
         }
         const int states = (kmax + 1) << lg;
         for (int i = tid; i < states; i += DP_T) {
-            const int v = i == 0 ? 0 : DP_INF;
+            const unsigned v = i == 0 ? 0 : DP_NONE;
             tab[0][i] = v;
             tab[1][i] = v;
         }
+        if (tid < 2) tab[tid][DP_SMALL_STATES] = DP_NONE;
         for (int t = tid; t < r; t += DP_T) {
             const int id = proc[t];
             req_o[t] = o[id];
@@ -1179,36 +1207,58 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
         }
         __syncthreads();
         const size_t per_t = (size_t)(kmax + 1) << (lg - 6);
-        for (int t = 0; t < r; ++t) {
-            const int oi = req_o[t], load = req_load[t], gi = req_g[t];
-            const int rows = t + 1 < kmax ? t + 1 : kmax;
-            const int cnt = rows << lg;
-            const int *src = tab[t & 1];
-            int *dst = tab[(t + 1) & 1];
-            for (int base = 0; base < cnt; base += DP_T) {
-                const int idx = base + tid;
-                if (idx < cnt) {  // whole wavefronts: cnt is a multiple of 64
-                    const int k = (idx >> lg) + 1, m = idx & (Mp - 1), at = idx + Mp;
-                    const int old = src[at];
-                    int cand = DP_INF;
-                    if (m <= M && m >= load) {
-                        const int prev = src[at - Mp - load];
-                        // (o <= M < 2^13 and k <= DP_SMALL_STATES / 64: 32 bits hold the sum.  150 requests of
-                        // lengths up to 8, M = 128: 1473 us in 64 bits, so 1351)
-                        const bool fits = feas_mode == 0 || m + (int)__umul24((unsigned)oi, (unsigned)k) <= M;
-                        if (prev != DP_INF && fits) cand = prev + gi;
-                    }
-                    const bool take = cand < old;
-                    dst[at] = take ? cand : old;
-                    const unsigned long long bal = __builtin_amdgcn_ballot_w64(take);
-                    if (lane == 0) bits[(size_t)t * per_t + ((size_t)k << (lg - 6)) + (m >> 6)] = bal;
+        const int parts = uniform((M >> 6) + 1);  // of a row, 64 loads each, that hold states
+        const int k_step = uniform(DP_NW / parts), part_step = DP_NW - k_step * parts;
+        const int k_first = uniform(1 + wave / parts), part_first = wave - (k_first - 1) * parts;
+        // where the records of this wavefront's turn number `lane` lie
+        const int turn = wave + DP_NW * lane, mine = ((1 + turn / parts) << (lg - 6)) + turn % parts;
+        const unsigned none = (unsigned)(unsigned long long)(lds_word *)&tab[0][DP_SMALL_STATES];
+        const int row = 4 << lg;  // (bytes)
+        for (int t = 0; t < r; t += 2) {
+            const bool two = t + 1 < r;
+            const int l1 = uniform(req_load[t]), l2 = two ? uniform(req_load[t + 1]) : DP_SMALL_STATES;  // (more than any load)
+            const int o1 = PROFILE ? uniform(req_o[t]) : 0, o2 = PROFILE && two ? uniform(req_o[t + 1]) : 0;
+            const unsigned g1 = (unsigned)uniform(req_g[t]), g2 = two ? (unsigned)uniform(req_g[t + 1]) : 0;
+            const int rows = min(t + 2, kmax);
+            const unsigned src = (unsigned)(unsigned long long)(lds_word *)&tab[(t >> 1) & 1][lane];
+            unsigned *dst = &tab[((t >> 1) + 1) & 1][lane];
+            unsigned rec[4] = {0, 0, 0, 0};  // lane j: the records of turn j
+            int turns = 0;
+            for (int k = k_first, part = part_first; k <= rows; ++turns) {
+                const int first = (k << lg) + 64 * part, m = 64 * part + lane;
+                const unsigned at = src + 4 * (unsigned)first;
+                // what lacks the first request, the second, both: to be read where its load is one, and under the profile where the
+                // memory at the completions leaves room (o <= M < 2^13 and k <= DP_SMALL_STATES / 64: 32 bits hold it)
+                bool in1 = m >= l1, in2 = m >= l2, in12 = m >= (k > 1 ? l1 + l2 : DP_SMALL_STATES);
+                if (PROFILE) {
+                    const int most1 = M - o1 * k, most2 = M - o2 * k, most12 = min(M - o1 * (k - 1) + l2, most2);
+                    in1 = in1 && m <= most1;
+                    in2 = in2 && m <= most2;
+                    in12 = in12 && m <= most12;
+                }
+                const unsigned at1 = in1 ? at - (unsigned)(row + 4 * l1) : none, at2 = in2 ? at - (unsigned)(row + 4 * l2) : none;
+                const unsigned at12 = in12 ? at - (unsigned)(2 * row + 4 * (l1 + l2)) : none;
+                const unsigned f = *(lds_word *)(unsigned long long)at, f1 = *(lds_word *)(unsigned long long)at1 + g1;
+                const unsigned f2 = *(lds_word *)(unsigned long long)at2, f12 = *(lds_word *)(unsigned long long)at12 + g1;
+                const unsigned a = min(f, f1), b = min(f2, f12) + g2;
+                dst[first] = min(a, b);
+                keep(rec, __builtin_amdgcn_ballot_w64(f1 < f), __builtin_amdgcn_ballot_w64(b < a), turns);
+                k += k_step;
+                part += part_step;
+                if (part >= parts) {
+                    part -= parts;
+                    ++k;
                 }
             }
-            __syncthreads();
+            if (lane < turns) {
+                bits[(size_t)t * per_t + mine] = (unsigned long long)rec[1] << 32 | rec[0];
+                if (two) bits[(size_t)(t + 1) * per_t + mine] = (unsigned long long)rec[3] << 32 | rec[2];
+            }
+            tables_written();
         }
         long long bS;
         int bk, bm;
-        argmin_body(tab[r & 1], 1, 1, kmax, M, Mp, tie_rule, L, bS, bk, bm);
+        argmin_body(tab[((r + 1) >> 1) & 1], kmax, M, lg, tie_rule, L, bS, bk, bm);
         if (tid == 0) publish_batch(bS, bk, gb, n - r, nb, batch_end_out, F_out, words);
         if (bk < 1) break;  // uniform
         __threadfence_block();
@@ -1340,7 +1390,7 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
                               hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(dp_small_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
+    hipLaunchKernelGGL(feas_mode == KVSCHED_FEAS_SUM_OF_PEAKS ? dp_small_kernel<false> : dp_small_kernel<true>, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
                        l.by_cost, l.buf0, l.buf1, l.batch_of, (unsigned long long *)records, order_out, batch_end_out, F_out,
                        num_batches_out, d_words);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
