@@ -715,7 +715,7 @@ __device__ __forceinline__ void order_of_places(const SortedArgs &p, const Large
                                                 int lo, int hi, u64 own, u64 *tile, int *count)
 {
     typedef typename std::conditional<NARROW, unsigned, u64>::type Key;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n, first = 64 * blockIdx.x, i = min(first + lane, n - 1);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n, first = 64 * blockIdx.x;
     const u64 low = p.packed ? field_mask(p.o_bits + p.id_bits) : field_mask(p.id_bits);
     Key *const keys = (Key *)tile;
     const Key mine = (Key)(own & low);
