@@ -197,8 +197,10 @@ def reg_rows(o_max: int) -> int:
     return next(nr for nr in (9, 33, 65, 129, 225) if rows <= nr)
 
 
-def timeline_kernel_name(C: int, n: int, o_max: int, resumed: bool) -> str:
-    """The kernel that kvsched_simulate places C explicit rows with."""
+def timeline_kernel_name(C: int, n: int, o_max: int, resumed: bool, lengths: int = 0) -> str:
+    """The kernel that kvsched_simulate places C explicit rows with, the decodes of so many different lengths."""
+    if 0 < lengths <= 4 and 2048 < o_max <= 14336 and n >= 8192 and not resumed:
+        return "event_rows_kernel"  # (visits no rounds one by one: the credit below is not its work)
     if n <= 8 or (n <= 16 and C >= 8192) or (n <= 32 and C >= 32768):
         return f"short_rows_kernel<{8 if n <= 8 else 16 if n <= 16 else 32}>"
     return f"timeline_reg_kernel<{reg_rows(o_max)},{'1,false,true,true' if resumed else '4,false,false,false'}>"
@@ -542,8 +544,8 @@ def bench_rows(args, ctx, dev, cfg: int) -> int:
     resumed_rows = int((resume > 0).sum().item())
     rejoined_rows = int(rejoined.sum().item())
     hbm_bytes = int((8 * (stop - resume) + 8).sum().item()) + 8 * n  # order entries read, completion rounds written, for the positions placed
-    kernel = timeline_kernel_name(C, n, o_max, resumed_rows > 0)
-    grouped = kernel.startswith("timeline_reg") and resumed_rows == 0 and reg_rows(o_max) >= 33
+    kernel = timeline_kernel_name(C, n, o_max, resumed_rows > 0, int(torch.unique(o64).numel()))
+    grouped = kernel == "event_rows_kernel" or (kernel.startswith("timeline_reg") and resumed_rows == 0 and reg_rows(o_max) >= 33)
     names = {1: "config 1: tiny exact, n=8, M=48, all 8! orders + the Sorted-F order",
              2: "config 2: short conversation, n=200, M=16384, Sorted-F order + 4095 random pairwise swaps",
              3: "config 3: mixed chat+summarization, n=2000, M=131072, C=16384 "
