@@ -1145,8 +1145,8 @@ __global__ __launch_bounds__(DP_T) void dp_finish_kernel(const unsigned long lon
 // are scalars that step from turn to turn, only parts that hold loads up to M are visited, and a turn's records wait in a lane each
 // until the step's end, where one store takes all.  The barrier of a step is for LDS alone.  1620 cycles for two requests of 30 rows
 // of 101 loads (2320 with one request a step, every state computing its place); of a batch of 105 requests the walk back takes a
-// third as long as all steps, the best state and the lists 9 % each.  200 requests of lengths up to 8, M = 100 1303 -> 995 us; 100 of
-// them 382 -> 300, under the profile 423 -> 369; 60 176 -> 142 and 179 -> 157; 30, M = 60 94 -> 85.
+// third as long as all steps, the best state and the lists 9 % each.  200 requests of lengths up to 8, M = 100 1303 -> 1022 us; 100 of
+// them 382 -> 307, under the profile 423 -> 375; 60 176 -> 145 and 179 -> 159; 30, M = 60 94 -> 85.
 constexpr int DP_SMALL_STATES = 12288;  // (kmax + 1) * Mp at most; two int tables = 96 KB of LDS
 constexpr int DP_SMALL_N = 1024;
 static_assert(DP_SMALL_STATES / 64 <= 64 * DP_NW, "a lane per turn");
@@ -1156,15 +1156,14 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // A barrier for what is in LDS alone: the records on their way to memory are not waited for.
 __device__ __forceinline__ void tables_written() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Lane l of the four becomes a's and b's halves (the same in all lanes; M0 and one scalar are what the instruction takes, two
-// instructions after a vector instruction has written it).
+// Lane l (the same in all lanes) of the four becomes a's and b's halves.
 __device__ __forceinline__ void keep(unsigned (&to)[4], unsigned long long a, unsigned long long b, int l)
 {
-    asm("s_mov_b32 m0, %8\n\ts_nop 1\n\tv_writelane_b32 %0, %4, m0\n\tv_writelane_b32 %1, %5, m0\n\t"
-        "v_writelane_b32 %2, %6, m0\n\tv_writelane_b32 %3, %7, m0"
-        : "+v"(to[0]), "+v"(to[1]), "+v"(to[2]), "+v"(to[3])
-        : "s"((unsigned)a), "s"((unsigned)(a >> 32)), "s"((unsigned)b), "s"((unsigned)(b >> 32)), "s"(l)
-        : "m0");
+    const bool here = (int)(threadIdx.x & 63) == l;
+    to[0] = here ? (unsigned)a : to[0];
+    to[1] = here ? (unsigned)(a >> 32) : to[1];
+    to[2] = here ? (unsigned)b : to[2];
+    to[3] = here ? (unsigned)(b >> 32) : to[3];
 }
 
 typedef __attribute__((address_space(3))) const unsigned lds_word;
