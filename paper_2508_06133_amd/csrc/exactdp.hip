@@ -1168,7 +1168,6 @@ __device__ __forceinline__ void keep(unsigned (&to)[4], unsigned long long a, un
 
 typedef __attribute__((address_space(3))) const unsigned lds_word;
 
-template <bool PROFILE>
 __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t *s, const int32_t *o, int32_t M,
                                                         int32_t ga, int32_t gb, int32_t feas_mode, int32_t tie_rule, int lg, int *proc, int *by_o,
                                                         int *by_cost, int *buf0, int *buf1, int *batch_of,
@@ -1213,48 +1212,54 @@ __global__ __launch_bounds__(DP_T) void dp_small_kernel(int32_t n, const int32_t
         const int turn = wave + DP_NW * lane, mine = ((1 + turn / parts) << (lg - 6)) + turn % parts;
         const unsigned none = (unsigned)(unsigned long long)(lds_word *)&tab[0][DP_SMALL_STATES];
         const int row = 4 << lg;  // (bytes)
-        for (int t = 0; t < r; t += 2) {
-            const bool two = t + 1 < r;
-            const int l1 = uniform(req_load[t]), l2 = two ? uniform(req_load[t + 1]) : DP_SMALL_STATES;  // (more than any load)
-            const int o1 = PROFILE ? uniform(req_o[t]) : 0, o2 = PROFILE && two ? uniform(req_o[t + 1]) : 0;
-            const unsigned g1 = (unsigned)uniform(req_g[t]), g2 = two ? (unsigned)uniform(req_g[t + 1]) : 0;
-            const int rows = min(t + 2, kmax);
-            const unsigned src = (unsigned)(unsigned long long)(lds_word *)&tab[(t >> 1) & 1][lane];
-            unsigned *dst = &tab[((t >> 1) + 1) & 1][lane];
-            unsigned rec[4] = {0, 0, 0, 0};  // lane j: the records of turn j
-            int turns = 0;
-            for (int k = k_first, part = part_first; k <= rows; ++turns) {
-                const int first = (k << lg) + 64 * part, m = 64 * part + lane;
-                const unsigned at = src + 4 * (unsigned)first;
-                // what lacks the first request, the second, both: to be read where its load is one, and under the profile where the
-                // memory at the completions leaves room (o <= M < 2^13 and k <= DP_SMALL_STATES / 64: 32 bits hold it)
-                bool in1 = m >= l1, in2 = m >= l2, in12 = m >= (k > 1 ? l1 + l2 : DP_SMALL_STATES);
-                if (PROFILE) {
-                    const int most1 = M - o1 * k, most2 = M - o2 * k, most12 = min(M - o1 * (k - 1) + l2, most2);
-                    in1 = in1 && m <= most1;
-                    in2 = in2 && m <= most2;
-                    in12 = in12 && m <= most12;
+        auto steps = [&](auto profile) __attribute__((always_inline)) {
+            constexpr bool PROFILE = decltype(profile)::value;
+            for (int t = 0; t < r; t += 2) {
+                const bool two = t + 1 < r;
+                const int l1 = uniform(req_load[t]), l2 = two ? uniform(req_load[t + 1]) : DP_SMALL_STATES;  // (more than any load)
+                const int o1 = PROFILE ? uniform(req_o[t]) : 0, o2 = PROFILE && two ? uniform(req_o[t + 1]) : 0;
+                const unsigned g1 = (unsigned)uniform(req_g[t]), g2 = two ? (unsigned)uniform(req_g[t + 1]) : 0;
+                const int rows = min(t + 2, kmax);
+                const unsigned src = (unsigned)(unsigned long long)(lds_word *)&tab[(t >> 1) & 1][lane];
+                unsigned *dst = &tab[((t >> 1) + 1) & 1][lane];
+                unsigned rec[4] = {0, 0, 0, 0};  // lane j: the records of turn j
+                int turns = 0;
+                for (int k = k_first, part = part_first; k <= rows; ++turns) {
+                    const int first = (k << lg) + 64 * part, m = 64 * part + lane;
+                    const unsigned at = src + 4 * (unsigned)first;
+                    // what lacks the first request, the second, both: to be read where its load is one, and under the profile where the
+                    // memory at the completions leaves room (o <= M < 2^13 and k <= DP_SMALL_STATES / 64: 32 bits hold it)
+                    bool in1 = m >= l1, in2 = m >= l2, in12 = m >= (k > 1 ? l1 + l2 : DP_SMALL_STATES);
+                    if (PROFILE) {
+                        const int most1 = M - o1 * k, most2 = M - o2 * k, most12 = min(M - o1 * (k - 1) + l2, most2);
+                        in1 = in1 && m <= most1;
+                        in2 = in2 && m <= most2;
+                        in12 = in12 && m <= most12;
+                    }
+                    const unsigned at1 = in1 ? at - (unsigned)(row + 4 * l1) : none, at2 = in2 ? at - (unsigned)(row + 4 * l2) : none;
+                    const unsigned at12 = in12 ? at - (unsigned)(2 * row + 4 * (l1 + l2)) : none;
+                    const unsigned f = *(lds_word *)(unsigned long long)at, f1 = *(lds_word *)(unsigned long long)at1 + g1;
+                    const unsigned f2 = *(lds_word *)(unsigned long long)at2, f12 = *(lds_word *)(unsigned long long)at12 + g1;
+                    const unsigned a = min(f, f1), b = min(f2, f12) + g2;
+                    dst[first] = min(a, b);
+                    keep(rec, __builtin_amdgcn_ballot_w64(f1 < f), __builtin_amdgcn_ballot_w64(b < a), turns);
+                    k += k_step;
+                    part += part_step;
+                    if (part >= parts) {
+                        part -= parts;
+                        ++k;
+                    }
                 }
-                const unsigned at1 = in1 ? at - (unsigned)(row + 4 * l1) : none, at2 = in2 ? at - (unsigned)(row + 4 * l2) : none;
-                const unsigned at12 = in12 ? at - (unsigned)(2 * row + 4 * (l1 + l2)) : none;
-                const unsigned f = *(lds_word *)(unsigned long long)at, f1 = *(lds_word *)(unsigned long long)at1 + g1;
-                const unsigned f2 = *(lds_word *)(unsigned long long)at2, f12 = *(lds_word *)(unsigned long long)at12 + g1;
-                const unsigned a = min(f, f1), b = min(f2, f12) + g2;
-                dst[first] = min(a, b);
-                keep(rec, __builtin_amdgcn_ballot_w64(f1 < f), __builtin_amdgcn_ballot_w64(b < a), turns);
-                k += k_step;
-                part += part_step;
-                if (part >= parts) {
-                    part -= parts;
-                    ++k;
+                if (lane < turns) {
+                    bits[(size_t)t * per_t + mine] = (unsigned long long)rec[1] << 32 | rec[0];
+                    if (two) bits[(size_t)(t + 1) * per_t + mine] = (unsigned long long)rec[3] << 32 | rec[2];
                 }
+                tables_written();
             }
-            if (lane < turns) {
-                bits[(size_t)t * per_t + mine] = (unsigned long long)rec[1] << 32 | rec[0];
-                if (two) bits[(size_t)(t + 1) * per_t + mine] = (unsigned long long)rec[3] << 32 | rec[2];
-            }
-            tables_written();
-        }
+        };
+        // (one kernel for both: with two of them the compiler calls what it has in place in the kernels above, whose calls then take 1 % longer)
+        if (feas_mode) steps(std::true_type());
+        else steps(std::false_type());
         long long bS;
         int bk, bm;
         argmin_body(tab[((r + 1) >> 1) & 1], kmax, M, lg, tie_rule, L, bS, bk, bm);
@@ -1389,7 +1394,7 @@ int kvs_launch_exact_dp_small(int32_t n, const int32_t *s, const int32_t *o, int
                               hipStream_t st)
 {
     const DpLists l = dp_lists(lists, n);
-    hipLaunchKernelGGL(feas_mode == KVSCHED_FEAS_SUM_OF_PEAKS ? dp_small_kernel<false> : dp_small_kernel<true>, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
+    hipLaunchKernelGGL(dp_small_kernel, dim3(1), dim3(DP_T), 0, st, n, s, o, M, ga, gb, feas_mode, tie_rule, lg, l.proc, l.by_o,
                        l.by_cost, l.buf0, l.buf1, l.batch_of, (unsigned long long *)records, order_out, batch_end_out, F_out,
                        num_batches_out, d_words);
     return launched() ? KVSCHED_OK : KVSCHED_EHIP;
