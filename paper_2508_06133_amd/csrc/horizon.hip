@@ -4,6 +4,7 @@
 // the committed part of the order is the prefix of positions already admitted.
 #include "kvsched_internal.h"
 #include "device_util.h"
+#include "sort_util.h"
 
 #include <limits.h>
 
@@ -35,7 +36,9 @@ __global__ __launch_bounds__(256) void apply_best_move_kernel(const int32_t *ord
 }
 
 // The values of a workgroup of 1024 that order statistics are taken of: HELD of them per thread stay in registers
-// (16384 in all), any beyond are fetched again at every turn.
+// (16384 in all), any beyond are fetched again at every turn.  A turn is a chain of comparisons, a sum over the lanes, one LDS word and a
+// barrier, some fifteen turns an order statistic: with the sum by exchanges through LDS and registers that hold nothing compared as
+// well, horizon_choose_kernel and horizon_advance_kernel 12 and 15 us at 10000 requests, 9 and 11.5 now.
 constexpr int HELD = 16;
 template <class F>
 struct Values {
@@ -57,15 +60,19 @@ struct Values {
     // how many values are <= v (every thread receives it; v < INT_MAX)
     __device__ __forceinline__ int up_to(int v)
     {
-        int c = 0;
+        unsigned c = 0;
 #pragma unroll
-        for (int e = 0; e < HELD; ++e) c += held[e] <= v;
+        for (int g = 0; g < HELD; g += 4) {
+            if (1024 * g >= count) continue;  // (uniform)
+#pragma unroll
+            for (int e = g; e < g + 4; ++e) c += held[e] <= v;
+        }
         for (int k = threadIdx.x + 1024 * HELD; k < count; k += 1024) c += at(k) <= v;
-        for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
-        turn = (turn + 1) % 3;  // (the word of the turn after next is cleared behind this turn's barrier)
-        if ((threadIdx.x & 63) == 0) atomicAdd(&sum[turn], c);
+        c = wave_scan_u32(c);
+        turn = turn < 2 ? turn + 1 : 0;  // (the word of the turn after next is cleared behind this turn's barrier)
+        if ((threadIdx.x & 63) == 63) atomicAdd(&sum[turn], (int)c);
         __syncthreads();
-        if (threadIdx.x == 0) sum[(turn + 2) % 3] = 0;
+        if (threadIdx.x == 0) sum[turn > 0 ? turn - 1 : 2] = 0;
         return sum[turn];
     }
 
@@ -190,8 +197,8 @@ __device__ __forceinline__ void commit_point(int n, int placed, START start, COM
     }
     int admitted = 0;
     for (int q = threadIdx.x; q < placed; q += 1024) admitted += start(q) <= T;
-    for (int d = 32; d > 0; d >>= 1) admitted += __shfl_xor(admitted, d);
-    if ((threadIdx.x & 63) == 0) atomicAdd(&lds[4], admitted);
+    admitted = (int)wave_scan_u32((unsigned)admitted);
+    if ((threadIdx.x & 63) == 63) atomicAdd(&lds[4], admitted);
     __syncthreads();
     if (threadIdx.x == 0) {
         result_out[0] = lds[4];
