@@ -36,19 +36,21 @@ __global__ __launch_bounds__(256) void apply_best_move_kernel(const int32_t *ord
 }
 
 // The values of a workgroup of 1024 that order statistics are taken of: HELD of them per thread stay in registers
-// (16384 in all), any beyond are fetched again at every turn.  A turn is a chain of comparisons, a sum over the lanes, one LDS word and a
-// barrier, some fifteen turns an order statistic: with the sum by exchanges through LDS and registers that hold nothing compared as
-// well, horizon_choose_kernel and horizon_advance_kernel 12 and 15 us at 10000 requests, 9 and 11.5 now.
-constexpr int HELD = 16;
+// (16384 in all), any beyond are fetched again at every turn.  A turn counts the values in 1024 parts of the range that is left, in LDS,
+// and takes the part that holds the one looked for: two turns up to 2^20.  (By halving the range, some fifteen turns of comparisons, a sum over the
+// lanes, a word of LDS and a barrier: horizon_choose_kernel and horizon_advance_kernel 9.2 and 11.5 us at 10000 requests, 8.4 and 9.9 now.)
+constexpr int HELD = 16, PARTS = 1024;
+struct StatLds {
+    int part[PARTS], wave[16], most, chosen, before, upto;
+};
 template <class F>
 struct Values {
     F at;
     int count;
     int held[HELD];
-    int *sum;  // one word of LDS, and the turn's parity
-    int turn;
+    StatLds &L;
 
-    __device__ __forceinline__ Values(F f, int n, int *lds) : at(f), count(n), sum(lds), turn(0)
+    __device__ __forceinline__ Values(F f, int n, StatLds &lds) : at(f), count(n), L(lds)
     {
 #pragma unroll
         for (int e = 0; e < HELD; ++e) {
@@ -57,44 +59,54 @@ struct Values {
         }
     }
 
-    // how many values are <= v (every thread receives it; v < INT_MAX)
-    __device__ __forceinline__ int up_to(int v)
+    // the k-th smallest, 1 <= k <= count, and how many are no larger; values lie in [0, 2^30)
+    __device__ __forceinline__ int kth(int k, int &upto)
     {
-        unsigned c = 0;
-#pragma unroll
-        for (int g = 0; g < HELD; g += 4) {
-            if (1024 * g >= count) continue;  // (uniform)
-#pragma unroll
-            for (int e = g; e < g + 4; ++e) c += held[e] <= v;
-        }
-        for (int k = threadIdx.x + 1024 * HELD; k < count; k += 1024) c += at(k) <= v;
-        c = wave_scan_u32(c);
-        turn = turn < 2 ? turn + 1 : 0;  // (the word of the turn after next is cleared behind this turn's barrier)
-        if ((threadIdx.x & 63) == 63) atomicAdd(&sum[turn], (int)c);
-        __syncthreads();
-        if (threadIdx.x == 0) sum[turn > 0 ? turn - 1 : 2] = 0;
-        return sum[turn];
-    }
-
-    // the k-th smallest, 1 <= k <= count; values lie in [0, 2^30)
-    __device__ __forceinline__ int kth(int k)
-    {
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         int mx = 0;
 #pragma unroll
         for (int e = 0; e < HELD; ++e)
             if (held[e] != INT_MAX) mx = max(mx, held[e]);
-        for (int q = threadIdx.x + 1024 * HELD; q < count; q += 1024) mx = max(mx, at(q));
+        for (int q = tid + 1024 * HELD; q < count; q += 1024) mx = max(mx, at(q));
         mx = wave_max_i32(mx);
+        if (tid == 0) L.most = 0;
+        L.part[tid] = 0;
         __syncthreads();
-        if ((threadIdx.x & 63) == 0) atomicMax(&sum[3], mx);
+        if (lane == 0) atomicMax(&L.most, mx);
         __syncthreads();
-        int lo = 0, hi = sum[3];
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo) >> 1);
-            if (up_to(mid) >= k) hi = mid;
-            else lo = mid + 1;
+        int base = 0, before = 0;  // the values below base
+        for (int shift = max(22 - __builtin_clz(L.most | 1), 0);; shift = max(shift - 10, 0)) {
+            auto enter = [&](int v) {
+                const unsigned part = (unsigned)(v - base) >> shift;
+                if (part < PARTS) atomicAdd(&L.part[part], 1);
+            };
+#pragma unroll
+            for (int g = 0; g < HELD; g += 4) {
+                if (1024 * g >= count) continue;  // (uniform)
+#pragma unroll
+                for (int e = g; e < g + 4; ++e) enter(held[e]);
+            }
+            for (int q = tid + 1024 * HELD; q < count; q += 1024) enter(at(q));
+            __syncthreads();
+            const int mine = L.part[tid];
+            int incl = (int)wave_scan_u32((unsigned)mine);
+            if (lane == 63) L.wave[wave] = incl;
+            L.part[tid] = 0;
+            __syncthreads();
+            incl += before;
+            for (int w = 0; w < 15; ++w) incl += w < wave ? L.wave[w] : 0;
+            if (incl >= k && incl - mine < k) {
+                L.chosen = tid;
+                L.before = incl - mine;
+                L.upto = incl;
+            }
+            __syncthreads();
+            base += L.chosen << shift;
+            before = L.before;
+            if (shift == 0) break;
         }
-        return lo;
+        upto = L.upto;
+        return base;
     }
 };
 
@@ -151,8 +163,7 @@ __global__ __launch_bounds__(1024) void horizon_choose_kernel(HorizonKept h, int
                                                               const int64_t *result, const int32_t *words, int32_t stride,
                                                               long long completed_in, int32_t complete_every, int32_t full)
 {
-    __shared__ int lds[4];
-    if (threadIdx.x < 4) lds[threadIdx.x] = 0;
+    __shared__ StatLds lds;
     const int first_block = min(max(words[KVS_W_MINPOS], 0) >> 6, (n - 1) >> 6);  // no move touches what lies before
     const long long best = result[0];
     if (best >= 0) {
@@ -170,7 +181,8 @@ __global__ __launch_bounds__(1024) void horizon_choose_kernel(HorizonKept h, int
     if (!full && k <= placed && best >= 0) {  // (uniform)
         auto completion = [&](int p) { return h.start[p] + h.o[min(max(h.order[p], 0), n - 1)]; };
         Values<decltype(completion)> c(completion, placed, lds);
-        limit = c.kth((int)max(k, 1ll));
+        int upto;
+        limit = c.kth((int)max(k, 1ll), upto);
     }
     if (threadIdx.x == 0) {
         h.ctrl[KVS_HZ_FIRST] = first_block;
@@ -186,22 +198,21 @@ __global__ __launch_bounds__(1024) void horizon_choose_kernel(HorizonKept h, int
 // nondecreasing along it), requests completed by T, T}.
 template <class START, class COMPLETION>
 __device__ __forceinline__ void commit_point(int n, int placed, START start, COMPLETION completion, long long completed_in,
-                                             int complete_every, int64_t *result_out, int *lds)
+                                             int complete_every, int64_t *result_out, StatLds &lds, int *sum)
 {
     const int k = (int)max(min(min(completed_in + complete_every, (long long)n), (long long)placed), 1ll);
     int T = 0, done = 0;
     if (placed > 0) {
         Values<COMPLETION> c(completion, placed, lds);
-        T = c.kth(k);
-        done = c.up_to(T);
+        T = c.kth(k, done);
     }
     int admitted = 0;
     for (int q = threadIdx.x; q < placed; q += 1024) admitted += start(q) <= T;
     admitted = (int)wave_scan_u32((unsigned)admitted);
-    if ((threadIdx.x & 63) == 63) atomicAdd(&lds[4], admitted);
+    if ((threadIdx.x & 63) == 63) atomicAdd(sum, admitted);
     __syncthreads();
     if (threadIdx.x == 0) {
-        result_out[0] = lds[4];
+        result_out[0] = *sum;
         result_out[1] = done;
         result_out[2] = T;
     }
@@ -211,15 +222,16 @@ __global__ __launch_bounds__(1024) void horizon_advance_kernel(HorizonKept h, co
                                                               long long completed_in, int32_t complete_every,
                                                               int32_t *completion_out, int64_t *result_out)
 {
-    __shared__ int lds[5];
-    if (threadIdx.x < 5) lds[threadIdx.x] = 0;
+    __shared__ StatLds lds;
+    __shared__ int sum;
+    if (threadIdx.x == 0) sum = 0;
     __syncthreads();
     const int placed = min(h.ctrl[KVS_HZ_PLACED], n);
     auto start = [&](int p) { return h.start[p]; };
     auto completion = [&](int p) { return h.start[p] + h.o[min(max(order[p], 0), n - 1)]; };
     if (completion_out)
         for (int p = threadIdx.x; p < placed; p += 1024) completion_out[min(max(order[p], 0), n - 1)] = completion(p);
-    commit_point(n, placed, start, completion, completed_in, complete_every, result_out, lds);
+    commit_point(n, placed, start, completion, completed_in, complete_every, result_out, lds, &sum);
     if (threadIdx.x == 0) h.ctrl[KVS_HZ_AVAIL] = min(placed >> 6, blocks);
 }
 
@@ -227,12 +239,13 @@ __global__ __launch_bounds__(1024) void horizon_advance_by_id_kernel(const int32
                                                                     const int32_t *o, int32_t n, long long completed_in,
                                                                     int32_t complete_every, int64_t *result_out)
 {
-    __shared__ int lds[5];
-    if (threadIdx.x < 5) lds[threadIdx.x] = 0;
+    __shared__ StatLds lds;
+    __shared__ int sum;
+    if (threadIdx.x == 0) sum = 0;
     __syncthreads();
     auto start = [&](int p) { return by_id[order[p]] - o[order[p]]; };
     auto completion = [&](int i) { return by_id[i]; };
-    commit_point(n, n, start, completion, completed_in, complete_every, result_out, lds);
+    commit_point(n, n, start, completion, completed_in, complete_every, result_out, lds, &sum);
 }
 
 __global__ __launch_bounds__(256) void horizon_completion_kernel(HorizonKept h, const int32_t *order, const int32_t *o,
