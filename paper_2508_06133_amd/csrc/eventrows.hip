@@ -145,6 +145,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
     int32_t *crow = p.completion_out ? p.completion_out + (size_t)cand * (size_t)n : nullptr;
 
     // The ids and lengths of a chunk, position 64 q + lane of it in number q.  (Past the end the last position's, or the shortest.)
+    // No length is read by an id that has not been clamped.
     int id[PIECES], sv[PIECES], ov[PIECES], id_next[PIECES];
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) id[q] = id_next[q] = 0, sv[q] = ov[q] = 1;
@@ -160,8 +161,9 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
     };
     bool strange = false;  // an id that there is not
     for (int w = lane; w < words; w += WAVE) met[w] = 0;
+    auto clamped = [&](int raw) __attribute__((always_inline)) -> int { return min(max(raw, 0), n - 1); };
     auto meet = [&](int raw) __attribute__((always_inline)) -> int {
-        const int r = min(max(raw, 0), n - 1);
+        const int r = clamped(raw);
         strange |= raw != r;
         atomicOr(&met[r >> 5], 1u << (r & 31));
         return r;
@@ -182,7 +184,8 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
 #pragma unroll
             for (int q = 0; q < PIECES; ++q) {
                 if (first + WAVE * q >= n) continue;
-                if (first + WAVE * q + lane < n) id[q] = meet(id[q]);  // (not the others: lanes that mean one word take turns)
+                // (the lanes past the end hold the last id as it stands, which may be none; met they are not: lanes that mean one word take turns)
+                id[q] = first + WAVE * q + lane < n ? meet(id[q]) : clamped(id[q]);
                 length_of(q);
             }
         }

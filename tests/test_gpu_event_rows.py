@@ -118,3 +118,42 @@ def test_faulty(n):
                     assert status == kvsched.DEV_BAD_LENGTH and (tel == -1).all()
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("lengths", ["few", "many"])
+@pytest.mark.parametrize("n", [33, 100, 127, 577, 1500, 8193, 8255])
+def test_faulty_last_position(n, lengths):
+    """A row whose LAST id is none: the lanes past the end of the row, which take that position's id, read nothing by it.  Many lengths: the
+    kernel is launched and leaves the rows to the timeline kernel (from 8192 positions on by itself, else because the call before had few)."""
+    from paper_2508_06133_amd import kvsched
+
+    assert n % 64 != 0
+    rng = np.random.default_rng(n)
+    s, o, M = _lengths(rng, "bimodal", n)
+    o[:2] = 1, 4096
+    few = o.astype(np.int32)
+    if lengths == "many":
+        o = rng.integers(1, 400, n)
+        o[:2] = 1, 4096
+    s, o = s.astype(np.int32), o.astype(np.int32)
+    orders = _orders(rng, s, o, M, 5)
+    orders[1, n - 1] = -1
+    orders[2, n - 1] = n
+    orders[3, n - 1] = 2**31 - 1
+    good = [0, 4]
+    tel_o, comp_o = oracle.simulate_many(s, o, M, orders[good])
+    for bound in (0, 4096):
+        ctx = kvsched.Context(0)
+        try:
+            ctx.set_o_max(bound)
+            for call in range(2):
+                print(f"event rows, last id: n={n} {lengths} bound={bound} call={call}", flush=True)
+                ctx.simulate(_dev(orders[good]), _dev(s), _dev(few), M)
+                tel, comp = ctx.simulate(_dev(orders), _dev(s), _dev(o), M)
+                assert ctx.device_status() == kvsched.DEV_BAD_ORDER
+                tel, comp = tel.cpu().numpy(), comp.cpu().numpy()
+                assert (tel[[1, 2, 3]] == -1).all() and (tel[good] == tel_o).all() and (comp[good] == comp_o).all()
+                only, _ = ctx.simulate(_dev(orders), _dev(s), _dev(o), M, completions=False)
+                assert (only.cpu().numpy() == tel).all()
+        finally:
+            ctx.close()
