@@ -1127,7 +1127,7 @@ static int horizon_step_plain(kvsched_ctx *ctx, int32_t *order, int32_t n, const
         ctx->hz_completion = 2;
         ctx->hz_n = n;
     }
-    return kvs_launch_horizon_advance_by_id(order, comp, o, n, completed_in, complete_every, result_out + 3, st);
+    return kvs_launch_horizon_advance_by_id(order, comp, o, n, completed_in, complete_every, result_out, st);
 }
 
 int kvsched_best_neighbor(kvsched_ctx *ctx, const int32_t *base_order, int32_t n, const int32_t *moves, int32_t K,

@@ -59,7 +59,8 @@ struct Values {
         }
     }
 
-    // the k-th smallest, 1 <= k <= count, and how many are no larger; values lie in [0, 2^30)
+    // the k-th smallest, 1 <= k <= count, and how many are no larger; values lie in [0, 2^30) (of others fewer than k may be counted: then
+    // the answer is of no use, but the same in every call)
     __device__ __forceinline__ int kth(int k, int &upto)
     {
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -69,7 +70,7 @@ struct Values {
             if (held[e] != INT_MAX) mx = max(mx, held[e]);
         for (int q = tid + 1024 * HELD; q < count; q += 1024) mx = max(mx, at(q));
         mx = wave_max_i32(mx);
-        if (tid == 0) L.most = 0;
+        if (tid == 0) L.most = L.chosen = L.before = L.upto = 0;
         L.part[tid] = 0;
         __syncthreads();
         if (lane == 0) atomicMax(&L.most, mx);
@@ -235,17 +236,23 @@ __global__ __launch_bounds__(1024) void horizon_advance_kernel(HorizonKept h, co
     if (threadIdx.x == 0) h.ctrl[KVS_HZ_AVAIL] = min(placed >> 6, blocks);
 }
 
+// result: all six of the step's numbers, of which the last three are written here.  An order or lengths that are faulty (result[2] < 0, the
+// latency of the order before the move) have no timeline: the ids may be none, completion rounds may be missing, and nothing is committed.
 __global__ __launch_bounds__(1024) void horizon_advance_by_id_kernel(const int32_t *order, const int32_t *by_id,
                                                                     const int32_t *o, int32_t n, long long completed_in,
-                                                                    int32_t complete_every, int64_t *result_out)
+                                                                    int32_t complete_every, int64_t *result)
 {
     __shared__ StatLds lds;
     __shared__ int sum;
+    if (result[2] < 0) {  // (uniform)
+        if (threadIdx.x < 3) result[3 + threadIdx.x] = 0;
+        return;
+    }
     if (threadIdx.x == 0) sum = 0;
     __syncthreads();
     auto start = [&](int p) { return by_id[order[p]] - o[order[p]]; };
     auto completion = [&](int i) { return by_id[i]; };
-    commit_point(n, n, start, completion, completed_in, complete_every, result_out, lds, &sum);
+    commit_point(n, n, start, completion, completed_in, complete_every, result + 3, lds, &sum);
 }
 
 __global__ __launch_bounds__(256) void horizon_completion_kernel(HorizonKept h, const int32_t *order, const int32_t *o,
@@ -296,10 +303,10 @@ int kvs_launch_horizon_advance(const HorizonKept &h, const int32_t *order, int32
 }
 
 int kvs_launch_horizon_advance_by_id(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
-                                     int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st)
+                                     int64_t completed_in, int32_t complete_every, int64_t *result, hipStream_t st)
 {
     hipLaunchKernelGGL(horizon_advance_by_id_kernel, dim3(1), dim3(1024), 0, st, order, completion, o, n,
-                       (long long)completed_in, complete_every, result_out);
+                       (long long)completed_in, complete_every, result);
     return ok();
 }
 

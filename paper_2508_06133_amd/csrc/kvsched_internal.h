@@ -294,9 +294,9 @@ int kvs_launch_horizon_choose(const HorizonKept &h, int32_t *order, int32_t n, c
 // After the new order's timeline: commit point; completion rounds by request id if wanted.
 int kvs_launch_horizon_advance(const HorizonKept &h, const int32_t *order, int32_t n, int32_t blocks, int64_t completed_in,
                                int32_t complete_every, int32_t *completion_out, int64_t *result_out, hipStream_t st);
-// The same from completion rounds by request id.
+// The same from completion rounds by request id (result: all six of the step's numbers; nothing is committed of an order that is faulty).
 int kvs_launch_horizon_advance_by_id(const int32_t *order, const int32_t *completion, const int32_t *o, int32_t n,
-                                     int64_t completed_in, int32_t complete_every, int64_t *result_out, hipStream_t st);
+                                     int64_t completed_in, int32_t complete_every, int64_t *result, hipStream_t st);
 int kvs_launch_apply_best_move(const int32_t *order, int32_t n, const int32_t *moves, const int64_t *result,
                                int32_t *order_out, hipStream_t st);
 int kvs_launch_horizon_completion(const HorizonKept &h, const int32_t *order, const int32_t *o, int32_t n,
