@@ -80,6 +80,14 @@ __device__ __forceinline__ unsigned long long ballot(bool v) { return __builtin_
 // max(a - b, 0) of numbers from 0 on
 __device__ __forceinline__ int beyond(int a, int b) { return (int)__builtin_elementwise_sub_sat((unsigned)a, (unsigned)b); }
 
+__device__ __forceinline__ void wave_sync()
+{
+    // LDS traffic of one wavefront is served in order; this keeps the compiler from moving accesses across a point where lanes
+    // read what other lanes wrote, or write where they have read
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The completion rounds ahead, a lane each.
 struct Events {
     int t = 0;  // start round of the last request
@@ -161,6 +169,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
     };
     bool strange = false;  // an id that there is not
     for (int w = lane; w < words; w += WAVE) met[w] = 0;
+    wave_sync();
     auto clamped = [&](int raw) __attribute__((always_inline)) -> int { return min(max(raw, 0), n - 1); };
     auto meet = [&](int raw) __attribute__((always_inline)) -> int {
         const int r = clamped(raw);
@@ -237,6 +246,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
             kept_id[WAVE * q + lane] = id[q];
             id[q] = id_next[q];
         }
+        wave_sync();
         fetch_lengths(chunk + CHUNK);
         fetch_ids(id_next, chunk + 2 * CHUNK);
         for (int q = 0; q < BLOCKS && chunk + GROUP * q < n; ++q) {
@@ -381,6 +391,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
             *(four *)&kept_s[GROUP * q + 4 * lane] = done;
         }
         if (e.full || bad_length) break;
+        wave_sync();
         if (crow) {
             // what the next chunk takes has arrived before the stores are issued
 #pragma unroll
@@ -390,6 +401,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
                 const int k = chunk + WAVE * q + lane;
                 if (k < n) crow[kept_id[WAVE * q + lane]] = kept_s[WAVE * q + lane];
             }
+            wave_sync();
         }
     }
     if (p.todo && lane == 0) p.todo[cand] = e.full;
@@ -397,6 +409,7 @@ __global__ __launch_bounds__(WAVE) void event_rows_kernel(SimParams p)
     if (bad_length) {  // (the ids behind have not all been looked at)
         for (int k = lane; k < n; k += WAVE) meet(row[k]);
     }
+    wave_sync();
     // n ids that there are set n bits exactly if none is there twice
     bool missing = false;
     for (int w = lane; w < words; w += WAVE) missing |= met[w] != (32 * w + 32 <= n ? ~0u : (1u << (n & 31)) - 1u);
