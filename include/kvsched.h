@@ -170,7 +170,10 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
  * KVSCHED_RESUME_AUTO: when the plan and the wait for row 0 are likely to cost less than the
  * skipped positions save (at least 4096 rows, 385 positions and 8 million positions in all; 16384 rows
  * when the states are handed over between two launches); 0 = never; rows > 0 = whenever there are
- * that many rows (and more than 128 positions). */
+ * that many rows (and more than 128 positions).  By default, and without a bound from
+ * kvsched_set_o_max(), rows whose decodes have four lengths or fewer, the longest between 2048 and
+ * 14336, are not resumed but placed in a way that is mostly faster.  (Rows that differ from row 0 near
+ * their end alone may be quicker resumed: give a number here.) */
 #define KVSCHED_RESUME_AUTO (-1)
 int kvsched_set_resume_min_rows(kvsched_ctx *ctx, int32_t rows);
 

@@ -144,14 +144,23 @@ int wait_for_scan(kvsched_ctx *ctx, hipStream_t st)
     }
 }
 
-// The longest decode that the length scan found (after wait_for_scan).
+// The longest decode that the length scan found (after wait_for_scan), 1 at least.
+int32_t scanned_longest(const kvsched_ctx *ctx)
+{
+    const int32_t omax = ctx->h_scan[KVS_H_OMAX] & INT32_MAX;
+    return omax < 1 ? 1 : omax;
+}
+
 int scanned_bound(const kvsched_ctx *ctx, int32_t *o_bound_out)
 {
-    const int32_t omax = ctx->h_scan[KVS_H_OMAX];
+    const int32_t omax = scanned_longest(ctx);
     if (omax > KVSCHED_MAX_O) return KVSCHED_ERANGE;
-    *o_bound_out = omax < 1 ? 1 : omax;
+    *o_bound_out = omax;
     return KVSCHED_OK;
 }
+
+// ... and whether the decode lengths are few (a scan_lengths_kernel that was asked to tell).
+bool scanned_few(const kvsched_ctx *ctx) { return ctx->h_scan[KVS_H_OMAX] < 0; }
 
 // Enqueue the length scan; unless the caller supplied a bound, wait for the largest decode
 // length.  *o_bound_out is what the timeline kernels size their ring from.
@@ -530,29 +539,40 @@ static bool scans_here(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_b
 static int32_t next_status_word(const kvsched_ctx *ctx) { return KVS_W_STATUS_TURN + (ctx->status_turn ^ 1); }
 
 // Are timelines of n positions, no prefix shared, placed by the event kernel (eventrows.hip)?  Where the decodes are few, which the kernel
-// sees for itself, and may be long: with decodes up to 2048 the timeline kernel's 33 rows are as fast (1000 orders of 10000 with four
-// lengths 2260 us, 2660 here).  If they are not few, or a row has too many completions ahead, the timeline kernel's launch behind it
-// places the rows; so a launch is wasted, 3 us.  From 8192 positions on that is next to nothing beside a timeline (700 us and more); for shorter
-// ones what the context has seen last of the lengths decides, which may be out of date and then costs that launch, or the time
-// of the other kernel.  Not while the stream is captured, as the list of rows left lies in memory that later calls may replace
-// (orders of up to 64 have none); not where the caller asks for rows to be resumed, nor where they are by themselves unless the lengths are known to be few.
+// sees for itself, and may be long.  If they are not few, or a row has too many completions ahead, the timeline kernel's launch behind it
+// places the rows.  Not while the stream is captured, as the list of rows left lies in memory that later calls may replace
+// (orders of up to 64 have none); not where the caller asks for rows to be resumed.
+// few: by this call's scan, where the host has waited for it (no bound from the caller, or a wrong guess); -1: not known.  Then `hint` is what
+// the context has seen last, of an earlier call, and may be out of date.  Orders that would not be resumed lose a launch by it, 3 us, or the
+// other kernel's time; from 8192 positions on, 700 us and more, they take the launch unasked.  Rows that would be resumed could lose all that
+// resuming saves (a hint out of date, 16384 rows of 2000 mixed requests: exchanges anywhere 1570 -> 1750, in the last tenth 890 -> 1780), so they
+// are resumed while it is not known.
+// Against resumed rows, one call (us, resumed and here; rows that exchange two positions in the last tenth, anywhere, and 64 pairs): bimodal
+// lengths, 16384 rows of 2000 1360 958, 3390 980, 3710 1230; 8192 of 1000 813 473, 1690 500, 1890 680; 32768 of 500 1175 1263, 3560 1275, 4640
+// 1620; 4096 of 20000 2350 853, 2340 874, 2110 892; four lengths up to 4096, 16384 of 2000 1112 1547, 3190 1650, 3770 2230; 8192 of 1000
+// 664 662, 1125 724, 1390 917; 32768 of 500 1512 1662, 3680 1700, 4940 2000; 4096 of 20000, random orders 5920 6400.  So rows that differ in the
+// last tenth alone are up to 1.4 times slower here from 16384 rows on; a caller who has such rows declares their prefix or asks
+// for resuming.
+// Decodes up to 2048 stay with the timeline kernel's 33 rows.  The lengths decide which is faster there (us, 33 rows and here): of 1 and
+// 2048, 1000 orders of 10000 1756 347, 4000 of 2000 831 398, 2 of 200 196 85; of 1, 300, 900 and 2048 1670 816, 714 896, 326 108; of 1, 300 and
+// 1024 1360 854, 513 834, 412 104.
 constexpr int32_t kEventsUnasked = 8192;
 constexpr int32_t kEventsFrom = 2048;
-static bool by_events(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bound, bool few, hipStream_t st)
+static bool by_events(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bound, int few, bool hint, hipStream_t st)
 {
     if (o_bound <= kEventsFrom || o_bound > KVS_REG_MAX_O || n > KVS_EVENTS_MAX_N) return false;
     const bool resume = resume_pays(ctx, C, n, o_bound);
     if (ctx->resume_min_rows != KVSCHED_RESUME_AUTO && resume) return false;
-    if (!few && (resume || n < kEventsUnasked)) return false;
+    if (few == 0 || (few < 0 && (resume || (!hint && n < kEventsUnasked)))) return false;
     return n <= WAVE_POSITIONS || !capturing(st);
 }
 
 // kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
 // longer one (only where rows are not resumed and no prefix is placed ahead).  scan: no length scan is enqueued before
 // (scans_here), the launch does it and, if gated, leaves its result in pinned memory under number ctx->scan_seq.
-// status_word: where faulty rows are reported.
+// status_word: where faulty rows are reported.  few: whether the decode lengths are few, by this call's scan (-1: not known yet).
 static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, const int32_t *s,
-                           const int32_t *o, int64_t M, int32_t o_bound, bool gated, bool scan, int32_t status_word, int64_t *tel_out,
+                           const int32_t *o, int64_t M, int32_t o_bound, bool gated, bool scan, int32_t status_word, int few, int64_t *tel_out,
                            int32_t *completion_out, int32_t common_prefix, hipStream_t st)
 {
     const int32_t o_limit = gated ? o_bound : INT32_MAX;
@@ -609,7 +629,7 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     const int32_t *resumed_blocks = nullptr, *resumed_row0 = nullptr, *rejoined = nullptr;
     p.few_out = ctx->h_scan + KVS_H_FEW;
     p.few_known = __atomic_load_n(p.few_out, __ATOMIC_RELAXED);
-    const bool events = cp == 0 && by_events(ctx, C, n, o_bound, p.few_known != 0, st);
+    const bool events = cp == 0 && by_events(ctx, C, n, o_bound, few, p.few_known != 0, st);
     if (cp == 0 && !events && resume_pays(ctx, C, n, o_bound)) {
         const int32_t nblk = (n - 1) / WAVE_POSITIONS;
         const int32_t stride = kvs_reg_state_words(o_bound);
@@ -766,12 +786,12 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
         if (scan) status_word = next_status_word(ctx);
         else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq, ctx->h_scan + KVS_H_FEW);
         if (rc == KVSCHED_OK)
-            rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, scan, status_word, tel_out, completion_out, 0, st);
+            rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, scan, status_word, -1, tel_out, completion_out, 0, st);
         if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);
         if (rc != KVSCHED_OK) return rc;
     } else if (ctx->o_max_bound > 0 && scans_here(ctx, C, n, ctx->o_max_bound, common_prefix, st)) {
         ctx->o_file = kvs_reg_file_bound(ctx->o_max_bound);
-        return simulate_within(ctx, orders, C, n, s, o, M, ctx->o_max_bound, false, true, next_status_word(ctx), tel_out,
+        return simulate_within(ctx, orders, C, n, s, o, M, ctx->o_max_bound, false, true, next_status_word(ctx), -1, tel_out,
                                completion_out, common_prefix, st);
     }
     int32_t o_bound = 0;
@@ -779,12 +799,14 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
     if (rc != KVSCHED_OK) return rc;
     ctx->o_file = kvs_reg_file_bound(o_bound);
     if (guess >= o_bound) return KVSCHED_OK;
+    const int few = scan || ctx->o_max_bound > 0 ? -1 : scanned_few(ctx);
     if (scan && o_bound > KVS_REG_MAX_O) {  // (whose kernels report in the scan's word)
         status_word = KVS_W_STATUS;
         rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);
         if (rc != KVSCHED_OK) return rc;
     }
-    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, false, false, status_word, tel_out, completion_out, common_prefix, st);
+    return simulate_within(ctx, orders, C, n, s, o, M, o_bound, false, false, status_word, few, tel_out, completion_out, common_prefix,
+                           st);
 }
 
 // The three Phase-1 solvers; (ga, gb) = (0, 1) is the F-metric.
@@ -1104,8 +1126,7 @@ static int horizon_step_plain(kvsched_ctx *ctx, int32_t *order, int32_t n, const
     if (rc != KVSCHED_OK) return rc;
     hipLaunchKernelGGL(kvs_copy_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, order, new_order, n);
     if (hipGetLastError() != hipSuccess) return KVSCHED_EHIP;
-    const int32_t o_bound = ctx->o_max_bound > 0 ? ctx->o_max_bound
-                                                 : (ctx->h_scan[KVS_H_OMAX] < 1 ? 1 : ctx->h_scan[KVS_H_OMAX]);
+    const int32_t o_bound = ctx->o_max_bound > 0 ? ctx->o_max_bound : scanned_longest(ctx);
     SimParams p;
     p.src.orders = order;
     p.src.base = nullptr;

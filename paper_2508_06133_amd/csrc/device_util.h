@@ -46,12 +46,12 @@ __device__ __forceinline__ void to_host(int32_t *host, int value)
 {
     __hip_atomic_store(host, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// ... the longest decode and the number in one store, behind which nothing waits
-__device__ __forceinline__ void longest_to_host(int32_t *host, int longest, int seq)
+// ... the longest decode, whether the decode lengths are few and the number in one store, behind which nothing waits
+__device__ __forceinline__ void longest_to_host(int32_t *host, int longest, int seq, bool few = false)
 {
     static_assert(KVS_H_OMAX == 0 && KVS_H_SEQ == 1, "one word of 64 bits");
-    __hip_atomic_store((unsigned long long *)host, (unsigned long long)(unsigned)seq << 32 | (unsigned)longest, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store((unsigned long long *)host, (unsigned long long)(unsigned)seq << 32 | (few ? 1u << 31 : 0u) | (unsigned)longest,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // What a length scan leaves behind, by one lane of a launch that has had none ahead of it (SimParams::scan_here).

@@ -34,7 +34,7 @@ enum {
 // What the length scan leaves in pinned host memory for a call that waits for it.
 // ... and what the exact DP leaves there between batches.
 enum {
-    KVS_H_OMAX = 0,  // (it and the number are one word of 64 bits)
+    KVS_H_OMAX = 0,  // (it and the number are one word of 64 bits; its sign bit: the decode lengths are few, see KVS_H_FEW)
     KVS_H_SEQ = 1,   // number of the launch that has written the others
     KVS_H_MINPOS = 2,
     KVS_H_MAXPOS = 3,
@@ -42,7 +42,7 @@ enum {
     KVS_H_KMAX = 5,
     KVS_H_KMIN = 6,
     KVS_H_BATCHES = 7,
-    KVS_H_FEW = 8,  // 1: the last backlog looked over had few decode lengths (few_lengths); nobody waits for it
+    KVS_H_FEW = 8,  // 1: the last backlog looked over had few decode lengths (few_lengths); nobody waits for it, so it may be an earlier call's
     KVS_H_COUNT = 16
 };
 

@@ -116,6 +116,7 @@ __global__ __launch_bounds__(WAVE *WPB) void timeline_kernel(SimParams p)
 // Bound by latency: one workgroup up to 4096 lengths and moves, then one per 4096 (at most 64; 100000 lengths: 41 us
 // by one workgroup, 5 us so), the last to finish writes the results.  A caller that waits for them (host, in pinned
 // memory) finds them there: the wait is one store across the bus instead of a copy and a stream synchronisation.
+constexpr int kScanFew = 1 << 30;  // among the flags (no status bit): the decode lengths are few
 __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, const int32_t *o, int32_t n, int32_t M,
                                                             int32_t o_bound, const int32_t *moves, int32_t K,
                                                             int32_t *words, int32_t *host, int32_t seq, int32_t *few_out)
@@ -136,12 +137,13 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
         else if (i != j) lowest = min(lowest, min(i, j));
         top = max(top, min(max(max(i, j), 0), n - 1));  // (as the timeline kernel clamps)
     }
+    bool few = false;
     if (few_out && first < WAVE) {
-        const bool few = few_lengths(o[sampled(first, n)]);
+        few = few_lengths(o[sampled(first, n)]);
         if (first == 0) to_host(few_out, few ? 1 : 0);
     }
     mx = wave_max_i32(mx);
-    flag = wave_max_i32(flag & 1) | wave_max_i32(flag & KVSCHED_DEV_O_MAX);
+    flag = wave_max_i32(flag & 1) | wave_max_i32(flag & KVSCHED_DEV_O_MAX) | (few ? kScanFew : 0);
     lowest = ~wave_max_i32(~lowest);
     top = wave_max_i32(top);
     if ((threadIdx.x & 63) == 0) {
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
         top = atomicExch(&words[KVS_W_SCAN_MAXPOS], -1);
         atomicExch(&words[KVS_W_SCAN_DONE], 0);
     }
-    words[KVS_W_STATUS] = flag;
+    words[KVS_W_STATUS] = flag & ~kScanFew;
     words[KVS_W_STATUS_AT] = KVS_W_STATUS;
     words[KVS_W_OMAX] = mx;
     words[KVS_W_MINPOS] = lowest;
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(1024) void scan_lengths_kernel(const int32_t *s, co
             to_host(&host[KVS_H_MAXPOS], top);
             device_writes_done();
         }
-        longest_to_host(host, mx, seq);
+        longest_to_host(host, mx, seq, (flag & kScanFew) != 0);
     }
 }
 

@@ -157,3 +157,39 @@ def test_faulty_last_position(n, lengths):
                 assert (only.cpu().numpy() == tel).all()
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("bound", [0, 4096])
+def test_rows_that_would_be_resumed(bound):
+    """Rows that would be resumed are placed a lane per completion round where this call's lengths are known to be few, whatever those of the call
+    before were: without a bound from the caller (several workgroups look them over); with one they are always resumed."""
+    from paper_2508_06133_amd import kvsched
+
+    n, rows = 4500, 4096
+    rng = np.random.default_rng(7)
+    s, few, M = _lengths(rng, "bimodal", n)
+    many = rng.integers(1, 400, n)
+    few[:2] = many[:2] = 1, 4096
+    base = rng.permutation(n).astype(np.int32)
+    orders = np.tile(base, (rows, 1))
+    for r in range(1, rows):
+        i, j = rng.integers(64, n, 2)
+        orders[r, i], orders[r, j] = orders[r, j], orders[r, i]
+    d_orders, d_s, lengths = _dev(orders), _dev(s), {"few": _dev(few), "many": _dev(many)}
+    ctx, plain = kvsched.Context(0), kvsched.Context(0)
+    try:
+        plain.set_resume_min_rows(0)
+        ctx.set_o_max(bound)
+        want = {k: plain.simulate(d_orders, d_s, o, M) for k, o in lengths.items()}
+        for call, which in enumerate(["few", "many", "few", "few", "many", "many", "few", "few", "few", "many"]):
+            print(f"event rows, would be resumed: bound={bound} call {call} {which}", flush=True)
+            tel, comp = ctx.simulate(d_orders, d_s, lengths[which], M)
+            assert bool((tel == want[which][0]).all()) and bool((comp == want[which][1]).all()) and ctx.device_status() == 0
+            resumed = bool((ctx.simulate_resume_positions(rows) > 0).any())
+            assert resumed == (bound > 0 or which == "many")
+        for k, o in (("few", few), ("many", many)):  # the plain context itself, a few rows against the oracle
+            t, c = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), M, orders[:3])
+            assert (want[k][0][:3].cpu().numpy() == t).all() and (want[k][1][:3].cpu().numpy() == c).all()
+    finally:
+        ctx.close()
+        plain.close()
