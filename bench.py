@@ -47,9 +47,8 @@ PEAK_HBM_BYTES = 8.0e12
 # pass with the rows' limits, moving the register file) is overhead and is not credited, so where
 # requests are placed one by one the fraction below cannot exceed the share of issue slots the kernel
 # uses.  Requests that start together and are placed as a group visit far fewer rounds than the credit
-# counts: launches of explicit rows that resume nothing do so (config 5, where nearly all requests start
-# in bursts, reads 2.1 with 23 % of the issue slots in use), and there the fraction is no bound
-# ("credit_is_bound" says which).
+# counts: launches of explicit rows that resume nothing do so, and there the fraction is no bound
+# ("credit_is_bound" says which).  Rows of few decode lengths (config 5) visit no rounds at all: no credit is reported.
 OPS_PER_INSPECTED = 0.5
 OPS_PER_UPDATED = 1.0
 # The credit in use before the admission check became a plain maximum over the rows (add, min per row
@@ -68,10 +67,6 @@ PROFILED = {
     "config3": {"traffic_bytes": int((42771.0 * 1.99974 + 77500.4 * 1.0) * 1024),
                 "issue": {"valu": 0.926, "scalar_and_branch": 0.770, "lane_slots_per_visit": 3.09,
                           "source": "profiles/timeline_kernel_config3_counters.md"}},
-    # profiles/timeline_kernel_config5_rows65.md (one wavefront per SIMD, two on one of them)
-    "config5": {"traffic_bytes": None,
-                "issue": {"valu": 0.230, "scalar_and_branch": 0.128, "lane_slots_per_visit": 0.082,
-                          "source": "profiles/timeline_kernel_config5_rows65.md"}},
     # profiles/timeline_kernel_config4_moves.md (candidates' launches; the counters give 1.08 vector
     # instructions per SIMD and four nominal clocks: saturated)
     "config4": {"traffic_bytes": None,
@@ -162,7 +157,7 @@ def cpu_baseline_rows(inst, make_rows, C: int, tel_gpu, what: str):
 
 def roofline_object(kernel: str, inspected: int, updated: int, kernel_ms_total: float, launches: int, workload: str,
                     hbm_bytes: int, extra: dict | None = None):
-    """Integer-VALU roofline of the timeline kernel: credited lane-ops = inspected / 2 + updated."""
+    """Integer-VALU roofline of the timeline kernel: credited lane-ops = inspected / 2 + updated (of the event kernel: its bytes alone)."""
     secs = kernel_ms_total * 1e-3
     visits = inspected + updated
     ops = OPS_PER_INSPECTED * inspected + OPS_PER_UPDATED * updated
@@ -187,6 +182,9 @@ def roofline_object(kernel: str, inspected: int, updated: int, kernel_ms_total: 
         "hbm": {"algorithmic_bytes": hbm_bytes, "achieved_GBps": hbm_bytes / secs / 1e9,
                 "frac_of_8TBps": hbm_bytes / secs / PEAK_HBM_BYTES},
     }
+    if kernel == "event_rows_kernel":  # it visits no rounds one by one: the credit is not its work, nor are the counters its own
+        obj.update({k: None for k in ("achieved", "frac", "visits", "inspected", "updated", "ops_per_visit",
+                                      "frac_at_two_ops_per_visit", "traffic", "issue_measured")}, bound="latency")
     if extra:
         obj.update(extra)
     return obj
@@ -200,7 +198,7 @@ def reg_rows(o_max: int) -> int:
 def timeline_kernel_name(C: int, n: int, o_max: int, resumed: bool, lengths: int = 0) -> str:
     """The kernel that kvsched_simulate places C explicit rows with, the decodes of so many different lengths."""
     if 0 < lengths <= 4 and 2048 < o_max <= 14336 and n >= 8192 and not resumed:
-        return "event_rows_kernel"  # (visits no rounds one by one: the credit below is not its work)
+        return "event_rows_kernel"
     if n <= 8 or (n <= 16 and C >= 8192) or (n <= 32 and C >= 32768):
         return f"short_rows_kernel<{8 if n <= 8 else 16 if n <= 16 else 32}>"
     return f"timeline_reg_kernel<{reg_rows(o_max)},{'1,false,true,true' if resumed else '4,false,false,false'}>"
