@@ -162,6 +162,10 @@ int scanned_bound(const kvsched_ctx *ctx, int32_t *o_bound_out)
 // ... and whether the decode lengths are few (a scan_lengths_kernel that was asked to tell).
 bool scanned_few(const kvsched_ctx *ctx) { return ctx->h_scan[KVS_H_OMAX] < 0; }
 
+// Where a launch that looks the lengths over leaves whether they are few, which matters beyond kEventsFrom alone (by_events).
+constexpr int32_t kEventsFrom = 2048;
+int32_t *few_word(const kvsched_ctx *ctx, int32_t o_bound) { return o_bound > kEventsFrom ? ctx->h_scan + KVS_H_FEW : nullptr; }
+
 // Enqueue the length scan; unless the caller supplied a bound, wait for the largest decode
 // length.  *o_bound_out is what the timeline kernels size their ring from.
 int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t n, int64_t M, hipStream_t st,
@@ -173,12 +177,12 @@ int scan_and_bound(kvsched_ctx *ctx, const int32_t *s, const int32_t *o, int32_t
     if (ctx->o_max_bound > 0) {
         *o_bound_out = ctx->o_max_bound;
         return kvs_launch_scan_lengths(s, o, n, (int32_t)M, ctx->o_max_bound, ctx->d_words, st, moves, K, nullptr, 0,
-                                       moves ? nullptr : ctx->h_scan + KVS_H_FEW);
+                                       moves ? nullptr : few_word(ctx, ctx->o_max_bound));
     }
     if (capturing(st)) return KVSCHED_EHIP;
     // (the first and last position the moves touch come with it)
     int rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, moves, K, ctx->h_scan,
-                                     next_seq(ctx), moves ? nullptr : ctx->h_scan + KVS_H_FEW);
+                                     next_seq(ctx), moves ? nullptr : few_word(ctx, INT32_MAX));
     if (rc != KVSCHED_OK) return rc;
     rc = wait_for_scan(ctx, st);
     if (rc != KVSCHED_OK) return rc;
@@ -557,7 +561,6 @@ static int32_t next_status_word(const kvsched_ctx *ctx) { return KVS_W_STATUS_TU
 // 2048, 1000 orders of 10000 1756 347, 4000 of 2000 831 398, 2 of 200 196 85; of 1, 300, 900 and 2048 1670 816, 714 896, 326 108; of 1, 300 and
 // 1024 1360 854, 513 834, 412 104.
 constexpr int32_t kEventsUnasked = 8192;
-constexpr int32_t kEventsFrom = 2048;
 static bool by_events(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bound, int few, bool hint, hipStream_t st)
 {
     if (o_bound <= kEventsFrom || o_bound > KVS_REG_MAX_O || n > KVS_EVENTS_MAX_N) return false;
@@ -627,8 +630,8 @@ static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, i
     ctx->resume_rows = 0;
     ctx->rejoin_offset = 0;
     const int32_t *resumed_blocks = nullptr, *resumed_row0 = nullptr, *rejoined = nullptr;
-    p.few_out = ctx->h_scan + KVS_H_FEW;
-    p.few_known = __atomic_load_n(p.few_out, __ATOMIC_RELAXED);
+    p.few_out = few_word(ctx, o_bound);
+    p.few_known = p.few_out ? __atomic_load_n(p.few_out, __ATOMIC_RELAXED) : 0;
     const bool events = cp == 0 && by_events(ctx, C, n, o_bound, few, p.few_known != 0, st);
     if (cp == 0 && !events && resume_pays(ctx, C, n, o_bound)) {
         const int32_t nblk = (n - 1) / WAVE_POSITIONS;
@@ -784,7 +787,8 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
         next_seq(ctx);
         scan = scans_here(ctx, C, n, guess, common_prefix, st);
         if (scan) status_word = next_status_word(ctx);
-        else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq, ctx->h_scan + KVS_H_FEW);
+        else rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st, nullptr, 0, ctx->h_scan, ctx->scan_seq,
+                                          few_word(ctx, INT32_MAX));
         if (rc == KVSCHED_OK)
             rc = simulate_within(ctx, orders, C, n, s, o, M, guess, true, scan, status_word, -1, tel_out, completion_out, 0, st);
         if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);
