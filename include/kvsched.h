@@ -172,8 +172,9 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
  * when the states are handed over between two launches); 0 = never; rows > 0 = whenever there are
  * that many rows (and more than 128 positions).  By default, and without a bound from
  * kvsched_set_o_max(), rows whose decodes have four lengths or fewer, the longest between 2048 and
- * 14336, are not resumed but placed in a way that is mostly faster.  (Rows that differ from row 0 near
- * their end alone may be quicker resumed: give a number here.) */
+ * 14336, are not resumed but placed in a way that is mostly faster.  (Where it is not, with a budget
+ * below 64 of the longest decodes, the rows are resumed after all if half of 16 among them agree with
+ * row 0 over two thirds of their positions.) */
 #define KVSCHED_RESUME_AUTO (-1)
 int kvsched_set_resume_min_rows(kvsched_ctx *ctx, int32_t rows);
 

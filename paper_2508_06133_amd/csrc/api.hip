@@ -551,12 +551,10 @@ static int32_t next_status_word(const kvsched_ctx *ctx) { return KVS_W_STATUS_TU
 // other kernel's time; from 8192 positions on, 700 us and more, they take the launch unasked.  Rows that would be resumed could lose all that
 // resuming saves (a hint out of date, 16384 rows of 2000 mixed requests: exchanges anywhere 1570 -> 1750, in the last tenth 890 -> 1780), so they
 // are resumed while it is not known.
-// Against resumed rows, one call (us, resumed and here; rows that exchange two positions in the last tenth, anywhere, and 64 pairs): bimodal
-// lengths, 16384 rows of 2000 1360 958, 3390 980, 3710 1230; 8192 of 1000 813 473, 1690 500, 1890 680; 32768 of 500 1175 1263, 3560 1275, 4640
-// 1620; 4096 of 20000 2350 853, 2340 874, 2110 892; four lengths up to 4096, 16384 of 2000 1112 1547, 3190 1650, 3770 2230; 8192 of 1000
-// 664 662, 1125 724, 1390 917; 32768 of 500 1512 1662, 3680 1700, 4940 2000; 4096 of 20000, random orders 5920 6400.  So rows that differ in the
-// last tenth alone are up to 1.4 times slower here from 16384 rows on; a caller who has such rows declares their prefix or asks
-// for resuming.
+// Known few, such rows are placed here unless they differ from row 0 late (differ_late), as resumed rows cost the less the later they do.  One call
+// (us, resumed and here): rows that exchange two positions anywhere, bimodal lengths, 16384 rows of 2000 2414 847, 8192 of 1000 1234 501, 32768 of
+// 500 3187 1081, 4096 of 20000 2205 602; four lengths up to 4096, 16384 of 2000 1806 851, 32768 of 500 2115 969; all of 4096, 3463 1639 and
+// 4320 1671; random orders, four lengths 3197 2160 and 2868 1877.
 // Decodes up to 2048 stay with the timeline kernel's 33 rows.  The lengths decide which is faster there (us, 33 rows and here): of 1 and
 // 2048, 1000 orders of 10000 1756 347, 4000 of 2000 831 398, 2 of 200 196 85; of 1, 300, 900 and 2048 1670 816, 714 896, 326 108; of 1, 300 and
 // 1024 1360 854, 513 834, 412 104.
@@ -570,10 +568,32 @@ static bool by_events(const kvsched_ctx *ctx, int32_t C, int32_t n, int32_t o_bo
     return n <= WAVE_POSITIONS || !capturing(st);
 }
 
+// Rows that would be resumed and whose lengths are few: do they differ from row 0 so late that resuming them is the quicker way?  Looked up in
+// KVS_AGREE_ROWS of them, for which the host waits once more (10 us); yes if half of these agree with row 0 over two thirds.  The event kernel pays for
+// all of a row, and the more the fewer requests start together, that is the smaller the budget is against them.  (us, resumed and by events,
+// exchanges in the last tenth, and over the last 0.3 alone: lengths 500 to 2500, 16384 rows of 4000, budgets of 12288 2960 7825, 7616 7860; of
+// 160000 946 951, 1443 986; of 400000 818 451, 1062 472; 32768 of 1000, 12288 1382 3508, 3856 3540; 40000 770 1203, 2177 1212; 400000 576 434;
+// bimodal, 32768 of 400, 12288 1123 1582, 2666 1576; 16000 910 920; 400000 462 130; four lengths from 2100 on, 32768 of 1000, 40000 1068 2015, 3224
+// 2008; 400000 589 530, 988 543; of 1, 100 and 14000 the 225 rows always lose, 19606 5476 at the most.)  With a budget of 64 of the longest decodes, or
+// decodes beyond 8192, the rows are not looked at.
+constexpr int32_t kLateBudget = 64, kLateMaxO = 8192;
+static int differ_late(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, int64_t M, int32_t o_bound, hipStream_t st, bool *late)
+{
+    *late = false;
+    if (o_bound > kLateMaxO || M >= (int64_t)kLateBudget * o_bound) return KVSCHED_OK;
+    const int32_t first = (int32_t)((int64_t)n * 2 / 3);
+    int rc = kvs_launch_rows_agree(orders, C, n, first, ctx->d_words, ctx->h_scan, o_bound, next_seq(ctx), st);
+    if (rc == KVSCHED_OK) rc = wait_for_scan(ctx, st);
+    if (rc != KVSCHED_OK) return rc;
+    *late = 2 * ctx->h_scan[KVS_H_AGREE] >= KVS_AGREE_ROWS;
+    return KVSCHED_OK;
+}
+
 // kvsched_simulate for decodes of at most o_bound.  gated: nothing is written when the length scan enqueued before finds a
 // longer one (only where rows are not resumed and no prefix is placed ahead).  scan: no length scan is enqueued before
 // (scans_here), the launch does it and, if gated, leaves its result in pinned memory under number ctx->scan_seq.
-// status_word: where faulty rows are reported.  few: whether the decode lengths are few, by this call's scan (-1: not known yet).
+// status_word: where faulty rows are reported.  few: whether the decode lengths are few, by this call's scan (-1: not known yet), and the rows, if they
+// would be resumed, do not differ late (by_events).
 static int simulate_within(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t n, const int32_t *s,
                            const int32_t *o, int64_t M, int32_t o_bound, bool gated, bool scan, int32_t status_word, int few, int64_t *tel_out,
                            int32_t *completion_out, int32_t common_prefix, hipStream_t st)
@@ -803,7 +823,13 @@ int kvsched_simulate(kvsched_ctx *ctx, const int32_t *orders, int32_t C, int32_t
     if (rc != KVSCHED_OK) return rc;
     ctx->o_file = kvs_reg_file_bound(o_bound);
     if (guess >= o_bound) return KVSCHED_OK;
-    const int few = scan || ctx->o_max_bound > 0 ? -1 : scanned_few(ctx);
+    int few = scan || ctx->o_max_bound > 0 ? -1 : scanned_few(ctx);
+    if (few > 0 && common_prefix < kMinSharedPrefix && resume_pays(ctx, C, n, o_bound) && by_events(ctx, C, n, o_bound, few, false, st)) {
+        bool late;
+        rc = differ_late(ctx, orders, C, n, M, o_bound, st, &late);
+        if (rc != KVSCHED_OK) return rc;
+        if (late) few = 0;
+    }
     if (scan && o_bound > KVS_REG_MAX_O) {  // (whose kernels report in the scan's word)
         status_word = KVS_W_STATUS;
         rc = kvs_launch_scan_lengths(s, o, n, (int32_t)M, 0, ctx->d_words, st);

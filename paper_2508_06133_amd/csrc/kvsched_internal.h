@@ -25,6 +25,7 @@ enum {
     KVS_W_SCAN_MINPOS = 18,  // INT_MAX between calls
     KVS_W_SCAN_MAXPOS = 19,  // -1 between calls
     KVS_W_SCAN_DONE = 20,
+    KVS_W_AGREE = 21,  // workgroups of rows_agree_kernel that are done << 16 | rows that agree
     KVS_W_ARGMIN_DONE = 24,
     KVS_W_ARGMIN_PART = 32,  // two int64 per workgroup
     KVS_ARGMIN_GROUPS = 64,
@@ -43,6 +44,7 @@ enum {
     KVS_H_KMIN = 6,
     KVS_H_BATCHES = 7,
     KVS_H_FEW = 8,  // 1: the last backlog looked over had few decode lengths (few_lengths); nobody waits for it, so it may be an earlier call's
+    KVS_H_AGREE = 9,  // of KVS_AGREE_ROWS rows of the call, those that agree with row 0 over their leading positions
     KVS_H_COUNT = 16
 };
 
@@ -322,6 +324,11 @@ int kvs_launch_check_prefix(const int32_t *orders, int32_t C, int32_t n, int32_t
 int kvs_launch_broadcast_prefix(const int32_t *prefix, int32_t cp, int32_t C, int32_t n, int32_t *completion,
                                 hipStream_t st);
 // rows resumed from snapshots of row 0 (see SimParams)
+constexpr int32_t KVS_AGREE_ROWS = 16;
+// How many of KVS_AGREE_ROWS rows spread over the call agree with row 0 on their first `first` positions, to host[KVS_H_AGREE], and then the
+// number `seq`, beside it what a length scan has left there: the longest decode, and that the lengths are few.  C >= 2.
+int kvs_launch_rows_agree(const int32_t *orders, int32_t C, int32_t n, int32_t first, int32_t *d_words, int32_t *host, int32_t longest,
+                          int32_t seq, hipStream_t st);
 int kvs_launch_shared_blocks(const int32_t *orders, int32_t C, int32_t n, int32_t *blocks, int32_t *diff_first,
                              int32_t *diff_last, hipStream_t st);
 // tel[c] += tel[base] for the candidates that stopped early (rejoin[c] != INT_MAX), c != base

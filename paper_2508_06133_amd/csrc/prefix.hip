@@ -3,6 +3,7 @@
 // the same timeline state (admission is in order, Algorithm 1's Phase 2), so the prefix is run
 // once and its state handed to all of them.
 #include "kvsched_internal.h"
+#include "device_util.h"
 #include "phase1_util.h"
 
 #include <limits.h>
@@ -247,7 +248,32 @@ __global__ __launch_bounds__(256) void resume_plan_kernel(const int32_t *sorted,
     resume_pos_out[c] = w >= first ? 64 * blocks[c] : 0;
 }
 
+// A workgroup a row; the last to finish tells the host, which waits (see kvs_launch_rows_agree).
+__global__ __launch_bounds__(1024) void rows_agree_kernel(const int32_t *orders, int32_t C, int32_t n, int32_t first, int32_t *words,
+                                                          int32_t *host, int32_t longest, int32_t seq)
+{
+    const int32_t *row = orders + (1 + (size_t)blockIdx.x * (size_t)(C - 1) / KVS_AGREE_ROWS) * (size_t)n;
+    bool differs = false;
+#pragma unroll 4
+    for (int k = threadIdx.x; k < first; k += 1024) differs |= row[k] != orders[k];
+    const int mine = 1 << 16 | (__syncthreads_or(differs) != 0 ? 0 : 1);
+    if (threadIdx.x != 0) return;
+    const int all = atomicAdd(&words[KVS_W_AGREE], mine) + mine;
+    if (all >> 16 < KVS_AGREE_ROWS) return;
+    words[KVS_W_AGREE] = 0;
+    to_host(&host[KVS_H_AGREE], all & 0xffff);
+    device_writes_done();
+    longest_to_host(host, longest, seq, true);
+}
+
 }  // namespace
+
+int kvs_launch_rows_agree(const int32_t *orders, int32_t C, int32_t n, int32_t first, int32_t *d_words, int32_t *host, int32_t longest,
+                          int32_t seq, hipStream_t st)
+{
+    hipLaunchKernelGGL(rows_agree_kernel, dim3(KVS_AGREE_ROWS), dim3(1024), 0, st, orders, C, n, first, d_words, host, longest, seq);
+    return hipGetLastError() == hipSuccess ? KVSCHED_OK : KVSCHED_EHIP;
+}
 
 int kvs_launch_shared_blocks(const int32_t *orders, int32_t C, int32_t n, int32_t *blocks, int32_t *diff_first,
                              int32_t *diff_last, hipStream_t st)

@@ -193,3 +193,36 @@ def test_rows_that_would_be_resumed(bound):
     finally:
         ctx.close()
         plain.close()
+
+
+@pytest.mark.parametrize("n,rows,differs,budget,resumed", [(2100, 4096, 0.9, 12288, True), (2100, 4096, 0.1, 12288, False), (2100, 4096, 0.9, 1 << 19, False),
+                                                           (2100, 4096, 0.65, 12288, False), (2100, 4096, 0.67, 12288, True), (403, 20500, 0.9, 12288, True)])
+def test_rows_that_differ_late(n, rows, differs, budget, resumed):
+    """Without a bound, rows that agree with row 0 over two thirds and more are resumed where the budget is small, though their lengths are
+    few; the number of the length scan and of the look at the rows that follows it are told apart over several calls."""
+    from paper_2508_06133_amd import kvsched
+
+    rng = np.random.default_rng(n)
+    o = rng.choice([500, 1000, 2000, 2500], n)
+    o[0] = 2500
+    s = rng.integers(1, 3000, n)
+    orders = np.tile(rng.permutation(n).astype(np.int32), (rows, 1))
+    lo = int(differs * n)
+    for r in range(1, rows):
+        j = rng.integers(lo + 1, n)
+        orders[r, lo], orders[r, j] = orders[r, j], orders[r, lo]
+    d_orders, d_s, d_o = _dev(orders), _dev(s), _dev(o)
+    ctx, plain = kvsched.Context(0), kvsched.Context(0)
+    try:
+        plain.set_resume_min_rows(0)
+        want = plain.simulate(d_orders, d_s, d_o, budget)
+        for call in range(3):
+            print(f"event rows, differ late: n={n} rows={rows} from {differs} budget={budget} call {call}", flush=True)
+            tel, comp = ctx.simulate(d_orders, d_s, d_o, budget)
+            assert bool((tel == want[0]).all()) and bool((comp == want[1]).all()) and ctx.device_status() == 0
+            assert bool((ctx.simulate_resume_positions(rows) > 0).any()) == resumed
+        t, c = oracle.simulate_many(s.astype(np.int32), o.astype(np.int32), budget, orders[:3])
+        assert (tel[:3].cpu().numpy() == t).all() and (comp[:3].cpu().numpy() == c).all()
+    finally:
+        ctx.close()
+        plain.close()
