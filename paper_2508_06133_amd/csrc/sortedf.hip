@@ -1332,14 +1332,18 @@ __global__ __launch_bounds__(1024) void batch_chain_kernel(SortedArgs p, LargeAr
             __syncthreads();
         }
         if (loaded && tid < 64) {  // follow the chain as far as it is known
-            while (a < n && a < first + window) {
-                const int k = __builtin_amdgcn_readfirstlane((int)next_in[a - first]);
+            // (by scalars, which the compiler cannot tell by itself: with a branch by the lane in each step the loop's time hung on where in the
+            // instruction cache it lay, e.g. 4000 requests in some 2000 batches under the profile constraint 225 or 243 us a call)
+            int at = __builtin_amdgcn_readfirstlane(a), b = __builtin_amdgcn_readfirstlane(nb);
+            const int known_to = __builtin_amdgcn_readfirstlane(min(n, first + window));
+            while (at < known_to) {
+                const int k = __builtin_amdgcn_readfirstlane((int)next_in[at - first]);
                 if (k < 1) break;
-                a += k;
-                if (tid == 0) p.batch_end_out[nb] = a;
-                ++nb;
+                at += k;
+                if (tid == 0) p.batch_end_out[b] = at;
+                ++b;
             }
-            if (tid == 0) sh[0] = a, sh[1] = nb;
+            if (tid == 0) sh[0] = at, sh[1] = b;
         }
         if (loaded) {
             __syncthreads();
