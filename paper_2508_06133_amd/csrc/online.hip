@@ -401,9 +401,10 @@ __device__ __forceinline__ int plan_batch(u64 *wk, int m, int M, u64 *bkey, u64 
     if (RMAX == 1 || K <= 64) {
         const unsigned of = v[0] & ~IN;
         u64 members = __builtin_amdgcn_ballot_w64(v[0] >= IN), others = __builtin_amdgcn_ballot_w64(v[0] < NONE);
-        const int reach = __popcll(__builtin_amdgcn_ballot_w64(w[0] <= w_most + slack) & (members | others));
+        const u64 room = __builtin_amdgcn_ballot_w64(w[0] <= w_most + slack);
+        const int reach = __popcll(room & (members | others));
         const int behind = RMAX > 1 && m > 64 ? __builtin_amdgcn_readlane(w[RMAX > 1 ? 1 : 0], 0) : INT_MAX;  // the next row's first
-        bool none_left = false;
+        bool none_left = (room & others) == 0 && behind > w_most + slack;  // (no masks where the budget holds all of the window)
         for (int count = max((reach + 7) & ~7, 8); !none_left && count <= 64; count = count < 64 ? 64 : 65)
             none_left = exchange_in_lanes(w[0], of, count, count >= 64 ? behind : count < m ? __builtin_amdgcn_readlane(w[0], count & 63) : INT_MAX,
                                           slack, w_most, members, others);
