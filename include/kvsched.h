@@ -387,7 +387,8 @@ int kvsched_best_neighbor_static(kvsched_ctx *ctx, const int32_t *base_order, in
  *   complete_every  >= 1: completions to wait for before re-planning
  *   completion_out  [n]    int32 or NULL: completion rounds of the new order, by request id
  *   result_out      [6]    int64: {best move, its total latency, latency of the order before
- *                   the move, committed positions, requests completed by T, T}
+ *                   the move, committed positions, requests completed by T, T}; if `order` or the lengths are
+ *                   faulty the first three are -1 and the others say nothing
  *
  * Without completion_out the new order's timeline is placed only as far as the commit point needs it
  * (kvsched_horizon_completion() gives what it has).  Between steps the context keeps that timeline's states at every
